@@ -41,6 +41,11 @@ __device__ __forceinline__ void copy16_to_lds_async_stream(const void* gbase, ui
   asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
                :: "v"(goff), "s"(gbase), "s"(lds_addr) : "memory", "m0");
 }
+// the same without the hint (data that many workgroups read)
+__device__ __forceinline__ void copy16_to_lds_async_at(const void* gbase, uint32_t goff, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :: "v"(goff), "s"(gbase), "s"(lds_addr) : "memory", "m0");
+}
 // ... or a full 64-bit address per lane (rows gathered from anywhere in a large allocation).
 __device__ __forceinline__ void copy16_to_lds_async_stream64(const void* gaddr, uint32_t lds_addr) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"

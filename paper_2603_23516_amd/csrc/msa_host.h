@@ -58,7 +58,7 @@ struct ScorePlan {
   int n_splits;          // blocks per KV head
   int q_per_pass;        // queries scored per launch (8 or 16)
   int n_pass;
-  int mode;              // scan mode: 0 filter, 1 dense lists, 2 score matrix + row top-k
+  int mode;              // scan mode: 0 filter, 1 dense lists, 2 score matrix + row top-k (all heads: always 2)
   int tiles_per_wave;    // mode 2: contiguous tiles per wave
   size_t off_mat;        // mode 2: byte offset of the fp32 score matrix [Hkv][BM][N]
   int exchange;          // 1: waves exchange running maxima to tighten their thresholds
@@ -67,6 +67,8 @@ struct ScorePlan {
   size_t off_qop;        // byte offset of the prepared query operands
   int n_qtiles;          // 8-query operand tiles (padded to whole passes)
   int all_heads;         // 1: score_scan_all_kernel (scope ALL with more than one KV head)
+  int seg_docs;          // all heads: documents per segment of the bank (one score matrix each)
+  int part_docs;         // all heads: documents per part of a matrix row (n_splits parts per query in all)
   int n_sel;             // selections per query token: Hkv, or 1 for scope ALL
   size_t off_tok;        // byte offset of the per-token winner keys (token pooling)
   int merge_parts;       // > 1: two-level merge, first level over merge_lpp lists per block

@@ -22,6 +22,8 @@
 #include "msa_device.h"
 #include "msa_host.h"
 
+#include <type_traits>
+
 namespace msa {
 
 constexpr int kPrefetch = 4;         // tiles in flight per wave
@@ -641,164 +643,211 @@ void score_scan_kernel(ScoreArgs a) {
 // the per-group scores above, so one selection serves all heads.  A wave's stream interleaves the
 // heads: entry e = (tile e / HKV, head e % HKV) through the same ring of kPrefetch loads; the
 // per-head partial scores are scaled by that head's 1/|key| and summed, and after the last head the
-// document max / threshold / candidate-list logic runs exactly as in score_scan_kernel.  The
-// A operands of all HKV heads (8 queries per pass) are too many for registers at two waves per SIMD,
-// so a workgroup of four waves (four independent streams) shares one LDS copy of them and every
-// wave re-reads the slices of the head at hand.  HKV in {2, 4, 8} (one group: the plain kernel
-// already computes this).
-constexpr int kAllWaves = 4;
+// document maxima go to the score matrix mat[query of the pass][document of the segment], from which
+// topk_rows_kernel selects.
+//
+// Bound: the stream of the index (every key once per pass).  A pass therefore takes up to 32 queries (NQT tiles of
+// 8): their A operands, HKV x NS x NQT x 1 KiB, lie in LDS once per workgroup and every wave re-reads the slices of
+// the head at hand, NQT bytes of LDS per byte of index, a third of the LDS rate at NQT = 4.  With one selection per
+// token the matrix is 4 B per (query, document) beside the HKV * C * 2 d B of index behind it: under 1 % at 32
+// queries, and it needs no thresholds, lists, sorts or merges of the streams' lists (24 queries over 8192 documents:
+// three 8-query passes 88 us + list merge 59 us -> 24 us + row top-k 8 us).
+//
+// Eight streams per workgroup: the operands of 32 queries leave room for one workgroup per CU, and eight waves of
+// four 4 KiB tiles are what keeps the memory system busy.  A wave takes UNITS of 2^ushift tiles (at most 16
+// documents), unit w, w + W, ...: at any moment the waves read one contiguous window of the index, and a unit's
+// scores leave as one run of up to 64 bytes per query.  HKV in {2, 4, 8} (one group: the plain kernel computes this).
+constexpr int kAllWaves = 8;
+constexpr int kAllRun = 16;  // documents a wave collects per query before it writes them
+
+constexpr int kAllGroups = 256;  // workgroups: one per CU
+
+// log2(tiles per unit): the unit that keeps the longest stream shortest (whole units per wave), of equals the largest
+static int scan_all_ushift(long long seg_tiles, int C) {
+  const long long waves = (long long)kAllGroups * kAllWaves;
+  int best = 0;
+  long long best_len = 0;
+  for (int us = 0; (1 << us) <= C; ++us) {  // a unit holds at most kAllRun = 16 documents: 16 / C per tile
+    const long long units = (seg_tiles + (1 << us) - 1) >> us;
+    const long long len = ((units + waves - 1) / waves) << us;
+    if (us == 0 || len <= best_len) {
+      best = us;
+      best_len = len;
+    }
+  }
+  return best;
+}
+
+struct ScanAllArgs {
+  const uint4* qop;       // [HKV][n_qtiles][NS][64] prepared A operands (prep_scan_operands_kernel)
+  const uint16_t* KR;     // tiled
+  const float* inv_norm;  // null: dot product
+  float* mat;             // [queries of the pass][mat_stride]
+  long long mat_stride;   // documents per row
+  int n_qtiles, qt0;      // operand tiles in all, first one of this pass
+  int nq;                 // queries of this pass (<= 8 NQT)
+  int C;
+  long long tiles;        // tiles per head in the index
+  long long tile0;        // first tile of this segment
+  long long seg_tiles;    // tiles of this segment
+  int seg_docs;           // documents of this segment
+  int ushift;             // log2(tiles per unit)
+};
 
 // STREAM: the index is far larger than the caches and read once per pass -> streaming loads (load_stream16); a small
 // index that several passes re-read is served partly from the caches and measured faster with plain loads.
-template <int D, int HKV, bool COS, bool STREAM>
-__global__ __launch_bounds__(64 * kAllWaves) void score_scan_all_kernel(ScoreArgs a) {
+template <int D, int HKV, int NQT, bool STREAM>
+__global__ __launch_bounds__(64 * kAllWaves) void score_scan_all_kernel(ScanAllArgs a) {
   constexpr int NS = D / 32;
-  constexpr int NQ = 8;
-  constexpr int CAP = 128;  // entries per (wave, query) list: 8 KiB of LDS per wave
+  constexpr int NQ = 8 * NQT;
   constexpr int TILE_ELEMS = 16 * D;
   constexpr int UT = HKV >= kPrefetch ? 1 : kPrefetch / HKV;  // tiles per unrolled group of entries
   static_assert((UT * HKV) % kPrefetch == 0, "ring slots must be compile-time");
+  constexpr int NOP = HKV * NQT * NS;                        // KiB of operands
+  constexpr int OPW = (NOP + kAllWaves - 1) / kAllWaves;     // copies per wave
 
-  __shared__ uint4 Aop[HKV][NS][64];
-  __shared__ unsigned long long cand_all[kAllWaves][NQ * CAP];
-  __shared__ int cnt_all[kAllWaves][NQ];
-  __shared__ float thr_all[kAllWaves][NQ];
+  __shared__ uint4 Aop[HKV][NQT][NS][64];
+  __shared__ float run_s[kAllWaves][NQ][kAllRun];
 
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  unsigned long long* cand = cand_all[wave];
-  int* cnt_s = cnt_all[wave];
-  float* thr_s = thr_all[wave];
-  for (int e = threadIdx.x; e < HKV * NS * 64; e += 64 * kAllWaves) {
-    const int h = e / (NS * 64), rest = e % (NS * 64);
-    Aop[h][rest / 64][rest % 64] = a.qop[((long long)h * a.n_qtiles + a.q0 / 8) * NS * 64 + rest];
-  }
-  __syncthreads();
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  float (*run)[kAllRun] = run_s[wave];
   const int rr = lane >> 4;
   const int n = lane & 15;
-  const int sp = blockIdx.x * kAllWaves + wave;
-  if (sp >= a.n_splits) return;  // wave-uniform; no block-wide barrier follows
-  const long long S = a.n_splits;
-  const long long n_it = (a.tiles - sp + S - 1) / S;  // >= 1 because n_splits <= tiles
-  const long long i_last = n_it - 1;
-  const uint16_t* KRl = a.KR + lane * 8;
-  const float* inl = COS ? a.inv_norm + n : nullptr;
-  auto tile_of = [&](long long it) { return sp + (it < n_it ? it : i_last) * S; };
 
-  auto load_tile16 = [](const uint16_t* p) {
-    return STREAM ? load_stream16(p) : *reinterpret_cast<const uint4*>(p);
+  // ---- operands: global -> LDS, requested first; the tiles requested next stay in flight across their wait -------
+  const uint32_t op_lds = lds_addr_of(&Aop[0][0][0][0]);
+#pragma unroll
+  for (int i = 0; i < OPW; ++i) {
+    int e = i * kAllWaves + wave;  // (head, tile, slice)
+    e = e < NOP ? e : NOP - 1;     // past the end: the last piece again (the same bytes to the same place)
+    const int h = e / (NQT * NS), rest = e % (NQT * NS);
+    const uint4* src = a.qop + (((long long)h * a.n_qtiles + a.qt0) * NS + rest) * 64;
+    copy16_to_lds_async_at(src, lane * 16, op_lds + e * 1024);
+  }
+
+  const long long W = (long long)gridDim.x * kAllWaves;
+  const long long w = (long long)blockIdx.x * kAllWaves + wave;
+  const int umask = (1 << a.ushift) - 1;
+  const long long units = (a.seg_tiles + umask) >> a.ushift;
+  const long long n_it = w < units ? ((units - w + W - 1) / W) << a.ushift : 0;  // tiles of this wave
+  const uint16_t* KRl = a.KR + lane * 8;
+  // dot product: the loads of the reciprocal norms run all the same (from the index, inside it: a tile has more bytes
+  // than its norms), so that the loads in flight are the same on every path, and a one takes their place
+  const bool cos = a.inv_norm != nullptr;
+  const float* inl = (cos ? a.inv_norm : reinterpret_cast<const float*>(a.KR)) + n;
+  // tile number inside the segment; past the wave's end or the segment's: see clamp below
+  auto tile_at = [&](long long it) { return ((w + (it >> a.ushift) * W) << a.ushift) + (it & umask); };
+  auto load_at = [&](long long it) {  // always a tile of the index
+    const long long t = tile_at(it);
+    return a.tile0 + (t < a.seg_tiles ? t : a.seg_tiles - 1);
   };
-  uint4 buf[kPrefetch][NS];
+  auto load_tile16 = [](const uint16_t* p) {
+    const u32x4_t* v = reinterpret_cast<const u32x4_t*>(p);
+    return STREAM ? __builtin_nontemporal_load(v) : *v;
+  };
+  u32x4_t buf[kPrefetch][NS];  // whole vectors throughout: element-wise uses would be put back together with copies
   float binv[kPrefetch];
 #pragma unroll
   for (int u = 0; u < kPrefetch; ++u) {
     const int h = u % HKV;
-    const long long t = tile_of(u / HKV);
+    const long long t = load_at(u / HKV);
 #pragma unroll
     for (int s = 0; s < NS; ++s)
       buf[u][s] = load_tile16(KRl + ((long long)h * a.tiles + t) * TILE_ELEMS + s * 512);
-    binv[u] = COS ? inl[((long long)h * a.tiles + t) * 16] : 1.0f;
+    binv[u] = inl[((long long)h * a.tiles + t) * 16];
   }
+  wait_copies_but<kPrefetch * (NS + 1)>();  // the operands are older than the tiles
+  lds_barrier();
+  if (n_it == 0) return;  // wave-uniform; no workgroup barrier follows
 
-  float thr[2];
-  int cnt[2];
-#pragma unroll
-  for (int e = 0; e < 2; ++e) {
-    thr[e] = (a.q0 + 2 * rr + e < a.BM) ? -INFINITY : INFINITY;
-    cnt[e] = 0;
-  }
-  int limit = 2 * a.k < 32 ? 32 : 2 * a.k;
-  if (limit > CAP - 16) limit = CAP - 16;
   const int dpt = 16 / a.C;
   const int ndoc = n / a.C;
-  const bool lead_lane = (n & (a.C - 1)) == 0;
-  const uint32_t below = (1u << n) - 1u;
+  const bool lead = (n & (a.C - 1)) == 0;
   const float inv_heads = 1.0f / (float)HKV;
+  const int dshift = a.ushift + 4 - (31 - __clz(a.C));  // log2(documents per unit): dpt << ushift <= kAllRun
+  const int du = 1 << dshift;
 
   for (long long base = 0; base < n_it; base += UT) {
 #pragma unroll
     for (int ut = 0; ut < UT; ++ut) {
       const long long it = base + ut;
-      const long long t = sp + it * S;
-      float tot[2] = {0.f, 0.f};
+      float tot[NQT][2];
+#pragma unroll
+      for (int tq = 0; tq < NQT; ++tq) tot[tq][0] = tot[tq][1] = 0.f;
 #pragma unroll
       for (int h = 0; h < HKV; ++h) {
         const int slot = (ut * HKV + h) % kPrefetch;
-        uint4 cur[NS];
+        // products first, where the tile landed; the next tile of the slot is requested into the same registers
+        // afterwards (see score_scan_kernel)
+        float part[NQT][2];
+        // the entry is awaited HERE: its uses pass through volatile asm, so that no use of a later entry (and the
+        // wait for it) moves up ahead of the requests in between
 #pragma unroll
-        for (int s = 0; s < NS; ++s) cur[s] = buf[slot][s];
-        const float cinv = binv[slot];
+        for (int s = 0; s < NS; ++s) asm volatile("" : "+v"(buf[slot][s]));
+        asm volatile("" : "+v"(binv[slot]));
+        const float inv = cos ? binv[slot] : 1.0f;
+#pragma unroll
+        for (int tq = 0; tq < NQT; ++tq) {
+          f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+          for (int s = 0; s < NS; ++s) acc = mfma16(as_bf16x8(Aop[h][tq][s][lane]), __builtin_bit_cast(bf16x8_t, buf[slot][s]), acc);
+          part[tq][0] = acc[0] + acc[1];
+          part[tq][1] = acc[2] + acc[3];
+          asm volatile("" : "+v"(part[tq][0]), "+v"(part[tq][1]));
+        }
+        asm volatile("" ::: "memory");
         {  // the entry kPrefetch ahead of this one takes over the slot (always issued)
           const int en = ut * HKV + h + kPrefetch;
           const int hn = en % HKV;
-          const long long tn = tile_of(base + en / HKV);
+          const long long tn = load_at(base + en / HKV);
 #pragma unroll
           for (int s = 0; s < NS; ++s)
             buf[slot][s] = load_tile16(KRl + ((long long)hn * a.tiles + tn) * TILE_ELEMS + s * 512);
-          binv[slot] = COS ? inl[((long long)hn * a.tiles + tn) * 16] : 1.0f;
+          binv[slot] = inl[((long long)hn * a.tiles + tn) * 16];
         }
-        f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int s = 0; s < NS; ++s) acc = mfma16(as_bf16x8(Aop[h][s][lane]), as_bf16x8(cur[s]), acc);
-        tot[0] += (acc[0] + acc[1]) * cinv;
-        tot[1] += (acc[2] + acc[3]) * cinv;
+        for (int tq = 0; tq < NQT; ++tq) {
+          tot[tq][0] = fmaf(part[tq][0], inv, tot[tq][0]);
+          tot[tq][1] = fmaf(part[tq][1], inv, tot[tq][1]);
+        }
       }
-      const long long doc = t * dpt + ndoc;
-      const bool lead = lead_lane && it < n_it && doc < a.N;
-      bool over = false;
+      if (UT > 1 && it >= n_it) break;  // wave-uniform
+      const int in_unit = (int)(it & umask);
+      // document maxima, one level of the exchange at a time for all scores (the branches are wave-uniform)
 #pragma unroll
-      for (int e = 0; e < 2; ++e) {
-        const float sc = group_max_rt(tot[e] * inv_heads, a.C);
-        const bool pred = lead && sc >= thr[e];
-        const unsigned long long m = __ballot(pred);
-        const uint32_t half = (rr & 2) ? (uint32_t)(m >> 32) : (uint32_t)m;
-        const uint32_t row = (half >> ((rr & 1) * 16)) & 0xffffu;
-        if (pred) cand[(2 * rr + e) * CAP + cnt[e] + __popc(row & below)] = make_key(sc, (uint32_t)doc);
-        cnt[e] += __popc(row);
-        over = over || cnt[e] > limit;
+      for (int tq = 0; tq < NQT; ++tq) {
+        tot[tq][0] *= inv_heads;
+        tot[tq][1] *= inv_heads;
       }
-      if (__any(over)) {
-        if (n == 0) {
-          cnt_s[2 * rr] = cnt[0];
-          cnt_s[2 * rr + 1] = cnt[1];
-          thr_s[2 * rr] = thr[0];
-          thr_s[2 * rr + 1] = thr[1];
+      auto level = [&](auto ctrl) {
+#pragma unroll
+        for (int tq = 0; tq < NQT; ++tq) {
+          tot[tq][0] = fmaxf(tot[tq][0], dpp_f<decltype(ctrl)::value>(tot[tq][0]));
+          tot[tq][1] = fmaxf(tot[tq][1], dpp_f<decltype(ctrl)::value>(tot[tq][1]));
         }
-        wave_sync();
-        for (int qi = 0; qi < NQ; ++qi) {
-          const int c = cnt_s[qi];
-          if (c > limit) {  // wave-uniform
-            unsigned long long* cl = cand + qi * CAP;
-            const int nc = prune_list<CAP>(cl, c, a.k, lane);
-            if (lane == 0) {
-              cnt_s[qi] = nc;
-              thr_s[qi] = key_score(cl[a.k - 1]);
-            }
-          }
+      };
+      if (a.C >= 2) level(std::integral_constant<int, kDppXor1>{});
+      if (a.C >= 4) level(std::integral_constant<int, kDppXor2>{});
+      if (a.C >= 8) level(std::integral_constant<int, kDppHalfMirror>{});
+      if (a.C >= 16) level(std::integral_constant<int, kDppMirror>{});
+      if (lead) {
+#pragma unroll
+        for (int tq = 0; tq < NQT; ++tq) {
+          run[8 * tq + 2 * rr][in_unit * dpt + ndoc] = tot[tq][0];
+          run[8 * tq + 2 * rr + 1][in_unit * dpt + ndoc] = tot[tq][1];
         }
+      }
+      if (in_unit == umask) {  // the unit is complete: one run of du documents per query
         wave_sync();
-        cnt[0] = cnt_s[2 * rr];
-        cnt[1] = cnt_s[2 * rr + 1];
-        thr[0] = thr_s[2 * rr];
-        thr[1] = thr_s[2 * rr + 1];
+        const long long doc0 = (tile_at(it) - umask) * dpt;  // document inside the segment
+        const int j = lane & (du - 1), qo = lane >> dshift, qpi = 64 >> dshift;
+        if (doc0 + j < a.seg_docs) {
+          for (int qi = qo; qi < a.nq; qi += qpi) a.mat[qi * a.mat_stride + doc0 + j] = run[qi][j];
+        }
         wave_sync();
       }
     }
-  }
-
-  if (n == 0) {
-    cnt_s[2 * rr] = cnt[0];
-    cnt_s[2 * rr + 1] = cnt[1];
-  }
-  wave_sync();
-  for (int qi = 0; qi < NQ; ++qi) {
-    const int qg = a.q0 + qi;
-    if (qg >= a.BM) break;  // wave-uniform
-    const int c = cnt_s[qi];
-    unsigned long long* cl = cand + qi * CAP;
-    const int nc = prune_list<CAP, 16>(cl, c, a.k, lane);
-    unsigned long long* dst = a.ws + ((long long)qg * a.n_splits + sp) * a.k;
-    if (lane < a.k) dst[lane] = (lane < nc) ? cl[lane] : 0ull;
   }
 }
 
@@ -909,48 +958,67 @@ __global__ __launch_bounds__(256) void pool_tokens_kernel(const unsigned long lo
   }
 }
 
-// Top-k of one row of document scores (MODE 2 of the scan): mat[g][qg][0..N).  One workgroup per row.
-//   1. every thread takes the best score of its strided share of the row; every wave finds (a lower bound
+// Top-k of the rows of a document score matrix (MODE 2 of the scan, all-heads scan).  One workgroup per (row, part
+// of the row).
+//   1. every thread takes the best score of its strided share of the part; every wave finds (a lower bound
 //      on) the k-th best of its 64 lane maxima by a bitwise search with ballots, and the largest of the four
-//      waves' bounds is a lower bound theta on the k-th best score of the row: some wave holds k distinct
+//      waves' bounds is a lower bound theta on the k-th best score of the part: some wave holds k distinct
 //      documents scoring at least that much;
 //   2. every document scoring >= theta goes to LDS (a few k of them) and is ranked by counting on the full
 //      key.
 // Exact, ties included (keys are (score, ~doc): a total order; theta compares scores only, so equal scores
 // survive together).  If more survive than LDS holds (adversarial order), k rounds of a block-wide arg-max
-// over the row take over.
+// over the part take over.
 constexpr int kRowSurv = 2048;
-constexpr int kRowRegs = 32;  // scores a thread keeps in registers between the two passes
+constexpr int kRowRegs = 32;        // scores a thread keeps in registers between the two passes (8: short rows)
+constexpr int kRowPart = 8192;      // documents per part of a long row: what 32 registers per thread hold
 
-__global__ __launch_bounds__(256) void topk_rows_kernel(const float* __restrict__ mat,
-                                                        int32_t* __restrict__ out_idx,
-                                                        float* __restrict__ out_score,
-                                                        unsigned long long* __restrict__ out_key, int BM,
-                                                        int n_sel, int N, int k) {
-  __shared__ unsigned long long surv[kRowSurv];
+struct RowsArgs {
+  const float* mat;           // [selections][queries of the pass][stride]
+  long long stride;           // documents per matrix row
+  int rows_q, q0, BM;         // queries of the pass, first one, queries in all
+  int n_sel;                  // selections per query
+  int n_docs, doc0;           // documents of a row and the number of its first one
+  int parts, part_docs;       // parts of a row
+  int part0, parts_total;     // part lists: number of this launch's first part, parts per (selection, query)
+  int k;
+  int32_t* out_idx;           // whole rows: the final selection ...
+  float* out_score;
+  unsigned long long* out_key;   // ... or (not null) its sorted keys [BM][n_sel][k]
+  unsigned long long* part_keys; // not null: sorted keys per part, [n_sel][BM][parts_total][k]
+};
+
+template <int REGS>
+__global__ __launch_bounds__(256) void topk_rows_kernel(RowsArgs a) {
+  __shared__ unsigned long long surv[kRowSurv + 8];
   __shared__ unsigned long long red[4];
   __shared__ uint32_t theta_w[4];
   __shared__ int n_surv;
   const int tid = threadIdx.x;
-  const int qg = blockIdx.x % BM;
-  const int g = blockIdx.x / BM;
-  const float* row = mat + ((long long)g * BM + qg) * N;
-  const long long o_base = ((long long)qg * n_sel + g) * k;
-  float v[kRowRegs];
+  const int k = a.k;
+  const int part = blockIdx.x % a.parts;
+  const int row_no = blockIdx.x / a.parts;
+  const int qg = a.q0 + row_no % a.rows_q;
+  const int g = row_no / a.rows_q;
+  const int first = part * a.part_docs;
+  const int N = a.n_docs - first < a.part_docs ? a.n_docs - first : a.part_docs;  // documents of this part
+  const float* row = a.mat + (long long)row_no * a.stride + first;
+  const uint32_t doc0 = (uint32_t)(a.doc0 + first);
+  float v[REGS];
   unsigned long long best = 0ull;
 #pragma unroll
-  for (int u = 0; u < kRowRegs; ++u) {
+  for (int u = 0; u < REGS; ++u) {
     const int i = u * 256 + tid;
     v[u] = (i < N) ? row[i] : 0.f;
   }
 #pragma unroll
-  for (int u = 0; u < kRowRegs; ++u) {
+  for (int u = 0; u < REGS; ++u) {
     const int i = u * 256 + tid;
-    const unsigned long long x = (i < N) ? make_key(v[u], (uint32_t)i) : 0ull;
+    const unsigned long long x = (i < N) ? make_key(v[u], doc0 + i) : 0ull;
     best = x > best ? x : best;
   }
-  for (int i = kRowRegs * 256 + tid; i < N; i += 256) {  // rows longer than the register share
-    const unsigned long long x = make_key(row[i], (uint32_t)i);
+  for (int i = REGS * 256 + tid; i < N; i += 256) {  // rows longer than the register share
+    const unsigned long long x = make_key(row[i], doc0 + i);
     best = x > best ? x : best;
   }
   {
@@ -976,36 +1044,49 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(const float* __restrict_
     }
   };
 #pragma unroll
-  for (int u = 0; u < kRowRegs; ++u) {
+  for (int u = 0; u < REGS; ++u) {
     const int i = u * 256 + tid;
-    keep((i < N) ? make_key(v[u], (uint32_t)i) : 0ull);
+    keep((i < N) ? make_key(v[u], doc0 + i) : 0ull);
   }
-  for (int i = kRowRegs * 256 + tid; i < N; i += 256) keep(make_key(row[i], (uint32_t)i));
+  for (int i = REGS * 256 + tid; i < N; i += 256) keep(make_key(row[i], doc0 + i));
   __syncthreads();
   const int ns = n_surv;
+  const long long o_base = a.part_keys
+                               ? (((long long)g * a.BM + qg) * a.parts_total + a.part0 + part) * k
+                               : ((long long)qg * a.n_sel + g) * k;
   auto emit = [&](int rank, unsigned long long x) {
-    if (out_key) {
-      out_key[o_base + rank] = x;
+    if (a.part_keys) {
+      a.part_keys[o_base + rank] = x;
+    } else if (a.out_key) {
+      a.out_key[o_base + rank] = x;
     } else {
-      out_idx[o_base + rank] = x ? (int32_t)key_doc(x) : -1;
-      if (out_score) out_score[o_base + rank] = x ? key_score(x) : -INFINITY;
+      a.out_idx[o_base + rank] = x ? (int32_t)key_doc(x) : -1;
+      if (a.out_score) a.out_score[o_base + rank] = x ? key_score(x) : -INFINITY;
     }
   };
   if (ns <= kRowSurv) {
+    if (tid < 8) surv[ns + tid] = 0ull;  // the rank count below reads eight at a time (zero: greater than no key)
+    __syncthreads();
     for (int i = tid; i < ns; i += 256) {
       const unsigned long long x = surv[i];
       int rank = 0;
-      for (int j = 0; j < ns; ++j) rank += (surv[j] > x) ? 1 : 0;
+      for (int j = 0; j < ns; j += 8) {
+        unsigned long long y[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) y[u] = surv[j + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) rank += (y[u] > x) ? 1 : 0;
+      }
       if (rank < k) emit(rank, x);
     }
-    for (int i = ns + tid; i < k; i += 256) emit(i, 0ull);  // fewer than k documents (cannot happen for k <= N)
+    for (int i = ns + tid; i < k; i += 256) emit(i, 0ull);  // fewer than k documents (a short part)
     return;
   }
   unsigned long long prev = ~0ull;
   for (int round = 0; round < k; ++round) {
     unsigned long long bst = 0ull;
     for (int i = tid; i < N; i += 256) {
-      const unsigned long long x = make_key(row[i], (uint32_t)i);
+      const unsigned long long x = make_key(row[i], doc0 + i);
       if (x < prev && x > bst) bst = x;
     }
 #pragma unroll
@@ -1022,6 +1103,13 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(const float* __restrict_
     if (tid == 0) emit(round, bst);
     prev = bst ? bst : 0ull;
   }
+}
+
+static void launch_topk_rows(const RowsArgs& ra, hipStream_t st) {
+  const unsigned blocks = (unsigned)(ra.rows_q * ra.n_sel * ra.parts);
+  const int n = ra.n_docs < ra.part_docs ? ra.n_docs : ra.part_docs;
+  if (n <= 8 * 256) hipLaunchKernelGGL(topk_rows_kernel<8>, dim3(blocks), dim3(256), 0, st, ra);
+  else hipLaunchKernelGGL(topk_rows_kernel<kRowRegs>, dim3(blocks), dim3(256), 0, st, ra);
 }
 
 // Combine the n_lists sorted lists (k entries each, zero-padded) of one (query, group).
@@ -1256,6 +1344,35 @@ static void add_token_pool(const Dims& dm, int BM, int k, ScorePlan* p) {
     p->ws_bytes += round_up256((size_t)BM * p->n_sel * k * sizeof(unsigned long long));
 }
 
+// All-heads scan: passes of up to 32 queries over segments of the bank; the score matrix of one (pass, segment) stays
+// under 24 MB, which bounds the workspace and keeps the matrix in the cache behind the L2s between the scan that
+// writes it and the selection that reads it.  Rows beyond 16384 documents are selected from in parts of 8192 (one
+// workgroup each) whose lists the merge kernel combines; up to there one workgroup per row, without the merge launch,
+// is the faster way.
+static void plan_all_heads(const Dims& dm, int BM, int k, ScorePlan* p) {
+  constexpr long long kMatBytes = (long long)24 << 20;
+  p->mode = 2;
+  p->tiles_per_wave = 0;
+  p->exchange = p->it_publish = p->it_adopt = 0;
+  p->off_gmax = 0;
+  p->n_pass = (BM + 31) / 32;
+  const int even = (BM + p->n_pass - 1) / p->n_pass;  // queries per pass, all passes alike
+  p->q_per_pass = even <= 8 ? 8 : (even <= 16 ? 16 : 32);
+  p->n_pass = (BM + p->q_per_pass - 1) / p->q_per_pass;
+  p->part_docs = dm.N <= 2 * kRowPart ? dm.N : kRowPart;
+  long long seg = kMatBytes / (4 * p->q_per_pass) / p->part_docs * p->part_docs;
+  if (seg > dm.N || dm.N <= 2 * kRowPart) seg = dm.N;
+  p->seg_docs = (int)seg;
+  p->n_splits = (dm.N + p->part_docs - 1) / p->part_docs;  // parts of a row = lists per query
+  size_t end = p->n_splits > 1 ? round_up256((size_t)BM * p->n_splits * k * sizeof(unsigned long long)) : 0;
+  p->n_qtiles = p->n_pass * (p->q_per_pass / 8);
+  p->off_qop = end;
+  end += round_up256((size_t)dm.Hkv * p->n_qtiles * (dm.d / 32) * 64 * 16);
+  p->off_mat = end;
+  end += round_up256((size_t)p->q_per_pass * p->seg_docs * sizeof(float));
+  p->ws_bytes = end;
+}
+
 ScorePlan plan_score(const Dims& dm, int BM, int k) {
   ScorePlan p;
   // one selection per KV group, or (literal Eq. 2 head mean, more than one group) one for all heads
@@ -1279,16 +1396,21 @@ ScorePlan plan_score(const Dims& dm, int BM, int k) {
     add_token_pool(dm, BM, k, &p);
     return p;
   }
-  p.q_per_pass = (BM <= 8 || p.all_heads) ? 8 : ((BM <= 16 || k > 24) ? 16 : 32);
+  if (p.all_heads) {
+    plan_all_heads(dm, BM, k, &p);
+    add_token_pool(dm, BM, k, &p);
+    return p;
+  }
+  p.q_per_pass = BM <= 8 ? 8 : ((BM <= 16 || k > 24) ? 16 : 32);
   p.n_pass = (BM + p.q_per_pass - 1) / p.q_per_pass;
-  long long ns = p.all_heads ? 2048 : 2048 / dm.Hkv;  // ~8 waves per CU on 256 CUs
+  long long ns = 2048 / dm.Hkv;  // ~8 waves per CU on 256 CUs
   if (ns < 1) ns = 1;
   // streams of at least kPrefetch tiles; with 32 queries per pass the lists (64 entries each) must
   // also hold every document of the stream without pruning, so streams stay short there
   const long long min_len = kPrefetch;
   const long long by_tiles = (dm.tiles + min_len - 1) / min_len;
   if (ns > by_tiles) ns = by_tiles;
-  if (ns > 1024 && !p.all_heads) ns = 1024;
+  if (ns > 1024) ns = 1024;
   if (ns < 1) ns = 1;
   const long long tiles_per_split = (dm.tiles + ns - 1) / ns;
   p.n_splits = (int)((dm.tiles + tiles_per_split - 1) / tiles_per_split);
@@ -1299,7 +1421,7 @@ ScorePlan plan_score(const Dims& dm, int BM, int k) {
   // lists' LDS and the matrix stays small; else MODE 1 (dense lists) when the lists hold the stream.
   p.mode = 0;
   p.tiles_per_wave = 0;
-  if (!p.all_heads) {
+  {
     const long long dpt = 16 / dm.C;
     const long long n_it_max = (dm.tiles + p.n_splits - 1) / p.n_splits;
     const long long cap = kListBytes / (8 * p.q_per_pass), capf = kListBytes / (4 * p.q_per_pass);
@@ -1313,7 +1435,7 @@ ScorePlan plan_score(const Dims& dm, int BM, int k) {
       p.mode = 1;
     }
   }
-  p.exchange = (!p.all_heads && p.mode == 0 && n_it_min >= 64 && p.n_splits >= k && p.n_splits <= 256) ? 1 : 0;
+  p.exchange = (p.mode == 0 && n_it_min >= 64 && p.n_splits >= k && p.n_splits <= 256) ? 1 : 0;
   // exchange events sit at the head of a group of kPrefetch iterations
   p.it_publish = (int)(n_it_min / 12) / kPrefetch * kPrefetch;
   p.it_adopt = p.it_publish + 3 * kPrefetch;
@@ -1402,28 +1524,79 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
   }
   // an index of more than 512 MB outgrows the 256 MB of cache behind the L2s even across passes
   const bool stream_index = (size_t)dm.Hkv * dm.tiles * 16 * dm.d * 2 > ((size_t)512 << 20);
-  const int wpb = pl.all_heads ? kAllWaves : kScanWaves;
-  dim3 grid((pl.n_splits + wpb - 1) / wpb, pl.all_heads ? 1 : dm.Hkv), block(64 * wpb);
+  RowsArgs ra;
+  ra.mat = (const float*)((char*)ws + pl.off_mat);
+  ra.BM = BM;
+  ra.n_sel = pl.n_sel;
+  ra.k = k;
+  ra.out_idx = out_idx;
+  ra.out_score = out_score;
+  ra.out_key = tok_keys;
+  if (pl.all_heads) {
+    ScanAllArgs sa;
+    sa.qop = (const uint4*)((char*)ws + pl.off_qop);
+    sa.KR = (const uint16_t*)KR;
+    sa.inv_norm = a.inv_norm;
+    sa.mat = (float*)((char*)ws + pl.off_mat);
+    sa.mat_stride = pl.seg_docs;
+    sa.n_qtiles = pl.n_qtiles;
+    sa.C = dm.C;
+    sa.tiles = dm.tiles;
+    ra.stride = pl.seg_docs;
+    ra.part_docs = pl.part_docs;
+    ra.parts_total = pl.n_splits;
+    ra.part_keys = pl.n_splits > 1 ? (unsigned long long*)ws : nullptr;
+    const int nqt = pl.q_per_pass / 8;  // 1, 2 or 4
+    profile_mark(dm, false, st);
+    for (int pass = 0; pass < pl.n_pass; ++pass) {
+      const int q0 = pass * pl.q_per_pass;
+      const int nq = BM - q0 < pl.q_per_pass ? BM - q0 : pl.q_per_pass;
+      for (int doc0 = 0; doc0 < dm.N; doc0 += pl.seg_docs) {
+        const int n_docs = dm.N - doc0 < pl.seg_docs ? dm.N - doc0 : pl.seg_docs;
+        sa.qt0 = pass * nqt;
+        sa.nq = nq;
+        sa.tile0 = (long long)doc0 * dm.C / 16;  // doc0 is a multiple of 8192 (or 0)
+        sa.seg_docs = n_docs;
+        sa.seg_tiles = ((long long)n_docs * dm.C + 15) / 16;
+        sa.ushift = scan_all_ushift(sa.seg_tiles, dm.C);
+        const long long units = (sa.seg_tiles + (1 << sa.ushift) - 1) >> sa.ushift;
+        const long long wgs = (units + kAllWaves - 1) / kAllWaves;
+        dim3 grid((unsigned)(wgs < kAllGroups ? wgs : kAllGroups)), block(64 * kAllWaves);
+#define MSA_SCAN_ALL(DD, HH, QQ) \
+  do { \
+    if (stream_index) hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, QQ, true>), grid, block, 0, st, sa); \
+    else hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, QQ, false>), grid, block, 0, st, sa); \
+  } while (0)
+#define MSA_SCAN_ALL_Q(DD, HH) \
+  do { \
+    if (nqt == 1) MSA_SCAN_ALL(DD, HH, 1); else if (nqt == 2) MSA_SCAN_ALL(DD, HH, 2); else MSA_SCAN_ALL(DD, HH, 4); \
+  } while (0)
+        if (dm.d == 128) {
+          if (dm.Hkv == 2) MSA_SCAN_ALL_Q(128, 2); else if (dm.Hkv == 4) MSA_SCAN_ALL_Q(128, 4); else MSA_SCAN_ALL_Q(128, 8);
+        } else {
+          if (dm.Hkv == 2) MSA_SCAN_ALL_Q(64, 2); else if (dm.Hkv == 4) MSA_SCAN_ALL_Q(64, 4); else MSA_SCAN_ALL_Q(64, 8);
+        }
+#undef MSA_SCAN_ALL_Q
+#undef MSA_SCAN_ALL
+        if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
+        if (pass == pl.n_pass - 1 && doc0 + n_docs == dm.N) profile_mark(dm, true, st);
+        ra.rows_q = nq;
+        ra.q0 = q0;
+        ra.n_docs = n_docs;
+        ra.doc0 = doc0;
+        ra.parts = (n_docs + pl.part_docs - 1) / pl.part_docs;
+        ra.part0 = doc0 / pl.part_docs;
+        launch_topk_rows(ra, st);
+        if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
+      }
+    }
+    if (pl.n_splits > 1) return merge((const unsigned long long*)ws, pl.n_splits);
+    return pool_tokens();
+  }
+  dim3 grid((pl.n_splits + kScanWaves - 1) / kScanWaves, dm.Hkv), block(64 * kScanWaves);
   profile_mark(dm, false, st);
   for (int pass = 0; pass < pl.n_pass; ++pass) {
     a.q0 = pass * pl.q_per_pass;
-    if (pl.all_heads) {
-#define MSA_SCAN_ALL(DD, HH) \
-  do { \
-    if (dm.cos && stream_index) hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, true, true>), grid, block, 0, st, a); \
-    else if (dm.cos) hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, true, false>), grid, block, 0, st, a); \
-    else if (stream_index) hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, false, true>), grid, block, 0, st, a); \
-    else hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, false, false>), grid, block, 0, st, a); \
-  } while (0)
-      if (dm.d == 128) {
-        if (dm.Hkv == 2) MSA_SCAN_ALL(128, 2); else if (dm.Hkv == 4) MSA_SCAN_ALL(128, 4); else MSA_SCAN_ALL(128, 8);
-      } else {
-        if (dm.Hkv == 2) MSA_SCAN_ALL(64, 2); else if (dm.Hkv == 4) MSA_SCAN_ALL(64, 4); else MSA_SCAN_ALL(64, 8);
-      }
-#undef MSA_SCAN_ALL
-      if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
-      continue;
-    }
     const int nqt = pl.q_per_pass / 8;  // 1, 2 or 4
 #define MSA_SCAN(DD, QQ, CC) \
   do { \
@@ -1450,8 +1623,14 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
   }
   profile_mark(dm, true, st);
   if (pl.mode == 2) {
-    hipLaunchKernelGGL(topk_rows_kernel, dim3(BM * pl.n_sel), dim3(256), 0, st, (const float*)a.mat, out_idx,
-                       out_score, tok_keys, BM, pl.n_sel, dm.N, k);
+    ra.stride = dm.N;
+    ra.rows_q = BM;
+    ra.q0 = 0;
+    ra.n_docs = ra.part_docs = dm.N;
+    ra.doc0 = ra.part0 = 0;
+    ra.parts = ra.parts_total = 1;
+    ra.part_keys = nullptr;
+    launch_topk_rows(ra, st);
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
     return pool_tokens();
   }

@@ -1,0 +1,47 @@
+"""Branches of the work plans at the sizes where they can go wrong, against the float64 oracle (tolerances as in
+test_gpu_parity.py)."""
+import numpy as np
+import pytest
+import torch
+
+import msa_synth as S
+import paper_2603_23516_amd as msa
+from oracle import msa_oracle as O
+
+from test_gpu_parity import check_topk_generic, dev, say, upload_oracle_index
+
+pytestmark = pytest.mark.gpu
+
+
+def random_index(seed, N, Hkv, C, d):
+    _, KRb = S.normal_bf16(seed, (Hkv, N * C, d))
+    return KRb, 1.0 / np.maximum(np.linalg.norm(KRb, axis=-1), O.EPS_NORM)
+
+
+# (N, Hkv, r, C, d, B, M, k, sim): the all-heads scan writes a score matrix
+ALL_SCAN = [
+    (5, 8, 1, 8, 128, 1, 1, 5, "cos"),            # fewer tiles than one workgroup has waves
+    (1037, 4, 2, 16, 128, 9, 1, 33, "cos"),       # 16-query pass, one document per tile
+    (8193, 8, 1, 8, 128, 25, 1, 16, "cos"),       # 32-query pass, units of several tiles, ragged last tile
+    (4099, 8, 2, 1, 64, 33, 1, 20, "dot"),        # two passes, sixteen documents per tile
+    (16400, 2, 1, 2, 64, 2, 2, 64, "cos"),        # rows in three parts, the last of 16 documents (fewer than k)
+    (200007, 2, 1, 1, 64, 25, 1, 7, "cos"),       # two segments of the bank
+]
+
+
+@pytest.mark.parametrize("N,Hkv,r,C,d,B,M,k,sim", ALL_SCAN)
+def test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim):
+    say(f"all-heads scan N={N} Hkv={Hkv} C={C} d={d} B={B} M={M} k={k} {sim}")
+    cfg = msa.MsaConfig(N, 8 * C, 8, Hkv * r, Hkv, d, 1e6, select_scope=msa.MSA_SCOPE_ALL,
+                        sim=msa.MSA_SIM_COS if sim == "cos" else msa.MSA_SIM_DOT)
+    KRb, inv = random_index(51000 + N, N, Hkv, C, d)
+    qb, q = S.normal_bf16(51001 + N, (B, M, Hkv * r, d))
+    KRb[:, 3 * C] = KRb[:, (N - 2) * C]          # two documents with an equal chunk
+    inv = 1.0 / np.maximum(np.linalg.norm(KRb, axis=-1), O.EPS_NORM)
+    dKR, dinv = upload_oracle_index(cfg, KRb, inv)
+    for pool in (False, True):
+        cfg_p = cfg.replace(token_pool=int(pool))
+        ws = torch.full((msa.score_topk_workspace_bytes(cfg_p, B, M, k),), 0xFF, dtype=torch.uint8, device="cuda")
+        idx, val = msa.msa_score_topk(cfg_p, dev(qb), dKR, dinv if sim == "cos" else None, k, workspace=ws)
+        torch.cuda.synchronize()
+        check_topk_generic(q, KRb, C, N, idx, val, k, sim, "all", pool, atol=2e-5 if sim == "cos" else 2e-4)
