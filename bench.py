@@ -509,7 +509,7 @@ def main():
                       "median_ms": score_all[args.steps // 2], "min_ms": score_all[0],
                       "entry_point_ms": score_call_ms,
                       "entry_point_frac": ab["score"] / (score_call_ms * 1e-3) / 1e9 / HBM_PEAK_GBS} if flops is None else
-                     {"bound": "mfma", "kernel": ("score_gemm_all_kernel" if args.scope == "all" else "score_gemm_kernel") +
+                     {"bound": "mfma", "kernel": ("score_wide_kernel" if args.scope == "all" else "score_gemm_kernel") +
                       (" on the hi parts of the queries (inside msa_score_topk = fold + one-pass GEMM + candidates and exact "
                        "scores + gated two-pass GEMM and merge)" if one_pass else " (inside msa_score_topk = fold + GEMM + merge)"),
                       "achieved": flops / (score_ms * 1e-3) / 1e12, "peak": MFMA_BF16_PEAK_TFLOPS,

@@ -23,10 +23,9 @@ struct Dims {
 
 // Work split of the MFMA-bound scoring path for many query tokens (msa_score_gemm.hip).
 struct GemmPlan {
-  int all_heads;         // 1: head mean over every head (select_scope = ALL): score_gemm_all_kernel
-  int n_qblocks;         // blocks of 256 (128: k > 8, or all heads) query tokens
+  int n_qblocks;         // blocks of 256 (128: k > 8) query tokens
   int n_splits;          // key-range splits per (head, token block)
-  int stages_per_split;  // 64-key stages per split (all heads: ranges of stages per split)
+  int stages_per_split;  // 64-key stages per split
   size_t off_lists;      // byte offset of the candidate lists (after the folded fp32 queries)
   // One-pass filter (cosine, d = 128, eight chunks per document, one selection per KV group): the product runs on
   // the bf16 hi parts of the folded queries alone; every document whose one-pass score lies within twice the error
@@ -52,6 +51,25 @@ int launch_score_gemm_scan(const Dims& dm, const GemmPlan& pl, const void* q_rou
                            const void* KR, const float* inv_norm, int k, void* ws, hipStream_t st,
                            int32_t* out_idx, float* out_score, unsigned long long* out_key, const int** gate_flags);
 
+// Folds the heads of BM tokens: qf fp32 [BM][Hkv][d], and where not null eps, flags, qop (see fold_queries_kernel).
+int launch_fold_queries(const Dims& dm, const void* q_route, int BM, float* qf, float* eps, int* flags, int n_flags,
+                        uint4* qop, int n_rt, int pair, hipStream_t st);
+
+// Head mean over every head for many query tokens (msa_score_wide.hip): passes of tokens, segments of the bank.
+struct WidePlan {
+  int pair;              // 1: hi and lo rows (dot product), 32 tokens per workgroup; 0: hi rows alone, 64
+  int pass_tokens;       // query tokens per pass
+  int n_tb;              // token blocks (64 operand rows) of a whole pass
+  int seg_docs;          // documents per segment (one score matrix)
+  size_t off_qf, off_qop, off_eps, off_best, off_mat;
+  size_t ws_bytes;
+};
+bool wide_path_applies(const Dims& dm, int BM);
+WidePlan plan_score_wide(const Dims& dm, int BM, int k);
+int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, int BM, const void* KR,
+                      const float* inv_norm, int k, void* ws, hipStream_t st, int32_t* out_idx, float* out_score,
+                      unsigned long long* out_key);
+
 // Work split of the routing scan (depends only on the problem size, so the workspace size is a
 // pure function of the arguments).
 struct ScorePlan {
@@ -74,7 +92,9 @@ struct ScorePlan {
   int merge_parts;       // > 1: two-level merge, first level over merge_lpp lists per block
   int merge_lpp;
   size_t off_part;       // byte offset of the first-level winners
-  int use_gemm;          // 1: many query tokens -> the GEMM path below
+  int use_wide;          // 1: all heads, more tokens than one pass of the scan -> msa_score_wide.hip
+  WidePlan wide;
+  int use_gemm;          // 1: many query tokens, a selection per KV group -> msa_score_gemm.hip
   GemmPlan gemm;
   size_t ws_bytes;
 };

@@ -682,10 +682,10 @@ struct ScanAllArgs {
   const uint4* qop;       // [HKV][n_qtiles][NS][64] prepared A operands (prep_scan_operands_kernel)
   const uint16_t* KR;     // tiled
   const float* inv_norm;  // null: dot product
-  float* mat;             // [queries of the pass][mat_stride]
+  float* mat;             // [queries][mat_stride]
   long long mat_stride;   // documents per row
-  int n_qtiles, qt0;      // operand tiles in all, first one of this pass
-  int nq;                 // queries of this pass (<= 8 NQT)
+  int n_qtiles;           // operand tiles
+  int nq;                 // queries (<= 8 NQT)
   int C;
   long long tiles;        // tiles per head in the index
   long long tile0;        // first tile of this segment
@@ -722,7 +722,7 @@ __global__ __launch_bounds__(64 * kAllWaves) void score_scan_all_kernel(ScanAllA
     int e = i * kAllWaves + wave;  // (head, tile, slice)
     e = e < NOP ? e : NOP - 1;     // past the end: the last piece again (the same bytes to the same place)
     const int h = e / (NQT * NS), rest = e % (NQT * NS);
-    const uint4* src = a.qop + (((long long)h * a.n_qtiles + a.qt0) * NS + rest) * 64;
+    const uint4* src = a.qop + ((long long)h * a.n_qtiles * NS + rest) * 64;
     copy16_to_lds_async_at(src, lane * 16, op_lds + e * 1024);
   }
 
@@ -843,7 +843,7 @@ __global__ __launch_bounds__(64 * kAllWaves) void score_scan_all_kernel(ScanAllA
         const long long doc0 = (tile_at(it) - umask) * dpt;  // document inside the segment
         const int j = lane & (du - 1), qo = lane >> dshift, qpi = 64 >> dshift;
         if (doc0 + j < a.seg_docs) {
-          for (int qi = qo; qi < a.nq; qi += qpi) a.mat[qi * a.mat_stride + doc0 + j] = run[qi][j];
+          for (int qi = qo; qi < a.nq; qi += qpi) a.mat[qi * a.mat_stride + doc0 + j] = fmaxf(run[qi][j], -INFINITY);  // (not a number: last)
         }
         wave_sync();
       }
@@ -858,17 +858,21 @@ __global__ __launch_bounds__(64 * kAllWaves) void score_scan_all_kernel(ScanAllA
 // D is in m*'s list with exactly its pooled score.  Ranking the union by (best listed score desc,
 // index asc) therefore reproduces the pooled top-k exactly.  One block per (batch row, scope slot):
 // k rounds of a block-wide arg-max over the M*k listed keys, skipping documents already taken.
-constexpr int kPoolSurv = 4096;  // survivors kept in LDS
+// The listed entries at or above a floor go through a hash table in LDS that keeps the best entry per document (rounds
+// of arg-max that skip the documents taken pay two barriers per selected document: 150 tokens, k = 32: 58 -> 8 us).
+constexpr int kPoolThreads = 1024;
+constexpr int kPoolSlots = 8192;                  // hash table
+constexpr int kPoolDocs = kPoolSlots / 4;         // documents it takes (every thread can be one insertion past it)
 
-__global__ __launch_bounds__(256) void pool_tokens_kernel(const unsigned long long* __restrict__ tok_keys,
+__global__ __launch_bounds__(kPoolThreads) void pool_tokens_kernel(const unsigned long long* __restrict__ tok_keys,
                                                           int32_t* __restrict__ out_idx,
                                                           float* __restrict__ out_score, int M, int S,
                                                           int k) {
-  __shared__ unsigned long long surv[kPoolSurv];
-  __shared__ unsigned long long red[4];
+  __shared__ unsigned long long slots[kPoolSlots];
+  __shared__ unsigned long long surv[kPoolDocs + 8];
+  __shared__ unsigned long long red[kPoolThreads / 64];
   __shared__ uint32_t taken[MSA_MAX_TOPK];
-  __shared__ uint32_t floor_s;
-  __shared__ int n_surv;
+  __shared__ int n_docs, n_surv;
   const int tid = threadIdx.x;
   const int b = blockIdx.x / S;
   const int sl = blockIdx.x % S;
@@ -889,57 +893,78 @@ __global__ __launch_bounds__(256) void pool_tokens_kernel(const unsigned long lo
     __syncthreads();
     best = red[0];
 #pragma unroll
-    for (int w = 1; w < 4; ++w) best = red[w] > best ? red[w] : best;
+    for (int w = 1; w < kPoolThreads / 64; ++w) best = red[w] > best ? red[w] : best;
     return best;
   };
+  for (int i = tid; i < kPoolSlots; i += kPoolThreads) slots[i] = 0ull;
+  if (tid == 0) n_docs = n_surv = 0;
   // 1. A floor: one token's k listed documents already have pooled scores >= its k-th listed score,
   //    so the pooled k-th best score is at least the largest such k-th score; lower entries drop out.
   unsigned long long fl = 0ull;
-  for (int m = tid; m < M; m += 256) {
+  for (int m = tid; m < M; m += kPoolThreads) {
     const unsigned long long x = tok_keys[(((long long)b * M + m) * S + sl) * k + (k - 1)];
     fl = x > fl ? x : fl;
   }
-  fl = block_max(fl);
-  if (tid == 0) {
-    floor_s = (uint32_t)(fl >> 32);  // score bits only: entries that tie with the floor stay
-    n_surv = 0;
-  }
-  __syncthreads();
-  const uint32_t floor_bits = floor_s;
-  // 2. Survivors into LDS.
-  for (int i = tid; i < T; i += 256) {
+  fl = block_max(fl);  // (its barriers also order the cleared table)
+  const uint32_t floor_bits = (uint32_t)(fl >> 32);  // score bits only: entries that tie with the floor stay
+  // 2. The best entry of every document.  A slot belongs to one document once it is filled (the low half of a key);
+  //    the table is never full, so every search ends.
+  for (int i = tid; i < T; i += kPoolThreads) {
     const unsigned long long x = key_at(i);
-    if (x != 0ull && (uint32_t)(x >> 32) >= floor_bits) {
-      const int slot = atomicAdd(&n_surv, 1);
-      if (slot < kPoolSurv) surv[slot] = x;
+    if (x == 0ull || (uint32_t)(x >> 32) < floor_bits) continue;
+    if (*(volatile int*)&n_docs > kPoolDocs) break;  // too many documents: the rounds below take over
+    uint32_t h = ((uint32_t)x * 2654435761u) >> 19;  // 13 bits: kPoolSlots
+    static_assert(kPoolSlots == 1 << 13, "hash width");
+    for (;;) {
+      const unsigned long long old = atomicCAS(&slots[h], 0ull, x);
+      if (old == 0ull) {
+        atomicAdd(&n_docs, 1);
+        break;
+      }
+      if ((uint32_t)old == (uint32_t)x) {
+        atomicMax(&slots[h], x);
+        break;
+      }
+      h = (h + 1) & (kPoolSlots - 1);
     }
   }
   __syncthreads();
-  const int ns = n_surv;
-  if (ns <= kPoolSurv) {
-    // 3. k rounds of arg-max over the survivors; the entries of a chosen document are erased.
-    for (int round = 0; round < k; ++round) {
-      unsigned long long best = 0ull;
-      for (int i = tid; i < ns; i += 256) best = surv[i] > best ? surv[i] : best;
-      best = block_max(best);
-      if (tid == 0) {
-        out_idx[o_base + round] = best ? (int32_t)key_doc(best) : -1;
-        if (out_score) out_score[o_base + round] = best ? key_score(best) : -INFINITY;
+  if (n_docs <= kPoolDocs) {
+    // 3. Documents side by side, ranked by counting.
+    for (int i = tid; i < kPoolSlots; i += kPoolThreads) {
+      const unsigned long long x = slots[i];
+      if (x != 0ull) surv[atomicAdd(&n_surv, 1)] = x;
+    }
+    __syncthreads();
+    const int ns = n_surv;
+    if (tid < 8) surv[ns + tid] = 0ull;  // the rank count reads eight at a time (zero: greater than no key)
+    __syncthreads();
+    for (int i = tid; i < ns; i += kPoolThreads) {
+      const unsigned long long x = surv[i];
+      int rank = 0;
+      for (int j = 0; j < ns; j += 8) {
+        unsigned long long y[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) y[u] = surv[j + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) rank += (y[u] > x) ? 1 : 0;
       }
-      if (best != 0ull) {
-        const uint32_t low = (uint32_t)best;  // ~doc: identical for every entry of that document
-        for (int i = tid; i < ns; i += 256)
-          if ((uint32_t)surv[i] == low) surv[i] = 0ull;
+      if (rank < k) {
+        out_idx[o_base + rank] = (int32_t)key_doc(x);
+        if (out_score) out_score[o_base + rank] = key_score(x);
       }
-      __syncthreads();
+    }
+    for (int i = ns + tid; i < k; i += kPoolThreads) {  // fewer than k documents
+      out_idx[o_base + i] = -1;
+      if (out_score) out_score[o_base + i] = -INFINITY;
     }
     return;
   }
-  // Fallback (more survivors than LDS holds): rounds over the lists in memory, skipping taken documents.
+  // Fallback (more documents than the table takes): rounds over the lists in memory, skipping taken documents.
   unsigned long long prev = ~0ull;
   for (int round = 0; round < k; ++round) {
     unsigned long long best = 0ull;
-    for (int i = tid; i < T; i += 256) {
+    for (int i = tid; i < T; i += kPoolThreads) {
       const unsigned long long x = key_at(i);
       if (x == 0ull || x >= prev || x <= best) continue;  // keys of one document differ in the score bits only
       const uint32_t doc = key_doc(x);
@@ -974,9 +999,9 @@ constexpr int kRowRegs = 32;        // scores a thread keeps in registers betwee
 constexpr int kRowPart = 8192;      // documents per part of a long row: what 32 registers per thread hold
 
 struct RowsArgs {
-  const float* mat;           // [selections][queries of the pass][stride]
+  const float* mat;           // [selections][BM][stride]
   long long stride;           // documents per matrix row
-  int rows_q, q0, BM;         // queries of the pass, first one, queries in all
+  int BM;                     // queries
   int n_sel;                  // selections per query
   int n_docs, doc0;           // documents of a row and the number of its first one
   int parts, part_docs;       // parts of a row
@@ -998,8 +1023,8 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(RowsArgs a) {
   const int k = a.k;
   const int part = blockIdx.x % a.parts;
   const int row_no = blockIdx.x / a.parts;
-  const int qg = a.q0 + row_no % a.rows_q;
-  const int g = row_no / a.rows_q;
+  const int qg = row_no % a.BM;
+  const int g = row_no / a.BM;
   const int first = part * a.part_docs;
   const int N = a.n_docs - first < a.part_docs ? a.n_docs - first : a.part_docs;  // documents of this part
   const float* row = a.mat + (long long)row_no * a.stride + first;
@@ -1106,7 +1131,7 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(RowsArgs a) {
 }
 
 static void launch_topk_rows(const RowsArgs& ra, hipStream_t st) {
-  const unsigned blocks = (unsigned)(ra.rows_q * ra.n_sel * ra.parts);
+  const unsigned blocks = (unsigned)(ra.BM * ra.n_sel * ra.parts);
   const int n = ra.n_docs < ra.part_docs ? ra.n_docs : ra.part_docs;
   if (n <= 8 * 256) hipLaunchKernelGGL(topk_rows_kernel<8>, dim3(blocks), dim3(256), 0, st, ra);
   else hipLaunchKernelGGL(topk_rows_kernel<kRowRegs>, dim3(blocks), dim3(256), 0, st, ra);
@@ -1344,9 +1369,9 @@ static void add_token_pool(const Dims& dm, int BM, int k, ScorePlan* p) {
     p->ws_bytes += round_up256((size_t)BM * p->n_sel * k * sizeof(unsigned long long));
 }
 
-// All-heads scan: passes of up to 32 queries over segments of the bank; the score matrix of one (pass, segment) stays
-// under 24 MB, which bounds the workspace and keeps the matrix in the cache behind the L2s between the scan that
-// writes it and the selection that reads it.  Rows beyond 16384 documents are selected from in parts of 8192 (one
+// All-heads scan: one pass of up to 32 queries (more take the wide kernel) over segments of the bank; the score matrix
+// of one segment stays under 24 MB, which bounds the workspace and keeps the matrix in the cache behind the L2s between
+// the scan that writes it and the selection that reads it.  Rows beyond 16384 documents are selected from in parts of 8192 (one
 // workgroup each) whose lists the merge kernel combines; up to there one workgroup per row, without the merge launch,
 // is the faster way.
 static void plan_all_heads(const Dims& dm, int BM, int k, ScorePlan* p) {
@@ -1355,17 +1380,15 @@ static void plan_all_heads(const Dims& dm, int BM, int k, ScorePlan* p) {
   p->tiles_per_wave = 0;
   p->exchange = p->it_publish = p->it_adopt = 0;
   p->off_gmax = 0;
-  p->n_pass = (BM + 31) / 32;
-  const int even = (BM + p->n_pass - 1) / p->n_pass;  // queries per pass, all passes alike
-  p->q_per_pass = even <= 8 ? 8 : (even <= 16 ? 16 : 32);
-  p->n_pass = (BM + p->q_per_pass - 1) / p->q_per_pass;
+  p->n_pass = 1;
+  p->q_per_pass = BM <= 8 ? 8 : (BM <= 16 ? 16 : 32);
   p->part_docs = dm.N <= 2 * kRowPart ? dm.N : kRowPart;
   long long seg = kMatBytes / (4 * p->q_per_pass) / p->part_docs * p->part_docs;
   if (seg > dm.N || dm.N <= 2 * kRowPart) seg = dm.N;
   p->seg_docs = (int)seg;
   p->n_splits = (dm.N + p->part_docs - 1) / p->part_docs;  // parts of a row = lists per query
   size_t end = p->n_splits > 1 ? round_up256((size_t)BM * p->n_splits * k * sizeof(unsigned long long)) : 0;
-  p->n_qtiles = p->n_pass * (p->q_per_pass / 8);
+  p->n_qtiles = p->q_per_pass / 8;
   p->off_qop = end;
   end += round_up256((size_t)dm.Hkv * p->n_qtiles * (dm.d / 32) * 64 * 16);
   p->off_mat = end;
@@ -1378,7 +1401,15 @@ ScorePlan plan_score(const Dims& dm, int BM, int k) {
   // one selection per KV group, or (literal Eq. 2 head mean, more than one group) one for all heads
   p.all_heads = (dm.scope_all && dm.Hkv > 1) ? 1 : 0;
   p.n_sel = dm.scope_all ? 1 : dm.Hkv;
-  p.use_gemm = gemm_path_applies(dm, BM, k) ? 1 : 0;
+  p.use_wide = wide_path_applies(dm, BM) ? 1 : 0;
+  p.use_gemm = !p.use_wide && gemm_path_applies(dm, BM, k) ? 1 : 0;
+  if (p.use_wide) {
+    p.wide = plan_score_wide(dm, BM, k);
+    p.n_splits = 1;
+    p.ws_bytes = p.wide.ws_bytes;
+    add_token_pool(dm, BM, k, &p);
+    return p;
+  }
   if (p.use_gemm) {
     p.gemm = plan_score_gemm(dm, BM, k);
     p.n_splits = p.gemm.n_splits;
@@ -1457,7 +1488,7 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
   unsigned long long* tok_keys = dm.token_pool ? (unsigned long long*)((char*)ws + pl.off_tok) : nullptr;
   auto pool_tokens = [&]() -> int {
     if (!dm.token_pool) return MSA_OK;
-    hipLaunchKernelGGL(pool_tokens_kernel, dim3(B * pl.n_sel), dim3(256), 0, st,
+    hipLaunchKernelGGL(pool_tokens_kernel, dim3(B * pl.n_sel), dim3(kPoolThreads), 0, st,
                        (const unsigned long long*)tok_keys, out_idx, out_score, M, pl.n_sel, k);
     return hipGetLastError() == hipSuccess ? MSA_OK : MSA_ERR_HIP;
   };
@@ -1480,6 +1511,11 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
     return pool_tokens();
   };
+  if (pl.use_wide) {
+    const int rc = launch_score_wide(dm, pl.wide, q_route, BM, KR, inv_norm, k, ws, st, out_idx, out_score, tok_keys);
+    if (rc != MSA_OK) return rc;
+    return pool_tokens();
+  }
   if (pl.use_gemm) {
     const int rc = launch_score_gemm_scan(dm, pl.gemm, q_route, BM, KR, inv_norm, k, ws, st, out_idx, out_score,
                                           tok_keys, &gate);
@@ -1548,47 +1584,40 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
     ra.part_keys = pl.n_splits > 1 ? (unsigned long long*)ws : nullptr;
     const int nqt = pl.q_per_pass / 8;  // 1, 2 or 4
     profile_mark(dm, false, st);
-    for (int pass = 0; pass < pl.n_pass; ++pass) {
-      const int q0 = pass * pl.q_per_pass;
-      const int nq = BM - q0 < pl.q_per_pass ? BM - q0 : pl.q_per_pass;
-      for (int doc0 = 0; doc0 < dm.N; doc0 += pl.seg_docs) {
-        const int n_docs = dm.N - doc0 < pl.seg_docs ? dm.N - doc0 : pl.seg_docs;
-        sa.qt0 = pass * nqt;
-        sa.nq = nq;
-        sa.tile0 = (long long)doc0 * dm.C / 16;  // doc0 is a multiple of 8192 (or 0)
-        sa.seg_docs = n_docs;
-        sa.seg_tiles = ((long long)n_docs * dm.C + 15) / 16;
-        sa.ushift = scan_all_ushift(sa.seg_tiles, dm.C);
-        const long long units = (sa.seg_tiles + (1 << sa.ushift) - 1) >> sa.ushift;
-        const long long wgs = (units + kAllWaves - 1) / kAllWaves;
-        dim3 grid((unsigned)(wgs < kAllGroups ? wgs : kAllGroups)), block(64 * kAllWaves);
+    for (int doc0 = 0; doc0 < dm.N; doc0 += pl.seg_docs) {
+      const int n_docs = dm.N - doc0 < pl.seg_docs ? dm.N - doc0 : pl.seg_docs;
+      sa.nq = BM;
+      sa.tile0 = (long long)doc0 * dm.C / 16;  // doc0 is a multiple of 8192 (or 0)
+      sa.seg_docs = n_docs;
+      sa.seg_tiles = ((long long)n_docs * dm.C + 15) / 16;
+      sa.ushift = scan_all_ushift(sa.seg_tiles, dm.C);
+      const long long units = (sa.seg_tiles + (1 << sa.ushift) - 1) >> sa.ushift;
+      const long long wgs = (units + kAllWaves - 1) / kAllWaves;
+      dim3 grid((unsigned)(wgs < kAllGroups ? wgs : kAllGroups)), block(64 * kAllWaves);
 #define MSA_SCAN_ALL(DD, HH, QQ) \
-  do { \
-    if (stream_index) hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, QQ, true>), grid, block, 0, st, sa); \
-    else hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, QQ, false>), grid, block, 0, st, sa); \
-  } while (0)
+do { \
+  if (stream_index) hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, QQ, true>), grid, block, 0, st, sa); \
+  else hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, QQ, false>), grid, block, 0, st, sa); \
+} while (0)
 #define MSA_SCAN_ALL_Q(DD, HH) \
-  do { \
-    if (nqt == 1) MSA_SCAN_ALL(DD, HH, 1); else if (nqt == 2) MSA_SCAN_ALL(DD, HH, 2); else MSA_SCAN_ALL(DD, HH, 4); \
-  } while (0)
-        if (dm.d == 128) {
-          if (dm.Hkv == 2) MSA_SCAN_ALL_Q(128, 2); else if (dm.Hkv == 4) MSA_SCAN_ALL_Q(128, 4); else MSA_SCAN_ALL_Q(128, 8);
-        } else {
-          if (dm.Hkv == 2) MSA_SCAN_ALL_Q(64, 2); else if (dm.Hkv == 4) MSA_SCAN_ALL_Q(64, 4); else MSA_SCAN_ALL_Q(64, 8);
-        }
+do { \
+  if (nqt == 1) MSA_SCAN_ALL(DD, HH, 1); else if (nqt == 2) MSA_SCAN_ALL(DD, HH, 2); else MSA_SCAN_ALL(DD, HH, 4); \
+} while (0)
+      if (dm.d == 128) {
+        if (dm.Hkv == 2) MSA_SCAN_ALL_Q(128, 2); else if (dm.Hkv == 4) MSA_SCAN_ALL_Q(128, 4); else MSA_SCAN_ALL_Q(128, 8);
+      } else {
+        if (dm.Hkv == 2) MSA_SCAN_ALL_Q(64, 2); else if (dm.Hkv == 4) MSA_SCAN_ALL_Q(64, 4); else MSA_SCAN_ALL_Q(64, 8);
+      }
 #undef MSA_SCAN_ALL_Q
 #undef MSA_SCAN_ALL
-        if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
-        if (pass == pl.n_pass - 1 && doc0 + n_docs == dm.N) profile_mark(dm, true, st);
-        ra.rows_q = nq;
-        ra.q0 = q0;
-        ra.n_docs = n_docs;
-        ra.doc0 = doc0;
-        ra.parts = (n_docs + pl.part_docs - 1) / pl.part_docs;
-        ra.part0 = doc0 / pl.part_docs;
-        launch_topk_rows(ra, st);
-        if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
-      }
+      if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
+      if (doc0 + n_docs == dm.N) profile_mark(dm, true, st);
+      ra.n_docs = n_docs;
+      ra.doc0 = doc0;
+      ra.parts = (n_docs + pl.part_docs - 1) / pl.part_docs;
+      ra.part0 = doc0 / pl.part_docs;
+      launch_topk_rows(ra, st);
+      if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
     }
     if (pl.n_splits > 1) return merge((const unsigned long long*)ws, pl.n_splits);
     return pool_tokens();
@@ -1624,8 +1653,6 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
   profile_mark(dm, true, st);
   if (pl.mode == 2) {
     ra.stride = dm.N;
-    ra.rows_q = BM;
-    ra.q0 = 0;
     ra.n_docs = ra.part_docs = dm.N;
     ra.doc0 = ra.part0 = 0;
     ra.parts = ra.parts_total = 1;

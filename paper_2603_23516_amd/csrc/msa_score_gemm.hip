@@ -64,11 +64,14 @@ __device__ __forceinline__ float gsum(float x) {
 // score of any document computed from the bf16 hi parts of qf alone and its exact score: for a unit key,
 // |(qf - hi(qf)) . key| <= |qf - hi(qf)|, plus the rounding of two fp32 accumulations over d products; and it clears
 // the fallback flags of the token blocks.
+// With qop != null it also stores the bf16 hi parts (pair: hi and lo parts) as MFMA A operands, [Hkv][n_rt][d/32][64]:
+// lane 16q + n of a tile's slice s holds dims 32s + 8q .. + 8 of row n.
 template <int D>
 __global__ __launch_bounds__(64) void fold_queries_kernel(const uint16_t* __restrict__ q_route,
                                                           float* __restrict__ qf, int Hq, int Hkv,
                                                           int r, int cos, float* __restrict__ eps,
-                                                          int* __restrict__ flags, int n_flags) {
+                                                          int* __restrict__ flags, int n_flags,
+                                                          uint4* __restrict__ qop, int n_rt, int pair) {
   constexpr int LPH = D / 8, HPL = 64 / LPH;
   const int lane = threadIdx.x;
   const int g = blockIdx.x % Hkv;
@@ -96,15 +99,22 @@ __global__ __launch_bounds__(64) void fold_queries_kernel(const uint16_t* __rest
 #pragma unroll
     for (int e = 0; e < 8; ++e) f[e] += __shfl_xor(f[e], off, 64);
   }
-  float err2 = 0.f, n2 = 0.f;
+  float err2 = 0.f, n2 = 0.f, hi[8], lo[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
     const float x = f[e] / (float)r;
-    float hi, lo;
-    split_bf16(x, hi, lo);
-    err2 += lo * lo;
+    split_bf16(x, hi[e], lo[e]);
+    err2 += lo[e] * lo[e];
     n2 += x * x;
     f[e] = x;
+  }
+  if (qop != nullptr && hs == 0) {
+    // row of the token: 16 tokens per tile (hi), or 8 with hi and lo in neighbouring rows
+    const long long row = pair ? 2 * qg : qg;
+    uint4* dst = qop + (((long long)g * n_rt + (row >> 4)) * (D / 32) + (piece >> 2)) * 64 + (piece & 3) * 16 + (row & 15);
+    dst[0] = make_uint4(pack_bf16(hi[0], hi[1]), pack_bf16(hi[2], hi[3]), pack_bf16(hi[4], hi[5]), pack_bf16(hi[6], hi[7]));
+    if (pair)
+      dst[1] = make_uint4(pack_bf16(lo[0], lo[1]), pack_bf16(lo[2], lo[3]), pack_bf16(lo[4], lo[5]), pack_bf16(lo[6], lo[7]));
   }
   if (hs == 0) {
     float* dst = qf + (qg * Hkv + g) * D + piece * 8;
@@ -480,305 +490,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
   }
 }
 
-// ---- Eq. 2 as printed for many query tokens: head mean over EVERY head (select_scope = ALL) -----------
-// The chunk score is the mean over the KV groups g of  inv_norm_g(key) * (qf_g(token) . key_g):  every group
-// has its own keys and its own reciprocal norms, so the groups' products cannot share one accumulator; each is
-// scaled by its group's 1/|key| and added to a running total, and the document max and the top-k run ONCE on the
-// total -- eight times the matrix work per selection of the per-group kernel above, and an epilogue that is
-// amortised over the groups.
-//
-// A workgroup owns 128 query tokens (4 waves x 32) and a range of key stages.  The stages are walked in RANGES of
-// R stages (R x 64 keys): for each group in turn the wave loads that group's folded queries of its 32 tokens
-// (fp32 from the workspace, split into bf16 hi + lo operands in registers) and multiplies them with the group's
-// keys of the range, streamed through the same three-buffer ring of asynchronous global -> LDS copies (entry e of
-// the stream = range e / (HKV R), group (e / R) % HKV, stage e % R of the range); the totals of the range's
-// 2 R sub-tiles stay in registers until the last group has been added.
-constexpr int all_range(int KL) { return KL <= 8 ? 3 : 2; }  // stages per range (what the registers hold)
-
-// HIONLY: the one-pass filter, as in score_gemm_kernel (hi parts only, both per-lane lists written out whole:
-// [BM][n_splits][2][KL]); the two-pass form behind it runs only for the token blocks flagged in a.flags.
-template <int D, int KL, int HKV, bool HIONLY>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void score_gemm_all_kernel(GemmArgs a) {
-  constexpr int NS8 = D / 16;
-  constexpr int SUB_BYTES = 32 * D * 2;
-  constexpr int STAGE_BYTES = 2 * SUB_BYTES;
-  constexpr int TILE_ELEMS = 16 * D;
-  constexpr int LOADS = STAGE_BYTES / (256 * 16);
-  constexpr int R = all_range(KL);
-  constexpr int MRG_BYTES = 4 * 32 * 2 * KL * 8;
-  constexpr int RING_BYTES = 3 * STAGE_BYTES;
-  __shared__ __attribute__((aligned(16))) unsigned char smem[RING_BYTES > MRG_BYTES ? RING_BYTES : MRG_BYTES];
-  __shared__ __attribute__((aligned(16))) float ibuf[3][64];
-  __shared__ __attribute__((aligned(16))) float ones[64];
-  typedef unsigned long long mrg_row_t[2 * KL];
-  mrg_row_t* const mrg = reinterpret_cast<mrg_row_t*>(smem);
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int h = lane >> 5;
-  const int c = lane & 31;
-  // Workgroups go to the eight XCDs in turn (blockIdx % 8), each XCD with an L2 of its own: the token blocks of one
-  // key split are kept on one XCD, so that XCD streams only its splits' part of the index from memory and the
-  // other token blocks find it in the L2.
-  int vb = blockIdx.x;
-  {
-    const int total = a.n_qblocks * a.n_splits;
-    if (total % 8 == 0) vb = (blockIdx.x % 8) * (total / 8) + blockIdx.x / 8;
-  }
-  const int qb = vb % a.n_qblocks;
-  const int ks = vb / a.n_qblocks;
-  if (!HIONLY && a.flags != nullptr && a.flags[qb] == 0) return;  // block-uniform, ahead of any barrier
-  const long long n_sub = (a.tiles + 1) / 2;
-  const long long n_stage = (n_sub + 1) / 2;
-  const long long n_range = (n_stage + R - 1) / R;
-  const long long r0 = (long long)ks * a.stages_per_split;  // ranges per split
-  long long r1 = r0 + a.stages_per_split;
-  if (r1 > n_range) r1 = n_range;
-  if (tid < 64) ones[tid] = 1.0f;
-  const int tok = qb * 128 + wave * 32 + c;
-  const int n_rg = (r1 > r0) ? (int)(r1 - r0) : 0;  // ranges of this workgroup
-
-  float lsc[KL];
-  int ldoc[KL];
-#pragma unroll
-  for (int p = 0; p < KL; ++p) {
-    lsc[p] = -INFINITY;
-    ldoc[p] = -1;
-  }
-  constexpr int kPend = 2;
-  float psc[kPend];
-  int pdoc[kPend];
-  int pcnt = 0;
-#pragma unroll
-  for (int q = 0; q < kPend; ++q) {
-    psc[q] = -INFINITY;
-    pdoc[q] = -1;
-  }
-  auto flush = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int q = kPend - 1; q >= 0; --q) {  // oldest first: among equal scores the lower document stays ahead
-      const float sc = psc[q];
-      const int doc = pdoc[q];
-      const bool ok = q < pcnt && sc > lsc[KL - 1];
-#pragma unroll
-      for (int p = KL - 1; p >= 0; --p) {
-        const float above = (p > 0) ? lsc[p - 1] : INFINITY;
-        const int above_d = (p > 0) ? ldoc[p - 1] : -1;
-        const bool shift = ok && sc > above;
-        const bool here = ok && !shift && sc > lsc[p];
-        lsc[p] = shift ? above : (here ? sc : lsc[p]);
-        ldoc[p] = shift ? above_d : (here ? doc : ldoc[p]);
-      }
-    }
-    pcnt = 0;
-  };
-
-  constexpr int TILE_BYTES = TILE_ELEMS * 2;
-  constexpr int TPC = 4096 / TILE_BYTES;
-  const uint32_t goff_full = tid * 16;
-  const uint32_t goff_wrap = (tid * 16) % TILE_BYTES;
-  // The workgroup's stream of stages, in the order it multiplies them: range (local number rl), group, stage of the
-  // range.  All of it is kept in small 32-bit counters: no division in the loop (64-bit divisions by HKV * R and a
-  // 64-bit modulus per stage were 14 scalar instructions per MFMA).  Past the end the last entry is fetched again.
-  auto fetch = [&](int rl, int g, int st, unsigned char* kdst, float* idst) __attribute__((always_inline)) {
-    if (rl >= n_rg) {
-      rl = n_rg - 1;
-      g = HKV - 1;
-      st = R - 1;
-    }
-    const long long sg = (r0 + rl) * R + st;  // may lie past the last stage of the index: fetched clamped, its documents masked
-    const unsigned char* KRg = reinterpret_cast<const unsigned char*>(a.KR) + (long long)g * a.tiles * TILE_BYTES;
-    const float* ing = a.inv_norm ? a.inv_norm + (long long)g * a.tiles * 16 : nullptr;
-#pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
-      long long tile = 4 * sg + TPC * i;
-      if (tile >= a.tiles) tile = a.tiles - 1;
-      uint32_t goff = goff_full;
-      if constexpr (TPC > 1) goff = (tile + TPC <= a.tiles) ? goff_full : goff_wrap;
-      copy16_to_lds_async(KRg + tile * TILE_BYTES, goff, kdst + (i * 256 + wave * 64) * 16);
-    }
-    {
-      long long key0 = sg * 64;
-      const long long last = a.tiles * 16 - 1;
-      if (key0 > last) key0 = last;
-      const int room = (int)(last - key0 < 63 ? last - key0 : 63);
-      const float* src = ing ? ing + key0 : reinterpret_cast<const float*>(KRg);
-      copy4_to_lds_async(src, (uint32_t)((ing && lane > room) ? room : lane) * 4, idst);
-    }
-  };
-  auto wait_oldest_copy = [&]() __attribute__((always_inline)) {
-    if constexpr (LOADS == 4)
-      asm volatile("s_waitcnt vmcnt(5)" ::: "memory");
-    else
-      asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
-  };
-  // ring slot of a stage: (number of the stage in the stream) mod 3 = (slot of its group's first stage + st) mod 3
-  auto mod3 = [](int x) -> int { return x >= 6 ? x - 6 : (x >= 3 ? x - 3 : x); };
-  auto ring_k = [&](int slot) -> unsigned char* { return smem + slot * STAGE_BYTES; };
-  auto ring_i = [&](int slot) -> float* { return ibuf[slot]; };
-
-  if (n_rg > 0) {
-    fetch(0, 0, 0, ring_k(0), ring_i(0));
-    fetch(0, 0, 1, ring_k(1), ring_i(1));
-    wait_oldest_copy();
-  }
-  __syncthreads();
-  const float inv_groups = 1.0f / (float)HKV;
-  int slot0 = 0;  // ring slot of the current group's first stage (always 0 when R == 3)
-  for (int rl = 0; rl < n_rg; ++rl) {  // block-uniform
-    const long long rg = r0 + rl;
-    f32x16_t tot[2 * R];
-#pragma unroll
-    for (int t = 0; t < 2 * R; ++t)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) tot[t][i] = 0.f;
-    for (int g = 0; g < HKV; ++g) {
-      // this group's folded queries of the wave's 32 tokens: hi and lo operands
-      bf16x8_t Bhi[NS8], Blo[HIONLY ? 1 : NS8];
-#pragma unroll
-      for (int s = 0; s < NS8; ++s) {
-        float x[8];
-        if (tok < a.BM) {
-          const float4* src =
-              reinterpret_cast<const float4*>(a.qf + ((long long)tok * HKV + g) * D + 16 * s + 8 * h);
-          const float4 u0 = src[0], u1 = src[1];
-          x[0] = u0.x; x[1] = u0.y; x[2] = u0.z; x[3] = u0.w;
-          x[4] = u1.x; x[5] = u1.y; x[6] = u1.z; x[7] = u1.w;
-        } else {
-#pragma unroll
-          for (int i = 0; i < 8; ++i) x[i] = 0.f;
-        }
-        uint32_t wh[4], wl[4];
-#pragma unroll
-        for (int jj = 0; jj < 4; ++jj) split_pack_bf16(x[2 * jj], x[2 * jj + 1], wh[jj], wl[jj]);
-        Bhi[s] = as_bf16x8(make_uint4(wh[0], wh[1], wh[2], wh[3]));
-        if constexpr (!HIONLY) Blo[s] = as_bf16x8(make_uint4(wl[0], wl[1], wl[2], wl[3]));
-      }
-      // The operands are complete HERE, ahead of the first ring copy of the group.  The compiler waits for its own
-      // loads with vmcnt(0) where they are first used; left to itself it places that use (and the wait) behind the
-      // copy request of the first stage, and the wait then also covers the copies that were requested a moment ago.
-#pragma unroll
-      for (int s = 0; s < NS8; ++s) {
-        asm volatile("" : "+v"(Bhi[s]));
-        if constexpr (!HIONLY) asm volatile("" : "+v"(Blo[s]));
-      }
-#pragma unroll
-      for (int st = 0; st < R; ++st) {
-        {  // the stage two ahead in the stream: always issued (past the end: the last entry again)
-          constexpr int RR = R;
-          const int fst = (st + 2 < RR) ? st + 2 : st + 2 - RR;
-          int fg = g, frl = rl;
-          if (st + 2 >= RR) {
-            fg = g + 1;
-            if (fg == HKV) {
-              fg = 0;
-              frl = rl + 1;
-            }
-          }
-          const int fslot = mod3(slot0 + st + 2);
-          fetch(frl, fg, fst, ring_k(fslot), ring_i(fslot));
-        }
-        const int cslot = mod3(slot0 + st);
-        const unsigned char* kcur = ring_k(cslot);
-        const float* icur = a.inv_norm ? ring_i(cslot) : ones;
-#pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-          const unsigned char* kc = kcur + sub * SUB_BYTES;
-          bf16x8_t av[NS8];
-#pragma unroll
-          for (int s = 0; s < NS8; ++s)
-            av[s] = as_bf16x8(*reinterpret_cast<const uint4*>(
-                &kc[(c >> 4) * (TILE_ELEMS * 2) + ((2 * s + h) * 16 + (c & 15)) * 16]));
-          f32x16_t acc;
-#pragma unroll
-          for (int i = 0; i < 16; ++i) acc[i] = 0.f;
-#pragma unroll
-          for (int s = 0; s < NS8; ++s) {
-            acc = mfma32(av[s], Bhi[s], acc);
-            if constexpr (!HIONLY) acc = mfma32(av[s], Blo[s], acc);
-          }
-          const float* ic = a.inv_norm ? icur + 32 * sub : ones;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            const float4 v = *reinterpret_cast<const float4*>(&ic[8 * j + 4 * h]);
-            tot[2 * st + sub][4 * j] += acc[4 * j] * v.x;
-            tot[2 * st + sub][4 * j + 1] += acc[4 * j + 1] * v.y;
-            tot[2 * st + sub][4 * j + 2] += acc[4 * j + 2] * v.z;
-            tot[2 * st + sub][4 * j + 3] += acc[4 * j + 3] * v.w;
-          }
-        }
-        wait_oldest_copy();
-        __syncthreads();
-      }
-      if constexpr (R != 3) slot0 = mod3(slot0 + R);
-    }
-    // ---- the range's totals are complete: head mean, document max, per-lane lists ----------------------
-#pragma unroll
-    for (int t = 0; t < 2 * R; ++t) {
-      const long long sub_tile = (rg * R + t / 2) * 2 + (t & 1);  // 32 keys
-      auto push = [&](float sc, int doc) __attribute__((always_inline)) {
-        const bool ok = doc < a.N && sc > lsc[KL - 1];
-        if (__any(ok)) {
-#pragma unroll
-          for (int q = kPend - 1; q > 0; --q) {
-            psc[q] = ok ? psc[q - 1] : psc[q];
-            pdoc[q] = ok ? pdoc[q - 1] : pdoc[q];
-          }
-          psc[0] = ok ? sc : psc[0];
-          pdoc[0] = ok ? doc : pdoc[0];
-          pcnt += ok ? 1 : 0;
-          if (__any(pcnt == kPend)) flush();
-        }
-      };
-      float m4[4];  // max over the lane's four rows 8j + 4h .. + 3, head mean applied
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        m4[j] = fmaxf(fmaxf(tot[t][4 * j], tot[t][4 * j + 1]), fmaxf(tot[t][4 * j + 2], tot[t][4 * j + 3])) * inv_groups;
-      if (a.C == 8) {
-        const int doc0 = (int)sub_tile * 4 + 2 * h;
-        push(max_across_halves_pair(m4[0], m4[2]), doc0);
-        push(max_across_halves_pair(m4[1], m4[3]), doc0 + 1);
-      } else if (a.C == 4) {
-#pragma unroll
-        for (int j = 0; j < 4; ++j) push(m4[j], (int)sub_tile * 8 + 2 * j + h);
-      } else {  // C == 16
-        push(max_across_halves_pair(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3])), (int)sub_tile * 2 + h);
-      }
-    }
-  }
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  flush();
-  if constexpr (HIONLY) {
-    if (tok < a.BM) {
-      unsigned long long* dst = a.ws + (((long long)tok * a.n_splits + ks) * 2 + h) * KL;
-#pragma unroll
-      for (int p = 0; p < KL; ++p) dst[p] = (ldoc[p] >= 0) ? make_key(lsc[p], (uint32_t)ldoc[p]) : 0ull;
-    }
-    return;
-  }
-#pragma unroll
-  for (int p = 0; p < KL; ++p)
-    mrg[wave * 32 + c][h * KL + p] = (ldoc[p] >= 0) ? make_key(lsc[p], (uint32_t)ldoc[p]) : 0ull;
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-  {
-    const unsigned long long* both = mrg[wave * 32 + c];
-#pragma unroll
-    for (int p = 0; p < KL; ++p) {
-      const unsigned long long key = both[h * KL + p];
-      int rank = p;
-#pragma unroll
-      for (int o = 0; o < KL; ++o) rank += (both[(1 - h) * KL + o] > key) ? 1 : 0;
-      if (tok < a.BM && rank < a.k) {
-        unsigned long long* dst = a.ws + ((long long)tok * a.n_splits + ks) * a.k;
-        dst[rank] = key;
-      }
-    }
-  }
-}
-
 // ---- one-pass filter: candidates, exact scores ----------------------------------------------------------
 // One wave per (token, KV group).  Input: the 2 * n_splits per-lane lists of the one-pass product (sorted, KL
 // entries each, zero = empty), whose scores s~ differ from the exact scores s by at most eps.  Let t~ be the k-th
@@ -803,22 +514,17 @@ __global__ __launch_bounds__(256) void score_filter_select_kernel(const unsigned
                                                                   float* __restrict__ out_score,
                                                                   unsigned long long* __restrict__ out_key, int BM,
                                                                   int Hkv, int n_splits, int KL, int k,
-                                                                  int tokens_per_wg, int n_qblocks, long long tiles,
-                                                                  int all_heads) {
+                                                                  int tokens_per_wg, int n_qblocks, long long tiles) {
   constexpr int PER = kFilterMaxEntries / 64;
   constexpr int D = 128, C = 8;
   __shared__ int32_t cand_s[4][kFilterMaxCand];
   __shared__ unsigned long long keys_s[4][kFilterMaxCand];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  // one selection per (token, KV group), or (head mean over every head) per token: then the score of a chunk is the
-  // mean over the groups of the groups' scores, and the bound the mean of the groups' bounds
-  const int S = all_heads ? 1 : Hkv;    // selections per token
-  const int GS = all_heads ? Hkv : 1;   // groups per selection
   const long long pair = (long long)blockIdx.x * 4 + wave;
-  if (pair >= (long long)BM * S) return;  // wave-uniform; no workgroup barrier below
-  const int g = (int)(pair % S);
-  const int tok = (int)(pair / S);
+  if (pair >= (long long)BM * Hkv) return;  // wave-uniform; no workgroup barrier below
+  const int g = (int)(pair % Hkv);
+  const int tok = (int)(pair / Hkv);
   int32_t* cand = cand_s[wave];
   unsigned long long* keys = keys_s[wave];
 
@@ -843,10 +549,7 @@ __global__ __launch_bounds__(256) void score_filter_select_kernel(const unsigned
     if (ge >= k) prefix = cnd;  // wave-uniform
   }
   // fewer than k entries in all (prefix == 0): every entry is a candidate
-  float e_sel = 0.f;
-  for (int gg = 0; gg < GS; ++gg) e_sel += eps[(long long)tok * Hkv + g + gg];
-  e_sel /= (float)GS;
-  const float band = prefix ? unorderable(prefix) - 2.0f * e_sel : -INFINITY;
+  const float band = prefix ? unorderable(prefix) - 2.0f * eps[(long long)tok * Hkv + g] : -INFINITY;
   int total = 0;
   bool overflow = false;
 #pragma unroll
@@ -862,61 +565,51 @@ __global__ __launch_bounds__(256) void score_filter_select_kernel(const unsigned
     }
   }
   overflow = __any(overflow) || total > kFilterMaxCand;
-  if (lane == 0 && overflow) flags[g * n_qblocks + tok / tokens_per_wg] = 1;  // (all heads: g = 0)
+  if (lane == 0 && overflow) flags[g * n_qblocks + tok / tokens_per_wg] = 1;
   const int n = total < kFilterMaxCand ? total : kFilterMaxCand;
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
 
   // ---- exact scores ------------------------------------------------------------------------------------
   const int ch = lane >> 3, part = lane & 7;  // chunk of the document, 16-dim part of the key
-  const float inv_gs = 1.0f / (float)GS;
+  float q[16];
+  {
+    const float4* qs = reinterpret_cast<const float4*>(qf + ((long long)tok * Hkv + g) * D + 16 * part);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float4 v = qs[i];
+      q[4 * i] = v.x; q[4 * i + 1] = v.y; q[4 * i + 2] = v.z; q[4 * i + 3] = v.w;
+    }
+  }
+  const uint16_t* KRg = KR + (long long)g * tiles * (16 * D);
+  const float* ing = inv_norm + (long long)g * tiles * 16;
   for (int j0 = 0; j0 < n; j0 += 4) {  // wave-uniform; four candidates at a time, all their loads in flight together
     long long doc[4];
-    float tot[4] = {0.f, 0.f, 0.f, 0.f};  // the chunk's score, summed over the groups of the selection
+    uint4 a0[4], a1[4];
+    float kinv[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) doc[u] = cand[j0 + u < n ? j0 + u : n - 1];  // past the end: the last one again
-    for (int gg = 0; gg < GS; ++gg) {
-      const int gk = g + gg;  // KV group whose keys and folded query are multiplied
-      float q[16];
-      {
-        const float4* qs = reinterpret_cast<const float4*>(qf + ((long long)tok * Hkv + gk) * D + 16 * part);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float4 v = qs[i];
-          q[4 * i] = v.x; q[4 * i + 1] = v.y; q[4 * i + 2] = v.z; q[4 * i + 3] = v.w;
-        }
-      }
-      const uint16_t* KRg = KR + (long long)gk * tiles * (16 * D);
-      const float* ing = inv_norm + (long long)gk * tiles * 16;
-      uint4 a0[4], a1[4];
-      float kinv[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const long long key = doc[u] * C + ch;       // routing key of this lane's chunk
-        const long long tile = key >> 4;
-        const int slot = (int)(key & 15);
-        // tile layout [d / 8][16 keys][8 dims]: dims 16 part .. + 15 are pieces 2 part and 2 part + 1 of the key
-        const uint16_t* kp = KRg + tile * (16 * D) + (2 * part * 16 + slot) * 8;
-        a0[u] = *reinterpret_cast<const uint4*>(kp);
-        a1[u] = *reinterpret_cast<const uint4*>(kp + 16 * 8);
-        kinv[u] = ing[key];
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const uint32_t w[8] = {a0[u].x, a0[u].y, a0[u].z, a0[u].w, a1[u].x, a1[u].y, a1[u].z, a1[u].w};
-        float acc = 0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          acc = fmaf(q[2 * i], bf16_lo(w[i]), acc);
-          acc = fmaf(q[2 * i + 1], bf16_hi(w[i]), acc);
-        }
-        acc = gsum<8>(acc);                          // the chunk's dot product, in its eight lanes
-        tot[u] += acc * kinv[u];
-      }
+    for (int u = 0; u < 4; ++u) {
+      doc[u] = cand[j0 + u < n ? j0 + u : n - 1];  // past the end: the last one again
+      const long long key = doc[u] * C + ch;       // routing key of this lane's chunk
+      const long long tile = key >> 4;
+      const int slot = (int)(key & 15);
+      // tile layout [d / 8][16 keys][8 dims]: dims 16 part .. + 15 are pieces 2 part and 2 part + 1 of the key
+      const uint16_t* kp = KRg + tile * (16 * D) + (2 * part * 16 + slot) * 8;
+      a0[u] = *reinterpret_cast<const uint4*>(kp);
+      a1[u] = *reinterpret_cast<const uint4*>(kp + 16 * 8);
+      kinv[u] = ing[key];
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      float sc = tot[u] * inv_gs;
+      const uint32_t w[8] = {a0[u].x, a0[u].y, a0[u].z, a0[u].w, a1[u].x, a1[u].y, a1[u].z, a1[u].w};
+      float acc = 0.f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        acc = fmaf(q[2 * i], bf16_lo(w[i]), acc);
+        acc = fmaf(q[2 * i + 1], bf16_hi(w[i]), acc);
+      }
+      acc = gsum<8>(acc);                            // the chunk's dot product, in its eight lanes
+      float sc = acc * kinv[u];
       sc = fmaxf(sc, __shfl_xor(sc, 8, 64));         // document max over the eight chunks
       sc = fmaxf(sc, __shfl_xor(sc, 16, 64));
       sc = fmaxf(sc, __shfl_xor(sc, 32, 64));
@@ -925,7 +618,7 @@ __global__ __launch_bounds__(256) void score_filter_select_kernel(const unsigned
   }
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
   __builtin_amdgcn_wave_barrier();
-  const long long o_base = ((long long)tok * S + g) * k;
+  const long long o_base = ((long long)tok * Hkv + g) * k;
   if (lane < n) {
     const unsigned long long mine = keys[lane];
     int rank = 0;
@@ -957,38 +650,6 @@ bool gemm_path_applies(const Dims& dm, int BM, int k) {
 
 GemmPlan plan_score_gemm(const Dims& dm, int BM, int k) {
   GemmPlan p;
-  p.all_heads = (dm.scope_all && dm.Hkv > 1) ? 1 : 0;
-  if (p.all_heads) {
-    // one workgroup per (128 tokens, range of key stages); the per-token lists are [BM][n_splits][k]
-    p.n_qblocks = (BM + 127) / 128;
-    const long long n_stage = ((dm.tiles + 1) / 2 + 1) / 2;
-    const int R = all_range(k <= 8 ? 8 : 16);
-    const long long n_range = (n_stage + R - 1) / R;
-    long long want = (2 * 256) / (long long)p.n_qblocks;
-    if (want < 1) want = 1;
-    long long by_len = (n_range + 3) / 4;                            // at least 4 ranges per split
-    long long ns = want < by_len ? want : by_len;
-    if (ns < 1) ns = 1;
-    if (ns > 64) ns = 64;
-    p.stages_per_split = (int)((n_range + ns - 1) / ns);             // RANGES per split on this path
-    p.n_splits = (int)((n_range + p.stages_per_split - 1) / p.stages_per_split);
-    p.off_lists = round_up256((size_t)BM * dm.Hkv * dm.d * sizeof(float));
-    p.ws_bytes = p.off_lists + round_up256((size_t)BM * p.n_splits * k * sizeof(unsigned long long));
-    p.list_len = (k <= 8) ? 8 : 16;
-    p.tokens_per_wg = 128;
-    p.filter = (dm.cos && dm.d == 128 && dm.C == 8 && 2 * p.n_splits * p.list_len <= kFilterMaxEntries) ? 1 : 0;
-    p.off_eps = p.off_flags = p.off_flists = 0;
-    if (p.filter) {  // as below, with one selection per token
-      p.off_flists = p.off_lists;
-      size_t end = p.off_flists + round_up256((size_t)BM * p.n_splits * 2 * p.list_len * sizeof(unsigned long long));
-      p.off_eps = end;
-      end += round_up256((size_t)BM * dm.Hkv * sizeof(float));
-      p.off_flags = end;
-      end += round_up256((size_t)p.n_qblocks * sizeof(int));
-      p.ws_bytes = end;
-    }
-    return p;
-  }
   const int tokens_per_wg = (k <= 8) ? 256 : 128;
   p.n_qblocks = (BM + tokens_per_wg - 1) / tokens_per_wg;
   const long long n_stage = ((dm.tiles + 1) / 2 + 1) / 2;           // stages of 64 keys
@@ -1022,21 +683,27 @@ GemmPlan plan_score_gemm(const Dims& dm, int BM, int k) {
   return p;
 }
 
+int launch_fold_queries(const Dims& dm, const void* q_route, int BM, float* qf, float* eps, int* flags, int n_flags,
+                        uint4* qop, int n_rt, int pair, hipStream_t st) {
+  if (dm.d == 128)
+    hipLaunchKernelGGL(fold_queries_kernel<128>, dim3((unsigned)(BM * dm.Hkv)), dim3(64), 0, st,
+                       (const uint16_t*)q_route, qf, dm.Hq, dm.Hkv, dm.r, dm.cos, eps, flags, n_flags, qop, n_rt, pair);
+  else
+    hipLaunchKernelGGL(fold_queries_kernel<64>, dim3((unsigned)(BM * dm.Hkv)), dim3(64), 0, st,
+                       (const uint16_t*)q_route, qf, dm.Hq, dm.Hkv, dm.r, dm.cos, eps, flags, n_flags, qop, n_rt, pair);
+  return hipGetLastError() == hipSuccess ? MSA_OK : MSA_ERR_HIP;
+}
+
 int launch_score_gemm_scan(const Dims& dm, const GemmPlan& pl, const void* q_route, int BM, const void* KR,
                            const float* inv_norm, int k, void* ws, hipStream_t st, int32_t* out_idx,
                            float* out_score, unsigned long long* out_key, const int** gate_flags) {
   float* qf = (float*)ws;
   float* eps = pl.filter ? (float*)((char*)ws + pl.off_eps) : nullptr;
   int* flags = pl.filter ? (int*)((char*)ws + pl.off_flags) : nullptr;
-  const int n_flags = pl.filter ? (pl.all_heads ? 1 : dm.Hkv) * pl.n_qblocks : 0;
+  const int n_flags = pl.filter ? dm.Hkv * pl.n_qblocks : 0;
   *gate_flags = flags;
-  if (dm.d == 128)
-    hipLaunchKernelGGL(fold_queries_kernel<128>, dim3((unsigned)(BM * dm.Hkv)), dim3(64), 0, st,
-                       (const uint16_t*)q_route, qf, dm.Hq, dm.Hkv, dm.r, dm.cos, eps, flags, n_flags);
-  else
-    hipLaunchKernelGGL(fold_queries_kernel<64>, dim3((unsigned)(BM * dm.Hkv)), dim3(64), 0, st,
-                       (const uint16_t*)q_route, qf, dm.Hq, dm.Hkv, dm.r, dm.cos, eps, flags, n_flags);
-  if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
+  const int rf = launch_fold_queries(dm, q_route, BM, qf, eps, flags, n_flags, nullptr, 0, 0, st);
+  if (rf != MSA_OK) return rf;
   GemmArgs a;
   a.flags = nullptr;
   a.qf = qf;
@@ -1052,46 +719,6 @@ int launch_score_gemm_scan(const Dims& dm, const GemmPlan& pl, const void* q_rou
   a.n_qblocks = pl.n_qblocks;
   a.n_splits = pl.n_splits;
   a.stages_per_split = pl.stages_per_split;
-  if (pl.all_heads) {
-    const unsigned nb = (unsigned)(pl.n_qblocks * pl.n_splits);
-#define MSA_GEMM_ALL(DD, HH, ONE) \
-  do { \
-    if (k <= 8) hipLaunchKernelGGL((score_gemm_all_kernel<DD, 8, HH, ONE>), dim3(nb), dim3(256), 0, st, a); \
-    else hipLaunchKernelGGL((score_gemm_all_kernel<DD, 16, HH, ONE>), dim3(nb), dim3(256), 0, st, a); \
-  } while (0)
-#define MSA_GEMM_ALL128(ONE) \
-  do { \
-    if (dm.Hkv == 2) MSA_GEMM_ALL(128, 2, ONE); else if (dm.Hkv == 4) MSA_GEMM_ALL(128, 4, ONE); \
-    else MSA_GEMM_ALL(128, 8, ONE); \
-  } while (0)
-    if (pl.filter) {  // d = 128: one-pass product -> candidates -> exact scores -> two-pass kernel where flagged
-      a.ws = (unsigned long long*)((char*)ws + pl.off_flists);
-      profile_mark(dm, false, st);
-      MSA_GEMM_ALL128(true);
-      profile_mark(dm, true, st);
-      if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
-      hipLaunchKernelGGL(score_filter_select_kernel, dim3((unsigned)((BM + 3) / 4)), dim3(256), 0, st,
-                         (const unsigned long long*)a.ws, (const float*)eps, (const float*)qf, (const uint16_t*)KR,
-                         inv_norm, flags, out_idx, out_score, out_key, BM, dm.Hkv, pl.n_splits, pl.list_len, k,
-                         pl.tokens_per_wg, pl.n_qblocks, dm.tiles, 1);
-      if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
-      a.ws = (unsigned long long*)((char*)ws + pl.off_lists);
-      a.flags = flags;
-      MSA_GEMM_ALL128(false);
-      return hipGetLastError() == hipSuccess ? MSA_OK : MSA_ERR_HIP;
-    }
-    profile_mark(dm, false, st);
-    if (dm.d == 128) {
-      MSA_GEMM_ALL128(false);
-    } else {
-      if (dm.Hkv == 2) MSA_GEMM_ALL(64, 2, false); else if (dm.Hkv == 4) MSA_GEMM_ALL(64, 4, false);
-      else MSA_GEMM_ALL(64, 8, false);
-    }
-#undef MSA_GEMM_ALL128
-#undef MSA_GEMM_ALL
-    profile_mark(dm, true, st);
-    return hipGetLastError() == hipSuccess ? MSA_OK : MSA_ERR_HIP;
-  }
   const unsigned blocks = (unsigned)(dm.Hkv * pl.n_qblocks * pl.n_splits);
   if (pl.filter) {
     // one-pass product -> candidates -> exact scores; then the two-pass kernel for the flagged token blocks only
@@ -1104,7 +731,7 @@ int launch_score_gemm_scan(const Dims& dm, const GemmPlan& pl, const void* q_rou
     hipLaunchKernelGGL(score_filter_select_kernel, dim3((unsigned)((BM * dm.Hkv + 3) / 4)), dim3(256), 0, st,
                        (const unsigned long long*)a.ws, (const float*)eps, (const float*)qf, (const uint16_t*)KR,
                        inv_norm, flags, out_idx, out_score, out_key, BM, dm.Hkv, pl.n_splits, pl.list_len, k,
-                       pl.tokens_per_wg, pl.n_qblocks, dm.tiles, 0);
+                       pl.tokens_per_wg, pl.n_qblocks, dm.tiles);
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
     a.ws = (unsigned long long*)((char*)ws + pl.off_lists);
     a.flags = flags;

@@ -1,0 +1,613 @@
+// msa_score_topk with the head mean over EVERY head (select_scope = ALL, Eq. 2 of the paper as printed) for more query
+// tokens than one pass of the all-heads scan takes (B*M > 32): the chunk score is the mean over the KV groups g of
+//     inv_norm_g(key) * (qf_g(token) . key_g),
+// qf_g the folded routing query of the group.  Every group has its own keys and reciprocal norms, so the groups'
+// products cannot share an accumulator: each is scaled and added to a running total, eight groups of matrix work per
+// score.  With one selection per token the scores themselves are few (4 B per token and document against
+// 2 * Hkv * C * d flops), so they go to a score matrix and the selection is a kernel of its own.
+//
+//   fold_queries_kernel   folds the heads of every (token, group) into one fp32 query, and stores its bf16 hi part (or
+//                         hi and lo parts) as MFMA operands.
+//   score_wide_kernel     a workgroup holds the operands of 64 operand rows and all groups in LDS (128 KiB at Hkv = 8,
+//                         d = 128) for its whole life; eight waves stream units of 64 keys straight into registers
+//                         (the index is stored in operand order), multiply them with all 64 rows, group after group,
+//                         and write the document maxima.  The waves never synchronise after the operands are in.
+//   score_wide_select_kernel  per token: the candidates of the matrix row and their exact scores.
+//
+// One pass (cosine): only the hi parts are multiplied, 64 tokens per workgroup.  The matrix then holds scores within
+// the bound eps that fold_queries_kernel writes; every document within 2 eps of the k-th best is scored again in fp32
+// from the folded fp32 query.  The dot product has no such bound (keys of any length): there hi and lo parts are
+// neighbouring rows (32 tokens per workgroup), and the matrix holds the scores to ~16 bits of the query, as the scan's.
+//
+// Bound: the matrix cores, then LDS (every operand read feeds four products: 64 of 128 B per cycle and CU at the full
+// matrix rate) and the L2 (a key is read once per 64 rows: 64 B per cycle and CU).  The workgroups of all token blocks
+// that read the same keys sit on one XCD and walk them together, so the index comes from memory once per XCD-resident
+// group of blocks. Measured: 150 tokens, k = 32, 97656 documents: kernel 3 x 142 us (three
+// segments; 192 padded rows, 0.72 PFLOP/s), selection 48 + 24 + 24 us; the call 4.87 ms as 19 passes of the scan -> 0.55
+// ms.  2048 tokens, 32768 documents, k = 8: 2.4 ms (a GEMM that reloaded its operands at every group switch) -> 1.84 ms.
+#include "msa_device.h"
+#include "msa_host.h"
+
+namespace msa {
+
+constexpr int kWideWaves = 8;
+constexpr int kWideRows = 64;    // operand rows per workgroup: four tiles of 16
+constexpr int kWideTiles = 4;    // 16-key tiles per unit
+constexpr int kWideGroups = 256; // workgroups: one per CU (LDS)
+constexpr int kWidePass = 1024;  // query tokens per pass: bounds the workspace
+constexpr size_t kWideMat = (size_t)20 << 20;  // bytes of the score matrix: bounds the workspace, stays in cache
+
+struct WideArgs {
+  const uint4* qop;        // [Hkv][n_rt][d/32][64] operand tiles of 16 rows
+  const uint16_t* KR;
+  const float* inv_norm;   // null: dot product
+  float* mat;              // [tokens of the pass][mat_stride]
+  long long mat_stride;
+  int n_rt;                // operand tiles in all (a multiple of 4)
+  int n_tb;                // token blocks (of 64 rows)
+  int n_streams;           // key streams: n_tb * n_streams workgroups
+  int nq;                  // tokens of the pass
+  int C;
+  long long tiles;         // tiles per head in the index
+  long long tile0;         // first tile of the segment
+  int seg_tiles, seg_docs; // tiles and documents of the segment
+};
+
+template <int D, int HKV, bool PAIR>
+__global__ __launch_bounds__(64 * kWideWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void score_wide_kernel(WideArgs a) {
+  constexpr int NS = D / 32;
+  constexpr int NT = kWideRows / 16;
+  constexpr int KT = kWideTiles;
+  constexpr int TILE_ELEMS = 16 * D;
+  constexpr int NOP = HKV * NT * NS;  // KiB of operands
+  static_assert(NOP % kWideWaves == 0 && HKV % 2 == 0, "whole copies per wave; ring of two entries");
+
+  __shared__ uint4 Aop[HKV][NT][NS][64];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // Workgroups go to the eight XCDs in turn (blockIdx % 8); each XCD takes a run of (stream, token block) pairs, so the
+  // token blocks of a key stream share an XCD.
+  const int total = a.n_tb * a.n_streams;
+  const int vb = (blockIdx.x & 7) * ((total + 7) / 8) + (blockIdx.x >> 3);
+  if (vb >= total) return;  // the grid is rounded up to whole XCDs
+  const int tb = vb % a.n_tb;
+  const int stream = vb / a.n_tb;
+
+  // ---- operands: global -> LDS, requested first; the keys requested next stay in flight across their wait ---------
+  const uint32_t op_lds = lds_addr_of(&Aop[0][0][0][0]);
+#pragma unroll
+  for (int i = 0; i < NOP / kWideWaves; ++i) {
+    const int e = i * kWideWaves + wave;  // (group, tile, slice)
+    const int g = e / (NT * NS), rest = e % (NT * NS);
+    const uint4* src = a.qop + (((long long)g * a.n_rt + tb * NT) * NS + rest) * 64;
+    copy16_to_lds_async_at(src, lane * 16, op_lds + e * 1024);
+  }
+
+  const int W = a.n_streams * kWideWaves;
+  const int w = stream * kWideWaves + wave;
+  const int units = (a.seg_tiles + KT - 1) / KT;
+  // Addresses: a base that is the same in every lane (scalar registers) plus the lane's own 32-bit offset, which is
+  // worked out from an opaque copy of the lane number every time: known ahead of the loop it would be added to the bases
+  // there, and the sums would need registers the loop does not have.
+  typedef const __attribute__((address_space(1))) char* gptr_t;
+  const gptr_t kr0 = (gptr_t)a.KR + a.tile0 * (TILE_ELEMS * 2);
+  const gptr_t in0 = (gptr_t)a.inv_norm + a.tile0 * 64;  // (PAIR: not read)
+  const int last_tile = a.seg_tiles - 1;
+
+  u32x4_t buf[2][KT][NS];
+  float binv[2][KT];
+  // unit u, group g into ring slot: always issued, past the end the last tile again
+  auto request = [&](int u, int g, u32x4_t (&b)[KT][NS], float (&bi)[KT]) __attribute__((always_inline)) {
+    uint32_t ln = lane;
+    asm volatile("" : "+v"(ln));
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      int t = u * KT + kt;
+      t = t < last_tile ? t : last_tile;
+      const long long at = g * a.tiles + t;
+      const gptr_t p = kr0 + at * (TILE_ELEMS * 2);
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+        b[kt][s] = *(const __attribute__((address_space(1))) u32x4_t*)(p + s * 1024 + (size_t)(ln * 16));
+      if constexpr (!PAIR) bi[kt] = *(const __attribute__((address_space(1))) float*)(in0 + at * 64 + (size_t)((ln & 15) * 4));
+    }
+  };
+  request(w, 0, buf[0], binv[0]);
+  request(w, 1, buf[1], binv[1]);
+  wait_copies_but<2 * KT * (NS + (PAIR ? 0 : 1))>();  // the operands are older than the keys
+  lds_barrier();
+
+  const int dpt = 16 / a.C;
+  const float inv_heads = 1.0f / (float)HKV;
+  // The operand reads run two ahead of the products (a ring of four slices that goes on from group to group): four
+  // products of 16 cycles each per read, so a read has about 128 cycles to land.  The order is the one written here:
+  // left to itself the scheduler reads every slice right before its products.
+  constexpr int NA = NT * NS;  // slices per group
+  bf16x8_t ar[4];
+  const uint4* const A0 = &Aop[0][0][0][0] + lane;
+  ar[0] = as_bf16x8(A0[0]);
+  ar[1] = as_bf16x8(A0[64]);
+  for (int u = w; u < units; u += W) {
+    float tot[NT][KT][4];
+#pragma unroll
+    for (int g = 0; g < HKV; ++g) {
+      const int slot = g & 1;
+      // the entry is awaited HERE: its uses pass through volatile asm, so that no use of a later entry (and the wait
+      // for it) moves up ahead of the requests in between
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) asm volatile("" : "+v"(buf[slot][kt][s]));
+        if constexpr (!PAIR) asm volatile("" : "+v"(binv[slot][kt]));
+      }
+#pragma unroll
+      for (int tq = 0; tq < NT; ++tq) {
+        f32x4_t acc[KT];
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+          const int i = tq * NS + s;
+          static_assert(NA % 4 == 0, "ring slots must be compile-time");
+          ar[(i + 2) & 3] = as_bf16x8(A0[((g * NA + i + 2) % (HKV * NA)) * 64]);
+          __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+          for (int kt = 0; kt < KT; ++kt)
+            acc[kt] = mfma16(ar[i & 3], __builtin_bit_cast(bf16x8_t, buf[slot][kt][s]),
+                             s == 0 ? f32x4_t{0.f, 0.f, 0.f, 0.f} : acc[kt]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            if constexpr (PAIR)
+              tot[tq][kt][i] = g == 0 ? acc[kt][i] : tot[tq][kt][i] + acc[kt][i];
+            else
+              tot[tq][kt][i] = g == 0 ? acc[kt][i] * binv[slot][kt] : fmaf(acc[kt][i], binv[slot][kt], tot[tq][kt][i]);
+          }
+        // the totals are formed HERE (deferred, the accumulators of all tiles would be live together)
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt)
+          asm volatile("" : "+v"(tot[tq][kt][0]), "+v"(tot[tq][kt][1]), "+v"(tot[tq][kt][2]), "+v"(tot[tq][kt][3]));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      asm volatile("" ::: "memory");  // every product of the entry is issued before its slot is requested again
+      request(g + 2 < HKV ? u : u + W, (g + 2) % HKV, buf[slot], binv[slot]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+
+    // ---- head mean, document maxima (every lane of a document's C lanes gets it), store ---------------------------
+    constexpr int NR = PAIR ? 2 : 4;  // tokens per lane and tile
+    int le = lane;  // (opaque, as above)
+    asm volatile("" : "+v"(le));
+    const int rr = le >> 4, n = le & 15;
+#pragma unroll
+    for (int tq = 0; tq < NT; ++tq) {
+      float m[NR][KT];
+#pragma unroll
+      for (int i = 0; i < NR; ++i)
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) m[i][kt] = PAIR ? tot[tq][kt][2 * i] + tot[tq][kt][2 * i + 1] : tot[tq][kt][i];
+      // one instruction per maximum (fmaxf of an exchanged value takes three: the exchange, and a canonicalising
+      // maximum first); the exchange reads its operand two wait states after the write at the earliest
+#define MSA_LEVEL(CTRL) \
+  do { \
+    for (int i = 0; i < NR; ++i) \
+      asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 " CTRL " row_mask:0xf bank_mask:0xf\n\t" \
+          "v_max_f32_dpp %1, %1, %1 " CTRL " row_mask:0xf bank_mask:0xf\n\t" \
+          "v_max_f32_dpp %2, %2, %2 " CTRL " row_mask:0xf bank_mask:0xf\n\t" \
+          "v_max_f32_dpp %3, %3, %3 " CTRL " row_mask:0xf bank_mask:0xf" \
+          : "+v"(m[i][0]), "+v"(m[i][1]), "+v"(m[i][2]), "+v"(m[i][3])); \
+  } while (0)
+      static_assert(KT == 4, "four values per statement");
+      if (a.C >= 2) MSA_LEVEL("quad_perm:[1,0,3,2]");
+      if (a.C >= 4) MSA_LEVEL("quad_perm:[2,3,0,1]");
+      if (a.C >= 8) MSA_LEVEL("row_half_mirror");
+      if (a.C >= 16) MSA_LEVEL("row_mirror");
+#undef MSA_LEVEL
+      // The C lanes of a document take the unit's tiles in turn, up to four at once: one store then writes up to
+      // 4 dpt documents of a token (a run of 32 bytes at C = 8).
+      const int par = a.C < KT ? a.C : KT;   // tiles per store
+      for (int k0 = 0; k0 < KT; k0 += par) {  // wave-uniform
+        const int kt = k0 + (n & (par - 1));
+        const int doc = (u * KT + kt) * dpt + n / a.C;
+        const bool on = (n & (a.C - 1)) < par && doc < a.seg_docs;
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+          const int tok = tb * (kWideRows / (PAIR ? 2 : 1)) + tq * (PAIR ? 8 : 16) + rr * NR + i;
+          // (through empty asm: as selects between elements of the array they would become an indexed load of it)
+          float c0 = m[i][0], c1 = m[i][1], c2 = m[i][2], c3 = m[i][3];
+          asm volatile("" : "+v"(c0), "+v"(c1), "+v"(c2), "+v"(c3));
+          const float lo = (kt & 1) ? c1 : c0, hi = (kt & 1) ? c3 : c2;
+          if (on && tok < a.nq) a.mat[tok * a.mat_stride + doc] = fmaxf(((kt & 2) ? hi : lo) * inv_heads, -INFINITY);  // (not a number: last)
+        }
+      }
+    }
+  }
+}
+
+// ---- selection -------------------------------------------------------------------------------------------------
+// One workgroup per token.  Input: the token's matrix row of a segment (scores s~ within eps of the exact scores s;
+// eps = 0: the exact scores), and the k best of the segments before, as sorted keys with exact scores.  Let t~ be the
+// k-th largest s~ of the segment.  k documents have s >= t~ - eps, so a document of the exact k best has
+// s~ >= s - eps >= t~ - 2 eps; and it is none of the k best if s~ + eps is below the k-th best exact score so far.
+//   1. a lower bound theta of t~ as in topk_rows_kernel; the documents with s~ >= theta - 2 eps go to LDS;
+//   2. t~ by rank counting among them; what is left of them after the two conditions are the candidates;
+//   3. the candidates' exact scores: Eq. 2 in fp32 from the folded fp32 query and the bf16 keys, eight lanes per key;
+//   4. the k best of candidates and earlier winners by rank counting on the full key.
+// If more survive than LDS holds (adversarial order), the row is taken in windows of kWideSurv documents: step 3 and 4
+// for those of a window that can still be among the k best.
+constexpr int kWideSel = 512;      // threads
+constexpr int kWideSurv = 2048;
+constexpr int kWideRegs = 64;      // scores a thread keeps in registers (16: short rows)
+
+struct WideSelArgs {
+  const float* mat;
+  long long mat_stride;
+  const float* eps;        // [tokens][Hkv], or null: the matrix holds the exact scores
+  const float* qf;         // [tokens][Hkv][d]
+  const uint16_t* KR;
+  const float* inv_norm;
+  unsigned long long* best;  // [tokens][k] keys of the segments so far
+  int first, last;           // first segment: nothing in best yet; last: the result goes out
+  int32_t* out_idx;
+  float* out_score;
+  unsigned long long* out_key;
+  int Hkv, C, k;
+  int n_docs, doc0;        // documents of the segment, number of the first
+  int tok0;                // token number of the pass's first token
+  long long tiles;
+};
+
+template <int D, int REGS>
+__global__ __launch_bounds__(kWideSel) void score_wide_select_kernel(WideSelArgs a) {
+  constexpr int NW = kWideSel / 64;
+  __shared__ unsigned long long surv[kWideSurv + MSA_MAX_TOPK + 8];
+  __shared__ float qs[8 * D];
+  __shared__ unsigned long long best_s[MSA_MAX_TOPK];
+  __shared__ uint32_t theta_w[NW];
+  __shared__ uint32_t kth_s;
+  __shared__ int n_surv;
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int tok = blockIdx.x;
+  const int k = a.k, N = a.n_docs;
+  const float* row = a.mat + (long long)tok * a.mat_stride;
+  float eps = 0.f;
+  if (a.eps != nullptr) {
+    for (int g = 0; g < a.Hkv; ++g) eps += a.eps[(long long)tok * a.Hkv + g];
+    eps /= (float)a.Hkv;
+    for (int i = tid; i < a.Hkv * D; i += kWideSel) qs[i] = a.qf[(long long)tok * a.Hkv * D + i];
+  }
+  int n_best = 0;  // earlier winners
+  if (!a.first) {
+    n_best = k;
+    if (tid < k) best_s[tid] = a.best[(long long)tok * k + tid];
+  }
+  if (tid == 0) n_surv = 0;
+
+  // exact scores of the documents surv[0 .. ns), in place of their keys; eight lanes per (document, chunk)
+  auto rescore = [&](int ns) {
+    if (a.eps == nullptr) return;
+    const int part = tid & 7;
+    const int per = kWideSel / 8 / a.C;      // documents per round (C <= 16)
+    const int ch = (tid >> 3) & (a.C - 1);
+    const float inv_g = 1.0f / (float)a.Hkv;
+    for (int j0 = 0; j0 < ns; j0 += per) {   // block-uniform
+      const int j = j0 + (tid >> 3) / a.C;
+      const uint32_t doc = key_doc(surv[j < ns ? j : ns - 1]);
+      const long long key = (long long)doc * a.C + ch;
+      const uint16_t* kp = a.KR + (key >> 4) * (16 * D) + (part * (D / 64) * 16 + (int)(key & 15)) * 8;
+      float tot = 0.f;
+      for (int g0 = 0; g0 < a.Hkv; g0 += 4) {  // the loads of four groups in flight (Hkv = 2: the last one again, dropped)
+        uint4 kv[4][D / 64];
+        float inv[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const int g = g0 + u < a.Hkv ? g0 + u : a.Hkv - 1;
+          const uint16_t* p = kp + (long long)g * a.tiles * (16 * D);
+#pragma unroll
+          for (int x = 0; x < D / 64; ++x)   // dims (D/8) part .. + D/8: pieces of 8, 128 elements apart in a tile
+            kv[u][x] = *reinterpret_cast<const uint4*>(p + x * 128);
+          inv[u] = a.inv_norm[(long long)g * a.tiles * 16 + key];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (g0 + u >= a.Hkv) break;  // block-uniform
+          float acc = 0.f;
+#pragma unroll
+          for (int x = 0; x < D / 64; ++x) {
+            const float* q = &qs[(g0 + u) * D + part * (D / 8) + 8 * x];
+            const uint4 w = kv[u][x];
+            acc = fmaf(q[0], bf16_lo(w.x), acc);
+            acc = fmaf(q[1], bf16_hi(w.x), acc);
+            acc = fmaf(q[2], bf16_lo(w.y), acc);
+            acc = fmaf(q[3], bf16_hi(w.y), acc);
+            acc = fmaf(q[4], bf16_lo(w.z), acc);
+            acc = fmaf(q[5], bf16_hi(w.z), acc);
+            acc = fmaf(q[6], bf16_lo(w.w), acc);
+            acc = fmaf(q[7], bf16_hi(w.w), acc);
+          }
+          acc += dpp_f<kDppXor1>(acc);
+          acc += dpp_f<kDppXor2>(acc);
+          acc += dpp_f<kDppHalfMirror>(acc);   // the key's dot product, in its eight lanes
+          tot += acc * inv[u];
+        }
+      }
+      float sc = tot * inv_g;
+      for (int off = 8; off < 8 * a.C && off < 64; off <<= 1) sc = fmaxf(sc, __shfl_xor(sc, off, 64));
+      if (a.C == 16) {  // a document's chunks sit in two waves
+        float* half = reinterpret_cast<float*>(&surv[kWideSurv + MSA_MAX_TOPK]);  // 8 keys = 16 floats: one per half
+        __syncthreads();
+        if (lane == 0) half[tid >> 6] = sc;
+        __syncthreads();
+        sc = fmaxf(sc, half[(tid >> 6) ^ 1]);
+      }
+      __syncthreads();  // every lane has read its document
+      if (part == 0 && ch == 0 && j < ns) surv[j] = make_key(sc, doc);
+    }
+    __syncthreads();
+  };
+  // surv[0 .. ns) and best_s[0 .. n_best): the k best, sorted, into best_s
+  auto merge = [&](int ns) {
+    __syncthreads();
+    if (tid < n_best) surv[ns + tid] = best_s[tid];
+    if (tid < 8) surv[ns + n_best + tid] = 0ull;  // read eight at a time below (zero: greater than no key)
+    __syncthreads();
+    const int all = ns + n_best;
+    for (int i = tid; i < all; i += kWideSel) {
+      const unsigned long long x = surv[i];
+      int rank = 0;
+      for (int j = 0; j < all; j += 8) {
+        unsigned long long y[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) y[u] = surv[j + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) rank += (y[u] > x) ? 1 : 0;
+      }
+      if (rank < k && x != 0ull) best_s[rank] = x;
+    }
+    n_best = all < k ? all : k;  // (documents are distinct, so are their keys)
+    __syncthreads();
+  };
+  // lowest matrix value that can still be among the k best, as the order-preserving image of a score
+  auto floor_of = [&](float t, float width) { return orderable(t - width); };
+
+  // ---- 1. theta ------------------------------------------------------------------------------------------------
+  float v[REGS];
+#pragma unroll
+  for (int u = 0; u < REGS; ++u) {
+    const int i = u * kWideSel + tid;
+    v[u] = (i < N) ? row[i] : -INFINITY;
+  }
+  // the rest of a row longer than the registers hold, eight loads in flight
+  auto rest_of_row = [&](auto use) {
+    for (int i0 = REGS * kWideSel + tid; i0 < N; i0 += 8 * kWideSel) {
+      float x[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) x[u] = (i0 + u * kWideSel < N) ? row[i0 + u * kWideSel] : -INFINITY;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) use(i0 + u * kWideSel, x[u]);
+    }
+  };
+  uint32_t ob = 0u;  // the best score of this lane (0: no document)
+  auto best_of = [&](int i, float x) {
+    const uint32_t o = i < N ? orderable(x) : 0u;
+    ob = o > ob ? o : ob;
+  };
+#pragma unroll
+  for (int u = 0; u < REGS; ++u) best_of(u * kWideSel + tid, v[u]);
+  rest_of_row(best_of);
+  {
+    uint32_t prefix = 0u;
+    for (int bit = 31; bit >= 12; --bit) {
+      const uint32_t cnd = prefix | (1u << bit);
+      if (__popcll(__ballot(ob >= cnd)) >= k) prefix = cnd;  // wave-uniform
+    }
+    if (lane == 0) theta_w[tid >> 6] = prefix;
+  }
+  __syncthreads();
+  uint32_t theta = theta_w[0];
+#pragma unroll
+  for (int i = 1; i < NW; ++i) theta = theta_w[i] > theta ? theta_w[i] : theta;
+  uint32_t lim = theta ? floor_of(unorderable(theta), 2.f * eps) : 0u;
+  if (!a.first) {  // the k-th best so far (0: fewer than k)
+    const unsigned long long kb = best_s[k - 1];
+    const uint32_t l2 = kb ? floor_of(key_score(kb), eps) : 0u;
+    lim = l2 > lim ? l2 : lim;
+  }
+  auto keep = [&](int i, float s) {
+    if (i < N && orderable(s) >= lim) {
+      const int slot = atomicAdd(&n_surv, 1);
+      if (slot < kWideSurv) surv[slot] = make_key(s, (uint32_t)(a.doc0 + i));
+    }
+  };
+#pragma unroll
+  for (int u = 0; u < REGS; ++u) keep(u * kWideSel + tid, v[u]);
+  rest_of_row(keep);
+  __syncthreads();
+  int ns = n_surv;
+  __syncthreads();
+  if (ns <= kWideSurv) {
+    // ---- 2. t~, candidates -----------------------------------------------------------------------------------------
+    if (a.eps != nullptr && ns > k) {
+      if (tid < 8) surv[ns + tid] = 0ull;
+      __syncthreads();
+      unsigned long long mine[kWideSurv / kWideSel];
+#pragma unroll
+      for (int u = 0; u < kWideSurv / kWideSel; ++u) {
+        const int i = u * kWideSel + tid;
+        mine[u] = i < ns ? surv[i] : 0ull;
+        if (u * kWideSel < ns) {  // block-uniform
+          int rank = 0;
+          for (int j = 0; j < ns; j += 8) {
+            unsigned long long y[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) y[q] = surv[j + q];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) rank += (y[q] > mine[u]) ? 1 : 0;
+          }
+          if (i < ns && rank == k - 1) kth_s = (uint32_t)(mine[u] >> 32);
+        }
+      }
+      if (tid == 0) n_surv = 0;
+      __syncthreads();
+      const uint32_t l2 = floor_of(unorderable(kth_s), 2.f * eps);
+      lim = l2 > lim ? l2 : lim;
+#pragma unroll
+      for (int u = 0; u < kWideSurv / kWideSel; ++u)
+        if (mine[u] != 0ull && (uint32_t)(mine[u] >> 32) >= lim) surv[atomicAdd(&n_surv, 1)] = mine[u];
+      __syncthreads();
+      ns = n_surv;
+    }
+    // ---- 3., 4. ------------------------------------------------------------------------------------------------------
+    rescore(ns);
+    merge(ns);
+  } else {
+    for (int w0 = 0; w0 < N; w0 += kWideSurv) {  // block-uniform
+      if (tid == 0) n_surv = 0;
+      const unsigned long long kb = n_best == k ? best_s[k - 1] : 0ull;
+      const uint32_t l2 = kb ? floor_of(key_score(kb), eps) : 0u;
+      __syncthreads();
+      for (int i = w0 + tid; i < w0 + kWideSurv && i < N; i += kWideSel) {
+        const uint32_t o = orderable(row[i]);
+        if (o >= lim && o >= l2) surv[atomicAdd(&n_surv, 1)] = make_key(row[i], (uint32_t)(a.doc0 + i));
+      }
+      __syncthreads();
+      ns = n_surv;
+      __syncthreads();
+      rescore(ns);
+      merge(ns);
+    }
+  }
+  if (tid < k) {
+    const unsigned long long x = tid < n_best ? best_s[tid] : 0ull;
+    const long long o = (long long)(a.tok0 + tok) * k + tid;
+    if (!a.last) {
+      a.best[(long long)tok * k + tid] = x;
+    } else if (a.out_key != nullptr) {
+      a.out_key[o] = x;
+    } else {
+      a.out_idx[o] = x ? (int32_t)key_doc(x) : -1;
+      if (a.out_score != nullptr) a.out_score[o] = x ? key_score(x) : -INFINITY;
+    }
+  }
+}
+
+// ---- host side -----------------------------------------------------------------------------------------------------
+// More tokens than one pass of the all-heads scan takes.
+bool wide_path_applies(const Dims& dm, int BM) { return dm.scope_all && dm.Hkv > 1 && BM > 32; }
+
+WidePlan plan_score_wide(const Dims& dm, int BM, int k) {
+  WidePlan p;
+  p.pair = dm.cos ? 0 : 1;
+  const int n_pass = (BM + kWidePass - 1) / kWidePass;
+  p.pass_tokens = (BM + n_pass - 1) / n_pass;
+  const int per_wg = kWideRows / (p.pair ? 2 : 1);
+  p.n_tb = (p.pass_tokens + per_wg - 1) / per_wg;
+  // segments of whole units (64 documents are whole units for every C), all alike
+  long long seg = (long long)(kWideMat / sizeof(float)) / p.pass_tokens;
+  if (seg < 64) seg = 64;
+  const long long n_seg = (dm.N + seg - 1) / seg;
+  seg = ((dm.N + n_seg - 1) / n_seg + 63) / 64 * 64;
+  p.seg_docs = (int)(seg < dm.N ? seg : dm.N);
+  size_t end = 0;
+  p.off_qf = end;
+  end += round_up256((size_t)p.pass_tokens * dm.Hkv * dm.d * sizeof(float));
+  p.off_qop = end;
+  end += round_up256((size_t)dm.Hkv * p.n_tb * (kWideRows / 16) * (dm.d / 32) * 64 * 16);
+  p.off_eps = end;
+  end += round_up256((size_t)p.pass_tokens * dm.Hkv * sizeof(float));
+  p.off_best = end;
+  end += round_up256((size_t)p.pass_tokens * k * sizeof(unsigned long long));
+  p.off_mat = end;
+  end += round_up256((size_t)p.pass_tokens * p.seg_docs * sizeof(float));
+  p.ws_bytes = end;
+  return p;
+}
+
+int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, int BM, const void* KR,
+                      const float* inv_norm, int k, void* ws, hipStream_t st, int32_t* out_idx, float* out_score,
+                      unsigned long long* out_key) {
+  char* const w = (char*)ws;
+  WideArgs a;
+  a.qop = (const uint4*)(w + pl.off_qop);
+  a.KR = (const uint16_t*)KR;
+  a.inv_norm = dm.cos ? inv_norm : nullptr;
+  a.mat = (float*)(w + pl.off_mat);
+  a.mat_stride = pl.seg_docs;
+  a.C = dm.C;
+  a.tiles = dm.tiles;
+  WideSelArgs s;
+  s.mat = a.mat;
+  s.mat_stride = pl.seg_docs;
+  s.eps = pl.pair ? nullptr : (const float*)(w + pl.off_eps);
+  s.qf = (const float*)(w + pl.off_qf);
+  s.KR = a.KR;
+  s.inv_norm = a.inv_norm;
+  s.best = (unsigned long long*)(w + pl.off_best);
+  s.out_idx = out_idx;
+  s.out_score = out_score;
+  s.out_key = out_key;
+  s.Hkv = dm.Hkv;
+  s.C = dm.C;
+  s.k = k;
+  s.tiles = dm.tiles;
+  const int per_wg = kWideRows / (pl.pair ? 2 : 1);
+  profile_mark(dm, false, st);
+  for (int tok0 = 0; tok0 < BM; tok0 += pl.pass_tokens) {
+    const int nq = BM - tok0 < pl.pass_tokens ? BM - tok0 : pl.pass_tokens;
+    a.nq = nq;
+    a.n_rt = pl.n_tb * (kWideRows / 16);
+    a.n_tb = (nq + per_wg - 1) / per_wg;
+    const int rc = launch_fold_queries(dm, (const uint16_t*)q_route + (size_t)tok0 * dm.Hq * dm.d, nq,
+                                       (float*)(w + pl.off_qf), pl.pair ? nullptr : (float*)(w + pl.off_eps), nullptr, 0,
+                                       (uint4*)(w + pl.off_qop), a.n_rt, pl.pair, st);
+    if (rc != MSA_OK) return rc;
+    for (int doc0 = 0; doc0 < dm.N; doc0 += pl.seg_docs) {
+      const int n_docs = dm.N - doc0 < pl.seg_docs ? dm.N - doc0 : pl.seg_docs;
+      a.tile0 = (long long)doc0 * dm.C / 16;  // doc0 is a multiple of 64 (or 0)
+      a.seg_docs = n_docs;
+      a.seg_tiles = (int)(((long long)n_docs * dm.C + 15) / 16);
+      const int units = (a.seg_tiles + kWideTiles - 1) / kWideTiles;
+      int streams = kWideGroups / a.n_tb;
+      if (streams < 1) streams = 1;
+      const int most = (units + kWideWaves - 1) / kWideWaves;
+      if (streams > most) streams = most;
+      a.n_streams = streams;
+      dim3 grid((unsigned)((a.n_tb * streams + 7) / 8 * 8)), block(64 * kWideWaves);
+#define MSA_WIDE(DD, HH) \
+  do { \
+    if (pl.pair) hipLaunchKernelGGL((score_wide_kernel<DD, HH, true>), grid, block, 0, st, a); \
+    else hipLaunchKernelGGL((score_wide_kernel<DD, HH, false>), grid, block, 0, st, a); \
+  } while (0)
+      if (dm.d == 128) {
+        if (dm.Hkv == 2) MSA_WIDE(128, 2); else if (dm.Hkv == 4) MSA_WIDE(128, 4); else MSA_WIDE(128, 8);
+      } else {
+        if (dm.Hkv == 2) MSA_WIDE(64, 2); else if (dm.Hkv == 4) MSA_WIDE(64, 4); else MSA_WIDE(64, 8);
+      }
+#undef MSA_WIDE
+      if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
+      s.first = doc0 == 0;
+      s.last = doc0 + n_docs == dm.N;
+      s.n_docs = n_docs;
+      s.doc0 = doc0;
+      s.tok0 = tok0;
+#define MSA_WIDE_SELECT(DD) \
+  do { \
+    if (n_docs <= 16 * kWideSel) \
+      hipLaunchKernelGGL((score_wide_select_kernel<DD, 16>), dim3((unsigned)nq), dim3(kWideSel), 0, st, s); \
+    else \
+      hipLaunchKernelGGL((score_wide_select_kernel<DD, kWideRegs>), dim3((unsigned)nq), dim3(kWideSel), 0, st, s); \
+  } while (0)
+      if (dm.d == 128) MSA_WIDE_SELECT(128); else MSA_WIDE_SELECT(64);
+#undef MSA_WIDE_SELECT
+      if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
+    }
+  }
+  profile_mark(dm, true, st);
+  return MSA_OK;
+}
+
+}  // namespace msa

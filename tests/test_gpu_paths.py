@@ -45,3 +45,45 @@ def test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim):
         idx, val = msa.msa_score_topk(cfg_p, dev(qb), dKR, dinv if sim == "cos" else None, k, workspace=ws)
         torch.cuda.synchronize()
         check_topk_generic(q, KRb, C, N, idx, val, k, sim, "all", pool, atol=2e-5 if sim == "cos" else 2e-4)
+
+
+# (N, Hkv, r, C, d, B, M, k, sim): more tokens than a pass of the scan -> the wide kernel and its selection
+ALL_WIDE = [
+    (70, 8, 1, 8, 128, 1, 33, 17, "cos"),         # one token more than the scan takes, a ragged unit
+    (5003, 8, 2, 8, 128, 2, 75, 32, "cos"),       # three token blocks, the last ragged
+    (1037, 4, 2, 16, 128, 1, 65, 64, "cos"),      # one document per tile, the largest k
+    (4099, 8, 1, 1, 64, 1, 70, 20, "dot"),        # hi and lo rows, sixteen documents per tile
+    (30011, 2, 1, 2, 64, 1, 300, 9, "cos"),       # two segments of the bank
+    (333, 2, 1, 4, 128, 1, 1030, 3, "cos"),       # two passes of tokens
+    (5, 2, 1, 8, 64, 3, 20, 5, "dot"),            # as many documents as are selected
+]
+
+
+@pytest.mark.parametrize("N,Hkv,r,C,d,B,M,k,sim", ALL_WIDE)
+def test_all_heads_wide(N, Hkv, r, C, d, B, M, k, sim):
+    test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim)
+
+
+@pytest.mark.parametrize("copies", [300, 4000])
+def test_all_heads_wide_more_candidates_than_k(copies):
+    """Copies of one document tie exactly: all of them are candidates of every token (4000: more than the selection
+    keeps on chip, so the row goes through it in windows); ties go to the lower index."""
+    N, Hkv, C, d, M, k = 6000, 2, 8, 64, 40, 12
+    say(f"all-heads selection with {copies} copies of the best document")
+    cfg = msa.MsaConfig(N, 8 * C, 8, Hkv, Hkv, d, 1e6, select_scope=msa.MSA_SCOPE_ALL)
+    KRb, _ = random_index(52000, N, Hkv, C, d)
+    qb, q = S.normal_bf16(52001, (1, M, Hkv, d))
+    rng = np.random.default_rng(52002)
+    at = rng.permutation(N)[:copies]
+    first = KRb.reshape(Hkv, N, C, d)
+    first[:, at] = np.abs(first[:, at[:1]])
+    qb = qb & 0x7FFF                              # every query component positive: the copies are every token's best
+    q = np.abs(q)
+    inv = 1.0 / np.maximum(np.linalg.norm(KRb, axis=-1), O.EPS_NORM)
+    dKR, dinv = upload_oracle_index(cfg, KRb, inv)
+    idx, val = msa.msa_score_topk(cfg, dev(qb), dKR, dinv, k)
+    torch.cuda.synchronize()
+    want = np.sort(at)[:k]
+    assert np.array_equal(idx.cpu().numpy(), np.broadcast_to(want, (1, M, 1, k)))
+    _, s = O.score_topk(q, KRb, C, k, "cos", "all", False)[1:]
+    assert np.allclose(val.cpu().numpy(), s[..., want], rtol=0, atol=2e-5)
