@@ -23,7 +23,8 @@ struct Dims {
 
 // Work split of the MFMA-bound scoring path for many query tokens (msa_score_gemm.hip).
 struct GemmPlan {
-  int n_qblocks;         // blocks of 256 (128: k > 8) query tokens
+  int n_qblocks;         // blocks of tokens_per_wg query tokens (two-pass form)
+  int tb1, n_qblocks1;   // one-pass form: 32-token blocks per wave (1, 2), blocks of 128 * tb1 query tokens
   int n_splits;          // key-range splits per (head, token block)
   int stages_per_split;  // 64-key stages per split
   size_t off_lists;      // byte offset of the candidate lists (after the folded fp32 queries)
@@ -32,7 +33,7 @@ struct GemmPlan {
   // bound of the k-th best one-pass score is scored again exactly, and token blocks whose per-lane lists overflow
   // inside that band are redone by the two-pass kernel.
   int filter;            // 1: the filter applies
-  int list_len;          // entries per per-lane list (8: k <= 8, 16: k <= 16)
+  int list_len;          // entries per per-lane list of the one-pass product (8: k <= 8, else 16)
   int tokens_per_wg;     // query tokens per workgroup = per fallback flag
   size_t off_eps;        // fp32 [BM][Hkv]: bound on |one-pass score - exact score| per (token, KV group)
   size_t off_flags;      // int32 [Hkv][n_qblocks]: 1 = this token block is redone by the two-pass kernel
@@ -40,7 +41,7 @@ struct GemmPlan {
                          // (the two-pass kernel's lists, off_lists, reuse this memory afterwards)
   size_t ws_bytes;
 };
-constexpr int kFilterMaxCand = 32;
+constexpr int kFilterMaxCand = 64;
 bool gemm_path_applies(const Dims& dm, int BM, int k);
 GemmPlan plan_score_gemm(const Dims& dm, int BM, int k);
 // Enqueues the scoring kernels.  Without the filter the per-split lists are left for score_merge_kernel.  With it

@@ -26,10 +26,11 @@ namespace msa {
 
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
-constexpr int kGemmMaxK = 16;     // longest per-lane list (k <= 16)
-// Two shapes of the kernel: k <= 8 keeps two 32-token blocks per wave (256 tokens per workgroup) with 8-entry
+constexpr int kGemmMaxK = 32;     // longest per-lane list
+// Shapes of the kernel: k <= 8 keeps two 32-token blocks per wave (256 tokens per workgroup) with 8-entry
 // per-lane lists; 8 < k <= 16 keeps one block per wave (128 tokens per workgroup) with 16-entry lists -- the longer
-// lists take the registers of the second block's query operands.
+// lists take the registers of the second block's query operands -- and 16 < k <= 32 the same with 32-entry lists
+// (two-pass form only: behind the one-pass filter 16 entries per list do, see plan_score_gemm).
 
 __device__ __forceinline__ f32x16_t mfma32(bf16x8_t a, bf16x8_t b, f32x16_t c) {
   // D(32x32) += A(32x16) * B(16x32).  Lane l: A[l%32][8(l/32)..+8], B[8(l/32)..+8][l%32],
@@ -495,7 +496,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
 // entries each, zero = empty), whose scores s~ differ from the exact scores s by at most eps.  Let t~ be the k-th
 // largest s~.  The k documents with the largest s~ all have s >= t~ - eps, so the k-th largest exact score is at
 // least t~ - eps, and every document of the exact top-k has s~ >= s - eps >= t~ - 2 eps: the candidates are all
-// list entries with s~ >= t~ - 2 eps.  A lane's list holds the KL >= k best documents that lane saw; it can have
+// list entries with s~ >= t~ - 2 eps.  A lane's list holds the KL best documents that lane saw; it can have
 // dropped a candidate only if it is full and its last entry is itself inside the band -- then, or with more than
 // kFilterMaxCand candidates, the token's block is flagged and redone by the two-pass kernel.
 //
@@ -652,10 +653,20 @@ GemmPlan plan_score_gemm(const Dims& dm, int BM, int k) {
   GemmPlan p;
   const int tokens_per_wg = (k <= 8) ? 256 : 128;
   p.n_qblocks = (BM + tokens_per_wg - 1) / tokens_per_wg;
+  // The one-pass form has the registers for two blocks per wave at either list length (every key read from LDS then
+  // serves 64 tokens; 2048 tokens, 32768 documents, k = 16: call 1425 -> 1346 us).  Up to 128 tokens one block per wave:
+  // the second would be padding (100 tokens, 97656 documents, k = 8: 480 -> 352 us).
+  p.tb1 = BM > 128 ? 2 : 1;
+  p.n_qblocks1 = (BM + 128 * p.tb1 - 1) / (128 * p.tb1);
+  const bool one_pass = dm.cos && dm.d == 128 && dm.C == 8;
   const long long n_stage = ((dm.tiles + 1) / 2 + 1) / 2;           // stages of 64 keys
-  long long want = (2 * 256) / ((long long)dm.Hkv * p.n_qblocks);  // ~2 workgroups per CU
+  long long want = (2 * 256) / ((long long)dm.Hkv * (one_pass ? p.n_qblocks1 : p.n_qblocks));  // ~2 workgroups per CU
   if (want < 1) want = 1;
-  long long by_len = (n_stage + 31) / 32;                          // at least 32 stages per split
+  // At least 8 stages (512 keys) per split: a small bank (234 tokens, 678 documents of 8 chunks) is worth spreading over
+  // the chip (with at least 32 stages: 89 us, with 8: 73 us; 64 tokens, 4096 documents, k = 8: 95 -> 51 us).
+  long long by_len = (n_stage + 7) / 8;
+  // k > 16: at least four splits, so that the k best of a token meet 16-entry lists (8 or more) with room to spare
+  if (k > 16 && want < 4) want = 4;
   long long ns = want < by_len ? want : by_len;
   if (ns < 1) ns = 1;
   if (ns > 64) ns = 64;
@@ -667,7 +678,10 @@ GemmPlan plan_score_gemm(const Dims& dm, int BM, int k) {
   p.tokens_per_wg = tokens_per_wg;
   // The one-pass filter: cosine (the bound needs unit keys), the shape the exact-score kernel is written for, and
   // few enough list entries per token for one wave.
-  p.filter = (dm.cos && dm.d == 128 && dm.C == 8 && 2 * p.n_splits * p.list_len <= kFilterMaxEntries) ? 1 : 0;
+  // With k > 16 the lists are shorter than k: right as long as no list is full of documents inside the band (those
+  // blocks are redone), worth it with several lists per token (mean load k / (2 n_splits) <= 4 of 16 entries).
+  p.filter = (one_pass && 2 * p.n_splits * p.list_len <= kFilterMaxEntries &&
+              (k <= 16 || 8 * p.n_splits >= k)) ? 1 : 0;
   p.off_eps = p.off_flags = p.off_flists = 0;
   if (p.filter) {
     // the two-pass kernel's lists (fallback) reuse the memory of the one-pass lists, which are twice as long
@@ -724,8 +738,16 @@ int launch_score_gemm_scan(const Dims& dm, const GemmPlan& pl, const void* q_rou
     // one-pass product -> candidates -> exact scores; then the two-pass kernel for the flagged token blocks only
     a.ws = (unsigned long long*)((char*)ws + pl.off_flists);
     profile_mark(dm, false, st);
-    if (k <= 8) hipLaunchKernelGGL((score_gemm_kernel<128, 2, 8, true, true>), dim3(blocks), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((score_gemm_kernel<128, 1, 16, true, true>), dim3(blocks), dim3(256), 0, st, a);
+    a.n_qblocks = pl.n_qblocks1;
+    const unsigned blocks1 = (unsigned)(dm.Hkv * pl.n_qblocks1 * pl.n_splits);
+    if (pl.tb1 == 2) {
+      if (k <= 8) hipLaunchKernelGGL((score_gemm_kernel<128, 2, 8, true, true>), dim3(blocks1), dim3(256), 0, st, a);
+      else hipLaunchKernelGGL((score_gemm_kernel<128, 2, 16, true, true>), dim3(blocks1), dim3(256), 0, st, a);
+    } else {
+      if (k <= 8) hipLaunchKernelGGL((score_gemm_kernel<128, 1, 8, true, true>), dim3(blocks1), dim3(256), 0, st, a);
+      else hipLaunchKernelGGL((score_gemm_kernel<128, 1, 16, true, true>), dim3(blocks1), dim3(256), 0, st, a);
+    }
+    a.n_qblocks = pl.n_qblocks;
     profile_mark(dm, true, st);
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
     hipLaunchKernelGGL(score_filter_select_kernel, dim3((unsigned)((BM * dm.Hkv + 3) / 4)), dim3(256), 0, st,
@@ -736,7 +758,8 @@ int launch_score_gemm_scan(const Dims& dm, const GemmPlan& pl, const void* q_rou
     a.ws = (unsigned long long*)((char*)ws + pl.off_lists);
     a.flags = flags;
     if (k <= 8) hipLaunchKernelGGL((score_gemm_kernel<128, 2, 8, true, false>), dim3(blocks), dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((score_gemm_kernel<128, 1, 16, true, false>), dim3(blocks), dim3(256), 0, st, a);
+    else if (k <= 16) hipLaunchKernelGGL((score_gemm_kernel<128, 1, 16, true, false>), dim3(blocks), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((score_gemm_kernel<128, 1, 32, true, false>), dim3(blocks), dim3(256), 0, st, a);
     return hipGetLastError() == hipSuccess ? MSA_OK : MSA_ERR_HIP;
   }
   profile_mark(dm, false, st);
@@ -747,8 +770,10 @@ int launch_score_gemm_scan(const Dims& dm, const GemmPlan& pl, const void* q_rou
   } while (0)
   if (k <= 8) {
     if (dm.d == 128) MSA_GEMM(128, 2, 8); else MSA_GEMM(64, 2, 8);
-  } else {
+  } else if (k <= 16) {
     if (dm.d == 128) MSA_GEMM(128, 1, 16); else MSA_GEMM(64, 1, 16);
+  } else {
+    if (dm.d == 128) MSA_GEMM(128, 1, 32); else MSA_GEMM(64, 1, 32);
   }
 #undef MSA_GEMM
   profile_mark(dm, true, st);

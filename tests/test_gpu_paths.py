@@ -47,6 +47,48 @@ def test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim):
         check_topk_generic(q, KRb, C, N, idx, val, k, sim, "all", pool, atol=2e-5 if sim == "cos" else 2e-4)
 
 
+# (N, Hkv, r, C, d, B, M, k, sim): the scoring GEMM with more than 16 selected documents
+GEMM_K32 = [
+    (5003, 2, 2, 8, 128, 1, 300, 32, "cos"),      # one-pass filter, two token blocks per wave, lists shorter than k
+    (700, 2, 1, 8, 128, 1, 100, 17, "cos"),       # one token block per wave
+    (40, 2, 1, 8, 128, 1, 64, 32, "cos"),         # one short split: no filter
+    (613, 4, 1, 16, 128, 1, 130, 20, "cos"),      # two-pass form, 32-entry lists
+    (901, 2, 1, 4, 64, 2, 35, 32, "dot"),
+]
+
+
+@pytest.mark.parametrize("N,Hkv,r,C,d,B,M,k,sim", GEMM_K32)
+def test_prefill_scoring_k_above_16(N, Hkv, r, C, d, B, M, k, sim):
+    say(f"scoring GEMM N={N} Hkv={Hkv} C={C} d={d} B={B} M={M} k={k} {sim}")
+    cfg = msa.MsaConfig(N, 8 * C, 8, Hkv * r, Hkv, d, 1e6, sim=msa.MSA_SIM_COS if sim == "cos" else msa.MSA_SIM_DOT)
+    KRb, inv = random_index(53000 + N, N, Hkv, C, d)
+    qb, q = S.normal_bf16(53001 + N, (B, M, Hkv * r, d))
+    dKR, dinv = upload_oracle_index(cfg, KRb, inv)
+    for pool in (False, True):
+        idx, val = msa.msa_score_topk(cfg.replace(token_pool=int(pool)), dev(qb), dKR, dinv if sim == "cos" else None, k)
+        torch.cuda.synchronize()
+        check_topk_generic(q, KRb, C, N, idx, val, k, sim, "group", pool, atol=2e-5 if sim == "cos" else 2e-4)
+
+
+def test_prefill_scoring_k_above_16_neighbouring_winners():
+    """The best documents of every token lie side by side: more of them in one list of the one-pass filter than it
+    holds, so every token block is redone by the two-pass form with 32-entry lists."""
+    N, Hkv, C, d, M, k = 4000, 2, 8, 128, 70, 24
+    cfg = msa.MsaConfig(N, 8 * C, 8, Hkv, Hkv, d, 1e6)
+    KRb, _ = random_index(54000, N, Hkv, C, d)
+    qb, q = S.normal_bf16(54001, (1, M, Hkv, d))
+    qb, q = qb & 0x7FFF, np.abs(q)                # every query component positive ...
+    docs = KRb.reshape(Hkv, N, C, d)
+    docs[:, 1000:1100] = np.abs(docs[:, 1000:1100])   # ... and so are the keys of a hundred neighbours
+    inv = 1.0 / np.maximum(np.linalg.norm(KRb, axis=-1), O.EPS_NORM)
+    dKR, dinv = upload_oracle_index(cfg, KRb, inv)
+    idx, val = msa.msa_score_topk(cfg, dev(qb), dKR, dinv, k)
+    torch.cuda.synchronize()
+    got = idx.cpu().numpy()
+    assert got.min() >= 1000 and got.max() < 1100
+    check_topk_generic(q, KRb, C, N, idx, val, k, "cos", "group", False)
+
+
 # (N, Hkv, r, C, d, B, M, k, sim): more tokens than a pass of the scan -> the wide kernel and its selection
 ALL_WIDE = [
     (70, 8, 1, 8, 128, 1, 33, 17, "cos"),         # one token more than the scan takes, a ragged unit
