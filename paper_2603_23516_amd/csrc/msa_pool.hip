@@ -5,9 +5,10 @@
 //
 // One wavefront owns one chunk of one tensor.  RoPE pairs element u with u + d/2, so a lane loads
 // the 16-byte piece `pc` of a row together with piece pc + d/16 (the partner half): d/16 lanes
-// cover a row and a wave-wide pair of loads covers 1024/d rows.  The lane's eight angles
-// (cos, sin)(p theta_u) start from a double-precision range reduction at the lane's first row and
-// advance by the constant row stride with one complex multiply per load pair.
+// cover a row and a wave-wide pair of loads covers 1024/d rows.  The angles of the lane's first row,
+// (cos, sin)(p theta_u), come from a double-precision range reduction; the rows a constant stride apart
+// are summed by Horner's rule.  With the vector work of the angles shared by a workgroup and halved per row the keys
+// stream as fast as the values: 4.3 GB at d = 128 781 -> 704 us, 0.5 GB at d = 64 150 -> 114 us, P = 32 378 -> 295 us.
 #include "msa_device.h"
 #include "msa_host.h"
 
@@ -23,48 +24,40 @@ __global__ __launch_bounds__(256) void pool_chunks_kernel(const uint16_t* __rest
                                                           uint16_t* __restrict__ Xbar,
                                                           const int32_t* __restrict__ lens,
                                                           int32_t* __restrict__ pooled_lens, int doc_begin,
-                                                          long long n_chunks, int Hkv, int G, int P,
+                                                          uint32_t n_pairs, int Hkv, int G, int P,
                                                           int C, PoolTheta th) {
   constexpr int LPR = D / 16;    // lanes per row (each holds a piece and its partner half)
   constexpr int RPL = 64 / LPR;  // rows per wave-wide load pair
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const long long cid = (long long)blockIdx.x * 4 + wave;
-  if (cid >= n_chunks) return;  // wave-uniform
-  const int j = (int)(cid % C);
-  const long long t = cid / C;
-  const int g = (int)(t % Hkv);
-  const long long doc = doc_begin + t / Hkv;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // Keys: a workgroup takes the same chunk of four (document, head) pairs (they share their angles), neighbouring
+  // workgroups neighbouring chunks.  Values: chunks in order.
+  const uint32_t cid = blockIdx.x * 4u + wave;
+  const uint32_t j = ROT ? blockIdx.x % (uint32_t)C : cid % (uint32_t)C;
+  const uint32_t t = ROT ? blockIdx.x / (uint32_t)C * 4 + wave : cid / (uint32_t)C;
+  const bool live = t < n_pairs;  // wave-uniform
+  const int g = (int)(t % (uint32_t)Hkv);
+  const long long doc = live ? doc_begin + t / (uint32_t)Hkv : doc_begin;
   const uint16_t* src = X + ((doc * Hkv + g) * (long long)G + (long long)j * P) * D;
   const int pc = lane % LPR;
   const int rowoff = lane / LPR;
   // tokens of this chunk (wave-uniform): a tail chunk is short, a chunk past the end has none and pools to zero
-  int n_rows = P;
-  if (lens != nullptr) {
+  int n_rows = live ? P : 0;
+  if (lens != nullptr && live) {
     int len = lens[doc];
     len = len < 1 ? 1 : (len > G ? G : len);
-    n_rows = len - j * P;
+    n_rows = len - (int)j * P;
     n_rows = n_rows < 0 ? 0 : (n_rows > P ? P : n_rows);
     if (pooled_lens != nullptr && g == 0 && j == 0 && lane == 0) pooled_lens[doc] = (len + P - 1) / P;
   }
 
-  float2 cs[8], stp[8];
-  if (ROT) {
+  // load pairs per batch: with the rotation four (eight cost it too many registers: 704 -> 705 us at d = 128, 114 ->
+  // 132 at d = 64), without it eight (703 -> 684 us)
+  constexpr int NB = ROT ? 4 : 8;
+  uint4 v1[NB], v2[NB];
+  auto load = [&](int it0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      cs[e] = cis_pos(j * P + rowoff, th.th[8 * pc + e]);
-      stp[e] = th.estep[8 * pc + e];
-    }
-  }
-  float a1[8], a2[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) a1[e] = a2[e] = 0.f;
-
-  const int iters = (P + RPL - 1) / RPL;
-  for (int it0 = 0; it0 < iters; it0 += 4) {
-    uint4 v1[4], v2[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < NB; ++u) {
       const int row = (it0 + u) * RPL + rowoff;
       if (row < n_rows) {
         const uint16_t* rp = src + (long long)row * D + pc * 8;
@@ -74,8 +67,35 @@ __global__ __launch_bounds__(256) void pool_chunks_kernel(const uint16_t* __rest
         v1[u] = v2[u] = make_uint4(0, 0, 0, 0);
       }
     }
+  };
+  const int iters = (P + RPL - 1) / RPL;
+  const int last0 = (iters - 1) / NB * NB;  // the batches run from the last to the first (see below)
+  load(last0);  // on its way while the angles are worked out
+  __shared__ float2 cs_s[ROT ? 8 : 1][64];
+  float2 stp[8];
+  if (ROT) {
+    // The four waves have the same chunk number and so the same angles: each works out a quarter of them.
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int i = 0; i < 2; ++i) {
+      const int e = 2 * wave + i;
+      cs_s[e][lane] = cis_pos((int)j * P + rowoff, th.th[8 * pc + e]);
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) stp[e] = th.estep[8 * pc + e];
+    lds_barrier();
+  }
+  if (!live) return;  // wave-uniform, behind the only barrier
+  float a1[8], a2[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) a1[e] = a2[e] = 0.f;
+
+  // The sum of the rotated rows of a lane, rows RPL apart, is evaluated from its last row to its first (Horner's rule on
+  // the pairs as complex numbers): z = x + z e^{i RPL theta}, and the angle of the lane's first row comes in once, at
+  // the end.  That is four multiply-adds per pair and row, where rotating every row takes four more for the next angle.
+  for (int it0 = last0; it0 >= 0; it0 -= NB) {
+    if (it0 < last0) load(it0);
+#pragma unroll
+    for (int u = NB - 1; u >= 0; --u) {
       const uint32_t w1[4] = {v1[u].x, v1[u].y, v1[u].z, v1[u].w};
       const uint32_t w2[4] = {v2[u].x, v2[u].y, v2[u].z, v2[u].w};
 #pragma unroll
@@ -83,11 +103,12 @@ __global__ __launch_bounds__(256) void pool_chunks_kernel(const uint16_t* __rest
         const float p0 = bf16_lo(w1[jj]), p1 = bf16_hi(w1[jj]);
         const float q0 = bf16_lo(w2[jj]), q1 = bf16_hi(w2[jj]);
         if (ROT) {
-          const float2 c0 = cs[2 * jj], c1 = cs[2 * jj + 1];
-          a1[2 * jj] += p0 * c0.x - q0 * c0.y;
-          a1[2 * jj + 1] += p1 * c1.x - q1 * c1.y;
-          a2[2 * jj] += q0 * c0.x + p0 * c0.y;
-          a2[2 * jj + 1] += q1 * c1.x + p1 * c1.y;
+          const float2 w0 = stp[2 * jj], w1s = stp[2 * jj + 1];
+          const float z0 = a1[2 * jj], z1 = a1[2 * jj + 1];
+          a1[2 * jj] = fmaf(z0, w0.x, fmaf(-a2[2 * jj], w0.y, p0));
+          a1[2 * jj + 1] = fmaf(z1, w1s.x, fmaf(-a2[2 * jj + 1], w1s.y, p1));
+          a2[2 * jj] = fmaf(a2[2 * jj], w0.x, fmaf(z0, w0.y, q0));
+          a2[2 * jj + 1] = fmaf(a2[2 * jj + 1], w1s.x, fmaf(z1, w1s.y, q1));
         } else {
           a1[2 * jj] += p0;
           a1[2 * jj + 1] += p1;
@@ -95,10 +116,14 @@ __global__ __launch_bounds__(256) void pool_chunks_kernel(const uint16_t* __rest
           a2[2 * jj + 1] += q1;
         }
       }
-      if (ROT) {
+    }
+  }
+  if (ROT) {
 #pragma unroll
-        for (int e = 0; e < 8; ++e) cs[e] = cmul(cs[e], stp[e]);
-      }
+    for (int e = 0; e < 8; ++e) {
+      const float2 z = cmul(make_float2(a1[e], a2[e]), cs_s[e][lane]);
+      a1[e] = z.x;
+      a2[e] = z.y;
     }
   }
   // combine the RPL row groups that hold the same columns
@@ -124,10 +149,12 @@ __global__ __launch_bounds__(256) void pool_chunks_kernel(const uint16_t* __rest
 
 int launch_pool_kv(const Dims& dm, const void* K, const void* V, int doc_begin, int doc_count,
                    void* Kbar, void* Vbar, int32_t* pooled_lens, hipStream_t st) {
-  const long long n_chunks = (long long)doc_count * dm.Hkv * dm.C;
-  if (n_chunks == 0) return MSA_OK;
-  const long long blocks = (n_chunks + 3) / 4;
-  if (blocks > 0x7fffffffLL) return MSA_ERR_UNSUPPORTED;
+  const long long pairs = (long long)doc_count * dm.Hkv;
+  if (pairs == 0) return MSA_OK;
+  const long long blocks = (pairs + 3) / 4 * dm.C;  // keys; values: four chunks each, no more than that
+  // (32-bit chunk numbers: a bank beyond them would hold more than 4 TB)
+  if (blocks > 0x3fffffffLL || pairs > 0xfffffff0LL) return MSA_ERR_UNSUPPORTED;
+  const uint32_t n_pairs = (uint32_t)pairs;
   PoolTheta th;
   const int rpl = 64 / (dm.d / 16);
   for (int u = 0; u < 64; ++u) {
@@ -138,19 +165,19 @@ int launch_pool_kv(const Dims& dm, const void* K, const void* V, int doc_begin, 
   if (Kbar != nullptr) {
     if (dm.d == 128)
       hipLaunchKernelGGL((pool_chunks_kernel<128, true>), grid, block, 0, st, (const uint16_t*)K,
-                         (uint16_t*)Kbar, dm.lens, pooled_lens, doc_begin, n_chunks, dm.Hkv, dm.G, dm.P, dm.C, th);
+                         (uint16_t*)Kbar, dm.lens, pooled_lens, doc_begin, n_pairs, dm.Hkv, dm.G, dm.P, dm.C, th);
     else
       hipLaunchKernelGGL((pool_chunks_kernel<64, true>), grid, block, 0, st, (const uint16_t*)K,
-                         (uint16_t*)Kbar, dm.lens, pooled_lens, doc_begin, n_chunks, dm.Hkv, dm.G, dm.P, dm.C, th);
+                         (uint16_t*)Kbar, dm.lens, pooled_lens, doc_begin, n_pairs, dm.Hkv, dm.G, dm.P, dm.C, th);
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
   }
   if (Vbar != nullptr) {
     if (dm.d == 128)
       hipLaunchKernelGGL((pool_chunks_kernel<128, false>), grid, block, 0, st, (const uint16_t*)V,
-                         (uint16_t*)Vbar, dm.lens, Kbar == nullptr ? pooled_lens : nullptr, doc_begin, n_chunks, dm.Hkv, dm.G, dm.P, dm.C, th);
+                         (uint16_t*)Vbar, dm.lens, Kbar == nullptr ? pooled_lens : nullptr, doc_begin, n_pairs, dm.Hkv, dm.G, dm.P, dm.C, th);
     else
       hipLaunchKernelGGL((pool_chunks_kernel<64, false>), grid, block, 0, st, (const uint16_t*)V,
-                         (uint16_t*)Vbar, dm.lens, Kbar == nullptr ? pooled_lens : nullptr, doc_begin, n_chunks, dm.Hkv, dm.G, dm.P, dm.C, th);
+                         (uint16_t*)Vbar, dm.lens, Kbar == nullptr ? pooled_lens : nullptr, doc_begin, n_pairs, dm.Hkv, dm.G, dm.P, dm.C, th);
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
   }
   return MSA_OK;

@@ -129,3 +129,30 @@ def test_all_heads_wide_more_candidates_than_k(copies):
     assert np.array_equal(idx.cpu().numpy(), np.broadcast_to(want, (1, M, 1, k)))
     _, s = O.score_topk(q, KRb, C, k, "cos", "all", False)[1:]
     assert np.allclose(val.cpu().numpy(), s[..., want], rtol=0, atol=2e-5)
+
+
+@pytest.mark.parametrize("N,Hkv,G,P,d,first,count", [(5, 3, 56, 8, 64, 1, 3), (3, 1, 24, 24, 128, 0, 3), (7, 5, 256, 64, 128, 6, 1)])
+def test_pool_chunks_by_pairs(N, Hkv, G, P, d, first, count):
+    """Pooled bank where the (document, head) pairs do not fill the workgroups, chunks do not fill a batch of loads, and
+    a part of the bank is addressed; a bf16 mean is the rounded exact one, or its neighbour where the exact mean lies
+    within fp32 summation error (P terms of at most ~6, rotation angles to ~1e-6) of a rounding tie."""
+    cfg = msa.MsaConfig(N, G, P, Hkv, Hkv, d, 1e4)
+    Kb, K = S.normal_bf16(55000, (N, Hkv, G, d))
+    Vb, V = S.normal_bf16(55001, (N, Hkv, G, d))
+    lens = np.maximum(1, (np.arange(N) * 37 + 5) % (G + 1)).astype(np.int32)
+    for ragged in (False, True):
+        c = cfg.replace(doc_lens=torch.from_numpy(lens).cuda() if ragged else None)
+        Kbar = torch.full((N, Hkv, G // P, d), 7.0, dtype=torch.bfloat16, device="cuda")
+        Vbar = Kbar.clone()
+        kw = dict(pooled_lens=torch.zeros(N, dtype=torch.int32, device="cuda")) if ragged else {}
+        msa.msa_pool_kv(c, dev(Kb), dev(Vb), doc_begin=first, doc_count=count, Kbar=Kbar, Vbar=Vbar, **kw)
+        torch.cuda.synchronize()
+        for X, got in ((O.rope(K, np.arange(G), 1e4), Kbar), (V, Vbar)):
+            got = got.float().cpu().numpy().astype(np.float64)
+            assert np.all(got[:first] == 7.0) and np.all(got[first + count:] == 7.0)
+            for i in range(first, first + count):
+                n = int(lens[i]) if ragged else G
+                for j in range(G // P):
+                    rows = X[i, :, j * P:min(n, (j + 1) * P)]
+                    want = rows.mean(1) if rows.shape[1] else np.zeros((Hkv, d))
+                    assert np.abs(got[i, :, j] - want).max() <= 2.0 ** -8 * np.abs(want).max() + 1e-5
