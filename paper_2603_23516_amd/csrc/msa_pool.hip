@@ -32,9 +32,10 @@ __global__ __launch_bounds__(256) void pool_chunks_kernel(const uint16_t* __rest
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // Keys: a workgroup takes the same chunk of four (document, head) pairs (they share their angles), neighbouring
   // workgroups neighbouring chunks.  Values: chunks in order.
-  const uint32_t cid = blockIdx.x * 4u + wave;
-  const uint32_t j = ROT ? blockIdx.x % (uint32_t)C : cid % (uint32_t)C;
-  const uint32_t t = ROT ? blockIdx.x / (uint32_t)C * 4 + wave : cid / (uint32_t)C;
+  const uint32_t bq = blockIdx.x / (uint32_t)C, br = blockIdx.x % (uint32_t)C;
+  const uint32_t in_row = 4 * br + wave;  // values: chunk 4 blockIdx + wave = 4 bq C + in_row
+  const uint32_t j = ROT ? br : in_row % (uint32_t)C;
+  const uint32_t t = 4 * bq + (ROT ? wave : in_row / (uint32_t)C);
   const bool live = t < n_pairs;  // wave-uniform
   const int g = (int)(t % (uint32_t)Hkv);
   const long long doc = live ? doc_begin + t / (uint32_t)Hkv : doc_begin;
@@ -152,8 +153,7 @@ int launch_pool_kv(const Dims& dm, const void* K, const void* V, int doc_begin, 
   const long long pairs = (long long)doc_count * dm.Hkv;
   if (pairs == 0) return MSA_OK;
   const long long blocks = (pairs + 3) / 4 * dm.C;  // keys; values: four chunks each, no more than that
-  // (32-bit chunk numbers: a bank beyond them would hold more than 4 TB)
-  if (blocks > 0x3fffffffLL || pairs > 0xfffffff0LL) return MSA_ERR_UNSUPPORTED;
+  if (blocks > 0x7fffffffLL || pairs > 0xfffffff0LL) return MSA_ERR_UNSUPPORTED;
   const uint32_t n_pairs = (uint32_t)pairs;
   PoolTheta th;
   const int rpl = 64 / (dm.d / 16);

@@ -520,7 +520,7 @@ WidePlan plan_score_wide(const Dims& dm, int BM, int k) {
   p.off_eps = end;
   end += round_up256((size_t)p.pass_tokens * dm.Hkv * sizeof(float));
   p.off_best = end;
-  end += round_up256((size_t)p.pass_tokens * k * sizeof(unsigned long long));
+  end += round_up256((size_t)BM * k * sizeof(unsigned long long));  // (each pass has its own tokens')
   p.off_mat = end;
   end += round_up256((size_t)p.pass_tokens * p.seg_docs * sizeof(float));
   p.ws_bytes = end;
@@ -546,7 +546,6 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
   s.qf = (const float*)(w + pl.off_qf);
   s.KR = a.KR;
   s.inv_norm = a.inv_norm;
-  s.best = (unsigned long long*)(w + pl.off_best);
   s.out_idx = out_idx;
   s.out_score = out_score;
   s.out_key = out_key;
@@ -589,6 +588,7 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
       }
 #undef MSA_WIDE
       if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
+      s.best = (unsigned long long*)(w + pl.off_best) + (size_t)tok0 * k;
       s.first = doc0 == 0;
       s.last = doc0 + n_docs == dm.N;
       s.n_docs = n_docs;
