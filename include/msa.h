@@ -266,6 +266,35 @@ int msa_fetch_selected(const msa_config_t* cfg, const void* K_host, const void* 
                        int32_t B, int32_t M, int32_t k, void* K_stage, void* V_stage, int32_t* idx_stage,
                        int32_t* lens_stage, msa_stream_t stream);
 
+/*
+ * Several routed layers on their banks in one call (Section 3.2.1: routing in the latter half of the layers): for every
+ * layer in turn msa_score_topk(cfg, ...) on stream `route`, then msa_sparse_attend(attend_cfg, ...) on stream `attend`;
+ * a layer's attention waits for its selection, the next layer is routed meanwhile.  Exactly those calls, in that order,
+ * with their checks (a refused layer ends the call with its status; the layers before it have been enqueued).
+ *   fork      event: recorded on `caller`, awaited by both streams first
+ *   join      event: recorded on `attend` last, awaited by `caller`
+ * With route == attend the scored events are not used.  All events are the caller's and may be reused by the next call.
+ */
+typedef struct {
+  const void* q;          /* bf16 [B][M][Hq][d] */
+  const void* KR;
+  const float* inv_norm;
+  int32_t* idx;           /* [B][M'][S][k]: written, then attended */
+  float* score;           /* may be NULL */
+  const void* K;          /* the bank that attend_cfg describes */
+  const void* V;
+  const void* Kloc;
+  const void* Vloc;
+  void* out;
+  float* lse;             /* may be NULL */
+  void* scored_event;     /* hipEvent_t */
+  int32_t B, M, Lloc;     /* as in the two calls */
+} msa_layer_t;
+int msa_layers_step(const msa_config_t* cfg, const msa_config_t* attend_cfg, const msa_layer_t* layers,
+                    int32_t n_layers, int32_t k, int32_t local_pos0, const int32_t* q_pos, void* score_workspace,
+                    size_t score_workspace_bytes, void* attend_workspace, size_t attend_workspace_bytes,
+                    msa_stream_t caller, msa_stream_t route, msa_stream_t attend, void* fork_event, void* join_event);
+
 #ifdef __cplusplus
 }
 #endif

@@ -21,7 +21,7 @@ EXPORTS = ("msa_version", "msa_status_string", "msa_routing_keys_bytes", "msa_in
            "msa_pooled_bank_bytes", "msa_score_topk_workspace_bytes",
            "msa_sparse_attend_workspace_bytes", "msa_build_routing_keys", "msa_pool_kv", "msa_score_topk",
            "msa_sparse_attend", "msa_fetch_slots", "msa_fetch_selected",
-           "msa_noalloc_scratch_bytes", "msa_score_topk_noalloc")
+           "msa_noalloc_scratch_bytes", "msa_score_topk_noalloc", "msa_layers_step")
 
 
 class MsaConfig(ctypes.Structure):
@@ -74,6 +74,12 @@ class MsaConfig(ctypes.Structure):
         return (self.n_docs * self.chunks_per_doc + 15) // 16
 
 
+class MsaLayer(ctypes.Structure):
+    """msa_layer_t: one routed layer of msa_layers_step."""
+    _fields_ = [(n, ctypes.c_void_p) for n in ("q", "KR", "inv_norm", "idx", "score", "K", "V", "Kloc", "Vloc", "out",
+                                               "lse", "scored_event")] + [(n, ctypes.c_int32) for n in ("B", "M", "Lloc")]
+
+
 class MsaError(RuntimeError):
     def __init__(self, status, where):
         self.status = status
@@ -124,6 +130,8 @@ def load_library():
     lib.msa_sparse_attend.restype = ctypes.c_int
     lib.msa_sparse_attend.argtypes = [cfgp, vp, i32, i32, vp, vp, vp, i32, vp, vp, i32, i32, vp, vp,
                                       vp, vp, sz, vp]
+    lib.msa_layers_step.restype = ctypes.c_int
+    lib.msa_layers_step.argtypes = [cfgp, cfgp, ctypes.POINTER(MsaLayer)] + [i32] * 3 + [vp, vp, sz, vp, sz] + [vp] * 5
     _lib = lib
     return lib
 
@@ -133,12 +141,11 @@ def status_string(status):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _stream(stream, device):
-    s = stream if stream is not None else torch.cuda.current_stream(device)
-    return ctypes.c_void_p(s.cuda_stream)
+    return (stream if stream is not None else torch.cuda.current_stream(device)).cuda_stream
 
 
 def _check(rc, where):
@@ -296,6 +303,24 @@ def msa_sparse_attend(cfg, q, K, V, idx, Kloc, Vloc, local_pos0, q_pos, out=None
                                           _ptr(lse), _ptr(workspace), workspace.numel(), _stream(stream, dev))
     _check(rc, "msa_sparse_attend")
     return out, lse
+
+
+def msa_layers_step(cfg, attend_cfg, layers, k, local_pos0, q_pos, ws_score, ws_attend, caller, route, attend,
+                    fork_event, join_event):
+    """layers: a sequence of tuples (q, KR, inv_norm, idx, score, K, V, Kloc, Vloc, out, lse, scored event); streams and
+    events are torch.cuda ones (an event has been recorded once, which creates it)."""
+    _need(q_pos, torch.int32, "q_pos")
+    arr = (MsaLayer * len(layers))()
+    for a, y in zip(arr, layers):
+        _need(y[0], torch.bfloat16, "q")
+        (a.q, a.KR, a.inv_norm, a.idx, a.score, a.K, a.V, a.Kloc, a.Vloc, a.out, a.lse) = [_ptr(t) for t in y[:11]]
+        a.scored_event = y[11].cuda_event
+        a.B, a.M, a.Lloc = y[0].shape[0], y[0].shape[1], 0 if y[7] is None else y[7].shape[2]
+    rc = load_library().msa_layers_step(ctypes.byref(cfg), ctypes.byref(attend_cfg), arr, len(layers), k,
+                                        local_pos0, _ptr(q_pos), _ptr(ws_score), ws_score.numel(), _ptr(ws_attend),
+                                        ws_attend.numel(), caller.cuda_stream, route.cuda_stream, attend.cuda_stream,
+                                        fork_event.cuda_event, join_event.cuda_event)
+    _check(rc, "msa_layers_step")
 
 
 def fetch_slots(cfg, B, M, k):

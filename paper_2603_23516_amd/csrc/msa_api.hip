@@ -310,4 +310,38 @@ int msa_sparse_attend(const msa_config_t* cfg, const void* q, int32_t B, int32_t
                        lse, workspace, cfg->bank_keys_rotated, (hipStream_t)stream);
 }
 
+int msa_layers_step(const msa_config_t* cfg, const msa_config_t* attend_cfg, const msa_layer_t* layers,
+                    int32_t n_layers, int32_t k, int32_t local_pos0, const int32_t* q_pos, void* score_workspace,
+                    size_t score_workspace_bytes, void* attend_workspace, size_t attend_workspace_bytes,
+                    msa_stream_t caller, msa_stream_t route, msa_stream_t attend, void* fork_event, void* join_event) {
+  if (n_layers < 0 || (n_layers > 0 && layers == nullptr) || fork_event == nullptr || join_event == nullptr)
+    return MSA_ERR_INVALID_ARG;
+  const bool two = route != attend;
+  for (int32_t l = 0; two && l < n_layers; ++l)
+    if (layers[l].scored_event == nullptr) return MSA_ERR_INVALID_ARG;
+  const hipStream_t sc = (hipStream_t)caller, sr = (hipStream_t)route, sa = (hipStream_t)attend;
+  auto after = [](hipEvent_t e, hipStream_t from, hipStream_t to) {
+    return hipEventRecord(e, from) == hipSuccess && hipStreamWaitEvent(to, e, 0) == hipSuccess;
+  };
+  if (!after((hipEvent_t)fork_event, sc, sr)) return MSA_ERR_HIP;
+  if (two && hipStreamWaitEvent(sa, (hipEvent_t)fork_event, 0) != hipSuccess) return MSA_ERR_HIP;
+  int rc = MSA_OK;
+  for (int32_t l = 0; l < n_layers && rc == MSA_OK; ++l) {
+    const msa_layer_t& y = layers[l];
+    rc = msa_score_topk(cfg, y.q, y.B, y.M, y.KR, y.inv_norm, k, y.idx, y.score, score_workspace, score_workspace_bytes,
+                        route);
+    if (rc == MSA_OK && two && !after((hipEvent_t)y.scored_event, sr, sa)) rc = MSA_ERR_HIP;
+    if (rc == MSA_OK)
+      rc = msa_sparse_attend(attend_cfg, y.q, y.B, y.M, y.K, y.V, y.idx, k, y.Kloc, y.Vloc, y.Lloc, local_pos0, q_pos,
+                             y.out, y.lse, attend_workspace, attend_workspace_bytes, attend);
+  }
+  // what was enqueued is awaited by the caller whatever the status: the attention stream holds the last of it, except
+  // where a layer was refused between its two halves
+  if (rc != MSA_OK && two) {
+    if (!after((hipEvent_t)join_event, sr, sc)) return MSA_ERR_HIP;
+  }
+  if (!after((hipEvent_t)join_event, sa, sc)) return MSA_ERR_HIP;
+  return rc;
+}
+
 }  // extern "C"
