@@ -40,6 +40,7 @@ struct AttendArgs {
   unsigned long long nonce;     // this launch's tag of the counters (48 bits, non-zero)
   uint16_t* final_out;          // with tickets: the merged output [BM][Hq][D] and (or null) log-sum-exp
   float* final_lse;
+  int lin_per, lin_total;  // decode kernel, linear split: steps per workgroup, steps in all; 0: the grid says it
 };
 
 // Shared-selection prefill: unnormalised partials of every (token, head, split) in the layout the

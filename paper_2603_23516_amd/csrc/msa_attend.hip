@@ -36,7 +36,10 @@
 
 namespace msa {
 
-template <int D, int MODE>
+constexpr int kMaxFused = 8;  // splits that the last-arriving workgroup merges; more are read faster by a launch of
+                              // their own (12 pairs of 97 steps: 16 splits merged here 21 us, 20 by a launch 16 us)
+
+template <int D, int MODE, bool LIN>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attend_partial_kernel(AttendArgs a, RopeTheta th) {
   constexpr int NS = D / 32;        // MFMA k-slices per key row
@@ -57,25 +60,76 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
   // lane-indexed kernel argument is) could only be awaited together with every prefetch in flight
   __shared__ double theta_s[HALF];
 
-  const int tid = threadIdx.x;
+  // Linear split (LIN): the steps of all (query, KV head) pairs in one line, cut into equal ranges, one per
+  // workgroup; a range can end inside a pair and go on with the next (see plan_attend).  Otherwise the grid says it:
+  // (split, KV head, query).
+  int pos = 0, end = 0;
+  if (LIN) {
+    pos = blockIdx.x * a.lin_per;
+    end = pos + a.lin_per < a.lin_total ? pos + a.lin_per : a.lin_total;
+  }
+  for (bool first = true;; first = false) {  // block-uniform
+  // an opaque copy of the thread number: what follows from it would otherwise be worked out once, ahead of this loop, and
+  // kept in registers that the stream inside does not have
+  int tid = threadIdx.x;
+  if (LIN) asm volatile("" : "+v"(tid));
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = LIN ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
   const int rr = lane >> 4;
   const int n = lane & 15;
-  const int sp = blockIdx.x;
-  const int g = blockIdx.y;
-  const int bm = blockIdx.z;
+  int sp = blockIdx.x, g = blockIdx.y, bm = blockIdx.z;
+  int ns = a.ph_splits;  // partials of this pair
+  int lin_sb = 0, lin_se = 0;
+  if (LIN) {
+    const int pair = pos / a.steps_total;
+    lin_sb = pos - pair * a.steps_total;
+    lin_se = lin_sb + (end - pos) < a.steps_total ? lin_sb + (end - pos) : a.steps_total;
+    pos += lin_se - lin_sb;
+    g = pair % a.Hkv;
+    bm = pair / a.Hkv;
+    const int fb = pair * a.steps_total / a.lin_per;  // first workgroup of the pair
+    sp = blockIdx.x - fb;
+    ns = ((pair + 1) * a.steps_total - 1) / a.lin_per - fb + 1;
+  }
   const int b = bm / a.M;
+
+  // ---- everything small is requested together: position, selection, queries, angles (the first keys and values ahead of
+  // the tables that follow measured no faster: 17.4 against 16.8 us at one stream, 67 against 64 at twelve) --------------
+  const float2 e1_u = th.e1[tid % HALF], e16_u = th.e16[tid % HALF];  // (needed first)
+  const double th_u = th.th[tid % HALF];
   const int qpos = a.q_pos[bm];
+  const long long idx_row = (a.idx_rows_per_b == 1) ? b : bm;
+  // selected documents of this (query, KV head): lane j holds idx[j] (k <= 64)
+  const int my_idx = (lane < a.k) ? a.idx[(idx_row * a.idx_sel + (a.idx_sel == 1 ? 0 : g)) * a.k + lane] : -1;
+  constexpr int QE = 8 * HALF / 256;  // pairs of query elements per thread (r <= 8)
+  uint32_t qx1[QE] = {}, qx2[QE] = {};
+  double qth[QE] = {};
+#pragma unroll
+  for (int i = 0; i < QE; ++i) {
+    const int e = tid + 256 * i;
+    if (256 * i >= a.r * HALF) break;  // block-uniform
+    if (e >= a.r * HALF) continue;
+    const int hh = e / HALF, u = e % HALF;
+    const uint16_t* qp = a.q + ((long long)bm * a.Hq + g * a.r + hh) * D;
+    qx1[i] = qp[u];
+    qx2[i] = qp[u + HALF];
+    qth[i] = th.th[u];
+  }
+  // ... and the number of rows that document holds
+  int my_len = a.G;
+  if (a.lens != nullptr && my_idx >= 0 && my_idx < a.N) {
+    const int l = a.lens[my_idx];
+    my_len = l < 1 ? 1 : (l > a.G ? a.G : l);
+  }
   int n_vis = qpos - a.pos0 + 1;  // visible local tokens
   n_vis = n_vis < 0 ? 0 : (n_vis > a.Lloc ? a.Lloc : n_vis);
 
-  // ---- block prologue: rotation tables and rotated queries ------------------------------------
+  // ---- rotation tables and rotated queries --------------------------------------------------------------------
   // base0[n][u] = e^{i n theta_u}, n < 16, by repeated multiplication with the host's e^{i theta_u}
   // (at most 15 fp32 complex products: error ~1e-6, far below the bf16 rounding of the rotated keys)
-  for (int e = tid; e < 4 * HALF; e += 256) {
-    const int u = e % HALF, n4 = e / HALF;  // this thread fills positions 4*n4 .. 4*n4 + 3
-    const float2 w = th.e1[u];
+  if (first && tid < 4 * HALF) {
+    const int u = tid % HALF, n4 = tid / HALF;  // this thread fills positions 4*n4 .. 4*n4 + 3
+    const float2 w = e1_u;
     const float2 w2 = cmul(w, w);
     const float2 w4 = cmul(w2, w2);
     float2 cur = make_float2(1.f, 0.f);
@@ -86,20 +140,23 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
       cur = cmul(cur, w);
     }
   }
-  if (tid < HALF) {
-    step16[tid] = th.e16[tid];
-    theta_s[tid] = th.th[tid];
+  if (first && tid < HALF) {
+    step16[tid] = e16_u;
+    theta_s[tid] = th_u;
   }
-  for (int e = tid; e < a.r * HALF; e += 256) {
-    const int hh = e / HALF, u = e % HALF;
-    const uint16_t* qp = a.q + ((long long)bm * a.Hq + g * a.r + hh) * D;
-    const float x1 = __uint_as_float((uint32_t)qp[u] << 16);
-    const float x2 = __uint_as_float((uint32_t)qp[u + HALF] << 16);
-    const float2 cs = cis_pos(qpos, th.th[u]);
-    qrot[hh][u] = (x1 * cs.x - x2 * cs.y) * a.qscale;
-    qrot[hh][u + HALF] = (x2 * cs.x + x1 * cs.y) * a.qscale;
+#pragma unroll
+  for (int i = 0; i < QE; ++i) {
+    const int e = tid + 256 * i;
+    if (e < a.r * HALF) {
+      const int hh = e / HALF, u = e % HALF;
+      const float x1 = __uint_as_float(qx1[i] << 16);
+      const float x2 = __uint_as_float(qx2[i] << 16);
+      const float2 c = cis_pos(qpos, qth[i]);
+      qrot[hh][u] = (x1 * c.x - x2 * c.y) * a.qscale;
+      qrot[hh][u + HALF] = (x2 * c.x + x1 * c.y) * a.qscale;
+    }
   }
-  __syncthreads();
+  lds_barrier();
 
   // B operand of the score product: column n = head slot (head n/2, hi or lo half)
   bf16x8_t bq[NS];
@@ -133,17 +190,6 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
   constexpr int NVL = 32 * D * 2 / 1024;  // wave-wide 16-byte copies covering 32 value rows
   constexpr int PPR = D / 8;              // 16-byte pieces per row
 
-  // selected documents of this (query, KV head): lane j holds idx[j] (k <= 64)
-  const long long idx_row = (a.idx_rows_per_b == 1) ? b : bm;
-  const int my_idx =
-      (lane < a.k) ? a.idx[(idx_row * a.idx_sel + (a.idx_sel == 1 ? 0 : g)) * a.k + lane] : -1;
-  // ... and the number of rows that document holds
-  int my_len = a.G;
-  if (a.lens != nullptr && my_idx >= 0 && my_idx < a.N) {
-    const int l = a.lens[my_idx];
-    my_len = l < 1 ? 1 : (l > a.G ? a.G : l);
-  }
-
   // ---- this wave's steps -----------------------------------------------------------------------
   // With document lengths (MODE 0, 1) the steps are numbered over what is really there -- slot j
   // contributes ceil(len_j / 32) steps, none for a pad, then come the steps of the visible local rows
@@ -164,8 +210,12 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
     steps_total = mem_steps + ((n_vis + 31) >> 5);
     steps_per_split = (steps_total + a.n_splits - 1) / a.n_splits;
   }
-  const int sb = sp * steps_per_split;
+  int sb = sp * steps_per_split;
   int se = sb + steps_per_split;
+  if (LIN) {
+    sb = lin_sb;
+    se = lin_se;
+  }
   if (se > steps_total) se = steps_total;
   if (se < sb) se = sb;  // nothing left for this block
   int spw = (se - sb + kAttWaves - 1) / kAttWaves;
@@ -550,6 +600,38 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
     }
   }
   __syncthreads();
+  auto combine = [&]() __attribute__((always_inline)) {
+  int tid = threadIdx.x;  // (opaque: nothing of this is worked out ahead of the stream and kept across it)
+  asm volatile("" : "+v"(tid));
+  const int lane = tid & 63, wave = tid >> 6;
+  if (a.tickets != nullptr && ns == 1) {  // the only split: its result is the result
+    for (int e = tid; e < a.r * (D / 2); e += 256) {
+      const int hh = e / (D / 2), d2 = e % (D / 2);
+      const int s0 = 2 * hh;
+      float mx = -INFINITY;
+#pragma unroll
+      for (int w = 0; w < kAttWaves; ++w) mx = fmaxf(mx, wm[w][s0]);
+      float o0 = 0.f, o1 = 0.f, lsum = 0.f;
+      if (mx != -INFINITY) {
+#pragma unroll
+        for (int w = 0; w < kAttWaves; ++w) {
+          const float mw = wm[w][s0];
+          const float f = (mw == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mw - mx);
+          const float2* wo = reinterpret_cast<const float2*>(&stage[w][0]) + d2;
+          const float2 x = wo[s0 * (D / 2)], y = wo[(s0 + 1) * (D / 2)];
+          o0 += f * (x.x + y.x);
+          o1 += f * (x.y + y.y);
+          lsum += f * wl[w][s0];
+        }
+      }
+      const long long qh = (long long)bm * a.Hq + g * a.r + hh;
+      reinterpret_cast<uint32_t*>(a.final_out + qh * D)[d2] =
+          pack_bf16((lsum > 0.f) ? o0 / lsum : 0.f, (lsum > 0.f) ? o1 / lsum : 0.f);
+      if (a.final_lse != nullptr && d2 == 0)
+        a.final_lse[qh] = (lsum > 0.f) ? (mx + log2f(lsum)) * 0.6931471805599453f : -INFINITY;
+    }
+    return;
+  }
   for (int e = tid; e < a.r * D; e += 256) {
     const int hh = e / D, dd = e % D;
     const int s0 = 2 * hh;
@@ -587,20 +669,40 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
   if (tid == 0) {
     unsigned long long* word = a.tickets + (long long)bm * a.Hkv + g;
     const uint32_t before = arrive_at(word, a.nonce);
-    last_s = (before + 1u == (uint32_t)gridDim.x) ? 1 : 0;
+    last_s = (before + 1u == (uint32_t)ns) ? 1 : 0;
   }
   __syncthreads();
   if (!last_s) return;
-  // (m, l) of every (head, split), all loads independent; the staging area is free again (every wave passed the
-  // barriers above after its last use)
-  const int ns = a.ph_splits;
+  // (m, l) of every (head, split) and the partials of the thread's first output elements, all loads independent; the
+  // staging area is free again (every wave passed the barriers above after its last use)
+  // (ns <= kMaxFused)
   float2* mls = reinterpret_cast<float2*>(&stage[0][0]);  // [r][ns]: (max, sum), then (weight, sum)
-  for (int t = tid; t < a.r * ns; t += 256) {
+  auto part_of = [&](int e) {  // a thread owns two adjacent output elements of one head
+    const long long qh = (long long)bm * a.Hq + g * a.r + e / (D / 2);
+    return reinterpret_cast<const unsigned long long*>(a.part_o + qh * a.ph_splits * D) + e % (D / 2);
+  };
+  unsigned long long v[kMaxFused];
+  auto fetch = [&](int e) {
+    const unsigned long long* po = part_of(e < a.r * (D / 2) ? e : 0);
+#pragma unroll
+    for (int u = 0; u < kMaxFused; ++u) v[u] = load_dev(po + (long long)(u < ns ? u : ns - 1) * (D / 2));
+  };
+  unsigned long long ml_v[kMaxFused * 8 / 256 + 1];
+#pragma unroll
+  for (int i = 0; i <= kMaxFused * 8 / 256; ++i) {
+    int t = tid + 256 * i;
+    t = t < a.r * ns ? t : 0;
     const int hh = t / ns, s = t - hh * ns;
     const long long qh = (long long)bm * a.Hq + g * a.r + hh;
-    mls[t] = __builtin_bit_cast(float2, load_dev(reinterpret_cast<const unsigned long long*>(a.part_ml + qh * ns + s)));
+    ml_v[i] = load_dev(reinterpret_cast<const unsigned long long*>(a.part_ml + qh * a.ph_splits + s));
   }
-  __syncthreads();
+  fetch(tid);
+#pragma unroll
+  for (int i = 0; i <= kMaxFused * 8 / 256; ++i) {
+    const int t = tid + 256 * i;
+    if (t < a.r * ns) mls[t] = __builtin_bit_cast(float2, ml_v[i]);
+  }
+  lds_barrier();
   for (int hh = wave; hh < a.r; hh += kAttWaves) {  // one wave per head: maximum, weights, normaliser
     float mx = -INFINITY;
     for (int s = lane; s < ns; s += 64) mx = fmaxf(mx, mls[hh * ns + s].x);
@@ -608,10 +710,10 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
     float lsum = 0.f;
     for (int s = lane; s < ns; s += 64) {
-      const float2 v = mls[hh * ns + s];
-      const float f = (v.x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(v.x - mx);
+      const float2 x = mls[hh * ns + s];
+      const float f = (x.x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(x.x - mx);
       mls[hh * ns + s].x = f;
-      lsum += f * v.y;
+      lsum += f * x.y;
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
@@ -620,29 +722,20 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
       wl[0][hh] = lsum;
     }
   }
-  __syncthreads();
-  for (int e = tid; e < a.r * (D / 2); e += 256) {  // a thread owns two adjacent output elements of one head
+  lds_barrier();
+  for (int e = tid; e < a.r * (D / 2); e += 256) {
     const int hh = e / (D / 2), d2 = e % (D / 2);
     const long long qh = (long long)bm * a.Hq + g * a.r + hh;
-    const unsigned long long* po = reinterpret_cast<const unsigned long long*>(a.part_o + qh * ns * D) + d2;
     const float2* w = mls + hh * ns;
+    if (e != tid) fetch(e);
     float o0 = 0.f, o1 = 0.f;
-    int s = 0;
-    for (; s + 8 <= ns; s += 8) {
-      unsigned long long v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = load_dev(po + (long long)(s + u) * (D / 2));
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
+    for (int u = 0; u < kMaxFused; ++u) {
+      if (u < ns) {
         const float2 x = __builtin_bit_cast(float2, v[u]);
-        o0 += w[s + u].x * x.x;
-        o1 += w[s + u].x * x.y;
+        o0 += w[u].x * x.x;
+        o1 += w[u].x * x.y;
       }
-    }
-    for (; s < ns; ++s) {
-      const float2 x = __builtin_bit_cast(float2, load_dev(po + (long long)s * (D / 2)));
-      o0 += w[s].x * x.x;
-      o1 += w[s].x * x.y;
     }
     const float lsum = wl[0][hh], mx = wm[0][hh];
     const float r0 = (lsum > 0.f) ? o0 / lsum : 0.f, r1 = (lsum > 0.f) ? o1 / lsum : 0.f;
@@ -651,6 +744,11 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
       a.final_lse[qh] = (lsum > 0.f) ? (mx + log2f(lsum)) * 0.6931471805599453f : -INFINITY;
   }
   if (tid == 0) store_dev(a.tickets + (long long)bm * a.Hkv + g, 0ull);  // ready for a replay of this launch
+  };
+  combine();
+  if (!LIN || pos >= end) return;  // block-uniform
+  lds_barrier();  // the next pair takes over the staging areas and tables
+  }
 }
 
 // Log-sum-exp merge of the split partials of one (query, head); one thread per output element.
@@ -750,6 +848,7 @@ AttendPlan plan_attend(const Dims& dm, int B, int M, int k, int Lloc, int bank_k
   p.split_local = (!p.prefill && M >= 16 && Lloc >= 32 &&
                    (dm.r == 1 || dm.r == 2 || dm.r == 4 || dm.r == 8)) ? 1 : 0;
   p.mem_splits = p.loc_splits = 0;
+  p.lin_per = p.lin_blocks = 0;
   p.mem_steps_per_split = p.loc_steps_per_split = 0;
   if (p.split_local) {
     p.tpw = 32 / dm.r;
@@ -759,15 +858,53 @@ AttendPlan plan_attend(const Dims& dm, int B, int M, int k, int Lloc, int bank_k
                          &p.loc_steps_per_split);
     p.n_splits = p.mem_splits + p.loc_splits;
     p.steps_per_split = p.mem_steps_per_split;
-  } else {
+  } else if (p.prefill || p.steps_total == 0) {
     p.n_splits = split(p.steps_total, pairs, kAttWaves, kMaxAttSplits, &p.steps_per_split);
+  } else {
+    // Decode kernel alone (documents of full length: the work of every workgroup is known; with lengths this is the most
+    // it can be).  A CU streams as fast with one workgroup of the d = 128 kernel as with two, so the chip counts as 256 places (512 at d = 64), and a grid of P n
+    // workgroups of `per` steps takes ceil(P n / places) rounds of per + 8 steps (8: prologue and merge).  The candidates
+    // are the largest n of one to four rounds, and the most splits that merge without a launch of their own.
+    const long long S = p.steps_total, places = dm.d == 128 ? 256 : 512;
+    long long best = -1, best_n = 1;
+    for (int i = 0; i <= 5; ++i) {
+      long long n = i == 0 ? 1 : (i == 5 ? kMaxFused : i * places / pairs);
+      if (n > S / kAttWaves) n = S / kAttWaves;
+      if (n > kMaxAttSplits) n = kMaxAttSplits;
+      if (n < 1) n = 1;
+      const long long per = (S + n - 1) / n;
+      const long long wave_steps = ((per + kAttWaves - 1) / kAttWaves + 1) / 2 * 2;  // two steps per trip of the loop
+      const long long rounds = (pairs * n + places - 1) / places;
+      // (short workgroups wait for latencies more than for the memory: a second one in the CU costs half)
+      const long long stream = wave_steps * kAttWaves * (per <= 16 ? rounds + 1 : 2 * rounds) / 2;
+      const long long cost = stream + (per <= 16 ? (rounds + 1) / 2 : rounds) * 8 + (n > kMaxFused ? 4 : 0);
+      if (best < 0 || cost < best) {
+        best = cost;
+        best_n = n;
+      }
+    }
+    p.steps_per_split = (int)((S + best_n - 1) / best_n);
+    p.n_splits = (int)((S + p.steps_per_split - 1) / p.steps_per_split);
+    // Documents of full length: where that leaves places idle (360 workgroups in two rounds of 256) and a place's share is worth it, the steps of
+    // all pairs in one line are cut into equal ranges, one per place, whatever pairs they end in (measured, d = 128, 45
+    // streams of 376 steps: 432 -> 359 us; 20 of 289: 161 -> 130; 12 of 216: 83 -> 64; d = 64, 37 of 245: 133 -> 99.
+    // With shares below 64 steps the second prologue costs more than the round: 8 pooled streams of 36 steps 19 -> 31.)
+    const long long total = S * pairs, share = total / places + 8;
+    long long per = ((total + places - 1) / places + 7) / 8 * 8;
+    const long long slots = (S - 1) / per + 2;  // workgroups that can meet in one pair
+    if (dm.lens == nullptr && total >= 64 * places && total < (1ll << 30) && pairs < 8 * places &&
+        best * 100 > share * 115 && slots <= kMaxFused) {
+      p.lin_per = (int)per;
+      p.lin_blocks = (int)((total + per - 1) / per);
+      p.n_splits = (int)slots;
+    }
   }
   const size_t o_bytes = round_up256((size_t)BM * dm.Hq * p.n_splits * dm.d * sizeof(float));
   p.off_ml = o_bytes;
   p.ws_bytes = o_bytes + round_up256((size_t)BM * dm.Hq * p.n_splits * sizeof(float2));
   // decode kernel alone: its last-arriving workgroup per (query, KV head) merges the splits, no merge launch
   // (few splits only: with many, the separate merge launch, one workgroup per head, is the faster way to read them)
-  p.fused_merge = (!p.prefill && !p.split_local && p.n_splits <= 16) ? 1 : 0;
+  p.fused_merge = (!p.prefill && !p.split_local && p.n_splits <= kMaxFused) ? 1 : 0;
   p.off_tickets = p.ws_bytes;
   if (p.fused_merge) p.ws_bytes += round_up256((size_t)BM * dm.Hkv * sizeof(unsigned long long));
   // the tiled kernel reads keys that were rotated once per (batch row, KV head): all steps of a shared
@@ -803,6 +940,7 @@ int launch_attend(const Dims& dm, const AttendPlan& pl, const void* q, int B, in
                   const void* V, const int32_t* idx, int k, const void* Kloc, const void* Vloc,
                   int Lloc, int pos0, const int32_t* q_pos, void* out, float* lse, void* ws,
                   int bank_keys_rotated, hipStream_t st) {
+  const int BM = B * M;
   AttendArgs a;
   a.q = (const uint16_t*)q;
   a.K = (const uint16_t*)K;
@@ -837,6 +975,8 @@ int launch_attend(const Dims& dm, const AttendPlan& pl, const void* q, int B, in
   a.steps_per_split = pl.steps_per_split;
   a.n_splits = pl.n_splits;
   a.ph_splits = pl.n_splits;
+  a.lin_per = pl.lin_per;
+  a.lin_total = pl.lin_per > 0 ? pl.steps_total * BM * dm.Hkv : 0;
   a.split0 = 0;
   a.qscale = (float)(1.4426950408889634 / sqrt((double)dm.d));
   a.tickets = pl.fused_merge ? (unsigned long long*)((char*)ws + pl.off_tickets) : nullptr;
@@ -844,7 +984,6 @@ int launch_attend(const Dims& dm, const AttendPlan& pl, const void* q, int B, in
   a.final_out = (uint16_t*)out;
   a.final_lse = lse;
   const RopeTheta& th = rope_table(dm.base, dm.d);
-  const int BM = B * M;
   // how the bank is read (checked before anything is enqueued)
   const int mode = !bank_keys_rotated ? 0 : (dm.G % 32 == 0 ? 1 : 2);
   if (mode != 2 && dm.G % 32 != 0) return MSA_ERR_UNSUPPORTED;
@@ -873,9 +1012,13 @@ int launch_attend(const Dims& dm, const AttendPlan& pl, const void* q, int B, in
     if (rc != MSA_OK) return rc;
   } else {
     profile_mark(dm, false, st);
-    dim3 grid(a.n_splits, dm.Hkv, BM), block(256);
+    const dim3 grid = pl.lin_per > 0 ? dim3(pl.lin_blocks) : dim3(a.n_splits, dm.Hkv, BM);
+    const dim3 block(256);
 #define MSA_LAUNCH_ATTEND(DD, MM) \
-  hipLaunchKernelGGL((attend_partial_kernel<DD, MM>), grid, block, 0, st, a, th)
+  do { \
+    if (pl.lin_per > 0) hipLaunchKernelGGL((attend_partial_kernel<DD, MM, true>), grid, block, 0, st, a, th); \
+    else hipLaunchKernelGGL((attend_partial_kernel<DD, MM, false>), grid, block, 0, st, a, th); \
+  } while (0)
     if (dm.d == 128) {
       if (mode == 0) MSA_LAUNCH_ATTEND(128, 0);
       else if (mode == 1) MSA_LAUNCH_ATTEND(128, 1);

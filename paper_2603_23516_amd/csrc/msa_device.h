@@ -197,32 +197,26 @@ __device__ __forceinline__ void lds_barrier() {
 // Workgroups that produced parts of one result count themselves in; the one that arrives last combines the
 // parts.  The 64-bit word holds (nonce << 16 | arrivals); a word whose upper 48 bits are not this call's nonce
 // is a leftover (the caller's workspace has undefined contents) and counts as zero arrivals, so nothing has
-// to be cleared before the launch.  The first arrival installs the nonce with a compare-exchange; every later
-// one sees the nonce and counts itself with a plain fetch-add (arrivals that come together are then served by
-// the memory's atomic unit back to back instead of retrying one after the other).  Returns the number of
-// arrivals BEFORE this one.  Every path ends: an exchange fails only because another arrival installed the
-// nonce, after which the fetch-add path is taken.  The last arrival stores 0 when it is done, which keeps
-// replays of a captured launch (same nonce every time) correct.  nonce48 != 0; fewer than 65536 participants.
+// to be cleared before the launch.  Every arrival adds one first: where the word already carries the nonce that is
+// all (one round trip to the memory's atomic unit; a load ahead of it made it two).  An arrival that added to a leftover
+// is not counted by that; it installs the nonce with a compare-exchange, or finds it installed and adds again.  Returns
+// the number of arrivals BEFORE this one.  Every path ends: an exchange fails only because another arrival changed the
+// word, each does so to a leftover at most once, and one of them installs the nonce.  The last arrival stores 0 when it
+// is done, which keeps replays of a captured launch (same nonce every time) correct.  nonce48 != 0; fewer than 65536
+// participants.
 __device__ __forceinline__ uint32_t arrive_at(unsigned long long* word, unsigned long long nonce48) {
-  unsigned long long old = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if ((old >> 16) != nonce48) {
-    const unsigned long long first = (nonce48 << 16) | 1ull;
-    if (__hip_atomic_compare_exchange_strong(word, &old, first, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+  unsigned long long old = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if ((old >> 16) == nonce48) return (uint32_t)(old & 0xffffull);
+  old += 1ull;  // what this arrival left there
+  for (;;) {
+    if (__hip_atomic_compare_exchange_strong(word, &old, (nonce48 << 16) | 1ull, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT))
       return 0u;
-    if ((old >> 16) != nonce48) {
-      // the word changed between the load and the exchange without the nonce appearing: it can only have been
-      // a foreign write (the workspace is shared with something else); fall back to the exchange loop
-      for (;;) {
-        const uint32_t cnt = ((old >> 16) == nonce48) ? (uint32_t)(old & 0xffffull) : 0u;
-        if (__hip_atomic_compare_exchange_strong(word, &old, (nonce48 << 16) | (unsigned long long)(cnt + 1u),
-                                                 __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-          return cnt;
-      }
+    if ((old >> 16) == nonce48) {
+      old = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return (uint32_t)(old & 0xffffull);
     }
   }
-  old = __hip_atomic_fetch_add(word, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return (uint32_t)(old & 0xffffull);
 }
 
 }  // namespace msa

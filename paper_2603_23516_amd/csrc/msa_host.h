@@ -112,6 +112,8 @@ struct AttendPlan {
   int steps_total;       // + ceil(Lloc / 32)
   int steps_per_split;
   int n_splits;
+  int lin_per, lin_blocks;  // > 0: linear split of the decode kernel, steps per workgroup and workgroups (n_splits then
+                            // is the most workgroups that can meet in one (query, KV head) pair)
   int prefill;           // 1: shared selection and many tokens -> attend_prefill_kernel
   int split_local;       // 1: per-token selections and many tokens: the selected documents go through the decode
                          //    kernel, the local context (shared by the tokens) through attend_prefill_kernel

@@ -156,3 +156,52 @@ def test_pool_chunks_by_pairs(N, Hkv, G, P, d, first, count):
                     rows = X[i, :, j * P:min(n, (j + 1) * P)]
                     want = rows.mean(1) if rows.shape[1] else np.zeros((Hkv, d))
                     assert np.abs(got[i, :, j] - want).max() <= 2.0 ** -8 * np.abs(want).max() + 1e-5
+
+
+# (N, Hkv, r, G, d, B, M, k, Lloc, scope): the decode kernel's linear split, ranges that end inside pairs
+ATT_LINEAR = [
+    (40, 8, 4, 512, 128, 20, 1, 18, 5, "group"),      # 160 pairs of 289 steps in ranges of 184
+    (33, 8, 1, 512, 128, 45, 1, 20, 1791, "all"),     # 360 pairs of 376 in ranges of 536: one spans three pairs
+    (25, 2, 2, 256, 64, 150, 2, 21, 130, "group"),    # d = 64, two query tokens with selections of their own
+]
+
+
+@pytest.mark.parametrize("N,Hkv,r,G,d,B,M,k,Lloc,scope", ATT_LINEAR)
+def test_decode_attention_linear_split(N, Hkv, r, G, d, B, M, k, Lloc, scope):
+    """Against the oracle on some queries, and every query against the same call with one query alone (another split);
+    a pad and queries that see only a part of the local context among them."""
+    say(f"linear split N={N} Hkv={Hkv} r={r} G={G} d={d} B={B} M={M} k={k} Lloc={Lloc} {scope}")
+    cfg = msa.MsaConfig(N, G, G, Hkv * r, Hkv, d, 1e6, select_scope=msa.MSA_SCOPE_ALL if scope == "all" else msa.MSA_SCOPE_GROUP)
+    S_ = 1 if scope == "all" else Hkv
+    Kb, K = S.normal_bf16(56000, (N, Hkv, G, d))
+    Vb, V = S.normal_bf16(56001, (N, Hkv, G, d))
+    qb, q = S.normal_bf16(56002, (B, M, Hkv * r, d))
+    Klb, Kl = S.normal_bf16(56003, (B, Hkv, Lloc, d))
+    Vlb, Vl = S.normal_bf16(56004, (B, Hkv, Lloc, d))
+    rng = np.random.default_rng(56005)
+    idx = np.argsort(rng.random((B, M, S_, N)), axis=-1)[..., :k].astype(np.int32)
+    idx[:, :, :, k - 1] = -1
+    q_pos = G + rng.integers(-1, Lloc, (B, M)).astype(np.int32)
+    args = [dev(Kb), dev(Vb), torch.from_numpy(idx).cuda(), dev(Klb), dev(Vlb), G, torch.from_numpy(q_pos).cuda()]
+    ws = torch.full((msa.sparse_attend_workspace_bytes(cfg, B, M, k, Lloc),), 0xA5, dtype=torch.uint8, device="cuda")
+    dq = dev(qb)
+    out, lse = msa.msa_sparse_attend(cfg, dq, *args, workspace=ws)
+    again, lse2 = msa.msa_sparse_attend(cfg, dq, *args, workspace=ws)   # the arrival counters are ready for a replay
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), again.view(torch.int16)) and torch.equal(lse, lse2)
+    for b in range(B):
+        sl = slice(b, b + 1)
+        one, l1 = msa.msa_sparse_attend(cfg, dq[sl].clone(), args[0], args[1], args[2][sl].clone(), args[3][sl].clone(),
+                                        args[4][sl].clone(), G, args[6][sl].clone())
+        torch.cuda.synchronize()
+        # the same fp32 sums in another order, rounded to bf16 once: neighbours at most, which lie up to 2^-7 of the value
+        # apart (8 significant bits, at the low end of a binade)
+        x, y = out[b].float(), one[0].float()
+        assert (x - y).abs().max() <= 2.0 ** -7 * y.abs().max() + 1e-6
+        assert (lse[b] - l1[0]).abs().max() <= 1e-4
+    for b in (0, B // 2, B - 1):
+        oo, ol = O.sparse_attend(q[b:b + 1], K, V, idx[b:b + 1].astype(np.int64), Kl[b:b + 1], Vl[b:b + 1], G,
+                                 q_pos[b:b + 1], 1e6)
+        go = out[b:b + 1].float().cpu().numpy().astype(np.float64)
+        assert np.abs(go - oo).max() <= 2e-2 and np.linalg.norm(go - oo) <= 5e-3 * np.linalg.norm(oo)
+        assert np.allclose(lse[b:b + 1].cpu().numpy(), ol, rtol=0, atol=5e-3)
