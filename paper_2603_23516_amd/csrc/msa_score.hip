@@ -732,10 +732,11 @@ __global__ __launch_bounds__(64 * kAllWaves) void score_scan_all_kernel(ScanAllA
   const long long units = (a.seg_tiles + umask) >> a.ushift;
   const long long n_it = w < units ? ((units - w + W - 1) / W) << a.ushift : 0;  // tiles of this wave
   const uint16_t* KRl = a.KR + lane * 8;
-  // dot product: the loads of the reciprocal norms run all the same (from the index, inside it: a tile has more bytes
-  // than its norms), so that the loads in flight are the same on every path, and a one takes their place
+  // dot product: the loads of the reciprocal norms run all the same (from the first bytes of the index, always the
+  // same), so that the loads in flight are the same on every path, and a one takes their place
   const bool cos = a.inv_norm != nullptr;
   const float* inl = (cos ? a.inv_norm : reinterpret_cast<const float*>(a.KR)) + n;
+  const long long inv_stride = cos ? 16 : 0;
   // tile number inside the segment; past the wave's end or the segment's: see clamp below
   auto tile_at = [&](long long it) { return ((w + (it >> a.ushift) * W) << a.ushift) + (it & umask); };
   auto load_at = [&](long long it) {  // always a tile of the index
@@ -755,7 +756,7 @@ __global__ __launch_bounds__(64 * kAllWaves) void score_scan_all_kernel(ScanAllA
 #pragma unroll
     for (int s = 0; s < NS; ++s)
       buf[u][s] = load_tile16(KRl + ((long long)h * a.tiles + t) * TILE_ELEMS + s * 512);
-    binv[u] = inl[((long long)h * a.tiles + t) * 16];
+    binv[u] = inl[((long long)h * a.tiles + t) * inv_stride];
   }
   wait_copies_but<kPrefetch * (NS + 1)>();  // the operands are older than the tiles
   lds_barrier();
@@ -804,7 +805,7 @@ __global__ __launch_bounds__(64 * kAllWaves) void score_scan_all_kernel(ScanAllA
 #pragma unroll
           for (int s = 0; s < NS; ++s)
             buf[slot][s] = load_tile16(KRl + ((long long)hn * a.tiles + tn) * TILE_ELEMS + s * 512);
-          binv[slot] = inl[((long long)hn * a.tiles + tn) * 16];
+          binv[slot] = inl[((long long)hn * a.tiles + tn) * inv_stride];
         }
 #pragma unroll
         for (int tq = 0; tq < NQT; ++tq) {
@@ -986,7 +987,7 @@ __global__ __launch_bounds__(kPoolThreads) void pool_tokens_kernel(const unsigne
 // Top-k of the rows of a document score matrix (MODE 2 of the scan, all-heads scan).  One workgroup per (row, part
 // of the row).
 //   1. every thread takes the best score of its strided share of the part; every wave finds (a lower bound
-//      on) the k-th best of its 64 lane maxima by a bitwise search with ballots, and the largest of the four
+//      on) the k-th best of its 64 lane maxima by a bitwise search with ballots, and the largest of the
 //      waves' bounds is a lower bound theta on the k-th best score of the part: some wave holds k distinct
 //      documents scoring at least that much;
 //   2. every document scoring >= theta goes to LDS (a few k of them) and is ranked by counting on the full
@@ -1013,12 +1014,13 @@ struct RowsArgs {
   unsigned long long* part_keys; // not null: sorted keys per part, [n_sel][BM][parts_total][k]
 };
 
-template <int REGS>
-__global__ __launch_bounds__(256) void topk_rows_kernel(RowsArgs a) {
+template <int REGS, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void topk_rows_kernel(RowsArgs a) {
   __shared__ unsigned long long surv[kRowSurv + 8];
-  __shared__ unsigned long long red[4];
-  __shared__ uint32_t theta_w[4];
+  __shared__ unsigned long long red[WAVES];
+  __shared__ uint32_t theta_w[WAVES];
   __shared__ int n_surv;
+  constexpr int THREADS = 64 * WAVES;
   const int tid = threadIdx.x;
   const int k = a.k;
   const int part = blockIdx.x % a.parts;
@@ -1033,16 +1035,16 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(RowsArgs a) {
   unsigned long long best = 0ull;
 #pragma unroll
   for (int u = 0; u < REGS; ++u) {
-    const int i = u * 256 + tid;
+    const int i = u * THREADS + tid;
     v[u] = (i < N) ? row[i] : 0.f;
   }
 #pragma unroll
   for (int u = 0; u < REGS; ++u) {
-    const int i = u * 256 + tid;
+    const int i = u * THREADS + tid;
     const unsigned long long x = (i < N) ? make_key(v[u], doc0 + i) : 0ull;
     best = x > best ? x : best;
   }
-  for (int i = REGS * 256 + tid; i < N; i += 256) {  // rows longer than the register share
+  for (int i = REGS * THREADS + tid; i < N; i += THREADS) {  // rows longer than the register share
     const unsigned long long x = make_key(row[i], doc0 + i);
     best = x > best ? x : best;
   }
@@ -1059,9 +1061,9 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(RowsArgs a) {
   }
   if (tid == 0) n_surv = 0;
   __syncthreads();
-  const uint32_t th01 = theta_w[0] > theta_w[1] ? theta_w[0] : theta_w[1];
-  const uint32_t th23 = theta_w[2] > theta_w[3] ? theta_w[2] : theta_w[3];
-  const uint32_t theta = th01 > th23 ? th01 : th23;
+  uint32_t theta = theta_w[0];
+#pragma unroll
+  for (int w = 1; w < WAVES; ++w) theta = theta_w[w] > theta ? theta_w[w] : theta;
   auto keep = [&](unsigned long long x) {
     if (x != 0ull && (uint32_t)(x >> 32) >= theta) {
       const int slot = atomicAdd(&n_surv, 1);
@@ -1070,10 +1072,10 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(RowsArgs a) {
   };
 #pragma unroll
   for (int u = 0; u < REGS; ++u) {
-    const int i = u * 256 + tid;
+    const int i = u * THREADS + tid;
     keep((i < N) ? make_key(v[u], doc0 + i) : 0ull);
   }
-  for (int i = REGS * 256 + tid; i < N; i += 256) keep(make_key(row[i], doc0 + i));
+  for (int i = REGS * THREADS + tid; i < N; i += THREADS) keep(make_key(row[i], doc0 + i));
   __syncthreads();
   const int ns = n_surv;
   const long long o_base = a.part_keys
@@ -1092,7 +1094,7 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(RowsArgs a) {
   if (ns <= kRowSurv) {
     if (tid < 8) surv[ns + tid] = 0ull;  // the rank count below reads eight at a time (zero: greater than no key)
     __syncthreads();
-    for (int i = tid; i < ns; i += 256) {
+    for (int i = tid; i < ns; i += THREADS) {
       const unsigned long long x = surv[i];
       int rank = 0;
       for (int j = 0; j < ns; j += 8) {
@@ -1104,13 +1106,13 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(RowsArgs a) {
       }
       if (rank < k) emit(rank, x);
     }
-    for (int i = ns + tid; i < k; i += 256) emit(i, 0ull);  // fewer than k documents (a short part)
+    for (int i = ns + tid; i < k; i += THREADS) emit(i, 0ull);  // fewer than k documents (a short part)
     return;
   }
   unsigned long long prev = ~0ull;
   for (int round = 0; round < k; ++round) {
     unsigned long long bst = 0ull;
-    for (int i = tid; i < N; i += 256) {
+    for (int i = tid; i < N; i += THREADS) {
       const unsigned long long x = make_key(row[i], doc0 + i);
       if (x < prev && x > bst) bst = x;
     }
@@ -1124,17 +1126,25 @@ __global__ __launch_bounds__(256) void topk_rows_kernel(RowsArgs a) {
     __syncthreads();
     bst = red[0];
 #pragma unroll
-    for (int w = 1; w < 4; ++w) bst = red[w] > bst ? red[w] : bst;
+    for (int w = 1; w < WAVES; ++w) bst = red[w] > bst ? red[w] : bst;
     if (tid == 0) emit(round, bst);
     prev = bst ? bst : 0ull;
   }
 }
 
+// Waves per workgroup: sixteen where the rows leave the chip idle anyway (one round of 256 workgroups or fewer) and a row
+// is longer than four waves hold in registers: 32768 scores at once.  One workgroup then takes a row that went in parts
+// with a merge launch behind: 30000 documents of 64 dims, 2 queries, whole call 27.4 -> 24.6 us; 20000 of 128, one query,
+// 71.8 -> 68.
 static void launch_topk_rows(const RowsArgs& ra, hipStream_t st) {
   const unsigned blocks = (unsigned)(ra.BM * ra.n_sel * ra.parts);
   const int n = ra.n_docs < ra.part_docs ? ra.n_docs : ra.part_docs;
-  if (n <= 8 * 256) hipLaunchKernelGGL(topk_rows_kernel<8>, dim3(blocks), dim3(256), 0, st, ra);
-  else hipLaunchKernelGGL(topk_rows_kernel<kRowRegs>, dim3(blocks), dim3(256), 0, st, ra);
+#define MSA_TOPK_ROWS(RR, WW) \
+  hipLaunchKernelGGL((topk_rows_kernel<RR, WW>), dim3(blocks), dim3(64 * WW), 0, st, ra)
+  if (n <= 8 * 256) MSA_TOPK_ROWS(8, 4);
+  else if (blocks > 256 || n <= kRowPart) MSA_TOPK_ROWS(kRowRegs, 4);
+  else MSA_TOPK_ROWS(kRowRegs, 16);
+#undef MSA_TOPK_ROWS
 }
 
 // Combine the n_lists sorted lists (k entries each, zero-padded) of one (query, group).
@@ -1287,38 +1297,40 @@ __global__ __launch_bounds__(256) void score_merge_kernel(const unsigned long lo
   }
 }
 
-// One wave per (tile of 8 queries, KV head): fold the r heads of the group into one fp32 routing
+// One workgroup per (tile of 8 queries, KV head), a wave per 512 / D of its queries: fold the r heads of the group into one fp32 routing
 // query per token,  qf = (1/r) sum_h q_h / max(|q_h|, 1e-12)  (plain mean for the dot product), split it
 // into bf16 hi + lo and store the MFMA A operands of the tile: lane 16q + n holds row n (query n/2,
 // hi for even n, lo for odd n), dims 32s + 8q .. +8 of slice s.  Also resets the threshold-exchange
 // buffer of the scan to -inf.
 template <int D>
-__global__ __launch_bounds__(64) void prep_scan_operands_kernel(const uint16_t* __restrict__ q_route,
+__global__ __launch_bounds__(64 * (D / 64)) void prep_scan_operands_kernel(const uint16_t* __restrict__ q_route,
                                                                 uint4* __restrict__ qop, int BM, int Hq,
                                                                 int Hkv, int r, int cos, int n_qtiles,
                                                                 float* __restrict__ gmax, long long n_gmax) {
-  constexpr int NS = D / 32, LPH = D / 8, HPL = 64 / LPH;
+  constexpr int NS = D / 32, LPH = D / 8, HPL = 64 / LPH, WAVES = 8 / HPL;
   __shared__ float qf[8][D];
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int qt = blockIdx.x % n_qtiles;
   const int g = blockIdx.x / n_qtiles;
   if (gmax != nullptr) {
-    for (long long i = (long long)blockIdx.x * 64 + lane; i < n_gmax; i += (long long)gridDim.x * 64)
+    for (long long i = (long long)blockIdx.x * (64 * WAVES) + threadIdx.x; i < n_gmax;
+         i += (long long)gridDim.x * (64 * WAVES))
       gmax[i] = -INFINITY;
   }
   // Lane = (query lane / LPH, 16-byte piece lane % LPH): a lane loads the same piece of all r heads of
   // its query, so the head sum stays in the lane and the norms need only DPP sums over LPH <= 16 lanes.
   const int piece = lane % LPH;
-#pragma unroll
-  for (int pass = 0; pass < 8 / HPL; ++pass) {
-    const int qi = pass * HPL + lane / LPH;
-    const long long qg = (long long)qt * 8 + qi;
+  {
+    const int qi = wave * HPL + lane / LPH;
+    const bool live = (long long)qt * 8 + qi < BM;
+    const long long qg = live ? (long long)qt * 8 + qi : BM - 1;
+    // no branch around a load (rows past the end re-read the last query, heads past r the last head): all are in
+    // flight together
     uint4 v[8];
 #pragma unroll
     for (int hh = 0; hh < 8; ++hh) {
-      v[hh] = make_uint4(0, 0, 0, 0);
-      if (qg < BM && hh < r)
-        v[hh] = *reinterpret_cast<const uint4*>(q_route + (qg * Hq + g * r + hh) * D + piece * 8);
+      const int hc = hh < r ? hh : r - 1;
+      v[hh] = *reinterpret_cast<const uint4*>(q_route + (qg * Hq + g * r + hc) * D + piece * 8);
     }
     float f[8];
 #pragma unroll
@@ -1338,12 +1350,13 @@ __global__ __launch_bounds__(64) void prep_scan_operands_kernel(const uint16_t* 
       }
     }
 #pragma unroll
-    for (int e = 0; e < 8; ++e) qf[qi][piece * 8 + e] = f[e] / (float)r;
+    for (int e = 0; e < 8; ++e) qf[qi][piece * 8 + e] = live ? f[e] / (float)r : 0.f;
   }
-  wave_sync();
+  __syncthreads();
   const int rr = lane >> 4, n = lane & 15;
 #pragma unroll
-  for (int s = 0; s < NS; ++s) {
+  for (int sw = 0; sw < NS / WAVES; ++sw) {
+    const int s = sw * WAVES + wave;
     uint32_t w[4];
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj) {
@@ -1371,7 +1384,7 @@ static void add_token_pool(const Dims& dm, int BM, int k, ScorePlan* p) {
 
 // All-heads scan: one pass of up to 32 queries (more take the wide kernel) over segments of the bank; the score matrix
 // of one segment stays under 24 MB, which bounds the workspace and keeps the matrix in the cache behind the L2s between
-// the scan that writes it and the selection that reads it.  Rows beyond 16384 documents are selected from in parts of 8192 (one
+// the scan that writes it and the selection that reads it.  Rows beyond 32768 documents are selected from in parts of 8192 (one
 // workgroup each) whose lists the merge kernel combines; up to there one workgroup per row, without the merge launch,
 // is the faster way.
 static void plan_all_heads(const Dims& dm, int BM, int k, ScorePlan* p) {
@@ -1382,9 +1395,9 @@ static void plan_all_heads(const Dims& dm, int BM, int k, ScorePlan* p) {
   p->off_gmax = 0;
   p->n_pass = 1;
   p->q_per_pass = BM <= 8 ? 8 : (BM <= 16 ? 16 : 32);
-  p->part_docs = dm.N <= 2 * kRowPart ? dm.N : kRowPart;
+  p->part_docs = dm.N <= 4 * kRowPart ? dm.N : kRowPart;
   long long seg = kMatBytes / (4 * p->q_per_pass) / p->part_docs * p->part_docs;
-  if (seg > dm.N || dm.N <= 2 * kRowPart) seg = dm.N;
+  if (seg > dm.N || dm.N <= 4 * kRowPart) seg = dm.N;
   p->seg_docs = (int)seg;
   p->n_splits = (dm.N + p->part_docs - 1) / p->part_docs;  // parts of a row = lists per query
   size_t end = p->n_splits > 1 ? round_up256((size_t)BM * p->n_splits * k * sizeof(unsigned long long)) : 0;
@@ -1549,7 +1562,7 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
     const long long n_gmax = pl.exchange ? (long long)dm.Hkv * BM * pl.n_splits : 0;
     const unsigned blocks = (unsigned)(pl.n_qtiles * dm.Hkv);
     if (dm.d == 128)
-      hipLaunchKernelGGL(prep_scan_operands_kernel<128>, dim3(blocks), dim3(64), 0, st,
+      hipLaunchKernelGGL(prep_scan_operands_kernel<128>, dim3(blocks), dim3(128), 0, st,
                          (const uint16_t*)q_route, (uint4*)((char*)ws + pl.off_qop), BM, dm.Hq, dm.Hkv,
                          dm.r, dm.cos, pl.n_qtiles, a.gmax, n_gmax);
     else
