@@ -272,7 +272,8 @@ int msa_score_topk_noalloc(const msa_config_t* cfg, const void* q_route, int32_t
   if (misaligned(q_route) || misaligned(KR) || misaligned(inv_norm) || misaligned(out_idx) ||
       misaligned(out_score))
     return MSA_ERR_MISALIGNED;
-  const ScorePlan pl = plan_score(dm, B * M, k);
+  ScorePlan pl = plan_score(dm, B * M, k);
+  if (pl.ws_bytes > kNoAllocScratchBytes) pl = plan_score(dm, B * M, k, true);
   if (pl.ws_bytes > kNoAllocScratchBytes) return MSA_ERR_WORKSPACE;  // beyond the built-in scratch
   void* ws = nullptr;
   const int rs = scratch_on_current_device(&ws);

@@ -43,7 +43,7 @@ struct GemmPlan {
 };
 constexpr int kFilterMaxCand = 64;
 bool gemm_path_applies(const Dims& dm, int BM, int k);
-GemmPlan plan_score_gemm(const Dims& dm, int BM, int k);
+GemmPlan plan_score_gemm(const Dims& dm, int BM, int k, bool small);
 // Enqueues the scoring kernels.  Without the filter the per-split lists are left for score_merge_kernel.  With it
 // the exact winners of every token are written to out_idx / out_score (or out_key: sorted 64-bit keys, token pooling),
 // and the lists of the flagged token blocks are left for a merge that is gated by *gate_flags (device int32
@@ -99,7 +99,8 @@ struct ScorePlan {
   GemmPlan gemm;
   size_t ws_bytes;
 };
-ScorePlan plan_score(const Dims& dm, int BM, int k);
+// small: fewer, longer splits where the usual ones need more workspace than the built-in scratch holds.
+ScorePlan plan_score(const Dims& dm, int BM, int k, bool small = false);
 
 // record the caller's per-call events (msa_config_t.profile_*_event) around the dominant kernel; null = off
 inline void profile_mark(const Dims& dm, bool stop, hipStream_t st) {

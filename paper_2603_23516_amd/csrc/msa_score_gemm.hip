@@ -649,14 +649,19 @@ bool gemm_path_applies(const Dims& dm, int BM, int k) {
   return (dm.C == 4 || dm.C == 8 || dm.C == 16) && k <= kGemmMaxK && BM >= 64;
 }
 
-GemmPlan plan_score_gemm(const Dims& dm, int BM, int k) {
+// The lists of the usual plan are bounded by the workgroups in flight, not by the sizes: two per CU, each with two lists
+// of 8 or 16 entries for every one of its tokens (16 entries, two token blocks per wave: 32 MiB and the folded queries
+// on top).  `small` halves that for callers with a fixed buffer: one block per wave at 16 entries and, up to k = 16 (above,
+// the filter needs the splits), splits of at least 32 stages.  (The filter applies to both or to neither: the scores are
+// the same bits.)
+GemmPlan plan_score_gemm(const Dims& dm, int BM, int k, bool small) {
   GemmPlan p;
   const int tokens_per_wg = (k <= 8) ? 256 : 128;
   p.n_qblocks = (BM + tokens_per_wg - 1) / tokens_per_wg;
   // The one-pass form has the registers for two blocks per wave at either list length (every key read from LDS then
   // serves 64 tokens; 2048 tokens, 32768 documents, k = 16: call 1425 -> 1346 us).  Up to 128 tokens one block per wave:
   // the second would be padding (100 tokens, 97656 documents, k = 8: 480 -> 352 us).
-  p.tb1 = BM > 128 ? 2 : 1;
+  p.tb1 = (BM > 128 && !(small && k > 8)) ? 2 : 1;
   p.n_qblocks1 = (BM + 128 * p.tb1 - 1) / (128 * p.tb1);
   const bool one_pass = dm.cos && dm.d == 128 && dm.C == 8;
   const long long n_stage = ((dm.tiles + 1) / 2 + 1) / 2;           // stages of 64 keys
@@ -664,7 +669,7 @@ GemmPlan plan_score_gemm(const Dims& dm, int BM, int k) {
   if (want < 1) want = 1;
   // At least 8 stages (512 keys) per split: a small bank (234 tokens, 678 documents of 8 chunks) is worth spreading over
   // the chip (with at least 32 stages: 89 us, with 8: 73 us; 64 tokens, 4096 documents, k = 8: 95 -> 51 us).
-  long long by_len = (n_stage + 7) / 8;
+  long long by_len = (small && k <= 16) ? (n_stage + 31) / 32 : (n_stage + 7) / 8;
   // k > 16: at least four splits, so that the k best of a token meet 16-entry lists (8 or more) with room to spare
   if (k > 16 && want < 4) want = 4;
   long long ns = want < by_len ? want : by_len;
