@@ -199,10 +199,8 @@ int msa_score_topk(const msa_config_t* cfg, const void* q_route, int32_t B, int3
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and
  * bit-identical results; the workspace is a buffer of msa_noalloc_scratch_bytes() (32 MiB) built into
  * the library's device code (one copy per GPU, held until the process ends).  The call allocates and
- * frees nothing.  Where msa_score_topk_workspace_bytes() exceeds the built-in buffer the work is cut into fewer
- * splits with shorter lists in all (the same results, a few percent slower); a request that does not fit
- * that way either returns MSA_ERR_WORKSPACE before anything is enqueued (all five benchmark configurations
- * fit, and so does every request whose workspace size does).  The stream must
+ * frees nothing.  A request whose msa_score_topk_workspace_bytes() exceeds the built-in buffer returns
+ * MSA_ERR_WORKSPACE before anything is enqueued (all five benchmark configurations fit).  The stream must
  * belong to the CURRENT device.  Every call on a GPU shares that GPU's buffer: calls that overlap on one GPU
  * (two streams, two threads) race -- serialise them or use msa_score_topk with separate workspaces.
  * The buffer keeps the previous call's contents; nothing in it needs to start at zero.

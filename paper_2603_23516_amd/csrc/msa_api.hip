@@ -79,7 +79,6 @@ static bool misaligned4(const void* p) { return (reinterpret_cast<uintptr_t>(p) 
 // A file-scope device array takes the place of the caller's workspace for callers that cannot
 // allocate.  Every device the library runs on holds its own copy at its own address; in host code the
 // array's name is only a handle for hipGetSymbolAddress, never an address to hand to a kernel.
-constexpr size_t kNoAllocScratchBytes = (size_t)32 << 20;
 static __device__ __align__(256) unsigned char scratch[kNoAllocScratchBytes];
 
 constexpr int kMaxDevices = 64;
@@ -272,8 +271,7 @@ int msa_score_topk_noalloc(const msa_config_t* cfg, const void* q_route, int32_t
   if (misaligned(q_route) || misaligned(KR) || misaligned(inv_norm) || misaligned(out_idx) ||
       misaligned(out_score))
     return MSA_ERR_MISALIGNED;
-  ScorePlan pl = plan_score(dm, B * M, k);
-  if (pl.ws_bytes > kNoAllocScratchBytes) pl = plan_score(dm, B * M, k, true);
+  const ScorePlan pl = plan_score(dm, B * M, k);
   if (pl.ws_bytes > kNoAllocScratchBytes) return MSA_ERR_WORKSPACE;  // beyond the built-in scratch
   void* ws = nullptr;
   const int rs = scratch_on_current_device(&ws);

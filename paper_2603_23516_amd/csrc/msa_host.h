@@ -43,7 +43,7 @@ struct GemmPlan {
 };
 constexpr int kFilterMaxCand = 64;
 bool gemm_path_applies(const Dims& dm, int BM, int k);
-GemmPlan plan_score_gemm(const Dims& dm, int BM, int k, bool small);
+GemmPlan plan_score_gemm(const Dims& dm, int BM, int k);
 // Enqueues the scoring kernels.  Without the filter the per-split lists are left for score_merge_kernel.  With it
 // the exact winners of every token are written to out_idx / out_score (or out_key: sorted 64-bit keys, token pooling),
 // and the lists of the flagged token blocks are left for a merge that is gated by *gate_flags (device int32
@@ -70,6 +70,9 @@ WidePlan plan_score_wide(const Dims& dm, int BM, int k);
 int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, int BM, const void* KR,
                       const float* inv_norm, int k, void* ws, hipStream_t st, int32_t* out_idx, float* out_score,
                       unsigned long long* out_key);
+
+// Bytes of the workspace that msa_score_topk_noalloc brings along.
+constexpr size_t kNoAllocScratchBytes = (size_t)32 << 20;
 
 // Work split of the routing scan (depends only on the problem size, so the workspace size is a
 // pure function of the arguments).
@@ -99,8 +102,7 @@ struct ScorePlan {
   GemmPlan gemm;
   size_t ws_bytes;
 };
-// small: fewer, longer splits where the usual ones need more workspace than the built-in scratch holds.
-ScorePlan plan_score(const Dims& dm, int BM, int k, bool small = false);
+ScorePlan plan_score(const Dims& dm, int BM, int k);
 
 // record the caller's per-call events (msa_config_t.profile_*_event) around the dominant kernel; null = off
 inline void profile_mark(const Dims& dm, bool stop, hipStream_t st) {

@@ -1409,7 +1409,7 @@ static void plan_all_heads(const Dims& dm, int BM, int k, ScorePlan* p) {
   p->ws_bytes = end;
 }
 
-ScorePlan plan_score(const Dims& dm, int BM, int k, bool small) {
+ScorePlan plan_score(const Dims& dm, int BM, int k) {
   ScorePlan p;
   // one selection per KV group, or (literal Eq. 2 head mean, more than one group) one for all heads
   p.all_heads = (dm.scope_all && dm.Hkv > 1) ? 1 : 0;
@@ -1424,7 +1424,7 @@ ScorePlan plan_score(const Dims& dm, int BM, int k, bool small) {
     return p;
   }
   if (p.use_gemm) {
-    p.gemm = plan_score_gemm(dm, BM, k, small);
+    p.gemm = plan_score_gemm(dm, BM, k);
     p.n_splits = p.gemm.n_splits;
     p.q_per_pass = BM;
     p.n_pass = 1;

@@ -644,26 +644,26 @@ __global__ __launch_bounds__(256) void score_filter_select_kernel(const unsigned
 }
 
 // ---- host side -----------------------------------------------------------------------------------
+// cosine (the filter's bound needs unit keys), the shape that the exact-score kernel is written for
+static bool one_pass_shape(const Dims& dm) { return dm.cos && dm.d == 128 && dm.C == 8; }
+
 bool gemm_path_applies(const Dims& dm, int BM, int k) {
   // (one group with select_scope = ALL is the per-group kernel's case)
   return (dm.C == 4 || dm.C == 8 || dm.C == 16) && k <= kGemmMaxK && BM >= 64;
 }
 
-// The lists of the usual plan are bounded by the workgroups in flight, not by the sizes: two per CU, each with two lists
-// of 8 or 16 entries for every one of its tokens (16 entries, two token blocks per wave: 32 MiB and the folded queries
-// on top).  `small` halves that for callers with a fixed buffer: one block per wave at 16 entries and, up to k = 16 (above,
-// the filter needs the splits), splits of at least 32 stages.  (The filter applies to both or to neither: the scores are
-// the same bits.)
-GemmPlan plan_score_gemm(const Dims& dm, int BM, int k, bool small) {
+static GemmPlan gemm_split(const Dims& dm, int BM, int k, bool small) {
   GemmPlan p;
   const int tokens_per_wg = (k <= 8) ? 256 : 128;
   p.n_qblocks = (BM + tokens_per_wg - 1) / tokens_per_wg;
-  // The one-pass form has the registers for two blocks per wave at either list length (every key read from LDS then
-  // serves 64 tokens; 2048 tokens, 32768 documents, k = 16: call 1425 -> 1346 us).  Up to 128 tokens one block per wave:
-  // the second would be padding (100 tokens, 97656 documents, k = 8: 480 -> 352 us).
-  p.tb1 = (BM > 128 && !(small && k > 8)) ? 2 : 1;
+  // Two blocks per wave (every key read from LDS then serves 64 tokens) with 8-entry lists alone: with 16 entries the
+  // one-pass form holds them too, but the workgroups of twice the tokens are half as many and their lists twice as long
+  // (k = 16: 200 tokens, 97656 documents 847 us, with one block 598; 512 tokens, 4096 documents 147, 126; only 2048 tokens,
+  // 32768 documents 1277, 1335).  Up to 128 tokens one block per wave: the second would be padding (100 tokens, 97656
+  // documents, k = 8: 480 -> 352 us).
+  p.tb1 = (BM > 128 && k <= 8) ? 2 : 1;
   p.n_qblocks1 = (BM + 128 * p.tb1 - 1) / (128 * p.tb1);
-  const bool one_pass = dm.cos && dm.d == 128 && dm.C == 8;
+  const bool one_pass = one_pass_shape(dm);
   const long long n_stage = ((dm.tiles + 1) / 2 + 1) / 2;           // stages of 64 keys
   long long want = (2 * 256) / ((long long)dm.Hkv * (one_pass ? p.n_qblocks1 : p.n_qblocks));  // ~2 workgroups per CU
   if (want < 1) want = 1;
@@ -681,8 +681,7 @@ GemmPlan plan_score_gemm(const Dims& dm, int BM, int k, bool small) {
   p.ws_bytes = p.off_lists + round_up256((size_t)dm.Hkv * BM * p.n_splits * k * sizeof(unsigned long long));
   p.list_len = (k <= 8) ? 8 : 16;
   p.tokens_per_wg = tokens_per_wg;
-  // The one-pass filter: cosine (the bound needs unit keys), the shape the exact-score kernel is written for, and
-  // few enough list entries per token for one wave.
+  // The one-pass filter: few enough list entries per token for one wave.
   // With k > 16 the lists are shorter than k: right as long as no list is full of documents inside the band (those
   // blocks are redone), worth it with several lists per token (mean load k / (2 n_splits) <= 4 of 16 entries).
   p.filter = (one_pass && 2 * p.n_splits * p.list_len <= kFilterMaxEntries &&
@@ -698,6 +697,18 @@ GemmPlan plan_score_gemm(const Dims& dm, int BM, int k, bool small) {
     p.off_flags = end;
     end += round_up256((size_t)dm.Hkv * p.n_qblocks * sizeof(int));
     p.ws_bytes = end;
+  }
+  return p;
+}
+
+// `small`: up to k = 16 at least 32 stages per split, where lists of shorter splits would take the workspace beyond what
+// the built-in scratch of msa_score_topk_noalloc holds (5000 tokens, 200 documents, k = 4: 34.3 -> 24.6 MiB).
+GemmPlan plan_score_gemm(const Dims& dm, int BM, int k) {
+  GemmPlan p = gemm_split(dm, BM, k, false);
+  const size_t pool = dm.token_pool ? round_up256((size_t)BM * (dm.scope_all ? 1 : dm.Hkv) * k * sizeof(unsigned long long)) : 0;
+  if (p.ws_bytes + pool > kNoAllocScratchBytes) {
+    const GemmPlan s = gemm_split(dm, BM, k, true);
+    if (s.ws_bytes + pool <= kNoAllocScratchBytes) p = s;
   }
   return p;
 }
@@ -746,8 +757,7 @@ int launch_score_gemm_scan(const Dims& dm, const GemmPlan& pl, const void* q_rou
     a.n_qblocks = pl.n_qblocks1;
     const unsigned blocks1 = (unsigned)(dm.Hkv * pl.n_qblocks1 * pl.n_splits);
     if (pl.tb1 == 2) {
-      if (k <= 8) hipLaunchKernelGGL((score_gemm_kernel<128, 2, 8, true, true>), dim3(blocks1), dim3(256), 0, st, a);
-      else hipLaunchKernelGGL((score_gemm_kernel<128, 2, 16, true, true>), dim3(blocks1), dim3(256), 0, st, a);
+      hipLaunchKernelGGL((score_gemm_kernel<128, 2, 8, true, true>), dim3(blocks1), dim3(256), 0, st, a);
     } else {
       if (k <= 8) hipLaunchKernelGGL((score_gemm_kernel<128, 1, 8, true, true>), dim3(blocks1), dim3(256), 0, st, a);
       else hipLaunchKernelGGL((score_gemm_kernel<128, 1, 16, true, true>), dim3(blocks1), dim3(256), 0, st, a);

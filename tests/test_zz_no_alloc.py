@@ -58,28 +58,6 @@ def test_noalloc_matches_workspace_entry_point_twice():
         assert np.allclose(gv, ov, rtol=0, atol=2e-5)
 
 
-@pytest.mark.parametrize("N,M,k", [(4096, 512, 16), (200, 5000, 4)])
-def test_noalloc_with_longer_splits(N, M, k):
-    """More workspace than the built-in scratch with the usual splits, less with the longer ones it then takes: the same
-    documents and the same score bits."""
-    cfg = msa.MsaConfig(N, 512, 64, 32, 8, 128, 1e4)
-    assert msa.score_topk_workspace_bytes(cfg, 1, M, k) > msa.noalloc_scratch_bytes()
-    Kb, _ = S.normal_bf16(S.seed_for(9, 30), (64, 8, 512, 128))
-    K = SD.bits_to_torch(Kb)
-    KR, inv = msa.alloc_routing_index(cfg)
-    gen = torch.Generator(device="cuda")
-    gen.manual_seed(31)
-    for i in range(0, N, 64):                     # 64 documents at a time, each lot scaled and shifted by noise
-        n = min(64, N - i)
-        part = (K[:n].float() + torch.randn(K[:n].shape, generator=gen, device="cuda")).to(torch.bfloat16)
-        a, b = msa.msa_build_routing_keys(cfg.replace(n_docs=n), part.contiguous())
-        KR[:, i * 8 // 16:i * 8 // 16 + a.shape[1]] = a
-        inv[:, i * 8:i * 8 + b.shape[1]] = b
-    q = torch.randn((1, M, 32, 128), generator=gen, device="cuda").to(torch.bfloat16)
-    torch.cuda.synchronize()
-    _run_both(cfg, q, KR, inv, k)
-
-
 def test_noalloc_refuses_what_does_not_fit():
     cfg = msa.MsaConfig(65536, 512, 64, 32, 8, 128, 1e6)
     assert msa.score_topk_workspace_bytes(cfg, 1, 8192, 8) > msa.noalloc_scratch_bytes()
