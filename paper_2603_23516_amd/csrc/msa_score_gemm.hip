@@ -649,7 +649,13 @@ static bool one_pass_shape(const Dims& dm) { return dm.cos && dm.d == 128 && dm.
 
 bool gemm_path_applies(const Dims& dm, int BM, int k) {
   // (one group with select_scope = ALL is the per-group kernel's case)
-  return (dm.C == 4 || dm.C == 8 || dm.C == 16) && k <= kGemmMaxK && BM >= 64;
+  if (!((dm.C == 4 || dm.C == 8 || dm.C == 16) && k <= kGemmMaxK && BM >= 64)) return false;
+  if (k <= 16 || one_pass_shape(dm)) return true;
+  // 32-entry lists without the filter: inserting into them is most of the work, and the scan is the faster way for few
+  // tokens over a small bank (k = 17..32: 132 tokens, 1491 documents of 8 chunks: scan 56 us, here 139; 290 tokens, 1461
+  // of 4: 115, 171; 191 tokens, 13935 of 8: 516, 316; 512 tokens, 78 of 8: 166, 94; the scan's time goes with the heads:
+  // two of them, 176 tokens, 10610 of 8: 100, 131)
+  return BM >= 320 || dm.NC >= 112000000 / ((long long)BM * dm.Hkv);
 }
 
 static GemmPlan gemm_split(const Dims& dm, int BM, int k, bool small) {
@@ -675,6 +681,8 @@ static GemmPlan gemm_split(const Dims& dm, int BM, int k, bool small) {
   long long ns = want < by_len ? want : by_len;
   if (ns < 1) ns = 1;
   if (ns > 64) ns = 64;
+  // with k > 16 no more lists than the filter reads: without it the 32-entry lists take over
+  if (k > 16 && one_pass && ns > kFilterMaxEntries / 32) ns = kFilterMaxEntries / 32;
   p.stages_per_split = (int)((n_stage + ns - 1) / ns);
   p.n_splits = (int)((n_stage + p.stages_per_split - 1) / p.stages_per_split);
   p.off_lists = round_up256((size_t)BM * dm.Hkv * dm.d * sizeof(float));

@@ -54,8 +54,10 @@ GEMM_K32 = [
     (5003, 2, 2, 8, 128, 1, 300, 32, "cos"),      # one-pass filter, two token blocks per wave, lists shorter than k
     (700, 2, 1, 8, 128, 1, 100, 17, "cos"),       # one token block per wave
     (40, 2, 1, 8, 128, 1, 64, 32, "cos"),         # one short split: no filter
-    (613, 4, 1, 16, 128, 1, 130, 20, "cos"),      # two-pass form, 32-entry lists
+    (613, 4, 1, 16, 128, 1, 130, 20, "cos"),      # few tokens, a small bank and no filter: the scan
     (901, 2, 1, 4, 64, 2, 35, 32, "dot"),
+    (613, 4, 1, 16, 128, 1, 321, 20, "cos"),      # two-pass form, 32-entry lists
+    (301, 2, 1, 4, 64, 2, 161, 32, "dot"),
 ]
 
 
