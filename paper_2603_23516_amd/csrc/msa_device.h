@@ -194,6 +194,35 @@ __device__ __forceinline__ void lds_barrier() {
 }
 
 // ---- arrival counter that needs no initialisation ------------------------------------------------
+// A lower bound on the k-th best score of a workgroup's candidates: ob is the order-preserving image of the best score
+// that this lane has seen (0: none), every lane's of another document.  The larger of
+//   the best wave's k-th best lane, and the worst wave's ceil(k / WAVES)-th best lane (that many in every wave are k);
+// the first alone says little once k nears the 64 lanes (k = 64, 13105 documents, sixteen waves: the worst of a wave's
+// lane maxima; the selection took 250 us, with the second bound 9).  The low 12 bits are clear.  Every thread calls it;
+// there is one barrier inside.
+template <int WAVES>
+__device__ __forceinline__ uint32_t kth_best_bound(uint32_t ob, int k, uint32_t (&wave_s)[2][WAVES]) {
+  const int share = (k + WAVES - 1) / WAVES;
+  uint32_t pk = 0u, ps = 0u;
+  for (int bit = 31; bit >= 12; --bit) {
+    const uint32_t ck = pk | (1u << bit), cs = ps | (1u << bit);
+    if (__popcll(__ballot(ob >= ck)) >= k) pk = ck;      // wave-uniform
+    if (__popcll(__ballot(ob >= cs)) >= share) ps = cs;
+  }
+  if ((threadIdx.x & 63) == 0) {
+    wave_s[0][threadIdx.x >> 6] = pk;
+    wave_s[1][threadIdx.x >> 6] = ps;
+  }
+  __syncthreads();
+  uint32_t most = wave_s[0][0], least = wave_s[1][0];
+#pragma unroll
+  for (int w = 1; w < WAVES; ++w) {
+    most = wave_s[0][w] > most ? wave_s[0][w] : most;
+    least = wave_s[1][w] < least ? wave_s[1][w] : least;
+  }
+  return most > least ? most : least;
+}
+
 // Workgroups that produced parts of one result count themselves in; the one that arrives last combines the
 // parts.  The 64-bit word holds (nonce << 16 | arrivals); a word whose upper 48 bits are not this call's nonce
 // is a leftover (the caller's workspace has undefined contents) and counts as zero arrivals, so nothing has

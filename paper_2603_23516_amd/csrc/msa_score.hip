@@ -986,10 +986,8 @@ __global__ __launch_bounds__(kPoolThreads) void pool_tokens_kernel(const unsigne
 
 // Top-k of the rows of a document score matrix (MODE 2 of the scan, all-heads scan).  One workgroup per (row, part
 // of the row).
-//   1. every thread takes the best score of its strided share of the part; every wave finds (a lower bound
-//      on) the k-th best of its 64 lane maxima by a bitwise search with ballots, and the largest of the
-//      waves' bounds is a lower bound theta on the k-th best score of the part: some wave holds k distinct
-//      documents scoring at least that much;
+//   1. every thread takes the best score of its strided share of the part, and kth_best_bound gives a lower bound theta
+//      on the k-th best score of the part;
 //   2. every document scoring >= theta goes to LDS (a few k of them) and is ranked by counting on the full
 //      key.
 // Exact, ties included (keys are (score, ~doc): a total order; theta compares scores only, so equal scores
@@ -1018,7 +1016,7 @@ template <int REGS, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void topk_rows_kernel(RowsArgs a) {
   __shared__ unsigned long long surv[kRowSurv + 8];
   __shared__ unsigned long long red[WAVES];
-  __shared__ uint32_t theta_w[WAVES];
+  __shared__ uint32_t theta_w[2][WAVES];
   __shared__ int n_surv;
   constexpr int THREADS = 64 * WAVES;
   const int tid = threadIdx.x;
@@ -1029,53 +1027,43 @@ __global__ __launch_bounds__(64 * WAVES) void topk_rows_kernel(RowsArgs a) {
   const int g = row_no / a.BM;
   const int first = part * a.part_docs;
   const int N = a.n_docs - first < a.part_docs ? a.n_docs - first : a.part_docs;  // documents of this part
-  const float* row = a.mat + (long long)row_no * a.stride + first;
+  const float* __restrict__ row = a.mat + (long long)row_no * a.stride + first;
   const uint32_t doc0 = (uint32_t)(a.doc0 + first);
+  if (tid == 0) n_surv = 0;
   float v[REGS];
-  unsigned long long best = 0ull;
 #pragma unroll
   for (int u = 0; u < REGS; ++u) {
     const int i = u * THREADS + tid;
     v[u] = (i < N) ? row[i] : 0.f;
   }
+  // the rest of a row longer than the registers hold, eight loads in flight
+  auto rest_of_row = [&](auto use) {
+    for (int i0 = REGS * THREADS + tid; i0 < N; i0 += 8 * THREADS) {
+      float x[8];
 #pragma unroll
-  for (int u = 0; u < REGS; ++u) {
-    const int i = u * THREADS + tid;
-    const unsigned long long x = (i < N) ? make_key(v[u], doc0 + i) : 0ull;
-    best = x > best ? x : best;
-  }
-  for (int i = REGS * THREADS + tid; i < N; i += THREADS) {  // rows longer than the register share
-    const unsigned long long x = make_key(row[i], doc0 + i);
-    best = x > best ? x : best;
-  }
-  {
-    // the order-preserving image of this lane's best score (0: the lane holds no document); the largest value
-    // whose low 12 bits are clear and that at least k lanes of the wave reach, 0 if fewer than k lanes hold one
-    const uint32_t ob = (uint32_t)(best >> 32);
-    uint32_t prefix = 0u;
-    for (int bit = 31; bit >= 12; --bit) {
-      const uint32_t cnd = prefix | (1u << bit);
-      if (__popcll(__ballot(ob >= cnd)) >= k) prefix = cnd;  // wave-uniform
+      for (int u = 0; u < 8; ++u) x[u] = (i0 + u * THREADS < N) ? row[i0 + u * THREADS] : 0.f;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) use(i0 + u * THREADS, x[u]);
     }
-    if ((tid & 63) == 0) theta_w[tid >> 6] = prefix;
-  }
-  if (tid == 0) n_surv = 0;
-  __syncthreads();
-  uint32_t theta = theta_w[0];
+  };
+  uint32_t ob = 0u;
+  auto best_of = [&](int i, float x) {
+    const uint32_t o = i < N ? orderable(x) : 0u;
+    ob = o > ob ? o : ob;
+  };
 #pragma unroll
-  for (int w = 1; w < WAVES; ++w) theta = theta_w[w] > theta ? theta_w[w] : theta;
-  auto keep = [&](unsigned long long x) {
-    if (x != 0ull && (uint32_t)(x >> 32) >= theta) {
+  for (int u = 0; u < REGS; ++u) best_of(u * THREADS + tid, v[u]);
+  rest_of_row(best_of);
+  const uint32_t theta = kth_best_bound<WAVES>(ob, k, theta_w);
+  auto keep = [&](int i, float x) {
+    if (i < N && orderable(x) >= theta) {
       const int slot = atomicAdd(&n_surv, 1);
-      if (slot < kRowSurv) surv[slot] = x;
+      if (slot < kRowSurv) surv[slot] = make_key(x, doc0 + i);
     }
   };
 #pragma unroll
-  for (int u = 0; u < REGS; ++u) {
-    const int i = u * THREADS + tid;
-    keep((i < N) ? make_key(v[u], doc0 + i) : 0ull);
-  }
-  for (int i = REGS * THREADS + tid; i < N; i += THREADS) keep(make_key(row[i], doc0 + i));
+  for (int u = 0; u < REGS; ++u) keep(u * THREADS + tid, v[u]);
+  rest_of_row(keep);
   __syncthreads();
   const int ns = n_surv;
   const long long o_base = a.part_keys

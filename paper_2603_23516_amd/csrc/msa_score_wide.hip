@@ -232,7 +232,7 @@ void score_wide_kernel(WideArgs a) {
 // eps = 0: the exact scores), and the k best of the segments before, as sorted keys with exact scores.  Let t~ be the
 // k-th largest s~ of the segment.  k documents have s >= t~ - eps, so a document of the exact k best has
 // s~ >= s - eps >= t~ - 2 eps; and it is none of the k best if s~ + eps is below the k-th best exact score so far.
-//   1. a lower bound theta of t~ as in topk_rows_kernel; the documents with s~ >= theta - 2 eps go to LDS;
+//   1. a lower bound theta of t~ (kth_best_bound); the documents with s~ >= theta - 2 eps go to LDS;
 //   2. t~ by rank counting among them; what is left of them after the two conditions are the candidates;
 //   3. the candidates' exact scores: Eq. 2 in fp32 from the folded fp32 query and the bf16 keys, eight lanes per key;
 //   4. the k best of candidates and earlier winners by rank counting on the full key.
@@ -266,14 +266,14 @@ __global__ __launch_bounds__(kWideSel) void score_wide_select_kernel(WideSelArgs
   __shared__ unsigned long long surv[kWideSurv + MSA_MAX_TOPK + 8];
   __shared__ float qs[8 * D];
   __shared__ unsigned long long best_s[MSA_MAX_TOPK];
-  __shared__ uint32_t theta_w[NW];
+  __shared__ uint32_t theta_w[2][NW];
   __shared__ uint32_t kth_s;
   __shared__ int n_surv;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int tok = blockIdx.x;
   const int k = a.k, N = a.n_docs;
-  const float* row = a.mat + (long long)tok * a.mat_stride;
+  const float* __restrict__ row = a.mat + (long long)tok * a.mat_stride;
   float eps = 0.f;
   if (a.eps != nullptr) {
     for (int g = 0; g < a.Hkv; ++g) eps += a.eps[(long long)tok * a.Hkv + g];
@@ -399,18 +399,7 @@ __global__ __launch_bounds__(kWideSel) void score_wide_select_kernel(WideSelArgs
 #pragma unroll
   for (int u = 0; u < REGS; ++u) best_of(u * kWideSel + tid, v[u]);
   rest_of_row(best_of);
-  {
-    uint32_t prefix = 0u;
-    for (int bit = 31; bit >= 12; --bit) {
-      const uint32_t cnd = prefix | (1u << bit);
-      if (__popcll(__ballot(ob >= cnd)) >= k) prefix = cnd;  // wave-uniform
-    }
-    if (lane == 0) theta_w[tid >> 6] = prefix;
-  }
-  __syncthreads();
-  uint32_t theta = theta_w[0];
-#pragma unroll
-  for (int i = 1; i < NW; ++i) theta = theta_w[i] > theta ? theta_w[i] : theta;
+  const uint32_t theta = kth_best_bound<NW>(ob, k, theta_w);
   uint32_t lim = theta ? floor_of(unorderable(theta), 2.f * eps) : 0u;
   if (!a.first) {  // the k-th best so far (0: fewer than k)
     const unsigned long long kb = best_s[k - 1];

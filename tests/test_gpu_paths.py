@@ -25,6 +25,7 @@ ALL_SCAN = [
     (8193, 8, 1, 8, 128, 25, 1, 16, "cos"),       # 32-query pass, units of several tiles, ragged last tile
     (4099, 8, 2, 1, 64, 33, 1, 20, "dot"),        # two passes, sixteen documents per tile
     (16400, 2, 1, 2, 64, 2, 2, 64, "cos"),        # whole rows held by sixteen waves
+    (12437, 8, 1, 8, 64, 5, 1, 64, "cos"),        # ... twelve documents per lane, as many winners as lanes in a wave
     (32768, 2, 1, 1, 64, 1, 1, 64, "cos"),        # the longest row that one workgroup takes
     (32785, 2, 1, 2, 64, 2, 2, 64, "cos"),        # rows in five parts, the last of 17 documents (fewer than k)
     (200007, 2, 1, 1, 64, 25, 1, 7, "cos"),       # two segments of the bank
