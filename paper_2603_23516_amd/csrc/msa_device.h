@@ -197,8 +197,8 @@ __device__ __forceinline__ void lds_barrier() {
 // A lower bound on the k-th best score of a workgroup's candidates: ob is the order-preserving image of the best score
 // that this lane has seen (0: none), every lane's of another document.  The larger of
 //   the best wave's k-th best lane, and the worst wave's ceil(k / WAVES)-th best lane (that many in every wave are k);
-// the first alone says little once k nears the 64 lanes (k = 64, 13105 documents, sixteen waves: the worst of a wave's
-// lane maxima; the selection took 250 us, with the second bound 9).  The low 12 bits are clear.  Every thread calls it;
+// the first alone says little once k nears the 64 lanes (k = 64: the worst of a wave's lane maxima; 5 rows of 12437
+// documents, sixteen waves each: 231 us, with the second bound 8.9).  The low 12 bits are clear.  Every thread calls it;
 // there is one barrier inside.
 template <int WAVES>
 __device__ __forceinline__ uint32_t kth_best_bound(uint32_t ob, int k, uint32_t (&wave_s)[2][WAVES]) {

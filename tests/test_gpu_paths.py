@@ -75,6 +75,13 @@ def test_prefill_scoring_k_above_16(N, Hkv, r, C, d, B, M, k, sim):
         check_topk_generic(q, KRb, C, N, idx, val, k, sim, "group", pool, atol=2e-5 if sim == "cos" else 2e-4)
 
 
+@pytest.mark.parametrize("M", [250, 700, 2000])
+def test_token_pooling_of_many_documents(M):
+    """One query head: the tokens' scores are alike and most of their listed documents reach the floor: 1300 and about
+    3000 of them (ranked from the table in LDS), and 6422 (more than it takes: rounds over the lists)."""
+    test_prefill_scoring_k_above_16(9001, 1, 1, 4, 64, 1, M, 16, "cos")
+
+
 def test_prefill_scoring_k_above_16_neighbouring_winners():
     """The best documents of every token lie side by side: more of them in one list of the one-pass filter than it
     holds, so every token block is redone by the two-pass form with 32-entry lists."""
