@@ -650,12 +650,18 @@ static bool one_pass_shape(const Dims& dm) { return dm.cos && dm.d == 128 && dm.
 bool gemm_path_applies(const Dims& dm, int BM, int k) {
   // (one group with select_scope = ALL is the per-group kernel's case)
   if (!((dm.C == 4 || dm.C == 8 || dm.C == 16) && k <= kGemmMaxK && BM >= 64)) return false;
-  if (k <= 16 || one_pass_shape(dm)) return true;
+  if (k <= 16) return true;
   // 32-entry lists without the filter: inserting into them is most of the work, and the scan is the faster way for few
-  // tokens over a small bank (k = 17..32: 132 tokens, 1491 documents of 8 chunks: scan 56 us, here 139; 290 tokens, 1461
-  // of 4: 115, 171; 191 tokens, 13935 of 8: 516, 316; 512 tokens, 78 of 8: 166, 94; the scan's time goes with the heads:
-  // two of them, 176 tokens, 10610 of 8: 100, 131)
-  return BM >= 320 || dm.NC >= 112000000 / ((long long)BM * dm.Hkv);
+  // tokens over a small bank.  k = 25..32: 162 tokens, 231 documents of 8 chunks, four heads: scan 90 us, here 95; 191
+  // tokens, 13935 of 8: 516, 316; 437 tokens, 122 of 8: 222, 101.  Up to k = 24 the scan takes 32 queries per pass, not 16:
+  // 132 tokens, 1491 of 8: 56, 139; 290 tokens, 1461 of 4: 115, 171; 512 tokens, 78 of 8: 166, 94.  The scan's time goes
+  // with the heads: two of them, 176 tokens, 10610 of 8: 100, 131; 437 tokens, 7919 of 4: 130, 169.
+  // With the filter it is so for little work only: 92 tokens, 190 documents, k = 20: 37, 46; 67 tokens, 3670 documents,
+  // four heads, k = 17: 52, 68; 99 tokens, 1425 documents, k = 32: 83, 60.
+  const bool wide_scan = k <= 24;
+  if (BM >= (one_pass_shape(dm) || !wide_scan ? 320 : 448)) return true;
+  const long long keys = one_pass_shape(dm) ? (wide_scan ? 12000000 : 4000000) : (wide_scan ? 160000000 : 112000000);
+  return dm.NC >= keys / ((long long)BM * dm.Hkv);
 }
 
 static GemmPlan gemm_split(const Dims& dm, int BM, int k, bool small) {

@@ -52,12 +52,14 @@ def test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim):
 
 # (N, Hkv, r, C, d, B, M, k, sim): the scoring GEMM with more than 16 selected documents
 GEMM_K32 = [
-    (5003, 2, 2, 8, 128, 1, 300, 32, "cos"),      # one-pass filter, two token blocks per wave, lists shorter than k
-    (700, 2, 1, 8, 128, 1, 100, 17, "cos"),       # one token block per wave
-    (40, 2, 1, 8, 128, 1, 64, 32, "cos"),         # one short split: no filter
+    (5003, 2, 2, 8, 128, 1, 300, 32, "cos"),      # one-pass filter, lists shorter than k
+    (700, 2, 1, 8, 128, 1, 100, 17, "cos"),       # little work: the scan
+    (40, 2, 1, 8, 128, 1, 64, 32, "cos"),
+    (3001, 2, 1, 8, 128, 1, 100, 25, "cos"),      # filter, one workgroup of tokens
+    (40, 2, 1, 8, 128, 1, 321, 32, "cos"),        # one short split: no filter
     (613, 4, 1, 16, 128, 1, 130, 20, "cos"),      # few tokens, a small bank and no filter: the scan
     (901, 2, 1, 4, 64, 2, 35, 32, "dot"),
-    (613, 4, 1, 16, 128, 1, 321, 20, "cos"),      # two-pass form, 32-entry lists
+    (613, 4, 1, 16, 128, 1, 449, 20, "cos"),      # two-pass form, 32-entry lists
     (301, 2, 1, 4, 64, 2, 161, 32, "dot"),
 ]
 
@@ -82,10 +84,11 @@ def test_token_pooling_of_many_documents(M):
     test_prefill_scoring_k_above_16(9001, 1, 1, 4, 64, 1, M, 16, "cos")
 
 
-def test_prefill_scoring_k_above_16_neighbouring_winners():
+@pytest.mark.parametrize("M", [70, 330])
+def test_prefill_scoring_k_above_16_neighbouring_winners(M):
     """The best documents of every token lie side by side: more of them in one list of the one-pass filter than it
-    holds, so every token block is redone by the two-pass form with 32-entry lists."""
-    N, Hkv, C, d, M, k = 4000, 2, 8, 128, 70, 24
+    holds, so every token block is redone by the two-pass form with 32-entry lists (M = 70: the scan's case)."""
+    N, Hkv, C, d, k = 4000, 2, 8, 128, 24
     cfg = msa.MsaConfig(N, 8 * C, 8, Hkv, Hkv, d, 1e6)
     KRb, _ = random_index(54000, N, Hkv, C, d)
     qb, q = S.normal_bf16(54001, (1, M, Hkv, d))
