@@ -36,6 +36,7 @@
 
 namespace msa {
 
+constexpr int kDecodeSlots = 1024;  // partials of the decode kernel, as long as there are fewer pairs
 constexpr int kMaxFused = 8;  // splits that the last-arriving workgroup merges; more are read faster by a launch of
                               // their own (12 pairs of 97 steps: 16 splits merged here 21 us, 20 by a launch 16 us)
 
@@ -817,6 +818,26 @@ __global__ __launch_bounds__(D) void attend_merge_kernel(const float* __restrict
   }
 }
 
+// Partials (splits of all pairs) that the decode kernel may use for this many (query, KV head) pairs of so many steps.  It
+// grows with both: a workspace sized for the most queries, documents and local rows of a program serves every smaller
+// call, whatever split that takes.
+static long long decode_slots(long long pairs, long long steps) {
+  long long n = steps / kAttWaves;
+  if (n > kMaxAttSplits) n = kMaxAttSplits;
+  if (n < 1) n = 1;
+  const long long all = pairs * n < kDecodeSlots ? pairs * n : kDecodeSlots;
+  return all > pairs ? all : pairs;
+}
+
+// Time of `groups` workgroups of the decode kernel that take `per` steps each and `prologues` prologues, in units that
+// make one more partial per pair the smallest difference.
+static long long decode_cost(long long per, long long prologues, long long groups, int d) {
+  const long long wave = ((per + kAttWaves - 1) / kAttWaves + 1) / 2 * 2;
+  const long long rest = groups % 512;
+  const long long rounds = d == 128 ? (groups + 255) / 256 * 6 : groups / 512 * 7 + (rest == 0 ? 0 : rest <= 256 ? 6 : 7);
+  return (wave + 5 * prologues) * rounds * 7;
+}
+
 AttendPlan plan_attend(const Dims& dm, int B, int M, int k, int Lloc, int bank_keys_rotated) {
   AttendPlan p;
   const int BM = B * M;
@@ -861,39 +882,33 @@ AttendPlan plan_attend(const Dims& dm, int B, int M, int k, int Lloc, int bank_k
   } else if (p.prefill || p.steps_total == 0) {
     p.n_splits = split(p.steps_total, pairs, kAttWaves, kMaxAttSplits, &p.steps_per_split);
   } else {
-    // Decode kernel alone (documents of full length: the work of every workgroup is known; with lengths this is the most
-    // it can be).  A CU streams as fast with one workgroup of the d = 128 kernel as with two, so the chip counts as 256 places (512 at d = 64), and a grid of P n
-    // workgroups of `per` steps takes ceil(P n / places) rounds of per + 8 steps (8: prologue and merge).  The candidates
-    // are the largest n of one to four rounds, and the most splits that merge without a launch of their own.
-    const long long S = p.steps_total, places = dm.d == 128 ? 256 : 512;
+    // Decode kernel alone.  Two workgroups are resident per CU; at d = 128 they stream no faster than one, at d = 64 six to
+    // seven.  A workgroup takes the steps of its longest wave, two per trip of the loop, and about five more for prologue
+    // and merge; a grid of P n of them so many rounds over the chip (documents of full length: the work of every
+    // workgroup is known; with lengths this is the most it can be).  Over 770 shapes the n of least cost was 2 % from the
+    // fastest of those tried.  (A rule that set the prologue at two steps and took rounds of short workgroups for half
+    // price split far too much where there are many pairs: 640 pairs of 89 steps 148 us, now 60; 7216 of 81 1747, 740.)
+    const long long S = p.steps_total;
+    const long long most = decode_slots(pairs, S) / pairs;
     long long best = -1, best_n = 1;
-    for (int i = 0; i <= 5; ++i) {
-      long long n = i == 0 ? 1 : (i == 5 ? kMaxFused : i * places / pairs);
-      if (n > S / kAttWaves) n = S / kAttWaves;
-      if (n > kMaxAttSplits) n = kMaxAttSplits;
-      if (n < 1) n = 1;
-      const long long per = (S + n - 1) / n;
-      const long long wave_steps = ((per + kAttWaves - 1) / kAttWaves + 1) / 2 * 2;  // two steps per trip of the loop
-      const long long rounds = (pairs * n + places - 1) / places;
-      // (short workgroups wait for latencies more than for the memory: a second one in the CU costs half)
-      const long long stream = wave_steps * kAttWaves * (per <= 16 ? rounds + 1 : 2 * rounds) / 2;
-      const long long cost = stream + (per <= 16 ? (rounds + 1) / 2 : rounds) * 8 + (n > kMaxFused ? 4 : 0);
-      if (best < 0 || cost < best) {
-        best = cost;
+    for (long long n = 1; n <= most; ++n) {
+      const long long c = decode_cost((S + n - 1) / n, 1, pairs * n, dm.d) + n;  // (of equals the fewest partials)
+      if (best < 0 || c < best) {
+        best = c;
         best_n = n;
       }
     }
     p.steps_per_split = (int)((S + best_n - 1) / best_n);
     p.n_splits = (int)((S + p.steps_per_split - 1) / p.steps_per_split);
-    // Documents of full length: where that leaves places idle (360 workgroups in two rounds of 256) and a place's share is worth it, the steps of
-    // all pairs in one line are cut into equal ranges, one per place, whatever pairs they end in (measured, d = 128, 45
-    // streams of 376 steps: 432 -> 359 us; 20 of 289: 161 -> 130; 12 of 216: 83 -> 64; d = 64, 37 of 245: 133 -> 99.
-    // With shares below 64 steps the second prologue costs more than the round: 8 pooled streams of 36 steps 19 -> 31.)
-    const long long total = S * pairs, share = total / places + 8;
-    long long per = ((total + places - 1) / places + 7) / 8 * 8;
+    // Documents of full length: where that leaves places idle (360 workgroups in two rounds of 256), the steps of all pairs
+    // in one line are cut into equal ranges, one per place, whatever pairs they end in: a prologue more per range.  d = 128:
+    // 280 pairs of 150 steps 0.83 of the time, 264 of 449 0.86, 264 of 398 0.90, 416 of 217 0.91.  Not for ranges of less
+    // than 112 steps (352 pairs of 57: 1.27) nor for such as meet more than three pairs (1944 pairs of 17: 1.68).
+    const long long places = dm.d == 128 ? 256 : 512, total = S * pairs;
+    const long long per = ((total + places - 1) / places + 7) / 8 * 8;
     const long long slots = (S - 1) / per + 2;  // workgroups that can meet in one pair
-    if (dm.lens == nullptr && total >= 64 * places && total < (1ll << 30) && pairs < 8 * places &&
-        best * 100 > share * 115 && slots <= kMaxFused) {
+    if (dm.lens == nullptr && per >= 112 && per <= 2 * S && total < (1ll << 30) && slots <= kMaxFused &&
+        slots <= most && decode_cost(per, 2, places, dm.d) * 100 < best * 85) {
       p.lin_per = (int)per;
       p.lin_blocks = (int)((total + per - 1) / per);
       p.n_splits = (int)slots;
@@ -911,9 +926,11 @@ AttendPlan plan_attend(const Dims& dm, int B, int M, int k, int Lloc, int bank_k
   // selection, or the local steps alone
   p.off_krot = 0;
   p.krot_steps = p.prefill ? p.steps_total : (p.split_local ? (Lloc + 31) / 32 : 0);
+  size_t krot_bytes = 0;
   if (p.krot_steps > 0) {
     p.off_krot = p.ws_bytes;
-    p.ws_bytes += round_up256((size_t)B * dm.Hkv * p.krot_steps * 32 * dm.d * 2);
+    krot_bytes = round_up256((size_t)B * dm.Hkv * p.krot_steps * 32 * dm.d * 2);
+    p.ws_bytes += krot_bytes;
   }
   return p;
 }

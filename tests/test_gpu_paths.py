@@ -173,20 +173,29 @@ def test_pool_chunks_by_pairs(N, Hkv, G, P, d, first, count):
                     assert np.abs(got[i, :, j] - want).max() <= 2.0 ** -8 * np.abs(want).max() + 1e-5
 
 
-# (N, Hkv, r, G, d, B, M, k, Lloc, scope): the decode kernel's linear split, ranges that end inside pairs
+# (N, Hkv, r, G, d, B, M, k, Lloc, scope, rotated): many (query, KV head) pairs in the decode kernel
 ATT_LINEAR = [
-    (40, 8, 4, 512, 128, 20, 1, 18, 5, "group"),      # 160 pairs of 289 steps in ranges of 184
-    (33, 8, 1, 512, 128, 45, 1, 20, 1791, "all"),     # 360 pairs of 376 in ranges of 536: one spans three pairs
-    (25, 2, 2, 256, 64, 150, 2, 21, 130, "group"),    # d = 64, two query tokens with selections of their own
+    (40, 8, 4, 512, 128, 20, 1, 18, 5, "group", 0),      # 160 pairs of 289 steps, three splits each
+    (33, 8, 1, 512, 128, 45, 1, 20, 1791, "all", 0),     # 360 pairs of 376, two
+    (25, 2, 2, 256, 64, 150, 2, 21, 130, "group", 0),    # 600 pairs of 173, one; two query tokens with selections of their own
+    # the linear split, ranges that end inside pairs
+    (40, 8, 4, 512, 128, 33, 1, 24, 430, "group", 0),    # 264 pairs of 398 steps in ranges of 416
+    (40, 8, 1, 512, 128, 35, 1, 9, 170, "all", 0),       # 280 of 150 in 168: ranges meet three pairs
+    (40, 8, 1, 512, 128, 33, 1, 24, 430, "all", 1),      # keys stored rotated
+    (70, 8, 1, 8, 128, 39, 1, 64, 2880, "group", 1),     # the same, four documents per step: 312 of 106 in 136
+    (30, 8, 1, 512, 64, 34, 1, 22, 1056, "group", 0),    # d = 64: 272 of 385 in 208
+    (50, 4, 2, 256, 64, 68, 1, 44, 1056, "all", 1),
+    (70, 8, 1, 16, 64, 34, 1, 64, 6976, "group", 1),     # 272 of 250 in 136
 ]
 
 
-@pytest.mark.parametrize("N,Hkv,r,G,d,B,M,k,Lloc,scope", ATT_LINEAR)
-def test_decode_attention_linear_split(N, Hkv, r, G, d, B, M, k, Lloc, scope):
+@pytest.mark.parametrize("N,Hkv,r,G,d,B,M,k,Lloc,scope,rotated", ATT_LINEAR)
+def test_decode_attention_linear_split(N, Hkv, r, G, d, B, M, k, Lloc, scope, rotated):
     """Against the oracle on some queries, and every query against the same call with one query alone (another split);
     a pad and queries that see only a part of the local context among them."""
-    say(f"linear split N={N} Hkv={Hkv} r={r} G={G} d={d} B={B} M={M} k={k} Lloc={Lloc} {scope}")
-    cfg = msa.MsaConfig(N, G, G, Hkv * r, Hkv, d, 1e6, select_scope=msa.MSA_SCOPE_ALL if scope == "all" else msa.MSA_SCOPE_GROUP)
+    say(f"linear split N={N} Hkv={Hkv} r={r} G={G} d={d} B={B} M={M} k={k} Lloc={Lloc} {scope} rotated={rotated}")
+    cfg = msa.MsaConfig(N, G, G, Hkv * r, Hkv, d, 1e6, bank_keys_rotated=rotated,
+                        select_scope=msa.MSA_SCOPE_ALL if scope == "all" else msa.MSA_SCOPE_GROUP)
     S_ = 1 if scope == "all" else Hkv
     Kb, K = S.normal_bf16(56000, (N, Hkv, G, d))
     Vb, V = S.normal_bf16(56001, (N, Hkv, G, d))
@@ -216,7 +225,7 @@ def test_decode_attention_linear_split(N, Hkv, r, G, d, B, M, k, Lloc, scope):
         assert (lse[b] - l1[0]).abs().max() <= 1e-4
     for b in (0, B // 2, B - 1):
         oo, ol = O.sparse_attend(q[b:b + 1], K, V, idx[b:b + 1].astype(np.int64), Kl[b:b + 1], Vl[b:b + 1], G,
-                                 q_pos[b:b + 1], 1e6)
+                                 q_pos[b:b + 1], 1e6, mem_rotated=bool(rotated))
         go = out[b:b + 1].float().cpu().numpy().astype(np.float64)
         assert np.abs(go - oo).max() <= 2e-2 and np.linalg.norm(go - oo) <= 5e-3 * np.linalg.norm(oo)
         assert np.allclose(lse[b:b + 1].cpu().numpy(), ol, rtol=0, atol=5e-3)
