@@ -128,7 +128,9 @@ uint64_t msa_pooled_bank_bytes(uint64_t tokens, uint32_t chunk, uint32_t heads, 
 
 /* Workspace requirements (bytes, multiple of 256).  0 if the arguments are invalid.  The attention workspace
  * holds the split-K partials and, where many query tokens share keys (token_pool = 1 with M >= 8, or the local
- * context with M >= 16), those keys rotated once: B * Hkv * ceil((k*G or 0) + Lloc, 32 rows) * d * 2 bytes more. */
+ * context with M >= 16), those keys rotated once: B * Hkv * ceil((k*G or 0) + Lloc, 32 rows) * d * 2 bytes more.
+ * It is the same with and without doc_lens and does not fall as k or Lloc grows (nor, for M < 8, as B does): sized for
+ * the longest local context and the most documents of a program it serves every shorter call. */
 size_t msa_score_topk_workspace_bytes(const msa_config_t* cfg, int32_t B, int32_t M, int32_t k);
 size_t msa_sparse_attend_workspace_bytes(const msa_config_t* cfg, int32_t B, int32_t M, int32_t k,
                                          int32_t Lloc);

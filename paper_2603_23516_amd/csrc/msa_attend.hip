@@ -862,6 +862,12 @@ AttendPlan plan_attend(const Dims& dm, int B, int M, int k, int Lloc, int bank_k
     const long long n = (steps + per - 1) / per;
     return n < 1 ? 1 : (int)n;
   };
+  auto split_most = [](long long steps, long long prs, long long min_per, int max_splits) -> long long {
+    long long n = (steps + min_per - 1) / min_per;  // (grows with the steps; what `split` gives does not always)
+    if (n > max_splits) n = max_splits;
+    if (n > (511 + prs) / prs) n = (511 + prs) / prs;
+    return n < 1 ? 1 : n;
+  };
   // Many query tokens that the shared-selection kernel above does not take (their own selections, or a
   // bank whose keys are stored rotated): every token gathers its documents (decode kernel), but the local
   // context is the same rows for all tokens of a batch row, so it goes through the tiled kernel once per
@@ -932,6 +938,23 @@ AttendPlan plan_attend(const Dims& dm, int B, int M, int k, int Lloc, int bank_k
     krot_bytes = round_up256((size_t)B * dm.Hkv * p.krot_steps * 32 * dm.d * 2);
     p.ws_bytes += krot_bytes;
   }
+  // The size to ask for is that of the most partials which a call of no more documents and local rows can use, with or
+  // without document lengths: a program that sized its workspace once is not refused later.
+  auto partials = [&](long long n) {  // n of every head of a group
+    return round_up256((size_t)n * dm.r * dm.d * sizeof(float)) + round_up256((size_t)n * dm.r * sizeof(float2)) +
+           round_up256((size_t)BM * dm.Hkv * sizeof(unsigned long long));
+  };
+  const long long all_pairs = (long long)BM * dm.Hkv;
+  size_t bound = partials(decode_slots(all_pairs, p.steps_total));
+  if (p.prefill || p.split_local) {
+    const long long tiles = (long long)B * p.n_ttiles * dm.Hkv;
+    const long long n = p.prefill ? split_most(p.steps_total, tiles, kAttWaves, kMaxAttSplits)
+                                  : split_most(p.steps_mem, all_pairs, kAttWaves, kMaxAttSplits / 2) +
+                                        split_most((Lloc + 31) / 32, tiles, 1, kMaxAttSplits / 2);
+    const size_t tiled = partials(all_pairs * n) + krot_bytes;
+    bound = tiled > bound ? tiled : bound;
+  }
+  p.ws_bytes = bound > p.ws_bytes ? bound : p.ws_bytes;
   return p;
 }
 

@@ -215,6 +215,33 @@ def test_long_prompts_fit_the_built_in_scratch(lib, n_docs, n_kv_heads, M, k, to
     assert 0 < msa.score_topk_workspace_bytes(c, 1, M, k) <= msa.noalloc_scratch_bytes()
 
 
+@pytest.mark.parametrize("n_kv_heads,r,d,G,rotated,token_pool", [
+    (8, 4, 128, 512, 0, 0), (2, 4, 64, 512, 0, 0), (8, 1, 64, 64, 0, 1), (4, 8, 128, 8, 1, 0), (8, 2, 128, 256, 1, 1)])
+def test_attention_workspace_serves_smaller_calls(lib, n_kv_heads, r, d, G, rotated, token_pool):
+    """A workspace sized for the longest local context and the most documents of a program is large enough for every shorter
+    call, with document lengths or without (and, where the decode kernel alone runs, for fewer sequences)."""
+    c = _cfg(n_docs=1000, doc_len=G, chunk=G, n_q_heads=n_kv_heads * r, n_kv_heads=n_kv_heads, head_dim=d,
+             bank_keys_rotated=rotated, token_pool=token_pool)
+    with_lens = _cfg(n_docs=1000, doc_len=G, chunk=G, n_q_heads=n_kv_heads * r, n_kv_heads=n_kv_heads, head_dim=d,
+                     bank_keys_rotated=rotated, token_pool=token_pool)
+    with_lens.doc_lens = 0x10000
+    size = msa.sparse_attend_workspace_bytes
+    Ls = (0, 1, 31, 32, 33, 170, 300, 512, 1000, 1024, 1791, 1792, 2048, 4096, 8192)
+    ks = (1, 2, 4, 8, 9, 12, 16, 20, 24, 32, 50, 64)
+    Bs = (1, 2, 3, 4, 6, 8, 9, 12, 16, 20, 33, 40, 45, 64, 100, 300)
+    for B in Bs:
+        for M in (1, 2, 7, 16, 100):
+            for k in (4, 16, 64):
+                by_L = [size(c, B, M, k, L) for L in Ls]
+                assert by_L == sorted(by_L) and by_L == [size(with_lens, B, M, k, L) for L in Ls], (B, M, k)
+            by_k = [size(c, B, M, k, 700) for k in ks]
+            assert by_k == sorted(by_k), (B, M)
+    for M in (1, 2, 7):
+        for L in (5, 2048):
+            by_B = [size(c, B, M, 16, L) for B in Bs]
+            assert by_B == sorted(by_B), (M, L)
+
+
 def test_fetch_validation(lib):
     c = _cfg()
     cb = ctypes.byref(c)
