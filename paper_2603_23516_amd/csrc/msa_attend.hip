@@ -893,7 +893,7 @@ AttendPlan plan_attend(const Dims& dm, int B, int M, int k, int Lloc, int bank_k
     // and merge; a grid of P n of them so many rounds over the chip (documents of full length: the work of every
     // workgroup is known; with lengths this is the most it can be).  Over 770 shapes the n of least cost was 2 % from the
     // fastest of those tried.  (A rule that set the prologue at two steps and took rounds of short workgroups for half
-    // price split far too much where there are many pairs: 640 pairs of 89 steps 148 us, now 60; 7216 of 81 1747, 740.)
+    // price split far too much where there are many pairs: 640 pairs of 89 steps 148 us, now 71; 7216 of 81 1747, 737.)
     const long long S = p.steps_total;
     const long long most = decode_slots(pairs, S) / pairs;
     long long best = -1, best_n = 1;

@@ -12,7 +12,9 @@
 
 namespace msa {
 
-template <int D>
+// UB: loads per batch.  Sixteen take a whole chunk of 64 rows at d = 128 at once (4.3 GB: 726 us with eight -> 706 us);
+// chunks of eight loads or fewer would pay for the empty half (P = 32, d = 64, 0.5 GB: 106 us, with eight 93).
+template <int D, int UB>
 __global__ __launch_bounds__(256) void build_routing_keys_kernel(
     const uint16_t* __restrict__ K, uint16_t* __restrict__ KR, float* __restrict__ inv_norm,
     const int32_t* __restrict__ lens, int doc_begin, long long n_chunks, int Hkv, int G, int P, int C,
@@ -48,7 +50,6 @@ __global__ __launch_bounds__(256) void build_routing_keys_kernel(
   for (int e = 0; e < 8; ++e) acc[e] = 0.f;
 
   const int iters = P / RPL;
-  constexpr int UB = 16;  // loads per batch: a whole chunk of 64 rows at d = 128 at once (4.3 GB: 726 us with 8 -> 706 us)
   for (int it0 = 0; it0 < iters; it0 += UB) {
     uint4 v[UB];
 #pragma unroll
@@ -134,15 +135,16 @@ int launch_build(const Dims& dm, const void* K, int doc_begin, int doc_count, vo
     int cshift = 0;
     while ((1 << cshift) < dm.C) ++cshift;
     dim3 grid((unsigned)blocks), block(256);
+    const int loads = dm.P / (512 / dm.d);  // of a chunk
+#define MSA_BUILD(DD, UU) \
+  hipLaunchKernelGGL((build_routing_keys_kernel<DD, UU>), grid, block, 0, st, (const uint16_t*)K, (uint16_t*)KR, inv_norm, \
+                     dm.lens, doc_begin, n_chunks, dm.Hkv, dm.G, dm.P, dm.C, cshift, (long long)dm.tiles)
     if (dm.d == 128) {
-      hipLaunchKernelGGL(build_routing_keys_kernel<128>, grid, block, 0, st, (const uint16_t*)K,
-                         (uint16_t*)KR, inv_norm, dm.lens, doc_begin, n_chunks, dm.Hkv, dm.G, dm.P, dm.C,
-                         cshift, (long long)dm.tiles);
+      if (loads > 8) MSA_BUILD(128, 16); else MSA_BUILD(128, 8);
     } else {
-      hipLaunchKernelGGL(build_routing_keys_kernel<64>, grid, block, 0, st, (const uint16_t*)K,
-                         (uint16_t*)KR, inv_norm, dm.lens, doc_begin, n_chunks, dm.Hkv, dm.G, dm.P, dm.C,
-                         cshift, (long long)dm.tiles);
+      if (loads > 8) MSA_BUILD(64, 16); else MSA_BUILD(64, 8);
     }
+#undef MSA_BUILD
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
   }
   const int n_pad = (int)(dm.tiles * 16 - dm.NC);

@@ -19,7 +19,7 @@ struct PoolTheta {
   float2 estep[64];  // (cos, sin)(RPL * theta_u), RPL = rows per wave-wide load
 };
 
-template <int D, bool ROT>
+template <int D, bool ROT, int NB>
 __global__ __launch_bounds__(256) void pool_chunks_kernel(const uint16_t* __restrict__ X,
                                                           uint16_t* __restrict__ Xbar,
                                                           const int32_t* __restrict__ lens,
@@ -52,9 +52,9 @@ __global__ __launch_bounds__(256) void pool_chunks_kernel(const uint16_t* __rest
     if (pooled_lens != nullptr && g == 0 && j == 0 && lane == 0) pooled_lens[doc] = (len + P - 1) / P;
   }
 
-  // load pairs per batch: with the rotation four (eight cost it too many registers: 704 -> 705 us at d = 128, 114 ->
-  // 132 at d = 64), without it eight (703 -> 684 us)
-  constexpr int NB = ROT ? 4 : 8;
+  // NB load pairs per batch: with the rotation four (eight cost it too many registers: 704 -> 705 us at d = 128, 114 ->
+  // 132 at d = 64), without it eight (703 -> 684 us), where a chunk has more than four (P = 8, d = 128, 0.5 GB: 222 us with
+  // eight, 162 with four)
   uint4 v1[NB], v2[NB];
   auto load = [&](int it0) __attribute__((always_inline)) {
 #pragma unroll
@@ -69,8 +69,9 @@ __global__ __launch_bounds__(256) void pool_chunks_kernel(const uint16_t* __rest
       }
     }
   };
-  const int iters = (P + RPL - 1) / RPL;
-  const int last0 = (iters - 1) / NB * NB;  // the batches run from the last to the first (see below)
+  // batches that hold tokens; they run from the last to the first (see below)
+  const int iters = n_rows > 0 ? __builtin_amdgcn_readfirstlane((n_rows + RPL - 1) / RPL) : 1;
+  const int last0 = (iters - 1) / NB * NB;
   load(last0);  // on its way while the angles are worked out
   __shared__ float2 cs_s[ROT ? 8 : 1][64];
   float2 stp[8];
@@ -162,24 +163,25 @@ int launch_pool_kv(const Dims& dm, const void* K, const void* V, int doc_begin, 
     th.estep[u] = make_float2((float)cos(rpl * th.th[u]), (float)sin(rpl * th.th[u]));
   }
   dim3 grid((unsigned)blocks), block(256);
+#define MSA_POOL(DD, RR, BB, X, OUT, LENS_OUT) \
+  hipLaunchKernelGGL((pool_chunks_kernel<DD, RR, BB>), grid, block, 0, st, (const uint16_t*)X, (uint16_t*)OUT, dm.lens, \
+                     LENS_OUT, doc_begin, n_pairs, dm.Hkv, dm.G, dm.P, dm.C, th)
   if (Kbar != nullptr) {
-    if (dm.d == 128)
-      hipLaunchKernelGGL((pool_chunks_kernel<128, true>), grid, block, 0, st, (const uint16_t*)K,
-                         (uint16_t*)Kbar, dm.lens, pooled_lens, doc_begin, n_pairs, dm.Hkv, dm.G, dm.P, dm.C, th);
-    else
-      hipLaunchKernelGGL((pool_chunks_kernel<64, true>), grid, block, 0, st, (const uint16_t*)K,
-                         (uint16_t*)Kbar, dm.lens, pooled_lens, doc_begin, n_pairs, dm.Hkv, dm.G, dm.P, dm.C, th);
+    if (dm.d == 128) MSA_POOL(128, true, 4, K, Kbar, pooled_lens);
+    else MSA_POOL(64, true, 4, K, Kbar, pooled_lens);
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
   }
   if (Vbar != nullptr) {
-    if (dm.d == 128)
-      hipLaunchKernelGGL((pool_chunks_kernel<128, false>), grid, block, 0, st, (const uint16_t*)V,
-                         (uint16_t*)Vbar, dm.lens, Kbar == nullptr ? pooled_lens : nullptr, doc_begin, n_pairs, dm.Hkv, dm.G, dm.P, dm.C, th);
-    else
-      hipLaunchKernelGGL((pool_chunks_kernel<64, false>), grid, block, 0, st, (const uint16_t*)V,
-                         (uint16_t*)Vbar, dm.lens, Kbar == nullptr ? pooled_lens : nullptr, doc_begin, n_pairs, dm.Hkv, dm.G, dm.P, dm.C, th);
+    int32_t* const lens_out = Kbar == nullptr ? pooled_lens : nullptr;
+    const bool long_chunk = dm.P > 4 * rpl;
+    if (dm.d == 128) {
+      if (long_chunk) MSA_POOL(128, false, 8, V, Vbar, lens_out); else MSA_POOL(128, false, 4, V, Vbar, lens_out);
+    } else {
+      if (long_chunk) MSA_POOL(64, false, 8, V, Vbar, lens_out); else MSA_POOL(64, false, 4, V, Vbar, lens_out);
+    }
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
   }
+#undef MSA_POOL
   return MSA_OK;
 }
 

@@ -146,7 +146,8 @@ def test_all_heads_wide_more_candidates_than_k(copies):
     assert np.allclose(val.cpu().numpy(), s[..., want], rtol=0, atol=2e-5)
 
 
-@pytest.mark.parametrize("N,Hkv,G,P,d,first,count", [(5, 3, 56, 8, 64, 1, 3), (3, 1, 24, 24, 128, 0, 3), (7, 5, 256, 64, 128, 6, 1)])
+@pytest.mark.parametrize("N,Hkv,G,P,d,first,count", [(5, 3, 56, 8, 64, 1, 3), (3, 1, 24, 24, 128, 0, 3), (7, 5, 256, 64, 128, 6, 1),
+                                                        (5, 2, 512, 128, 64, 1, 4)])
 def test_pool_chunks_by_pairs(N, Hkv, G, P, d, first, count):
     """Pooled bank where the (document, head) pairs do not fill the workgroups, chunks do not fill a batch of loads, and
     a part of the bank is addressed; a bf16 mean is the rounded exact one, or its neighbour where the exact mean lies
@@ -171,6 +172,26 @@ def test_pool_chunks_by_pairs(N, Hkv, G, P, d, first, count):
                     rows = X[i, :, j * P:min(n, (j + 1) * P)]
                     want = rows.mean(1) if rows.shape[1] else np.zeros((Hkv, d))
                     assert np.abs(got[i, :, j] - want).max() <= 2.0 ** -8 * np.abs(want).max() + 1e-5
+
+
+@pytest.mark.parametrize("G,P,d", [(256, 128, 64), (64, 32, 64), (128, 32, 128), (512, 256, 128)])
+def test_routing_keys_by_batches(G, P, d):
+    """Chunks of four and eight loads (one batch of eight), of sixteen and of sixty-four (batches of sixteen): a key is the
+    rounded exact mean, or its neighbour at a tie, as for the pooled bank above."""
+    N, Hkv = 5, 2
+    Kb, K = S.normal_bf16(57000, (N, Hkv, G, d))
+    lens = (np.arange(N) * 53 % G + 1).astype(np.int32)
+    for ragged in (False, True):
+        cfg = msa.MsaConfig(N, G, P, Hkv, Hkv, d, 1e4, doc_lens=torch.from_numpy(lens).cuda() if ragged else None)
+        KR, inv = msa.msa_build_routing_keys(cfg, dev(Kb))
+        torch.cuda.synchronize()
+        got = msa.untile_routing_keys(cfg, KR).float().cpu().numpy().astype(np.float64).reshape(Hkv, N, G // P, d)
+        for i in range(N):
+            n = int(lens[i]) if ragged else G
+            for j in range(G // P):
+                first = j * P if j * P < n else 0
+                want = K[i, :, first:min(n, first + P)].mean(1)
+                assert np.abs(got[:, i, j] - want).max() <= 2.0 ** -8 * np.abs(want).max() + 1e-5
 
 
 # (N, Hkv, r, G, d, B, M, k, Lloc, scope, rotated): many (query, KV head) pairs in the decode kernel
