@@ -91,6 +91,9 @@ struct ScorePlan {
   int all_heads;         // 1: score_scan_all_kernel (scope ALL with more than one KV head)
   int seg_docs;          // all heads: documents per segment of the bank (one score matrix each)
   int part_docs;         // all heads: documents per part of a matrix row (n_splits parts per query in all)
+  int window_parts;      // all heads: parts whose lists the buffer at the workspace's start holds
+  int n_windows;         // > 1: a list per query and window at off_windows
+  size_t off_windows;
   int n_sel;             // selections per query token: Hkv, or 1 for scope ALL
   size_t off_tok;        // byte offset of the per-token winner keys (token pooling)
   int merge_parts;       // > 1: two-level merge, first level over merge_lpp lists per block

@@ -1155,16 +1155,17 @@ constexpr int kMaxSub = 1152;
 constexpr int kMaxSurv = 2048;
 
 // out_key != null: the winners are written as 64-bit keys instead (input of pool_tokens_kernel).
-// parts > 1: first level of a two-level merge for very many lists.  Block (g, qg, part) combines
+// out_parts > 1: first level of a two-level merge for very many lists.  Block (g, qg, part), part < parts, combines
 // lists [part * lpp, (part + 1) * lpp) and writes its k winners as a sorted list of keys to
-// out_key[g][qg][part][k], the input layout of a second call with n_lists = parts.
+// out_key[g][qg][part0 + part][k], the input layout of a second call with n_lists = out_parts.
 __global__ __launch_bounds__(256) void score_merge_kernel(const unsigned long long* __restrict__ ws,
                                                           int32_t* __restrict__ out_idx,
                                                           float* __restrict__ out_score,
                                                           unsigned long long* __restrict__ out_key,
                                                           int BM, int Hkv, int n_lists_total, int k,
-                                                          int lpp, int parts, const int* __restrict__ gate,
-                                                          int gate_tokens, int gate_blocks) {
+                                                          int lpp, int parts, int part0, int out_parts,
+                                                          const int* __restrict__ gate, int gate_tokens,
+                                                          int gate_blocks) {
   __shared__ unsigned long long sub[kMaxSub];
   __shared__ unsigned long long surv[kMaxSurv];
   __shared__ unsigned long long red[4];
@@ -1181,7 +1182,7 @@ __global__ __launch_bounds__(256) void score_merge_kernel(const unsigned long lo
   const int T = n_lists * k;
   const unsigned long long* src = ws + (((long long)g * BM + qg) * n_lists_total + l0) * k;
   const long long o_base =
-      (parts > 1) ? (((long long)g * BM + qg) * parts + part) * k : ((long long)qg * Hkv + g) * k;
+      (out_parts > 1) ? (((long long)g * BM + qg) * out_parts + part0 + part) * k : ((long long)qg * Hkv + g) * k;
 
   const int depth = (k + n_lists - 1) / n_lists;  // entries taken from the head of every list
   // k <= P < k + n_lists; any kMaxSub >= k heads of lists bound the k-th best key just as well
@@ -1385,9 +1386,11 @@ static void add_token_pool(const Dims& dm, int BM, int k, ScorePlan* p) {
 // of one segment stays under 24 MB, which bounds the workspace and keeps the matrix in the cache behind the L2s between
 // the scan that writes it and the selection that reads it.  Rows beyond 32768 documents are selected from in parts of 8192 (one
 // workgroup each) whose lists the merge kernel combines; up to there one workgroup per row, without the merge launch,
-// is the faster way.
+// is the faster way.  The lists of very long banks (more than kListsBytes: 16 queries, k = 32, from 12.6 million documents
+// on) go through their buffer in windows of whole segments, each merged to one list per query when it is full: with a
+// matrix of 20 MB the workspace then stays within the built-in scratch for any bank that fits the card.
 static void plan_all_heads(const Dims& dm, int BM, int k, ScorePlan* p) {
-  constexpr long long kMatBytes = (long long)24 << 20;
+  constexpr long long kListsBytes = (long long)6 << 20;
   p->mode = 2;
   p->tiles_per_wave = 0;
   p->exchange = p->it_publish = p->it_adopt = 0;
@@ -1395,11 +1398,19 @@ static void plan_all_heads(const Dims& dm, int BM, int k, ScorePlan* p) {
   p->n_pass = 1;
   p->q_per_pass = BM <= 8 ? 8 : (BM <= 16 ? 16 : 32);
   p->part_docs = dm.N <= 4 * kRowPart ? dm.N : kRowPart;
-  long long seg = kMatBytes / (4 * p->q_per_pass) / p->part_docs * p->part_docs;
+  p->n_splits = (int)(((long long)dm.N + p->part_docs - 1) / p->part_docs);  // parts of a row = lists per query
+  const long long lists = kListsBytes / ((long long)BM * k * 8);             // ... that the buffer holds (384 or more)
+  const bool windows = p->n_splits > lists;
+  const long long mat_bytes = (long long)(windows ? 20 : 24) << 20;
+  long long seg = mat_bytes / (4 * p->q_per_pass) / p->part_docs * p->part_docs;
   if (seg > dm.N || dm.N <= 4 * kRowPart) seg = dm.N;
   p->seg_docs = (int)seg;
-  p->n_splits = (dm.N + p->part_docs - 1) / p->part_docs;  // parts of a row = lists per query
-  size_t end = p->n_splits > 1 ? round_up256((size_t)BM * p->n_splits * k * sizeof(unsigned long long)) : 0;
+  const int seg_parts = (p->seg_docs + p->part_docs - 1) / p->part_docs;
+  p->window_parts = windows ? (int)(lists / seg_parts * seg_parts) : p->n_splits;
+  p->n_windows = (p->n_splits + p->window_parts - 1) / p->window_parts;
+  size_t end = p->n_splits > 1 ? round_up256((size_t)BM * p->window_parts * k * sizeof(unsigned long long)) : 0;
+  p->off_windows = end;
+  if (windows) end += round_up256((size_t)BM * p->n_windows * k * sizeof(unsigned long long));
   p->n_qtiles = p->q_per_pass / 8;
   p->off_qop = end;
   end += round_up256((size_t)dm.Hkv * p->n_qtiles * (dm.d / 32) * 64 * 16);
@@ -1441,7 +1452,10 @@ ScorePlan plan_score(const Dims& dm, int BM, int k) {
   }
   if (p.all_heads) {
     plan_all_heads(dm, BM, k, &p);
+    const int parts = p.n_splits;
+    if (p.n_windows > 1) p.n_splits = p.n_windows;  // what the last merge combines
     add_token_pool(dm, BM, k, &p);
+    p.n_splits = parts;
     return p;
   }
   p.q_per_pass = BM <= 8 ? 8 : ((BM <= 16 || k > 24) ? 16 : 32);
@@ -1513,13 +1527,13 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
       unsigned long long* part_keys = (unsigned long long*)((char*)ws + pl.off_part);
       hipLaunchKernelGGL(score_merge_kernel, dim3(BM * pl.n_sel * pl.merge_parts), dim3(256), 0, st, lists,
                          (int32_t*)nullptr, (float*)nullptr, part_keys, BM, pl.n_sel, n_lists, k,
-                         pl.merge_lpp, pl.merge_parts, gate, gate_tokens, gate_blocks);
+                         pl.merge_lpp, pl.merge_parts, 0, pl.merge_parts, gate, gate_tokens, gate_blocks);
       if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
       lists = part_keys;
       n_lists = pl.merge_parts;
     }
     hipLaunchKernelGGL(score_merge_kernel, dim3(BM * pl.n_sel), dim3(256), 0, st, lists, out_idx, out_score,
-                       tok_keys, BM, pl.n_sel, n_lists, k, n_lists, 1, gate, gate_tokens, gate_blocks);
+                       tok_keys, BM, pl.n_sel, n_lists, k, n_lists, 1, 0, 1, gate, gate_tokens, gate_blocks);
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
     return pool_tokens();
   };
@@ -1592,11 +1606,12 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
     sa.tiles = dm.tiles;
     ra.stride = pl.seg_docs;
     ra.part_docs = pl.part_docs;
-    ra.parts_total = pl.n_splits;
     ra.part_keys = pl.n_splits > 1 ? (unsigned long long*)ws : nullptr;
+    unsigned long long* const window_keys = (unsigned long long*)((char*)ws + pl.off_windows);
     const int nqt = pl.q_per_pass / 8;  // 1, 2 or 4
     profile_mark(dm, false, st);
-    for (int doc0 = 0; doc0 < dm.N; doc0 += pl.seg_docs) {
+    for (long long seg0 = 0; seg0 < dm.N; seg0 += pl.seg_docs) {
+      const int doc0 = (int)seg0;
       const int n_docs = dm.N - doc0 < pl.seg_docs ? dm.N - doc0 : pl.seg_docs;
       sa.nq = BM;
       sa.tile0 = (long long)doc0 * dm.C / 16;  // doc0 is a multiple of 8192 (or 0)
@@ -1627,10 +1642,20 @@ do { \
       ra.n_docs = n_docs;
       ra.doc0 = doc0;
       ra.parts = (n_docs + pl.part_docs - 1) / pl.part_docs;
-      ra.part0 = doc0 / pl.part_docs;
+      const int part = doc0 / pl.part_docs, window = part / pl.window_parts;
+      const int last = pl.n_splits - window * pl.window_parts;  // parts from this window's first to the bank's last
+      ra.parts_total = last < pl.window_parts ? last : pl.window_parts;
+      ra.part0 = part - window * pl.window_parts;
       launch_topk_rows(ra, st);
       if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
+      if (pl.n_windows > 1 && ra.part0 + ra.parts == ra.parts_total) {
+        hipLaunchKernelGGL(score_merge_kernel, dim3(BM), dim3(256), 0, st, (const unsigned long long*)ws,
+                           (int32_t*)nullptr, (float*)nullptr, window_keys, BM, 1, ra.parts_total, k, ra.parts_total, 1,
+                           window, pl.n_windows, (const int*)nullptr, 1, 0);
+        if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
+      }
     }
+    if (pl.n_windows > 1) return merge(window_keys, pl.n_windows);
     if (pl.n_splits > 1) return merge((const unsigned long long*)ws, pl.n_splits);
     return pool_tokens();
   }

@@ -215,6 +215,15 @@ def test_long_prompts_fit_the_built_in_scratch(lib, n_docs, n_kv_heads, M, k, to
     assert 0 < msa.score_topk_workspace_bytes(c, 1, M, k) <= msa.noalloc_scratch_bytes()
 
 
+@pytest.mark.parametrize("n_docs,B,k", [(6000000, 32, 48), (20000000, 24, 32), (50000000, 4, 48), (50000000, 32, 9),
+                                        (500000000, 32, 32), (500000000, 24, 64)])
+@pytest.mark.parametrize("token_pool", [0, 1])
+def test_long_banks_fit_the_built_in_scratch(lib, n_docs, B, k, token_pool):
+    """One selection for all heads over very long banks: the lists of a row's parts do not grow with the bank."""
+    c = _cfg(n_docs=n_docs, doc_len=64, chunk=64, select_scope=msa.MSA_SCOPE_ALL, token_pool=token_pool)
+    assert 0 < msa.score_topk_workspace_bytes(c, B, 1, k) <= msa.noalloc_scratch_bytes()
+
+
 @pytest.mark.parametrize("n_kv_heads,r,d,G,rotated,token_pool", [
     (8, 4, 128, 512, 0, 0), (2, 4, 64, 512, 0, 0), (8, 1, 64, 64, 0, 1), (4, 8, 128, 8, 1, 0), (8, 2, 128, 256, 1, 1)])
 def test_attention_workspace_serves_smaller_calls(lib, n_kv_heads, r, d, G, rotated, token_pool):

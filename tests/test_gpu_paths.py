@@ -50,6 +50,42 @@ def test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim):
         check_topk_generic(q, KRb, C, N, idx, val, k, sim, "all", pool, atol=2e-5 if sim == "cos" else 2e-4)
 
 
+@pytest.mark.parametrize("pool", [0, 1])
+def test_all_heads_scan_lists_in_windows(pool):
+    """A bank of 416 parts, of whose lists the buffer holds 380 (32 queries, k = 64): two windows, the second short.
+    Against float64 scores on the GPU."""
+    N, Hkv, d, B, k = 3400007, 2, 64, 32, 64
+    say(f"all-heads scan, lists in windows: N={N} B={B} k={k} pool={pool}")
+    cfg = msa.MsaConfig(N, 64, 64, Hkv, Hkv, d, 1e6, select_scope=msa.MSA_SCOPE_ALL, token_pool=pool)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(58000)
+    KR, inv = msa.alloc_routing_index(cfg)
+    KR.normal_(generator=gen)
+    KR[:, -1, :, N % 16:] = 0
+    plain = KR.permute(0, 1, 3, 2, 4).reshape(Hkv, -1, d)[:, :N]
+    inv.zero_()
+    for g in range(Hkv):
+        inv[g, :N] = 1.0 / plain[g].float().norm(dim=-1)
+    q = torch.randn((B // 4, 4, Hkv, d) if pool else (B, 1, Hkv, d), generator=gen, device="cuda").to(torch.bfloat16)
+    ws = torch.full((msa.score_topk_workspace_bytes(cfg, q.shape[0], q.shape[1], k),), 0xFF, dtype=torch.uint8, device="cuda")
+    idx, val = msa.msa_score_topk(cfg, q, KR, inv, k, workspace=ws)
+    torch.cuda.synchronize()
+    x = q.double().reshape(B, Hkv, d)
+    x = x / x.norm(dim=-1, keepdim=True)
+    for b in range(0, B, 4):                      # four rows of scores at a time
+        ref = torch.zeros((4, N), dtype=torch.float64, device="cuda")
+        for g in range(Hkv):
+            kg = plain[g].double()
+            ref += x[b:b + 4, g] @ (kg / kg.norm(dim=-1, keepdim=True)).t().contiguous() / Hkv
+        if pool:
+            ref = ref.amax(0, keepdim=True)
+        for i in range(ref.shape[0]):
+            gi, gv = idx.reshape(-1, k)[b // 4 if pool else b + i].long(), val.reshape(-1, k)[b // 4 if pool else b + i].double()
+            best = ref[i].topk(k).values
+            assert gi.unique().numel() == k and (gv - ref[i][gi]).abs().max() <= 2e-5
+            assert (gv - best).abs().max() <= 2e-5    # the k best, in order (up to fp32 rounding of the scores)
+
+
 # (N, Hkv, r, C, d, B, M, k, sim): the scoring GEMM with more than 16 selected documents
 GEMM_K32 = [
     (5003, 2, 2, 8, 128, 1, 300, 32, "cos"),      # one-pass filter, lists shorter than k
