@@ -1006,7 +1006,7 @@ __global__ __launch_bounds__(kPoolThreads) void pool_tokens_kernel(const unsigne
 // over the part take over.
 constexpr int kRowSurv = 2048;
 constexpr int kRowRegs = 32;        // scores a thread keeps in registers between the two passes (8: short rows)
-constexpr int kRowPart = 8192;      // documents per part of a long row: what 32 registers per thread hold
+constexpr int kRowPart = 8192;      // documents per part of a long row: what 32 registers per thread of four waves hold
 
 struct RowsArgs {
   const float* mat;           // [selections][BM][stride]
@@ -1384,9 +1384,9 @@ static void add_token_pool(const Dims& dm, int BM, int k, ScorePlan* p) {
 
 // All-heads scan: one pass of up to 32 queries (more take the wide kernel) over segments of the bank; the score matrix
 // of one segment stays under 24 MB, which bounds the workspace and keeps the matrix in the cache behind the L2s between
-// the scan that writes it and the selection that reads it.  Rows beyond 32768 documents are selected from in parts of 8192 (one
+// the scan that writes it and the selection that reads it.  Rows beyond 32768 documents are selected from in parts (one
 // workgroup each) whose lists the merge kernel combines; up to there one workgroup per row, without the merge launch,
-// is the faster way.  The lists of very long banks (more than kListsBytes: 16 queries, k = 32, from 12.6 million documents
+// is the faster way.  The lists of very long banks (more than kListsBytes: 16 queries, k = 32, from 50 million documents
 // on) go through their buffer in windows of whole segments, each merged to one list per query when it is full: with a
 // matrix of 20 MB the workspace then stays within the built-in scratch for any bank that fits the card.
 static void plan_all_heads(const Dims& dm, int BM, int k, ScorePlan* p) {
@@ -1397,7 +1397,10 @@ static void plan_all_heads(const Dims& dm, int BM, int k, ScorePlan* p) {
   p->off_gmax = 0;
   p->n_pass = 1;
   p->q_per_pass = BM <= 8 ? 8 : (BM <= 16 ? 16 : 32);
-  p->part_docs = dm.N <= 4 * kRowPart ? dm.N : kRowPart;
+  // five segments or more: parts of 32768, which sixteen waves hold in registers, a quarter of the lists (32 queries, 4
+  // million documents, k = 64: 727 -> 619 us); fewer: the short ones are 1 to 3 % faster (24 queries, 40000 documents: 124, 127)
+  const bool many = (long long)dm.N * 4 * p->q_per_pass >= 5 * ((long long)24 << 20);
+  p->part_docs = dm.N <= 4 * kRowPart ? dm.N : (many ? 4 * kRowPart : kRowPart);
   p->n_splits = (int)(((long long)dm.N + p->part_docs - 1) / p->part_docs);  // parts of a row = lists per query
   const long long lists = kListsBytes / ((long long)BM * k * 8);             // ... that the buffer holds (384 or more)
   const bool windows = p->n_splits > lists;

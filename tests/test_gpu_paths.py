@@ -29,6 +29,7 @@ ALL_SCAN = [
     (32768, 2, 1, 1, 64, 1, 1, 64, "cos"),        # the longest row that one workgroup takes
     (32785, 2, 1, 2, 64, 2, 2, 64, "cos"),        # rows in five parts, the last of 17 documents (fewer than k)
     (200007, 2, 1, 1, 64, 25, 1, 7, "cos"),       # two segments of the bank
+    (983057, 2, 1, 1, 64, 17, 1, 64, "cos"),      # six segments in parts of 32768, the last of 17 documents
 ]
 
 
@@ -52,9 +53,9 @@ def test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim):
 
 @pytest.mark.parametrize("pool", [0, 1])
 def test_all_heads_scan_lists_in_windows(pool):
-    """A bank of 416 parts, of whose lists the buffer holds 380 (32 queries, k = 64): two windows, the second short.
+    """A bank of 388 parts, of whose lists the buffer holds 380 (32 queries, k = 64): two windows, the second short.
     Against float64 scores on the GPU."""
-    N, Hkv, d, B, k = 3400007, 2, 64, 32, 64
+    N, Hkv, d, B, k = 12700007, 2, 64, 32, 64
     say(f"all-heads scan, lists in windows: N={N} B={B} k={k} pool={pool}")
     cfg = msa.MsaConfig(N, 64, 64, Hkv, Hkv, d, 1e6, select_scope=msa.MSA_SCOPE_ALL, token_pool=pool)
     gen = torch.Generator(device="cuda")
