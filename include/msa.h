@@ -186,11 +186,12 @@ int msa_pool_kv(const msa_config_t* cfg, const void* K, const void* V, int32_t d
  *   out_score out  fp32  [B][M'][S][k], may be NULL
  *   workspace      >= msa_score_topk_workspace_bytes(cfg, B, M, k); contents undefined on entry/exit
  * Scores are accumulated in fp32; each query is carried as a bf16 (hi, lo) pair, so a score differs
- * from exact arithmetic by a few 1e-6 relative.  (With many query tokens, cosine, d = 128 and eight chunks per
- * document the matrix product runs on the hi parts alone as a filter, and the reported scores of the winners are
- * recomputed in fp32 from the fp32 folded query: the selection is the same as with exact scores.  The filter's
- * error band assumes |KR row| * inv_norm <= 1.01, which holds for what msa_build_routing_keys writes; an index
- * from elsewhere must keep to it.)
+ * from exact arithmetic by a few 1e-6 relative.  (With many query tokens -- more than 32 with select_scope = ALL, else 64
+ * or more --, cosine, d = 128 and eight chunks per document the matrix product runs on the hi parts alone as a filter,
+ * and the reported scores of the winners are recomputed in fp32 from the fp32 folded query: the selection is the same
+ * as with exact scores.  The filter's error band assumes |KR row| * inv_norm <= 1.01, which holds for what
+ * msa_build_routing_keys writes; an index of that shape from elsewhere must keep to it.  Every other shape is scored
+ * with both parts, whatever the norms.)
  */
 int msa_score_topk(const msa_config_t* cfg, const void* q_route, int32_t B, int32_t M,
                    const void* KR, const float* inv_norm, int32_t k, int32_t* out_idx,

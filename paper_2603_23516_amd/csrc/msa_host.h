@@ -58,7 +58,7 @@ int launch_fold_queries(const Dims& dm, const void* q_route, int BM, float* qf, 
 
 // Head mean over every head for many query tokens (msa_score_wide.hip): passes of tokens, segments of the bank.
 struct WidePlan {
-  int pair;              // 1: hi and lo rows (dot product), 32 tokens per workgroup; 0: hi rows alone, 64
+  int pair;              // 1: hi and lo rows, 32 tokens per workgroup; 0: hi rows alone, 64
   int pass_tokens;       // query tokens per pass
   int n_tb;              // token blocks (64 operand rows) of a whole pass
   int seg_docs;          // documents per segment (one score matrix)

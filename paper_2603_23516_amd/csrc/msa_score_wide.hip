@@ -14,10 +14,12 @@
 //                         and write the document maxima.  The waves never synchronise after the operands are in.
 //   score_wide_select_kernel  per token: the candidates of the matrix row and their exact scores.
 //
-// One pass (cosine): only the hi parts are multiplied, 64 tokens per workgroup.  The matrix then holds scores within
-// the bound eps that fold_queries_kernel writes; every document within 2 eps of the k-th best is scored again in fp32
-// from the folded fp32 query.  The dot product has no such bound (keys of any length): there hi and lo parts are
-// neighbouring rows (32 tokens per workgroup), and the matrix holds the scores to ~16 bits of the query, as the scan's.
+// One pass (cosine, d = 128, eight chunks per document): only the hi parts are multiplied, 64 tokens per workgroup.  The
+// matrix then holds scores within the bound eps that fold_queries_kernel writes; every document within 2 eps of the
+// k-th best is scored again in fp32 from the folded fp32 query.  The bound takes |key| * inv_norm for one, which the
+// interface asks of an index of that shape alone.  Otherwise, and for the dot product (keys of any length), hi and lo
+// parts are neighbouring rows (32 tokens per workgroup), and the matrix holds the scores to ~16 bits of the query, as
+// the scan's.
 //
 // Bound: the matrix cores, then LDS (every operand read feeds four products: 64 of 128 B per cycle and CU at the full
 // matrix rate) and the L2 (a key is read once per 64 rows: 64 B per cycle and CU).  The workgroups of all token blocks
@@ -53,7 +55,7 @@ struct WideArgs {
   int seg_tiles, seg_docs; // tiles and documents of the segment
 };
 
-template <int D, int HKV, bool PAIR>
+template <int D, int HKV, bool PAIR, bool COS>
 __global__ __launch_bounds__(64 * kWideWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void score_wide_kernel(WideArgs a) {
   constexpr int NS = D / 32;
@@ -93,7 +95,7 @@ void score_wide_kernel(WideArgs a) {
   // there, and the sums would need registers the loop does not have.
   typedef const __attribute__((address_space(1))) char* gptr_t;
   const gptr_t kr0 = (gptr_t)a.KR + a.tile0 * (TILE_ELEMS * 2);
-  const gptr_t in0 = (gptr_t)a.inv_norm + a.tile0 * 64;  // (PAIR: not read)
+  const gptr_t in0 = (gptr_t)a.inv_norm + a.tile0 * 64;  // (COS only)
   const int last_tile = a.seg_tiles - 1;
 
   u32x4_t buf[2][KT][NS];
@@ -111,12 +113,12 @@ void score_wide_kernel(WideArgs a) {
 #pragma unroll
       for (int s = 0; s < NS; ++s)
         b[kt][s] = *(const __attribute__((address_space(1))) u32x4_t*)(p + s * 1024 + (size_t)(ln * 16));
-      if constexpr (!PAIR) bi[kt] = *(const __attribute__((address_space(1))) float*)(in0 + at * 64 + (size_t)((ln & 15) * 4));
+      if constexpr (COS) bi[kt] = *(const __attribute__((address_space(1))) float*)(in0 + at * 64 + (size_t)((ln & 15) * 4));
     }
   };
   request(w, 0, buf[0], binv[0]);
   request(w, 1, buf[1], binv[1]);
-  wait_copies_but<2 * KT * (NS + (PAIR ? 0 : 1))>();  // the operands are older than the keys
+  wait_copies_but<2 * KT * (NS + (COS ? 1 : 0))>();  // the operands are older than the keys
   lds_barrier();
 
   const int dpt = 16 / a.C;
@@ -140,7 +142,7 @@ void score_wide_kernel(WideArgs a) {
       for (int kt = 0; kt < KT; ++kt) {
 #pragma unroll
         for (int s = 0; s < NS; ++s) asm volatile("" : "+v"(buf[slot][kt][s]));
-        if constexpr (!PAIR) asm volatile("" : "+v"(binv[slot][kt]));
+        if constexpr (COS) asm volatile("" : "+v"(binv[slot][kt]));
       }
 #pragma unroll
       for (int tq = 0; tq < NT; ++tq) {
@@ -161,10 +163,10 @@ void score_wide_kernel(WideArgs a) {
         for (int kt = 0; kt < KT; ++kt)
 #pragma unroll
           for (int i = 0; i < 4; ++i) {
-            if constexpr (PAIR)
-              tot[tq][kt][i] = g == 0 ? acc[kt][i] : tot[tq][kt][i] + acc[kt][i];
-            else
+            if constexpr (COS)
               tot[tq][kt][i] = g == 0 ? acc[kt][i] * binv[slot][kt] : fmaf(acc[kt][i], binv[slot][kt], tot[tq][kt][i]);
+            else
+              tot[tq][kt][i] = g == 0 ? acc[kt][i] : tot[tq][kt][i] + acc[kt][i];
           }
         // the totals are formed HERE (deferred, the accumulators of all tiles would be live together)
 #pragma unroll
@@ -245,8 +247,8 @@ constexpr int kWideRegs = 64;      // scores a thread keeps in registers (16: sh
 struct WideSelArgs {
   const float* mat;
   long long mat_stride;
-  const float* eps;        // [tokens][Hkv], or null: the matrix holds the exact scores
-  const float* qf;         // [tokens][Hkv][d]
+  const float* eps;        // BAND: [tokens][Hkv]
+  const float* qf;         // BAND: [tokens][Hkv][d]
   const uint16_t* KR;
   const float* inv_norm;
   unsigned long long* best;  // [tokens][k] keys of the segments so far
@@ -254,28 +256,29 @@ struct WideSelArgs {
   int32_t* out_idx;
   float* out_score;
   unsigned long long* out_key;
-  int Hkv, C, k;
+  int Hkv, k;
   int n_docs, doc0;        // documents of the segment, number of the first
   int tok0;                // token number of the pass's first token
   long long tiles;
 };
 
-template <int D, int REGS>
+// BAND: the matrix holds the one-pass scores (d = 128, eight chunks per document).
+template <bool BAND, int REGS>
 __global__ __launch_bounds__(kWideSel) void score_wide_select_kernel(WideSelArgs a) {
   constexpr int NW = kWideSel / 64;
+  constexpr int D = 128, C = 8;
   __shared__ unsigned long long surv[kWideSurv + MSA_MAX_TOPK + 8];
-  __shared__ float qs[8 * D];
+  __shared__ float qs[BAND ? 8 * D : 1];
   __shared__ unsigned long long best_s[MSA_MAX_TOPK];
   __shared__ uint32_t theta_w[2][NW];
   __shared__ uint32_t kth_s;
   __shared__ int n_surv;
   const int tid = threadIdx.x;
-  const int lane = tid & 63;
   const int tok = blockIdx.x;
   const int k = a.k, N = a.n_docs;
   const float* __restrict__ row = a.mat + (long long)tok * a.mat_stride;
   float eps = 0.f;
-  if (a.eps != nullptr) {
+  if constexpr (BAND) {
     for (int g = 0; g < a.Hkv; ++g) eps += a.eps[(long long)tok * a.Hkv + g];
     eps /= (float)a.Hkv;
     for (int i = tid; i < a.Hkv * D; i += kWideSel) qs[i] = a.qf[(long long)tok * a.Hkv * D + i];
@@ -289,15 +292,15 @@ __global__ __launch_bounds__(kWideSel) void score_wide_select_kernel(WideSelArgs
 
   // exact scores of the documents surv[0 .. ns), in place of their keys; eight lanes per (document, chunk)
   auto rescore = [&](int ns) {
-    if (a.eps == nullptr) return;
+    if constexpr (!BAND) return;
     const int part = tid & 7;
-    const int per = kWideSel / 8 / a.C;      // documents per round (C <= 16)
-    const int ch = (tid >> 3) & (a.C - 1);
+    constexpr int per = kWideSel / 8 / C;    // documents per round: one per wave
+    const int ch = (tid >> 3) & (C - 1);
     const float inv_g = 1.0f / (float)a.Hkv;
     for (int j0 = 0; j0 < ns; j0 += per) {   // block-uniform
-      const int j = j0 + (tid >> 3) / a.C;
+      const int j = j0 + (tid >> 3) / C;
       const uint32_t doc = key_doc(surv[j < ns ? j : ns - 1]);
-      const long long key = (long long)doc * a.C + ch;
+      const long long key = (long long)doc * C + ch;
       const uint16_t* kp = a.KR + (key >> 4) * (16 * D) + (part * (D / 64) * 16 + (int)(key & 15)) * 8;
       float tot = 0.f;
       for (int g0 = 0; g0 < a.Hkv; g0 += 4) {  // the loads of four groups in flight (Hkv = 2: the last one again, dropped)
@@ -336,14 +339,8 @@ __global__ __launch_bounds__(kWideSel) void score_wide_select_kernel(WideSelArgs
         }
       }
       float sc = tot * inv_g;
-      for (int off = 8; off < 8 * a.C && off < 64; off <<= 1) sc = fmaxf(sc, __shfl_xor(sc, off, 64));
-      if (a.C == 16) {  // a document's chunks sit in two waves
-        float* half = reinterpret_cast<float*>(&surv[kWideSurv + MSA_MAX_TOPK]);  // 8 keys = 16 floats: one per half
-        __syncthreads();
-        if (lane == 0) half[tid >> 6] = sc;
-        __syncthreads();
-        sc = fmaxf(sc, half[(tid >> 6) ^ 1]);
-      }
+#pragma unroll
+      for (int off = 8; off < 8 * C; off <<= 1) sc = fmaxf(sc, __shfl_xor(sc, off, 64));
       __syncthreads();  // every lane has read its document
       if (part == 0 && ch == 0 && j < ns) surv[j] = make_key(sc, doc);
     }
@@ -420,7 +417,7 @@ __global__ __launch_bounds__(kWideSel) void score_wide_select_kernel(WideSelArgs
   __syncthreads();
   if (ns <= kWideSurv) {
     // ---- 2. t~, candidates -----------------------------------------------------------------------------------------
-    if (a.eps != nullptr && ns > k) {
+    if (BAND && ns > k) {
       if (tid < 8) surv[ns + tid] = 0ull;
       __syncthreads();
       unsigned long long mine[kWideSurv / kWideSel];
@@ -490,7 +487,7 @@ bool wide_path_applies(const Dims& dm, int BM) { return dm.scope_all && dm.Hkv >
 
 WidePlan plan_score_wide(const Dims& dm, int BM, int k) {
   WidePlan p;
-  p.pair = dm.cos ? 0 : 1;
+  p.pair = (dm.cos && dm.d == 128 && dm.C == 8) ? 0 : 1;
   const int n_pass = (BM + kWidePass - 1) / kWidePass;
   p.pass_tokens = (BM + n_pass - 1) / n_pass;
   const int per_wg = kWideRows / (p.pair ? 2 : 1);
@@ -539,7 +536,6 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
   s.out_score = out_score;
   s.out_key = out_key;
   s.Hkv = dm.Hkv;
-  s.C = dm.C;
   s.k = k;
   s.tiles = dm.tiles;
   const int per_wg = kWideRows / (pl.pair ? 2 : 1);
@@ -567,8 +563,9 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
       dim3 grid((unsigned)((a.n_tb * streams + 7) / 8 * 8)), block(64 * kWideWaves);
 #define MSA_WIDE(DD, HH) \
   do { \
-    if (pl.pair) hipLaunchKernelGGL((score_wide_kernel<DD, HH, true>), grid, block, 0, st, a); \
-    else hipLaunchKernelGGL((score_wide_kernel<DD, HH, false>), grid, block, 0, st, a); \
+    if (!pl.pair) hipLaunchKernelGGL((score_wide_kernel<128, HH, false, true>), grid, block, 0, st, a); \
+    else if (dm.cos) hipLaunchKernelGGL((score_wide_kernel<DD, HH, true, true>), grid, block, 0, st, a); \
+    else hipLaunchKernelGGL((score_wide_kernel<DD, HH, true, false>), grid, block, 0, st, a); \
   } while (0)
       if (dm.d == 128) {
         if (dm.Hkv == 2) MSA_WIDE(128, 2); else if (dm.Hkv == 4) MSA_WIDE(128, 4); else MSA_WIDE(128, 8);
@@ -583,14 +580,14 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
       s.n_docs = n_docs;
       s.doc0 = doc0;
       s.tok0 = tok0;
-#define MSA_WIDE_SELECT(DD) \
+#define MSA_WIDE_SELECT(BB) \
   do { \
     if (n_docs <= 16 * kWideSel) \
-      hipLaunchKernelGGL((score_wide_select_kernel<DD, 16>), dim3((unsigned)nq), dim3(kWideSel), 0, st, s); \
+      hipLaunchKernelGGL((score_wide_select_kernel<BB, 16>), dim3((unsigned)nq), dim3(kWideSel), 0, st, s); \
     else \
-      hipLaunchKernelGGL((score_wide_select_kernel<DD, kWideRegs>), dim3((unsigned)nq), dim3(kWideSel), 0, st, s); \
+      hipLaunchKernelGGL((score_wide_select_kernel<BB, kWideRegs>), dim3((unsigned)nq), dim3(kWideSel), 0, st, s); \
   } while (0)
-      if (dm.d == 128) MSA_WIDE_SELECT(128); else MSA_WIDE_SELECT(64);
+      if (pl.pair) MSA_WIDE_SELECT(false); else MSA_WIDE_SELECT(true);
 #undef MSA_WIDE_SELECT
       if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
     }

@@ -158,12 +158,35 @@ def test_all_heads_wide(N, Hkv, r, C, d, B, M, k, sim):
     test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim)
 
 
-@pytest.mark.parametrize("copies", [300, 4000])
-def test_all_heads_wide_more_candidates_than_k(copies):
+@pytest.mark.parametrize("C,d", [(8, 64), (4, 128)])
+def test_all_heads_wide_takes_any_norms(C, d):
+    """An index whose reciprocal norms are not those of its keys (a hundred times them, more or less): scored as it is
+    wherever the one-pass filter, whose error band is that of unit keys, is not announced."""
+    N, Hkv, M, k = 3000, 2, 40, 8
+    say(f"all-heads scoring with norms of its own C={C} d={d}")
+    cfg = msa.MsaConfig(N, 8 * C, 8, Hkv, Hkv, d, 1e6, select_scope=msa.MSA_SCOPE_ALL)
+    KRb, inv = random_index(59000 + d, N, Hkv, C, d)
+    inv = (inv * np.random.default_rng(59001).uniform(50, 150, inv.shape)).astype(np.float32).astype(np.float64)
+    qb, q = S.normal_bf16(59002, (1, M, Hkv, d))
+    dKR, dinv = upload_oracle_index(cfg, KRb, inv)
+    idx, val = msa.msa_score_topk(cfg, dev(qb), dKR, dinv, k)
+    torch.cuda.synchronize()
+    x = q[0] / np.linalg.norm(q[0], axis=-1, keepdims=True)                     # [M][Hkv][d]
+    s = sum((x[:, g] @ KRb[g].T) * inv[g] for g in range(Hkv)) / Hkv
+    s = s.reshape(M, N, C).max(-1)
+    want = np.sort(s, axis=-1)[:, ::-1][:, :k]
+    got = idx.cpu().numpy()[0, :, 0]
+    # scores of up to ~60 with queries carried to 16 bits and fp32 sums: 2e-5 of the largest at most
+    assert np.abs(np.take_along_axis(s, got.astype(np.int64), -1) - want).max() <= 2e-5 * want.max()
+    assert np.abs(val.cpu().numpy()[0, :, 0] - want).max() <= 2e-5 * want.max()
+
+
+@pytest.mark.parametrize("copies,d", [(300, 64), (4000, 64), (300, 128), (4000, 128)])
+def test_all_heads_wide_more_candidates_than_k(copies, d):
     """Copies of one document tie exactly: all of them are candidates of every token (4000: more than the selection
     keeps on chip, so the row goes through it in windows); ties go to the lower index."""
-    N, Hkv, C, d, M, k = 6000, 2, 8, 64, 40, 12
-    say(f"all-heads selection with {copies} copies of the best document")
+    N, Hkv, C, M, k = 6000, 2, 8, 40, 12
+    say(f"all-heads selection with {copies} copies of the best document, d={d}")
     cfg = msa.MsaConfig(N, 8 * C, 8, Hkv, Hkv, d, 1e6, select_scope=msa.MSA_SCOPE_ALL)
     KRb, _ = random_index(52000, N, Hkv, C, d)
     qb, q = S.normal_bf16(52001, (1, M, Hkv, d))
