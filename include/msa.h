@@ -25,7 +25,8 @@
  *     before the call returns.
  *   - Ownership: the caller owns every buffer, workspace included.  The library allocates nothing,
  *     frees nothing and keeps no state between calls (msa_score_topk_noalloc brings its own fixed
- *     scratch buffer in place of a workspace).
+ *     scratch buffer in place of a workspace; a host thread keeps the last table of RoPE angles it made, constants
+ *     of rope_base and head_dim, 1.5 KB).
  *   - Asynchrony: work is enqueued on `stream` (a hipStream_t passed as void*, NULL = default
  *     stream); no call synchronises.  Outputs are valid once the stream reaches that point.
  *   - Errors: 0 on success, a negative msa_status otherwise.  Arguments are validated on the host
@@ -273,7 +274,8 @@ int msa_fetch_selected(const msa_config_t* cfg, const void* K_host, const void* 
  * Several routed layers on their banks in one call (Section 3.2.1: routing in the latter half of the layers): for every
  * layer in turn msa_score_topk(cfg, ...) on stream `route`, then msa_sparse_attend(attend_cfg, ...) on stream `attend`;
  * a layer's attention waits for its selection, the next layer is routed meanwhile.  Exactly those calls, in that order,
- * with their checks (a refused layer ends the call with its status; the layers before it have been enqueued).
+ * with their checks: the status of the first layer that either call would refuse, before anything is enqueued.  (After
+ * MSA_ERR_HIP the launches before the one that failed have been enqueued, and `caller` waits for them.)
  *   fork      event: recorded on `caller`, awaited by both streams first
  *   join      event: recorded on `attend` last, awaited by `caller`
  * With route == attend the scored events are not used.  All events are the caller's and may be reused by the next call.

@@ -105,6 +105,49 @@ static int scratch_on_current_device(void** out) {
   return MSA_OK;
 }
 
+// Everything that msa_score_topk refuses, and its plan.
+static int check_score(const msa_config_t* cfg, const void* q_route, int32_t B, int32_t M, const void* KR,
+                       const float* inv_norm, int32_t k, const int32_t* out_idx, const float* out_score,
+                       const void* workspace, size_t workspace_bytes, Dims* dm, ScorePlan* pl) {
+  const int rc = make_dims(cfg, dm);
+  if (rc != MSA_OK) return rc;
+  if (q_route == nullptr || KR == nullptr || out_idx == nullptr || workspace == nullptr)
+    return MSA_ERR_INVALID_ARG;
+  if (inv_norm == nullptr && dm->cos) return MSA_ERR_INVALID_ARG;
+  if (B < 1 || M < 1 || (int64_t)B * M > (1 << 20)) return MSA_ERR_INVALID_ARG;
+  if (k < 1 || k > dm->N) return MSA_ERR_INVALID_ARG;
+  if (k > MSA_MAX_TOPK) return MSA_ERR_UNSUPPORTED;
+  if (misaligned(q_route) || misaligned(KR) || misaligned(inv_norm) || misaligned(out_idx) ||
+      misaligned(out_score) || misaligned(workspace))
+    return MSA_ERR_MISALIGNED;
+  *pl = plan_score(*dm, B * M, k);
+  return workspace_bytes < pl->ws_bytes ? MSA_ERR_WORKSPACE : MSA_OK;
+}
+
+// The same for msa_sparse_attend.
+static int check_attend(const msa_config_t* cfg, const void* q, int32_t B, int32_t M, const void* K, const void* V,
+                        const int32_t* idx, int32_t k, const void* Kloc, const void* Vloc, int32_t Lloc,
+                        int32_t local_pos0, const int32_t* q_pos, const void* out, const float* lse,
+                        const void* workspace, size_t workspace_bytes, Dims* dm, AttendPlan* pl) {
+  const int rc = make_dims(cfg, dm, kForAttend);
+  if (rc != MSA_OK) return rc;
+  if (q == nullptr || K == nullptr || V == nullptr || idx == nullptr || q_pos == nullptr ||
+      out == nullptr || workspace == nullptr)
+    return MSA_ERR_INVALID_ARG;
+  if (B < 1 || M < 1 || Lloc < 0 || local_pos0 < 0) return MSA_ERR_INVALID_ARG;
+  if (Lloc > 0 && (Kloc == nullptr || Vloc == nullptr)) return MSA_ERR_INVALID_ARG;
+  if (k < 1) return MSA_ERR_INVALID_ARG;
+  if (k > MSA_MAX_TOPK || (int64_t)B * M > 65535 || !attend_doc_len_ok(cfg))
+    return MSA_ERR_UNSUPPORTED;
+  if ((int64_t)local_pos0 + Lloc > (1 << 24)) return MSA_ERR_UNSUPPORTED;
+  if (misaligned(q) || misaligned(K) || misaligned(V) || misaligned(idx) || misaligned(Kloc) ||
+      misaligned(Vloc) || misaligned(q_pos) || misaligned(out) || misaligned(lse) ||
+      misaligned(workspace) || misaligned4(dm->lens))
+    return MSA_ERR_MISALIGNED;
+  *pl = plan_attend(*dm, B, M, k, Lloc, cfg->bank_keys_rotated);
+  return workspace_bytes < pl->ws_bytes ? MSA_ERR_WORKSPACE : MSA_OK;
+}
+
 }  // namespace msa
 
 using namespace msa;
@@ -238,19 +281,9 @@ int msa_score_topk(const msa_config_t* cfg, const void* q_route, int32_t B, int3
                    const void* KR, const float* inv_norm, int32_t k, int32_t* out_idx,
                    float* out_score, void* workspace, size_t workspace_bytes, msa_stream_t stream) {
   Dims dm;
-  const int rc = make_dims(cfg, &dm);
+  ScorePlan pl;
+  const int rc = check_score(cfg, q_route, B, M, KR, inv_norm, k, out_idx, out_score, workspace, workspace_bytes, &dm, &pl);
   if (rc != MSA_OK) return rc;
-  if (q_route == nullptr || KR == nullptr || out_idx == nullptr || workspace == nullptr)
-    return MSA_ERR_INVALID_ARG;
-  if (inv_norm == nullptr && dm.cos) return MSA_ERR_INVALID_ARG;
-  if (B < 1 || M < 1 || (int64_t)B * M > (1 << 20)) return MSA_ERR_INVALID_ARG;
-  if (k < 1 || k > dm.N) return MSA_ERR_INVALID_ARG;
-  if (k > MSA_MAX_TOPK) return MSA_ERR_UNSUPPORTED;
-  if (misaligned(q_route) || misaligned(KR) || misaligned(inv_norm) || misaligned(out_idx) ||
-      misaligned(out_score) || misaligned(workspace))
-    return MSA_ERR_MISALIGNED;
-  const ScorePlan pl = plan_score(dm, B * M, k);
-  if (workspace_bytes < pl.ws_bytes) return MSA_ERR_WORKSPACE;
   return launch_score(dm, pl, q_route, B, M, KR, inv_norm, k, out_idx, out_score, workspace,
                       (hipStream_t)stream);
 }
@@ -288,23 +321,10 @@ int msa_sparse_attend(const msa_config_t* cfg, const void* q, int32_t B, int32_t
                       void* out, float* lse, void* workspace, size_t workspace_bytes,
                       msa_stream_t stream) {
   Dims dm;
-  const int rc = make_dims(cfg, &dm, kForAttend);
+  AttendPlan pl;
+  const int rc = check_attend(cfg, q, B, M, K, V, idx, k, Kloc, Vloc, Lloc, local_pos0, q_pos, out, lse, workspace,
+                              workspace_bytes, &dm, &pl);
   if (rc != MSA_OK) return rc;
-  if (q == nullptr || K == nullptr || V == nullptr || idx == nullptr || q_pos == nullptr ||
-      out == nullptr || workspace == nullptr)
-    return MSA_ERR_INVALID_ARG;
-  if (B < 1 || M < 1 || Lloc < 0 || local_pos0 < 0) return MSA_ERR_INVALID_ARG;
-  if (Lloc > 0 && (Kloc == nullptr || Vloc == nullptr)) return MSA_ERR_INVALID_ARG;
-  if (k < 1) return MSA_ERR_INVALID_ARG;
-  if (k > MSA_MAX_TOPK || (int64_t)B * M > 65535 || !attend_doc_len_ok(cfg))
-    return MSA_ERR_UNSUPPORTED;
-  if ((int64_t)local_pos0 + Lloc > (1 << 24)) return MSA_ERR_UNSUPPORTED;
-  if (misaligned(q) || misaligned(K) || misaligned(V) || misaligned(idx) || misaligned(Kloc) ||
-      misaligned(Vloc) || misaligned(q_pos) || misaligned(out) || misaligned(lse) ||
-      misaligned(workspace) || misaligned4(dm.lens))
-    return MSA_ERR_MISALIGNED;
-  const AttendPlan pl = plan_attend(dm, B, M, k, Lloc, cfg->bank_keys_rotated);
-  if (workspace_bytes < pl.ws_bytes) return MSA_ERR_WORKSPACE;
   return launch_attend(dm, pl, q, B, M, K, V, idx, k, Kloc, Vloc, Lloc, local_pos0, q_pos, out,
                        lse, workspace, cfg->bank_keys_rotated, (hipStream_t)stream);
 }
@@ -318,6 +338,18 @@ int msa_layers_step(const msa_config_t* cfg, const msa_config_t* attend_cfg, con
   const bool two = route != attend;
   for (int32_t l = 0; two && l < n_layers; ++l)
     if (layers[l].scored_event == nullptr) return MSA_ERR_INVALID_ARG;
+  for (int32_t l = 0; l < n_layers; ++l) {  // nothing is enqueued unless every layer is accepted
+    const msa_layer_t& y = layers[l];
+    Dims dm;
+    ScorePlan ps;
+    AttendPlan pa;
+    int rc = check_score(cfg, y.q, y.B, y.M, y.KR, y.inv_norm, k, y.idx, y.score, score_workspace, score_workspace_bytes,
+                         &dm, &ps);
+    if (rc == MSA_OK)
+      rc = check_attend(attend_cfg, y.q, y.B, y.M, y.K, y.V, y.idx, k, y.Kloc, y.Vloc, y.Lloc, local_pos0, q_pos, y.out,
+                        y.lse, attend_workspace, attend_workspace_bytes, &dm, &pa);
+    if (rc != MSA_OK) return rc;
+  }
   const hipStream_t sc = (hipStream_t)caller, sr = (hipStream_t)route, sa = (hipStream_t)attend;
   auto after = [](hipEvent_t e, hipStream_t from, hipStream_t to) {
     return hipEventRecord(e, from) == hipSuccess && hipStreamWaitEvent(to, e, 0) == hipSuccess;
@@ -335,7 +367,7 @@ int msa_layers_step(const msa_config_t* cfg, const msa_config_t* attend_cfg, con
                              y.out, y.lse, attend_workspace, attend_workspace_bytes, attend);
   }
   // what was enqueued is awaited by the caller whatever the status: the attention stream holds the last of it, except
-  // where a layer was refused between its two halves
+  // where a launch failed between the two halves of a layer
   if (rc != MSA_OK && two) {
     if (!after((hipEvent_t)join_event, sr, sc)) return MSA_ERR_HIP;
   }

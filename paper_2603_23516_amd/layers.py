@@ -100,7 +100,8 @@ class LayerStack:
     # ---- online: one batch of query tokens through every routed layer --------------------------------------
     def step(self, qs, Klocs, Vlocs, pos0, q_pos, outs, lses, overlap=True):
         """qs[l] bf16 [B][M][Hq][d]: the routing/attention query of layer l; Klocs[l], Vlocs[l] its local cache;
-        outs[l], lses[l] receive its attention output.  overlap=False runs everything on one stream."""
+        outs[l], lses[l] receive its attention output (None: not wanted).  overlap=False runs everything on one stream.
+        One host thread at a time: the stack's workspaces, selections and events are shared by its steps."""
         s_r = self.s_route
         s_a = self.s_attend if overlap else self.s_route
         cur = torch.cuda.current_stream(self.dev)
@@ -109,7 +110,8 @@ class LayerStack:
             # layers, 557 documents, 5 streams: 223 us -> 153; two layers, 956 documents, 2 streams: 141 -> 93)
             msa_layers_step(self.cfg, self.acfg,
                             [(qs[l], self.KR[l], self.inv[l], self.idx[l], self.val[l], self.Kbar[l], self.Vbar[l],
-                              Klocs[l], Vlocs[l], outs[l], lses[l], self.ev_scored[l]) for l in range(self.L)],
+                              Klocs[l], Vlocs[l], torch.empty_like(qs[l]) if outs[l] is None else outs[l], lses[l],
+                              self.ev_scored[l]) for l in range(self.L)],
                             self.k, pos0, q_pos, self.ws_s, self.ws_a, cur, s_r, s_a,
                             self.ev_fork, self.ev_join)
             return

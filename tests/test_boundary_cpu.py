@@ -251,6 +251,41 @@ def test_attention_workspace_serves_smaller_calls(lib, n_kv_heads, r, d, G, rota
             assert by_B == sorted(by_B), (M, L)
 
 
+def test_layers_step_checks_every_layer_first(lib):
+    """A layer that routing or attention would refuse is refused before anything is enqueued, wherever it stands: no device
+    is needed to see its status."""
+    E = msa
+    p = 0x10000
+    cfg, acfg = _cfg(), _cfg(doc_len=8, chunk=8, bank_keys_rotated=1)
+    B, M, k, Lloc = 2, 1, 4, 100
+    ws_s, ws_a = msa.score_topk_workspace_bytes(cfg, B, M, k), msa.sparse_attend_workspace_bytes(acfg, B, M, k, Lloc)
+
+    def step(change=None, n=3, at=2, k=k, fork=p, join=p, ws_s=ws_s, ws_a=ws_a, q_pos=p):
+        layers = (msa.MsaLayer * n)()
+        for y in layers:
+            for f in ("q", "KR", "inv_norm", "idx", "score", "K", "V", "Kloc", "Vloc", "out", "lse", "scored_event"):
+                setattr(y, f, p)
+            y.B, y.M, y.Lloc = B, M, Lloc
+        for f, v in (change or {}).items():
+            setattr(layers[at], f, v)
+        return lib.msa_layers_step(ctypes.byref(cfg), ctypes.byref(acfg), layers, n, k, k, q_pos, p, ws_s, p, ws_a, 1, 2, 3,
+                                   fork, join)
+
+    for at in (0, 1, 2):
+        for f in ("q", "KR", "inv_norm", "idx", "K", "V", "Kloc", "Vloc", "out", "scored_event"):
+            assert step({f: None}, at=at) == E.MSA_ERR_INVALID_ARG, f
+        for f in ("q", "KR", "inv_norm", "idx", "score", "K", "V", "Kloc", "Vloc", "out", "lse"):
+            assert step({f: p + 2}, at=at) == E.MSA_ERR_MISALIGNED, f
+        assert step({"B": 0}, at=at) == E.MSA_ERR_INVALID_ARG
+        assert step({"Lloc": -1}, at=at) == E.MSA_ERR_INVALID_ARG
+        assert step({"Lloc": 1 << 24}, at=at) == E.MSA_ERR_UNSUPPORTED
+        assert step({"B": 70000}, at=at) in (E.MSA_ERR_UNSUPPORTED, E.MSA_ERR_WORKSPACE)
+    assert step(k=0) == E.MSA_ERR_INVALID_ARG and step(k=65) == E.MSA_ERR_INVALID_ARG
+    assert step(ws_s=ws_s - 256) == E.MSA_ERR_WORKSPACE and step(ws_a=ws_a - 256) == E.MSA_ERR_WORKSPACE
+    assert step(fork=None) == E.MSA_ERR_INVALID_ARG and step(join=None) == E.MSA_ERR_INVALID_ARG
+    assert step(q_pos=None) == E.MSA_ERR_INVALID_ARG
+
+
 def test_fetch_validation(lib):
     c = _cfg()
     cb = ctypes.byref(c)

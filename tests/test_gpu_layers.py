@@ -73,3 +73,45 @@ def test_three_routed_layers_against_the_oracle(tier):
     index_bytes, bank_bytes = stack.bytes()
     assert index_bytes == L * (msa.routing_keys_bytes(cfg) + msa.inv_norm_bytes(cfg))
     assert bank_bytes == L * 2 * N * Hkv * C * d * 2
+
+
+def test_refused_layer_leaves_nothing_behind():
+    """A step with one layer that attention refuses raises before anything runs; the next step is whole, on one stream, on
+    two, and without outputs that are not wanted."""
+    L, N, Hkv, r, G, d, P, B, k, Lloc = 3, 60, 2, 2, 128, 64, 32, 2, 4, 33
+    Hq = Hkv * r
+    stack = LayerStack(msa.MsaConfig(N, G, P, Hq, Hkv, d, 1e4), L, B, 1, k, Lloc)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(97000)
+
+    def rnd(*shape):
+        return torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+    for l in range(L):
+        stack.set_layer_keys(l, rnd(N, Hkv, G, d))
+        stack.set_layer_values(l, rnd(N, Hkv, G, d))
+    qs, Kls, Vls = ([rnd(*s) for _ in range(L)] for s in ((B, 1, Hq, d), (B, Hkv, Lloc, d), (B, Hkv, Lloc, d)))
+    pos = torch.full((B, 1), k + Lloc - 1, dtype=torch.int32, device="cuda")
+    odd = torch.zeros(Kls[0].numel() + 1, dtype=torch.bfloat16, device="cuda")[1:].view(B, Hkv, Lloc, d)   # not 16-byte aligned
+    runs = []
+    for overlap in (True, False):
+        outs = [torch.full_like(q, 7.0) for q in qs]
+        lses = [torch.full((B, 1, Hq), 7.0, device="cuda") for _ in range(L)]
+        for i in stack.idx:
+            i.fill_(-7)
+        for at in range(L):
+            bad = [odd if l == at else x for l, x in enumerate(Kls)]
+            with pytest.raises(msa.MsaError) as e:
+                stack.step(qs, bad, Vls, k, pos, outs, lses, overlap=overlap)
+            assert e.value.status == msa.MSA_ERR_MISALIGNED
+        torch.cuda.synchronize()
+        assert all(bool((o == 7.0).all()) for o in outs + lses) and all(bool((i == -7).all()) for i in stack.idx)
+        stack.step(qs, Kls, Vls, k, pos, outs, lses, overlap=overlap)
+        torch.cuda.synchronize()
+        runs.append([t.clone() for t in outs + lses + stack.idx])
+        assert all(bool((i >= 0).all()) for i in stack.idx)
+        part = [torch.full_like(qs[0], 7.0)] + [None] * (L - 1)
+        stack.step(qs, Kls, Vls, k, pos, part, [None] * L, overlap=overlap)
+        torch.cuda.synchronize()
+        assert torch.equal(part[0].view(torch.int16), outs[0].view(torch.int16))
+    for a, b in zip(*runs):
+        assert torch.equal(a, b)
