@@ -471,17 +471,27 @@ def main():
     attend_gbs = ab["attend"] / (attend_ms * 1e-3) / 1e9
     build_gbs = ab["build"] / (build_ms * 1e-3) / 1e9
 
-    # the MFMA GEMM path (many query tokens).  Algorithmic flops: the folded form of Eq. 2, one routing query per (token,
-    # KV group): 2 * tokens * Hkv * keys * d.  Issued: twice that where the query travels as a bf16 (hi, lo) pair (head
-    # mean over every head; d = 64; 4 or 16 chunks per document), once where the product runs on the hi parts alone and
-    # the few candidates inside the error band are scored again exactly (per-group selections, cosine, d = 128, C = 8)
+    # the MFMA paths (many query tokens): the wide kernel from 33 tokens on with one selection for all heads, else the
+    # scoring GEMM from 64 tokens on (k = 17..32: from 448 on at the latest).  Algorithmic flops: the folded form of Eq. 2,
+    # one routing query per (token, KV group): 2 * tokens * Hkv * keys * d.  Issued: twice that where the query travels as a
+    # bf16 (hi, lo) pair, once where the product runs on the hi parts alone and the few candidates inside the error band are
+    # scored again exactly (cosine, d = 128, eight chunks per document)
     flops = flops_issued = None
-    one_pass = False
-    if nq >= 64 and k <= 16 and wl.C in (4, 8, 16):          # both selection scopes do the same matrix work
+    one_pass = wl.d == 128 and wl.C == 8
+    wide = args.scope == "all" and wl.Hkv > 1 and nq > 32
+    gemm = not (args.scope == "all" and wl.Hkv > 1) and wl.C in (4, 8, 16) and (
+        (nq >= 64 and k <= 16) or (nq >= 448 and k <= 32))
+    if wide or gemm:
         tiles = (wl.N * wl.C + 15) // 16
-        one_pass = args.scope == "group" and wl.d == 128 and wl.C == 8
         flops = 2.0 * nq * wl.Hkv * wl.N * wl.C * wl.d
         flops_issued = 2.0 * nq * wl.Hkv * tiles * 16 * (1 if one_pass else 2) * wl.d
+    if wide:
+        mfma_kernel = ("score_wide_kernel" + (" on the hi parts of the queries" if one_pass else "") +
+                       " (inside msa_score_topk = fold + wide kernel and selection per segment of the bank)")
+    else:
+        mfma_kernel = ("score_gemm_kernel" +
+                       (" on the hi parts of the queries (inside msa_score_topk = fold + one-pass GEMM + candidates and exact "
+                        "scores + gated two-pass GEMM and merge)" if one_pass else " (inside msa_score_topk = fold + GEMM + merge)"))
     # shared selection and many tokens: attention is a dense contraction on the matrix cores.  Algorithmic flops: two
     # products (QK, PV) of 2 flops per multiply-add over the keys each token sees; issued: twice that (bf16 (hi, lo) pairs
     # of Q and P)
@@ -509,9 +519,7 @@ def main():
                       "median_ms": score_all[args.steps // 2], "min_ms": score_all[0],
                       "entry_point_ms": score_call_ms,
                       "entry_point_frac": ab["score"] / (score_call_ms * 1e-3) / 1e9 / HBM_PEAK_GBS} if flops is None else
-                     {"bound": "mfma", "kernel": ("score_wide_kernel" if args.scope == "all" else "score_gemm_kernel") +
-                      (" on the hi parts of the queries (inside msa_score_topk = fold + one-pass GEMM + candidates and exact "
-                       "scores + gated two-pass GEMM and merge)" if one_pass else " (inside msa_score_topk = fold + GEMM + merge)"),
+                     {"bound": "mfma", "kernel": mfma_kernel,
                       "achieved": flops / (score_ms * 1e-3) / 1e12, "peak": MFMA_BF16_PEAK_TFLOPS,
                       "unit": "TFLOP/s", "frac": flops / (score_ms * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS,
                       "traffic": TRAFFIC.get("score"),

@@ -92,7 +92,8 @@ typedef struct msa_config {
                            DOMINANT kernel (the scan over the routing index, all passes, or the scoring GEMM;
                            the gather-attention kernel, or the tiled kernel of a shared selection) and stop
                            immediately after it, so that its duration can be told from the small kernels
-                           around it.  Nothing is kept after the call returns; other entry points ignore the
+                           around it (a bank that is scored in segments: from the first segment's kernel to the
+                           last's, the selections between them included).  Nothing is kept after the call returns; other entry points ignore the
                            fields; exactly one of the two being NULL is MSA_ERR_INVALID_ARG                */
 } msa_config_t;
 

@@ -539,7 +539,6 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
   s.k = k;
   s.tiles = dm.tiles;
   const int per_wg = kWideRows / (pl.pair ? 2 : 1);
-  profile_mark(dm, false, st);
   for (int tok0 = 0; tok0 < BM; tok0 += pl.pass_tokens) {
     const int nq = BM - tok0 < pl.pass_tokens ? BM - tok0 : pl.pass_tokens;
     a.nq = nq;
@@ -561,6 +560,7 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
       if (streams > most) streams = most;
       a.n_streams = streams;
       dim3 grid((unsigned)((a.n_tb * streams + 7) / 8 * 8)), block(64 * kWideWaves);
+      if (tok0 == 0 && doc0 == 0) profile_mark(dm, false, st);
 #define MSA_WIDE(DD, HH) \
   do { \
     if (!pl.pair) hipLaunchKernelGGL((score_wide_kernel<128, HH, false, true>), grid, block, 0, st, a); \
@@ -574,6 +574,7 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
       }
 #undef MSA_WIDE
       if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
+      if (tok0 + nq == BM && doc0 + n_docs == dm.N) profile_mark(dm, true, st);
       s.best = (unsigned long long*)(w + pl.off_best) + (size_t)tok0 * k;
       s.first = doc0 == 0;
       s.last = doc0 + n_docs == dm.N;
@@ -592,7 +593,6 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
       if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
     }
   }
-  profile_mark(dm, true, st);
   return MSA_OK;
 }
 
