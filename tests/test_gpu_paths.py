@@ -23,7 +23,8 @@ ALL_SCAN = [
     (5, 8, 1, 8, 128, 1, 1, 5, "cos"),            # fewer tiles than one workgroup has waves
     (1037, 4, 2, 16, 128, 9, 1, 33, "cos"),       # 16-query pass, one document per tile
     (8193, 8, 1, 8, 128, 25, 1, 16, "cos"),       # 32-query pass, units of several tiles, ragged last tile
-    (4099, 8, 2, 1, 64, 33, 1, 20, "dot"),        # two passes, sixteen documents per tile
+    (4099, 8, 2, 1, 64, 33, 1, 20, "dot"),        # one query more than the scan takes: the wide kernel
+    (4099, 8, 2, 1, 64, 20, 1, 20, "dot"),        # no norms to read, sixteen documents per tile
     (16400, 2, 1, 2, 64, 2, 2, 64, "cos"),        # whole rows held by sixteen waves
     (12437, 8, 1, 8, 64, 5, 1, 64, "cos"),        # ... twelve documents per lane, as many winners as lanes in a wave
     (32768, 2, 1, 1, 64, 1, 1, 64, "cos"),        # the longest row that one workgroup takes
@@ -150,6 +151,8 @@ ALL_WIDE = [
     (30011, 2, 1, 2, 64, 1, 300, 9, "cos"),       # two segments of the bank
     (333, 2, 1, 4, 128, 1, 1030, 3, "cos"),       # two passes of tokens
     (5, 2, 1, 8, 64, 3, 20, 5, "dot"),            # as many documents as are selected
+    (70001, 2, 1, 2, 64, 1, 35, 20, "cos"),       # one segment longer than a selecting workgroup's registers
+    (33001, 2, 1, 8, 128, 1, 35, 64, "cos"),      # ... and with the one-pass filter
 ]
 
 
