@@ -829,10 +829,12 @@ static long long decode_slots(long long pairs, long long steps) {
   return all > pairs ? all : pairs;
 }
 
-// Time of `groups` workgroups of the decode kernel that take `per` steps each and `prologues` prologues, in units that
-// make one more partial per pair the smallest difference.
-static long long decode_cost(long long per, long long prologues, long long groups, int d) {
-  const long long wave = ((per + kAttWaves - 1) / kAttWaves + 1) / 2 * 2;
+// Steps of the longest wave of a workgroup that takes `per`: two per trip of the loop.
+static long long longest_wave(long long per) { return ((per + kAttWaves - 1) / kAttWaves + 1) / 2 * 2; }
+
+// Time of `groups` workgroups of the decode kernel with `wave` steps in the longest wave and `prologues` prologues, in
+// units that make one more partial per pair the smallest difference.
+static long long decode_cost(long long wave, long long prologues, long long groups, int d) {
   const long long rest = groups % 512;
   const long long rounds = d == 128 ? (groups + 255) / 256 * 6 : groups / 512 * 7 + (rest == 0 ? 0 : rest <= 256 ? 6 : 7);
   return (wave + 5 * prologues) * rounds * 7;
@@ -897,12 +899,15 @@ AttendPlan plan_attend(const Dims& dm, int B, int M, int k, int Lloc, int bank_k
     const long long S = p.steps_total;
     const long long most = decode_slots(pairs, S) / pairs;
     long long best = -1, best_n = 1;
-    for (long long n = 1; n <= most; ++n) {
-      const long long c = decode_cost((S + n - 1) / n, 1, pairs * n, dm.d) + n;  // (of equals the fewest partials)
+    for (long long n = 1; n <= most;) {
+      const long long wave = longest_wave((S + n - 1) / n);
+      const long long c = decode_cost(wave, 1, pairs * n, dm.d) + n;  // (of equals the fewest partials)
       if (best < 0 || c < best) {
         best = c;
         best_n = n;
       }
+      if (wave <= 2) break;
+      n = (S + kAttWaves * (wave - 2) - 1) / (kAttWaves * (wave - 2));  // the fewest splits with a shorter wave
     }
     p.steps_per_split = (int)((S + best_n - 1) / best_n);
     p.n_splits = (int)((S + p.steps_per_split - 1) / p.steps_per_split);
@@ -914,7 +919,7 @@ AttendPlan plan_attend(const Dims& dm, int B, int M, int k, int Lloc, int bank_k
     const long long per = ((total + places - 1) / places + 7) / 8 * 8;
     const long long slots = (S - 1) / per + 2;  // workgroups that can meet in one pair
     if (dm.lens == nullptr && per >= 112 && per <= 2 * S && total < (1ll << 30) && slots <= kMaxFused &&
-        slots <= most && decode_cost(per, 2, places, dm.d) * 100 < best * 85) {
+        slots <= most && decode_cost(longest_wave(per), 2, places, dm.d) * 100 < best * 85) {
       p.lin_per = (int)per;
       p.lin_blocks = (int)((total + per - 1) / per);
       p.n_splits = (int)slots;
