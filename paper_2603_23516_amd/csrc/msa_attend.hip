@@ -913,13 +913,16 @@ AttendPlan plan_attend(const Dims& dm, int B, int M, int k, int Lloc, int bank_k
     p.n_splits = (int)((S + p.steps_per_split - 1) / p.steps_per_split);
     // Documents of full length: where that leaves places idle (360 workgroups in two rounds of 256), the steps of all pairs
     // in one line are cut into equal ranges, one per place, whatever pairs they end in: a prologue more per range.  d = 128:
-    // 280 pairs of 150 steps 0.83 of the time, 264 of 449 0.86, 264 of 398 0.90, 416 of 217 0.91.  Not for ranges of less
-    // than 112 steps (352 pairs of 57: 1.27) nor for such as meet more than three pairs (1944 pairs of 17: 1.68).
+    // 280 pairs of 150 steps 0.83 of the time, 264 of 449 0.86, 264 of 90 0.80, 416 of 217 0.91; d = 64: 280 of 152 0.89.
+    // Not where the cost promises less (d = 128: 0.85, of pairs under 96 steps 0.72; d = 64: 0.95), and not for ranges under
+    // 88 steps (80 at d = 64) or such as meet more than three pairs: 352 pairs of 57 steps 1.27, 396 of 70 1.07, 1944 of 17 1.68.
     const long long places = dm.d == 128 ? 256 : 512, total = S * pairs;
     const long long per = ((total + places - 1) / places + 7) / 8 * 8;
     const long long slots = (S - 1) / per + 2;  // workgroups that can meet in one pair
-    if (dm.lens == nullptr && per >= 112 && per <= 2 * S && total < (1ll << 30) && slots <= kMaxFused &&
-        slots <= most && decode_cost(longest_wave(per), 2, places, dm.d) * 100 < best * 85) {
+    const long long percent = dm.d == 64 ? 95 : (S >= 96 ? 85 : 72);
+    if (dm.lens == nullptr && per >= (dm.d == 64 ? 80 : 88) && per <= 2 * S && total < (1ll << 30) &&
+        slots <= kMaxFused && slots <= most &&
+        decode_cost(longest_wave(per), 2, places, dm.d) * 100 < best * percent) {
       p.lin_per = (int)per;
       p.lin_blocks = (int)((total + per - 1) / per);
       p.n_splits = (int)slots;
