@@ -223,6 +223,75 @@ __device__ __forceinline__ uint32_t kth_best_bound(uint32_t ob, int k, uint32_t 
   return most > least ? most : least;
 }
 
+// The k best of a row in which more documents than LDS holds reach any cheap bound: a query of zeros (an empty slot of a
+// batch) ties with every document.  v: the first REGS * THREADS scores in registers, thread-strided, the others are read
+// from the row; N >= k; theta: a lower bound on the k-th best, ob: the best of this lane (images).  Writes the k keys to out
+// (LDS), in no order; out_n and cnt_s are LDS too.  The k-th largest score is found bit by bit, counting, below the bits
+// that the bound shares with the largest score; of the documents that tie with it the first ones are taken.  (8 queries of
+// which 2 are zeros, 8192 documents: call 32 us, without them 29; by k = 16 rounds of a block-wide maximum 100.)
+template <int REGS, int WAVES>
+__device__ __forceinline__ void topk_of_ties(const float (&v)[REGS], const float* row, int N, uint32_t doc0, int k,
+                                             uint32_t theta, uint32_t ob, unsigned long long* out, int* out_n,
+                                             int (&cnt_s)[WAVES]) {
+  constexpr int THREADS = 64 * WAVES;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    const uint32_t o = __shfl_xor(ob, off, 64);
+    ob = o > ob ? o : ob;
+  }
+  __syncthreads();
+  if (lane == 0) cnt_s[wave] = (int)ob;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) ob = (uint32_t)cnt_s[w] > ob ? (uint32_t)cnt_s[w] : ob;
+  auto sum = [&](int of_wave) {  // of_wave is the same in a wave's lanes; two barriers
+    __syncthreads();
+    if (lane == 0) cnt_s[wave] = of_wave;
+    __syncthreads();
+    int total = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) total += cnt_s[w];
+    return total;
+  };
+  const int top = theta == ob ? -1 : 31 - __clz(theta ^ ob);  // highest bit that is not known
+  uint32_t kth = top < 0 ? theta : theta & ~((2u << top) - 1u);
+  for (int bit = top; bit >= 0; --bit) {
+    const uint32_t cnd = kth | (1u << bit);
+    int c = 0;
+#pragma unroll
+    for (int u = 0; u < REGS; ++u) c += __popcll(__ballot(u * THREADS + tid < N && orderable(v[u]) >= cnd));
+    for (int i0 = REGS * THREADS; i0 < N; i0 += THREADS) {
+      const int i = i0 + tid;
+      c += __popcll(__ballot(i < N && orderable(row[i < N ? i : N - 1]) >= cnd));
+    }
+    if (sum(c) >= k) kth = cnd;
+  }
+  if (tid == 0) *out_n = 0;
+  __syncthreads();
+  auto above = [&](int i, float x) {
+    if (i < N && orderable(x) > kth) out[atomicAdd(out_n, 1)] = make_key(x, doc0 + i);  // fewer than k
+  };
+#pragma unroll
+  for (int u = 0; u < REGS; ++u) above(u * THREADS + tid, v[u]);
+  for (int i = REGS * THREADS + tid; i < N; i += THREADS) above(i, row[i]);
+  __syncthreads();
+  int have = *out_n;
+  for (int i0 = 0; have < k && i0 < N; i0 += THREADS) {  // block-uniform
+    const int i = i0 + tid;
+    const float x = row[i < N ? i : N - 1];
+    const bool tie = i < N && orderable(x) == kth;
+    const unsigned long long m = __ballot(tie);
+    const int total = sum(__popcll(m));
+    int at = have + __popcll(m & ((1ull << lane) - 1ull));
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) at += w < wave ? cnt_s[w] : 0;
+    if (tie && at < k) out[at] = make_key(x, doc0 + i);
+    have += total;
+  }
+  __syncthreads();
+}
+
 // Workgroups that produced parts of one result count themselves in; the one that arrives last combines the
 // parts.  The 64-bit word holds (nonce << 16 | arrivals); a word whose upper 48 bits are not this call's nonce
 // is a leftover (the caller's workspace has undefined contents) and counts as zero arrivals, so nothing has

@@ -1002,8 +1002,7 @@ __global__ __launch_bounds__(kPoolThreads) void pool_tokens_kernel(const unsigne
 //   2. every document scoring >= theta goes to LDS (a few k of them) and is ranked by counting on the full
 //      key.
 // Exact, ties included (keys are (score, ~doc): a total order; theta compares scores only, so equal scores
-// survive together).  If more survive than LDS holds (adversarial order), k rounds of a block-wide arg-max
-// over the part take over.
+// survive together).  If more survive than LDS holds (ties), topk_of_ties takes over.
 constexpr int kRowSurv = 2048;
 constexpr int kRowRegs = 32;        // scores a thread keeps in registers between the two passes (8: short rows)
 constexpr int kRowPart = 8192;      // documents per part of a long row: what 32 registers per thread of four waves hold
@@ -1026,8 +1025,8 @@ struct RowsArgs {
 template <int REGS, int WAVES>
 __global__ __launch_bounds__(64 * WAVES) void topk_rows_kernel(RowsArgs a) {
   __shared__ unsigned long long surv[kRowSurv + 8];
-  __shared__ unsigned long long red[WAVES];
   __shared__ uint32_t theta_w[2][WAVES];
+  __shared__ int cnt_s[WAVES];
   __shared__ int n_surv;
   constexpr int THREADS = 64 * WAVES;
   const int tid = threadIdx.x;
@@ -1108,26 +1107,12 @@ __global__ __launch_bounds__(64 * WAVES) void topk_rows_kernel(RowsArgs a) {
     for (int i = ns + tid; i < k; i += THREADS) emit(i, 0ull);  // fewer than k documents (a short part)
     return;
   }
-  unsigned long long prev = ~0ull;
-  for (int round = 0; round < k; ++round) {
-    unsigned long long bst = 0ull;
-    for (int i = tid; i < N; i += THREADS) {
-      const unsigned long long x = make_key(row[i], doc0 + i);
-      if (x < prev && x > bst) bst = x;
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      const unsigned long long y = __shfl_xor(bst, off, 64);
-      bst = y > bst ? y : bst;
-    }
-    __syncthreads();
-    if ((tid & 63) == 0) red[tid >> 6] = bst;
-    __syncthreads();
-    bst = red[0];
-#pragma unroll
-    for (int w = 1; w < WAVES; ++w) bst = red[w] > bst ? red[w] : bst;
-    if (tid == 0) emit(round, bst);
-    prev = bst ? bst : 0ull;
+  topk_of_ties<REGS, WAVES>(v, row, N, doc0, k, theta, ob, surv, &n_surv, cnt_s);
+  if (tid < k) {
+    const unsigned long long x = surv[tid];
+    int rank = 0;
+    for (int j = 0; j < k; ++j) rank += (surv[j] > x) ? 1 : 0;
+    emit(rank, x);
   }
 }
 

@@ -125,7 +125,11 @@ __global__ __launch_bounds__(64) void fold_queries_kernel(const uint16_t* __rest
   if (eps != nullptr) {
     err2 = gsum<LPH>(err2);  // lanes 0 .. LPH-1 hold the D elements
     n2 = gsum<LPH>(n2);
-    if (lane == 0) eps[qg * Hkv + g] = 1.01f * sqrtf(err2) + 2e-5f * sqrtf(n2) + 1e-7f;
+    uint32_t bits = 0u;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) bits |= __float_as_uint(f[e]) << 1;
+    const bool any = __ballot(bits != 0u) != 0ull;  // a query of zeros scores zero in both: no band
+    if (lane == 0) eps[qg * Hkv + g] = any ? 1.01f * sqrtf(err2) + 2e-5f * sqrtf(n2) + 1e-7f : 0.f;
     if (lane == 0 && (int)blockIdx.x < n_flags) flags[blockIdx.x] = 0;
   }
 }

@@ -1,7 +1,7 @@
 """The arithmetic claim behind the one-pass filter of the prefill scoring GEMM, checked on the CPU.
 
 The GEMM multiplies only hi = bf16(q) of a folded fp32 routing query q and treats the result s~ as the exact
-cosine score s within eps = 1.01 |q - hi| + 2e-5 |q| + 1e-7 (fold_queries_kernel writes exactly this bound).  Every
+cosine score s within eps = 1.01 |q - hi| + 2e-5 |q| + 1e-7 (fold_queries_kernel writes exactly this bound; 0 for a query of zeros).  Every
 list entry with s~ >= t~ - 2 eps, t~ the k-th largest s~, is then scored again exactly.  Two facts are needed:
   (1) |s~ - s| <= eps for any stored key whose |key| * inv_norm <= 1 (up to bf16 rounding of the key), with the
       product accumulated in fp32 in any order;

@@ -161,6 +161,54 @@ def test_all_heads_wide(N, Hkv, r, C, d, B, M, k, sim):
     test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim)
 
 
+# (N, Hkv, C, d, B, M, k, scope, pool): a row's k best where every document ties
+ALL_TIED = [
+    (9000, 2, 8, 64, 3, 1, 16, "group", 0),       # row top-k, four waves, part of the row beyond the registers
+    (30001, 2, 1, 64, 2, 1, 64, "all", 0),        # sixteen waves
+    (40007, 2, 1, 64, 2, 1, 33, "all", 0),        # rows in parts, the last of 7239 documents
+    (70001, 2, 1, 64, 1, 40, 33, "all", 0),       # wide kernel, scores of hi and lo parts
+    (9001, 8, 8, 128, 1, 50, 20, "all", 0),       # ... and behind the one-pass filter
+    (30011, 2, 8, 128, 1, 400, 9, "all", 1),      # three segments, pooled
+]
+
+
+@pytest.mark.parametrize("N,Hkv,C,d,B,M,k,scope,pool", ALL_TIED)
+def test_queries_of_zeros(N, Hkv, C, d, B, M, k, scope, pool):
+    """Empty slots of a batch and padding of a question: a query of zeros scores zero with every document, so its
+    selection is the first k; the queries beside it are what they are without it."""
+    say(f"queries of zeros N={N} Hkv={Hkv} C={C} d={d} B={B} M={M} k={k} {scope} pool={pool}")
+    cfg = msa.MsaConfig(N, 8 * C, 8, Hkv, Hkv, d, 1e6, token_pool=pool,
+                        select_scope=msa.MSA_SCOPE_ALL if scope == "all" else msa.MSA_SCOPE_GROUP)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(60000 + N)
+    KR, inv = msa.alloc_routing_index(cfg)
+    KR.normal_(generator=gen)
+    inv.copy_(KR.float().pow(2).sum((2, 4)).rsqrt().reshape(Hkv, -1))
+    q = torch.randn((B, M, Hkv, d), generator=gen, device="cuda").to(torch.bfloat16)
+    flat = q.view(B * M, Hkv, d)
+    zero = torch.arange(B * M, device="cuda") % 2 == 1 if not pool else torch.ones(B * M, dtype=torch.bool, device="cuda")
+    if B * M == 2:
+        zero[1] = True
+    flat[zero] = 0
+    idx, val = msa.msa_score_topk(cfg, q, KR, inv, k)
+    torch.cuda.synchronize()
+    S_ = 1 if scope == "all" else Hkv
+    first = torch.arange(k, dtype=torch.int32, device="cuda")
+    if pool:
+        assert torch.equal(idx, first.expand_as(idx)) and bool((val == 0).all())
+        return
+    idx, val = idx.reshape(B * M, S_, k), val.reshape(B * M, S_, k)
+    assert torch.equal(idx[zero], first.expand_as(idx[zero])) and bool((val[zero] == 0).all())
+    rest = flat[~zero].clone().view(1, -1, Hkv, d)
+    if rest.shape[1] == B * M:
+        return
+    alone, score = msa.msa_score_topk(cfg, rest, KR, inv, k)
+    torch.cuda.synchronize()
+    # (fewer queries may take another kernel: the same documents but for ties of the rounded scores)
+    assert (val[~zero] - score.reshape(-1, S_, k)).abs().max() <= 2e-5
+    assert (idx[~zero] != alone.reshape(-1, S_, k)).float().mean() <= 0.01
+
+
 @pytest.mark.parametrize("C,d", [(8, 64), (4, 128)])
 def test_all_heads_wide_takes_any_norms(C, d):
     """An index whose reciprocal norms are not those of its keys (a hundred times them, more or less): scored as it is
