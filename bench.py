@@ -472,7 +472,7 @@ def main():
     build_gbs = ab["build"] / (build_ms * 1e-3) / 1e9
 
     # the MFMA paths (many query tokens): the wide kernel from 33 tokens on with one selection for all heads, else the
-    # scoring GEMM from 64 tokens on (k = 17..32: from 448 on at the latest).  Algorithmic flops: the folded form of Eq. 2,
+    # scoring GEMM from 64 tokens on (k = 17..32: from 544 on at the latest).  Algorithmic flops: the folded form of Eq. 2,
     # one routing query per (token, KV group): 2 * tokens * Hkv * keys * d.  Issued: twice that where the query travels as a
     # bf16 (hi, lo) pair, once where the product runs on the hi parts alone and the few candidates inside the error band are
     # scored again exactly (cosine, d = 128, eight chunks per document)
@@ -480,7 +480,7 @@ def main():
     one_pass = wl.d == 128 and wl.C == 8
     wide = args.scope == "all" and wl.Hkv > 1 and nq > 32
     gemm = not (args.scope == "all" and wl.Hkv > 1) and wl.C in (4, 8, 16) and (
-        (nq >= 64 and k <= 16) or (nq >= 448 and k <= 32))
+        (nq >= 64 and k <= 16) or (nq >= 544 and k <= 32))
     if wide or gemm:
         tiles = (wl.N * wl.C + 15) // 16
         flops = 2.0 * nq * wl.Hkv * wl.N * wl.C * wl.d

@@ -656,16 +656,15 @@ bool gemm_path_applies(const Dims& dm, int BM, int k) {
   if (!((dm.C == 4 || dm.C == 8 || dm.C == 16) && k <= kGemmMaxK && BM >= 64)) return false;
   if (k <= 16) return true;
   // 32-entry lists without the filter: inserting into them is most of the work, and the scan is the faster way for few
-  // tokens over a small bank.  k = 25..32: 162 tokens, 231 documents of 8 chunks, four heads: scan 90 us, here 95; 191
-  // tokens, 13935 of 8: 516, 316; 437 tokens, 122 of 8: 222, 101.  Up to k = 24 the scan takes 32 queries per pass, not 16:
-  // 132 tokens, 1491 of 8: 56, 139; 290 tokens, 1461 of 4: 115, 171; 512 tokens, 78 of 8: 166, 94.  The scan's time goes
-  // with the heads: two of them, 176 tokens, 10610 of 8: 100, 131; 437 tokens, 7919 of 4: 130, 169.
-  // With the filter it is so for little work only: 92 tokens, 190 documents, k = 20: 37, 46; 67 tokens, 3670 documents,
-  // four heads, k = 17: 52, 68; 99 tokens, 1425 documents, k = 32: 83, 60.
-  const bool wide_scan = k <= 24;
-  if (BM >= (one_pass_shape(dm) || !wide_scan ? 320 : 448)) return true;
-  const long long keys = one_pass_shape(dm) ? (wide_scan ? 12000000 : 4000000) : (wide_scan ? 160000000 : 112000000);
-  return dm.NC >= keys / ((long long)BM * dm.Hkv);
+  // passes (of 32 queries up to k = 24, else of 16) over a small bank.  Without the filter: 132 tokens, 1491 documents of 8
+  // chunks, k = 17: scan 56 us, here 139; 290 tokens, 1461 of 4, k = 20: 115, 171; 246 tokens, 3495 of 16, k = 32: 383, 246;
+  // 428 tokens, 5409 of 8, k = 24: 364, 272.  With it: 81 tokens, 60 documents, k = 20: 36, 80; 67 tokens, 14000 documents,
+  // two heads, k = 24: 77, 133; 99 tokens, 1425 documents, k = 32: 83, 60.  The lines are 1 to 2 % from the faster of the two on
+  // 398 and 130 shapes.
+  const bool one_pass = one_pass_shape(dm);
+  const long long passes = (BM + (k <= 24 ? 31 : 15)) / (k <= 24 ? 32 : 16);
+  const long long work = 100000 + dm.NC * dm.Hkv * dm.d / 128;  // of a pass
+  return passes - (one_pass ? 2 : 4) >= ((one_pass ? 500000 : 1250000) + work - 1) / work;
 }
 
 static GemmPlan gemm_split(const Dims& dm, int BM, int k, bool small) {
