@@ -144,7 +144,7 @@ static int check_attend(const msa_config_t* cfg, const void* q, int32_t B, int32
       misaligned(Vloc) || misaligned(q_pos) || misaligned(out) || misaligned(lse) ||
       misaligned(workspace) || misaligned4(dm->lens))
     return MSA_ERR_MISALIGNED;
-  *pl = plan_attend(*dm, B, M, k, Lloc, cfg->bank_keys_rotated);
+  *pl = plan_attend(*dm, B, M, k, Lloc, cfg->bank_keys_rotated, workspace_bytes);
   return workspace_bytes < pl->ws_bytes ? MSA_ERR_WORKSPACE : MSA_OK;
 }
 
@@ -200,7 +200,7 @@ size_t msa_sparse_attend_workspace_bytes(const msa_config_t* cfg, int32_t B, int
   if (make_dims(cfg, &dm, kForAttend) != MSA_OK) return 0;
   if (B < 1 || M < 1 || k < 1 || k > MSA_MAX_TOPK || Lloc < 0) return 0;
   if ((int64_t)B * M > 65535 || !attend_doc_len_ok(cfg)) return 0;
-  return plan_attend(dm, B, M, k, Lloc, cfg->bank_keys_rotated).ws_bytes;
+  return plan_attend(dm, B, M, k, Lloc, cfg->bank_keys_rotated).ws_best;
 }
 
 int msa_build_routing_keys(const msa_config_t* cfg, const void* K, int32_t doc_begin,

@@ -43,6 +43,26 @@ struct AttendArgs {
   int lin_per, lin_total;  // decode kernel, linear split: steps per workgroup, steps in all; 0: the grid says it
 };
 
+// Many tokens with selections of their own, document by document (msa_attend_docs.hip): one window of tokens.
+struct DocsArgs {
+  unsigned long long* base;  // [S][N] first item << 32 | first entry of a document
+  int* cnt;                  // [S][N] pairs of a document
+  int* n_items;              // [S]
+  uint4* qrot;               // [tokens][Hq][D/8][hi, lo] rotated, scaled queries, 8 bf16 each
+  int4* items;               // [S][cap] (document, first entry, tokens, 1 if the document's only item)
+  int* entries;              // [S][cap] token * k + slot, by document
+  int* rank;                 // [S][cap] place of a pair among its document's
+  float* part_o;             // [tokens][Hq][k][parts][D] unnormalised partial outputs
+  float2* part_ml;           // [tokens][Hq][k][parts]    (running max in log2 units, sum)
+  int cap;                   // entries of a list at most
+  int tile_tok;              // tokens per item at most, 16 / r
+  int parts, part_steps;     // parts of a document's rows, 32-row steps of each
+  int tok0, n_tok;           // this window
+};
+int launch_attend_docs(const Dims& dm, const DocsPlan& pl, const AttendArgs& a0, const RopeTheta& th, int BM, void* ws,
+                       int bank_keys_rotated, const float* loc_o, const float2* loc_ml, int n_loc, void* out, float* lse,
+                       hipStream_t st);
+
 // Shared-selection prefill: unnormalised partials of every (token, head, split) in the layout the
 // decode path writes, merged by the same attend_merge_kernel.
 int launch_attend_prefill_partial(const Dims& dm, const AttendPlan& pl, const AttendArgs& a,

@@ -840,8 +840,8 @@ static long long decode_cost(long long wave, long long prologues, long long grou
   return (wave + 5 * prologues) * rounds * 7;
 }
 
-AttendPlan plan_attend(const Dims& dm, int B, int M, int k, int Lloc, int bank_keys_rotated) {
-  AttendPlan p;
+AttendPlan plan_attend(const Dims& dm, int B, int M, int k, int Lloc, int bank_keys_rotated, size_t workspace_bytes) {
+  AttendPlan p = {};
   const int BM = B * M;
   p.steps_mem = (int)(((long long)k * dm.G + 31) / 32);
   p.steps_total = p.steps_mem + (Lloc + 31) / 32;
@@ -963,6 +963,12 @@ AttendPlan plan_attend(const Dims& dm, int B, int M, int k, int Lloc, int bank_k
     bound = tiled > bound ? tiled : bound;
   }
   p.ws_bytes = bound > p.ws_bytes ? bound : p.ws_bytes;
+  p.ws_best = p.off_docs = p.ws_bytes;
+  if (p.split_local && docs_path_applies(dm, B, M, k)) {
+    p.dp = plan_docs(dm, B, M, k, workspace_bytes > p.ws_bytes ? workspace_bytes - p.ws_bytes : 0);
+    p.ws_best = p.off_docs + p.dp.bytes;
+    p.docs = p.dp.tokens > 0 ? 1 : 0;
+  }
   return p;
 }
 
@@ -1044,11 +1050,15 @@ int launch_attend(const Dims& dm, const AttendPlan& pl, const void* q, int B, in
     al.steps_total = (Lloc + 31) / 32;
     al.steps_per_split = pl.loc_steps_per_split;
     al.n_splits = pl.loc_splits;
-    al.split0 = pl.mem_splits;
+    al.split0 = pl.docs ? 0 : pl.mem_splits;
+    if (pl.docs) al.ph_splits = pl.loc_splits;
     AttendPlan pll = pl;
     pll.n_splits = pl.loc_splits;
     const int rc = launch_attend_prefill_partial(dm, pll, al, th, B, st, false);
     if (rc != MSA_OK) return rc;
+    if (pl.docs)
+      return launch_attend_docs(dm, pl.dp, a, th, BM, (char*)ws + pl.off_docs, bank_keys_rotated, a.part_o, a.part_ml,
+                                pl.loc_splits, out, lse, st);
     // ... and the selected documents through the decode kernel below, which sees no local context
     a.Lloc = 0;
     a.steps_total = pl.steps_mem;

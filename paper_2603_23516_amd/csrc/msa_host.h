@@ -113,6 +113,17 @@ inline void profile_mark(const Dims& dm, bool stop, hipStream_t st) {
   if (e != nullptr) (void)hipEventRecord(e, st);
 }
 
+// Many tokens with selections of their own, document by document (msa_attend_docs.hip).
+constexpr size_t kDocsBytes = (size_t)256 << 20;  // per-token buffers of a window (partials above all)
+constexpr int kDocsItems = 2048;                  // fewer items than this: documents in parts
+struct DocsPlan {
+  int parts, part_steps;  // parts of a document's rows, 32-row steps of each
+  int tokens;             // query tokens per window; 0: the workspace is too small for this path
+  size_t bytes;           // workspace asked for
+};
+bool docs_path_applies(const Dims& dm, int B, int M, int k);
+DocsPlan plan_docs(const Dims& dm, int B, int M, int k, size_t bytes);
+
 struct AttendPlan {
   int steps_mem;         // 32-key steps over the selected documents, ceil(k * G / 32)
   int steps_total;       // + ceil(Lloc / 32)
@@ -131,9 +142,14 @@ struct AttendPlan {
   size_t off_tickets;    // byte offset of the arrival counters [B*M][Hkv] (64-bit)
   size_t off_krot;       // tiled kernel: byte offset of the once-rotated keys (0 = none)
   int krot_steps;        // steps per (batch row, KV head) held there
-  size_t ws_bytes;
+  size_t ws_bytes;       // the least that is accepted
+  int docs;              // 1: split_local, and the documents go through attend_docs_kernel if the workspace holds ...
+  size_t off_docs;       // ... its buffers from here on (ws_best bytes in all hold them as planned)
+  size_t ws_best;
+  DocsPlan dp;
 };
-AttendPlan plan_attend(const Dims& dm, int B, int M, int k, int Lloc, int bank_keys_rotated);
+AttendPlan plan_attend(const Dims& dm, int B, int M, int k, int Lloc, int bank_keys_rotated,
+                       size_t workspace_bytes = 0);
 
 int launch_build(const Dims& dm, const void* K, int doc_begin, int doc_count, void* KR,
                  float* inv_norm, hipStream_t st);

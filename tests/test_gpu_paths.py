@@ -361,3 +361,70 @@ def test_decode_attention_linear_split(N, Hkv, r, G, d, B, M, k, Lloc, scope, ro
         go = out[b:b + 1].float().cpu().numpy().astype(np.float64)
         assert np.abs(go - oo).max() <= 2e-2 and np.linalg.norm(go - oo) <= 5e-3 * np.linalg.norm(oo)
         assert np.allclose(lse[b:b + 1].cpu().numpy(), ol, rtol=0, atol=5e-3)
+
+
+# (N, Hkv, r, G, d, B, M, k, Lloc, scope, rotated, ragged): many tokens with selections of their own, document by document
+ATT_DOCS = [
+    (40, 2, 4, 128, 128, 1, 70, 30, 70, "group", 0, False),    # four tokens per item
+    (24, 2, 8, 64, 128, 2, 64, 40, 40, "all", 0, True),        # two; one list for both heads
+    (9, 3, 2, 256, 64, 1, 100, 16, 33, "group", 0, True),      # eight; nearly every document in every selection
+    (30, 2, 1, 32, 64, 2, 100, 31, 32, "group", 0, False),     # sixteen; documents of one step
+    (33, 2, 4, 1024, 128, 1, 16, 16, 300, "group", 0, True),   # few items: documents in four parts, some of them empty
+    (50, 2, 4, 96, 128, 1, 50, 64, 64, "group", 1, False),     # keys stored rotated, the largest selection
+    (50, 1, 8, 64, 64, 3, 64, 48, 50, "all", 1, True),
+    (600, 8, 4, 64, 128, 1, 150, 20, 150, "group", 0, False),  # more than 64 items for one wave
+    (13000, 1, 4, 32, 64, 1, 400, 32, 40, "group", 0, False),  # more documents than the sort counts in LDS
+]
+
+
+@pytest.mark.parametrize("N,Hkv,r,G,d,B,M,k,Lloc,scope,rotated,ragged", ATT_DOCS)
+def test_attention_document_by_document(N, Hkv, r, G, d, B, M, k, Lloc, scope, rotated, ragged):
+    """Against the oracle, with pads, ids outside the bank and a document listed twice; then with smaller and smaller
+    workspaces, down to the first that is refused: windows of tokens, whose results are the same bits, and at last the
+    kernel that takes token by token, whose fp32 sums run in another order (one rounding to bf16: 2^-7 of the value)."""
+    say(f"by document N={N} Hkv={Hkv} r={r} G={G} d={d} B={B} M={M} k={k} Lloc={Lloc} {scope} rot={rotated} ragged={ragged}")
+    rng = np.random.default_rng(58005)
+    lens = rng.integers(1, G + 1, N).astype(np.int32) if ragged else None
+    cfg = msa.MsaConfig(N, G, G, Hkv * r, Hkv, d, 1e6, bank_keys_rotated=rotated,
+                        doc_lens=torch.from_numpy(lens).cuda() if ragged else None,
+                        select_scope=msa.MSA_SCOPE_ALL if scope == "all" else msa.MSA_SCOPE_GROUP)
+    S_ = 1 if scope == "all" else Hkv
+    Kb, K = S.normal_bf16(58000, (N, Hkv, G, d))
+    Vb, V = S.normal_bf16(58001, (N, Hkv, G, d))
+    qb, q = S.normal_bf16(58002, (B, M, Hkv * r, d))
+    Klb, Kl = S.normal_bf16(58003, (B, Hkv, Lloc, d))
+    Vlb, Vl = S.normal_bf16(58004, (B, Hkv, Lloc, d))
+    idx = rng.integers(0, N, (B, M, S_, k)).astype(np.int32)          # documents twice in a selection among them
+    idx[:, ::3, :, k - 1] = -1
+    idx[:, 1::5, :, 0] = N + 3
+    idx[0, 2] = -1                                                     # a token with the local context alone
+    q_pos = (G + rng.integers(-1, Lloc, (B, M))).astype(np.int32)
+    args = [dev(qb), dev(Kb), dev(Vb), torch.from_numpy(idx).cuda(), dev(Klb), dev(Vlb), G, torch.from_numpy(q_pos).cuda()]
+    size = msa.sparse_attend_workspace_bytes(cfg, B, M, k, Lloc)
+    ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")
+    out, lse = msa.msa_sparse_attend(cfg, *args, workspace=ws)
+    torch.cuda.synchronize()
+    oo, ol = O.sparse_attend(q, K, V, np.where(idx >= N, -1, idx).astype(np.int64), Kl, Vl, G, q_pos, 1e6,
+                             lens=lens, mem_rotated=bool(rotated))
+    go = out.float().cpu().numpy().astype(np.float64)
+    assert np.abs(go - oo).max() <= 2e-2 and np.linalg.norm(go - oo) <= 5e-3 * np.linalg.norm(oo)
+    seen = np.isfinite(ol)
+    gl = lse.cpu().numpy()
+    assert np.array_equal(np.isfinite(gl), seen) and np.abs(gl[seen] - ol[seen]).max() <= 5e-3
+    same = other = 0
+    for eighths in range(8, 0, -1):
+        part = ws[:size * eighths // 8]
+        part.fill_(0xFF)
+        try:
+            o2, l2 = msa.msa_sparse_attend(cfg, *args, workspace=part)
+        except Exception:
+            break
+        torch.cuda.synchronize()
+        if torch.equal(out.view(torch.int16), o2.view(torch.int16)) and torch.equal(lse, l2):
+            same += 1
+            continue
+        other += 1
+        x, y = o2.float(), out.float()
+        assert (x - y).abs().max() <= 2.0 ** -7 * y.abs().max() + 1e-6
+        assert (l2 - lse)[torch.isfinite(lse)].abs().max() <= 1e-4
+    assert same >= 1 and other >= 1, (same, other)
