@@ -145,7 +145,10 @@ static int check_attend(const msa_config_t* cfg, const void* q, int32_t B, int32
       misaligned(workspace) || misaligned4(dm->lens))
     return MSA_ERR_MISALIGNED;
   *pl = plan_attend(*dm, B, M, k, Lloc, cfg->bank_keys_rotated, workspace_bytes);
-  return workspace_bytes < pl->ws_bytes ? MSA_ERR_WORKSPACE : MSA_OK;
+  // The least size serves every call (the one asked for before the documents were taken one by one); a size that misses what
+  // is asked for by less than its granule is a miscounted one.
+  const bool miscounted = workspace_bytes < pl->ws_best && pl->ws_best - workspace_bytes < 256;
+  return workspace_bytes < pl->ws_bytes || miscounted ? MSA_ERR_WORKSPACE : MSA_OK;
 }
 
 }  // namespace msa
