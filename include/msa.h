@@ -128,7 +128,9 @@ size_t msa_inv_norm_bytes(const msa_config_t* cfg);
 uint64_t msa_pooled_bank_bytes(uint64_t tokens, uint32_t chunk, uint32_t heads, uint32_t head_dim,
                                uint32_t n_layers, uint32_t bytes_per_elem, uint32_t n_tensors);
 
-/* Workspace requirements (bytes, multiple of 256).  0 if the arguments are invalid.  The attention workspace
+/* Workspace requirements (bytes, multiple of 256).  0 if the arguments are invalid.  Scoring with one selection for all
+ * heads asks for 1288 bytes per token of a pass for candidate lists where the bank is taken in several segments; a workspace
+ * without them is accepted too (every segment's candidates are then scored at once).  The attention workspace
  * holds the split-K partials and, where many query tokens share keys (token_pool = 1 with M >= 8, or the local
  * context with M >= 16), those keys rotated once: B * Hkv * ceil((k*G or 0) + Lloc, 32 rows) * d * 2 bytes more.
  * Where many tokens bring many selections of their own it also asks for the buffers of the path that takes them document

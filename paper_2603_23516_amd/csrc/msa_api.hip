@@ -105,6 +105,12 @@ static int scratch_on_current_device(void** out) {
   return MSA_OK;
 }
 
+// A workspace of the least size serves every call, by a plan with fewer buffers than the size asked for holds (programs that
+// were built with smaller sizes); a size that misses what is asked for by less than its granule is a miscounted one.
+static bool too_small(size_t have, size_t least, size_t asked) {
+  return have < least || (have < asked && asked - have < 256);
+}
+
 // Everything that msa_score_topk refuses, and its plan.
 static int check_score(const msa_config_t* cfg, const void* q_route, int32_t B, int32_t M, const void* KR,
                        const float* inv_norm, int32_t k, const int32_t* out_idx, const float* out_score,
@@ -120,8 +126,8 @@ static int check_score(const msa_config_t* cfg, const void* q_route, int32_t B, 
   if (misaligned(q_route) || misaligned(KR) || misaligned(inv_norm) || misaligned(out_idx) ||
       misaligned(out_score) || misaligned(workspace))
     return MSA_ERR_MISALIGNED;
-  *pl = plan_score(*dm, B * M, k);
-  return workspace_bytes < pl->ws_bytes ? MSA_ERR_WORKSPACE : MSA_OK;
+  *pl = plan_score(*dm, B * M, k, workspace_bytes);
+  return too_small(workspace_bytes, pl->ws_bytes, pl->ws_best) ? MSA_ERR_WORKSPACE : MSA_OK;
 }
 
 // The same for msa_sparse_attend.
@@ -145,10 +151,7 @@ static int check_attend(const msa_config_t* cfg, const void* q, int32_t B, int32
       misaligned(workspace) || misaligned4(dm->lens))
     return MSA_ERR_MISALIGNED;
   *pl = plan_attend(*dm, B, M, k, Lloc, cfg->bank_keys_rotated, workspace_bytes);
-  // The least size serves every call (the one asked for before the documents were taken one by one); a size that misses what
-  // is asked for by less than its granule is a miscounted one.
-  const bool miscounted = workspace_bytes < pl->ws_best && pl->ws_best - workspace_bytes < 256;
-  return workspace_bytes < pl->ws_bytes || miscounted ? MSA_ERR_WORKSPACE : MSA_OK;
+  return too_small(workspace_bytes, pl->ws_bytes, pl->ws_best) ? MSA_ERR_WORKSPACE : MSA_OK;
 }
 
 }  // namespace msa
@@ -194,7 +197,7 @@ size_t msa_score_topk_workspace_bytes(const msa_config_t* cfg, int32_t B, int32_
   if (make_dims(cfg, &dm) != MSA_OK) return 0;
   if (B < 1 || M < 1 || k < 1 || k > MSA_MAX_TOPK || k > dm.N) return 0;
   if ((int64_t)B * M > (1 << 20)) return 0;
-  return plan_score(dm, B * M, k).ws_bytes;
+  return plan_score(dm, B * M, k).ws_best;
 }
 
 size_t msa_sparse_attend_workspace_bytes(const msa_config_t* cfg, int32_t B, int32_t M, int32_t k,
@@ -308,7 +311,7 @@ int msa_score_topk_noalloc(const msa_config_t* cfg, const void* q_route, int32_t
       misaligned(out_score))
     return MSA_ERR_MISALIGNED;
   const ScorePlan pl = plan_score(dm, B * M, k);
-  if (pl.ws_bytes > kNoAllocScratchBytes) return MSA_ERR_WORKSPACE;  // beyond the built-in scratch
+  if (pl.ws_best > kNoAllocScratchBytes) return MSA_ERR_WORKSPACE;  // beyond the built-in scratch
   void* ws = nullptr;
   const int rs = scratch_on_current_device(&ws);
   if (rs != MSA_OK) return rs;

@@ -64,6 +64,8 @@ struct WidePlan {
   int seg_docs;          // documents per segment (one score matrix)
   size_t off_qf, off_qop, off_eps, off_best, off_mat;
   size_t ws_bytes;
+  size_t list_bytes;     // several segments, one pass: candidate lists of the tokens of a pass
+  size_t off_list;       // ... where they are; 0: the workspace has no room for them
 };
 bool wide_path_applies(const Dims& dm, int BM);
 WidePlan plan_score_wide(const Dims& dm, int BM, int k);
@@ -103,9 +105,11 @@ struct ScorePlan {
   WidePlan wide;
   int use_gemm;          // 1: many query tokens, a selection per KV group -> msa_score_gemm.hip
   GemmPlan gemm;
-  size_t ws_bytes;
+  size_t ws_bytes;       // the least that is accepted
+  size_t ws_best;        // what is asked for
 };
-ScorePlan plan_score(const Dims& dm, int BM, int k);
+// The plan for a workspace of this size (0: whatever is asked for).
+ScorePlan plan_score(const Dims& dm, int BM, int k, size_t workspace_bytes = 0);
 
 // record the caller's per-call events (msa_config_t.profile_*_event) around the dominant kernel; null = off
 inline void profile_mark(const Dims& dm, bool stop, hipStream_t st) {

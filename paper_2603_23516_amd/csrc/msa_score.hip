@@ -1407,7 +1407,7 @@ static void plan_all_heads(const Dims& dm, int BM, int k, ScorePlan* p) {
   p->ws_bytes = end;
 }
 
-ScorePlan plan_score(const Dims& dm, int BM, int k) {
+static ScorePlan plan_score_least(const Dims& dm, int BM, int k) {
   ScorePlan p;
   // one selection per KV group, or (literal Eq. 2 head mean, more than one group) one for all heads
   p.all_heads = (dm.scope_all && dm.Hkv > 1) ? 1 : 0;
@@ -1491,6 +1491,20 @@ ScorePlan plan_score(const Dims& dm, int BM, int k) {
   p.off_mat = p.ws_bytes;
   if (p.mode == 2) p.ws_bytes += round_up256((size_t)dm.Hkv * BM * dm.N * sizeof(float));
   add_token_pool(dm, BM, k, &p);
+  return p;
+}
+
+ScorePlan plan_score(const Dims& dm, int BM, int k, size_t workspace_bytes) {
+  ScorePlan p = plan_score_least(dm, BM, k);
+  p.ws_best = p.ws_bytes;
+  if (p.use_wide && p.wide.list_bytes > 0) {
+    // (asked for only where the built-in scratch, if it serves the call, still does)
+    const size_t with = p.ws_bytes + p.wide.list_bytes;
+    if (with <= kNoAllocScratchBytes || p.ws_bytes > kNoAllocScratchBytes) {
+      p.ws_best = with;
+      if (workspace_bytes == 0 || workspace_bytes >= with) p.wide.off_list = p.ws_bytes;
+    }
+  }
   return p;
 }
 

@@ -25,8 +25,8 @@
 // matrix rate) and the L2 (a key is read once per 64 rows: 64 B per cycle and CU).  The workgroups of all token blocks
 // that read the same keys sit on one XCD and walk them together, so the index comes from memory once per XCD-resident
 // group of blocks. Measured: 150 tokens, k = 32, 97656 documents: kernel 3 x 142 us (three
-// segments; 192 padded rows, 0.72 PFLOP/s), selection 48 + 24 + 24 us; the call 4.87 ms as 19 passes of the scan -> 0.55
-// ms.  2048 tokens, 32768 documents, k = 8: 2.4 ms (a GEMM that reloaded its operands at every group switch) -> 1.84 ms.
+// segments; 192 padded rows, 0.72 PFLOP/s), selection 18 + 18 + 46 us; the call 4.87 ms as 19 passes of the scan -> 0.50
+// ms.  2048 tokens, 32768 documents, k = 8: 2.4 ms (a GEMM that reloaded its operands at every group switch) -> 1.47 ms.
 #include "msa_device.h"
 #include "msa_host.h"
 
@@ -238,12 +238,18 @@ void score_wide_kernel(WideArgs a) {
 //   2. t~ by rank counting among them; what is left of them after the two conditions are the candidates;
 //   3. the candidates' exact scores: Eq. 2 in fp32 from the folded fp32 query and the bf16 keys, eight lanes per key;
 //   4. the k best of candidates and earlier winners by rank counting on the full key.
+// With several segments and room for the lists (WideSelArgs::list) the exact scores wait for the last one: a segment leaves
+// its candidates, as keys of matrix scores, in the token's list of up to kWideList, t~ is the k-th largest of list and
+// segment, and what falls below t~ - 2 eps is dropped.  Step 3, a gather of 16 KiB per document, is then done for the
+// candidates of the whole bank and not of each segment (150 tokens, k = 32, 97656 documents, three segments: selection 57 + 51 + 30 us -> 18 + 18 + 46).  A list
+// that would grow longer (copies of a few documents) is scored, and the token goes on with exact winners.
 // If more survive than LDS holds (ties), topk_of_ties takes the k best where the matrix holds the exact scores; else
 // the row is taken in windows of kWideSurv documents: step 3 and 4 for those of a window that can still be among the k
 // best.  (150 tokens, 50 of them zeros, k = 32, 97656 documents: through the windows the call took 57 ms, now 0.57; 100
 // tokens whose best 4000 documents are copies of two, of 8192: 2.2 ms, bound by the exact scores of the copies.)
 constexpr int kWideSel = 512;      // threads
 constexpr int kWideSurv = 2048;
+constexpr int kWideList = 160;     // candidates that wait for the last segment
 constexpr int kWideRegs = 64;      // scores a thread keeps in registers (16: short rows)
 
 struct WideSelArgs {
@@ -254,6 +260,8 @@ struct WideSelArgs {
   const uint16_t* KR;
   const float* inv_norm;
   unsigned long long* best;  // [tokens][k] keys of the segments so far
+  unsigned long long* list;  // BAND: [tokens][kWideList] candidates of the segments so far; null: exact winners in best
+  uint2* list_n;             // [tokens] (entries, image of the k-th largest; 0: fewer than k); (~0, ..): winners in best
   int first, last;           // first segment: nothing in best yet; last: the result goes out
   int32_t* out_idx;
   float* out_score;
@@ -269,7 +277,8 @@ template <bool BAND, int REGS>
 __global__ __launch_bounds__(kWideSel) void score_wide_select_kernel(WideSelArgs a) {
   constexpr int NW = kWideSel / 64;
   constexpr int D = 128, C = 8;
-  __shared__ unsigned long long surv[kWideSurv + MSA_MAX_TOPK + 8];
+  constexpr int kMost = kWideSurv + (BAND ? kWideList : 0);  // candidates at a time
+  __shared__ unsigned long long surv[kMost + MSA_MAX_TOPK + 8];
   __shared__ float qs[BAND ? 8 * D : 1];
   __shared__ unsigned long long best_s[MSA_MAX_TOPK];
   __shared__ uint32_t theta_w[2][NW];
@@ -287,7 +296,17 @@ __global__ __launch_bounds__(kWideSel) void score_wide_select_kernel(WideSelArgs
     for (int i = tid; i < a.Hkv * D; i += kWideSel) qs[i] = a.qf[(long long)tok * a.Hkv * D + i];
   }
   int n_best = 0;  // earlier winners
-  if (!a.first) {
+  int n_list = 0;  // earlier candidates
+  uint32_t list_kth = 0u;
+  bool listed = BAND && a.list != nullptr;
+  if (listed && !a.first) {
+    const uint2 l = a.list_n[tok];
+    listed = l.x != ~0u;
+    n_list = listed ? (int)l.x : 0;
+    list_kth = l.y;
+  }
+  unsigned long long* const list = listed ? a.list + (long long)tok * kWideList : nullptr;
+  if (!a.first && !listed) {
     n_best = k;
     if (tid < k) best_s[tid] = a.best[(long long)tok * k + tid];
   }
@@ -401,7 +420,10 @@ __global__ __launch_bounds__(kWideSel) void score_wide_select_kernel(WideSelArgs
   rest_of_row(best_of);
   const uint32_t theta = kth_best_bound<NW>(ob, k, theta_w);
   uint32_t lim = theta ? floor_of(unorderable(theta), 2.f * eps) : 0u;
-  if (!a.first) {  // the k-th best so far (0: fewer than k)
+  if (listed) {
+    const uint32_t l2 = list_kth ? floor_of(unorderable(list_kth), 2.f * eps) : 0u;
+    lim = l2 > lim ? l2 : lim;
+  } else if (!a.first) {  // the k-th best so far (0: fewer than k)
     const unsigned long long kb = best_s[k - 1];
     // (a tie loses to the documents of earlier segments)
     const uint32_t l2 = kb ? floor_of(key_score(kb), eps) + 1u : 0u;
@@ -419,14 +441,27 @@ __global__ __launch_bounds__(kWideSel) void score_wide_select_kernel(WideSelArgs
   __syncthreads();
   int ns = n_surv;
   __syncthreads();
-  if (ns <= kWideSurv) {
+  const bool over = ns > kWideSurv;  // block-uniform, as all below
+  if (n_list > 0) {
+    const int at = over ? 0 : ns;
+    if (tid < n_list) surv[at + tid] = list[tid];
+    ns += n_list;
+    __syncthreads();
+    if (over) {  // exact winners of those before
+      rescore(n_list);
+      merge(n_list);
+    }
+  }
+  if (over) listed = false;
+  if (!over) {
     // ---- 2. t~, candidates -----------------------------------------------------------------------------------------
     if (BAND && ns > k) {
       if (tid < 8) surv[ns + tid] = 0ull;
       __syncthreads();
-      unsigned long long mine[kWideSurv / kWideSel];
+      constexpr int kMine = (kMost + kWideSel - 1) / kWideSel;
+      unsigned long long mine[kMine];
 #pragma unroll
-      for (int u = 0; u < kWideSurv / kWideSel; ++u) {
+      for (int u = 0; u < kMine; ++u) {
         const int i = u * kWideSel + tid;
         mine[u] = i < ns ? surv[i] : 0ull;
         if (u * kWideSel < ns) {  // block-uniform
@@ -443,13 +478,19 @@ __global__ __launch_bounds__(kWideSel) void score_wide_select_kernel(WideSelArgs
       }
       if (tid == 0) n_surv = 0;
       __syncthreads();
-      const uint32_t l2 = floor_of(unorderable(kth_s), 2.f * eps);
+      list_kth = kth_s;
+      const uint32_t l2 = floor_of(unorderable(list_kth), 2.f * eps);
       lim = l2 > lim ? l2 : lim;
 #pragma unroll
-      for (int u = 0; u < kWideSurv / kWideSel; ++u)
+      for (int u = 0; u < kMine; ++u)
         if (mine[u] != 0ull && (uint32_t)(mine[u] >> 32) >= lim) surv[atomicAdd(&n_surv, 1)] = mine[u];
       __syncthreads();
       ns = n_surv;
+    }
+    if (listed && !a.last && ns <= kWideList) {
+      if (tid < ns) a.list[(long long)tok * kWideList + tid] = surv[tid];
+      if (tid == 0) a.list_n[tok] = make_uint2((uint32_t)ns, list_kth);
+      return;
     }
     // ---- 3., 4. ------------------------------------------------------------------------------------------------------
     rescore(ns);
@@ -474,6 +515,7 @@ __global__ __launch_bounds__(kWideSel) void score_wide_select_kernel(WideSelArgs
       merge(ns);
     }
   }
+  if (BAND && tid == 0 && a.list != nullptr) a.list_n[tok] = make_uint2(~0u, 0u);
   if (tid < k) {
     const unsigned long long x = tid < n_best ? best_s[tid] : 0ull;
     const long long o = (long long)(a.tok0 + tok) * k + tid;
@@ -517,6 +559,10 @@ WidePlan plan_score_wide(const Dims& dm, int BM, int k) {
   p.off_mat = end;
   end += round_up256((size_t)p.pass_tokens * p.seg_docs * sizeof(float));
   p.ws_bytes = end;
+  p.list_bytes = !p.pair && p.seg_docs < dm.N
+                     ? round_up256((size_t)p.pass_tokens * kWideList * 8) + round_up256((size_t)p.pass_tokens * sizeof(uint2))
+                     : 0;
+  p.off_list = 0;
   return p;
 }
 
@@ -545,6 +591,8 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
   s.Hkv = dm.Hkv;
   s.k = k;
   s.tiles = dm.tiles;
+  s.list = pl.off_list != 0 ? (unsigned long long*)(w + pl.off_list) : nullptr;
+  s.list_n = pl.off_list != 0 ? (uint2*)(w + pl.off_list + round_up256((size_t)pl.pass_tokens * kWideList * 8)) : nullptr;
   const int per_wg = kWideRows / (pl.pair ? 2 : 1);
   for (int tok0 = 0; tok0 < BM; tok0 += pl.pass_tokens) {
     const int nq = BM - tok0 < pl.pass_tokens ? BM - tok0 : pl.pass_tokens;

@@ -257,6 +257,58 @@ def test_all_heads_wide_more_candidates_than_k(copies, d):
     assert np.allclose(val.cpu().numpy(), s[..., want], rtol=0, atol=2e-5)
 
 
+# (N, Hkv, M, k, copies, zeros): several segments, d = 128 and eight chunks: candidates wait for the last segment
+ALL_LISTED = [
+    (20000, 2, 1000, 32, 0, 0),       # four segments
+    (20011, 4, 700, 64, 0, 3),        # a query of zeros in three: exact from its first segment on
+    (20000, 2, 600, 12, 300, 0),      # more candidates than wait: exact winners from the segment on where they do not fit
+    (9000, 2, 1024, 9, 5000, 5),      # more than the selection holds
+    (5300, 8, 1000, 64, 100, 0),      # two segments
+]
+
+
+@pytest.mark.parametrize("N,Hkv,M,k,copies,zeros", ALL_LISTED)
+def test_all_heads_wide_candidates_of_all_segments(N, Hkv, M, k, copies, zeros):
+    """The same winners and the same exact scores, bit for bit, as where every segment's candidates are scored at once,
+    which a workspace without room for the lists does; and the scores of float64."""
+    say(f"all-heads lists N={N} Hkv={Hkv} M={M} k={k} copies={copies} zeros={zeros}")
+    C, d = 8, 128
+    cfg = msa.MsaConfig(N, 8 * C, 8, Hkv, Hkv, d, 1e6, select_scope=msa.MSA_SCOPE_ALL)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(61000 + N + k)
+    KR, inv = msa.alloc_routing_index(cfg)
+    KR.normal_(generator=gen)
+    q = torch.randn((1, M, Hkv, d), generator=gen, device="cuda").to(torch.bfloat16)
+    if copies:  # [Hkv][tiles][d/8][16][8], two documents per tile
+        q = q.abs()
+        docs = KR.view(Hkv, -1, d // 8, 2, 8, 8)
+        at = torch.randperm(N, generator=gen, device="cuda")[:copies]
+        docs[:, at // 2, :, at % 2] = docs[:, 0, :, 0].abs().unsqueeze(0)
+    if zeros:
+        q[:, ::zeros] = 0
+    inv.copy_(KR.float().pow(2).sum((2, 4)).rsqrt().reshape(Hkv, -1))
+    size = msa.score_topk_workspace_bytes(cfg, 1, M, k)
+    least = size - (M * 160 * 8 + 255) // 256 * 256 - (M * 8 + 255) // 256 * 256
+    got = []
+    for n in (size, least):
+        ws = torch.full((n,), 0xFF, dtype=torch.uint8, device="cuda")
+        got.append(msa.msa_score_topk(cfg, q, KR, inv, k, workspace=ws))
+        torch.cuda.synchronize()
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    idx, val = got[0][0][0, :, 0].long(), got[0][1][0, :, 0]
+    x = q[0].double()
+    x = x / x.norm(dim=-1, keepdim=True).clamp_min(1e-12)
+    keys = msa.untile_routing_keys(cfg, KR).double().reshape(Hkv, N, C, d)
+    s = None
+    for g in range(Hkv):
+        kg = keys[g] / keys[g].norm(dim=-1, keepdim=True)
+        part = x[:, g] @ kg.reshape(N * C, d).t()
+        s = part if s is None else s.add_(part)
+    s = (s / Hkv).reshape(M, N, C).amax(-1)
+    assert (s.topk(k, dim=1).values - val.double()).abs().max() <= 2e-5
+    assert (s.gather(1, idx) - val.double()).abs().max() <= 2e-5
+
+
 @pytest.mark.parametrize("N,Hkv,G,P,d,first,count", [(5, 3, 56, 8, 64, 1, 3), (3, 1, 24, 24, 128, 0, 3), (7, 5, 256, 64, 128, 6, 1),
                                                         (5, 2, 512, 128, 64, 1, 4)])
 def test_pool_chunks_by_pairs(N, Hkv, G, P, d, first, count):
