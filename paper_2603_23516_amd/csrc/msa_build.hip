@@ -14,8 +14,11 @@ namespace msa {
 
 // UB: loads per batch.  Sixteen take a whole chunk of 64 rows at d = 128 at once (4.3 GB: 726 us with eight -> 706 us);
 // chunks of eight loads or fewer would pay for the empty half (P = 32, d = 64, 0.5 GB: 106 us, with eight 93).
-template <int D, int UB>
-__global__ __launch_bounds__(256) void build_routing_keys_kernel(
+// RUN: eight waves take the eight chunks of half a tile (eight or sixteen chunks per document, every document full); their
+// pieces meet in LDS and leave as whole lines (128 bytes: piece c of eight keys) past the L2 (4.3 GB: 703 us with 16-byte
+// stores from every wave, 676).
+template <int D, int UB, bool RUN>
+__global__ __launch_bounds__(RUN ? 512 : 256) void build_routing_keys_kernel(
     const uint16_t* __restrict__ K, uint16_t* __restrict__ KR, float* __restrict__ inv_norm,
     const int32_t* __restrict__ lens, int doc_begin, long long n_chunks, int Hkv, int G, int P, int C,
     int cshift, long long tiles) {
@@ -23,8 +26,8 @@ __global__ __launch_bounds__(256) void build_routing_keys_kernel(
   constexpr int RPL = 64 / LPR;  // rows per wave-wide load
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const long long cid = (long long)blockIdx.x * 4 + wave;
-  if (cid >= n_chunks) return;  // wave-uniform
+  const long long cid = (long long)blockIdx.x * (RUN ? 8 : 4) + wave;
+  if (cid >= n_chunks) return;  // wave-uniform (RUN: never, whole documents)
   const int j = (int)(cid & (C - 1));  // C is a power of two
   const uint32_t t = (uint32_t)(cid >> cshift);  // (document, head): fits 32 bits (checked by the launcher)
   const int g = (int)(t % (uint32_t)Hkv);
@@ -33,7 +36,7 @@ __global__ __launch_bounds__(256) void build_routing_keys_kernel(
   // document score is a max over chunks, which a repeated chunk cannot change.
   // The wave of chunk 0 writes those slots too.
   int n_rows = P, repeat_from = C;
-  if (lens != nullptr) {
+  if (!RUN && lens != nullptr) {
     int len = lens[doc];
     len = len < 1 ? 1 : (len > G ? G : len);
     n_rows = len - j * P;
@@ -52,13 +55,16 @@ __global__ __launch_bounds__(256) void build_routing_keys_kernel(
   const int iters = P / RPL;
   for (int it0 = 0; it0 < iters; it0 += UB) {
     uint4 v[UB];
+    const uint16_t* rp = src + (it0 * RPL + rowoff) * D + piece * 8;
+    if ((it0 + UB) * RPL <= n_rows) {  // wave-uniform: whole batch, no condition on a load
 #pragma unroll
-    for (int u = 0; u < UB; ++u) {
-      const int it = it0 + u;
-      if (it < iters && it * RPL + rowoff < n_rows) {
-        v[u] = load_stream16(src + (long long)(it * RPL + rowoff) * D + piece * 8);
-      } else {
+      for (int u = 0; u < UB; ++u) v[u] = load_stream16(rp + u * RPL * D);
+    } else {
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        const int it = it0 + u;
         v[u] = make_uint4(0, 0, 0, 0);
+        if (it < iters && it * RPL + rowoff < n_rows) v[u] = load_stream16(rp + u * RPL * D);
       }
     }
 #pragma unroll
@@ -75,16 +81,13 @@ __global__ __launch_bounds__(256) void build_routing_keys_kernel(
   }
   // combine the RPL row groups that hold the same columns
 #pragma unroll
-  for (int off = LPR; off < 64; off <<= 1) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] += __shfl_xor(acc[e], off, 64);
-  }
-  const float fp = (float)n_rows;
+  for (int e = 0; e < 8; ++e) acc[e] = add_row_groups<LPR>(acc[e]);
+  mean_of(acc, n_rows);
   uint4 o;
-  o.x = pack_bf16(acc[0] / fp, acc[1] / fp);
-  o.y = pack_bf16(acc[2] / fp, acc[3] / fp);
-  o.z = pack_bf16(acc[4] / fp, acc[5] / fp);
-  o.w = pack_bf16(acc[6] / fp, acc[7] / fp);
+  o.x = pack_bf16(acc[0], acc[1]);
+  o.y = pack_bf16(acc[2], acc[3]);
+  o.z = pack_bf16(acc[4], acc[5]);
+  o.w = pack_bf16(acc[6], acc[7]);
 
   // squared norm of the ROUNDED key
   float ss = 0.f;
@@ -97,6 +100,21 @@ __global__ __launch_bounds__(256) void build_routing_keys_kernel(
   for (int off = 1; off < LPR; off <<= 1) ss += __shfl_xor(ss, off, 64);
 
   const float inv = 1.0f / fmaxf(sqrtf(ss), 1e-12f);
+  if constexpr (RUN) {
+    __shared__ uint4 pieces[LPR][8];
+    __shared__ float norms[8];
+    if (rowoff == 0) pieces[piece][wave] = o;
+    if (lane == 0) norms[wave] = inv;
+    __syncthreads();
+    const int x = threadIdx.x;  // piece x / 8 of key x % 8
+    const long long c0 = doc * C + (j & ~7);  // first key of the run
+    if (x < LPR * 8) {
+      uint16_t* dst = KR + ((long long)g * tiles + (c0 >> 4)) * (16 * D) + ((x >> 3) * 16 + (int)(c0 & 15) + (x & 7)) * 8;
+      store_stream16(dst, pieces[x >> 3][x & 7]);
+    }
+    if (x < 8 && inv_norm != nullptr) inv_norm[(long long)g * tiles * 16 + c0 + x] = norms[x];
+    return;
+  }
   for (int jj = j; jj < C; jj = jj < repeat_from ? repeat_from : jj + 1) {  // wave-uniform: slot j, then the repeats
     const long long c = doc * C + jj;  // key number inside head g
     const long long tile = c >> 4;
@@ -134,17 +152,23 @@ int launch_build(const Dims& dm, const void* K, int doc_begin, int doc_count, vo
     if (blocks > 0x7fffffffLL || (long long)doc_count * dm.Hkv > 0xffffffffLL) return MSA_ERR_UNSUPPORTED;
     int cshift = 0;
     while ((1 << cshift) < dm.C) ++cshift;
-    dim3 grid((unsigned)blocks), block(256);
+    const bool run = dm.C >= 8 && dm.lens == nullptr;
+    dim3 grid((unsigned)(run ? blocks / 2 : blocks)), block(run ? 512 : 256);
     const int loads = dm.P / (512 / dm.d);  // of a chunk
-#define MSA_BUILD(DD, UU) \
-  hipLaunchKernelGGL((build_routing_keys_kernel<DD, UU>), grid, block, 0, st, (const uint16_t*)K, (uint16_t*)KR, inv_norm, \
+#define MSA_BUILD_AS(DD, UU, RR) \
+  hipLaunchKernelGGL((build_routing_keys_kernel<DD, UU, RR>), grid, block, 0, st, (const uint16_t*)K, (uint16_t*)KR, inv_norm, \
                      dm.lens, doc_begin, n_chunks, dm.Hkv, dm.G, dm.P, dm.C, cshift, (long long)dm.tiles)
+#define MSA_BUILD(DD, UU) \
+  do { \
+    if (run) MSA_BUILD_AS(DD, UU, true); else MSA_BUILD_AS(DD, UU, false); \
+  } while (0)
     if (dm.d == 128) {
       if (loads > 8) MSA_BUILD(128, 16); else MSA_BUILD(128, 8);
     } else {
       if (loads > 8) MSA_BUILD(64, 16); else MSA_BUILD(64, 8);
     }
 #undef MSA_BUILD
+#undef MSA_BUILD_AS
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
   }
   const int n_pad = (int)(dm.tiles * 16 - dm.NC);

@@ -73,6 +73,13 @@ __device__ __forceinline__ uint4 load_stream16(const void* p) {
   const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
   return make_uint4(v.x, v.y, v.z, v.w);
 }
+// Results of a long read stream that nobody reads soon: kept in the L2 and written back at some later time they turn the
+// memory around between reading and writing (4.3 GB read and 1/64 of it written: 684 us, with the hint 659, nothing
+// written 619).  Whole 64-byte runs per instruction only.
+__device__ __forceinline__ void store_stream16(void* p, uint4 v) {
+  const u32x4_t x = {v.x, v.y, v.z, v.w};
+  __builtin_nontemporal_store(x, reinterpret_cast<u32x4_t*>(p));
+}
 __device__ __forceinline__ float load_stream(const float* p) { return __builtin_nontemporal_load(p); }
 
 // ---- transposing LDS read -------------------------------------------------------------------------
@@ -121,6 +128,7 @@ __device__ __forceinline__ float dpp_f(float x) {
 constexpr int kDppXor1 = 0xB1;        // quad_perm [1,0,3,2]
 constexpr int kDppXor2 = 0x4E;        // quad_perm [2,3,0,1]
 constexpr int kDppHalfMirror = 0x141; // lane i <-> 7 - i inside each group of 8
+constexpr int kDppRor8 = 0x128;       // lane i <- lane (i + 8) % 16 inside each row of 16
 constexpr int kDppMirror = 0x140;     // lane i <-> 15 - i inside each row of 16
 
 // Max over aligned groups of C consecutive lanes (C in {1,2,4,8,16}); every lane gets the result.
@@ -131,6 +139,40 @@ __device__ __forceinline__ float group_max(float x) {
   if (C >= 8) x = fmaxf(x, dpp_f<kDppHalfMirror>(x));
   if (C >= 16) x = fmaxf(x, dpp_f<kDppMirror>(x));
   return x;
+}
+
+// Sums over the lanes that differ in bit 4 and 5 of the lane number (16 apart, 32 apart); every lane gets the result.
+// Vector instructions, where __shfl_xor goes through the LDS unit.
+__device__ __forceinline__ float add_xor32(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float add_xor16(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+// x summed over the lanes that share lane % LPR (LPR in {4, 8, 16}).
+template <int LPR>
+__device__ __forceinline__ float add_row_groups(float x) {
+  if (LPR <= 4) x += __shfl_xor(x, 4, 64);
+  if (LPR <= 8) x += dpp_f<kDppRor8>(x);
+  x = add_xor16(x);
+  return add_xor32(x);
+}
+
+// The sums of n rows (the same n in every lane) over n; by a power of two the product with its reciprocal is the quotient.
+__device__ __forceinline__ void mean_of(float (&acc)[8], int n) {
+  const float fn = (float)n;
+  if ((n & (n - 1)) == 0) {
+    const float rn = 1.0f / fn;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] *= rn;
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] /= fn;
+  }
 }
 
 // ---- rotary position encoding ---------------------------------------------------------------

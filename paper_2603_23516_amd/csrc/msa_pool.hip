@@ -8,7 +8,8 @@
 // cover a row and a wave-wide pair of loads covers 1024/d rows.  The angles of the lane's first row,
 // (cos, sin)(p theta_u), come from a double-precision range reduction; the rows a constant stride apart
 // are summed by Horner's rule.  With the vector work of the angles shared by a workgroup and halved per row the keys
-// stream as fast as the values: 4.3 GB at d = 128 781 -> 704 us, 0.5 GB at d = 64 150 -> 114 us, P = 32 378 -> 295 us.
+// stream as fast as the values: 4.3 GB at d = 128 781 -> 704 us, 0.5 GB at d = 64 150 -> 114 us, P = 32 378 -> 295 us.  Both
+// end at what reading together with writing allows: 685 and 668 us for 4.3 GB and 1/64 of it (read alone 620).
 #include "msa_device.h"
 #include "msa_host.h"
 
@@ -57,15 +58,21 @@ __global__ __launch_bounds__(256) void pool_chunks_kernel(const uint16_t* __rest
   // eight, 162 with four)
   uint4 v1[NB], v2[NB];
   auto load = [&](int it0) __attribute__((always_inline)) {
+    const uint16_t* rp = src + (it0 * RPL + rowoff) * D + pc * 8;
+    if ((it0 + NB) * RPL <= n_rows) {  // wave-uniform: whole batch, no condition on a load
 #pragma unroll
-    for (int u = 0; u < NB; ++u) {
-      const int row = (it0 + u) * RPL + rowoff;
-      if (row < n_rows) {
-        const uint16_t* rp = src + (long long)row * D + pc * 8;
-        v1[u] = load_stream16(rp);
-        v2[u] = load_stream16(rp + D / 2);
-      } else {
+      for (int u = 0; u < NB; ++u) {
+        v1[u] = load_stream16(rp + u * RPL * D);
+        v2[u] = load_stream16(rp + u * RPL * D + D / 2);
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < NB; ++u) {
         v1[u] = v2[u] = make_uint4(0, 0, 0, 0);
+        if ((it0 + u) * RPL + rowoff < n_rows) {
+          v1[u] = load_stream16(rp + u * RPL * D);
+          v2[u] = load_stream16(rp + u * RPL * D + D / 2);
+        }
       }
     }
   };
@@ -130,22 +137,25 @@ __global__ __launch_bounds__(256) void pool_chunks_kernel(const uint16_t* __rest
   }
   // combine the RPL row groups that hold the same columns
 #pragma unroll
-  for (int off = LPR; off < 64; off <<= 1) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      a1[e] += __shfl_xor(a1[e], off, 64);
-      a2[e] += __shfl_xor(a2[e], off, 64);
-    }
+  for (int e = 0; e < 8; ++e) {
+    a1[e] = add_row_groups<LPR>(a1[e]);
+    a2[e] = add_row_groups<LPR>(a2[e]);
   }
   if (rowoff == 0) {
-    const float fp = (float)(n_rows > 0 ? n_rows : 1);
+    mean_of(a1, n_rows > 0 ? n_rows : 1);
+    mean_of(a2, n_rows > 0 ? n_rows : 1);
     uint16_t* dst = Xbar + (((doc * Hkv + g) * (long long)C + j) * D) + pc * 8;
-    *reinterpret_cast<uint4*>(dst) =
-        make_uint4(pack_bf16(a1[0] / fp, a1[1] / fp), pack_bf16(a1[2] / fp, a1[3] / fp),
-                   pack_bf16(a1[4] / fp, a1[5] / fp), pack_bf16(a1[6] / fp, a1[7] / fp));
-    *reinterpret_cast<uint4*>(dst + D / 2) =
-        make_uint4(pack_bf16(a2[0] / fp, a2[1] / fp), pack_bf16(a2[2] / fp, a2[3] / fp),
-                   pack_bf16(a2[4] / fp, a2[5] / fp), pack_bf16(a2[6] / fp, a2[7] / fp));
+    const uint4 o1 = make_uint4(pack_bf16(a1[0], a1[1]), pack_bf16(a1[2], a1[3]), pack_bf16(a1[4], a1[5]), pack_bf16(a1[6], a1[7]));
+    const uint4 o2 = make_uint4(pack_bf16(a2[0], a2[1]), pack_bf16(a2[2], a2[3]), pack_bf16(a2[4], a2[5]), pack_bf16(a2[6], a2[7]));
+    // past the L2 where a store is a whole line and every chunk has its rows (0.5 GB at d = 64, whose stores are half
+    // lines: the encoding 274 us, with the hint 288; documents of different lengths 1493 and 1510)
+    if (D == 128 && lens == nullptr) {
+      store_stream16(dst, o1);
+      store_stream16(dst + D / 2, o2);
+    } else {
+      *reinterpret_cast<uint4*>(dst) = o1;
+      *reinterpret_cast<uint4*>(dst + D / 2) = o2;
+    }
   }
 }
 

@@ -357,6 +357,28 @@ def test_routing_keys_by_batches(G, P, d):
                 assert np.abs(got[:, i, j] - want).max() <= 2.0 ** -8 * np.abs(want).max() + 1e-5
 
 
+@pytest.mark.parametrize("G,P,d,first,count", [(64, 8, 64, 0, 5), (512, 64, 128, 1, 3), (256, 16, 128, 2, 3), (1024, 64, 64, 4, 1)])
+def test_routing_keys_by_runs(G, P, d, first, count):
+    """Eight and sixteen chunks per document, none short: eight keys leave together.  Keys as above, the norms those of the
+    rounded keys (fp32 sums and a square root: 2e-6 of the value), and no slot of a document that was not asked for."""
+    N, Hkv, C = 5, 3, G // P
+    Kb, K = S.normal_bf16(57100, (N, Hkv, G, d))
+    cfg = msa.MsaConfig(N, G, P, Hkv, Hkv, d, 1e4)
+    KR, inv = msa.alloc_routing_index(cfg)
+    KR.fill_(7.0)
+    inv.fill_(7.0)
+    msa.msa_build_routing_keys(cfg, dev(Kb), doc_begin=first, doc_count=count, KR=KR, inv_norm=inv)
+    torch.cuda.synchronize()
+    got = msa.untile_routing_keys(cfg, KR).float().cpu().numpy().astype(np.float64).reshape(Hkv, N, C, d)
+    norm = inv.cpu().numpy().astype(np.float64).reshape(Hkv, -1)[:, :N * C].reshape(Hkv, N, C)
+    there = np.arange(N)[(np.arange(N) >= first) & (np.arange(N) < first + count)]
+    rest = np.setdiff1d(np.arange(N), there)
+    want = K.reshape(N, Hkv, C, P, d).mean(3).transpose(1, 0, 2, 3)
+    assert np.abs(got[:, there] - want[:, there]).max() <= 2.0 ** -8 * np.abs(want).max() + 1e-5
+    assert np.abs(norm[:, there] * np.linalg.norm(got[:, there], axis=-1) - 1).max() <= 2e-6
+    assert np.all(got[:, rest] == 7.0) and np.all(norm[:, rest] == 7.0)
+
+
 # (N, Hkv, r, G, d, B, M, k, Lloc, scope, rotated): many (query, KV head) pairs in the decode kernel
 ATT_LINEAR = [
     (40, 8, 4, 512, 128, 20, 1, 18, 5, "group", 0),      # 160 pairs of 289 steps, three splits each
