@@ -1119,13 +1119,16 @@ __global__ __launch_bounds__(64 * WAVES) void topk_rows_kernel(RowsArgs a) {
 // Waves per workgroup: sixteen where the rows leave the chip idle anyway (one round of 256 workgroups or fewer) and a row
 // is longer than four waves hold in registers: 32768 scores at once.  One workgroup then takes a row that went in parts
 // with a merge launch behind: 30000 documents of 64 dims, 2 queries, whole call 27.4 -> 24.6 us; 20000 of 128, one query,
-// 71.8 -> 68.
+// 71.8 -> 68.  Eight waves for rows of 2049 to 8192 documents: a thread's share is 16 scores, not 32 (64 rows of 8192: 7.2 -> 5.9
+// us, 24 rows 6.5 -> 5.1; sixteen waves 6.0 and 5.4).  Shorter rows gain nothing (8 rows of 2048: call 12.3 us with four
+// waves, 12.1 with eight, 12.8 with sixteen; 24 of 700 11.0, 11.3, 14.1).
 static void launch_topk_rows(const RowsArgs& ra, hipStream_t st) {
   const unsigned blocks = (unsigned)(ra.BM * ra.n_sel * ra.parts);
   const int n = ra.n_docs < ra.part_docs ? ra.n_docs : ra.part_docs;
 #define MSA_TOPK_ROWS(RR, WW) \
   hipLaunchKernelGGL((topk_rows_kernel<RR, WW>), dim3(blocks), dim3(64 * WW), 0, st, ra)
   if (n <= 8 * 256) MSA_TOPK_ROWS(8, 4);
+  else if (blocks <= 256 && n <= 16 * 512) MSA_TOPK_ROWS(16, 8);
   else if (blocks > 256 || n <= kRowPart) MSA_TOPK_ROWS(kRowRegs, 4);
   else MSA_TOPK_ROWS(kRowRegs, 16);
 #undef MSA_TOPK_ROWS

@@ -34,6 +34,24 @@ ALL_SCAN = [
 ]
 
 
+# (N, Hkv, B, k): rows of the scan's score matrix that eight waves take, at the edges of their range
+ROWS_EIGHT = [(2048, 2, 3, 17), (2049, 2, 3, 64), (5000, 4, 2, 1), (8192, 8, 8, 33), (8193, 2, 2, 64), (4100, 8, 33, 20)]
+
+
+@pytest.mark.parametrize("N,Hkv,B,k", ROWS_EIGHT)
+def test_row_selection(N, Hkv, B, k):
+    """Scores of float64 to fp32 rounding, and the documents that have them."""
+    say(f"row selection N={N} Hkv={Hkv} B={B} k={k}")
+    C, d = 8, 64
+    cfg = msa.MsaConfig(N, 8 * C, 8, Hkv, Hkv, d, 1e6)
+    KRb, inv = random_index(53000 + N, N, Hkv, C, d)
+    qb, q = S.normal_bf16(53001, (B, 1, Hkv, d))
+    dKR, dinv = upload_oracle_index(cfg, KRb, inv)
+    idx, val = msa.msa_score_topk(cfg, dev(qb), dKR, dinv, k)
+    torch.cuda.synchronize()
+    check_topk_generic(q, KRb, C, N, idx, val, k, "cos", "group", False)
+
+
 @pytest.mark.parametrize("N,Hkv,r,C,d,B,M,k,sim", ALL_SCAN)
 def test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim):
     say(f"all-heads scan N={N} Hkv={Hkv} C={C} d={d} B={B} M={M} k={k} {sim}")
