@@ -66,6 +66,11 @@ class LayerStack:
             self.acfg = self.pcfg.replace(n_docs=n_slots)
         self.ws_a = torch.empty(sparse_attend_workspace_bytes(self.acfg, B, M, k, Lloc), dtype=torch.uint8, device=device)
         self.s_route, self.s_attend = torch.cuda.Stream(device), torch.cuda.Stream(device)
+        self.last = None   # the stream that the last step of the "hbm" tier was called on
+        # Attention beside the next layer's scan pays for its hand-over between streams only where that scan is long.  Four
+        # layers of 8 heads of 128, us per step on one stream / on two: index of 17 MB (5 queries, two layers) 62 / 88, 68 MB
+        # (16 queries) 266 / 274, 136 MB (8 queries) 225 / 210, 136 MB (one query) 205 / 192.
+        self.two_streams = n_layers > 1 and self.KR[0].numel() * 2 >= 100 << 20
         self.ev_scored = [torch.cuda.Event() for _ in range(n_layers)]
         self.ev_fork, self.ev_join = torch.cuda.Event(), torch.cuda.Event()
         for ev in self.ev_scored + [self.ev_fork, self.ev_join]:
@@ -106,6 +111,14 @@ class LayerStack:
         s_a = self.s_attend if overlap else self.s_route
         cur = torch.cuda.current_stream(self.dev)
         if self.tier == "hbm":
+            # Routing runs on the caller's stream: handed to a stream of its own and joined again, small steps waited more
+            # than they worked (two layers, 1000 documents, 5 queries 87 us -> 62; four, 256 documents, 2 queries 141 -> 95).
+            # Steps from different streams follow each other all the same, since they share the workspaces.
+            if not torch.cuda.is_current_stream_capturing():
+                if self.last is not None and self.last != cur:
+                    cur.wait_stream(self.last)
+                self.last = cur
+            s_r, s_a = cur, self.s_attend if overlap and self.two_streams else cur
             # the whole step in one native call: as single calls from here the host was the bound of small steps (four
             # layers, 557 documents, 5 streams: 223 us -> 153; two layers, 956 documents, 2 streams: 141 -> 93)
             msa_layers_step(self.cfg, self.acfg,

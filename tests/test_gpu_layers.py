@@ -115,3 +115,58 @@ def test_refused_layer_leaves_nothing_behind():
         assert torch.equal(part[0].view(torch.int16), outs[0].view(torch.int16))
     for a, b in zip(*runs):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("two", [False, True])
+def test_steps_from_several_streams_and_a_graph(two):
+    """Steps called on two streams in turn share the stack's workspaces: they follow each other, with attention beside the
+    next layer's routing or not; and a captured step replays with eager steps between its replays."""
+    L, N, Hkv, r, G, d, P, B, k, Lloc = 3, 3000, 4, 2, 256, 64, 32, 6, 8, 70
+    Hq = Hkv * r
+    stack = LayerStack(msa.MsaConfig(N, G, P, Hq, Hkv, d, 1e4), L, B, 1, k, Lloc)
+    assert not stack.two_streams
+    stack.two_streams = two
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(98000)
+
+    def rnd(*shape):
+        return torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+    for l in range(L):
+        stack.set_layer_keys(l, rnd(N, Hkv, G, d))
+        stack.set_layer_values(l, rnd(N, Hkv, G, d))
+    Kls, Vls = ([rnd(B, Hkv, Lloc, d) for _ in range(L)] for _ in range(2))
+    pos = torch.full((B, 1), k + Lloc - 1, dtype=torch.int32, device="cuda")
+    batches = [[rnd(B, 1, Hq, d) for _ in range(L)] for _ in range(6)]
+
+    def buffers():
+        return [torch.zeros(B, 1, Hq, d, dtype=torch.bfloat16, device="cuda") for _ in range(L)]
+    lses = [None] * L
+    want = []
+    for qs in batches:
+        outs = buffers()
+        stack.step(qs, Kls, Vls, k, pos, outs, lses, overlap=False)
+        torch.cuda.synchronize()
+        want.append(outs)
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    got = [buffers() for _ in batches]
+    torch.cuda.synchronize()
+    for i, qs in enumerate(batches):
+        with torch.cuda.stream(streams[i % 2]):
+            stack.step(qs, Kls, Vls, k, pos, got[i], lses)
+    torch.cuda.synchronize()
+    for x, y in zip(want, got):
+        assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(x, y))
+    fixed, outs = [q.clone() for q in batches[0]], buffers()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        stack.step(fixed, Kls, Vls, k, pos, outs, lses)
+    for i in (3, 1, 5):
+        for a, b in zip(fixed, batches[i]):
+            a.copy_(b)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(outs, want[i]))
+        eager = buffers()
+        stack.step(batches[2], Kls, Vls, k, pos, eager, lses)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(eager, want[2]))
