@@ -63,6 +63,10 @@ int launch_attend_docs(const Dims& dm, const DocsPlan& pl, const AttendArgs& a0,
                        int bank_keys_rotated, const float* loc_o, const float2* loc_ml, int n_loc, void* out, float* lse,
                        hipStream_t st);
 
+// Merge of many rows: n1 partials of rows [row0, row0 + rows) counted from row0 and n2 of all rows.
+int launch_merge2(int d, const float* o1, const float2* ml1, int n1, const float* o2, const float2* ml2, int n2, uint16_t* out,
+                  float* lse, long long row0, long long rows, hipStream_t st);
+
 // Shared-selection prefill: unnormalised partials of every (token, head, split) in the layout the
 // decode path writes, merged by the same attend_merge_kernel.
 int launch_attend_prefill_partial(const Dims& dm, const AttendPlan& pl, const AttendArgs& a,

@@ -756,6 +756,7 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
 // The (max, sum) pairs are loaded split-parallel and reduced through LDS so that no thread walks a
 // chain of dependent loads.
 constexpr int kMaxAttSplits = 256;
+constexpr long long kMergeWaves = 4096;
 
 template <int D>
 __global__ __launch_bounds__(D) void attend_merge_kernel(const float* __restrict__ part_o,
@@ -1091,6 +1092,10 @@ int launch_attend(const Dims& dm, const AttendPlan& pl, const void* q, int B, in
   }
   if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
   if (direct || pl.fused_merge) return MSA_OK;
+  // Rows enough for every wave slot of the chip: a wave each; fewer rows (of more partials) a workgroup each.
+  const long long rows = (long long)BM * dm.Hq;
+  if (rows >= kMergeWaves)
+    return launch_merge2(dm.d, a.part_o, a.part_ml, pl.n_splits, a.part_o, a.part_ml, 0, (uint16_t*)out, lse, 0, rows, st);
   if (dm.d == 128)
     hipLaunchKernelGGL(attend_merge_kernel<128>, dim3(BM * dm.Hq), dim3(128), 0, st,
                        (const float*)a.part_o, (const float2*)a.part_ml, (uint16_t*)out, lse,

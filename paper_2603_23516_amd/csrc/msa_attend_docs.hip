@@ -608,28 +608,44 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
 }
 
 // Partials of two kinds for every (token, head): n1 of its selected documents, tokens counted from tok0, and n2 of the
-// local context, all tokens.  One wave per (token, head), four per workgroup; a lane owns D / 64 adjacent outputs.
+// local context, all tokens.  One wave per (token, head), four per workgroup; a lane owns D / 64 adjacent outputs.  The first
+// eight partials are requested together with the (max, sum) pairs: where there are no more, a row is one round trip
+// (32000 rows of two partials, one workgroup each: 19.3 us, so 14).
 template <int D>
 __global__ __launch_bounds__(256) void attend_merge2_kernel(const float* __restrict__ o1, const float2* __restrict__ ml1,
                                                             int n1, const float* __restrict__ o2,
                                                             const float2* __restrict__ ml2, int n2, uint16_t* __restrict__ out,
                                                             float* __restrict__ lse, long long row0, long long rows) {
   constexpr int V = D / 64;
+  constexpr int U = 8;
   const int lane = threadIdx.x & 63;
-  const long long row = (long long)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const long long row = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (row >= rows) return;
   const int ns = n1 + n2;
   const float2* m1 = ml1 + row * n1;
   const float2* m2 = ml2 + (row0 + row) * n2;
+  typedef float vec_t __attribute__((ext_vector_type(V)));
+  const float* p1 = o1 + row * n1 * D + lane * V;
+  const float* p2 = o2 + (row0 + row) * n2 * D + lane * V;
+  vec_t v[U];
+  auto fetch = [&](int s0) {  // (past the end: the last one again)
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int s = s0 + u < ns ? s0 + u : ns - 1;
+      v[u] = *reinterpret_cast<const vec_t*>(s < n1 ? p1 + (long long)s * D : p2 + (long long)(s - n1) * D);
+    }
+  };
   float2 ml[4];  // 256 partials at most
-  float mx = -INFINITY;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int s = lane + 64 * i;
     ml[i] = make_float2(-INFINITY, 0.f);
     if (64 * i < ns && s < ns) ml[i] = s < n1 ? m1[s] : m2[s - n1];
-    mx = fmaxf(mx, ml[i].x);
   }
+  fetch(0);
+  float mx = -INFINITY;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) mx = fmaxf(mx, ml[i].x);
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
   float lsum = 0.f, w[4];
@@ -641,23 +657,14 @@ __global__ __launch_bounds__(256) void attend_merge2_kernel(const float* __restr
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
   float acc[V] = {};
-  typedef float vec_t __attribute__((ext_vector_type(V)));
-  const float* p1 = o1 + row * n1 * D + lane * V;
-  const float* p2 = o2 + (row0 + row) * n2 * D + lane * V;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     if (64 * i >= ns) break;
     const int top = ns - 64 * i < 64 ? ns - 64 * i : 64;
-    for (int j0 = 0; j0 < top; j0 += 8) {
-      vec_t v[8];
+    for (int j0 = 0; j0 < top; j0 += U) {
+      if (i + j0 > 0) fetch(64 * i + j0);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        int s = 64 * i + j0 + u;
-        s = s < ns ? s : ns - 1;
-        v[u] = *reinterpret_cast<const vec_t*>(s < n1 ? p1 + (long long)s * D : p2 + (long long)(s - n1) * D);
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
+      for (int u = 0; u < U; ++u) {
         if (j0 + u >= top) break;
         const float f = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w[i]), j0 + u));
 #pragma unroll
@@ -674,6 +681,14 @@ __global__ __launch_bounds__(256) void attend_merge2_kernel(const float* __restr
   else
     out[qh * D + lane] = (uint16_t)(pack_bf16(res[0], 0.f) & 0xffffu);
   if (lse != nullptr && lane == 0) lse[qh] = lsum > 0.f ? (mx + log2f(lsum)) * 0.6931471805599453f : -INFINITY;
+}
+
+int launch_merge2(int d, const float* o1, const float2* ml1, int n1, const float* o2, const float2* ml2, int n2, uint16_t* out,
+                  float* lse, long long row0, long long rows, hipStream_t st) {
+  const dim3 grid((unsigned)((rows + 3) / 4)), block(256);
+  if (d == 128) hipLaunchKernelGGL(attend_merge2_kernel<128>, grid, block, 0, st, o1, ml1, n1, o2, ml2, n2, out, lse, row0, rows);
+  else hipLaunchKernelGGL(attend_merge2_kernel<64>, grid, block, 0, st, o1, ml1, n1, o2, ml2, n2, out, lse, row0, rows);
+  return hipGetLastError() == hipSuccess ? MSA_OK : MSA_ERR_HIP;
 }
 
 // Bytes of the fixed buffers and of those that grow with the tokens of a window.
@@ -771,12 +786,13 @@ int launch_attend_docs(const Dims& dm, const DocsPlan& pl, const AttendArgs& a0,
     else hipLaunchKernelGGL((group_kernel<DD, false>), ggrid, dim3(kGroupThreads), 0, st, a, da, th); \
     if (bank_keys_rotated) hipLaunchKernelGGL((attend_docs_kernel<DD, false>), dim3((unsigned)wgs), dim3(256), 0, st, a, da, th); \
     else hipLaunchKernelGGL((attend_docs_kernel<DD, true>), dim3((unsigned)wgs), dim3(256), 0, st, a, da, th); \
-    hipLaunchKernelGGL(attend_merge2_kernel<DD>, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, da.part_o, da.part_ml, \
-                       a.k * pl.parts, loc_o, loc_ml, n_loc, (uint16_t*)out, lse, (long long)t0 * dm.Hq, rows); \
   } while (0)
     if (dm.d == 128) MSA_DOCS(128);
     else MSA_DOCS(64);
 #undef MSA_DOCS
+    const int rc = launch_merge2(dm.d, da.part_o, da.part_ml, a.k * pl.parts, loc_o, loc_ml, n_loc, (uint16_t*)out, lse,
+                                 (long long)t0 * dm.Hq, rows, st);
+    if (rc != MSA_OK) return rc;
   }
   profile_mark(dm, true, st);
   return hipGetLastError() == hipSuccess ? MSA_OK : MSA_ERR_HIP;
