@@ -520,3 +520,32 @@ def test_attention_document_by_document(N, Hkv, r, G, d, B, M, k, Lloc, scope, r
         assert (x - y).abs().max() <= 2.0 ** -7 * y.abs().max() + 1e-6
         assert (l2 - lse)[torch.isfinite(lse)].abs().max() <= 1e-4
     assert same >= 1 and other >= 1, (same, other)
+
+
+@pytest.mark.parametrize("scope", ["group", "all"])
+def test_attention_document_by_document_of_shared_selections(scope):
+    """One selection for all tokens of a batch row over keys stored rotated (the tiled kernel takes raw keys alone): every
+    document is shared by all of them; against the oracle and against tokens with copies of that selection."""
+    N, Hkv, r, G, d, B, M, k, Lloc = 50, 2, 4, 96, 128, 2, 64, 16, 64
+    say(f"by document, shared selections, {scope}")
+    S_ = 1 if scope == "all" else Hkv
+    scope_ = msa.MSA_SCOPE_ALL if scope == "all" else msa.MSA_SCOPE_GROUP
+    cfg = msa.MsaConfig(N, G, G, Hkv * r, Hkv, d, 1e6, bank_keys_rotated=1, token_pool=1, select_scope=scope_)
+    Kb, K = S.normal_bf16(58100, (N, Hkv, G, d))
+    Vb, V = S.normal_bf16(58101, (N, Hkv, G, d))
+    qb, q = S.normal_bf16(58102, (B, M, Hkv * r, d))
+    Klb, Kl = S.normal_bf16(58103, (B, Hkv, Lloc, d))
+    Vlb, Vl = S.normal_bf16(58104, (B, Hkv, Lloc, d))
+    idx = np.random.default_rng(58105).integers(0, N, (B, 1, S_, k)).astype(np.int32)
+    idx[:, :, :, 3] = -1
+    q_pos = np.tile(G + np.arange(M, dtype=np.int32), (B, 1))
+    tail = [dev(Klb), dev(Vlb), G, torch.from_numpy(q_pos).cuda()]
+    out, lse = msa.msa_sparse_attend(cfg, dev(qb), dev(Kb), dev(Vb), torch.from_numpy(idx).cuda(), *tail)
+    each = np.ascontiguousarray(np.broadcast_to(idx, (B, M, S_, k)))
+    out2, lse2 = msa.msa_sparse_attend(cfg.replace(token_pool=0), dev(qb), dev(Kb), dev(Vb), torch.from_numpy(each).cuda(), *tail)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int16), out2.view(torch.int16)) and torch.equal(lse, lse2)
+    oo, ol = O.sparse_attend(q, K, V, idx.astype(np.int64), Kl, Vl, G, q_pos, 1e6, mem_rotated=True)
+    go = out.float().cpu().numpy().astype(np.float64)
+    assert np.abs(go - oo).max() <= 2e-2 and np.linalg.norm(go - oo) <= 5e-3 * np.linalg.norm(oo)
+    assert np.abs(lse.cpu().numpy() - ol).max() <= 5e-3
