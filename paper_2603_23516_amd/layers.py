@@ -67,10 +67,13 @@ class LayerStack:
         self.ws_a = torch.empty(sparse_attend_workspace_bytes(self.acfg, B, M, k, Lloc), dtype=torch.uint8, device=device)
         self.s_route, self.s_attend = torch.cuda.Stream(device), torch.cuda.Stream(device)
         self.last = None   # the stream that the last step of the "hbm" tier was called on
-        # Attention beside the next layer's scan pays for its hand-over between streams only where that scan is long.  Four
-        # layers of 8 heads of 128, us per step on one stream / on two: index of 17 MB (5 queries, two layers) 62 / 88, 68 MB
-        # (16 queries) 266 / 274, 136 MB (8 queries) 225 / 210, 136 MB (one query) 205 / 192.
-        self.two_streams = n_layers > 1 and self.KR[0].numel() * 2 >= 100 << 20
+        # Attention beside the next layer's scan pays for its hand-over between streams where there are layers enough, the
+        # scan is long and the attention is more than a few workgroups; a scan of a GB has the memory to itself anyway.
+        # Layers of 8 heads of 128, us per step on one stream / on two: four layers with an index of 68 MB (16 queries) 266 /
+        # 274, 136 MB (8 queries) 225 / 210, 200 MB (8) 287 / 262, (2 queries) 261 / 302, 333 MB (8) 386 / 360; three of
+        # 136 MB 171 / 166, two of 268 MB 178 / 186, two of 1.6 GB 599 / 620.
+        index = self.KR[0].numel() * 2
+        self.two_streams = n_layers >= 4 and B * M >= 3 and 100 << 20 <= index <= 1 << 30
         self.ev_scored = [torch.cuda.Event() for _ in range(n_layers)]
         self.ev_fork, self.ev_join = torch.cuda.Event(), torch.cuda.Event()
         for ev in self.ev_scored + [self.ev_fork, self.ev_join]:
