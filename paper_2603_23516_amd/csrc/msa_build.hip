@@ -17,7 +17,8 @@ namespace msa {
 // RUN: eight waves take the eight chunks of half a tile (eight or sixteen chunks per document, every document full); their
 // pieces meet in LDS and leave as whole lines (128 bytes: piece c of eight keys) past the L2 (4.3 GB: 703 us with 16-byte
 // stores from every wave, 676).
-template <int D, int UB, bool RUN>
+// HUGE: chunks of 2^31 elements or more, whose offsets need 64 bits (a form of its own: half a percent elsewhere).
+template <int D, int UB, bool RUN, bool HUGE>
 __global__ __launch_bounds__(RUN ? 512 : 256) void build_routing_keys_kernel(
     const uint16_t* __restrict__ K, uint16_t* __restrict__ KR, float* __restrict__ inv_norm,
     const int32_t* __restrict__ lens, int doc_begin, long long n_chunks, int Hkv, int G, int P, int C,
@@ -55,8 +56,8 @@ __global__ __launch_bounds__(RUN ? 512 : 256) void build_routing_keys_kernel(
   const int iters = P / RPL;
   for (int it0 = 0; it0 < iters; it0 += UB) {
     uint4 v[UB];
-    const uint16_t* rp = src + (it0 * RPL + rowoff) * D + piece * 8;
-    if ((it0 + UB) * RPL <= n_rows) {  // wave-uniform: whole batch, no condition on a load
+    const uint16_t* rp = HUGE ? src + (long long)it0 * (RPL * D) + (rowoff * D + piece * 8) : src + (it0 * RPL + rowoff) * D + piece * 8;
+    if (HUGE ? UB * RPL <= n_rows - it0 * RPL : (it0 + UB) * RPL <= n_rows) {  // wave-uniform: whole batch, no condition on a load
 #pragma unroll
       for (int u = 0; u < UB; ++u) v[u] = load_stream16(rp + u * RPL * D);
     } else {
@@ -152,15 +153,18 @@ int launch_build(const Dims& dm, const void* K, int doc_begin, int doc_count, vo
     if (blocks > 0x7fffffffLL || (long long)doc_count * dm.Hkv > 0xffffffffLL) return MSA_ERR_UNSUPPORTED;
     int cshift = 0;
     while ((1 << cshift) < dm.C) ++cshift;
-    const bool run = dm.C >= 8 && dm.lens == nullptr;
+    const bool huge = (long long)dm.P * dm.d > 0x7fffffffLL;
+    const bool run = dm.C >= 8 && dm.lens == nullptr && !huge;
     dim3 grid((unsigned)(run ? blocks / 2 : blocks)), block(run ? 512 : 256);
     const int loads = dm.P / (512 / dm.d);  // of a chunk
-#define MSA_BUILD_AS(DD, UU, RR) \
-  hipLaunchKernelGGL((build_routing_keys_kernel<DD, UU, RR>), grid, block, 0, st, (const uint16_t*)K, (uint16_t*)KR, inv_norm, \
+#define MSA_BUILD_AS(DD, UU, RR, HH) \
+  hipLaunchKernelGGL((build_routing_keys_kernel<DD, UU, RR, HH>), grid, block, 0, st, (const uint16_t*)K, (uint16_t*)KR, inv_norm, \
                      dm.lens, doc_begin, n_chunks, dm.Hkv, dm.G, dm.P, dm.C, cshift, (long long)dm.tiles)
 #define MSA_BUILD(DD, UU) \
   do { \
-    if (run) MSA_BUILD_AS(DD, UU, true); else MSA_BUILD_AS(DD, UU, false); \
+    if (huge) MSA_BUILD_AS(DD, 16, false, true); \
+    else if (run) MSA_BUILD_AS(DD, UU, true, false); \
+    else MSA_BUILD_AS(DD, UU, false, false); \
   } while (0)
     if (dm.d == 128) {
       if (loads > 8) MSA_BUILD(128, 16); else MSA_BUILD(128, 8);

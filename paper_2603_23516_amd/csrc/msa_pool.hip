@@ -20,7 +20,10 @@ struct PoolTheta {
   float2 estep[64];  // (cos, sin)(RPL * theta_u), RPL = rows per wave-wide load
 };
 
-template <int D, bool ROT, int NB>
+// HUGE: chunks of 2^31 elements or more, whose offsets need 64 bits.  A form of its own, since in 64 bits the kernel loses 2 to
+// 3 % where a chunk is a single batch (4.3 GB in chunks of 32 rows of 128: the encoding 2286 us, 2322; 0.5 GB, 64 of 64: 276,
+// 285).
+template <int D, bool ROT, int NB, bool HUGE>
 __global__ __launch_bounds__(256) void pool_chunks_kernel(const uint16_t* __restrict__ X,
                                                           uint16_t* __restrict__ Xbar,
                                                           const int32_t* __restrict__ lens,
@@ -58,8 +61,8 @@ __global__ __launch_bounds__(256) void pool_chunks_kernel(const uint16_t* __rest
   // eight, 162 with four)
   uint4 v1[NB], v2[NB];
   auto load = [&](int it0) __attribute__((always_inline)) {
-    const uint16_t* rp = src + (it0 * RPL + rowoff) * D + pc * 8;
-    if ((it0 + NB) * RPL <= n_rows) {  // wave-uniform: whole batch, no condition on a load
+    const uint16_t* rp = HUGE ? src + (long long)it0 * (RPL * D) + (rowoff * D + pc * 8) : src + (it0 * RPL + rowoff) * D + pc * 8;
+    if (HUGE ? NB * RPL <= n_rows - it0 * RPL : (it0 + NB) * RPL <= n_rows) {  // wave-uniform: whole batch, no condition on a load
 #pragma unroll
       for (int u = 0; u < NB; ++u) {
         v1[u] = load_stream16(rp + u * RPL * D);
@@ -69,7 +72,7 @@ __global__ __launch_bounds__(256) void pool_chunks_kernel(const uint16_t* __rest
 #pragma unroll
       for (int u = 0; u < NB; ++u) {
         v1[u] = v2[u] = make_uint4(0, 0, 0, 0);
-        if ((it0 + u) * RPL + rowoff < n_rows) {
+        if (HUGE ? u * RPL + rowoff < n_rows - it0 * RPL : (it0 + u) * RPL + rowoff < n_rows) {
           v1[u] = load_stream16(rp + u * RPL * D);
           v2[u] = load_stream16(rp + u * RPL * D + D / 2);
         }
@@ -77,7 +80,7 @@ __global__ __launch_bounds__(256) void pool_chunks_kernel(const uint16_t* __rest
     }
   };
   // batches that hold tokens; they run from the last to the first (see below)
-  const int iters = n_rows > 0 ? __builtin_amdgcn_readfirstlane((n_rows + RPL - 1) / RPL) : 1;
+  const int iters = n_rows > 0 ? __builtin_amdgcn_readfirstlane(HUGE ? (n_rows - 1) / RPL + 1 : (n_rows + RPL - 1) / RPL) : 1;
   const int last0 = (iters - 1) / NB * NB;
   load(last0);  // on its way while the angles are worked out
   __shared__ float2 cs_s[ROT ? 8 : 1][64];
@@ -173,9 +176,14 @@ int launch_pool_kv(const Dims& dm, const void* K, const void* V, int doc_begin, 
     th.estep[u] = make_float2((float)cos(rpl * th.th[u]), (float)sin(rpl * th.th[u]));
   }
   dim3 grid((unsigned)blocks), block(256);
-#define MSA_POOL(DD, RR, BB, X, OUT, LENS_OUT) \
-  hipLaunchKernelGGL((pool_chunks_kernel<DD, RR, BB>), grid, block, 0, st, (const uint16_t*)X, (uint16_t*)OUT, dm.lens, \
+#define MSA_POOL_AS(DD, RR, BB, HH, X, OUT, LENS_OUT) \
+  hipLaunchKernelGGL((pool_chunks_kernel<DD, RR, BB, HH>), grid, block, 0, st, (const uint16_t*)X, (uint16_t*)OUT, dm.lens, \
                      LENS_OUT, doc_begin, n_pairs, dm.Hkv, dm.G, dm.P, dm.C, th)
+#define MSA_POOL(DD, RR, BB, X, OUT, LENS_OUT) \
+  do { \
+    if (huge) MSA_POOL_AS(DD, RR, 4, true, X, OUT, LENS_OUT); else MSA_POOL_AS(DD, RR, BB, false, X, OUT, LENS_OUT); \
+  } while (0)
+  const bool huge = (long long)dm.P * dm.d > 0x7fffffffLL;
   if (Kbar != nullptr) {
     if (dm.d == 128) MSA_POOL(128, true, 4, K, Kbar, pooled_lens);
     else MSA_POOL(64, true, 4, K, Kbar, pooled_lens);
@@ -192,6 +200,7 @@ int launch_pool_kv(const Dims& dm, const void* K, const void* V, int doc_begin, 
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
   }
 #undef MSA_POOL
+#undef MSA_POOL_AS
   return MSA_OK;
 }
 

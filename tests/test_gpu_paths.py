@@ -397,6 +397,33 @@ def test_routing_keys_by_runs(G, P, d, first, count):
     assert np.all(got[:, rest] == 7.0) and np.all(norm[:, rest] == 7.0)
 
 
+@pytest.mark.parametrize("d", [128, 64])
+def test_chunk_of_more_elements_than_an_int_counts(d):
+    """One document in one chunk of 2^31 elements and 4096 rows more, zero but for rows on both sides of the 2^31st
+    element: sums of integers, exact in fp32, and the mean rounded once (2^-8 of it).  The pooled keys likewise in the pairs
+    whose angle stays under 1e-5 over the whole chunk."""
+    half = 2 ** 31 // d
+    G = half + 4096
+    say(f"chunk of {G} rows of {d}")
+    cfg = msa.MsaConfig(1, G, G, 1, 1, d, 1e38)
+    X = torch.zeros((1, 1, G, d), dtype=torch.bfloat16, device="cuda")
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(57200)
+    for at, n in ((0, 40), (half - 24, 64), (G - 200, 200)):
+        X[0, 0, at:at + n] = torch.randint(1, 9, (n, d), generator=gen, device="cuda").to(torch.bfloat16)
+    want = sum(X[0, 0, i:i + (1 << 22)].float().sum(0).double() for i in range(0, G, 1 << 22)) / G
+    KR, inv = msa.msa_build_routing_keys(cfg, X)
+    Kbar, Vbar = msa.msa_pool_kv(cfg, X, X)
+    torch.cuda.synchronize()
+    still = [u for u in range(d) if 1e38 ** (-2.0 * (u % (d // 2)) / d) * G < 1e-5]
+    assert len(still) >= d // 2
+    assert ((Kbar.reshape(d).double() - want).abs() <= (2.0 ** -8 + 2e-5) * want)[still].all()
+    key = msa.untile_routing_keys(cfg, KR).reshape(-1, d)[0].double()
+    for got in (key, Vbar.reshape(d).double()):
+        assert ((got - want).abs() <= 2.0 ** -8 * want).all()
+    assert abs(float(inv.reshape(-1)[0]) * float(key.norm()) - 1) <= 2e-6
+
+
 # (N, Hkv, r, G, d, B, M, k, Lloc, scope, rotated): many (query, KV head) pairs in the decode kernel
 ATT_LINEAR = [
     (40, 8, 4, 512, 128, 20, 1, 18, 5, "group", 0),      # 160 pairs of 289 steps, three splits each
