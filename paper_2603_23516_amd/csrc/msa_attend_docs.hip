@@ -696,10 +696,18 @@ static size_t docs_fixed_bytes(const Dims& dm) {
   const size_t S = dm.scope_all ? 1 : dm.Hkv;
   return round_up256(S * dm.N * 8) + round_up256(S * dm.N * 4) + round_up256(S * 4);
 }
-static size_t docs_window_bytes(const Dims& dm, int k, int parts, size_t tokens) {
+static size_t docs_window_bytes(const Dims& dm, int k, int slots, size_t tokens) {  // slots: partials per (token, head)
   const size_t S = dm.scope_all ? 1 : dm.Hkv, e = S * tokens * k;
   return round_up256(tokens * dm.Hq * dm.d * 4) + round_up256(e * 16) + 2 * round_up256(e * 4) +
-         round_up256(tokens * dm.Hq * k * parts * dm.d * 4) + round_up256(tokens * dm.Hq * k * parts * 8);
+         round_up256(tokens * dm.Hq * slots * dm.d * 4) + round_up256(tokens * dm.Hq * slots * 8);
+}
+
+// Parts of a document where the items (at most one per token, slot and KV head) are few.
+static int docs_parts(const Dims& dm, long long BM, int k) {
+  const long long steps = dm.G / 32;
+  int parts = 1;
+  while (parts < 4 && 2 * parts * k <= 128 && BM * k * dm.Hkv * parts < kDocsItems && steps / (2 * parts) >= 4 && steps % (2 * parts) == 0) parts *= 2;
+  return parts;
 }
 
 // Where the documents are certain to be shared (twice as many pairs as documents) or the pairs are many, and the rows that
@@ -717,25 +725,28 @@ bool docs_path_applies(const Dims& dm, int B, int M, int k) {
 DocsPlan plan_docs(const Dims& dm, int B, int M, int k, size_t bytes) {
   DocsPlan p = {};
   const long long BM = (long long)B * M, steps = dm.G / 32;
-  // parts of a document where the items (at most one per token, slot and KV head) are few
-  long long parts = 1;
-  while (parts < 4 && 2 * parts * k <= 128 && BM * k * dm.Hkv * parts < kDocsItems && steps / (2 * parts) >= 4 && steps % (2 * parts) == 0) parts *= 2;
-  p.parts = (int)parts;
-  p.part_steps = (int)(steps / parts);
+  p.parts = docs_parts(dm, BM, k);
+  p.part_steps = (int)(steps / p.parts);
+  // Parts become fewer as k grows; the size to ask for is that of the most partials which a call of no more documents uses.
+  int slots = 0;
+  for (int kk = 1; kk <= k; ++kk) {
+    const int s = kk * docs_parts(dm, BM, kk);
+    slots = s > slots ? s : slots;
+  }
   const size_t fixed = docs_fixed_bytes(dm);
   // tokens whose partials fit: in all at most kDocsBytes, but 64 tokens at least
   size_t least = BM < 64 ? BM : 64;
   size_t window = kDocsBytes;
-  const size_t whole = docs_window_bytes(dm, k, p.parts, BM), few = docs_window_bytes(dm, k, p.parts, least);
+  const size_t whole = docs_window_bytes(dm, k, slots, BM), few = docs_window_bytes(dm, k, slots, least);
   if (whole < window) window = whole;
   if (few > window) window = few;
   p.bytes = fixed + window;
   const size_t have = bytes < p.bytes ? bytes : p.bytes;
-  if (have < fixed + few) return p;  // tokens = 0: the workspace is too small for this path
+  if (have < fixed + docs_window_bytes(dm, k, k * p.parts, least)) return p;  // tokens = 0: the workspace is too small for this path
   long long lo = least, hi = BM;
   while (lo < hi) {
     const long long mid = (lo + hi + 1) / 2;
-    if (fixed + docs_window_bytes(dm, k, p.parts, mid) <= have)
+    if (fixed + docs_window_bytes(dm, k, k * p.parts, mid) <= have)
       lo = mid;
     else
       hi = mid - 1;

@@ -251,6 +251,24 @@ def test_attention_workspace_serves_smaller_calls(lib, n_kv_heads, r, d, G, rota
             assert by_B == sorted(by_B), (M, L)
 
 
+@pytest.mark.parametrize("n_kv_heads,r,d,rotated,scope", [(8, 4, 128, 0, 0), (1, 8, 128, 0, 0), (2, 4, 128, 0, 1), (8, 1, 64, 0, 0),
+                                                          (2, 2, 64, 1, 0)])
+def test_attention_workspace_of_shared_documents_serves_smaller_calls(lib, n_kv_heads, r, d, rotated, scope):
+    """The same where tokens are more than the documents can serve apart, so that documents are taken one by one, in parts
+    while they are few: no size falls from one selected document to the next, or with the local context."""
+    size = msa.sparse_attend_workspace_bytes
+    for N in (33, 64, 100, 200):
+        for G in (256, 512, 1024, 2048):
+            c = _cfg(n_docs=N, doc_len=G, chunk=G, n_q_heads=n_kv_heads * r, n_kv_heads=n_kv_heads, head_dim=d,
+                     bank_keys_rotated=rotated, select_scope=scope)
+            for B, M in ((1, 16), (1, 17), (2, 16), (1, 40), (1, 64), (3, 50), (1, 300)):
+                by_k = [size(c, B, M, k, 512) for k in range(1, 65)]
+                assert by_k == sorted(by_k), (N, G, B, M)
+                for k in (8, 16, 33, 64):
+                    by_L = [size(c, B, M, k, L) for L in (0, 31, 32, 100, 512, 1000, 4096)]
+                    assert by_L == sorted(by_L), (N, G, B, M, k)
+
+
 def test_layers_step_checks_every_layer_first(lib):
     """A layer that routing or attention would refuse is refused before anything is enqueued, wherever it stands: no device
     is needed to see its status."""
