@@ -136,8 +136,9 @@ uint64_t msa_pooled_bank_bytes(uint64_t tokens, uint32_t chunk, uint32_t heads, 
  * Where many tokens bring many selections of their own it also asks for the buffers of the path that takes them document
  * by document: up to 256 MiB (64 tokens' partials if those are more) and 12 bytes per document and selection list.  A
  * workspace without them is accepted too; it is then used for fewer tokens at a time, or the tokens are taken one by one.
- * It is the same with and without doc_lens and does not fall as k or Lloc grows (nor, for M < 8, as B does): sized for
- * the longest local context and the most documents of a program it serves every shorter call. */
+ * Every size from the one without these extra buffers on is accepted, every smaller one refused (MSA_ERR_WORKSPACE).
+ * The attention workspace is the same with and without doc_lens and does not fall as k or Lloc grows (nor, for M < 8, as
+ * B does): sized for the longest local context and the most documents of a program it serves every shorter call. */
 size_t msa_score_topk_workspace_bytes(const msa_config_t* cfg, int32_t B, int32_t M, int32_t k);
 size_t msa_sparse_attend_workspace_bytes(const msa_config_t* cfg, int32_t B, int32_t M, int32_t k,
                                          int32_t Lloc);

@@ -105,13 +105,8 @@ static int scratch_on_current_device(void** out) {
   return MSA_OK;
 }
 
-// A workspace of the least size serves every call, by a plan with fewer buffers than the size asked for holds (programs that
-// were built with smaller sizes); a size that misses what is asked for by less than its granule is a miscounted one.
-static bool too_small(size_t have, size_t least, size_t asked) {
-  return have < least || (have < asked && asked - have < 256);
-}
-
-// Everything that msa_score_topk refuses, and its plan.
+// Everything that msa_score_topk refuses, and its plan.  (A workspace of the least size serves every call, by a plan with fewer
+// buffers than the size asked for holds.)
 static int check_score(const msa_config_t* cfg, const void* q_route, int32_t B, int32_t M, const void* KR,
                        const float* inv_norm, int32_t k, const int32_t* out_idx, const float* out_score,
                        const void* workspace, size_t workspace_bytes, Dims* dm, ScorePlan* pl) {
@@ -127,7 +122,7 @@ static int check_score(const msa_config_t* cfg, const void* q_route, int32_t B, 
       misaligned(out_score) || misaligned(workspace))
     return MSA_ERR_MISALIGNED;
   *pl = plan_score(*dm, B * M, k, workspace_bytes);
-  return too_small(workspace_bytes, pl->ws_bytes, pl->ws_best) ? MSA_ERR_WORKSPACE : MSA_OK;
+  return workspace_bytes < pl->ws_bytes ? MSA_ERR_WORKSPACE : MSA_OK;
 }
 
 // The same for msa_sparse_attend.
@@ -151,7 +146,7 @@ static int check_attend(const msa_config_t* cfg, const void* q, int32_t B, int32
       misaligned(workspace) || misaligned4(dm->lens))
     return MSA_ERR_MISALIGNED;
   *pl = plan_attend(*dm, B, M, k, Lloc, cfg->bank_keys_rotated, workspace_bytes);
-  return too_small(workspace_bytes, pl->ws_bytes, pl->ws_best) ? MSA_ERR_WORKSPACE : MSA_OK;
+  return workspace_bytes < pl->ws_bytes ? MSA_ERR_WORKSPACE : MSA_OK;
 }
 
 }  // namespace msa

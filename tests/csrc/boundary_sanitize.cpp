@@ -24,12 +24,32 @@ static msa_config_t cfg(int32_t N, int32_t G, int32_t P, int32_t Hq, int32_t Hkv
   return c;
 }
 
+// The workspace limit of a request: `status` gives its status with so many bytes, and `asked` are accepted.  Where fewer are
+// accepted too, the limit is the least size of the plans (a multiple of 256), and every size from there on is accepted.
+template <class F>
+static size_t workspace_limit(size_t asked, F status) {
+  if (status(asked - 1) == MSA_ERR_WORKSPACE) return asked;
+  size_t no = 0, yes = asked - 1;
+  CHECK(status(no) == MSA_ERR_WORKSPACE);
+  while (yes - no > 1) {
+    const size_t mid = no + (yes - no) / 2;
+    (status(mid) == MSA_ERR_WORKSPACE ? no : yes) = mid;
+  }
+  CHECK(yes % 256 == 0);
+  for (size_t less : {(size_t)1, (size_t)255, (size_t)256, yes / 2})
+    if (less <= yes) CHECK(status(yes - less) == MSA_ERR_WORKSPACE);
+  for (size_t more : {yes + 1, yes + 255, yes + 256, yes + (asked - yes) / 2, asked - 257, asked - 256, asked - 255, asked - 2})
+    if (more >= yes && more < asked) CHECK(status(more) == MSA_ERR_HIP);
+  return yes;
+}
+
 int main() {
   setenv("HIP_VISIBLE_DEVICES", "-1", 1);
   setenv("ROCR_VISIBLE_DEVICES", "", 1);
   void* p = reinterpret_cast<void*>(0x10000);
   const size_t big = ~(size_t)0 >> 1;
 
+  int below_s = 0, below = 0;  // requests that accept less than they ask for
   // ---- sizes at the limits: N*C just below 2^31 keys per head, B*M = 2^20 query tokens, k = 64 ----
   const int32_t Ns[] = {1, 2, 15, 17, 97656, (1 << 28) - 1, 0x7fffffff / 16};
   const int32_t BMs[][2] = {{1, 1}, {8, 1}, {33, 1}, {1, 2048}, {1 << 10, 1 << 10}, {1, 1 << 20}, {65535, 1}};
@@ -58,11 +78,18 @@ int main() {
                 // a valid request reaches the launch stage and fails there (no device code, no device)
                 const int rc = msa_score_topk(&c, p, bm[0], bm[1], p, (const float*)p, k, (int32_t*)p, (float*)p, p, big, nullptr);
                 CHECK(rc == MSA_ERR_HIP);
-                CHECK(msa_score_topk(&c, p, bm[0], bm[1], p, (const float*)p, k, (int32_t*)p, (float*)p, p, ws - 1, nullptr) == MSA_ERR_WORKSPACE);
+                const size_t least = workspace_limit(ws, [&](size_t bytes) {
+                  return msa_score_topk(&c, p, bm[0], bm[1], p, (const float*)p, k, (int32_t*)p, (float*)p, p, bytes, nullptr);
+                });
+                // (candidate lists, where one selection for all heads is taken from a bank in several segments)
+                CHECK(least == ws || (scope == MSA_SCOPE_ALL && (int64_t)bm[0] * bm[1] > 32 && C == 8 && d == 128));
+                CHECK((unsigned __int128)least >= lo);
+                below_s += least < ws;
                 const int rn = msa_score_topk_noalloc(&c, p, bm[0], bm[1], p, (const float*)p, k, (int32_t*)p, (float*)p, nullptr);
                 CHECK(rn == (ws > msa_noalloc_scratch_bytes() ? MSA_ERR_WORKSPACE : MSA_ERR_HIP));
               }
           }
+  CHECK(below_s > 0);
   // ---- attention plans: long documents, many tokens, the largest local context -------------------
   for (int32_t G : {32, 512, 1 << 20})
     for (int32_t Lloc : {0, 1, 2048, (1 << 24) - 1024})
@@ -78,9 +105,16 @@ int main() {
             const int rc = msa_sparse_attend(&c, p, bm[0], bm[1], p, p, (const int32_t*)p, k, p, p, Lloc, 512, (const int32_t*)p, p,
                                              (float*)p, p, big, nullptr);
             CHECK(rc == MSA_ERR_HIP);
-            CHECK(msa_sparse_attend(&c, p, bm[0], bm[1], p, p, (const int32_t*)p, k, p, p, Lloc, 512, (const int32_t*)p, p,
-                                    (float*)p, p, ws - 1, nullptr) == MSA_ERR_WORKSPACE);
+            const size_t least = workspace_limit(ws, [&](size_t bytes) {
+              return msa_sparse_attend(&c, p, bm[0], bm[1], p, p, (const int32_t*)p, k, p, p, Lloc, 512, (const int32_t*)p, p,
+                                       (float*)p, p, bytes, nullptr);
+            });
+            // (buffers of the path that takes many tokens' own selections document by document)
+            CHECK(least == ws || (pool == 0 && bm[1] >= 16 && Lloc >= 32));
+            CHECK((unsigned __int128)least >= (unsigned __int128)bm[0] * bm[1] * 32 * 128 * 4);
+            below += least < ws;
           }
+  CHECK(below > 0);
   // pooled bank with short stored-rotated documents
   {
     msa_config_t c = cfg(1 << 24, 8, 8, 32, 8, 128);
