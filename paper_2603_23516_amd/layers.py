@@ -3,18 +3,19 @@
 Section 3.2.1 applies routing in the latter half of the model's layers; Section 3.4.2 keeps, for every routed layer,
 the routing keys in device memory and the pooled content bank (K-bar, V-bar) either in device memory or, tiered, in
 host DRAM from which the selected documents are fetched.  A LayerStack holds those per-layer banks and runs, for one
-batch of query tokens, score + top-k -> (fetch) -> attention in every layer.  Scoring runs on one stream and fetch +
-attention on another: layer l + 1 is routed while layer l's winners are still being fetched and attended (the
-layers' queries are inputs here; in a model they come out of the layer below, which orders the streams the same
-way through events).
+batch of query tokens, score + top-k -> (fetch) -> attention in every layer.  Where the banks are in device memory a step
+runs on the caller's stream, its attention on a second one where that pays; with host banks scoring runs on one stream
+and fetch + attention on another.  With two streams layer l + 1 is routed while layer l's winners are still being fetched
+and attended (the layers' queries are inputs here; in a model they come out of the layer below, which orders the streams
+the same way through events).
 
 Orchestration only: every step of the path runs in the library's kernels.
 """
 import torch
 
-from . import (MsaConfig, msa_build_routing_keys, msa_fetch_selected, msa_layers_step, msa_pool_kv, msa_score_topk,
-               msa_sparse_attend, score_topk_workspace_bytes, sparse_attend_workspace_bytes, alloc_routing_index,
-               fetch_slots)
+from . import (MSA_ERR_HIP, MsaConfig, MsaError, msa_build_routing_keys, msa_fetch_selected, msa_layers_step,
+               msa_pool_kv, msa_score_topk, msa_sparse_attend, score_topk_workspace_bytes, sparse_attend_workspace_bytes,
+               alloc_routing_index, fetch_slots)
 
 
 class LayerStack:
@@ -65,8 +66,11 @@ class LayerStack:
             self.idx_stage = torch.empty_like(self.idx[0])
             self.acfg = self.pcfg.replace(n_docs=n_slots)
         self.ws_a = torch.empty(sparse_attend_workspace_bytes(self.acfg, B, M, k, Lloc), dtype=torch.uint8, device=device)
+        # (The "hbm" tier routes on the caller's stream.  s_route is made, and used once below, all the same: the four hardware
+        # queues go round the streams as they are first used, and an s_attend on the caller's queue runs no work beside it.
+        # Four layers of 197 MB, 12 queries, the sixth stack of a program: 293 us with the pair, 350 with s_attend alone, 317 on
+        # one stream.)
         self.s_route, self.s_attend = torch.cuda.Stream(device), torch.cuda.Stream(device)
-        self.last = None   # the stream that the last step of the "hbm" tier was called on
         # Attention beside the next layer's scan pays for its hand-over between streams where there are layers enough, the
         # scan is long and the attention is more than a few workgroups; a scan of a GB has the memory to itself anyway.
         # Layers of 8 heads of 128, us per step on one stream / on two: four layers with an index of 68 MB (16 queries) 266 /
@@ -74,9 +78,10 @@ class LayerStack:
         # 136 MB 171 / 166, two of 268 MB 178 / 186, two of 1.6 GB 599 / 620.
         index = self.KR[0].numel() * 2
         self.two_streams = n_layers >= 4 and B * M >= 3 and 100 << 20 <= index <= 1 << 30
+        self.last_id = None   # torch's number of the stream that the last step of the "hbm" tier was called on
         self.ev_scored = [torch.cuda.Event() for _ in range(n_layers)]
-        self.ev_fork, self.ev_join = torch.cuda.Event(), torch.cuda.Event()
-        for ev in self.ev_scored + [self.ev_fork, self.ev_join]:
+        self.ev_fork, self.ev_join, self.ev_captured = torch.cuda.Event(), torch.cuda.Event(), torch.cuda.Event()
+        for ev in self.ev_scored + [self.ev_fork, self.ev_join, self.ev_captured]:
             ev.record(self.s_route)   # an event exists from its first record on
 
     # ---- offline stage (Section 3.4.1, Stage 1), one layer at a time; K and V may be the same buffer refilled ----
@@ -109,28 +114,39 @@ class LayerStack:
     def step(self, qs, Klocs, Vlocs, pos0, q_pos, outs, lses, overlap=True):
         """qs[l] bf16 [B][M][Hq][d]: the routing/attention query of layer l; Klocs[l], Vlocs[l] its local cache;
         outs[l], lses[l] receive its attention output (None: not wanted).  overlap=False runs everything on one stream.
-        One host thread at a time: the stack's workspaces, selections and events are shared by its steps."""
-        s_r = self.s_route
-        s_a = self.s_attend if overlap else self.s_route
+        One host thread at a time: the stack's workspaces, selections and events are shared by its steps.  Steps of the
+        "hbm" tier from different streams follow each other; replays of a captured step are ordered by whoever replays it."""
         cur = torch.cuda.current_stream(self.dev)
         if self.tier == "hbm":
             # Routing runs on the caller's stream: handed to a stream of its own and joined again, small steps waited more
             # than they worked (two layers, 1000 documents, 5 queries 87 us -> 62; four, 256 documents, 2 queries 141 -> 95).
-            # Steps from different streams follow each other all the same, since they share the workspaces.
-            if not torch.cuda.is_current_stream_capturing():
-                if self.last is not None and self.last != cur:
-                    cur.wait_stream(self.last)
-                self.last = cur
-            s_r, s_a = cur, self.s_attend if overlap and self.two_streams else cur
+            # Steps from different streams follow each other all the same, since they share the workspaces: each waits for
+            # the event at the end of the step before (nothing else that its stream holds, and no stream is kept).
+            capturing = torch.cuda.is_current_stream_capturing()
+            join = self.ev_captured if capturing else self.ev_join
+            if not capturing:
+                # the same stream again has the end of that step ahead of it (a second wait is 4 us with two streams); but one
+                # that is not torch's own may be a new one in the place of one that was destroyed
+                own = cur.cuda_stream == 0 or cur.stream_id != cur.cuda_stream
+                if not own or cur.stream_id != self.last_id:
+                    cur.wait_event(self.ev_join)
+                self.last_id = cur.stream_id if own else None
+            s_a = self.s_attend if overlap and self.two_streams else cur
             # the whole step in one native call: as single calls from here the host was the bound of small steps (four
             # layers, 557 documents, 5 streams: 223 us -> 153; two layers, 956 documents, 2 streams: 141 -> 93)
-            msa_layers_step(self.cfg, self.acfg,
-                            [(qs[l], self.KR[l], self.inv[l], self.idx[l], self.val[l], self.Kbar[l], self.Vbar[l],
-                              Klocs[l], Vlocs[l], torch.empty_like(qs[l]) if outs[l] is None else outs[l], lses[l],
-                              self.ev_scored[l]) for l in range(self.L)],
-                            self.k, pos0, q_pos, self.ws_s, self.ws_a, cur, s_r, s_a,
-                            self.ev_fork, self.ev_join)
+            try:
+                msa_layers_step(self.cfg, self.acfg,
+                                [(qs[l], self.KR[l], self.inv[l], self.idx[l], self.val[l], self.Kbar[l], self.Vbar[l],
+                                  Klocs[l], Vlocs[l], torch.empty_like(qs[l]) if outs[l] is None else outs[l], lses[l],
+                                  self.ev_scored[l]) for l in range(self.L)],
+                                self.k, pos0, q_pos, self.ws_s, self.ws_a, cur, cur, s_a, self.ev_fork, join)
+            except MsaError as e:
+                if e.status == MSA_ERR_HIP and not capturing:   # part of the step may run: the caller's stream awaits it
+                    join.record(cur)
+                raise
             return
+        s_r = self.s_route
+        s_a = self.s_attend if overlap else s_r
         s_r.wait_stream(cur)
         if overlap:
             s_a.wait_stream(cur)

@@ -170,3 +170,81 @@ def test_steps_from_several_streams_and_a_graph(two):
         stack.step(batches[2], Kls, Vls, k, pos, eager, lses)
         torch.cuda.synchronize()
         assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(eager, want[2]))
+
+
+def small_stack(two):
+    L, N, Hkv, r, G, d, P, B, k, Lloc = 2, 500, 2, 2, 64, 64, 32, 3, 4, 40
+    stack = LayerStack(msa.MsaConfig(N, G, P, Hkv * r, Hkv, d, 1e4), L, B, 1, k, Lloc)
+    stack.two_streams = two
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(98500)
+
+    def rnd(*shape):
+        return torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+    for l in range(L):
+        stack.set_layer_keys(l, rnd(N, Hkv, G, d))
+        stack.set_layer_values(l, rnd(N, Hkv, G, d))
+    qs, Kls, Vls = ([rnd(*x) for _ in range(L)] for x in ((B, 1, Hkv * r, d), (B, Hkv, Lloc, d), (B, Hkv, Lloc, d)))
+    outs = [torch.zeros_like(q) for q in qs]
+    args = (qs, Kls, Vls, k, torch.full((B, 1), k + Lloc - 1, dtype=torch.int32, device="cuda"), outs, [None] * L)
+    torch.cuda.synchronize()
+    return stack, args
+
+
+def apart():
+    """Two streams that run beside each other (streams share a few hardware queues)."""
+    x = torch.zeros(1, device="cuda")
+    first = torch.cuda.Stream()
+    for other in [torch.cuda.Stream() for _ in range(8)]:
+        torch.cuda.synchronize()
+        with torch.cuda.stream(first):
+            torch.cuda._sleep(200_000_000)
+        with torch.cuda.stream(other):
+            x.add_(1)
+        other.synchronize()
+        if not first.query():
+            torch.cuda.synchronize()
+            return first, other
+    pytest.skip("no two streams run beside each other here")
+
+
+@pytest.mark.parametrize("two", [False, True])
+def test_step_waits_for_the_step_before_alone(two):
+    """Work that a caller put on its stream behind a step does not hold up the next step from another stream."""
+    stack, args = small_stack(two)
+    first, other = apart()
+    stack.step(*args)
+    torch.cuda.synchronize()
+    want = [o.clone() for o in args[5]]
+    with torch.cuda.stream(first):
+        stack.step(*args)
+        torch.cuda._sleep(1_000_000_000)   # half a second
+    with torch.cuda.stream(other):
+        stack.step(*args)
+    other.synchronize()
+    assert not first.query()
+    torch.cuda.synchronize()
+    assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(want, args[5]))
+
+
+def test_step_after_its_last_stream_was_destroyed():
+    """The stack keeps no stream of its callers: one that its owner has destroyed is not touched again."""
+    import ctypes
+    loaded = {line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64" in line}
+    assert len(loaded) == 1
+    hip = ctypes.CDLL(loaded.pop())   # the runtime that torch uses, not another copy of it
+    stack, args = small_stack(False)
+    stack.step(*args)
+    torch.cuda.synchronize()
+    want = [o.clone() for o in args[5]]
+    for _ in range(3):
+        handle = ctypes.c_void_p()
+        assert hip.hipStreamCreate(ctypes.byref(handle)) == 0
+        with torch.cuda.stream(torch.cuda.ExternalStream(handle.value)):
+            stack.step(*args)
+        torch.cuda.synchronize()
+        assert hip.hipStreamDestroy(handle) == 0
+        assert not any(isinstance(v, torch.cuda.Stream) and v.cuda_stream == handle.value for v in vars(stack).values())
+        stack.step(*args)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a.view(torch.int16), b.view(torch.int16)) for a, b in zip(want, args[5]))
