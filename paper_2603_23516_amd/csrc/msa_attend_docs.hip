@@ -40,6 +40,10 @@ template <int D, bool LDS>  // LDS: a document's counters fit there (N <= kLdsDo
 __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
   constexpr int HALF = D / 2;
   const int tid = threadIdx.x;
+  auto selection = [&](int t, int s) {  // of a token of the window: where list s begins in idx
+    t += da.tok0;
+    return ((long long)(a.idx_rows_per_b == 1 ? t / a.M : t) * a.idx_sel + s) * a.k;
+  };
   if ((int)blockIdx.x >= a.idx_sel) {  // ---- queries of up to four tokens
     __shared__ float2 cs[4][HALF];
     const int t0 = ((int)blockIdx.x - a.idx_sel) * 4;
@@ -48,6 +52,15 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, Docs
       cs[tid / HALF][tid % HALF] = cis_pos(t < da.n_tok ? a.q_pos[da.tok0 + t] : 0, th.th[tid % HALF]);
     }
     __syncthreads();
+    // empty partials where a slot holds no document: the maximum alone, the merge does not look at their outputs
+    for (int x = tid; x < 4 * a.Hq * a.k; x += kGroupThreads) {
+      const int slot = x % a.k, row = x / a.k, t = t0 + row / a.Hq;
+      if (t >= da.n_tok) break;
+      const int d = a.idx[selection(t, a.idx_sel == 1 ? 0 : row % a.Hq / a.r) + slot];
+      if (d >= 0 && d < a.N) continue;
+      float2* ml = da.part_ml + ((long long)t0 * a.Hq * a.k + x) * da.parts;
+      for (int p = 0; p < da.parts; ++p) ml[p] = make_float2(-INFINITY, 0.f);
+    }
     constexpr int PPH = HALF / 8;  // 16-byte pieces per half row
     for (int e = tid; e < 4 * a.Hq * PPH; e += kGroupThreads) {
       const int pc = e % PPH, head = e / PPH % a.Hq, t4 = e / PPH / a.Hq;
@@ -97,9 +110,7 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, Docs
   int4* const items = da.items + (long long)s * da.cap;
   auto doc_of = [&](int e) {  // -1: past the end, a pad, or no document of the bank
     if (e >= E) return -1;
-    const int t = da.tok0 + e / a.k;
-    const long long row = a.idx_rows_per_b == 1 ? t / a.M : t;
-    const int d = a.idx[(row * a.idx_sel + s) * a.k + e % a.k];
+    const int d = a.idx[selection(e / a.k, s) + e % a.k];
     return d >= 0 && d < a.N ? d : -1;
   };
   auto phase = [&]() {  // stores and atomics of the phase are complete for everyone
@@ -196,14 +207,6 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, Docs
         if (c[i] > 0) {
           const int left = c[i] - rk[i];
           items[(int)(b[i] >> 32) + rk[i] / T] = make_int4(d[i], at, left < T ? left : T, c[i] > T ? 0 : 1);
-        }
-      } else {  // no document: empty partials of every head that uses this list
-        const int heads = a.Hq / a.idx_sel;
-        for (int h = 0; h < heads * da.parts; ++h) {
-          const long long ph = ((long long)(e / a.k) * a.Hq + s * heads + h / da.parts) * (a.k * da.parts) +
-                               e % a.k * da.parts + h % da.parts;
-          da.part_ml[ph] = make_float2(-INFINITY, 0.f);
-          for (int u = 0; u < D; u += 4) *reinterpret_cast<float4*>(da.part_o + ph * D + u) = make_float4(0.f, 0.f, 0.f, 0.f);
         }
       }
     }
@@ -651,8 +654,9 @@ __global__ __launch_bounds__(256) void attend_merge2_kernel(const float* __restr
   float lsum = 0.f, w[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    w[i] = (ml[i].x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(ml[i].x - mx);
-    lsum += w[i] * ml[i].y;
+    const bool empty = ml[i].x == -INFINITY;  // (its sum and outputs may be anything)
+    w[i] = empty ? -1.f : __builtin_amdgcn_exp2f(ml[i].x - mx);
+    lsum += empty ? 0.f : w[i] * ml[i].y;
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
@@ -667,6 +671,7 @@ __global__ __launch_bounds__(256) void attend_merge2_kernel(const float* __restr
       for (int u = 0; u < U; ++u) {
         if (j0 + u >= top) break;
         const float f = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(w[i]), j0 + u));
+        if (f < 0.f) continue;  // wave-uniform
 #pragma unroll
         for (int c = 0; c < V; ++c) acc[c] += f * v[u][c];
       }

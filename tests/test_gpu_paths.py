@@ -576,3 +576,46 @@ def test_attention_document_by_document_of_shared_selections(scope):
     go = out.float().cpu().numpy().astype(np.float64)
     assert np.abs(go - oo).max() <= 2e-2 and np.linalg.norm(go - oo) <= 5e-3 * np.linalg.norm(oo)
     assert np.abs(lse.cpu().numpy() - ol).max() <= 5e-3
+
+
+@pytest.mark.parametrize("scope,r,k", [("all", 4, 8), ("group", 4, 16), ("group", 8, 8)])
+def test_attention_document_by_document_of_pads(scope, r, k):
+    """Selections without a document: the local context alone, against the oracle, from a workspace full of NaN; and sooner
+    than with documents (128 documents shared by all; pads that were written out as empty partials by the one sorting
+    workgroup of a list took up to five times as long)."""
+    N, Hkv, G, d, B, M, Lloc = 128, 8, 512, 128, 1, 100, 100
+    say(f"by document, pads, {scope} r={r} k={k}")
+    S_ = 1 if scope == "all" else Hkv
+    cfg = msa.MsaConfig(N, G, G, Hkv * r, Hkv, d, 1e6, select_scope=msa.MSA_SCOPE_ALL if scope == "all" else msa.MSA_SCOPE_GROUP)
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(58200)
+    K, V = (torch.randn((N, Hkv, G, d), generator=gen, device="cuda").to(torch.bfloat16) for _ in range(2))
+    qb, q = S.normal_bf16(58201, (B, M, Hkv * r, d))
+    Klb, Kl = S.normal_bf16(58202, (B, Hkv, Lloc, d))
+    Vlb, Vl = S.normal_bf16(58203, (B, Hkv, Lloc, d))
+    q_pos = (G + np.arange(M, dtype=np.int32)).reshape(B, M)
+    some = torch.rand((B, M, S_, N), generator=gen, device="cuda").topk(k, dim=-1).indices.to(torch.int32)
+    none = torch.full_like(some, -1)
+    none[:, :, :, ::2] = N
+    ws = torch.empty(msa.sparse_attend_workspace_bytes(cfg, B, M, k, Lloc), dtype=torch.uint8, device="cuda")
+    dq, dKl, dVl, dpos = dev(qb), dev(Klb), dev(Vlb), torch.from_numpy(q_pos).cuda()
+    took = []
+    for idx in (some, none):
+        ws.fill_(0xFF)
+        out, lse = msa.msa_sparse_attend(cfg, dq, K, V, idx, dKl, dVl, G, dpos, workspace=ws)
+        best = 1e9
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(10):
+                msa.msa_sparse_attend(cfg, dq, K, V, idx, dKl, dVl, G, dpos, out, lse, ws)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b))
+        took.append(best)
+    oo, ol = O.sparse_attend(q, np.zeros((1, Hkv, G, d)), np.zeros((1, Hkv, G, d)), np.full((B, M, S_, k), -1, dtype=np.int64), Kl, Vl,
+                             G, q_pos, 1e6)
+    go = out.float().cpu().numpy().astype(np.float64)
+    assert np.abs(go - oo).max() <= 2e-2 and np.linalg.norm(go - oo) <= 5e-3 * np.linalg.norm(oo)
+    assert np.abs(lse.cpu().numpy() - ol).max() <= 5e-3
+    assert took[1] < took[0], took
