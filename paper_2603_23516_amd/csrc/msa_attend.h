@@ -47,25 +47,30 @@ struct AttendArgs {
 struct DocsArgs {
   unsigned long long* base;  // [S][N] first item << 32 | first entry of a document
   int* cnt;                  // [S][N] pairs of a document
-  int* n_items;              // [S]
+  int* n_items;              // [S], and [S] 1 where the list is taken in chains
   uint4* qrot;               // [tokens][Hq][D/8][hi, lo] rotated, scaled queries, 8 bf16 each
-  int4* items;               // [S][cap] (document, first entry, tokens, 1 if the document's only item)
-  int* entries;              // [S][cap] token * k + slot, by document
-  int* rank;                 // [S][cap] place of a pair among its document's
+  int4* items;               // [S][cap] (document, first entry, tokens, 1 if the document's only item) or, a chain,
+                             // (token << 6 | number, first entry, documents, 2; the token's last 3)
+  int* entries;              // [S][cap] token << 6 | slot, by document; of a chain its documents
+  int* rank;                 // [S][tokens << kshift] place of a pair among its document's
   float* part_o;             // [tokens][Hq][k][parts][D] unnormalised partial outputs
   float2* part_ml;           // [tokens][Hq][k][parts]    (running max in log2 units, sum)
   int cap;                   // entries of a list at most
   int tile_tok;              // tokens per item at most, 16 / r
   int parts, part_steps;     // parts of a document's rows, 32-row steps of each
-  int tok0, n_tok;           // this window
+  int kshift;                // 2^kshift >= k
+  int chain, n_chains;       // documents of a chain, chains of a token at most
+  int tok0, n_tok, n_all;    // this window; tokens of the call
 };
 int launch_attend_docs(const Dims& dm, const DocsPlan& pl, const AttendArgs& a0, const RopeTheta& th, int BM, void* ws,
                        int bank_keys_rotated, const float* loc_o, const float2* loc_ml, int n_loc, void* out, float* lse,
                        hipStream_t st);
 
-// Merge of many rows: n1 partials of rows [row0, row0 + rows) counted from row0 and n2 of all rows.
+// Merge of many rows: n1 partials of rows [row0, row0 + rows) counted from row0 and n2 of all rows.  Of heads whose list
+// (per_list heads of the Hq each) is chained the first n_chained of the n1 only.
 int launch_merge2(int d, const float* o1, const float2* ml1, int n1, const float* o2, const float2* ml2, int n2, uint16_t* out,
-                  float* lse, long long row0, long long rows, hipStream_t st);
+                  float* lse, long long row0, long long rows, hipStream_t st, const int* chained = nullptr, int n_chained = 0,
+                  int Hq = 1, int per_list = 1);
 
 // Shared-selection prefill: unnormalised partials of every (token, head, split) in the layout the
 // decode path writes, merged by the same attend_merge_kernel.

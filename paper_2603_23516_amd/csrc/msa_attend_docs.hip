@@ -7,21 +7,26 @@
 //   group_kernel         sorts the (token, slot) pairs of every selection list by document (counting sort; one
 //                        workgroup per list) into ITEMS of up to 16 / r tokens of one document, and, in its
 //                        other workgroups, rotates and scales the queries once, bf16 (hi, lo) in the order of
-//                        the matrix operand.
+//                        the matrix operand.  Where the pairs hardly share a document an item is a CHAIN instead, up
+//                        to four documents of one token.
 //   attend_docs_kernel   one WAVE per item (or per part of an item's rows where there are few): the columns of
 //                        the score product are the item's (token, head) pairs, so one pass over the document's
 //                        rows serves all of them.  A wave walks its items as one stream of 32-row steps; keys and
-//                        values of the next item are in flight while the last steps of this one are worked on.
+//                        values of the next item are in flight while the last steps of this one are worked on.  At the
+//                        end of an item they are awaited together with the next queries, the one drain per item.
 //                        No barrier after the prologue.
-// A (token, slot, part) leaves one partial (max, sum, output) per head; attend_merge2_kernel combines them with
+// An item leaves one partial (max, sum, output) per token, part and head; attend_merge2_kernel combines them with
 // those of the local context (tiled kernel).  What a column holds does not depend on the columns beside it, so the
-// order in which the sort places the pairs changes no bit of the result.
+// order in which the sort places the pairs changes no bit of the result; a token's chains are its slots in order.
 //
 // Bound: memory (every document and KV head once, then again from the L2 for every 16 / r tokens beyond the first), two
 // waves per SIMD with 24 KiB of requests in flight each.  One item per WAVE: four waves on one item would have to merge
-// their outputs through LDS once per 256 KiB read.  512 tokens of 8 of 4096 documents (512 rows, 8 heads of 128):
-// 1113 us token by token, 768 (sort 14, documents 640, local context 36, merge 28); 300 of 16 of 200 documents 1210 ->
-// 315; 1024 of 32 of 500 9.0 -> 1.96 ms.  Documents in parts cost more than they spread (a part pays for the chain
+// their outputs through LDS once per 256 KiB read.  512 tokens of 8 of 4096 documents (512 rows, 8 heads of 128), half of
+// them among 32 of a topic: 1067 us token by token, 710 (sort 12, documents 650, local context 26, merge 28); selections
+// drawn at random 1332, 983; 300 of 16 of 200 documents 1210, 315; 1024 of 32 of 500 9.0 ms, 1.96.
+// Partials are written between the reads, and that costs more than their bytes: 67 MB of them among 8.6 GB 92 us, whichever
+// way they are stored, and 45 for the instructions.  So with no document shared at all (the same sizes) items of one document
+// took 1480 us, chains 1372, token by token 1367.  Documents in parts cost more than they spread (a part pays for the chain
 // item - pairs - queries): 64 tokens of 4 of 8192 86 us whole, 94 in halves, so parts are for very few items only.
 //
 // Arithmetic per step is the decode kernel's (msa_attend.hip: keys rotated in fp32 by a recurrence, rounded to
@@ -40,8 +45,7 @@ template <int D, bool LDS>  // LDS: a document's counters fit there (N <= kLdsDo
 __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
   constexpr int HALF = D / 2;
   const int tid = threadIdx.x;
-  auto selection = [&](int t, int s) {  // of a token of the window: where list s begins in idx
-    t += da.tok0;
+  auto selection = [&](int t, int s) {  // of a token of the call: where list s begins in idx
     return ((long long)(a.idx_rows_per_b == 1 ? t / a.M : t) * a.idx_sel + s) * a.k;
   };
   if ((int)blockIdx.x >= a.idx_sel) {  // ---- queries of up to four tokens
@@ -56,7 +60,7 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, Docs
     for (int x = tid; x < 4 * a.Hq * a.k; x += kGroupThreads) {
       const int slot = x % a.k, row = x / a.k, t = t0 + row / a.Hq;
       if (t >= da.n_tok) break;
-      const int d = a.idx[selection(t, a.idx_sel == 1 ? 0 : row % a.Hq / a.r) + slot];
+      const int d = a.idx[selection(da.tok0 + t, a.idx_sel == 1 ? 0 : row % a.Hq / a.r) + slot];
       if (d >= 0 && d < a.N) continue;
       float2* ml = da.part_ml + ((long long)t0 * a.Hq * a.k + x) * da.parts;
       for (int p = 0; p < da.parts; ++p) ml[p] = make_float2(-INFINITY, 0.f);
@@ -94,65 +98,138 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, Docs
     }
     return;
   }
-  // ---- one list of selections.  What a phase leaves for the next is in LDS, or goes through this XCD's L2, at workgroup
-  // scope: atomics are done there, stores are written through to it, and values are read back with an addition of nothing,
-  // which no line of the vector L1 can serve.  (Device scope, i.e. memory: 40 us for 4096 pairs per list.)  A thread takes
-  // up to kPairs pairs at a time, so that their round trips overlap.
+  // ---- one list of selections: pair e = (token e >> kshift, slot e & (2^kshift - 1)).  A phase's results are in LDS, or in
+  // memory that this workgroup alone touches, at workgroup scope: the atomics and the barrier order them for its waves, and
+  // nothing has to reach the other XCDs before the end of the launch.  (Device scope, i.e. memory: 40 us for 4096 pairs per
+  // list.)  A thread takes up to kPairs pairs at a time, their loads together.
   __shared__ unsigned long long base_s[LDS ? kLdsDocs : 1];
   __shared__ int cnt_s[LDS ? kLdsDocs : 1];
-  __shared__ int n_entries_s, n_items_s;
+  __shared__ int n_entries_s, n_items_s, n_valid_s, n_tiles_s;
   const int s = blockIdx.x, lane = tid & 63;
-  const int E = da.n_tok * a.k, T = da.tile_tok;
+  const int sh = da.kshift, E = da.n_tok << sh, T = da.tile_tok;
   int* const cnt = LDS ? cnt_s : da.cnt + (long long)s * a.N;
   unsigned long long* const base = LDS ? base_s : da.base + (long long)s * a.N;
-  int* const rank = da.rank + (long long)s * da.cap;
+  int* const rank = da.rank + (long long)s * (da.n_tok << sh);
   int* const entries = da.entries + (long long)s * da.cap;
   int4* const items = da.items + (long long)s * da.cap;
-  auto doc_of = [&](int e) {  // -1: past the end, a pad, or no document of the bank
-    if (e >= E) return -1;
-    const int d = a.idx[selection(e / a.k, s) + e % a.k];
-    return d >= 0 && d < a.N ? d : -1;
-  };
   auto phase = [&]() {  // stores and atomics of the phase are complete for everyone
     wait_stores_done();
     __syncthreads();
   };
-  if (tid == 0) n_entries_s = n_items_s = 0;
-  int d[kPairs], rk[kPairs];
-  const bool once = E <= kPairs * kGroupThreads;  // documents and ranks of all pairs stay in registers
-  auto docs_at = [&](int e0) {
+  if (tid == 0) n_entries_s = n_items_s = n_valid_s = n_tiles_s = 0;
+  int d[kPairs], rk[kPairs];  // document (-1: past the end, a pad, or no document of the bank), place among its pairs
+  auto docs_at = [&](int e0, int tok_from, int pairs_to) {  // (no branch around a load)
+    int x[kPairs];
 #pragma unroll
-    for (int i = 0; i < kPairs; ++i) d[i] = doc_of(e0 + i * kGroupThreads + tid);
+    for (int i = 0; i < kPairs; ++i) {
+      const int e = e0 + i * kGroupThreads + tid, slot = e & ((1 << sh) - 1);
+      const bool ok = e < pairs_to && slot < a.k;
+      x[i] = a.idx[selection(tok_from + (ok ? e >> sh : 0), s) + (ok ? slot : 0)];
+      d[i] = ok ? 0 : -1;
+    }
+#pragma unroll
+    for (int i = 0; i < kPairs; ++i) d[i] = d[i] == 0 && x[i] >= 0 && x[i] < a.N ? x[i] : -1;
   };
   auto add = [](auto* p, auto v) { return __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
-  for (int e0 = 0; e0 < E; e0 += kPairs * kGroupThreads) {
-    docs_at(e0);
-#pragma unroll
-    for (int i = 0; i < kPairs; ++i)
-      if (d[i] >= 0) __hip_atomic_store(cnt + d[i], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  }
-  phase();
-  for (int e0 = 0; e0 < E; e0 += kPairs * kGroupThreads) {
-    if (!once) docs_at(e0);
-#pragma unroll
-    for (int i = 0; i < kPairs; ++i) rk[i] = d[i] >= 0 ? add(cnt + d[i], 1) : 1;
-    if (!once) {
+  auto read = [](auto* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
+  const unsigned long long below = (1ull << lane) - 1ull;
+  int have_from = -1, have_to = 0;  // the tokens whose documents and places are in registers
+  // the places of the pairs of [tok_from, tok_to) among those of their documents; `decide` counts pairs and tiles
+  auto count_pairs = [&](int tok_from, int tok_to, bool decide) {
+    const int to = (tok_to - tok_from) << sh;
+    for (int e0 = 0; e0 < to; e0 += kPairs * kGroupThreads) {
+      docs_at(e0, tok_from, to);
 #pragma unroll
       for (int i = 0; i < kPairs; ++i)
-        if (d[i] >= 0) rank[e0 + i * kGroupThreads + tid] = rk[i];
+        if (d[i] >= 0) __hip_atomic_store(cnt + d[i], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     }
+    phase();
+    const bool keep = to <= kPairs * kGroupThreads;
+    int n_valid = 0, n_tiles = 0;
+    for (int e0 = 0; e0 < to; e0 += kPairs * kGroupThreads) {
+      if (!keep) docs_at(e0, tok_from, to);
+#pragma unroll
+      for (int i = 0; i < kPairs; ++i) rk[i] = d[i] >= 0 ? add(cnt + d[i], 1) : 1;
+      if (!keep && to == E) {
+#pragma unroll
+        for (int i = 0; i < kPairs; ++i)
+          if (d[i] >= 0) rank[e0 + i * kGroupThreads + tid] = rk[i];
+      }
+      if (decide) {
+#pragma unroll
+        for (int i = 0; i < kPairs; ++i) {
+          n_valid += __popcll(__ballot(d[i] >= 0));
+          n_tiles += __popcll(__ballot(d[i] >= 0 && rk[i] % T == 0));
+        }
+      }
+    }
+    if (decide && lane == 0) {
+      atomicAdd(&n_valid_s, n_valid);
+      atomicAdd(&n_tiles_s, n_tiles);
+    }
+    phase();
+    have_from = keep ? tok_from : -1;
+    have_to = tok_to;
+  };
+  // Where hardly a document has a second token the pairs are taken as they come: chains of up to `chain` documents of one
+  // token, one partial each.  Decided over all tokens of the call, so that its windows change no bit.
+  const int t1 = da.tok0 + da.n_tok;
+  count_pairs(0, da.n_all, true);
+  const bool chains = 10ll * n_valid_s < 11ll * n_tiles_s;
+  if (!chains && da.n_tok != da.n_all) count_pairs(da.tok0, t1, false);
+  const bool once = have_from == da.tok0 && have_to == t1;  // documents and ranks of all pairs stay in registers
+  if (chains) {
+    const unsigned long long mine = (sh == 6 ? ~0ull : (1ull << (1 << sh)) - 1ull) << (lane & ~((1 << sh) - 1) & 63);
+    for (int e0 = 0; e0 < E; e0 += kPairs * kGroupThreads) {
+      if (!once) docs_at(e0, da.tok0, E);
+      unsigned long long valid[kPairs], lead[kPairs];
+      int be = 0, bi = 0;
+#pragma unroll
+      for (int i = 0; i < kPairs; ++i) {
+        valid[i] = __ballot(d[i] >= 0);
+        lead[i] = __ballot(d[i] >= 0 && __popcll(valid[i] & mine & below) % da.chain == 0);
+        be += __popcll(valid[i]);
+        bi += __popcll(lead[i]);
+      }
+      if (lane == 0) {
+        be = atomicAdd(&n_entries_s, be);
+        bi = atomicAdd(&n_items_s, bi);
+      }
+      be = __shfl(be, 0, 64);
+      bi = __shfl(bi, 0, 64);
+#pragma unroll
+      for (int i = 0; i < kPairs; ++i) {
+        if (d[i] >= 0) {
+          const int at = be + __popcll(valid[i] & below);
+          entries[at] = d[i];
+          if ((lead[i] >> lane) & 1) {
+            const int before = __popcll(valid[i] & mine & below), left = __popcll(valid[i] & mine & ~below);
+            const int t = (e0 + i * kGroupThreads + tid) >> sh;
+            items[bi + __popcll(lead[i] & below)] =
+                make_int4((t << 6) | before / da.chain, at, left < da.chain ? left : da.chain, left <= da.chain ? 3 : 2);
+          }
+        }
+        be += __popcll(valid[i]);
+        bi += __popcll(lead[i]);
+      }
+    }
+    __syncthreads();
+    if (tid == 0) {
+      da.n_items[s] = n_items_s;
+      da.n_items[a.idx_sel + s] = 1;
+    }
+    return;
   }
-  phase();
   // the first pair of a document reserves its places; a wave adds up its documents first
   for (int e0 = 0; e0 < E; e0 += kPairs * kGroupThreads) {
     if (!once) {
-      docs_at(e0);
+      docs_at(e0, da.tok0, E);
 #pragma unroll
       for (int i = 0; i < kPairs; ++i) rk[i] = d[i] >= 0 ? rank[e0 + i * kGroupThreads + tid] : 1;
     }
     int c[kPairs], pc = 0, pt = 0;
 #pragma unroll
-    for (int i = 0; i < kPairs; ++i) c[i] = rk[i] == 0 ? add(cnt + d[i], 0) : 0;
+    for (int i = 0; i < kPairs; ++i) c[i] = rk[i] == 0 ? read(cnt + d[i]) : 0;
 #pragma unroll
     for (int i = 0; i < kPairs; ++i) {
       pc += c[i];
@@ -186,7 +263,7 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, Docs
   phase();
   for (int e0 = 0; e0 < E; e0 += kPairs * kGroupThreads) {
     if (!once) {
-      docs_at(e0);
+      docs_at(e0, da.tok0, E);
 #pragma unroll
       for (int i = 0; i < kPairs; ++i) rk[i] = d[i] >= 0 ? rank[e0 + i * kGroupThreads + tid] : 1;
     }
@@ -194,25 +271,29 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, Docs
     int c[kPairs];
 #pragma unroll
     for (int i = 0; i < kPairs; ++i) {
-      b[i] = d[i] >= 0 ? add(base + d[i], 0ull) : 0ull;
-      c[i] = d[i] >= 0 && rk[i] % T == 0 ? add(cnt + d[i], 0) : 0;
+      b[i] = d[i] >= 0 ? read(base + d[i]) : 0ull;
+      c[i] = d[i] >= 0 && rk[i] % T == 0 ? read(cnt + d[i]) : 0;
     }
 #pragma unroll
     for (int i = 0; i < kPairs; ++i) {
+      if (d[i] < 0) continue;
       const int e = e0 + i * kGroupThreads + tid;
-      if (e >= E) break;
-      if (d[i] >= 0) {
-        const int at = (int)(unsigned)b[i] + rk[i];
-        entries[at] = e;
-        if (c[i] > 0) {
-          const int left = c[i] - rk[i];
-          items[(int)(b[i] >> 32) + rk[i] / T] = make_int4(d[i], at, left < T ? left : T, c[i] > T ? 0 : 1);
-        }
+      const int at = (int)(unsigned)b[i] + rk[i];
+      entries[at] = (e >> sh << 6) | (e & ((1 << sh) - 1));
+      if (c[i] > 0) {
+        const int left = c[i] - rk[i];
+        items[(int)(b[i] >> 32) + rk[i] / T] = make_int4(d[i], at, left < T ? left : T, c[i] > T ? 0 : 1);
       }
     }
   }
-  if (tid == 0) da.n_items[s] = n_items_s;
+  if (tid == 0) {
+    da.n_items[s] = n_items_s;
+    da.n_items[a.idx_sel + s] = 0;
+  }
 }
+
+constexpr int kFetch = 32, kFetchPairs = 192;  // items looked up at a time, at most: 32 of up to four entries, 12 of sixteen
+constexpr int kMaxChain = 4;
 
 // ---- attention, document by document -------------------------------------------------------------------------
 template <int D, bool ROT>  // ROT: raw bank keys, rotated here with positions 0..G-1; else used as stored
@@ -230,7 +311,8 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
   __shared__ float2 step16[HALF];     // e^{i 16 theta_u}
   __shared__ float2 estart[kAttWaves][HALF];
   __shared__ double theta_s[HALF];
-  __shared__ int4 desc[kAttWaves][64];
+  __shared__ int4 desc[kAttWaves][kFetch];  // items to come, and their entries
+  __shared__ int entry[kAttWaves][kFetchPairs];
   __shared__ __attribute__((aligned(16))) unsigned char stage[kAttWaves][2 * VBYTES];
 
   const int tid = threadIdx.x;
@@ -264,6 +346,8 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
   // ---- this wave's share of the items: [g][item][part] in one line, an eighth of it per XCD (workgroups go round the
   // XCDs in turn), so that the tiles of a document that many tokens selected meet in one L2
   auto items_upto = [&]() {  // lane g: items of the KV heads up to g
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));
     int upto = lane < a.Hkv ? da.n_items[a.idx_sel == 1 ? 0 : lane] : 0;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
@@ -279,11 +363,18 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
   const int first_x = lo + (int)(blockIdx.x >> 3) * kAttWaves + wave;
   if (first_x >= hi) return;  // (no barrier below)
 
-  // Descriptors of the next 64 items of this wave: document, its rows, first entry, tokens | part << 8 |
-  // the document's only item << 15 | KV head << 16.
+  // Descriptors of the next items of this wave: document and its rows, or a chain's token << 6 | number; tokens | part << 8 |
+  // the token's last chain << 14 | nobody else reads its rows << 15 | KV head << 16; documents of a chain, or 0.  And their
+  // entries: the (token, slot) of each of the item's tokens, or each of a chain's documents (the last one again past their
+  // number).
   // In LDS: the stream below has no registers for them.
+  const int T = da.tile_tok, tl = n / a.r;  // (r is a power of two: tl < T)
+  const int per_item = T < kMaxChain ? kMaxChain : T;
+  const int n_fetch = kFetch * per_item <= kFetchPairs ? kFetch : kFetchPairs / per_item;
   auto fetch_items = [&](int x0) {
-    const int x = x0 + lane * stride;
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    const int x = x0 + ln * stride;
     const int upto = items_upto();
     const int xi = x / da.parts, part = x - xi * da.parts;
     int g = 0, before = 0;
@@ -294,14 +385,25 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
         before = u;
       }
     }
-    if (x < hi) {
-      const int4 it = da.items[(long long)(a.idx_sel == 1 ? 0 : g) * da.cap + (xi - before)];
+    int first = 0, cnt = 0;
+    if (x < hi && ln < n_fetch) {
+      const int list = a.idx_sel == 1 ? 0 : g;
+      const int4 it = da.items[(long long)list * da.cap + (xi - before)];
+      const bool chain = it.w >= 2;
       int len = a.G;
-      if (a.lens != nullptr) {
+      if (a.lens != nullptr && !chain) {
         len = a.lens[it.x];
         len = len < 1 ? 1 : (len > a.G ? a.G : len);
       }
-      desc[wave][lane] = make_int4(it.x, len, it.y, it.z | (part << 8) | (it.w << 15) | (g << 16));
+      desc[wave][ln] = make_int4(it.x, len, (chain ? 1 : it.z) | (part << 8) | (it.w == 3 ? 0x4000 : 0) | (it.w != 0 ? 0x8000 : 0) | (g << 16),
+                                 chain ? it.z : 0);
+      first = list * da.cap + it.y;
+      cnt = it.z;
+    }
+    for (int p0 = 0; p0 < n_fetch * per_item; p0 += 64) {
+      const int p = p0 + ln, of = p / per_item, i = p - of * per_item;
+      const int f = __shfl(first, of & 63, 64), c = __shfl(cnt, of & 63, 64);
+      if (p < n_fetch * per_item && c > 0) entry[wave][p] = da.entries[f + (i < c ? i : c - 1)];
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -312,16 +414,15 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
     long long off;  // element offset of its first row in K and V
     int rows;       // rows of its item from there on, 32 or more: a whole step (0: an empty part of a short document)
     int p_first;    // position of the first row
-    int left;       // steps of its item after this one
-    int at, what;   // the item
+    int left;       // steps of its document after this one, + kGoesOn if others of the chain follow
+    int what;       // the item
+    int pair;       // token << 6 | slot of the partial of this lane's column
   };
+  constexpr int kGoesOn = 1 << 30;
   int c_x = first_x, c_lane = 0;  // the cursor's item
-  auto open_item = [&](Step& s) {
-    const int4 d = desc[wave][c_lane];
-    const int doc = __builtin_amdgcn_readfirstlane(d.x), len = __builtin_amdgcn_readfirstlane(d.y);
-    s.at = __builtin_amdgcn_readfirstlane(d.z);
-    s.what = __builtin_amdgcn_readfirstlane(d.w);
-    const int part = (s.what >> 8) & 0x7f, g = s.what >> 16;
+  int c_doc = 0, c_docs = 0;      // ... and document of a chain
+  auto open_rows = [&](Step& s, int doc, int len) {
+    const int part = (s.what >> 8) & 0x3f, g = s.what >> 16;
     const int most = da.part_steps * 32;
     int p0 = part * most;
     int rows = len - p0;  // rows of the document from this part on
@@ -332,17 +433,45 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
     s.rows = rows;
     s.off = (((long long)doc * a.Hkv + g) * a.G + p0) * D;
   };
+  auto open_of_chain = [&](Step& s) {
+    const int doc = __builtin_amdgcn_readfirstlane(entry[wave][c_lane * per_item + c_doc]);
+    int len = a.G;
+    if (a.lens != nullptr) {  // (a scalar load: a vector load would be awaited with everything in flight)
+      len = ((const __attribute__((address_space(4))) int32_t*)a.lens)[doc];
+      len = len < 1 ? 1 : (len > a.G ? a.G : len);
+    }
+    open_rows(s, doc, len);
+    if (++c_doc < c_docs) s.left += kGoesOn;
+  };
+  auto open_item = [&](Step& s) {
+    const int4 d = desc[wave][c_lane];
+    const int x = __builtin_amdgcn_readfirstlane(d.x);
+    s.what = __builtin_amdgcn_readfirstlane(d.z);
+    c_docs = __builtin_amdgcn_readfirstlane(d.w);
+    c_doc = 0;
+    if (c_docs > 0) {
+      s.pair = x;
+      open_of_chain(s);
+    } else {
+      s.pair = entry[wave][c_lane * per_item + tl];
+      open_rows(s, x, __builtin_amdgcn_readfirstlane(d.y));
+    }
+  };
   auto advance = [&](Step& s) -> bool {  // false: the stream has ended, s stays
-    if (s.left > 0) {
+    if ((s.left & ~kGoesOn) > 0) {
       s.off += 32 * D;
       s.p_first += 32;
       s.rows -= 32;
       --s.left;
       return true;
     }
+    if (s.left != 0) {
+      open_of_chain(s);
+      return true;
+    }
     if (c_x + stride >= hi) return false;
     c_x += stride;
-    if (++c_lane == 64) {
+    if (++c_lane == n_fetch) {
       c_lane = 0;
       fetch_items(c_x);
     }
@@ -406,25 +535,30 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
   const int vt_lane = (4 * rr + (n >> 2)) * (D * 2) + (n >> 2) * 32 + ((n >> 1) & 1) * 16 + (n & 1) * 8;
 
   // ---- the item at hand: queries (B operands, column n = (token n / r, head n % r)), running softmax -------------
-  const int tl = n / a.r, hh = n - tl * a.r;
   bf16x8_t bqh[NS], bql[NS];
-  int ph = 0;  // partial slot of this lane's column
   float m_run = -INFINITY, l_run = 0.f;
   int cur_p = -1;  // position of key 0 of the sub-tile the rotation state is valid for; -1 = invalid
   f32x4_t o[NCB];
-  auto begin_item = [&](const Step& s) {
-    const int cnt = s.what & 0xff, part = (s.what >> 8) & 0x7f, g = s.what >> 16;
-    const int e = da.entries[(long long)(a.idx_sel == 1 ? 0 : g) * da.cap + s.at + (tl < cnt ? tl : cnt - 1)];
-    const int t = e / a.k;
-    const int row = t * a.Hq + g * a.r + hh;
-    ph = (row * a.k + (e - t * a.k)) * da.parts + part;
-    const uint4* qp = da.qrot + (long long)row * (D / 4) + 2 * rr;
+  // What follows is worked out from an opaque copy of the lane number, here and in end_item: kept across the stream it would
+  // spill, and a reload is awaited with everything in flight.
+  auto head_row = [&](const Step& s, int ln) {  // (token, head) of the lane's column, inside the window
+    return (s.pair >> 6) * a.Hq + (s.what >> 16) * a.r + (ln & (a.r - 1));
+  };
+  auto issue_queries = [&](const Step& s) {
+    int ln = lane;
+    asm volatile("" : "+v"(ln));
+    gptr_t qb = (gptr_t)uni64((unsigned long long)da.qrot);
+    const unsigned at = (unsigned)head_row(s, ln) * (D * 4) + 32 * (ln >> 4);  // (a window's buffers stay under 4 GB)
 #pragma unroll
     for (int sl = 0; sl < NS; ++sl) {
-      bqh[sl] = as_bf16x8(qp[8 * sl]);
-      bql[sl] = as_bf16x8(qp[8 * sl + 1]);
+      const u32x4_t h = *(gvec_t)(qb + (at + 128 * sl)), l = *(gvec_t)(qb + (at + 128 * sl + 16));
+      bqh[sl] = as_bf16x8(make_uint4(h.x, h.y, h.z, h.w));
+      bql[sl] = as_bf16x8(make_uint4(l.x, l.y, l.z, l.w));
     }
-    // awaited here: left to the next turn, its waits would be placed for this path, i.e. drain every request in flight
+  };
+  auto begin_item = [&]() {
+    // the queries are awaited here: left to the next turn, its waits would be placed for this path, i.e. drain every request
+    // in flight
 #pragma unroll
     for (int sl = 0; sl < NS; ++sl) asm volatile("" : "+v"(bqh[sl]), "+v"(bql[sl]));
     m_run = -INFINITY;
@@ -433,25 +567,54 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
 #pragma unroll
     for (int c = 0; c < NCB; ++c) o[c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   };
-  auto end_item = [&](const Step& s) {
+  // The outputs of the item's columns go through the stage whose values have been used, so that a store writes whole rows
+  // (an empty partial, maximum -inf, may hold anything: the merge does not look at it).
+  auto end_item = [&](const Step& s, int cur_stage) {
+    int ln = lane, wv = wave;
+    asm volatile("" : "+v"(ln), "+v"(wv));
+    const int cols = (s.what & 0xff) * a.r, part = (s.what >> 8) & 0x3f, col = ln & 15;
+    const unsigned ph = (unsigned)(head_row(s, ln) * a.k + (s.pair & 63)) * (unsigned)da.parts + part;
     float l = l_run;
     l += __shfl_xor(l, 16, 64);
     l += __shfl_xor(l, 32, 64);
-    if (tl < (s.what & 0xff)) {
-      const bool any = m_run != -INFINITY;
-      float* po = da.part_o + (long long)ph * D + 4 * rr;
+    unsigned char* const st = &stage[wv][0] + cur_stage * VBYTES;
 #pragma unroll
-      for (int c = 0; c < NCB; ++c)
-        *reinterpret_cast<float4*>(po + 16 * c) = any ? make_float4(o[c][0], o[c][1], o[c][2], o[c][3])
-                                                      : make_float4(0.f, 0.f, 0.f, 0.f);
-      if (rr == 0) da.part_ml[ph] = make_float2(m_run, l);
+    for (int c = 0; c < NCB; ++c)
+      *reinterpret_cast<f32x4_t*>(st + col * (D * 4) + ((4 * c + (ln >> 4)) ^ col) * 16) = o[c];
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    typedef __attribute__((address_space(1))) char* gout_t;
+    gout_t ob = (gout_t)uni64((unsigned long long)da.part_o);
+    gout_t mb = (gout_t)uni64((unsigned long long)da.part_ml);
+    const float m = m_run;
+    begin_item();
+    if (ln < cols)
+      *(__attribute__((address_space(1))) unsigned long long*)(mb + ph * 8u) =
+          __builtin_bit_cast(unsigned long long, make_float2(m, l));
+    if (s.what & 0x4000) {  // the partials that the merge looks at behind a token's last chain: empty
+      const unsigned at = (unsigned)((s.pair >> 6) * a.Hq + (s.what >> 16) * a.r) * a.k;
+      const int next = (s.pair & 63) + 1 + ln;
+      if (next < da.n_chains)
+        for (int h = 0; h < a.r; ++h)
+          for (int p = 0; p < da.parts; ++p)
+            *(__attribute__((address_space(1))) unsigned long long*)(mb + ((at + h * a.k + next) * da.parts + p) * 8u) =
+                __builtin_bit_cast(unsigned long long, make_float2(-INFINITY, 0.f));
     }
+    constexpr int CPS = 1024 / (D * 4);  // columns of a wave-wide store
+    for (int c0 = 0; c0 < cols; c0 += CPS) {  // wave-uniform
+      const int c = c0 + ln / (64 / CPS), piece = ln % (64 / CPS);
+      const unsigned pc = (unsigned)__shfl((int)ph, c, 64);
+      const u32x4_t v = *reinterpret_cast<const u32x4_t*>(st + c * (D * 4) + (piece ^ c) * 16);
+      if (c < cols) *(__attribute__((address_space(1))) u32x4_t*)(ob + (pc * (D * 4) + piece * 16)) = v;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   };
 
   fetch_items(c_x);
   Step s0, s1, s2;  // the step worked on, the next two
   open_item(s0);
-  begin_item(s0);
+  issue_queries(s0);
   s1 = s0;
   bool more1 = advance(s1), more2 = false;  // s1, s2 are steps of the stream (else repeats whose requests go unused)
   s2 = s1;
@@ -460,6 +623,7 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
   issue_keys(s0, kA);
   issue_values(s0, 0);
   issue_keys(s1, kB);
+  begin_item();
 
   float2 cs[NU];  // (cos, sin)((cur_p + n) * theta_u), u = 32s' + 8rr + j at index 8s' + j
   bool live = true;
@@ -492,6 +656,7 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
           for (int j = 0; j < 8; ++j) {
             const int u = 32 * s2i + 8 * rr_ + j;
             cs[8 * s2i + j] = cmul(estart[wv][u], base0[n_][u]);
+            if (j & 1) __builtin_amdgcn_sched_barrier(0);
           }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -542,7 +707,10 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
       }
     }
     if (ROT) cur_p += 32;
-    issue_keys(s2, kraw);  // the keys of the step after next (this step's are in the scores now)
+    // the keys of the step after next (this step's are in the scores now); on an item's last step as many requests for the
+    // queries of the next one, whose keys then follow behind the outputs
+    const bool last = live && s0.left == 0;
+    issue_keys(s2, kraw);
 
     // ---- online softmax (exp2 domain) ---------------------------------------------------------------------
     float mx = fmaxf(fmaxf(fmaxf(sc[0][0], sc[0][1]), fmaxf(sc[0][2], sc[0][3])),
@@ -576,7 +744,8 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
     const bf16x8_t pbh = as_bf16x8(make_uint4(pwh[0], pwh[1], pwh[2], pwh[3]));
     const bf16x8_t pbl = as_bf16x8(make_uint4(pwl[0], pwl[1], pwl[2], pwl[3]));
 
-    // ---- second product (requests younger than this step's values: keys of the next two steps, the next values) ---
+    // ---- second product (requests younger than this step's values: keys of the next two steps or, for the second, the next
+    // queries; the next values) ---
     wait_copies_but<NVL + 4 * NS>();
     {
       const unsigned char* vt = &stage[wave][0] + cur_stage * VBYTES;
@@ -593,9 +762,9 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
       }
     }
     // ---- next turn -------------------------------------------------------------------------------------------
-    if (live && s0.left == 0) {  // the item is complete
-      end_item(s0);
-      if (more1) begin_item(s1);
+    if (last) {  // the item is complete (behind the last one s1 repeats it, and the queries go unused)
+      issue_queries(s1);
+      end_item(s0, cur_stage);
     }
     live = more1;
     s0 = s1;
@@ -618,17 +787,19 @@ template <int D>
 __global__ __launch_bounds__(256) void attend_merge2_kernel(const float* __restrict__ o1, const float2* __restrict__ ml1,
                                                             int n1, const float* __restrict__ o2,
                                                             const float2* __restrict__ ml2, int n2, uint16_t* __restrict__ out,
-                                                            float* __restrict__ lse, long long row0, long long rows) {
+                                                            float* __restrict__ lse, long long row0, long long rows,
+                                                            const int* __restrict__ chained, int n_chained, int Hq, int per_list) {
   constexpr int V = D / 64;
   constexpr int U = 8;
   const int lane = threadIdx.x & 63;
   const long long row = (long long)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (row >= rows) return;
-  const int ns = n1 + n2;
   const float2* m1 = ml1 + row * n1;
+  const float* p1 = o1 + row * n1 * D + lane * V;
+  if (chained != nullptr && chained[(int)(row % Hq) / per_list] != 0) n1 = n_chained;
+  const int ns = n1 + n2;
   const float2* m2 = ml2 + (row0 + row) * n2;
   typedef float vec_t __attribute__((ext_vector_type(V)));
-  const float* p1 = o1 + row * n1 * D + lane * V;
   const float* p2 = o2 + (row0 + row) * n2 * D + lane * V;
   vec_t v[U];
   auto fetch = [&](int s0) {  // (past the end: the last one again)
@@ -689,21 +860,27 @@ __global__ __launch_bounds__(256) void attend_merge2_kernel(const float* __restr
 }
 
 int launch_merge2(int d, const float* o1, const float2* ml1, int n1, const float* o2, const float2* ml2, int n2, uint16_t* out,
-                  float* lse, long long row0, long long rows, hipStream_t st) {
+                  float* lse, long long row0, long long rows, hipStream_t st, const int* chained, int n_chained, int Hq,
+                  int per_list) {
   const dim3 grid((unsigned)((rows + 3) / 4)), block(256);
-  if (d == 128) hipLaunchKernelGGL(attend_merge2_kernel<128>, grid, block, 0, st, o1, ml1, n1, o2, ml2, n2, out, lse, row0, rows);
-  else hipLaunchKernelGGL(attend_merge2_kernel<64>, grid, block, 0, st, o1, ml1, n1, o2, ml2, n2, out, lse, row0, rows);
+  if (d == 128) hipLaunchKernelGGL(attend_merge2_kernel<128>, grid, block, 0, st, o1, ml1, n1, o2, ml2, n2, out, lse, row0, rows, chained, n_chained, Hq, per_list);
+  else hipLaunchKernelGGL(attend_merge2_kernel<64>, grid, block, 0, st, o1, ml1, n1, o2, ml2, n2, out, lse, row0, rows, chained, n_chained, Hq, per_list);
   return hipGetLastError() == hipSuccess ? MSA_OK : MSA_ERR_HIP;
 }
 
 // Bytes of the fixed buffers and of those that grow with the tokens of a window.
 static size_t docs_fixed_bytes(const Dims& dm) {
   const size_t S = dm.scope_all ? 1 : dm.Hkv;
-  return round_up256(S * dm.N * 8) + round_up256(S * dm.N * 4) + round_up256(S * 4);
+  return round_up256(S * dm.N * 8) + round_up256(S * dm.N * 4) + round_up256(S * 8);
+}
+static int slot_bits(int k) {  // the least power of two that holds k slots
+  int b = 0;
+  while ((1 << b) < k) ++b;
+  return b;
 }
 static size_t docs_window_bytes(const Dims& dm, int k, int slots, size_t tokens) {  // slots: partials per (token, head)
   const size_t S = dm.scope_all ? 1 : dm.Hkv, e = S * tokens * k;
-  return round_up256(tokens * dm.Hq * dm.d * 4) + round_up256(e * 16) + 2 * round_up256(e * 4) +
+  return round_up256(tokens * dm.Hq * dm.d * 4) + round_up256(e * 16) + round_up256(e * 4) + round_up256((S * tokens << slot_bits(k)) * 4) +
          round_up256(tokens * dm.Hq * slots * dm.d * 4) + round_up256(tokens * dm.Hq * slots * 8);
 }
 
@@ -716,15 +893,26 @@ static int docs_parts(const Dims& dm, long long BM, int k) {
 }
 
 // Where the documents are certain to be shared (twice as many pairs as documents) or the pairs are many, and the rows that
-// the decode kernel would gather are worth three launches more.  Against that kernel, us: 16 tokens of 16 of 64 documents
-// (512 rows, 8 heads of 128) 91 -> 71, 50 of 8 of 1000 (128 rows) 78 -> 57, 200 of 4 of 8000 (64 rows) 77 -> 70, 16 of 16
-// of 8000 (1024 rows) 177 -> 170; on the other side of the line 64 of 4 of 8192 (512 rows) 82 -> 86, 32 of 20 of 2000 (two
-// heads of 64) 45 -> 67, 64 of 4 of 128 (64 rows of 64) 27 -> 31.
+// the decode kernel would gather are worth three launches more.  Against that kernel, us, selections of which half are among
+// 4 k documents of a topic / drawn at random / without a document in common (512 rows, 8 heads of 128 and r = 4 unless said):
+//   512 tokens of 8 of 4096 documents   1067 -> 710   1332 -> 983   1367 -> 1372
+//   64 of 32 of 8192                     589 -> 463    681 -> 715    691 -> 712
+//   40 of 16 of 8192                     251 -> 183    286 -> 250    289 -> 254
+//   100 of 16 of 4000 (128 rows)         147 -> 119    174 -> 185    192 -> 208
+//   64 of 12 of 2000 (256 rows)          117 -> 107    143 -> 161    158 -> 168
+//   300 of 16 of 8192, r = 8             716 -> 588    842 -> 806    860 -> 960
+// and 16 tokens of 16 of 64 documents 91 -> 71.  On the other side of the lines: 64 of 4 of 8192 82 -> 86, 32 of 20 of 2000
+// (two heads of 64) 45 -> 67, 64 of 4 of 128 (64 rows of 64) 27 -> 31.  Sharing grows with the tokens of a topic: 16 tokens
+// under 1 GiB (16 of 8000, 1024 rows) 176 -> 174, 199 -> 213, 200 -> 215, and with r = 8, where an item takes two tokens, 32
+// (32 of 8192) 180 -> 182, 191 -> 211, 196 -> 216, and 2 x 64 (16 of 4096, 128 rows) 95 -> 93, 107 -> 115, 108 -> 128.
 bool docs_path_applies(const Dims& dm, int B, int M, int k) {
   const long long S = dm.scope_all ? 1 : dm.Hkv, pairs = (long long)B * M * k, items = pairs * dm.Hkv;
   const long long bytes = items * dm.G * dm.d * 4;
   if (dm.G % 32 != 0 || dm.Hkv > 64 || S * dm.N > (8 << 20)) return false;
-  return bytes >= (1ll << 30) || (items >= 3072 && bytes >= (96ll << 20)) || (pairs >= 2ll * dm.N && bytes >= (256ll << 20));
+  const bool certain = pairs >= 2ll * dm.N;
+  if (!certain && dm.r == 8 && M < 128) return false;
+  return bytes >= (1ll << 30) || (items >= 3072 && bytes >= (96ll << 20) && (certain || M >= 32)) ||
+         (certain && bytes >= (256ll << 20));
 }
 
 DocsPlan plan_docs(const Dims& dm, int B, int M, int k, size_t bytes) {
@@ -732,6 +920,15 @@ DocsPlan plan_docs(const Dims& dm, int B, int M, int k, size_t bytes) {
   const long long BM = (long long)B * M, steps = dm.G / 32;
   p.parts = docs_parts(dm, BM, k);
   p.part_steps = (int)(steps / p.parts);
+  // documents of a chain: the fewest steps of the busiest wave, two for what a chain costs besides its documents
+  p.chain = 1;
+  for (long long c = 2, best = (BM * k * dm.Hkv + 2047) / 2048 * (steps + 2); c <= kMaxChain && p.parts == 1; ++c) {
+    const long long cost = (BM * dm.Hkv * ((k + c - 1) / c) + 2047) / 2048 * (c * steps + 2);
+    if (cost <= best) {
+      best = cost;
+      p.chain = (int)c;
+    }
+  }
   // Parts become fewer as k grows; the size to ask for is that of the most partials which a call of no more documents uses.
   int slots = 0;
   for (int kk = 1; kk <= k; ++kk) {
@@ -775,17 +972,21 @@ int launch_attend_docs(const Dims& dm, const DocsPlan& pl, const AttendArgs& a0,
   const size_t W = pl.tokens, e = (size_t)S * W * a0.k, parts = (size_t)W * dm.Hq * a0.k * pl.parts;
   da.base = (unsigned long long*)take((size_t)S * dm.N * 8);
   da.cnt = (int*)take((size_t)S * dm.N * 4);
-  da.n_items = (int*)take((size_t)S * 4);
+  da.n_items = (int*)take((size_t)S * 8);
   da.qrot = (uint4*)take(W * dm.Hq * dm.d * 4);
   da.items = (int4*)take(e * 16);
   da.entries = (int*)take(e * 4);
-  da.rank = (int*)take(e * 4);
+  da.rank = (int*)take((size_t)S * W * 4 << slot_bits(a0.k));
   da.part_o = (float*)take(parts * dm.d * 4);
   da.part_ml = (float2*)take(parts * 8);
   da.cap = (int)(W * a0.k);
   da.tile_tok = 16 / dm.r;
   da.parts = pl.parts;
   da.part_steps = pl.part_steps;
+  da.kshift = slot_bits(a0.k);
+  da.chain = pl.chain;
+  da.n_chains = (a0.k + pl.chain - 1) / pl.chain;
+  da.n_all = BM;
   AttendArgs a = a0;
   profile_mark(dm, false, st);
   for (int t0 = 0; t0 < BM; t0 += pl.tokens) {
@@ -807,7 +1008,7 @@ int launch_attend_docs(const Dims& dm, const DocsPlan& pl, const AttendArgs& a0,
     else MSA_DOCS(64);
 #undef MSA_DOCS
     const int rc = launch_merge2(dm.d, da.part_o, da.part_ml, a.k * pl.parts, loc_o, loc_ml, n_loc, (uint16_t*)out, lse,
-                                 (long long)t0 * dm.Hq, rows, st);
+                                 (long long)t0 * dm.Hq, rows, st, da.n_items + S, da.n_chains * pl.parts, dm.Hq, dm.Hq / S);
     if (rc != MSA_OK) return rc;
   }
   profile_mark(dm, true, st);

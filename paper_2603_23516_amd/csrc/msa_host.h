@@ -122,6 +122,7 @@ constexpr size_t kDocsBytes = (size_t)256 << 20;  // per-token buffers of a wind
 constexpr int kDocsItems = 2048;                  // fewer items than this: documents in parts
 struct DocsPlan {
   int parts, part_steps;  // parts of a document's rows, 32-row steps of each
+  int chain;              // documents of one token that share a partial, at most, where hardly any are shared
   int tokens;             // query tokens per window; 0: the workspace is too small for this path
   size_t bytes;           // workspace asked for
 };

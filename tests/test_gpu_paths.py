@@ -619,3 +619,82 @@ def test_attention_document_by_document_of_pads(scope, r, k):
     assert np.abs(go - oo).max() <= 2e-2 and np.linalg.norm(go - oo) <= 5e-3 * np.linalg.norm(oo)
     assert np.abs(lse.cpu().numpy() - ol).max() <= 5e-3
     assert took[1] < took[0], took
+
+
+def attend_least(cfg, args, ws):
+    """The least workspace size that a call accepts (sizes above it are all accepted)."""
+    no, yes = 0, ws.numel()
+    while yes - no > 1:
+        mid = (no + yes) // 2
+        try:
+            msa.msa_sparse_attend(cfg, *args, workspace=ws[:mid])
+            yes = mid
+        except msa.MsaError as e:
+            assert e.status == msa.MSA_ERR_WORKSPACE
+            no = mid
+    return yes
+
+
+# (N, Hkv, r, G, d, B, M, k, Lloc, scope, rotated, ragged): no document in two selections, so that an item is a chain of a
+# token's documents, of up to ...
+ATT_CHAINS = [
+    (1600, 4, 2, 64, 64, 1, 96, 16, 96, "group", 0, False),     # ... four
+    (800, 8, 4, 64, 64, 1, 128, 6, 40, "group", 0, True),       # ... three, two per token
+    (1600, 2, 8, 64, 128, 1, 128, 12, 50, "all", 1, True),      # ... two; items of two tokens were they shared
+    (1600, 4, 1, 64, 64, 2, 48, 16, 32, "group", 1, True),      # ... four; of sixteen
+    (400, 4, 2, 2048, 128, 1, 20, 16, 33, "group", 0, True),    # ... one, the documents in two parts
+    (13000, 1, 4, 32, 64, 1, 800, 16, 40, "group", 0, False),   # counters in memory, documents looked up again by every phase
+]
+
+
+@pytest.mark.parametrize("N,Hkv,r,G,d,B,M,k,Lloc,scope,rotated,ragged", ATT_CHAINS)
+def test_attention_of_selections_without_common_documents(N, Hkv, r, G, d, B, M, k, Lloc, scope, rotated, ragged):
+    """With pads, ids outside the bank, tokens with one document and with none, from workspaces full of NaN: against the
+    oracle (small documents), and against the kernel that takes token by token, whose fp32 sums run in another order (one
+    rounding to bf16: 2^-7 of the value)."""
+    say(f"chains N={N} Hkv={Hkv} r={r} G={G} d={d} B={B} M={M} k={k} Lloc={Lloc} {scope} rot={rotated} ragged={ragged}")
+    rng = np.random.default_rng(58300 + N)
+    lens = rng.integers(1, G + 1, N).astype(np.int32) if ragged else None
+    cfg = msa.MsaConfig(N, G, G, Hkv * r, Hkv, d, 1e6, bank_keys_rotated=rotated,
+                        doc_lens=torch.from_numpy(lens).cuda() if ragged else None,
+                        select_scope=msa.MSA_SCOPE_ALL if scope == "all" else msa.MSA_SCOPE_GROUP)
+    S_ = 1 if scope == "all" else Hkv
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(58300)
+    K, V = (torch.empty((N, Hkv, G, d), dtype=torch.bfloat16, device="cuda").normal_(generator=gen) for _ in range(2))
+    qb, q = S.normal_bf16(58301, (B, M, Hkv * r, d))
+    Klb, Kl = S.normal_bf16(58302, (B, Hkv, Lloc, d))
+    Vlb, Vl = S.normal_bf16(58303, (B, Hkv, Lloc, d))
+    idx = np.stack([rng.permutation(N)[:B * M * k].reshape(B, M, k) for _ in range(S_)], axis=2).astype(np.int32)
+    idx[:, ::3, :, k // 2] = -1
+    idx[:, 1::5, :, 0] = N + 3
+    idx[0, 2] = -1
+    idx[0, 5, :, 1:] = -1
+    idx[0, 7, :, :k - 1] = -1
+    q_pos = (G + rng.integers(-1, Lloc, (B, M))).astype(np.int32)
+    args = [dev(qb), K, V, torch.from_numpy(idx).cuda(), dev(Klb), dev(Vlb), G, torch.from_numpy(q_pos).cuda()]
+    ws = torch.empty(msa.sparse_attend_workspace_bytes(cfg, B, M, k, Lloc), dtype=torch.uint8, device="cuda")
+    least = attend_least(cfg, args, ws)
+    assert least < ws.numel()
+    ws.fill_(0xFF)
+    out, lse = msa.msa_sparse_attend(cfg, *args, workspace=ws)
+    torch.cuda.synchronize()
+    up = lambda n: (n + 255) // 256 * 256
+    flags = least + up(S_ * N * 8) + up(S_ * N * 4)
+    assert (ws[flags + 4 * S_:flags + 8 * S_].view(torch.int32) == 1).all()      # every list in chains
+    ws.fill_(0xFF)
+    o2, l2 = msa.msa_sparse_attend(cfg, *args, workspace=ws[:least])
+    torch.cuda.synchronize()
+    x, y = o2.float(), out.float()
+    assert torch.isfinite(y).all() and (x - y).abs().max() <= 2.0 ** -7 * y.abs().max() + 1e-6
+    seen = torch.isfinite(l2)
+    assert torch.equal(torch.isfinite(lse), seen) and (l2 - lse)[seen].abs().max() <= 1e-4
+    if N * G > 1 << 18:
+        return
+    to64 = lambda t: t.float().cpu().numpy().astype(np.float64)
+    oo, ol = O.sparse_attend(q, to64(K), to64(V), np.where(idx >= N, -1, idx).astype(np.int64), Kl, Vl, G, q_pos, 1e6,
+                             lens=lens, mem_rotated=bool(rotated))
+    go = to64(out)
+    assert np.abs(go - oo).max() <= 2e-2 and np.linalg.norm(go - oo) <= 5e-3 * np.linalg.norm(oo)
+    seen = np.isfinite(ol)
+    assert np.abs(lse.cpu().numpy()[seen] - ol[seen]).max() <= 5e-3
