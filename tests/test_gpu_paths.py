@@ -482,6 +482,31 @@ def test_decode_attention_linear_split(N, Hkv, r, G, d, B, M, k, Lloc, scope, ro
         assert np.allclose(lse[b:b + 1].cpu().numpy(), ol, rtol=0, atol=5e-3)
 
 
+def attend_least(cfg, args, ws):
+    """The least workspace size that a call accepts (sizes above it are all accepted)."""
+    no, yes = 0, ws.numel()
+    while yes - no > 1:
+        mid = (no + yes) // 2
+        try:
+            msa.msa_sparse_attend(cfg, *args, workspace=ws[:mid])
+            yes = mid
+        except msa.MsaError as e:
+            assert e.status == msa.MSA_ERR_WORKSPACE
+            no = mid
+    return yes
+
+
+def docs_window(Hkv, r, G, d, S_, k, BM, tokens):
+    """Workspace of the document-by-document path that grows with the tokens of a window."""
+    up = lambda n: (n + 255) // 256 * 256
+    steps, parts = G // 32, 1
+    while parts < 4 and 2 * parts * k <= 128 and BM * k * Hkv * parts < 2048 and steps // (2 * parts) >= 4 and steps % (2 * parts) == 0:
+        parts *= 2
+    e, rows = S_ * tokens * k, tokens * Hkv * r
+    return (up(rows * d * 4) + up(e * 16) + up(e * 4) + up(S_ * tokens * 4 << (k - 1).bit_length()) +
+            up(rows * k * parts * d * 4) + up(rows * k * parts * 8))
+
+
 # (N, Hkv, r, G, d, B, M, k, Lloc, scope, rotated, ragged): many tokens with selections of their own, document by document
 ATT_DOCS = [
     (40, 2, 4, 128, 128, 1, 70, 30, 70, "group", 0, False),    # four tokens per item
@@ -498,9 +523,10 @@ ATT_DOCS = [
 
 @pytest.mark.parametrize("N,Hkv,r,G,d,B,M,k,Lloc,scope,rotated,ragged", ATT_DOCS)
 def test_attention_document_by_document(N, Hkv, r, G, d, B, M, k, Lloc, scope, rotated, ragged):
-    """Against the oracle, with pads, ids outside the bank and a document listed twice; then with smaller and smaller
-    workspaces, down to the first that is refused: windows of tokens, whose results are the same bits, and at last the
-    kernel that takes token by token, whose fp32 sums run in another order (one rounding to bf16: 2^-7 of the value)."""
+    """Against the oracle, with pads, ids outside the bank and a document listed twice; then with the smaller workspaces
+    that the path takes: windows of tokens, whose results are the same bits; and with one byte less than the smallest of
+    them and the least that is accepted, which the kernel that takes token by token serves, whose fp32 sums run in another
+    order (one rounding to bf16: 2^-7 of the value)."""
     say(f"by document N={N} Hkv={Hkv} r={r} G={G} d={d} B={B} M={M} k={k} Lloc={Lloc} {scope} rot={rotated} ragged={ragged}")
     rng = np.random.default_rng(58005)
     lens = rng.integers(1, G + 1, N).astype(np.int32) if ragged else None
@@ -530,23 +556,31 @@ def test_attention_document_by_document(N, Hkv, r, G, d, B, M, k, Lloc, scope, r
     seen = np.isfinite(ol)
     gl = lse.cpu().numpy()
     assert np.array_equal(np.isfinite(gl), seen) and np.abs(gl[seen] - ol[seen]).max() <= 5e-3
-    same = other = 0
-    for eighths in range(8, 0, -1):
-        part = ws[:size * eighths // 8]
+    least, BM = attend_least(cfg, args, ws), B * M
+    up = lambda n: (n + 255) // 256 * 256
+    path = least + up(S_ * N * 8) + up(S_ * N * 4) + up(S_ * 8)
+    need = lambda tokens: path + docs_window(Hkv, r, G, d, S_, k, BM, tokens)
+    assert need(BM) <= size
+    several = uneven = 0
+    for tokens in sorted({BM, BM - 1, BM // 2, 2 * BM // 5, 64} - set(range(min(64, BM))) - set(range(BM + 1, 65))):
+        part = ws[:need(tokens)]
         part.fill_(0xFF)
-        try:
-            o2, l2 = msa.msa_sparse_attend(cfg, *args, workspace=part)
-        except Exception:
-            break
+        o2, l2 = msa.msa_sparse_attend(cfg, *args, workspace=part)
         torch.cuda.synchronize()
-        if torch.equal(out.view(torch.int16), o2.view(torch.int16)) and torch.equal(lse, l2):
-            same += 1
-            continue
-        other += 1
+        assert torch.equal(out.view(torch.int16), o2.view(torch.int16)) and torch.equal(lse, l2), tokens
+        n = -(-BM // tokens)
+        several += n > 1
+        uneven += BM % -(-BM // n) != 0
+    assert several >= (BM > 64) and uneven >= (BM >= 200), (several, uneven)
+    for bytes_ in (need(min(64, BM)) - 1, least):
+        part = ws[:bytes_]
+        part.fill_(0xFF)
+        o2, l2 = msa.msa_sparse_attend(cfg, *args, workspace=part)
+        torch.cuda.synchronize()
+        assert not torch.equal(lse, l2)      # another order of the sums: the path was left
         x, y = o2.float(), out.float()
         assert (x - y).abs().max() <= 2.0 ** -7 * y.abs().max() + 1e-6
         assert (l2 - lse)[torch.isfinite(lse)].abs().max() <= 1e-4
-    assert same >= 1 and other >= 1, (same, other)
 
 
 @pytest.mark.parametrize("scope", ["group", "all"])
@@ -621,20 +655,6 @@ def test_attention_document_by_document_of_pads(scope, r, k):
     assert took[1] < took[0], took
 
 
-def attend_least(cfg, args, ws):
-    """The least workspace size that a call accepts (sizes above it are all accepted)."""
-    no, yes = 0, ws.numel()
-    while yes - no > 1:
-        mid = (no + yes) // 2
-        try:
-            msa.msa_sparse_attend(cfg, *args, workspace=ws[:mid])
-            yes = mid
-        except msa.MsaError as e:
-            assert e.status == msa.MSA_ERR_WORKSPACE
-            no = mid
-    return yes
-
-
 # (N, Hkv, r, G, d, B, M, k, Lloc, scope, rotated, ragged): no document in two selections, so that an item is a chain of a
 # token's documents, of up to ...
 ATT_CHAINS = [
@@ -682,6 +702,12 @@ def test_attention_of_selections_without_common_documents(N, Hkv, r, G, d, B, M,
     up = lambda n: (n + 255) // 256 * 256
     flags = least + up(S_ * N * 8) + up(S_ * N * 4)
     assert (ws[flags + 4 * S_:flags + 8 * S_].view(torch.int32) == 1).all()      # every list in chains
+    if B * M > 64:   # windows of tokens: the same bits
+        part = ws[:flags + up(S_ * 8) + docs_window(Hkv, r, G, d, S_, k, B * M, 70)]
+        part.fill_(0xFF)
+        o2, l2 = msa.msa_sparse_attend(cfg, *args, workspace=part)
+        torch.cuda.synchronize()
+        assert torch.equal(out.view(torch.int16), o2.view(torch.int16)) and torch.equal(lse, l2)
     ws.fill_(0xFF)
     o2, l2 = msa.msa_sparse_attend(cfg, *args, workspace=ws[:least])
     torch.cuda.synchronize()
