@@ -1005,7 +1005,8 @@ __global__ __launch_bounds__(kPoolThreads) void pool_tokens_kernel(const unsigne
 // survive together).  If more survive than LDS holds (ties), topk_of_ties takes over.
 constexpr int kRowSurv = 2048;
 constexpr int kRowRegs = 32;        // scores a thread keeps in registers between the two passes (8: short rows)
-constexpr int kRowPart = 8192;      // documents per part of a long row: what 32 registers per thread of four waves hold
+constexpr int kRowPart = 8192;      // documents per part of a long row: what 32 registers per thread of four waves hold, or
+                                    // 16 of eight
 
 struct RowsArgs {
   const float* mat;           // [selections][BM][stride]
@@ -1128,8 +1129,8 @@ static void launch_topk_rows(const RowsArgs& ra, hipStream_t st) {
 #define MSA_TOPK_ROWS(RR, WW) \
   hipLaunchKernelGGL((topk_rows_kernel<RR, WW>), dim3(blocks), dim3(64 * WW), 0, st, ra)
   if (n <= 8 * 256) MSA_TOPK_ROWS(8, 4);
-  else if (blocks <= 256 && n <= 16 * 512) MSA_TOPK_ROWS(16, 8);
-  else if (blocks > 256 || n <= kRowPart) MSA_TOPK_ROWS(kRowRegs, 4);
+  else if (blocks > 256) MSA_TOPK_ROWS(kRowRegs, 4);
+  else if (n <= kRowPart) MSA_TOPK_ROWS(kRowPart / 512, 8);
   else MSA_TOPK_ROWS(kRowRegs, 16);
 #undef MSA_TOPK_ROWS
 }
