@@ -18,6 +18,20 @@ from . import (MSA_ERR_HIP, MsaConfig, MsaError, msa_build_routing_keys, msa_fet
                alloc_routing_index, fetch_slots)
 
 
+def attention_beside_routing(n_layers, queries, index_bytes):
+    """Whether a step with every bank in device memory puts attention on a second stream, beside the next layer's scan.
+
+    The second stream costs about 13 us per step for its hand-over, and every layer but the last wins some of its attention
+    back: the more, the longer the scans and the more queries.  Measured over 150 shapes, us per step on one stream / on two
+    (8 heads of 128, 16 documents, 1024 local rows; n layers of x MB, q queries): 2 of 56 to 937, 1 to 16 q: 74 / 87 to 543 /
+    553; 3 of 93, 4 q 133 / 134; 3 of 187, 8 q 214 / 203; 4 of 31, 1 q 133 / 147; 4 of 56, 1 q 142 / 148, 8 q 169 / 157; 4 of
+    128, 1 q 199 / 190, 16 q 256 / 239; 4 of 1525, 8 q 1149 / 1128; 6 of 31, 8 q 234 / 214; 8 of 16, 1 q 231 / 260, 8 q 280 /
+    262; 18 of 23, 8 q 673 / 531.  The rule is at most 2 % from the better way there, and at most 4.4 % over 30 shapes with
+    longer attention, where a few workgroups more or less decide (16 q, 4096 local rows: 4 of 78 351 / 366, 4 of 128 385 / 397;
+    2048 rows, 32 documents: 4 of 64 258 / 265, 4 of 93 280 / 273)."""
+    return index_bytes * (n_layers - 2) >= (64 if queries >= 8 else 128) << 20
+
+
 class LayerStack:
     def __init__(self, cfg, n_layers, B, M, k, Lloc, tier="hbm", device="cuda"):
         """cfg: the config of the un-pooled bank (N documents of G tokens, chunk P).  tier: "hbm" keeps every
@@ -71,13 +85,7 @@ class LayerStack:
         # Four layers of 197 MB, 12 queries, the sixth stack of a program: 293 us with the pair, 350 with s_attend alone, 317 on
         # one stream.)
         self.s_route, self.s_attend = torch.cuda.Stream(device), torch.cuda.Stream(device)
-        # Attention beside the next layer's scan pays for its hand-over between streams where there are layers enough, the
-        # scan is long and the attention is more than a few workgroups; a scan of a GB has the memory to itself anyway.
-        # Layers of 8 heads of 128, us per step on one stream / on two: four layers with an index of 68 MB (16 queries) 266 /
-        # 274, 136 MB (8 queries) 225 / 210, 200 MB (8) 287 / 262, (2 queries) 261 / 302, 333 MB (8) 386 / 360; three of
-        # 136 MB 171 / 166, two of 268 MB 178 / 186, two of 1.6 GB 599 / 620.
-        index = self.KR[0].numel() * 2
-        self.two_streams = n_layers >= 4 and B * M >= 3 and 100 << 20 <= index <= 1 << 30
+        self.two_streams = attention_beside_routing(n_layers, B * M, self.KR[0].numel() * 2)
         self.last_id = None   # torch's number of the stream that the last step of the "hbm" tier was called on
         self.ev_scored = [torch.cuda.Event() for _ in range(n_layers)]
         self.ev_fork, self.ev_join, self.ev_captured = torch.cuda.Event(), torch.cuda.Event(), torch.cuda.Event()
