@@ -37,7 +37,9 @@
 namespace msa {
 
 constexpr int kGroupThreads = 1024;
-constexpr int kLdsDocs = 12288;  // 147456 bytes
+constexpr int kLdsDocs = 12288;     // 147456 bytes
+constexpr int kSeenDocs = 1 << 19;  // bits in LDS
+constexpr int kMaxChain = 4;        // documents of a chain
 constexpr int kPairs = 4;  // (token, slot) pairs of a thread at a time
 
 // ---- sort by document, rotated queries ----------------------------------------------------------------------
@@ -104,7 +106,8 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, Docs
   // list.)  A thread takes up to kPairs pairs at a time, their loads together.
   __shared__ unsigned long long base_s[LDS ? kLdsDocs : 1];
   __shared__ int cnt_s[LDS ? kLdsDocs : 1];
-  __shared__ int n_entries_s, n_items_s, n_valid_s, n_tiles_s;
+  __shared__ int n_entries_s, n_items_s, n_valid_s, n_docs_s;
+  __shared__ unsigned seen_s[LDS ? 1 : kSeenDocs / 32];
   const int s = blockIdx.x, lane = tid & 63;
   const int sh = da.kshift, E = da.n_tok << sh, T = da.tile_tok;
   int* const cnt = LDS ? cnt_s : da.cnt + (long long)s * a.N;
@@ -116,7 +119,7 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, Docs
     wait_stores_done();
     __syncthreads();
   };
-  if (tid == 0) n_entries_s = n_items_s = n_valid_s = n_tiles_s = 0;
+  if (tid == 0) n_entries_s = n_items_s = n_valid_s = n_docs_s = 0;
   int d[kPairs], rk[kPairs];  // document (-1: past the end, a pad, or no document of the bank), place among its pairs
   auto docs_at = [&](int e0, int tok_from, int pairs_to) {  // (no branch around a load)
     int x[kPairs];
@@ -134,7 +137,7 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, Docs
   auto read = [](auto* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); };
   const unsigned long long below = (1ull << lane) - 1ull;
   int have_from = -1, have_to = 0;  // the tokens whose documents and places are in registers
-  // the places of the pairs of [tok_from, tok_to) among those of their documents; `decide` counts pairs and tiles
+  // the places of the pairs of [tok_from, tok_to) among those of their documents; `decide` counts pairs and documents
   auto count_pairs = [&](int tok_from, int tok_to, bool decide) {
     const int to = (tok_to - tok_from) << sh;
     for (int e0 = 0; e0 < to; e0 += kPairs * kGroupThreads) {
@@ -145,7 +148,7 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, Docs
     }
     phase();
     const bool keep = to <= kPairs * kGroupThreads;
-    int n_valid = 0, n_tiles = 0;
+    int n_valid = 0, n_docs = 0;
     for (int e0 = 0; e0 < to; e0 += kPairs * kGroupThreads) {
       if (!keep) docs_at(e0, tok_from, to);
 #pragma unroll
@@ -159,24 +162,49 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, Docs
 #pragma unroll
         for (int i = 0; i < kPairs; ++i) {
           n_valid += __popcll(__ballot(d[i] >= 0));
-          n_tiles += __popcll(__ballot(d[i] >= 0 && rk[i] % T == 0));
+          n_docs += __popcll(__ballot(d[i] >= 0 && rk[i] == 0));
         }
       }
     }
     if (decide && lane == 0) {
       atomicAdd(&n_valid_s, n_valid);
-      atomicAdd(&n_tiles_s, n_tiles);
+      atomicAdd(&n_docs_s, n_docs);
     }
     phase();
     have_from = keep ? tok_from : -1;
     have_to = tok_to;
   };
   // Where hardly a document has a second token the pairs are taken as they come: chains of up to `chain` documents of one
-  // token, one partial each.  Decided over all tokens of the call, so that its windows change no bit.
+  // token, one partial each.  Decided over all tokens of the call, so that its windows change no bit: where there are several
+  // by a bit per document in LDS (counting all tokens in every window took 134 us for 2048 tokens of 8 of 32768, 85 without).
   const int t1 = da.tok0 + da.n_tok;
-  count_pairs(0, da.n_all, true);
-  const bool chains = 10ll * n_valid_s < 11ll * n_tiles_s;
-  if (!chains && da.n_tok != da.n_all) count_pairs(da.tok0, t1, false);
+  const bool whole = da.n_tok == da.n_all;
+  if (whole || a.N > (LDS ? 32 * kLdsDocs : kSeenDocs)) {
+    count_pairs(0, da.n_all, true);
+  } else {
+    unsigned* const seen = LDS ? reinterpret_cast<unsigned*>(cnt_s) : seen_s;
+    for (int i = tid; i <= (a.N - 1) / 32; i += kGroupThreads) seen[i] = 0u;
+    __syncthreads();
+    const int to = da.n_all << sh;
+    int n_valid = 0, n_docs = 0;
+    for (int e0 = 0; e0 < to; e0 += kPairs * kGroupThreads) {
+      docs_at(e0, 0, to);
+#pragma unroll
+      for (int i = 0; i < kPairs; ++i) {
+        const unsigned bit = 1u << (d[i] & 31);
+        const bool first = d[i] >= 0 && (atomicOr(seen + (d[i] >> 5), bit) & bit) == 0;
+        n_valid += __popcll(__ballot(d[i] >= 0));
+        n_docs += __popcll(__ballot(first));
+      }
+    }
+    if (lane == 0) {
+      atomicAdd(&n_valid_s, n_valid);
+      atomicAdd(&n_docs_s, n_docs);
+    }
+    __syncthreads();
+  }
+  const bool chains = 10ll * n_valid_s < 11ll * n_docs_s;
+  if (!chains && !whole) count_pairs(da.tok0, t1, false);
   const bool once = have_from == da.tok0 && have_to == t1;  // documents and ranks of all pairs stay in registers
   if (chains) {
     const unsigned long long mine = (sh == 6 ? ~0ull : (1ull << (1 << sh)) - 1ull) << (lane & ~((1 << sh) - 1) & 63);
@@ -293,7 +321,6 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, Docs
 }
 
 constexpr int kFetch = 32, kFetchPairs = 192;  // items looked up at a time, at most: 32 of up to four entries, 12 of sixteen
-constexpr int kMaxChain = 4;
 
 // ---- attention, document by document -------------------------------------------------------------------------
 template <int D, bool ROT>  // ROT: raw bank keys, rotated here with positions 0..G-1; else used as stored
