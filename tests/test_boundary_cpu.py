@@ -312,7 +312,7 @@ SECOND_STREAM = [
     (4, 16, 56, 1.058), (4, 8, 56, 1.076), (4, 4, 56, 1.016), (4, 1, 128, 1.047), (4, 8, 128, 1.062), (4, 2, 187, 1.072),
     (4, 8, 515, 1.034), (4, 8, 1525, 1.018), (4, 8, 93, 0.987), (6, 1, 15, 0.856), (6, 8, 31, 1.097), (6, 1, 56, 1.049),
     (6, 12, 128, 1.144), (8, 1, 15, 0.889), (8, 8, 15, 1.071), (8, 1, 31, 0.988), (8, 8, 31, 1.227), (8, 1, 78, 1.131),
-    (18, 8, 23, 1.268), (18, 1, 56, 1.264),
+    (18, 8, 23, 1.268), (18, 1, 56, 1.264), (18, 8, 1525, 1.042), (8, 8, 1525, 1.032),
 ]
 # ... with long attention (32 documents and 2048 local rows, or 16 and 4096)
 SECOND_STREAM_LONG = [
