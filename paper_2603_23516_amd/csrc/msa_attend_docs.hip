@@ -43,7 +43,9 @@ constexpr int kMaxChain = 4;        // documents of a chain
 constexpr int kPairs = 4;  // (token, slot) pairs of a thread at a time
 
 // ---- sort by document, rotated queries ----------------------------------------------------------------------
-template <int D, bool LDS>  // LDS: a document's counters fit there (N <= kLdsDocs)
+// LDS: a document's counters fit there (N <= kLdsDocs).  WHOLE: the call is one window (a form of its own: with the code for
+// several in it 512 tokens of 8 of 4096 documents take 759 us, else 752).
+template <int D, bool LDS, bool WHOLE>
 __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
   constexpr int HALF = D / 2;
   const int tid = threadIdx.x;
@@ -107,7 +109,7 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, Docs
   __shared__ unsigned long long base_s[LDS ? kLdsDocs : 1];
   __shared__ int cnt_s[LDS ? kLdsDocs : 1];
   __shared__ int n_entries_s, n_items_s, n_valid_s, n_docs_s;
-  __shared__ unsigned seen_s[LDS ? 1 : kSeenDocs / 32];
+  __shared__ unsigned seen_s[LDS || WHOLE ? 1 : kSeenDocs / 32];
   const int s = blockIdx.x, lane = tid & 63;
   const int sh = da.kshift, E = da.n_tok << sh, T = da.tile_tok;
   int* const cnt = LDS ? cnt_s : da.cnt + (long long)s * a.N;
@@ -178,8 +180,7 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, Docs
   // token, one partial each.  Decided over all tokens of the call, so that its windows change no bit: where there are several
   // by a bit per document in LDS (counting all tokens in every window took 134 us for 2048 tokens of 8 of 32768, 85 without).
   const int t1 = da.tok0 + da.n_tok;
-  const bool whole = da.n_tok == da.n_all;
-  if (whole || a.N > (LDS ? 32 * kLdsDocs : kSeenDocs)) {
+  if (WHOLE || a.N > (LDS ? 32 * kLdsDocs : kSeenDocs)) {
     count_pairs(0, da.n_all, true);
   } else {
     unsigned* const seen = LDS ? reinterpret_cast<unsigned*>(cnt_s) : seen_s;
@@ -204,7 +205,7 @@ __global__ __launch_bounds__(kGroupThreads) void group_kernel(AttendArgs a, Docs
     __syncthreads();
   }
   const bool chains = 10ll * n_valid_s < 11ll * n_docs_s;
-  if (!chains && !whole) count_pairs(da.tok0, t1, false);
+  if (!WHOLE && !chains) count_pairs(da.tok0, t1, false);
   const bool once = have_from == da.tok0 && have_to == t1;  // documents and ranks of all pairs stay in registers
   if (chains) {
     const unsigned long long mine = (sh == 6 ? ~0ull : (1ull << (1 << sh)) - 1ull) << (lane & ~((1 << sh) - 1) & 63);
@@ -1024,16 +1025,21 @@ int launch_attend_docs(const Dims& dm, const DocsPlan& pl, const AttendArgs& a0,
     long long wgs = ((long long)da.n_tok * a.k * dm.Hkv * pl.parts + kAttWaves - 1) / kAttWaves;
     wgs = wgs < 512 ? (wgs + 7) / 8 * 8 : 512;
     const long long rows = (long long)da.n_tok * dm.Hq;
+#define MSA_GROUP(DD, LL) \
+  do { \
+    if (pl.tokens >= BM) hipLaunchKernelGGL((group_kernel<DD, LL, true>), ggrid, dim3(kGroupThreads), 0, st, a, da, th); \
+    else hipLaunchKernelGGL((group_kernel<DD, LL, false>), ggrid, dim3(kGroupThreads), 0, st, a, da, th); \
+  } while (0)
 #define MSA_DOCS(DD) \
   do { \
-    if (dm.N <= kLdsDocs) hipLaunchKernelGGL((group_kernel<DD, true>), ggrid, dim3(kGroupThreads), 0, st, a, da, th); \
-    else hipLaunchKernelGGL((group_kernel<DD, false>), ggrid, dim3(kGroupThreads), 0, st, a, da, th); \
+    if (dm.N <= kLdsDocs) MSA_GROUP(DD, true); else MSA_GROUP(DD, false); \
     if (bank_keys_rotated) hipLaunchKernelGGL((attend_docs_kernel<DD, false>), dim3((unsigned)wgs), dim3(256), 0, st, a, da, th); \
     else hipLaunchKernelGGL((attend_docs_kernel<DD, true>), dim3((unsigned)wgs), dim3(256), 0, st, a, da, th); \
   } while (0)
     if (dm.d == 128) MSA_DOCS(128);
     else MSA_DOCS(64);
 #undef MSA_DOCS
+#undef MSA_GROUP
     const int rc = launch_merge2(dm.d, da.part_o, da.part_ml, a.k * pl.parts, loc_o, loc_ml, n_loc, (uint16_t*)out, lse,
                                  (long long)t0 * dm.Hq, rows, st, da.n_items + S, da.n_chains * pl.parts, dm.Hq, dm.Hq / S);
     if (rc != MSA_OK) return rc;
