@@ -39,7 +39,7 @@ namespace msa {
 constexpr int kGroupThreads = 1024;
 constexpr int kLdsDocs = 12288;     // 147456 bytes
 constexpr int kSeenDocs = 1 << 19;  // bits in LDS
-constexpr int kMaxChain = 4;        // documents of a chain
+constexpr int kMaxChain = 4;        // documents of a chain (entries per item: 1 << 2 at least)
 constexpr int kPairs = 4;  // (token, slot) pairs of a thread at a time
 
 // ---- sort by document, rotated queries ----------------------------------------------------------------------
@@ -379,7 +379,7 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
     int upto = lane < a.Hkv ? da.n_items[a.idx_sel == 1 ? 0 : lane] : 0;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
-      const int x = __shfl_up(upto, off, 64);
+      const int x = __builtin_amdgcn_ds_bpermute((lane - off) * 4, upto);  // (from the opaque number, see head_row)
       if (lane >= off) upto += x;
     }
     return upto;
@@ -396,15 +396,17 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
   // entries: the (token, slot) of each of the item's tokens, or each of a chain's documents (the last one again past their
   // number).
   // In LDS: the stream below has no registers for them.
-  const int T = da.tile_tok, tl = n / a.r;  // (r is a power of two: tl < T)
-  const int per_item = T < kMaxChain ? kMaxChain : T;
-  const int n_fetch = kFetch * per_item <= kFetchPairs ? kFetch : kFetchPairs / per_item;
+  // (r, T, the entries per item and the parts are powers of two: shifts, since a division's reciprocal would be kept across
+  // the stream, spill, and be reloaded with everything in flight awaited)
+  const int T = da.tile_tok, rshift = 31 - __clz(a.r), pshift = 31 - __clz(da.parts);
+  const int eshift = T < kMaxChain ? 2 : 31 - __clz(T);
+  const int n_fetch = (kFetchPairs >> eshift) < kFetch ? kFetchPairs >> eshift : kFetch;
   auto fetch_items = [&](int x0) {
     int ln = lane;
     asm volatile("" : "+v"(ln));
     const int x = x0 + ln * stride;
     const int upto = items_upto();
-    const int xi = x / da.parts, part = x - xi * da.parts;
+    const int xi = x >> pshift, part = x - (xi << pshift);
     int g = 0, before = 0;
     for (int i = 0; i < a.Hkv; ++i) {
       const int u = __builtin_amdgcn_readlane(upto, i);
@@ -428,10 +430,10 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
       first = list * da.cap + it.y;
       cnt = it.z;
     }
-    for (int p0 = 0; p0 < n_fetch * per_item; p0 += 64) {
-      const int p = p0 + ln, of = p / per_item, i = p - of * per_item;
+    for (int p0 = 0; p0 < n_fetch << eshift; p0 += 64) {
+      const int p = p0 + ln, of = p >> eshift, i = p - (of << eshift);
       const int f = __shfl(first, of & 63, 64), c = __shfl(cnt, of & 63, 64);
-      if (p < n_fetch * per_item && c > 0) entry[wave][p] = da.entries[f + (i < c ? i : c - 1)];
+      if (of < n_fetch && c > 0) entry[wave][p] = da.entries[f + (i < c ? i : c - 1)];
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -462,7 +464,7 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
     s.off = (((long long)doc * a.Hkv + g) * a.G + p0) * D;
   };
   auto open_of_chain = [&](Step& s) {
-    const int doc = __builtin_amdgcn_readfirstlane(entry[wave][c_lane * per_item + c_doc]);
+    const int doc = __builtin_amdgcn_readfirstlane(entry[wave][(c_lane << eshift) + c_doc]);
     int len = a.G;
     if (a.lens != nullptr) {  // (a scalar load: a vector load would be awaited with everything in flight)
       len = ((const __attribute__((address_space(4))) int32_t*)a.lens)[doc];
@@ -481,7 +483,9 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
       s.pair = x;
       open_of_chain(s);
     } else {
-      s.pair = entry[wave][c_lane * per_item + tl];
+      int ln = lane;
+      asm volatile("" : "+v"(ln));
+      s.pair = entry[wave][(c_lane << eshift) + ((ln & 15) >> rshift)];  // (that is under T)
       open_rows(s, x, __builtin_amdgcn_readfirstlane(d.y));
     }
   };
