@@ -688,7 +688,7 @@ void attend_docs_kernel(AttendArgs a, DocsArgs da, RopeTheta th) {
           for (int j = 0; j < 8; ++j) {
             const int u = 32 * s2i + 8 * rr_ + j;
             cs[8 * s2i + j] = cmul(estart[wv][u], base0[n_][u]);
-            if (j & 1) __builtin_amdgcn_sched_barrier(0);
+            if (j & 1) __builtin_amdgcn_sched_barrier(0);  // (all 64 reads ahead of the products would spill the stream)
           }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -935,7 +935,8 @@ static int docs_parts(const Dims& dm, long long BM, int k) {
 //   300 of 16 of 8192, r = 8             716 -> 588    842 -> 806    860 -> 960
 // and 16 tokens of 16 of 64 documents 91 -> 71.  On the other side of the lines: 64 of 4 of 8192 82 -> 86, 32 of 20 of 2000
 // (two heads of 64) 45 -> 67, 64 of 4 of 128 (64 rows of 64) 27 -> 31.  Sharing grows with the tokens of a topic: 16 tokens
-// under 1 GiB (16 of 8000, 1024 rows) 176 -> 174, 199 -> 213, 200 -> 215, and with r = 8, where an item takes two tokens, 32
+// under 2.5 GiB (16 of 8000, 1024 rows) 174 -> 178, 200 -> 218, 202 -> 220, (64 of 8000) 333 -> 318, 353 -> 380, 357 -> 387,
+// where 20 of 32 of 8192 (1024 rows) go 490 -> 360, 515 -> 469, 519 -> 471; and with r = 8, where an item takes two tokens, 32
 // (32 of 8192) 180 -> 182, 191 -> 211, 196 -> 216, and 2 x 64 (16 of 4096, 128 rows) 95 -> 93, 107 -> 115, 108 -> 128.
 bool docs_path_applies(const Dims& dm, int B, int M, int k) {
   const long long S = dm.scope_all ? 1 : dm.Hkv, pairs = (long long)B * M * k, items = pairs * dm.Hkv;
@@ -943,7 +944,7 @@ bool docs_path_applies(const Dims& dm, int B, int M, int k) {
   if (dm.G % 32 != 0 || dm.Hkv > 64 || S * dm.N > (8 << 20)) return false;
   const bool certain = pairs >= 2ll * dm.N;
   if (!certain && dm.r == 8 && M < 128) return false;
-  return bytes >= (1ll << 30) || (items >= 3072 && bytes >= (96ll << 20) && (certain || M >= 32)) ||
+  return bytes >= (certain || M >= 32 ? 1ll << 30 : 5ll << 29) || (items >= 3072 && bytes >= (96ll << 20) && (certain || M >= 32)) ||
          (certain && bytes >= (256ll << 20));
 }
 

@@ -191,11 +191,11 @@ def small_stack(two):
     return stack, args
 
 
-def apart():
-    """Two streams that run beside each other (streams share a few hardware queues)."""
+def apart(n):
+    """A stream and n more whose work it does not hold up (streams share a few hardware queues)."""
     x = torch.zeros(1, device="cuda")
-    first = torch.cuda.Stream()
-    for other in [torch.cuda.Stream() for _ in range(8)]:
+    first, others = torch.cuda.Stream(), []
+    for other in [torch.cuda.Stream() for _ in range(12)]:
         torch.cuda.synchronize()
         with torch.cuda.stream(first):
             torch.cuda._sleep(200_000_000)
@@ -203,16 +203,18 @@ def apart():
             x.add_(1)
         other.synchronize()
         if not first.query():
-            torch.cuda.synchronize()
-            return first, other
-    pytest.skip("no two streams run beside each other here")
+            others.append(other)
+        torch.cuda.synchronize()
+        if len(others) == n:
+            return first, others
+    pytest.skip("no streams run beside each other here")
 
 
 @pytest.mark.parametrize("two", [False, True])
 def test_step_waits_for_the_step_before_alone(two):
     """Work that a caller put on its stream behind a step does not hold up the next step from another stream."""
     stack, args = small_stack(two)
-    first, other = apart()
+    first, (other, stack.s_attend) = apart(2)
     stack.step(*args)
     torch.cuda.synchronize()
     want = [o.clone() for o in args[5]]

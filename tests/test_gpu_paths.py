@@ -662,7 +662,7 @@ ATT_CHAINS = [
     (800, 8, 4, 64, 64, 1, 128, 6, 40, "group", 0, True),       # ... three, two per token
     (1600, 2, 8, 64, 128, 1, 128, 12, 50, "all", 1, True),      # ... two; items of two tokens were they shared
     (1600, 4, 1, 64, 64, 2, 48, 16, 32, "group", 1, True),      # ... four; of sixteen
-    (400, 4, 2, 2048, 128, 1, 20, 16, 33, "group", 0, True),    # ... one, the documents in two parts
+    (300, 4, 2, 2048, 128, 1, 32, 8, 33, "group", 0, True),     # ... one, the documents in two parts
     (13000, 1, 4, 32, 64, 1, 800, 16, 40, "group", 0, False),   # counters in memory, documents looked up again by every phase
     (530000, 1, 4, 32, 64, 1, 400, 32, 40, "group", 0, False),  # ... more documents than have a bit in LDS
 ]
