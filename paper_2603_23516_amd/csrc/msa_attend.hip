@@ -48,7 +48,8 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
   constexpr int NU = (NS / 2) * 8;  // rotation pairs per lane
   constexpr int NCB = D / 16;       // output column blocks
   constexpr int VBYTES = 32 * D * 2;  // the 32 value rows of a step in LDS
-  constexpr int OBYTES = 16 * D * 4;  // one wave's partial output in the merge
+  constexpr int OROW = D + 4;            // floats per row of a wave's partial output in the merge (rows start in other banks)
+  constexpr int OBYTES = 16 * OROW * 4;
   constexpr int STAGE = (2 * VBYTES > OBYTES ? 2 * VBYTES : OBYTES);  // two value stages per wave
 
   __shared__ float2 base0[16][HALF];  // e^{i n theta_u}: positions 0..15
@@ -75,7 +76,10 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
   int tid = threadIdx.x;
   if (LIN) asm volatile("" : "+v"(tid));
   const int lane = tid & 63;
-  const int wave = LIN ? __builtin_amdgcn_readfirstlane(tid >> 6) : tid >> 6;
+  // the same in every lane, which the compiler cannot tell from the thread number: where a step's rows lie is then worked
+  // out in scalar registers (1746 -> 1598 vector instructions per two steps at d = 128; a wave alone on its SIMD is bound
+  // by issuing them, 1.5 us a step)
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rr = lane >> 4;
   const int n = lane & 15;
   int sp = blockIdx.x, g = blockIdx.y, bm = blockIdx.z;
@@ -230,31 +234,33 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
     const uint16_t* Kb;
     const uint16_t* Vb;
     int rows_valid, p_first;
-    int st;         // step number
+    int slot, pin;  // MODE 0, 1, whole slots, memory steps: slot of the selection, first row of the step in its document
+    int doc;        // MODE 2, memory steps: document of the step's key row `lane % 32`
     unsigned mask;  // MODE 2, memory steps: bit i set = key row i belongs to a valid selection
     bool is_mem;    // a step over selected documents (else local context)
   };
-  // MODE 2: bank element offset of key row `row` (0..31) of memory step st, and whether its document
-  // is a valid selection.  Rows of pads, of ids outside the bank and past the k-th document point at
-  // document 0 (always present) so that their loads stay inside the bank; their scores are masked.
-  auto gather_row = [&](int st, int row, long long& off) -> bool {
-    const int tok = st * 32 + row;
+  // MODE 2: the document of every key row of memory step st, once per step in lanes 0 .. 31 (and again in 32 .. 63); the
+  // requests below fetch it from the lane that has it.  Rows of pads, of ids outside the bank and past the k-th document
+  // read document 0 (always present) so that their loads stay inside the bank; their scores are masked.
+  auto gather_rows = [&](int st, StepSrc& ss) {
+    const int tok = st * 32 + (lane & 31);
     const int slot = tok >> a.gshift;
     const int pin = tok & (a.G - 1);
     const int doc = __shfl(my_idx, slot < a.k ? slot : 0, 64);
     const int len = __shfl(my_len, slot < a.k ? slot : 0, 64);
     const bool ok = slot < a.k && doc >= 0 && doc < a.N && pin < len;
-    off = (((long long)(ok ? doc : 0) * a.Hkv + g) * a.G + (ok ? pin : 0)) * D;
-    return ok;
+    ss.doc = ok ? doc : 0;
+    ss.mask = (unsigned)__ballot(ok);  // lanes 0..31 cover the 32 rows
+  };
+  // ... and the byte offset of key row `row`, whose document is `doc`, in the bank (G <= 16 divides a step)
+  auto row_offset = [&](int doc, int row) -> unsigned long long {
+    return (unsigned long long)(unsigned)doc * (unsigned)(a.Hkv * a.G * D * 2) + (unsigned)((g * a.G + (row & (a.G - 1))) * D * 2);
   };
   auto locate = [&](int st, StepSrc& ss) -> bool {
-    ss.st = st;
     ss.mask = 0xffffffffu;
     ss.is_mem = st < mem_steps;
     if (MODE == 2 && st < mem_steps) {
-      long long off;
-      const bool ok = gather_row(st, lane & 31, off);
-      ss.mask = (unsigned)__ballot(ok);  // lanes 0..31 cover the 32 rows
+      gather_rows(st, ss);
       ss.Kb = a.K;
       ss.Vb = a.V;
       ss.rows_valid = 32;
@@ -269,9 +275,8 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
         slot = __popcll(__ballot(pre <= st));
         pin = (st - (slot > 0 ? __builtin_amdgcn_readlane(pre, slot - 1) : 0)) * 32;
       } else {
-        const int tok = st * 32;
-        slot = tok / a.G;
-        pin = tok - slot * a.G;
+        slot = ss.slot;
+        pin = ss.pin;
       }
       const int doc = __builtin_amdgcn_readlane(my_idx, slot);
       if (doc < 0 || doc >= a.N) return false;  // -1 pads, and ids outside the bank, are skipped
@@ -293,9 +298,27 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
     ss.p_first = a.pos0 + t0;
     return true;
   };
-  auto next_valid = [&](int st, StepSrc& ss) -> int {  // first step >= st with keys, or we
-    while (st < we && !locate(st, ss)) ++st;
+  auto place = [&](int st, StepSrc& ss) {  // (slot, pin) of step st
+    if (MODE == 2 || compact || st >= mem_steps) return;
+    ss.slot = st * 32 / a.G;
+    ss.pin = st * 32 - ss.slot * a.G;
+  };
+  auto follow = [&](StepSrc& ss) {  // ... of the step after
+    ss.pin += 32;
+    const bool over = ss.pin >= a.G;
+    ss.slot += over ? 1 : 0;
+    ss.pin = over ? 0 : ss.pin;
+  };
+  auto first_valid = [&](int st, StepSrc& ss) -> int {  // first step >= st (which ss is at) with keys, or we
+    while (st < we && !locate(st, ss)) {
+      ++st;
+      follow(ss);
+    }
     return st;
+  };
+  auto next_valid = [&](int st, StepSrc& ss) -> int {  // first step > st (which ss is at) with keys, or we
+    follow(ss);
+    return first_valid(st + 1, ss);
   };
   // Requests of one step.  The step's base addresses are wave-uniform (scalar registers) and every lane adds a
   // 32-bit byte offset, worked out here from an opaque copy of the lane number every time (a few instructions,
@@ -322,10 +345,9 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
     if (MODE == 2 && ss.is_mem) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        long long off;
-        gather_row(ss.st, 16 * h + n, off);
+        const unsigned long long off = row_offset(__shfl(ss.doc, 16 * h + n, 64), n);
 #pragma unroll
-        for (int s = 0; s < NS; ++s) kr[h][s] = ld((gvec_t)(kb + (off * 2 + 16 * rr + s * 64)));
+        for (int s = 0; s < NS; ++s) kr[h][s] = ld((gvec_t)(kb + (off + 16 * rr + s * 64)));
       }
     } else {
       const int last = ss.rows_valid - 1;
@@ -356,9 +378,8 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
         const int f = i * 64 + ln;
         const int row = f / PPR;
         const int piece = (f % PPR) ^ (2 * (row & 3));
-        long long off;
-        gather_row(ss.st, row, off);
-        copy16_to_lds_async_stream64(reinterpret_cast<const char*>(a.V) + (off * 2 + piece * 16), dst + i * 1024);
+        const unsigned long long off = row_offset(__shfl(ss.doc, row, 64), row);
+        copy16_to_lds_async_stream64(reinterpret_cast<const char*>(a.V) + (off + piece * 16), dst + i * 1024);
       }
     } else {
       const void* vb = reinterpret_cast<const void*>(uni64((unsigned long long)ss.Vb));
@@ -386,15 +407,18 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
   // step the requests repeat the last one (results unused), so the number of requests in flight never depends on
   // the path.  Two turns per trip of the loop, so that the two sets of key registers have fixed names.
   StepSrc s0, s1, s2;
-  int st0 = next_valid(wb, s0);
+  s0.slot = s0.pin = 0;
+  s0.doc = 0;
+  place(wb, s0);
+  int st0 = first_valid(wb, s0);
   int st1 = we, st2 = we;
   uint4 kA[2][NS], kB[2][NS];
   if (st0 < we) {
     s1 = s0;
-    st1 = next_valid(st0 + 1, s1);
+    st1 = next_valid(st0, s1);
     if (st1 >= we) s1 = s0;
     s2 = s1;
-    if (st1 < we) st2 = next_valid(st1 + 1, s2);
+    if (st1 < we) st2 = next_valid(st1, s2);
     if (st2 >= we) s2 = s1;
     issue_keys(s0, kA);
     issue_values(s0, 0);
@@ -569,7 +593,7 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
     s1 = s2;
     if (st2 < we) {
       StepSrc s3 = s2;
-      st2 = next_valid(st2 + 1, s3);
+      st2 = next_valid(st2, s3);
       if (st2 < we) s2 = s3;
     }
   };
@@ -590,11 +614,11 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
   l_run += __shfl_xor(l_run, 32, 64);
   __syncthreads();  // every wave is done with its value staging area
   {
-    float* wo = reinterpret_cast<float*>(&stage[wave][0]);  // [16 slots][D]
+    float* wo = reinterpret_cast<float*>(&stage[wave][0]);  // [16 slots][OROW]
 #pragma unroll
     for (int c = 0; c < NCB; ++c)
 #pragma unroll
-      for (int i = 0; i < 4; ++i) wo[n * D + 16 * c + 4 * rr + i] = o[c][i];
+      for (int i = 0; i < 4; ++i) wo[n * OROW + 16 * c + 4 * rr + i] = o[c][i];
     if (rr == 0) {
       wm[wave][n] = m_run;
       wl[wave][n] = l_run;
@@ -619,7 +643,7 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
           const float mw = wm[w][s0];
           const float f = (mw == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mw - mx);
           const float2* wo = reinterpret_cast<const float2*>(&stage[w][0]) + d2;
-          const float2 x = wo[s0 * (D / 2)], y = wo[(s0 + 1) * (D / 2)];
+          const float2 x = wo[s0 * (OROW / 2)], y = wo[(s0 + 1) * (OROW / 2)];
           o0 += f * (x.x + y.x);
           o1 += f * (x.y + y.y);
           lsum += f * wl[w][s0];
@@ -646,7 +670,7 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
         const float mw = wm[w][s0];
         const float f = (mw == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(mw - mx);
         const float* wo = reinterpret_cast<const float*>(&stage[w][0]);
-        osum += f * (wo[s0 * D + dd] + wo[(s0 + 1) * D + dd]);
+        osum += f * (wo[s0 * OROW + dd] + wo[(s0 + 1) * OROW + dd]);
         lsum += f * wl[w][s0];
       }
     }
@@ -674,71 +698,35 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
   }
   __syncthreads();
   if (!last_s) return;
-  // (m, l) of every (head, split) and the partials of the thread's first output elements, all loads independent; the
-  // staging area is free again (every wave passed the barriers above after its last use)
-  // (ns <= kMaxFused)
-  float2* mls = reinterpret_cast<float2*>(&stage[0][0]);  // [r][ns]: (max, sum), then (weight, sum)
-  auto part_of = [&](int e) {  // a thread owns two adjacent output elements of one head
-    const long long qh = (long long)bm * a.Hq + g * a.r + e / (D / 2);
-    return reinterpret_cast<const unsigned long long*>(a.part_o + qh * a.ph_splits * D) + e % (D / 2);
-  };
-  unsigned long long v[kMaxFused];
-  auto fetch = [&](int e) {
-    const unsigned long long* po = part_of(e < a.r * (D / 2) ? e : 0);
-#pragma unroll
-    for (int u = 0; u < kMaxFused; ++u) v[u] = load_dev(po + (long long)(u < ns ? u : ns - 1) * (D / 2));
-  };
-  unsigned long long ml_v[kMaxFused * 8 / 256 + 1];
-#pragma unroll
-  for (int i = 0; i <= kMaxFused * 8 / 256; ++i) {
-    int t = tid + 256 * i;
-    t = t < a.r * ns ? t : 0;
-    const int hh = t / ns, s = t - hh * ns;
-    const long long qh = (long long)bm * a.Hq + g * a.r + hh;
-    ml_v[i] = load_dev(reinterpret_cast<const unsigned long long*>(a.part_ml + qh * a.ph_splits + s));
-  }
-  fetch(tid);
-#pragma unroll
-  for (int i = 0; i <= kMaxFused * 8 / 256; ++i) {
-    const int t = tid + 256 * i;
-    if (t < a.r * ns) mls[t] = __builtin_bit_cast(float2, ml_v[i]);
-  }
-  lds_barrier();
-  for (int hh = wave; hh < a.r; hh += kAttWaves) {  // one wave per head: maximum, weights, normaliser
-    float mx = -INFINITY;
-    for (int s = lane; s < ns; s += 64) mx = fmaxf(mx, mls[hh * ns + s].x);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    float lsum = 0.f;
-    for (int s = lane; s < ns; s += 64) {
-      const float2 x = mls[hh * ns + s];
-      const float f = (x.x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(x.x - mx);
-      mls[hh * ns + s].x = f;
-      lsum += f * x.y;
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
-    if (lane == 0) {
-      wm[0][hh] = mx;
-      wl[0][hh] = lsum;
-    }
-  }
-  lds_barrier();
+  // A thread owns two adjacent output elements of one head; it asks for the (m, l) pairs and the partials of all splits
+  // (ns <= kMaxFused) at once and works the weights out itself: nothing to wait for but these loads (with the weights of
+  // every head made once, by a wave each, and handed over through LDS: 2.2 us from the last arrival to the result, now 1.4).
   for (int e = tid; e < a.r * (D / 2); e += 256) {
     const int hh = e / (D / 2), d2 = e % (D / 2);
     const long long qh = (long long)bm * a.Hq + g * a.r + hh;
-    const float2* w = mls + hh * ns;
-    if (e != tid) fetch(e);
-    float o0 = 0.f, o1 = 0.f;
+    const unsigned long long* po = reinterpret_cast<const unsigned long long*>(a.part_o + qh * a.ph_splits * D) + d2;
+    const unsigned long long* pm = reinterpret_cast<const unsigned long long*>(a.part_ml + qh * a.ph_splits);
+    unsigned long long v[kMaxFused], ml[kMaxFused];
+#pragma unroll
+    for (int u = 0; u < kMaxFused; ++u) {
+      const int at = u < ns ? u : ns - 1;
+      ml[u] = load_dev(pm + at);
+      v[u] = load_dev(po + (long long)at * (D / 2));
+    }
+    float mx = -INFINITY;
+#pragma unroll
+    for (int u = 0; u < kMaxFused; ++u) mx = fmaxf(mx, __builtin_bit_cast(float2, ml[u]).x);
+    float o0 = 0.f, o1 = 0.f, lsum = 0.f;
 #pragma unroll
     for (int u = 0; u < kMaxFused; ++u) {
       if (u < ns) {
-        const float2 x = __builtin_bit_cast(float2, v[u]);
-        o0 += w[u].x * x.x;
-        o1 += w[u].x * x.y;
+        const float2 m = __builtin_bit_cast(float2, ml[u]), x = __builtin_bit_cast(float2, v[u]);
+        const float f = (m.x == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m.x - mx);
+        lsum += f * m.y;
+        o0 += f * x.x;
+        o1 += f * x.y;
       }
     }
-    const float lsum = wl[0][hh], mx = wm[0][hh];
     const float r0 = (lsum > 0.f) ? o0 / lsum : 0.f, r1 = (lsum > 0.f) ? o1 / lsum : 0.f;
     reinterpret_cast<uint32_t*>(a.final_out + qh * D)[d2] = pack_bf16(r0, r1);
     if (a.final_lse != nullptr && d2 == 0)
