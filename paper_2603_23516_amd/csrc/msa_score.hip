@@ -187,18 +187,20 @@ __device__ __forceinline__ void fold_query_tile(const FoldRegs<D>& fr, long long
   }
   wave_sync();
   const int rr = lane >> 4, n = lane & 15;
+  uint32_t w[NS][4];  // (all of qf is read before the operands are written: they may lie in the same place)
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
-    uint32_t w[4];
 #pragma unroll
     for (int jj = 0; jj < 4; ++jj) {
       float h0, l0, h1, l1;
       split_bf16(qf[(n >> 1) * D + 32 * s + 8 * rr + 2 * jj], h0, l0);
       split_bf16(qf[(n >> 1) * D + 32 * s + 8 * rr + 2 * jj + 1], h1, l1);
-      w[jj] = (n & 1) ? pack_bf16(l0, l1) : pack_bf16(h0, h1);
+      w[s][jj] = (n & 1) ? pack_bf16(l0, l1) : pack_bf16(h0, h1);
     }
-    aop[s][lane] = make_uint4(w[0], w[1], w[2], w[3]);
   }
+  wave_sync();
+#pragma unroll
+  for (int s = 0; s < NS; ++s) aop[s][lane] = make_uint4(w[s][0], w[s][1], w[s][2], w[s][3]);
   wave_sync();
 }
 
@@ -672,6 +674,10 @@ constexpr int kAllWaves = 8;
 constexpr int kAllRun = 16;  // documents a wave collects per query before it writes them
 
 constexpr int kAllGroups = 256;  // workgroups: one per CU
+// (head, 8 queries) tiles that a workgroup of the all-heads scan folds itself: one for each of its waves, which takes less than
+// the launch that would prepare them (4 queries over 13401 documents 18.1 -> 16.4 us, one over 2048 14.5 -> 12.7, 8 over 8192
+// 30.3 -> 28.8); with two for each it takes longer (14 queries over 2048, 8 heads: 16.1 -> 18.2).
+constexpr int kAllFoldTiles = 8;
 
 // log2(tiles per unit): the unit that keeps the longest stream shortest (whole units per wave), of equals the largest
 static int scan_all_ushift(long long seg_tiles, int C) {
@@ -691,6 +697,8 @@ static int scan_all_ushift(long long seg_tiles, int C) {
 
 struct ScanAllArgs {
   const uint4* qop;       // [HKV][n_qtiles][NS][64] prepared A operands (prep_scan_operands_kernel)
+  const uint16_t* q_route;  // FOLD: the queries themselves
+  int q0, BM, Hq, r;        // FOLD: first query of the pass, queries of the call
   const uint16_t* KR;     // tiled
   const float* inv_norm;  // null: dot product
   float* mat;             // [queries][mat_stride]
@@ -707,7 +715,8 @@ struct ScanAllArgs {
 
 // STREAM: the index is far larger than the caches and read once per pass -> streaming loads (load_stream16); a small
 // index that several passes re-read is served partly from the caches and measured faster with plain loads.
-template <int D, int HKV, int NQT, bool STREAM>
+// FOLD: the workgroup folds the queries of every head itself, a wave per (head, tile of 8 queries): one launch less.
+template <int D, int HKV, int NQT, bool STREAM, bool FOLD>
 __global__ __launch_bounds__(64 * kAllWaves) void score_scan_all_kernel(ScanAllArgs a) {
   constexpr int NS = D / 32;
   constexpr int NQ = 8 * NQT;
@@ -727,14 +736,19 @@ __global__ __launch_bounds__(64 * kAllWaves) void score_scan_all_kernel(ScanAllA
   const int n = lane & 15;
 
   // ---- operands: global -> LDS, requested first; the tiles requested next stay in flight across their wait -------
-  const uint32_t op_lds = lds_addr_of(&Aop[0][0][0][0]);
+  FoldRegs<D> fr;
+  if constexpr (FOLD) {
+    if (wave < HKV * NQT) fold_query_load<D>(a.q_route, a.q0 / 8 + wave / HKV, wave % HKV, a.BM, a.Hq, a.r, fr, lane);
+  } else {
+    const uint32_t op_lds = lds_addr_of(&Aop[0][0][0][0]);
 #pragma unroll
-  for (int i = 0; i < OPW; ++i) {
-    int e = i * kAllWaves + wave;  // (head, tile, slice)
-    e = e < NOP ? e : NOP - 1;     // past the end: the last piece again (the same bytes to the same place)
-    const int h = e / (NQT * NS), rest = e % (NQT * NS);
-    const uint4* src = a.qop + ((long long)h * a.n_qtiles * NS + rest) * 64;
-    copy16_to_lds_async_at(src, lane * 16, op_lds + e * 1024);
+    for (int i = 0; i < OPW; ++i) {
+      int e = i * kAllWaves + wave;  // (head, tile, slice)
+      e = e < NOP ? e : NOP - 1;     // past the end: the last piece again (the same bytes to the same place)
+      const int h = e / (NQT * NS), rest = e % (NQT * NS);
+      const uint4* src = a.qop + ((long long)h * a.n_qtiles * NS + rest) * 64;
+      copy16_to_lds_async_at(src, lane * 16, op_lds + e * 1024);
+    }
   }
 
   const long long W = (long long)gridDim.x * kAllWaves;
@@ -760,16 +774,30 @@ __global__ __launch_bounds__(64 * kAllWaves) void score_scan_all_kernel(ScanAllA
   };
   u32x4_t buf[kPrefetch][NS];  // whole vectors throughout: element-wise uses would be put back together with copies
   float binv[kPrefetch];
-#pragma unroll
-  for (int u = 0; u < kPrefetch; ++u) {
+  auto first_entry = [&](int u) __attribute__((always_inline)) {
     const int h = u % HKV;
     const long long t = load_at(u / HKV);
 #pragma unroll
     for (int s = 0; s < NS; ++s)
       buf[u][s] = load_tile16(KRl + ((long long)h * a.tiles + t) * TILE_ELEMS + s * 512);
     binv[u] = inl[((long long)h * a.tiles + t) * inv_stride];
+  };
+  if constexpr (FOLD) {
+    // (the folding behind one request, not behind all of them: see score_scan_kernel)
+    first_entry(0);
+    for (int e = wave; e < HKV * NQT; e += kAllWaves) {
+      const int h = e % HKV, t = e / HKV;
+      if (e != wave) fold_query_load<D>(a.q_route, a.q0 / 8 + t, h, a.BM, a.Hq, a.r, fr, lane);
+      static_assert(8 * D * 4 == NS * 64 * 16, "the folded queries take the place of their operands");
+      fold_query_tile<D>(fr, a.q0 / 8 + t, a.BM, a.r, cos ? 1 : 0, reinterpret_cast<float*>(&Aop[h][t][0][0]), Aop[h][t], lane);
+    }
+#pragma unroll
+    for (int u = 1; u < kPrefetch; ++u) first_entry(u);
+  } else {
+#pragma unroll
+    for (int u = 0; u < kPrefetch; ++u) first_entry(u);
+    wait_copies_but<kPrefetch * (NS + 1)>();  // the operands are older than the tiles
   }
-  wait_copies_but<kPrefetch * (NS + 1)>();  // the operands are older than the tiles
   lds_barrier();
   if (n_it == 0) return;  // wave-uniform; no workgroup barrier follows
 
@@ -1587,7 +1615,7 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
   a.tiles_per_wave = pl.tiles_per_wave;
   a.n_qtiles = pl.n_qtiles;
   a.q_route = (const uint16_t*)q_route;
-  const bool fold_in_scan = !pl.all_heads && !pl.exchange;
+  const bool fold_in_scan = pl.all_heads ? pl.q_per_pass / 8 * dm.Hkv <= kAllFoldTiles : !pl.exchange;
   if (!fold_in_scan) {
     const long long n_gmax = pl.exchange ? (long long)dm.Hkv * BM * pl.n_splits : 0;
     const unsigned blocks = (unsigned)(pl.n_qtiles * dm.Hkv);
@@ -1614,6 +1642,11 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
   if (pl.all_heads) {
     ScanAllArgs sa;
     sa.qop = (const uint4*)((char*)ws + pl.off_qop);
+    sa.q_route = (const uint16_t*)q_route;
+    sa.q0 = 0;
+    sa.BM = BM;
+    sa.Hq = dm.Hq;
+    sa.r = dm.r;
     sa.KR = (const uint16_t*)KR;
     sa.inv_norm = a.inv_norm;
     sa.mat = (float*)((char*)ws + pl.off_mat);
@@ -1640,8 +1673,9 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
       dim3 grid((unsigned)(wgs < kAllGroups ? wgs : kAllGroups)), block(64 * kAllWaves);
 #define MSA_SCAN_ALL(DD, HH, QQ) \
 do { \
-  if (stream_index) hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, QQ, true>), grid, block, 0, st, sa); \
-  else hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, QQ, false>), grid, block, 0, st, sa); \
+  constexpr bool FF = HH * QQ <= kAllFoldTiles; /* fold_in_scan */ \
+  if (stream_index) hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, QQ, true, FF>), grid, block, 0, st, sa); \
+  else hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, QQ, false, FF>), grid, block, 0, st, sa); \
 } while (0)
 #define MSA_SCAN_ALL_Q(DD, HH) \
 do { \

@@ -70,6 +70,23 @@ def test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim):
         check_topk_generic(q, KRb, C, N, idx, val, k, sim, "all", pool, atol=2e-5 if sim == "cos" else 2e-4)
 
 
+# the same at the edge between queries that the scan's workgroups fold themselves and prepared ones
+ALL_FOLDED = [
+    (97, 8, 4, 8, 128, 8, 1, 16, "cos"),      # a tile for every wave
+    (97, 8, 4, 8, 128, 3, 3, 16, "cos"),      # one query more: prepared
+    (33, 4, 8, 16, 64, 16, 1, 5, "cos"),      # two tiles of queries
+    (33, 4, 3, 16, 64, 17, 1, 5, "dot"),
+    (2100, 2, 1, 1, 128, 6, 5, 9, "dot"),     # four tiles of two heads, the last of 6 queries
+    (70, 2, 2, 4, 64, 1, 1, 12, "cos"),       # waves without a tile
+    (70000, 2, 2, 2, 64, 2, 4, 20, "cos"),    # parts of rows
+]
+
+
+@pytest.mark.parametrize("N,Hkv,r,C,d,B,M,k,sim", ALL_FOLDED)
+def test_all_heads_scan_folds(N, Hkv, r, C, d, B, M, k, sim):
+    test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim)
+
+
 @pytest.mark.parametrize("pool", [0, 1])
 def test_all_heads_scan_lists_in_windows(pool):
     """A bank of 388 parts, of whose lists the buffer holds 380 (32 queries, k = 64): two windows, the second short.
