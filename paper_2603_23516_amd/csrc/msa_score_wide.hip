@@ -12,6 +12,7 @@
 //                         d = 128) for its whole life; eight waves stream units of 64 keys straight into registers
 //                         (the index is stored in operand order), multiply them with all 64 rows, group after group,
 //                         and write the document maxima.  The waves never synchronise after the operands are in.
+//   score_wide_rows_kernel    the same for up to 160 rows at once, one group's operands in LDS at a time.
 //   score_wide_select_kernel  per token: the candidates of the matrix row and their exact scores.
 //
 // One pass (cosine, d = 128, eight chunks per document): only the hi parts are multiplied, 64 tokens per workgroup.  The
@@ -29,6 +30,8 @@
 // ms.  2048 tokens, 32768 documents, k = 8: 2.4 ms (a GEMM that reloaded its operands at every group switch) -> 1.47 ms.
 #include "msa_device.h"
 #include "msa_host.h"
+
+#include <type_traits>
 
 namespace msa {
 
@@ -53,7 +56,63 @@ struct WideArgs {
   long long tiles;         // tiles per head in the index
   long long tile0;         // first tile of the segment
   int seg_tiles, seg_docs; // tiles and documents of the segment
+  int Hkv;
 };
+
+// Head mean, document maxima (every lane of a document's C lanes gets it), scores of unit u to the matrix; tok0: token of the
+// first operand row.
+template <int NT, bool PAIR, int KT>
+__device__ __forceinline__ void wide_store(const WideArgs& a, const float (&tot)[NT][KT][4], int u, int tok0, float inv_heads,
+                                           int lane) {
+  const int dpt = 16 / a.C;
+  constexpr int NR = PAIR ? 2 : 4;  // tokens per lane and tile
+  int le = lane;  // (opaque: worked out ahead of the caller's loop, what follows from it would take registers)
+  asm volatile("" : "+v"(le));
+  const int rr = le >> 4, n = le & 15;
+#pragma unroll
+  for (int tq = 0; tq < NT; ++tq) {
+    float m[NR][KT];
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt) m[i][kt] = PAIR ? tot[tq][kt][2 * i] + tot[tq][kt][2 * i + 1] : tot[tq][kt][i];
+    // one instruction per maximum (fmaxf of an exchanged value takes three: the exchange, and a canonicalising
+    // maximum first); the exchange reads its operand two wait states after the write at the earliest
+#define MSA_LEVEL(CTRL) \
+  do { \
+    for (int j = 0; j < NR * KT; j += 4) \
+      asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 " CTRL " row_mask:0xf bank_mask:0xf\n\t" \
+          "v_max_f32_dpp %1, %1, %1 " CTRL " row_mask:0xf bank_mask:0xf\n\t" \
+          "v_max_f32_dpp %2, %2, %2 " CTRL " row_mask:0xf bank_mask:0xf\n\t" \
+          "v_max_f32_dpp %3, %3, %3 " CTRL " row_mask:0xf bank_mask:0xf" \
+          : "+v"(m[j / KT][j % KT]), "+v"(m[(j + 1) / KT][(j + 1) % KT]), "+v"(m[(j + 2) / KT][(j + 2) % KT]), \
+            "+v"(m[(j + 3) / KT][(j + 3) % KT])); \
+  } while (0)
+    static_assert((KT == 2 || KT == 4) && NR * KT % 4 == 0, "four values per statement");
+    if (a.C >= 2) MSA_LEVEL("quad_perm:[1,0,3,2]");
+    if (a.C >= 4) MSA_LEVEL("quad_perm:[2,3,0,1]");
+    if (a.C >= 8) MSA_LEVEL("row_half_mirror");
+    if (a.C >= 16) MSA_LEVEL("row_mirror");
+#undef MSA_LEVEL
+    // The C lanes of a document take the unit's tiles in turn, up to four at once: one store then writes up to
+    // 4 dpt documents of a token (a run of 32 bytes at C = 8).
+    const int par = a.C < KT ? a.C : KT;   // tiles per store
+    for (int k0 = 0; k0 < KT; k0 += par) {  // wave-uniform
+      const int kt = k0 + (n & (par - 1));
+      const int doc = (u * KT + kt) * dpt + n / a.C;
+      const bool on = (n & (a.C - 1)) < par && doc < a.seg_docs;
+#pragma unroll
+      for (int i = 0; i < NR; ++i) {
+        const int tok = tok0 + tq * (PAIR ? 8 : 16) + rr * NR + i;
+        // (through empty asm: as selects between elements of the array they would become an indexed load of it)
+        float c0 = m[i][0], c1 = m[i][1], c2 = m[i][KT - 2], c3 = m[i][KT - 1];
+        asm volatile("" : "+v"(c0), "+v"(c1), "+v"(c2), "+v"(c3));
+        const float lo = (kt & 1) ? c1 : c0, hi = (kt & 1) ? c3 : c2;
+        if (on && tok < a.nq) a.mat[tok * a.mat_stride + doc] = fmaxf(((kt & 2) ? hi : lo) * inv_heads, -INFINITY);  // (not a number: last)
+      }
+    }
+  }
+}
 
 template <int D, int HKV, bool PAIR, bool COS>
 __global__ __launch_bounds__(64 * kWideWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
@@ -121,7 +180,6 @@ void score_wide_kernel(WideArgs a) {
   wait_copies_but<2 * KT * (NS + (COS ? 1 : 0))>();  // the operands are older than the keys
   lds_barrier();
 
-  const int dpt = 16 / a.C;
   const float inv_heads = 1.0f / (float)HKV;
   // The operand reads run two ahead of the products (a ring of four slices that goes on from group to group): four
   // products of 16 cycles each per read, so a read has about 128 cycles to land.  The order is the one written here:
@@ -179,54 +237,148 @@ void score_wide_kernel(WideArgs a) {
       __builtin_amdgcn_sched_barrier(0);
     }
 
-    // ---- head mean, document maxima (every lane of a document's C lanes gets it), store ---------------------------
-    constexpr int NR = PAIR ? 2 : 4;  // tokens per lane and tile
-    int le = lane;  // (opaque, as above)
-    asm volatile("" : "+v"(le));
-    const int rr = le >> 4, n = le & 15;
+    wide_store<NT, PAIR, KT>(a, tot, u, tb * (kWideRows / (PAIR ? 2 : 1)), inv_heads, lane);
+  }
+}
+
+// ---- more than 64 operand rows: a key is read once for up to 160 ----------------------------------------------------
+// score_wide_kernel with NT tiles of 16 rows (cosine, d = 128, one-pass): the operands of one group at a time lie in LDS,
+// 4 NT KiB, two groups in turn; the next group's are copied there (from the L2, all workgroups read the same ones) while this
+// one's are multiplied.  Eight waves, two per SIMD: 32 keys and all rows each, totals of 8 NT registers, the keys of two
+// groups 64.  The waves meet once per group, 8 NT products each.  Bound by the index (1.6 GB: 232 us) and, with 160 rows, the
+// operand reads from LDS, as many cycles as the products take.  (Four waves of 64 keys would halve the reads; their totals
+// and keys need the accumulation half of the register file, and the copies in and out of it cost as much.)
+constexpr int kRowsWaves = 8;
+constexpr int kRowsTiles = 2;   // 16-key tiles per unit
+constexpr int kRowsMost = 10;   // tiles of 16 rows
+
+template <int NT>
+__global__ __launch_bounds__(64 * kRowsWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void score_wide_rows_kernel(WideArgs a) {
+  constexpr int D = 128;
+  constexpr int NS = D / 32;
+  constexpr int KT = kRowsTiles;
+  constexpr int TILE_ELEMS = 16 * D;
+  constexpr int NOP = NT * NS;              // KiB of operands of a group
+  constexpr int OPW = NOP / kRowsWaves;     // copies of a wave
+  static_assert(NOP % kRowsWaves == 0, "whole copies per wave");
+
+  __shared__ uint4 Aop[2][NT][NS][64];
+
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int total = a.n_tb * a.n_streams;
+  const int vb = (blockIdx.x & 7) * ((total + 7) / 8) + (blockIdx.x >> 3);  // (see score_wide_kernel)
+  if (vb >= total) return;  // block-uniform: the grid is rounded up to whole XCDs
+  const int tb = vb % a.n_tb;
+  const int stream = vb / a.n_tb;
+  const int Hkv = a.Hkv;
+
+  const uint32_t op_lds = lds_addr_of(&Aop[0][0][0][0]);
+  // operands of group g -> place g & 1; row tiles past the last one: that one again (their scores are not stored)
+  auto copy_operands = [&](int g) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < OPW; ++i) {
+      const int e = i * kRowsWaves + wave;  // (tile, slice)
+      int t = tb * NT + e / NS;
+      t = t < a.n_rt ? t : a.n_rt - 1;
+      const uint4* src = a.qop + (((long long)g * a.n_rt + t) * NS + e % NS) * 64;
+      copy16_to_lds_async_at(src, lane * 16, op_lds + (g & 1) * (NOP * 1024) + e * 1024);
+    }
+  };
+
+  const int W = a.n_streams * kRowsWaves;
+  const int units = (a.seg_tiles + KT - 1) / KT;
+  typedef const __attribute__((address_space(1))) char* gptr_t;
+  const gptr_t kr0 = (gptr_t)a.KR + a.tile0 * (TILE_ELEMS * 2);
+  const gptr_t in0 = (gptr_t)a.inv_norm + a.tile0 * 64;
+  const int last_tile = a.seg_tiles - 1;
+
+  u32x4_t buf[2][KT][NS];
+  float binv[2][KT];
+  constexpr int kLoads = KT * (NS + 1);  // of a request
+  // unit u, group g into ring slot: always issued, past the end the last tile again
+  auto request = [&](int u, int g, u32x4_t (&b)[KT][NS], float (&bi)[KT]) __attribute__((always_inline)) {
+    uint32_t ln = lane;
+    asm volatile("" : "+v"(ln));
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+      int t = u * KT + kt;
+      t = t < last_tile ? t : last_tile;
+      const long long at = g * a.tiles + t;
+      const gptr_t p = kr0 + at * (TILE_ELEMS * 2);
+#pragma unroll
+      for (int s = 0; s < NS; ++s)
+        b[kt][s] = *(const __attribute__((address_space(1))) u32x4_t*)(p + s * 1024 + (size_t)(ln * 16));
+      bi[kt] = *(const __attribute__((address_space(1))) float*)(in0 + at * 64 + (size_t)((ln & 15) * 4));
+    }
+  };
+  const int u_first = stream * kRowsWaves;
+  copy_operands(0);
+  request(u_first + wave, 0, buf[0], binv[0]);
+  request(u_first + wave, 1, buf[1], binv[1]);
+
+  const float inv_heads = 1.0f / (float)Hkv;
+  constexpr int NA = NT * NS;  // slices of a group
+  constexpr int kAhead = 6;    // slices read ahead of their products: two products of 16 cycles each, an LDS read takes over 100
+  float tot[NT][KT][4];
+  // One group: products of its keys with all rows, into the totals; PAR: its place.
+  auto group = [&](auto par_c, int u, int g) __attribute__((always_inline)) {
+    constexpr int PAR = decltype(par_c)::value;
+    // This group's keys and operands have landed (the next group's keys, the youngest, may be on their way); behind the
+    // barrier everyone's part of the operands has, and everyone is done with the place of the group before.
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt) {
+#pragma unroll
+      for (int s = 0; s < NS; ++s) asm volatile("" : "+v"(buf[PAR][kt][s]));
+      asm volatile("" : "+v"(binv[PAR][kt]));
+    }
+    wait_copies_but<kLoads>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    copy_operands(g + 1 < Hkv ? g + 1 : 0);
+    const uint4* const A0 = &Aop[PAR][0][0][0] + lane;
+    bf16x8_t ar[8];
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i) ar[i] = as_bf16x8(A0[i * 64]);
 #pragma unroll
     for (int tq = 0; tq < NT; ++tq) {
-      float m[NR][KT];
+      f32x4_t acc[KT];
 #pragma unroll
-      for (int i = 0; i < NR; ++i)
+      for (int s = 0; s < NS; ++s) {
+        const int i = tq * NS + s;
+        if (i + kAhead < NA) ar[(i + kAhead) & 7] = as_bf16x8(A0[(i + kAhead) * 64]);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int kt = 0; kt < KT; ++kt) m[i][kt] = PAIR ? tot[tq][kt][2 * i] + tot[tq][kt][2 * i + 1] : tot[tq][kt][i];
-      // one instruction per maximum (fmaxf of an exchanged value takes three: the exchange, and a canonicalising
-      // maximum first); the exchange reads its operand two wait states after the write at the earliest
-#define MSA_LEVEL(CTRL) \
-  do { \
-    for (int i = 0; i < NR; ++i) \
-      asm("s_nop 1\n\tv_max_f32_dpp %0, %0, %0 " CTRL " row_mask:0xf bank_mask:0xf\n\t" \
-          "v_max_f32_dpp %1, %1, %1 " CTRL " row_mask:0xf bank_mask:0xf\n\t" \
-          "v_max_f32_dpp %2, %2, %2 " CTRL " row_mask:0xf bank_mask:0xf\n\t" \
-          "v_max_f32_dpp %3, %3, %3 " CTRL " row_mask:0xf bank_mask:0xf" \
-          : "+v"(m[i][0]), "+v"(m[i][1]), "+v"(m[i][2]), "+v"(m[i][3])); \
-  } while (0)
-      static_assert(KT == 4, "four values per statement");
-      if (a.C >= 2) MSA_LEVEL("quad_perm:[1,0,3,2]");
-      if (a.C >= 4) MSA_LEVEL("quad_perm:[2,3,0,1]");
-      if (a.C >= 8) MSA_LEVEL("row_half_mirror");
-      if (a.C >= 16) MSA_LEVEL("row_mirror");
-#undef MSA_LEVEL
-      // The C lanes of a document take the unit's tiles in turn, up to four at once: one store then writes up to
-      // 4 dpt documents of a token (a run of 32 bytes at C = 8).
-      const int par = a.C < KT ? a.C : KT;   // tiles per store
-      for (int k0 = 0; k0 < KT; k0 += par) {  // wave-uniform
-        const int kt = k0 + (n & (par - 1));
-        const int doc = (u * KT + kt) * dpt + n / a.C;
-        const bool on = (n & (a.C - 1)) < par && doc < a.seg_docs;
-#pragma unroll
-        for (int i = 0; i < NR; ++i) {
-          const int tok = tb * (kWideRows / (PAIR ? 2 : 1)) + tq * (PAIR ? 8 : 16) + rr * NR + i;
-          // (through empty asm: as selects between elements of the array they would become an indexed load of it)
-          float c0 = m[i][0], c1 = m[i][1], c2 = m[i][2], c3 = m[i][3];
-          asm volatile("" : "+v"(c0), "+v"(c1), "+v"(c2), "+v"(c3));
-          const float lo = (kt & 1) ? c1 : c0, hi = (kt & 1) ? c3 : c2;
-          if (on && tok < a.nq) a.mat[tok * a.mat_stride + doc] = fmaxf(((kt & 2) ? hi : lo) * inv_heads, -INFINITY);  // (not a number: last)
-        }
+        for (int kt = 0; kt < KT; ++kt)
+          acc[kt] = mfma16(ar[i & 7], __builtin_bit_cast(bf16x8_t, buf[PAR][kt][s]),
+                           s == 0 ? f32x4_t{0.f, 0.f, 0.f, 0.f} : acc[kt]);
+        __builtin_amdgcn_sched_barrier(0);
       }
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) tot[tq][kt][i] = fmaf(acc[kt][i], binv[PAR][kt], tot[tq][kt][i]);
     }
+    asm volatile("" ::: "memory");  // every product of the entry is issued before its slot is requested again
+    request(g + 2 < Hkv ? u : u + W, g + 2 < Hkv ? g + 2 : g + 2 - Hkv, buf[PAR], binv[PAR]);
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  for (int ub = u_first; ub < units; ub += W) {  // block-uniform
+    const int u = ub + wave;
+#pragma unroll
+    for (int tq = 0; tq < NT; ++tq)
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) tot[tq][kt][i] = 0.f;
+    for (int g = 0; g < Hkv; g += 2) {
+      group(std::integral_constant<int, 0>{}, u, g);
+      group(std::integral_constant<int, 1>{}, u, g + 1);
+    }
+    if (u < units) wide_store<NT, false, KT>(a, tot, u, tb * NT * 16, inv_heads, lane);
   }
+  wait_copies_but<0>();  // (requests past the end)
 }
 
 // ---- selection -------------------------------------------------------------------------------------------------
@@ -598,7 +750,7 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
     const int nq = BM - tok0 < pl.pass_tokens ? BM - tok0 : pl.pass_tokens;
     a.nq = nq;
     a.n_rt = pl.n_tb * (kWideRows / 16);
-    a.n_tb = (nq + per_wg - 1) / per_wg;
+    a.Hkv = dm.Hkv;
     const int rc = launch_fold_queries(dm, (const uint16_t*)q_route + (size_t)tok0 * dm.Hq * dm.d, nq,
                                        (float*)(w + pl.off_qf), pl.pair ? nullptr : (float*)(w + pl.off_eps), nullptr, 0,
                                        (uint4*)(w + pl.off_qop), a.n_rt, pl.pair, st);
@@ -608,13 +760,24 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
       a.tile0 = (long long)doc0 * dm.C / 16;  // doc0 is a multiple of 64 (or 0)
       a.seg_docs = n_docs;
       a.seg_tiles = (int)(((long long)n_docs * dm.C + 15) / 16);
-      const int units = (a.seg_tiles + kWideTiles - 1) / kWideTiles;
+      // More rows per key for 65 to 160 tokens of eight groups, whose blocks of 64 rows are two or three times the reads of a
+      // key, the third half empty (150 tokens, 97656 documents 496 -> 430 us; 80 401 -> 354; 70 over 300 41 -> 38; 120 over
+      // 1000 the same).  Up to 192 three blocks are full (190 over 20000 124 -> 124, on another card 127 -> 136).  More tokens
+      // are bound by the products, and these by the operand reads (600 tokens, 30000 documents 483 -> 494, 2048 over 32768
+      // 1477 -> 1714); with four groups the resident operands leave room for two workgroups per CU (100 tokens, 60000
+      // documents 157 -> 160).
+      const bool rows = !pl.pair && dm.Hkv == 8 && nq > kWideRows && nq <= 16 * kRowsMost;
+      const int units = (a.seg_tiles + (rows ? kRowsTiles : kWideTiles) - 1) / (rows ? kRowsTiles : kWideTiles);
+      const int waves = rows ? kRowsWaves : kWideWaves;
+      int nt = kWideRows / 16;
+      if (rows) nt = (nq + 31) / 32 * 2;
+      a.n_tb = rows ? (nq + 16 * nt - 1) / (16 * nt) : (nq + per_wg - 1) / per_wg;
       int streams = kWideGroups / a.n_tb;
       if (streams < 1) streams = 1;
-      const int most = (units + kWideWaves - 1) / kWideWaves;
+      const int most = (units + waves - 1) / waves;
       if (streams > most) streams = most;
       a.n_streams = streams;
-      dim3 grid((unsigned)((a.n_tb * streams + 7) / 8 * 8)), block(64 * kWideWaves);
+      dim3 grid((unsigned)((a.n_tb * streams + 7) / 8 * 8)), block(64 * waves);
       if (tok0 == 0 && doc0 == 0) profile_mark(dm, false, st);
 #define MSA_WIDE(DD, HH) \
   do { \
@@ -622,7 +785,11 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
     else if (dm.cos) hipLaunchKernelGGL((score_wide_kernel<DD, HH, true, true>), grid, block, 0, st, a); \
     else hipLaunchKernelGGL((score_wide_kernel<DD, HH, true, false>), grid, block, 0, st, a); \
   } while (0)
-      if (dm.d == 128) {
+      if (rows) {
+        if (nt == 6) hipLaunchKernelGGL(score_wide_rows_kernel<6>, grid, block, 0, st, a);
+        else if (nt == 8) hipLaunchKernelGGL(score_wide_rows_kernel<8>, grid, block, 0, st, a);
+        else hipLaunchKernelGGL(score_wide_rows_kernel<10>, grid, block, 0, st, a);
+      } else if (dm.d == 128) {
         if (dm.Hkv == 2) MSA_WIDE(128, 2); else if (dm.Hkv == 4) MSA_WIDE(128, 4); else MSA_WIDE(128, 8);
       } else {
         if (dm.Hkv == 2) MSA_WIDE(64, 2); else if (dm.Hkv == 4) MSA_WIDE(64, 4); else MSA_WIDE(64, 8);

@@ -196,6 +196,18 @@ def test_all_heads_wide(N, Hkv, r, C, d, B, M, k, sim):
     test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim)
 
 
+# the same at the edges of the kernel that reads a key once for 65 to 160 rows: numbers of row tiles, units that end inside a
+# wave's keys, fewer documents than a workgroup has waves
+ALL_ROWS = [(37, 8, 1, 8, 128, 1, 64, 9, "cos"), (37, 8, 1, 8, 128, 1, 65, 9, "cos"), (1003, 8, 2, 8, 128, 1, 96, 16, "cos"),
+            (2051, 8, 4, 8, 128, 1, 97, 32, "cos"), (5, 8, 1, 8, 128, 2, 64, 5, "cos"), (520, 8, 4, 8, 128, 3, 53, 12, "cos"),
+            (999, 8, 1, 8, 128, 1, 129, 16, "cos"), (4100, 8, 2, 8, 128, 1, 160, 8, "cos"), (300, 8, 1, 8, 128, 1, 161, 8, "cos")]
+
+
+@pytest.mark.parametrize("N,Hkv,r,C,d,B,M,k,sim", ALL_ROWS)
+def test_all_heads_wide_rows(N, Hkv, r, C, d, B, M, k, sim):
+    test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim)
+
+
 # (N, Hkv, C, d, B, M, k, scope, pool): a row's k best where every document ties
 ALL_TIED = [
     (9000, 2, 8, 64, 3, 1, 16, "group", 0),       # row top-k, four waves, part of the row beyond the registers
