@@ -52,9 +52,10 @@ int launch_score_gemm_scan(const Dims& dm, const GemmPlan& pl, const void* q_rou
                            const void* KR, const float* inv_norm, int k, void* ws, hipStream_t st,
                            int32_t* out_idx, float* out_score, unsigned long long* out_key, const int** gate_flags);
 
-// Folds the heads of BM tokens: qf fp32 [BM][Hkv][d], and where not null eps, flags, qop (see fold_queries_kernel).
+// Folds the heads of BM tokens: qf fp32 [BM][Hkv][d], and where not null eps, flags, qop (see fold_queries_kernel; every M
+// tokens take m_rows operand rows).
 int launch_fold_queries(const Dims& dm, const void* q_route, int BM, float* qf, float* eps, int* flags, int n_flags,
-                        uint4* qop, int n_rt, int pair, hipStream_t st);
+                        uint4* qop, int n_rt, int pair, int M, int m_rows, hipStream_t st);
 
 // Head mean over every head for many query tokens (msa_score_wide.hip): passes of tokens, segments of the bank.
 struct WidePlan {
@@ -67,6 +68,18 @@ struct WidePlan {
   size_t list_bytes;     // several segments, one pass: candidate lists of the tokens of a pass
   size_t off_list;       // ... where they are; 0: the workspace has no room for them
 };
+// Token pooling behind it without a selection per token: the best score of a block of a batch row's tokens per document,
+// exact scores of the documents that can be among the k best.
+struct WidePoolPlan {
+  int applies;           // 1: this shape, and the buffers fit where those of WidePlan lie
+  int nt, m_tiles, m_blocks;  // operand tiles of a token block; operand tiles and token blocks of a batch row
+  int part_docs, n_parts;     // documents of a part, parts of the bank
+  size_t off_qf, off_qop, off_eps, off_mat, off_parts, off_band, off_cnt, off_cand, off_keys;
+};
+WidePoolPlan plan_score_wide_pool(const Dims& dm, const WidePlan& pl, int B, int M, int k);
+int launch_score_wide_pool(const Dims& dm, const WidePoolPlan& pp, const void* q_route, int B, int M, const void* KR,
+                           const float* inv_norm, int k, void* ws, hipStream_t st, int32_t* out_idx, float* out_score);
+
 bool wide_path_applies(const Dims& dm, int BM);
 WidePlan plan_score_wide(const Dims& dm, int BM, int k);
 int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, int BM, const void* KR,

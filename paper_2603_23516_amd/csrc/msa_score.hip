@@ -1580,6 +1580,8 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
     return pool_tokens();
   };
   if (pl.use_wide) {
+    const WidePoolPlan pp = plan_score_wide_pool(dm, pl.wide, B, M, k);
+    if (pp.applies) return launch_score_wide_pool(dm, pp, q_route, B, M, KR, inv_norm, k, ws, st, out_idx, out_score);
     const int rc = launch_score_wide(dm, pl.wide, q_route, BM, KR, inv_norm, k, ws, st, out_idx, out_score, tok_keys);
     if (rc != MSA_OK) return rc;
     return pool_tokens();

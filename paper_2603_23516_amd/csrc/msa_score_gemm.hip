@@ -72,7 +72,7 @@ __global__ __launch_bounds__(64) void fold_queries_kernel(const uint16_t* __rest
                                                           float* __restrict__ qf, int Hq, int Hkv,
                                                           int r, int cos, float* __restrict__ eps,
                                                           int* __restrict__ flags, int n_flags,
-                                                          uint4* __restrict__ qop, int n_rt, int pair) {
+                                                          uint4* __restrict__ qop, int n_rt, int pair, int M, int m_rows) {
   constexpr int LPH = D / 8, HPL = 64 / LPH;
   const int lane = threadIdx.x;
   const int g = blockIdx.x % Hkv;
@@ -110,8 +110,9 @@ __global__ __launch_bounds__(64) void fold_queries_kernel(const uint16_t* __rest
     f[e] = x;
   }
   if (qop != nullptr && hs == 0) {
-    // row of the token: 16 tokens per tile (hi), or 8 with hi and lo in neighbouring rows
-    const long long row = pair ? 2 * qg : qg;
+    // row of the token: 16 tokens per tile (hi), or 8 with hi and lo in neighbouring rows; every M tokens take m_rows rows
+    const long long tk = m_rows == M ? qg : qg / M * m_rows + qg % M;
+    const long long row = pair ? 2 * tk : tk;
     uint4* dst = qop + (((long long)g * n_rt + (row >> 4)) * (D / 32) + (piece >> 2)) * 64 + (piece & 3) * 16 + (row & 15);
     dst[0] = make_uint4(pack_bf16(hi[0], hi[1]), pack_bf16(hi[2], hi[3]), pack_bf16(hi[4], hi[5]), pack_bf16(hi[6], hi[7]));
     if (pair)
@@ -731,13 +732,13 @@ GemmPlan plan_score_gemm(const Dims& dm, int BM, int k) {
 }
 
 int launch_fold_queries(const Dims& dm, const void* q_route, int BM, float* qf, float* eps, int* flags, int n_flags,
-                        uint4* qop, int n_rt, int pair, hipStream_t st) {
+                        uint4* qop, int n_rt, int pair, int M, int m_rows, hipStream_t st) {
   if (dm.d == 128)
     hipLaunchKernelGGL(fold_queries_kernel<128>, dim3((unsigned)(BM * dm.Hkv)), dim3(64), 0, st,
-                       (const uint16_t*)q_route, qf, dm.Hq, dm.Hkv, dm.r, dm.cos, eps, flags, n_flags, qop, n_rt, pair);
+                       (const uint16_t*)q_route, qf, dm.Hq, dm.Hkv, dm.r, dm.cos, eps, flags, n_flags, qop, n_rt, pair, M, m_rows);
   else
     hipLaunchKernelGGL(fold_queries_kernel<64>, dim3((unsigned)(BM * dm.Hkv)), dim3(64), 0, st,
-                       (const uint16_t*)q_route, qf, dm.Hq, dm.Hkv, dm.r, dm.cos, eps, flags, n_flags, qop, n_rt, pair);
+                       (const uint16_t*)q_route, qf, dm.Hq, dm.Hkv, dm.r, dm.cos, eps, flags, n_flags, qop, n_rt, pair, M, m_rows);
   return hipGetLastError() == hipSuccess ? MSA_OK : MSA_ERR_HIP;
 }
 
@@ -749,7 +750,7 @@ int launch_score_gemm_scan(const Dims& dm, const GemmPlan& pl, const void* q_rou
   int* flags = pl.filter ? (int*)((char*)ws + pl.off_flags) : nullptr;
   const int n_flags = pl.filter ? dm.Hkv * pl.n_qblocks : 0;
   *gate_flags = flags;
-  const int rf = launch_fold_queries(dm, q_route, BM, qf, eps, flags, n_flags, nullptr, 0, 0, st);
+  const int rf = launch_fold_queries(dm, q_route, BM, qf, eps, flags, n_flags, nullptr, 0, 0, BM, BM, st);
   if (rf != MSA_OK) return rf;
   GemmArgs a;
   a.flags = nullptr;

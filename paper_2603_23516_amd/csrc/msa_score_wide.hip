@@ -14,6 +14,7 @@
 //                         and write the document maxima.  The waves never synchronise after the operands are in.
 //   score_wide_rows_kernel    the same for up to 160 rows at once, one group's operands in LDS at a time.
 //   score_wide_select_kernel  per token: the candidates of the matrix row and their exact scores.
+//   pool_*_kernel             the same per batch row where the tokens are pooled.
 //
 // One pass (cosine, d = 128, eight chunks per document): only the hi parts are multiplied, 64 tokens per workgroup.  The
 // matrix then holds scores within the bound eps that fold_queries_kernel writes; every document within 2 eps of the
@@ -57,6 +58,8 @@ struct WideArgs {
   long long tile0;         // first tile of the segment
   int seg_tiles, seg_docs; // tiles and documents of the segment
   int Hkv;
+  int M;                   // pooled: tokens of a batch row ...
+  int m_tiles, m_blocks;   // ... its operand tiles, its token blocks (not pooled: n_rt, n_tb)
 };
 
 // Head mean, document maxima (every lane of a document's C lanes gets it), scores of unit u to the matrix; tok0: token of the
@@ -252,7 +255,44 @@ constexpr int kRowsWaves = 8;
 constexpr int kRowsTiles = 2;   // 16-key tiles per unit
 constexpr int kRowsMost = 10;   // tiles of 16 rows
 
-template <int NT>
+// The best score of a block's tokens (the first n_rows operand rows) for the documents of unit u.
+template <int NT, int KT>
+__device__ __forceinline__ void wide_store_pooled(const WideArgs& a, const float (&tot)[NT][KT][4], int u, int tb, int n_rows,
+                                                  float inv_heads, int lane) {
+  int le = lane;  // (opaque, see wide_store)
+  asm volatile("" : "+v"(le));
+  const int rr = le >> 4, n = le & 15;
+  float best[KT];
+#pragma unroll
+  for (int kt = 0; kt < KT; ++kt) best[kt] = -INFINITY;
+#pragma unroll
+  for (int tq = 0; tq < NT; ++tq) {
+    if (16 * tq + 16 <= n_rows) {  // wave-uniform
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) best[kt] = fmaxf(best[kt], tot[tq][kt][i]);
+    } else if (16 * tq < n_rows) {
+#pragma unroll
+      for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) best[kt] = fmaxf(best[kt], 16 * tq + 4 * rr + i < n_rows ? tot[tq][kt][i] : -INFINITY);
+    }
+  }
+  float mine = -INFINITY;
+#pragma unroll
+  for (int kt = 0; kt < KT; ++kt) {
+    best[kt] = fmaxf(best[kt], __shfl_xor(best[kt], 16, 64));
+    best[kt] = fmaxf(best[kt], __shfl_xor(best[kt], 32, 64));
+    best[kt] = group_max<8>(best[kt]);  // the eight chunks of a document
+    mine = (n & 7) == kt ? best[kt] : mine;
+  }
+  const int doc = 2 * (u * KT + (n & 7)) + (n >> 3);
+  if (rr == 0 && (n & 7) < KT && doc < a.seg_docs) a.mat[tb * a.mat_stride + doc] = fmaxf(mine * inv_heads, -INFINITY);  // (not a number: last)
+}
+
+// POOL: token pooling, the matrix holds the best score of a block's tokens.
+template <int NT, bool POOL>
 __global__ __launch_bounds__(64 * kRowsWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void score_wide_rows_kernel(WideArgs a) {
   constexpr int D = 128;
@@ -275,13 +315,15 @@ void score_wide_rows_kernel(WideArgs a) {
   const int Hkv = a.Hkv;
 
   const uint32_t op_lds = lds_addr_of(&Aop[0][0][0][0]);
+  const int tile_0 = tb / a.m_blocks * a.m_tiles + tb % a.m_blocks * NT;  // first operand tile
+  const int tile_n = (tb / a.m_blocks + 1) * a.m_tiles - 1;                // last one of the batch row
   // operands of group g -> place g & 1; row tiles past the last one: that one again (their scores are not stored)
   auto copy_operands = [&](int g) __attribute__((always_inline)) {
 #pragma unroll
     for (int i = 0; i < OPW; ++i) {
       const int e = i * kRowsWaves + wave;  // (tile, slice)
-      int t = tb * NT + e / NS;
-      t = t < a.n_rt ? t : a.n_rt - 1;
+      int t = tile_0 + e / NS;
+      t = t < tile_n ? t : tile_n;
       const uint4* src = a.qop + (((long long)g * a.n_rt + t) * NS + e % NS) * 64;
       copy16_to_lds_async_at(src, lane * 16, op_lds + (g & 1) * (NOP * 1024) + e * 1024);
     }
@@ -376,7 +418,10 @@ void score_wide_rows_kernel(WideArgs a) {
       group(std::integral_constant<int, 0>{}, u, g);
       group(std::integral_constant<int, 1>{}, u, g + 1);
     }
-    if (u < units) wide_store<NT, false, KT>(a, tot, u, tb * NT * 16, inv_heads, lane);
+    if (u < units) {
+      if constexpr (POOL) wide_store_pooled<NT, KT>(a, tot, u, tb, a.M - tb % a.m_blocks * (NT * 16), inv_heads, lane);
+      else wide_store<NT, false, KT>(a, tot, u, tb * NT * 16, inv_heads, lane);
+    }
   }
   wait_copies_but<0>();  // (requests past the end)
 }
@@ -682,6 +727,284 @@ __global__ __launch_bounds__(kWideSel) void score_wide_select_kernel(WideSelArgs
   }
 }
 
+
+// ---- token pooling -------------------------------------------------------------------------------------------------
+// The score of a document is its best over the tokens of a batch row, so no token needs a selection of its own.  The scoring
+// kernel leaves, per document, the best matrix score P~ of every block of tokens (within E, the largest of the tokens' bounds, of
+// the best exact score P); then, all per batch row:
+//   pool_parts_kernel   the best P~ of each of up to 512 parts of the bank, and E
+//   pool_cand_kernel    theta, a lower bound on the k-th best P~ from the parts' (kth_best_bound); the documents with
+//                       P~ >= theta - 2 E: the k best by P are among them (k documents have P >= theta - E)
+//   pool_score_kernel   their exact scores with every token, Eq. 2 in fp32 as in score_wide_select_kernel, and the best of them
+//   pool_best_kernel    the k best candidates
+// Where E is zero (queries of zeros) P~ is P, and of the documents that tie with theta a workgroup lists the first k.
+// 150 tokens, k = 32, 97656 documents: a selection for every token (matrix of 58 MB in three segments) and their pooling, whole
+// call 435 us, this way 325; 600 tokens, 30000 documents 503 -> 336, 150 over 300 48.8 -> 46.9.
+constexpr int kPoolParts = 512;
+constexpr int kPoolMost = 1024;  // tokens of a batch row
+constexpr int kPoolTok = 4;      // tokens per workgroup of pool_score_kernel
+
+struct WidePoolArgs {
+  const float* mat;        // [B * m_blocks][N]
+  const float* eps;        // [B * M][Hkv]
+  const float* qf;         // [B * M][Hkv][128]
+  const uint16_t* KR;
+  const float* inv_norm;
+  float* parts;            // [B][kPoolParts]
+  float* band;             // [B] E
+  int* cnt;                // [B] candidates
+  int* cand;               // [B][N]
+  unsigned long long* keys;  // [B][N] best exact score of a candidate
+  int32_t* out_idx;
+  float* out_score;
+  int N, M, Hkv, k, m_blocks, part_docs, n_parts;
+  int block_tokens;        // tokens of a block
+  long long tiles;
+};
+
+__device__ __forceinline__ float pooled_of(const WidePoolArgs& a, int b, int doc) {
+  const float* p = a.mat + (long long)b * a.m_blocks * a.N + doc;
+  float x = p[0];
+  for (int i = 1; i < a.m_blocks; ++i) x = fmaxf(x, p[(long long)i * a.N]);
+  return x;
+}
+
+// a wave per part; the last workgroup of a batch row: E
+__global__ __launch_bounds__(256) void pool_parts_kernel(WidePoolArgs a) {
+  __shared__ float red[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int b = blockIdx.y;
+  float best = -INFINITY;
+  if (blockIdx.x == gridDim.x - 1) {  // block-uniform
+    best = 0.f;
+    for (int m = tid; m < a.M; m += 256) {
+      float e = 0.f;
+      for (int g = 0; g < a.Hkv; ++g) e += a.eps[((long long)b * a.M + m) * a.Hkv + g];
+      best = fmaxf(best, e / (float)a.Hkv);
+    }
+  } else {
+    const int part = blockIdx.x * 4 + wave;
+    const int d0 = part * a.part_docs, d1 = d0 + a.part_docs < a.N ? d0 + a.part_docs : a.N;
+    for (int d = d0 + lane; d < d1; d += 64) best = fmaxf(best, pooled_of(a, b, d));
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) best = fmaxf(best, __shfl_xor(best, off, 64));
+  if (blockIdx.x == gridDim.x - 1) {
+    if (lane == 0) red[wave] = best;
+    __syncthreads();
+    if (tid == 0) {
+      a.band[b] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+      a.cnt[b] = 0;
+    }
+  } else if (lane == 0 && blockIdx.x * 4 + wave < a.n_parts) {
+    a.parts[(long long)b * kPoolParts + blockIdx.x * 4 + wave] = best;
+  }
+}
+
+__global__ __launch_bounds__(256) void pool_cand_kernel(WidePoolArgs a) {
+  __shared__ uint32_t theta_w[2][4];
+  __shared__ int tie_w[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int b = blockIdx.y;
+  uint32_t ob = 0u;
+#pragma unroll
+  for (int i = 0; i < kPoolParts / 256; ++i) {
+    const int p = i * 256 + tid;
+    const uint32_t o = p < a.n_parts ? orderable(a.parts[(long long)b * kPoolParts + p]) : 0u;
+    ob = o > ob ? o : ob;
+  }
+  const float band = a.band[b];
+  const uint32_t theta = kth_best_bound<4>(ob, a.k, theta_w);
+  const uint32_t lim = theta ? orderable(unorderable(theta) - 2.f * band) : 0u;
+  const int d0 = blockIdx.x * 4 * a.part_docs, d1 = d0 + 4 * a.part_docs < a.N ? d0 + 4 * a.part_docs : a.N;
+  int ties = 0;  // documents so far that tie with the limit
+  for (int i0 = d0; i0 < d1; i0 += 256) {  // block-uniform
+    const int d = i0 + tid;
+    const float x = d < d1 ? pooled_of(a, b, d) : -INFINITY;
+    const uint32_t o = orderable(x);
+    bool take = d < d1 && o >= lim;
+    if (band == 0.f) {  // block-uniform: the scores are exact; documents that tie with the limit in their order
+      const bool tie = d < d1 && o == lim;
+      const unsigned long long m = __ballot(tie);
+      __syncthreads();
+      if (lane == 0) tie_w[wave] = __popcll(m);
+      __syncthreads();
+      int before = ties + __popcll(m & ((1ull << lane) - 1ull));
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        before += w < wave ? tie_w[w] : 0;
+        ties += tie_w[w];
+      }
+      take = take && !(tie && before >= a.k);
+    }
+    if (take) {
+      const int slot = atomicAdd(&a.cnt[b], 1);
+      a.cand[(long long)b * a.N + slot] = d;
+      a.keys[(long long)b * a.N + slot] = band == 0.f ? make_key(x, (uint32_t)d) : 0ull;
+    }
+  }
+}
+
+// A workgroup takes kPoolTok tokens and four candidates, one per wave: the folded queries of the tokens lie in LDS, the keys of a
+// candidate, already fp32, in registers (lane: 16 dims of a chunk's key of every group).  A candidate passes over the blocks of
+// tokens whose best matrix score is too far below its best to hold its exact best.  Bound by latency and the reads of the
+// queries: with eight tokens of one candidate per wave and the queries from memory it took 37 us of the call below and 82 of
+// 1000 tokens over 2000 documents, now 18 and 30.
+template <int HKV>
+__global__ __launch_bounds__(256) void pool_score_kernel(WidePoolArgs a) {
+  constexpr int D = 128, C = 8;
+  __shared__ float4 qs[kPoolTok][HKV][D / 4];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b = blockIdx.y;
+  const float band = a.band[b];
+  if (band == 0.f) return;  // block-uniform: the keys are there
+  const int nc = a.cnt[b], quads = (nc + 3) / 4, chunks = (a.M + kPoolTok - 1) / kPoolTok;
+  const int part = lane & 7, ch = lane >> 3;
+  const int block_rows = a.block_tokens;
+  for (long long it = blockIdx.x; it < (long long)quads * chunks; it += gridDim.x) {  // block-uniform
+    const int quad = (int)(it / chunks), m0 = (int)(it % chunks) * kPoolTok;
+    const int blk = m0 / block_rows;  // (kPoolTok divides a block)
+    int doc = 0;
+    unsigned need = 0u;  // the candidates that these tokens matter to (the same in every wave)
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const int ci = 4 * quad + w;
+      const int d = a.cand[(long long)b * a.N + (ci < nc ? ci : nc - 1)];
+      doc = w == wave ? d : doc;
+      const float here = a.mat[((long long)b * a.m_blocks + blk) * a.N + d];
+      if (ci < nc && (a.m_blocks == 1 || here >= pooled_of(a, b, d) - 2.f * band)) need |= 1u << w;
+    }
+    need = __builtin_amdgcn_readfirstlane(need);
+    if (need == 0u) continue;
+    const int nt = a.M - m0 < kPoolTok ? a.M - m0 : kPoolTok;
+    __syncthreads();  // the queries of the item before are done with
+    {
+      const float4* src = reinterpret_cast<const float4*>(a.qf + ((long long)b * a.M + m0) * (HKV * D));
+      float4* dst = &qs[0][0][0];
+      for (int i = tid; i < nt * (HKV * D / 4); i += 256) dst[i] = src[i];
+    }
+    float kf[HKV][16], inv[HKV];
+    if ((need >> wave) & 1u) {
+      const long long key = (long long)doc * C + ch;
+      const uint16_t* kp = a.KR + (key >> 4) * (16 * D) + (part * (D / 64) * 16 + (int)(key & 15)) * 8;
+#pragma unroll
+      for (int g = 0; g < HKV; ++g) {
+        const uint16_t* p = kp + (long long)g * a.tiles * (16 * D);
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+          const uint4 w = *reinterpret_cast<const uint4*>(p + 128 * x);
+          const uint32_t v[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            kf[g][8 * x + 2 * i] = bf16_lo(v[i]);
+            kf[g][8 * x + 2 * i + 1] = bf16_hi(v[i]);
+          }
+        }
+        inv[g] = a.inv_norm[(long long)g * a.tiles * 16 + key];
+      }
+    }
+    __syncthreads();
+    if (((need >> wave) & 1u) == 0u) continue;  // wave-uniform; the next item's barriers come for every wave
+    float best = -INFINITY;
+    for (int t = 0; t < nt; ++t) {  // block-uniform
+      float tot = 0.f;
+#pragma unroll
+      for (int g = 0; g < HKV; ++g) {
+        float acc = 0.f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float4 q = qs[t][g][part * 4 + i];
+          acc = fmaf(q.x, kf[g][4 * i], acc);
+          acc = fmaf(q.y, kf[g][4 * i + 1], acc);
+          acc = fmaf(q.z, kf[g][4 * i + 2], acc);
+          acc = fmaf(q.w, kf[g][4 * i + 3], acc);
+        }
+        acc += dpp_f<kDppXor1>(acc);
+        acc += dpp_f<kDppXor2>(acc);
+        acc += dpp_f<kDppHalfMirror>(acc);  // the key's dot product, in its eight lanes
+        tot += acc * inv[g];
+      }
+      best = fmaxf(best, tot * (1.0f / (float)HKV));
+    }
+#pragma unroll
+    for (int off = 8; off < 8 * C; off <<= 1) best = fmaxf(best, __shfl_xor(best, off, 64));  // document max over its chunks
+    if (lane == 0) atomicMax(&a.keys[(long long)b * a.N + 4 * quad + wave], make_key(best, (uint32_t)doc));
+  }
+}
+
+constexpr int kPoolBest = 2048;  // candidates that LDS holds
+
+__global__ __launch_bounds__(512) void pool_best_kernel(WidePoolArgs a) {
+  __shared__ unsigned long long surv[kPoolBest];
+  __shared__ unsigned long long red[8];
+  __shared__ uint32_t theta_w[2][8];
+  __shared__ int n_surv;
+  const int tid = threadIdx.x;
+  const int b = blockIdx.x;
+  const unsigned long long* keys = a.keys + (long long)b * a.N;
+  const int nc = a.cnt[b];
+  if (tid == 0) n_surv = 0;
+  uint32_t ob = 0u;
+  for (int i = tid; i < nc; i += 512) {
+    const uint32_t o = (uint32_t)(keys[i] >> 32);
+    ob = o > ob ? o : ob;
+  }
+  const uint32_t theta = kth_best_bound<8>(ob, a.k, theta_w);  // (a barrier inside)
+  for (int i = tid; i < nc; i += 512) {
+    const unsigned long long x = keys[i];
+    if ((uint32_t)(x >> 32) >= theta) {
+      const int slot = atomicAdd(&n_surv, 1);
+      if (slot < kPoolBest) surv[slot] = x;
+    }
+  }
+  __syncthreads();
+  const int ns = n_surv;
+  auto emit = [&](int rank, unsigned long long x) {
+    const long long o = (long long)b * a.k + rank;
+    a.out_idx[o] = x ? (int32_t)key_doc(x) : -1;
+    if (a.out_score != nullptr) a.out_score[o] = x ? key_score(x) : -INFINITY;
+  };
+  if (ns <= kPoolBest) {
+    for (int i = tid; i < ns; i += 512) {
+      const unsigned long long x = surv[i];
+      int rank = 0;
+      for (int j = 0; j < ns; j += 8) {  // eight at a time, past the end whatever is there
+        unsigned long long y[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) y[u] = surv[j + u < kPoolBest ? j + u : 0];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) rank += (j + u < ns && y[u] > x) ? 1 : 0;
+      }
+      if (rank < a.k) emit(rank, x);
+    }
+    for (int i = ns + tid; i < a.k; i += 512) emit(i, 0ull);
+    return;
+  }
+  // more (copies of the best documents): k rounds of the largest key below the one before
+  unsigned long long prev = ~0ull;
+  for (int round = 0; round < a.k; ++round) {
+    unsigned long long best = 0ull;
+    for (int i = tid; i < nc; i += 512) {
+      const unsigned long long x = keys[i];
+      if (x < prev && x > best) best = x;
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      const unsigned long long y = __shfl_xor(best, off, 64);
+      best = y > best ? y : best;
+    }
+    __syncthreads();
+    if ((tid & 63) == 0) red[tid >> 6] = best;
+    __syncthreads();
+    best = red[0];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) best = red[w] > best ? red[w] : best;
+    if (tid == 0) emit(round, best);
+    prev = best;
+  }
+}
+
 // ---- host side -----------------------------------------------------------------------------------------------------
 // More tokens than one pass of the all-heads scan takes.
 bool wide_path_applies(const Dims& dm, int BM) { return dm.scope_all && dm.Hkv > 1 && BM > 32; }
@@ -718,6 +1041,105 @@ WidePlan plan_score_wide(const Dims& dm, int BM, int k) {
   return p;
 }
 
+WidePoolPlan plan_score_wide_pool(const Dims& dm, const WidePlan& pl, int B, int M, int k) {
+  WidePoolPlan p = {};
+  if (!dm.token_pool || pl.pair || M <= 32 || M > kPoolMost || B * M > kWidePass) return p;
+  p.m_blocks = (M + 16 * kRowsMost - 1) / (16 * kRowsMost);
+  // Every block reads the index: not where the blocks of the batch rows are more than those of 64 of all tokens (3 questions of
+  // 40 tokens over 60000 documents 277 -> 348 us).
+  if (B * p.m_blocks > (B * M + kWideRows - 1) / kWideRows) return p;
+  p.nt = ((M + p.m_blocks - 1) / p.m_blocks + 31) / 32 * 2;
+  p.m_tiles = (M + 15) / 16;
+  p.part_docs = (dm.N + kPoolParts - 1) / kPoolParts;
+  p.n_parts = (dm.N + p.part_docs - 1) / p.part_docs;
+  size_t end = 0;
+  auto take = [&](size_t bytes) {
+    const size_t at = end;
+    end += round_up256(bytes);
+    return at;
+  };
+  p.off_qf = take((size_t)B * M * dm.Hkv * dm.d * sizeof(float));
+  p.off_qop = take((size_t)dm.Hkv * B * p.m_tiles * (dm.d / 32) * 64 * 16);
+  p.off_eps = take((size_t)B * M * dm.Hkv * sizeof(float));
+  p.off_mat = take((size_t)B * p.m_blocks * dm.N * sizeof(float));
+  p.off_parts = take((size_t)B * kPoolParts * sizeof(float));
+  p.off_band = take((size_t)B * sizeof(float));
+  p.off_cnt = take((size_t)B * sizeof(int));
+  p.off_cand = take((size_t)B * dm.N * sizeof(int));
+  p.off_keys = take((size_t)B * dm.N * sizeof(unsigned long long));
+  p.applies = end <= pl.ws_bytes ? 1 : 0;  // (the bytes that a call has always been asked for)
+  return p;
+}
+
+int launch_score_wide_pool(const Dims& dm, const WidePoolPlan& pp, const void* q_route, int B, int M, const void* KR,
+                           const float* inv_norm, int k, void* ws, hipStream_t st, int32_t* out_idx, float* out_score) {
+  char* const w = (char*)ws;
+  const int n_rt = B * pp.m_tiles;
+  const int rc = launch_fold_queries(dm, q_route, B * M, (float*)(w + pp.off_qf), (float*)(w + pp.off_eps), nullptr, 0,
+                                     (uint4*)(w + pp.off_qop), n_rt, 0, M, 16 * pp.m_tiles, st);
+  if (rc != MSA_OK) return rc;
+  WideArgs a = {};
+  a.qop = (const uint4*)(w + pp.off_qop);
+  a.KR = (const uint16_t*)KR;
+  a.inv_norm = inv_norm;
+  a.mat = (float*)(w + pp.off_mat);
+  a.mat_stride = dm.N;
+  a.n_rt = n_rt;
+  a.n_tb = B * pp.m_blocks;
+  a.nq = B * M;
+  a.C = dm.C;
+  a.tiles = dm.tiles;
+  a.seg_tiles = (int)dm.tiles;
+  a.seg_docs = dm.N;
+  a.Hkv = dm.Hkv;
+  a.M = M;
+  a.m_tiles = pp.m_tiles;
+  a.m_blocks = pp.m_blocks;
+  const int units = (a.seg_tiles + kRowsTiles - 1) / kRowsTiles, most = (units + kRowsWaves - 1) / kRowsWaves;
+  a.n_streams = kWideGroups / a.n_tb;
+  if (a.n_streams < 1) a.n_streams = 1;
+  if (a.n_streams > most) a.n_streams = most;
+  const dim3 grid((unsigned)((a.n_tb * a.n_streams + 7) / 8 * 8)), block(64 * kRowsWaves);
+  profile_mark(dm, false, st);
+  if (pp.nt <= 4) hipLaunchKernelGGL((score_wide_rows_kernel<4, true>), grid, block, 0, st, a);
+  else if (pp.nt == 6) hipLaunchKernelGGL((score_wide_rows_kernel<6, true>), grid, block, 0, st, a);
+  else if (pp.nt == 8) hipLaunchKernelGGL((score_wide_rows_kernel<8, true>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((score_wide_rows_kernel<10, true>), grid, block, 0, st, a);
+  profile_mark(dm, true, st);
+  if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
+  WidePoolArgs p;
+  p.mat = a.mat;
+  p.eps = (const float*)(w + pp.off_eps);
+  p.qf = (const float*)(w + pp.off_qf);
+  p.KR = a.KR;
+  p.inv_norm = inv_norm;
+  p.parts = (float*)(w + pp.off_parts);
+  p.band = (float*)(w + pp.off_band);
+  p.cnt = (int*)(w + pp.off_cnt);
+  p.cand = (int*)(w + pp.off_cand);
+  p.keys = (unsigned long long*)(w + pp.off_keys);
+  p.out_idx = out_idx;
+  p.out_score = out_score;
+  p.N = dm.N;
+  p.M = M;
+  p.Hkv = dm.Hkv;
+  p.k = k;
+  p.m_blocks = pp.m_blocks;
+  p.block_tokens = 16 * pp.nt;
+  p.part_docs = pp.part_docs;
+  p.n_parts = pp.n_parts;
+  p.tiles = dm.tiles;
+  const unsigned quads = (unsigned)((pp.n_parts + 3) / 4);
+  hipLaunchKernelGGL(pool_parts_kernel, dim3(quads + 1, (unsigned)B), dim3(256), 0, st, p);
+  hipLaunchKernelGGL(pool_cand_kernel, dim3(quads, (unsigned)B), dim3(256), 0, st, p);
+  const dim3 sgrid(512, (unsigned)B);  // (about 100 candidates and 20 chunks of tokens)
+  if (dm.Hkv == 2) hipLaunchKernelGGL(pool_score_kernel<2>, sgrid, dim3(256), 0, st, p);
+  else if (dm.Hkv == 4) hipLaunchKernelGGL(pool_score_kernel<4>, sgrid, dim3(256), 0, st, p);
+  else hipLaunchKernelGGL(pool_score_kernel<8>, sgrid, dim3(256), 0, st, p);
+  hipLaunchKernelGGL(pool_best_kernel, dim3((unsigned)B), dim3(512), 0, st, p);
+  return hipGetLastError() == hipSuccess ? MSA_OK : MSA_ERR_HIP;
+}
+
 int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, int BM, const void* KR,
                       const float* inv_norm, int k, void* ws, hipStream_t st, int32_t* out_idx, float* out_score,
                       unsigned long long* out_key) {
@@ -751,9 +1173,11 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
     a.nq = nq;
     a.n_rt = pl.n_tb * (kWideRows / 16);
     a.Hkv = dm.Hkv;
+    a.M = nq;
+    a.m_tiles = a.n_rt;
     const int rc = launch_fold_queries(dm, (const uint16_t*)q_route + (size_t)tok0 * dm.Hq * dm.d, nq,
                                        (float*)(w + pl.off_qf), pl.pair ? nullptr : (float*)(w + pl.off_eps), nullptr, 0,
-                                       (uint4*)(w + pl.off_qop), a.n_rt, pl.pair, st);
+                                       (uint4*)(w + pl.off_qop), a.n_rt, pl.pair, nq, nq, st);
     if (rc != MSA_OK) return rc;
     for (int doc0 = 0; doc0 < dm.N; doc0 += pl.seg_docs) {
       const int n_docs = dm.N - doc0 < pl.seg_docs ? dm.N - doc0 : pl.seg_docs;
@@ -777,6 +1201,7 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
       const int most = (units + waves - 1) / waves;
       if (streams > most) streams = most;
       a.n_streams = streams;
+      a.m_blocks = a.n_tb;
       dim3 grid((unsigned)((a.n_tb * streams + 7) / 8 * 8)), block(64 * waves);
       if (tok0 == 0 && doc0 == 0) profile_mark(dm, false, st);
 #define MSA_WIDE(DD, HH) \
@@ -786,9 +1211,9 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
     else hipLaunchKernelGGL((score_wide_kernel<DD, HH, true, false>), grid, block, 0, st, a); \
   } while (0)
       if (rows) {
-        if (nt == 6) hipLaunchKernelGGL(score_wide_rows_kernel<6>, grid, block, 0, st, a);
-        else if (nt == 8) hipLaunchKernelGGL(score_wide_rows_kernel<8>, grid, block, 0, st, a);
-        else hipLaunchKernelGGL(score_wide_rows_kernel<10>, grid, block, 0, st, a);
+        if (nt == 6) hipLaunchKernelGGL((score_wide_rows_kernel<6, false>), grid, block, 0, st, a);
+        else if (nt == 8) hipLaunchKernelGGL((score_wide_rows_kernel<8, false>), grid, block, 0, st, a);
+        else hipLaunchKernelGGL((score_wide_rows_kernel<10, false>), grid, block, 0, st, a);
       } else if (dm.d == 128) {
         if (dm.Hkv == 2) MSA_WIDE(128, 2); else if (dm.Hkv == 4) MSA_WIDE(128, 4); else MSA_WIDE(128, 8);
       } else {

@@ -208,6 +208,48 @@ def test_all_heads_wide_rows(N, Hkv, r, C, d, B, M, k, sim):
     test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim)
 
 
+# tokens pooled by document: one token more than the scan takes, several blocks of tokens, batch rows, parts of one document
+POOL_DOCS = [(700, 2, 2, 8, 128, 1, 33, 20, "cos"), (1030, 4, 1, 8, 128, 2, 100, 9, "cos"), (64, 4, 2, 8, 128, 1, 330, 64, "cos"),
+             (515, 2, 1, 8, 128, 1, 1000, 5, "cos"), (2600, 8, 1, 8, 128, 4, 66, 33, "cos"), (40, 8, 1, 8, 128, 1, 40, 40, "cos"),
+             (5, 2, 1, 8, 128, 1, 49, 1, "cos")]
+
+
+@pytest.mark.parametrize("N,Hkv,r,C,d,B,M,k,sim", POOL_DOCS)
+def test_token_pooling_by_document(N, Hkv, r, C, d, B, M, k, sim):
+    test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim)
+
+
+@pytest.mark.parametrize("N,copies,k,zeros", [(6000, 3000, 16, 0), (3000, 100, 64, 39), (9000, 0, 64, 40)])
+def test_token_pooling_of_copies_and_zeros(N, copies, k, zeros):
+    """The best documents are copies of one (more of them than the last kernel's LDS takes), zeros of the 40 tokens are
+    zeros: copies are selected in their order, and with zeros alone the first k documents.  Against float64 scores."""
+    Hkv, d, M = 4, 128, 40
+    say(f"token pooling N={N} copies={copies} k={k} zeros={zeros}")
+    cfg = msa.MsaConfig(N, 64, 8, Hkv, Hkv, d, 1e6, select_scope=msa.MSA_SCOPE_ALL, token_pool=1)
+    KRb, _ = random_index(59000 + N, N, Hkv, 8, d)
+    qb, q = S.normal_bf16(59001, (1, M, Hkv, d))
+    qb, q = qb.copy(), q.copy()
+    qb[:, M - zeros:], q[:, M - zeros:] = 0, 0
+    at = np.arange(N - 1, N - 1 - copies, -1)
+    if copies:
+        KRb.reshape(Hkv, N, 8, d)[:, at, :] = q[0, 0][:, None, None, :]   # what the first token asks for, in every chunk
+    inv = 1.0 / np.maximum(np.linalg.norm(KRb, axis=-1), O.EPS_NORM)
+    dKR, dinv = upload_oracle_index(cfg, KRb, inv)
+    ws = torch.full((msa.score_topk_workspace_bytes(cfg, 1, M, k),), 0xFF, dtype=torch.uint8, device="cuda")
+    idx, val = msa.msa_score_topk(cfg, dev(qb), dKR, dinv, k, workspace=ws)
+    torch.cuda.synchronize()
+    _, ov, s = O.score_topk(q, KRb, 8, k, select_scope="all", token_pool=True)
+    gi, gv = idx.cpu().numpy().reshape(-1), val.cpu().numpy().reshape(-1)
+    assert len(set(gi.tolist())) == k
+    assert np.max(np.abs(gv - np.asarray(s, dtype=np.float64).reshape(-1)[gi])) <= 2e-5
+    assert np.max(np.abs(gv - np.asarray(ov).reshape(-1))) <= 2e-5
+    if copies:
+        n = min(copies, k)
+        assert np.array_equal(gi[:n], np.arange(N - copies, N - copies + n))
+    elif zeros == M:
+        assert np.array_equal(gi, np.arange(k)) and np.all(gv == 0)
+
+
 # (N, Hkv, C, d, B, M, k, scope, pool): a row's k best where every document ties
 ALL_TIED = [
     (9000, 2, 8, 64, 3, 1, 16, "group", 0),       # row top-k, four waves, part of the row beyond the registers
