@@ -43,6 +43,7 @@ struct GemmPlan {
 };
 constexpr int kFilterMaxCand = 64;
 bool gemm_path_applies(const Dims& dm, int BM, int k);
+bool gemm_path_of_two_passes(const Dims& dm, int BM, int k);
 GemmPlan plan_score_gemm(const Dims& dm, int BM, int k);
 // Enqueues the scoring kernels.  Without the filter the per-split lists are left for score_merge_kernel.  With it
 // the exact winners of every token are written to out_idx / out_score (or out_key: sorted 64-bit keys, token pooling),

@@ -1447,13 +1447,13 @@ static void plan_all_heads(const Dims& dm, int BM, int k, ScorePlan* p) {
   p->ws_bytes = end;
 }
 
-static ScorePlan plan_score_least(const Dims& dm, int BM, int k) {
+static ScorePlan plan_score_least(const Dims& dm, int BM, int k, bool two_passes = false) {
   ScorePlan p;
   // one selection per KV group, or (literal Eq. 2 head mean, more than one group) one for all heads
   p.all_heads = (dm.scope_all && dm.Hkv > 1) ? 1 : 0;
   p.n_sel = dm.scope_all ? 1 : dm.Hkv;
   p.use_wide = wide_path_applies(dm, BM) ? 1 : 0;
-  p.use_gemm = !p.use_wide && gemm_path_applies(dm, BM, k) ? 1 : 0;
+  p.use_gemm = !p.use_wide && (two_passes || gemm_path_applies(dm, BM, k)) ? 1 : 0;
   if (p.use_wide) {
     p.wide = plan_score_wide(dm, BM, k);
     p.n_splits = 1;
@@ -1537,6 +1537,13 @@ static ScorePlan plan_score_least(const Dims& dm, int BM, int k) {
 ScorePlan plan_score(const Dims& dm, int BM, int k, size_t workspace_bytes) {
   ScorePlan p = plan_score_least(dm, BM, k);
   p.ws_best = p.ws_bytes;
+  if (!p.use_wide && !p.use_gemm && gemm_path_of_two_passes(dm, BM, k)) {
+    ScorePlan g = plan_score_least(dm, BM, k, true);
+    if (g.ws_bytes <= p.ws_bytes) {  // (in the workspace that the scan asks for)
+      g.ws_bytes = g.ws_best = p.ws_bytes;
+      return g;
+    }
+  }
   if (p.use_wide && p.wide.list_bytes > 0) {
     // (asked for only where the built-in scratch, if it serves the call, still does)
     const size_t with = p.ws_bytes + p.wide.list_bytes;

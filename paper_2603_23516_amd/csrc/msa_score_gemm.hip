@@ -668,6 +668,18 @@ bool gemm_path_applies(const Dims& dm, int BM, int k) {
   return passes - (one_pass ? 2 : 4) >= ((one_pass ? 500000 : 1250000) + work - 1) / work;
 }
 
+// 33 to 63 tokens, two or more passes of the scan: the GEMM reads the index once, its token block of 128 half empty.  Worth it
+// from about 8000 documents of eight chunks and heads on, with k > 16, where its splits are half as many, from 20000 (48 tokens,
+// k = 8: 6000 documents 55 us by the scan, 54 here, 16000 131.5, 87, 40000 367, 158, 97000 709, 327; 33 of k = 16: 16000 130, 98,
+// 97000 664, 404; 48 of k = 24: 16000 133, 139, 40000 383, 240).  Four heads fill the chip half, so from twice the documents on
+// (33 of k = 8: 16000 66.6, 70.7, 40000 158, 116; k = 30 217, 235), two never (40000: 81, 114).  One pass, up to 32 tokens, is the
+// scan's (24 tokens, k = 16, 97000 documents 360, 397).
+bool gemm_path_of_two_passes(const Dims& dm, int BM, int k) {
+  if (!one_pass_shape(dm) || BM <= 32 || BM >= 64 || k > kGemmMaxK) return false;
+  if (dm.Hkv == 8) return dm.NC >= (k <= 16 ? 64000 : 160000);
+  return dm.Hkv == 4 && k <= 16 && dm.NC >= 320000;
+}
+
 static GemmPlan gemm_split(const Dims& dm, int BM, int k, bool small) {
   GemmPlan p;
   const int tokens_per_wg = (k <= 8) ? 256 : 128;

@@ -150,6 +150,16 @@ def test_prefill_scoring_k_above_16(N, Hkv, r, C, d, B, M, k, sim):
         check_topk_generic(q, KRb, C, N, idx, val, k, sim, "group", pool, atol=2e-5 if sim == "cos" else 2e-4)
 
 
+# 33 to 63 tokens over a bank that the scan would read twice: the GEMM from 64000 keys a head on (k > 16: 160000)
+GEMM_TWO_PASSES = [(8000, 8, 1, 8, 128, 33, 1, 8, "cos"), (8001, 8, 2, 8, 128, 3, 21, 16, "cos"), (7999, 8, 1, 8, 128, 40, 1, 8, "cos"),
+                   (20003, 8, 1, 8, 128, 35, 1, 24, "cos"), (8200, 8, 1, 8, 128, 32, 1, 8, "cos"), (40001, 4, 1, 8, 128, 63, 1, 5, "cos")]
+
+
+@pytest.mark.parametrize("N,Hkv,r,C,d,B,M,k,sim", GEMM_TWO_PASSES)
+def test_scoring_gemm_of_two_passes(N, Hkv, r, C, d, B, M, k, sim):
+    test_prefill_scoring_k_above_16(N, Hkv, r, C, d, B, M, k, sim)
+
+
 @pytest.mark.parametrize("M", [250, 700, 2000])
 def test_token_pooling_of_many_documents(M):
     """One query head: the tokens' scores are alike and most of their listed documents reach the floor: 1300 and about
