@@ -58,59 +58,71 @@ __device__ __forceinline__ float both_halves_sum(float x) {
 // the step numbering and the row clamping are the tiled kernel's (all Lloc local rows are prepared,
 // whatever the tokens of a tile can see).  Angles come straight from a double-precision range
 // reduction: no recurrence, so these keys are if anything more accurate than in-kernel rotation.
-template <int D>
-__global__ __launch_bounds__(256) void rotate_steps_kernel(AttendArgs a, RopeTheta th, uint16_t* __restrict__ Krot) {
+// Bound by those angles (two thirds of 13.6 us for 288 steps of 8 heads), which are the same for every head: a workgroup takes
+// the step of `heads` of them and works its angles out once (13.6 -> 10 us; two questions of 355 tokens 10.7 -> 8.8).  Grids that
+// leave the chip idle keep a head per workgroup (MULTI false).
+template <int D, bool MULTI>
+__global__ __launch_bounds__(256) void rotate_steps_kernel(AttendArgs a, RopeTheta th, uint16_t* __restrict__ Krot, int heads) {
   constexpr int HALF = D / 2;
   constexpr int PPH = D / 16;
   const int tid = threadIdx.x;
   if (tid >= 32 * PPH) return;
   const int kr = tid / PPH, pc = tid % PPH;
-  const int st = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
-  const uint16_t* Kb;
-  int rows_valid, p_first;
-  if (st < a.steps_mem) {
-    const long long idx_row = (a.idx_rows_per_b == 1) ? b : (long long)b * a.M;
-    const int32_t* idx_g = a.idx + (idx_row * a.idx_sel + (a.idx_sel == 1 ? 0 : g)) * a.k;
-    const int tok = st * 32;
-    const int slot = tok / a.G;
-    const int pin = tok - slot * a.G;
-    const int doc = idx_g[slot];
-    if (doc < 0 || doc >= a.N) return;
-    int len = a.G;
-    if (a.lens != nullptr) {
-      len = a.lens[doc];
-      len = len < 1 ? 1 : (len > a.G ? a.G : len);
-    }
-    if (pin >= len) return;
-    Kb = a.K + (((long long)doc * a.Hkv + g) * a.G + pin) * D;
-    rows_valid = len - pin < 32 ? len - pin : 32;
-    p_first = pin;
-  } else {
-    const int t0 = (st - a.steps_mem) * 32;
-    if (t0 >= a.Lloc) return;
-    Kb = a.Kloc + (((long long)b * a.Hkv + g) * a.Lloc + t0) * D;
-    rows_valid = a.Lloc - t0 < 32 ? a.Lloc - t0 : 32;
-    p_first = a.pos0 + t0;
-  }
-  const int row = kr < rows_valid ? kr : rows_valid - 1;
-  const uint16_t* rp = Kb + (long long)row * D + pc * 8;
-  const uint4 k1 = *reinterpret_cast<const uint4*>(rp);
-  const uint4 k2 = *reinterpret_cast<const uint4*>(rp + HALF);
-  const uint32_t w1[4] = {k1.x, k1.y, k1.z, k1.w}, w2[4] = {k2.x, k2.y, k2.z, k2.w};
-  uint32_t y1[4], y2[4];
+  const int st = blockIdx.x, b = blockIdx.z;
+  const bool is_mem = st < a.steps_mem;
+  const int slot = is_mem ? st * 32 / a.G : 0, pin = st * 32 - slot * a.G;
+  const int t0 = (st - a.steps_mem) * 32;
+  if (!is_mem && t0 >= a.Lloc) return;
+  const long long idx_row = (a.idx_rows_per_b == 1) ? b : (long long)b * a.M;
+  const int p = (is_mem ? pin : a.pos0 + t0) + kr;  // position of this thread's row (a row that does not exist is masked later)
+  float2 c[8];
+  if (MULTI) {
 #pragma unroll
-  for (int jj = 0; jj < 4; ++jj) {
-    const float2 c0 = cis_pos(p_first + row, th.th[8 * pc + 2 * jj]);
-    const float2 c1 = cis_pos(p_first + row, th.th[8 * pc + 2 * jj + 1]);
-    const float p0 = bf16_lo(w1[jj]), p1 = bf16_hi(w1[jj]);
-    const float q0 = bf16_lo(w2[jj]), q1 = bf16_hi(w2[jj]);
-    y1[jj] = pack_bf16(p0 * c0.x - q0 * c0.y, p1 * c1.x - q1 * c1.y);
-    y2[jj] = pack_bf16(q0 * c0.x + p0 * c0.y, q1 * c1.x + p1 * c1.y);
+    for (int j = 0; j < 8; ++j) c[j] = cis_pos(p, th.th[8 * pc + j]);
   }
-  unsigned char* blk = reinterpret_cast<unsigned char*>(Krot) +
-                       (((long long)b * a.Hkv + g) * a.steps_total + st) * (32 * D * 2);
-  *reinterpret_cast<uint4*>(&blk[(pc * 32 + kr) * 16]) = make_uint4(y1[0], y1[1], y1[2], y1[3]);
-  *reinterpret_cast<uint4*>(&blk[((pc + PPH) * 32 + kr) * 16]) = make_uint4(y2[0], y2[1], y2[2], y2[3]);
+  const int g0 = MULTI ? blockIdx.y * heads : blockIdx.y;
+  const int g1 = MULTI ? (g0 + heads < a.Hkv ? g0 + heads : a.Hkv) : g0 + 1;
+  for (int g = g0; g < g1; ++g) {  // block-uniform
+    const uint16_t* Kb;
+    int rows_valid;
+    if (is_mem) {
+      const int doc = a.idx[(idx_row * a.idx_sel + (a.idx_sel == 1 ? 0 : g)) * a.k + slot];
+      if (doc < 0 || doc >= a.N) continue;
+      int len = a.G;
+      if (a.lens != nullptr) {
+        len = a.lens[doc];
+        len = len < 1 ? 1 : (len > a.G ? a.G : len);
+      }
+      if (pin >= len) continue;
+      Kb = a.K + (((long long)doc * a.Hkv + g) * a.G + pin) * D;
+      rows_valid = len - pin < 32 ? len - pin : 32;
+    } else {
+      Kb = a.Kloc + (((long long)b * a.Hkv + g) * a.Lloc + t0) * D;
+      rows_valid = a.Lloc - t0 < 32 ? a.Lloc - t0 : 32;
+    }
+    const int row = kr < rows_valid ? kr : rows_valid - 1;
+    const uint16_t* rp = Kb + (long long)row * D + pc * 8;
+    const uint4 k1 = *reinterpret_cast<const uint4*>(rp);
+    const uint4 k2 = *reinterpret_cast<const uint4*>(rp + HALF);
+    const uint32_t w1[4] = {k1.x, k1.y, k1.z, k1.w}, w2[4] = {k2.x, k2.y, k2.z, k2.w};
+    uint32_t y1[4], y2[4];
+    if (!MULTI) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) c[j] = cis_pos(p, th.th[8 * pc + j]);
+    }
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      const float2 c0 = c[2 * jj], c1 = c[2 * jj + 1];
+      const float p0 = bf16_lo(w1[jj]), p1 = bf16_hi(w1[jj]);
+      const float q0 = bf16_lo(w2[jj]), q1 = bf16_hi(w2[jj]);
+      y1[jj] = pack_bf16(p0 * c0.x - q0 * c0.y, p1 * c1.x - q1 * c1.y);
+      y2[jj] = pack_bf16(q0 * c0.x + p0 * c0.y, q1 * c1.x + p1 * c1.y);
+    }
+    unsigned char* blk = reinterpret_cast<unsigned char*>(Krot) +
+                         (((long long)b * a.Hkv + g) * a.steps_total + st) * (32 * D * 2);
+    *reinterpret_cast<uint4*>(&blk[(pc * 32 + kr) * 16]) = make_uint4(y1[0], y1[1], y1[2], y1[3]);
+    *reinterpret_cast<uint4*>(&blk[((pc + PPH) * 32 + kr) * 16]) = make_uint4(y2[0], y2[1], y2[2], y2[3]);
+  }
 }
 
 template <int D>
@@ -176,7 +188,8 @@ void attend_prefill_kernel(AttendArgs a, RopeTheta th, int tpw,
   // the (still unused) key buffer
   float2* ang = reinterpret_cast<float2*>(smem) + wave * (16 * HALF);  // [16][HALF]
   for (int rd = 0; rd * 16 < tpw; ++rd) {
-    for (int e = lane; e < 16 * HALF; e += 64) {
+    // (only the wave's own: eight at r = 4; working out sixteen took 3 us of a kernel of 13)
+    for (int e = lane; e < (tpw < 16 ? tpw : 16) * HALF; e += 64) {
       const int t16 = e / HALF, u = e % HALF;
       const int m = m_tile + wave * tpw + rd * 16 + t16;
       const int qp = (rd * 16 + t16 < tpw && m < a.M) ? a.q_pos[(long long)b * a.M + m] : 0;
@@ -523,11 +536,18 @@ int launch_attend_prefill_partial(const Dims& dm, const AttendPlan& pl, const At
                                   const RopeTheta& th, int B, hipStream_t st, bool dominant) {
   if (a.Krot == nullptr) return MSA_ERR_INVALID_ARG;  // the plan always reserves the rotated keys
   {
-    dim3 rgrid(a.steps_total, dm.Hkv, B);
-    if (dm.d == 128)
-      hipLaunchKernelGGL(rotate_steps_kernel<128>, rgrid, dim3(256), 0, st, a, th, const_cast<uint16_t*>(a.Krot));
-    else
-      hipLaunchKernelGGL(rotate_steps_kernel<64>, rgrid, dim3(256), 0, st, a, th, const_cast<uint16_t*>(a.Krot));
+    // heads per workgroup: as many as leave two workgroups per CU
+    int heads = 1;
+    while (heads < dm.Hkv && (long long)a.steps_total * B * dm.Hkv >= 512ll * 2 * heads) heads *= 2;
+    dim3 rgrid(a.steps_total, (dm.Hkv + heads - 1) / heads, B);
+#define MSA_ROTATE(DD, MM) \
+  hipLaunchKernelGGL((rotate_steps_kernel<DD, MM>), rgrid, dim3(256), 0, st, a, th, const_cast<uint16_t*>(a.Krot), heads)
+    if (dm.d == 128) {
+      if (heads > 1) MSA_ROTATE(128, true); else MSA_ROTATE(128, false);
+    } else {
+      if (heads > 1) MSA_ROTATE(64, true); else MSA_ROTATE(64, false);
+    }
+#undef MSA_ROTATE
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
   }
   dim3 grid(pl.n_splits, dm.Hkv, B * pl.n_ttiles), block(256);
