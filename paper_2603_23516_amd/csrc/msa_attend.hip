@@ -235,13 +235,15 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
     const uint16_t* Vb;
     int rows_valid, p_first;
     int slot, pin;  // MODE 0, 1, whole slots, memory steps: slot of the selection, first row of the step in its document
-    int doc;        // MODE 2, memory steps: document of the step's key row `lane % 32`
+    unsigned row;   // MODE 2, memory steps: bank row of the step's key row `lane % 32`
     unsigned mask;  // MODE 2, memory steps: bit i set = key row i belongs to a valid selection
     bool is_mem;    // a step over selected documents (else local context)
   };
-  // MODE 2: the document of every key row of memory step st, once per step in lanes 0 .. 31 (and again in 32 .. 63); the
-  // requests below fetch it from the lane that has it.  Rows of pads, of ids outside the bank and past the k-th document
-  // read document 0 (always present) so that their loads stay inside the bank; their scores are masked.
+  // MODE 2: the bank row of every key row of memory step st, once per step in lanes 0 .. 31 (and again in 32 .. 63); the
+  // requests below fetch it from the lane that has it.  Rows of pads, of ids outside the bank, past a document's end and
+  // past the k-th document read the first row of document 0, which every bank has (a row past a document's end may hold
+  // anything, and a value that is not a number is one with a weight of zero too); their scores are masked.  Fewer than 2^32
+  // rows: of at least 128 bytes each.
   auto gather_rows = [&](int st, StepSrc& ss) {
     const int tok = st * 32 + (lane & 31);
     const int slot = tok >> a.gshift;
@@ -249,12 +251,12 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
     const int doc = __shfl(my_idx, slot < a.k ? slot : 0, 64);
     const int len = __shfl(my_len, slot < a.k ? slot : 0, 64);
     const bool ok = slot < a.k && doc >= 0 && doc < a.N && pin < len;
-    ss.doc = ok ? doc : 0;
+    ss.row = ok ? ((unsigned)doc * a.Hkv + g) * a.G + pin : (unsigned)(g * a.G);
     ss.mask = (unsigned)__ballot(ok);  // lanes 0..31 cover the 32 rows
   };
-  // ... and the byte offset of key row `row`, whose document is `doc`, in the bank (G <= 16 divides a step)
-  auto row_offset = [&](int doc, int row) -> unsigned long long {
-    return (unsigned long long)(unsigned)doc * (unsigned)(a.Hkv * a.G * D * 2) + (unsigned)((g * a.G + (row & (a.G - 1))) * D * 2);
+  // ... and the byte offset in the bank of key row `row` of the step
+  auto row_offset = [&](const StepSrc& ss, int row) -> unsigned long long {
+    return (unsigned long long)(unsigned)__shfl((int)ss.row, row, 64) * (unsigned)(D * 2);
   };
   auto locate = [&](int st, StepSrc& ss) -> bool {
     ss.mask = 0xffffffffu;
@@ -345,7 +347,7 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
     if (MODE == 2 && ss.is_mem) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const unsigned long long off = row_offset(__shfl(ss.doc, 16 * h + n, 64), n);
+        const unsigned long long off = row_offset(ss, 16 * h + n);
 #pragma unroll
         for (int s = 0; s < NS; ++s) kr[h][s] = ld((gvec_t)(kb + (off + 16 * rr + s * 64)));
       }
@@ -378,7 +380,7 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
         const int f = i * 64 + ln;
         const int row = f / PPR;
         const int piece = (f % PPR) ^ (2 * (row & 3));
-        const unsigned long long off = row_offset(__shfl(ss.doc, row, 64), row);
+        const unsigned long long off = row_offset(ss, row);
         copy16_to_lds_async_stream64(reinterpret_cast<const char*>(a.V) + (off + piece * 16), dst + i * 1024);
       }
     } else {
@@ -408,7 +410,7 @@ void attend_partial_kernel(AttendArgs a, RopeTheta th) {
   // the path.  Two turns per trip of the loop, so that the two sets of key registers have fixed names.
   StepSrc s0, s1, s2;
   s0.slot = s0.pin = 0;
-  s0.doc = 0;
+  s0.row = 0;
   place(wb, s0);
   int st0 = first_valid(wb, s0);
   int st1 = we, st2 = we;

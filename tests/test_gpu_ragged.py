@@ -201,6 +201,35 @@ def test_ragged_pooled_bank(name):
     attend_err(out2, lse2, oo, ol)
 
 
+@pytest.mark.parametrize("C", [1, 2, 8, 16, 32])
+def test_ragged_pooled_bank_rows_past_the_end(C):
+    """What rows past a document's end hold does not matter, not a number included, with pads in the selection and documents
+    that end inside a step; the first document is the shortest."""
+    say(f"ragged pooled bank, rows past the end are not a number: C={C}")
+    N, Hkv, r, d, k = 21, 2, 4, 128, 7
+    lens = 1 + np.arange(N) % C
+    dlens = torch.from_numpy(lens.astype(np.int32)).cuda()
+    acfg = msa.MsaConfig(N, C, C, Hkv * r, Hkv, d, 1e6, bank_keys_rotated=1, doc_lens=dlens)
+    rng = np.random.default_rng(77000 + C)
+    sel = np.stack([rng.permutation(N)[:k] for _ in range(2 * Hkv)]).reshape(2, 1, Hkv, k)
+    sel[0, 0, 0, 3] = -1
+    sel[1, 0, 1, :] = -1
+    sel[1, 0, 1, 2] = 0
+    dq, dK, dV = (dev(S.normal_bf16(77001 + i, s)[0]) for i, s in
+                  enumerate([(2, 1, Hkv * r, d), (N, Hkv, C, d), (N, Hkv, C, d)]))
+    dKl, dVl = (dev(S.normal_bf16(77005 + i, (2, Hkv, 9, d))[0]) for i in range(2))
+    dpos = torch.full((2, 1), k + 8, dtype=torch.int32, device="cuda")
+    past = (torch.arange(C, device="cuda")[None, :] >= dlens[:, None])[:, None, :, None]
+    res = []
+    for fill in (0.0, float("nan")):
+        out, lse = msa.msa_sparse_attend(acfg, dq, dK.masked_fill(past, fill), dV.masked_fill(past, fill),
+                                         torch.from_numpy(sel.astype(np.int32)).cuda(), dKl, dVl, k, dpos)
+        torch.cuda.synchronize()
+        res.append((out.view(torch.int16), lse))
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+    assert bool(torch.isfinite(res[1][1]).all())
+
+
 def test_ragged_full_lengths_are_the_uniform_bank():
     """doc_lens = G everywhere gives bit-identical results to no doc_lens at all, stage by stage; values
     outside [1, G] are clamped."""
