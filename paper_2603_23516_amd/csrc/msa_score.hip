@@ -216,7 +216,8 @@ __device__ __forceinline__ void fold_query_tile(const FoldRegs<D>& fr, long long
 //       of reading operands that prep_scan_operands_kernel prepared: one launch less, which is what short streams
 //       are made of.  Scans with the threshold exchange keep the prepared operands: that launch also resets the
 //       exchange buffer, and their waves never synchronise.
-template <int D, int NQT, bool COS, int MODE, bool FOLD>
+// STREAM: streaming loads of the index (load_stream16; see stream_index_of).
+template <int D, int NQT, bool COS, int MODE, bool FOLD, bool STREAM>
 __global__ __launch_bounds__(64 * kScanWaves) __attribute__((amdgpu_waves_per_eu(2)))
 void score_scan_kernel(ScoreArgs a) {
   constexpr bool DENSE = MODE != 0;
@@ -284,10 +285,8 @@ void score_scan_kernel(ScoreArgs a) {
   };
   const uint16_t* KRg = a.KR + (long long)g * a.tiles * TILE_ELEMS + lane * 8;
   const float* ing = COS ? a.inv_norm + (long long)g * a.tiles * 16 + n : nullptr;
-  // Long streams (MODE 0) read an index far larger than the caches exactly once: streaming loads.  The short
-  // streams of MODE 1 and 2 (an index of at most a few hundred MB) measured faster with plain loads.
   auto load_tile16 = [](const uint16_t* p) {
-    return MODE == 0 ? load_stream16(p) : *reinterpret_cast<const uint4*>(p);
+    return STREAM ? load_stream16(p) : *reinterpret_cast<const uint4*>(p);
   };
   uint4 buf[kPrefetch][NS];
   float binv[kPrefetch];
@@ -713,8 +712,7 @@ struct ScanAllArgs {
   int ushift;             // log2(tiles per unit)
 };
 
-// STREAM: the index is far larger than the caches and read once per pass -> streaming loads (load_stream16); a small
-// index that several passes re-read is served partly from the caches and measured faster with plain loads.
+// STREAM: streaming loads of the index (see stream_index_of).
 // FOLD: the workgroup folds the queries of every head itself, a wave per (head, tile of 8 queries): one launch less.
 template <int D, int HKV, int NQT, bool STREAM, bool FOLD>
 __global__ __launch_bounds__(64 * kAllWaves) void score_scan_all_kernel(ScanAllArgs a) {
@@ -1154,6 +1152,20 @@ __global__ __launch_bounds__(64 * WAVES) void topk_rows_kernel(RowsArgs a) {
     for (int j = 0; j < k; ++j) rank += (surv[j] > x) ? 1 : 0;
     emit(rank, x);
   }
+}
+
+// Streaming loads of the index in the score-matrix scans: in one pass from 128 MB on, always beyond the 256 MB of cache behind
+// the L2s.  A program reads more than that cache holds between two scans of an index (the selected documents of eight streams,
+// the indexes of its other layers, its weights), so the scan finds it cold, and plain loads spend their time on caching what
+// nobody reads again (index cold, whole call, 8 queries: 8192 documents, 134 MB, 33.5 -> 31.2 us, 13000 51.0 -> 47.3, 18000
+// 67.1 -> 60.5, 32768 110 -> 99; 24 queries over all heads 37.7 -> 34.1, 30000 documents 107 -> 97; 5000, 82 MB, 24.6 -> 23.8 in
+// one kernel, 24.6 in the other).  Routing over one index again and again with nothing read in between is what the plain loads
+// are better at while it fits that cache: 8192 documents 28.6 -> 29.3, 13000 43.8 -> 46.0, 5000 21.2 -> 22.5, and a second pass
+// (13000 documents, 48 queries, keeps them); from 16384 documents on it gains too (53.6 -> 53.5, 20000 68.1 -> 64.9, 32768 106 ->
+// 95.5).
+static bool stream_index_of(const Dims& dm, int n_pass) {
+  const size_t bytes = (size_t)dm.Hkv * dm.tiles * 16 * dm.d * 2;
+  return bytes > ((size_t)256 << 20) || (n_pass == 1 && bytes >= 128000000);
 }
 
 // Waves per workgroup: sixteen where the rows leave the chip idle anyway (one round of 256 workgroups or fewer) and a row
@@ -1635,8 +1647,7 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
                          dm.r, dm.cos, pl.n_qtiles, a.gmax, n_gmax);
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
   }
-  // an index of more than 512 MB outgrows the 256 MB of cache behind the L2s even across passes
-  const bool stream_index = (size_t)dm.Hkv * dm.tiles * 16 * dm.d * 2 > ((size_t)512 << 20);
+  const bool stream_index = stream_index_of(dm, pl.n_pass);
   RowsArgs ra;
   ra.mat = (const float*)((char*)ws + pl.off_mat);
   ra.BM = BM;
@@ -1723,10 +1734,11 @@ do { \
     const int nqt = pl.q_per_pass / 8;  // 1, 2 or 4
 #define MSA_SCAN(DD, QQ, CC) \
   do { \
-    if (pl.mode == 2) hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 2, true>), grid, block, 0, st, a); \
-    else if (pl.mode == 1) hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 1, true>), grid, block, 0, st, a); \
-    else if (fold_in_scan) hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 0, true>), grid, block, 0, st, a); \
-    else hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 0, false>), grid, block, 0, st, a); \
+    if (pl.mode == 2 && stream_index) hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 2, true, true>), grid, block, 0, st, a); \
+    else if (pl.mode == 2) hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 2, true, false>), grid, block, 0, st, a); \
+    else if (pl.mode == 1) hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 1, true, false>), grid, block, 0, st, a); \
+    else if (fold_in_scan) hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 0, true, true>), grid, block, 0, st, a); \
+    else hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 0, false, true>), grid, block, 0, st, a); \
   } while (0)
     if (dm.d == 128) {
       if (dm.cos) {

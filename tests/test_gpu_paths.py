@@ -160,6 +160,17 @@ def test_scoring_gemm_of_two_passes(N, Hkv, r, C, d, B, M, k, sim):
     test_prefill_scoring_k_above_16(N, Hkv, r, C, d, B, M, k, sim)
 
 
+# score-matrix scans at the edge between plain and streaming loads of the index (128 MB; two passes: 256 MB), tails of half a tile
+STREAMED = [(7812, 8, 1, 8, 128, 1, 1, 9, "cos"), (7813, 8, 1, 8, 128, 9, 1, 9, "cos"), (7815, 8, 1, 8, 128, 2, 1, 16, "dot"),
+            (7813, 8, 2, 8, 128, 20, 1, 16, "cos"), (31253, 4, 1, 8, 64, 3, 1, 8, "cos")]
+
+
+@pytest.mark.parametrize("scope", ["group", "all"])
+@pytest.mark.parametrize("N,Hkv,r,C,d,B,M,k,sim", STREAMED)
+def test_scans_with_streaming_loads(N, Hkv, r, C, d, B, M, k, sim, scope):
+    (test_all_heads_scan if scope == "all" else test_prefill_scoring_k_above_16)(N, Hkv, r, C, d, B, M, k, sim)
+
+
 @pytest.mark.parametrize("M", [250, 700, 2000])
 def test_token_pooling_of_many_documents(M):
     """One query head: the tokens' scores are alike and most of their listed documents reach the floor: 1300 and about
