@@ -81,6 +81,9 @@ WidePoolPlan plan_score_wide_pool(const Dims& dm, const WidePlan& pl, int B, int
 int launch_score_wide_pool(const Dims& dm, const WidePoolPlan& pp, const void* q_route, int B, int M, const void* KR,
                            const float* inv_norm, int k, void* ws, hipStream_t st, int32_t* out_idx, float* out_score);
 
+// Streaming loads of the routing index where n_pass passes of a call read it.
+bool stream_index_of(const Dims& dm, int n_pass);
+
 bool wide_path_applies(const Dims& dm, int BM);
 WidePlan plan_score_wide(const Dims& dm, int BM, int k);
 int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, int BM, const void* KR,

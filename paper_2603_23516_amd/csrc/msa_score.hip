@@ -1163,7 +1163,7 @@ __global__ __launch_bounds__(64 * WAVES) void topk_rows_kernel(RowsArgs a) {
 // are better at while it fits that cache: 8192 documents 28.6 -> 29.3, 13000 43.8 -> 46.0, 5000 21.2 -> 22.5, and a second pass
 // (13000 documents, 48 queries, keeps them); from 16384 documents on it gains too (53.6 -> 53.5, 20000 68.1 -> 64.9, 32768 106 ->
 // 95.5).
-static bool stream_index_of(const Dims& dm, int n_pass) {
+bool stream_index_of(const Dims& dm, int n_pass) {
   const size_t bytes = (size_t)dm.Hkv * dm.tiles * 16 * dm.d * 2;
   return bytes > ((size_t)256 << 20) || (n_pass == 1 && bytes >= 128000000);
 }

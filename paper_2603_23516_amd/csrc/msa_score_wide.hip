@@ -291,8 +291,11 @@ __device__ __forceinline__ void wide_store_pooled(const WideArgs& a, const float
   if (rr == 0 && (n & 7) < KT && doc < a.seg_docs) a.mat[tb * a.mat_stride + doc] = fmaxf(mine * inv_heads, -INFINITY);  // (not a number: last)
 }
 
-// POOL: token pooling, the matrix holds the best score of a block's tokens.
-template <int NT, bool POOL>
+// POOL: token pooling, the matrix holds the best score of a block's tokens.  STREAM: streaming loads of the keys, where the scans
+// have them too (stream_index_of; index cold, whole call: 150 tokens, pooled, 97656 documents 330 -> 317 us, 120 over 20000 94.7
+// -> 90.8, 400, three blocks, over 30000 266 -> 260; 160 not pooled over 97656 422 -> 415, 90 over 16000 80.7 -> 78.2; the same
+// calls again and again up to 3 % slower up to 256 MB, not beyond).
+template <int NT, bool POOL, bool STREAM>
 __global__ __launch_bounds__(64 * kRowsWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void score_wide_rows_kernel(WideArgs a) {
   constexpr int D = 128;
@@ -350,8 +353,10 @@ void score_wide_rows_kernel(WideArgs a) {
       const long long at = g * a.tiles + t;
       const gptr_t p = kr0 + at * (TILE_ELEMS * 2);
 #pragma unroll
-      for (int s = 0; s < NS; ++s)
-        b[kt][s] = *(const __attribute__((address_space(1))) u32x4_t*)(p + s * 1024 + (size_t)(ln * 16));
+      for (int s = 0; s < NS; ++s) {
+        const auto from = (const __attribute__((address_space(1))) u32x4_t*)(p + s * 1024 + (size_t)(ln * 16));
+        b[kt][s] = STREAM ? __builtin_nontemporal_load(from) : *from;
+      }
       bi[kt] = *(const __attribute__((address_space(1))) float*)(in0 + at * 64 + (size_t)((ln & 15) * 4));
     }
   };
@@ -1005,6 +1010,12 @@ __global__ __launch_bounds__(512) void pool_best_kernel(WidePoolArgs a) {
   }
 }
 
+#define MSA_WIDE_ROWS(NN, PP) \
+  do { \
+    if (stream_index_of(dm, 1)) hipLaunchKernelGGL((score_wide_rows_kernel<NN, PP, true>), grid, block, 0, st, a); \
+    else hipLaunchKernelGGL((score_wide_rows_kernel<NN, PP, false>), grid, block, 0, st, a); \
+  } while (0)
+
 // ---- host side -----------------------------------------------------------------------------------------------------
 // More tokens than one pass of the all-heads scan takes.
 bool wide_path_applies(const Dims& dm, int BM) { return dm.scope_all && dm.Hkv > 1 && BM > 32; }
@@ -1101,10 +1112,10 @@ int launch_score_wide_pool(const Dims& dm, const WidePoolPlan& pp, const void* q
   if (a.n_streams > most) a.n_streams = most;
   const dim3 grid((unsigned)((a.n_tb * a.n_streams + 7) / 8 * 8)), block(64 * kRowsWaves);
   profile_mark(dm, false, st);
-  if (pp.nt <= 4) hipLaunchKernelGGL((score_wide_rows_kernel<4, true>), grid, block, 0, st, a);
-  else if (pp.nt == 6) hipLaunchKernelGGL((score_wide_rows_kernel<6, true>), grid, block, 0, st, a);
-  else if (pp.nt == 8) hipLaunchKernelGGL((score_wide_rows_kernel<8, true>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((score_wide_rows_kernel<10, true>), grid, block, 0, st, a);
+  if (pp.nt <= 4) MSA_WIDE_ROWS(4, true);
+  else if (pp.nt == 6) MSA_WIDE_ROWS(6, true);
+  else if (pp.nt == 8) MSA_WIDE_ROWS(8, true);
+  else MSA_WIDE_ROWS(10, true);
   profile_mark(dm, true, st);
   if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
   WidePoolArgs p;
@@ -1211,9 +1222,9 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
     else hipLaunchKernelGGL((score_wide_kernel<DD, HH, true, false>), grid, block, 0, st, a); \
   } while (0)
       if (rows) {
-        if (nt == 6) hipLaunchKernelGGL((score_wide_rows_kernel<6, false>), grid, block, 0, st, a);
-        else if (nt == 8) hipLaunchKernelGGL((score_wide_rows_kernel<8, false>), grid, block, 0, st, a);
-        else hipLaunchKernelGGL((score_wide_rows_kernel<10, false>), grid, block, 0, st, a);
+        if (nt == 6) MSA_WIDE_ROWS(6, false);
+        else if (nt == 8) MSA_WIDE_ROWS(8, false);
+        else MSA_WIDE_ROWS(10, false);
       } else if (dm.d == 128) {
         if (dm.Hkv == 2) MSA_WIDE(128, 2); else if (dm.Hkv == 4) MSA_WIDE(128, 4); else MSA_WIDE(128, 8);
       } else {

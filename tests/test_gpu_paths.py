@@ -229,6 +229,12 @@ def test_all_heads_wide_rows(N, Hkv, r, C, d, B, M, k, sim):
     test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim)
 
 
+# the same with streaming loads of the index, from 128 MB on
+@pytest.mark.parametrize("N,M", [(7813, 40), (7813, 70), (7815, 100), (7814, 131), (7812, 150)])
+def test_all_heads_wide_rows_with_streaming_loads(N, M):
+    test_all_heads_scan(N, 8, 1, 8, 128, 1, M, 9, "cos")
+
+
 # tokens pooled by document: one token more than the scan takes, several blocks of tokens, batch rows, parts of one document
 POOL_DOCS = [(700, 2, 2, 8, 128, 1, 33, 20, "cos"), (1030, 4, 1, 8, 128, 2, 100, 9, "cos"), (64, 4, 2, 8, 128, 1, 330, 64, "cos"),
              (515, 2, 1, 8, 128, 1, 1000, 5, "cos"), (2600, 8, 1, 8, 128, 4, 66, 33, "cos"), (40, 8, 1, 8, 128, 1, 40, 40, "cos"),
