@@ -117,7 +117,8 @@ __device__ __forceinline__ void wide_store(const WideArgs& a, const float (&tot)
   }
 }
 
-template <int D, int HKV, bool PAIR, bool COS>
+// STREAM: streaming loads of the keys (a single token block: nobody else reads them).
+template <int D, int HKV, bool PAIR, bool COS, bool STREAM>
 __global__ __launch_bounds__(64 * kWideWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void score_wide_kernel(WideArgs a) {
   constexpr int NS = D / 32;
@@ -173,8 +174,10 @@ void score_wide_kernel(WideArgs a) {
       const long long at = g * a.tiles + t;
       const gptr_t p = kr0 + at * (TILE_ELEMS * 2);
 #pragma unroll
-      for (int s = 0; s < NS; ++s)
-        b[kt][s] = *(const __attribute__((address_space(1))) u32x4_t*)(p + s * 1024 + (size_t)(ln * 16));
+      for (int s = 0; s < NS; ++s) {
+        const auto from = (const __attribute__((address_space(1))) u32x4_t*)(p + s * 1024 + (size_t)(ln * 16));
+        b[kt][s] = STREAM ? __builtin_nontemporal_load(from) : *from;
+      }
       if constexpr (COS) bi[kt] = *(const __attribute__((address_space(1))) float*)(in0 + at * 64 + (size_t)((ln & 15) * 4));
     }
   };
@@ -1213,13 +1216,18 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
       if (streams > most) streams = most;
       a.n_streams = streams;
       a.m_blocks = a.n_tb;
+      // Streaming loads where one token block reads the keys and the cache behind the L2s cannot hold them: 40 tokens, 97656
+      // documents 357 -> 321 us, 64 over 20000 106 -> 101 (102.4 -> 98.1 again and again).  A smaller index gains nothing when it
+      // is cold and loses when it is not (50 over 8000 56.8, 57.9; again and again 49.6, 56.2).
+      const bool stream = a.n_tb == 1 && stream_index_of(dm, 2);
       dim3 grid((unsigned)((a.n_tb * streams + 7) / 8 * 8)), block(64 * waves);
       if (tok0 == 0 && doc0 == 0) profile_mark(dm, false, st);
 #define MSA_WIDE(DD, HH) \
   do { \
-    if (!pl.pair) hipLaunchKernelGGL((score_wide_kernel<128, HH, false, true>), grid, block, 0, st, a); \
-    else if (dm.cos) hipLaunchKernelGGL((score_wide_kernel<DD, HH, true, true>), grid, block, 0, st, a); \
-    else hipLaunchKernelGGL((score_wide_kernel<DD, HH, true, false>), grid, block, 0, st, a); \
+    if (!pl.pair && stream) hipLaunchKernelGGL((score_wide_kernel<128, HH, false, true, true>), grid, block, 0, st, a); \
+    else if (!pl.pair) hipLaunchKernelGGL((score_wide_kernel<128, HH, false, true, false>), grid, block, 0, st, a); \
+    else if (dm.cos) hipLaunchKernelGGL((score_wide_kernel<DD, HH, true, true, false>), grid, block, 0, st, a); \
+    else hipLaunchKernelGGL((score_wide_kernel<DD, HH, true, false, false>), grid, block, 0, st, a); \
   } while (0)
       if (rows) {
         if (nt == 6) MSA_WIDE_ROWS(6, false);

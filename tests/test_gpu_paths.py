@@ -229,8 +229,8 @@ def test_all_heads_wide_rows(N, Hkv, r, C, d, B, M, k, sim):
     test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim)
 
 
-# the same with streaming loads of the index, from 128 MB on
-@pytest.mark.parametrize("N,M", [(7813, 40), (7813, 70), (7815, 100), (7814, 131), (7812, 150)])
+# the same with streaming loads of the index, from 128 MB on; up to 64 tokens beyond 256 MB
+@pytest.mark.parametrize("N,M", [(7813, 40), (7813, 70), (7815, 100), (7814, 131), (7812, 150), (16384, 33), (16387, 64)])
 def test_all_heads_wide_rows_with_streaming_loads(N, M):
     test_all_heads_scan(N, 8, 1, 8, 128, 1, M, 9, "cos")
 
