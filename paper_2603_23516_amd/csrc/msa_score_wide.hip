@@ -28,7 +28,7 @@
 // that read the same keys sit on one XCD and walk them together, so the index comes from memory once per XCD-resident
 // group of blocks. Measured: 150 tokens, k = 32, 97656 documents: kernel 3 x 142 us (three
 // segments; 192 padded rows, 0.72 PFLOP/s), selection 18 + 18 + 46 us; the call 4.87 ms as 19 passes of the scan -> 0.50
-// ms.  2048 tokens, 32768 documents, k = 8: 2.4 ms (a GEMM that reloaded its operands at every group switch) -> 1.47 ms.
+// ms, before score_wide_rows_kernel and the pooling by document took that shape (0.31).  2048 tokens, 32768 documents, k = 8: 2.4 ms (a GEMM that reloaded its operands at every group switch) -> 1.47 ms.
 #include "msa_device.h"
 #include "msa_host.h"
 
