@@ -118,6 +118,8 @@ struct ScorePlan {
   int merge_parts;       // > 1: two-level merge, first level over merge_lpp lists per block
   int merge_lpp;
   size_t off_part;       // byte offset of the first-level winners
+  int nan_docs;          // 1: a query without a score that is a number selects the first k documents (the GEMM in the place of
+                         // a scan of mode 2; its lists alone would have no entry)
   int use_wide;          // 1: all heads, more tokens than one pass of the scan -> msa_score_wide.hip
   WidePlan wide;
   int use_gemm;          // 1: many query tokens, a selection per KV group -> msa_score_gemm.hip

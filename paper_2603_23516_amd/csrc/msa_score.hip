@@ -1198,6 +1198,8 @@ constexpr int kMaxSurv = 2048;
 // out_parts > 1: first level of a two-level merge for very many lists.  Block (g, qg, part), part < parts, combines
 // lists [part * lpp, (part + 1) * lpp) and writes its k winners as a sorted list of keys to
 // out_key[g][qg][part0 + part][k], the input layout of a second call with n_lists = out_parts.
+// nan_docs: a query without a candidate takes the first k documents, as the selection from a matrix row does, with the score that
+// the products of the scan have then (it ranks below all others in token pooling).
 __global__ __launch_bounds__(256) void score_merge_kernel(const unsigned long long* __restrict__ ws,
                                                           int32_t* __restrict__ out_idx,
                                                           float* __restrict__ out_score,
@@ -1205,7 +1207,7 @@ __global__ __launch_bounds__(256) void score_merge_kernel(const unsigned long lo
                                                           int BM, int Hkv, int n_lists_total, int k,
                                                           int lpp, int parts, int part0, int out_parts,
                                                           const int* __restrict__ gate, int gate_tokens,
-                                                          int gate_blocks) {
+                                                          int gate_blocks, int nan_docs) {
   __shared__ unsigned long long sub[kMaxSub];
   __shared__ unsigned long long surv[kMaxSurv];
   __shared__ unsigned long long red[4];
@@ -1293,12 +1295,14 @@ __global__ __launch_bounds__(256) void score_merge_kernel(const unsigned long lo
         }
       }
     }
-    for (int i = S + tid; i < k; i += 256) {  // fewer than k valid candidates (cannot happen for k <= N)
+    for (int i = S + tid; i < k; i += 256) {  // fewer than k candidates: no score of the query is a number
+      const bool nan = nan_docs && S == 0;
+      const float sc = __uint_as_float(0xffc00000u);
       if (out_key) {
-        out_key[o_base + i] = 0ull;
+        out_key[o_base + i] = nan ? make_key(sc, (uint32_t)i) : 0ull;
       } else {
-        out_idx[o_base + i] = -1;
-        if (out_score) out_score[o_base + i] = -INFINITY;
+        out_idx[o_base + i] = nan ? i : -1;
+        if (out_score) out_score[o_base + i] = nan ? sc : -INFINITY;
       }
     }
     return;
@@ -1461,6 +1465,7 @@ static void plan_all_heads(const Dims& dm, int BM, int k, ScorePlan* p) {
 
 static ScorePlan plan_score_least(const Dims& dm, int BM, int k, bool two_passes = false) {
   ScorePlan p;
+  p.nan_docs = 0;
   // one selection per KV group, or (literal Eq. 2 head mean, more than one group) one for all heads
   p.all_heads = (dm.scope_all && dm.Hkv > 1) ? 1 : 0;
   p.n_sel = dm.scope_all ? 1 : dm.Hkv;
@@ -1553,6 +1558,7 @@ ScorePlan plan_score(const Dims& dm, int BM, int k, size_t workspace_bytes) {
     ScorePlan g = plan_score_least(dm, BM, k, true);
     if (g.ws_bytes <= p.ws_bytes) {  // (in the workspace that the scan asks for)
       g.ws_bytes = g.ws_best = p.ws_bytes;
+      g.nan_docs = p.mode == 2 ? 1 : 0;
       return g;
     }
   }
@@ -1588,13 +1594,13 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
       unsigned long long* part_keys = (unsigned long long*)((char*)ws + pl.off_part);
       hipLaunchKernelGGL(score_merge_kernel, dim3(BM * pl.n_sel * pl.merge_parts), dim3(256), 0, st, lists,
                          (int32_t*)nullptr, (float*)nullptr, part_keys, BM, pl.n_sel, n_lists, k,
-                         pl.merge_lpp, pl.merge_parts, 0, pl.merge_parts, gate, gate_tokens, gate_blocks);
+                         pl.merge_lpp, pl.merge_parts, 0, pl.merge_parts, gate, gate_tokens, gate_blocks, pl.nan_docs);
       if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
       lists = part_keys;
       n_lists = pl.merge_parts;
     }
     hipLaunchKernelGGL(score_merge_kernel, dim3(BM * pl.n_sel), dim3(256), 0, st, lists, out_idx, out_score,
-                       tok_keys, BM, pl.n_sel, n_lists, k, n_lists, 1, 0, 1, gate, gate_tokens, gate_blocks);
+                       tok_keys, BM, pl.n_sel, n_lists, k, n_lists, 1, 0, 1, gate, gate_tokens, gate_blocks, pl.nan_docs);
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
     return pool_tokens();
   };
@@ -1719,7 +1725,7 @@ do { \
       if (pl.n_windows > 1 && ra.part0 + ra.parts == ra.parts_total) {
         hipLaunchKernelGGL(score_merge_kernel, dim3(BM), dim3(256), 0, st, (const unsigned long long*)ws,
                            (int32_t*)nullptr, (float*)nullptr, window_keys, BM, 1, ra.parts_total, k, ra.parts_total, 1,
-                           window, pl.n_windows, (const int*)nullptr, 1, 0);
+                           window, pl.n_windows, (const int*)nullptr, 1, 0, 0);
         if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
       }
     }

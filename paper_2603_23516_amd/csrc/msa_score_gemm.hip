@@ -668,21 +668,23 @@ bool gemm_path_applies(const Dims& dm, int BM, int k) {
   return passes - (one_pass ? 2 : 4) >= ((one_pass ? 500000 : 1250000) + work - 1) / work;
 }
 
-// 33 to 63 tokens, two or more passes of the scan: the GEMM reads the index once, its token block of 128 half empty.  Worth it
-// from about 8000 documents of eight chunks and heads on, with k > 16, where its splits are half as many, from 20000 (48 tokens,
-// k = 8: 6000 documents 55 us by the scan, 54 here, 16000 131.5, 87, 40000 367, 158, 97000 709, 327; 33 of k = 16: 16000 130, 98,
-// 97000 664, 404; 48 of k = 24: 16000 133, 139, 40000 383, 240).  Four heads fill the chip half, so from twice the documents on
-// (33 of k = 8: 16000 66.6, 70.7, 40000 158, 116; k = 30 217, 235), two never (40000: 81, 114).  One pass, up to 32 tokens, is the
-// scan's (24 tokens, k = 16, 97000 documents 360, 397).
+// 33 to 63 tokens, two or more passes of the scan: the GEMM reads the index once, its token block of 128 half empty.  In its
+// two-pass form, hi and lo parts as in the scan: the one-pass filter's error band is that of unit keys, which such calls do not
+// ask of an index (its tokens with norms of 50 to 150 times the keys' lost winners).  Worth it from about 8000 documents of eight
+// chunks and heads on, with k > 16, whose lists are what takes the time, from 40000 (48 tokens, k = 8: 6000 documents 61.5 us by
+// the scan, 56.5 here, 8000 74.1, 65.6, 16000 136, 103, 40000 370, 209, 97000 745, 434; 33 of k = 16: 16000 132, 102, 97000 664,
+// 402; 48 of k = 24: 24000 203, 271, 40000 385, 355, 97000 670, 615; 33 of k = 24 over 40000 345, 346).  Four heads fill the chip
+// half, so with k <= 16 from 40000 documents on (33 of k = 8: 24000 101, 107, 40000 164, 154; k = 32 218, 287), two never
+// (40000: 81, 114).  One pass, up to 32 tokens, is the scan's (24 tokens, k = 16, 97000 documents 360, 397).
 bool gemm_path_of_two_passes(const Dims& dm, int BM, int k) {
   if (!one_pass_shape(dm) || BM <= 32 || BM >= 64 || k > kGemmMaxK) return false;
-  if (dm.Hkv == 8) return dm.NC >= (k <= 16 ? 64000 : 160000);
+  if (dm.Hkv == 8) return dm.NC >= (k <= 16 ? 64000 : 320000);
   return dm.Hkv == 4 && k <= 16 && dm.NC >= 320000;
 }
 
 static GemmPlan gemm_split(const Dims& dm, int BM, int k, bool small) {
   GemmPlan p;
-  const int tokens_per_wg = (k <= 8) ? 256 : 128;
+  const int tokens_per_wg = (k <= 8 && BM >= 64) ? 256 : 128;
   p.n_qblocks = (BM + tokens_per_wg - 1) / tokens_per_wg;
   // Two blocks per wave (every key read from LDS then serves 64 tokens) with 8-entry lists alone: with 16 entries the
   // one-pass form holds them too, but the workgroups of twice the tokens are half as many and their lists twice as long
@@ -691,7 +693,7 @@ static GemmPlan gemm_split(const Dims& dm, int BM, int k, bool small) {
   // documents, k = 8: 480 -> 352 us).
   p.tb1 = (BM > 128 && k <= 8) ? 2 : 1;
   p.n_qblocks1 = (BM + 128 * p.tb1 - 1) / (128 * p.tb1);
-  const bool one_pass = one_pass_shape(dm);
+  const bool one_pass = one_pass_shape(dm) && BM >= 64;  // (fewer tokens: see gemm_path_of_two_passes)
   const long long n_stage = ((dm.tiles + 1) / 2 + 1) / 2;           // stages of 64 keys
   long long want = (2 * 256) / ((long long)dm.Hkv * (one_pass ? p.n_qblocks1 : p.n_qblocks));  // ~2 workgroups per CU
   if (want < 1) want = 1;
@@ -813,7 +815,7 @@ int launch_score_gemm_scan(const Dims& dm, const GemmPlan& pl, const void* q_rou
     if (dm.C == 8) hipLaunchKernelGGL((score_gemm_kernel<DD, TT, KK, true, false>), dim3(blocks), dim3(256), 0, st, a); \
     else hipLaunchKernelGGL((score_gemm_kernel<DD, TT, KK, false, false>), dim3(blocks), dim3(256), 0, st, a); \
   } while (0)
-  if (k <= 8) {
+  if (pl.tokens_per_wg == 256) {
     if (dm.d == 128) MSA_GEMM(128, 2, 8); else MSA_GEMM(64, 2, 8);
   } else if (k <= 16) {
     if (dm.d == 128) MSA_GEMM(128, 1, 16); else MSA_GEMM(64, 1, 16);

@@ -150,7 +150,7 @@ def test_prefill_scoring_k_above_16(N, Hkv, r, C, d, B, M, k, sim):
         check_topk_generic(q, KRb, C, N, idx, val, k, sim, "group", pool, atol=2e-5 if sim == "cos" else 2e-4)
 
 
-# 33 to 63 tokens over a bank that the scan would read twice: the GEMM from 64000 keys a head on (k > 16: 160000)
+# 33 to 63 tokens over a bank that the scan would read twice: the GEMM from 64000 keys a head on (k > 16 or four heads: 320000)
 GEMM_TWO_PASSES = [(8000, 8, 1, 8, 128, 33, 1, 8, "cos"), (8001, 8, 2, 8, 128, 3, 21, 16, "cos"), (7999, 8, 1, 8, 128, 40, 1, 8, "cos"),
                    (20003, 8, 1, 8, 128, 35, 1, 24, "cos"), (8200, 8, 1, 8, 128, 32, 1, 8, "cos"), (40001, 4, 1, 8, 128, 63, 1, 5, "cos")]
 
@@ -346,6 +346,61 @@ def test_all_heads_wide_takes_any_norms(C, d):
     # scores of up to ~60 with queries carried to 16 bits and fp32 sums: 2e-5 of the largest at most
     assert np.abs(np.take_along_axis(s, got.astype(np.int64), -1) - want).max() <= 2e-5 * want.max()
     assert np.abs(val.cpu().numpy()[0, :, 0] - want).max() <= 2e-5 * want.max()
+
+
+def device_index(seed, Hkv, NC, d):
+    """Random keys bf16 [Hkv][NC][d] on the device, and the same in the index's tiles."""
+    tiles = (NC + 15) // 16
+    keys = torch.randn((Hkv, tiles * 16, d), generator=torch.Generator("cuda").manual_seed(seed), device="cuda").to(torch.bfloat16)
+    return keys[:, :NC], keys.reshape(Hkv, tiles, 16, d // 8, 8).transpose(2, 3).contiguous()
+
+
+# 33 to 63 tokens above the lines of the GEMM that stands in for two passes of the scan, and below (24 of 20000)
+@pytest.mark.parametrize("N,Hkv,k", [(16000, 8, 8), (16001, 8, 12), (20000, 8, 24), (40003, 8, 24), (40001, 4, 8)])
+def test_scoring_of_two_passes_takes_any_norms(N, Hkv, k):
+    """As test_all_heads_wide_takes_any_norms, a selection per KV group."""
+    C, d, B = 8, 128, 40
+    say(f"scoring of two passes with norms of its own N={N} Hkv={Hkv} k={k}")
+    cfg = msa.MsaConfig(N, 8 * C, 8, Hkv, Hkv, d, 1e6)
+    keys, KR = device_index(60000 + N, Hkv, N * C, d)
+    inv = torch.zeros((Hkv, cfg.n_tiles * 16), device="cuda")
+    inv[:, :N * C] = 1.0 / keys.float().norm(dim=-1)
+    inv *= 50 + 100 * torch.rand(inv.shape, generator=torch.Generator("cuda").manual_seed(k), device="cuda")
+    q = dev(S.normal_bf16(60001, (B, 1, Hkv, d))[0])
+    idx, val = msa.msa_score_topk(cfg, q, KR, inv, k)
+    torch.cuda.synchronize()
+    x = q[:, 0].double()
+    x = x / x.norm(dim=-1, keepdim=True)
+    for g in range(Hkv):
+        s = ((x[:, g] @ keys[g].double().T.contiguous()) * inv[g, :N * C].double()).reshape(B, N, C).amax(-1)
+        want = s.topk(k, dim=1).values
+        # (the bound of test_all_heads_wide_takes_any_norms)
+        assert (s.gather(1, idx[:, 0, g].long()) - want).abs().max() <= 2e-5 * want.max()
+        assert (val[:, 0, g].double() - want).abs().max() <= 2e-5 * want.max()
+
+
+@pytest.mark.parametrize("pool", [0, 1])
+@pytest.mark.parametrize("k", [8, 16])
+def test_scoring_of_two_passes_of_not_a_number(k, pool):
+    """Queries that are not numbers select what they select in a call of one pass; the others are as they are alone."""
+    N, Hkv, C, d, B = 8100, 8, 8, 128, 20
+    say(f"scoring of two passes, queries that are not numbers k={k} pool={pool}")
+    cfg = msa.MsaConfig(N, 8 * C, 8, Hkv, Hkv, d, 1e6, token_pool=pool)
+    keys, KR = device_index(60700, Hkv, N * C, d)
+    inv = torch.zeros((Hkv, cfg.n_tiles * 16), device="cuda")
+    inv[:, :N * C] = 1.0 / keys.float().norm(dim=-1)
+    q = dev(S.normal_bf16(60701, (B, 2, Hkv, d))[0])
+    q[3], q[5, 1, 2], q[16, 0], q[19, 1, :, 7] = (float(x) for x in ("nan", "nan", "-nan", "inf"))
+    idx, val = msa.msa_score_topk(cfg, q, KR, inv, k)
+    parts = [msa.msa_score_topk(cfg, q[b:b + 10].contiguous(), KR, inv, k) for b in (0, 10)]
+    torch.cuda.synchronize()
+    one_i, one_v = (torch.cat([p[i] for p in parts]) for i in range(2))
+    nan = torch.isnan(one_v)
+    assert bool(nan[3].all()) and torch.equal(torch.isnan(val), nan) and torch.equal(idx[nan], one_i[nan])
+    assert torch.equal(torch.signbit(val[nan]), torch.signbit(one_v[nan]))
+    # both carry the queries as hi and lo parts: scores to fp32 rounding, other documents only where they tie to that
+    assert (val[~nan] - one_v[~nan]).abs().max() <= 2e-6
+    assert (idx != one_i).float().mean() <= 0.01
 
 
 @pytest.mark.parametrize("copies,d", [(300, 64), (4000, 64), (300, 128), (4000, 128)])
