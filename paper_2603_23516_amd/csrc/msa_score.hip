@@ -1188,11 +1188,14 @@ static void launch_topk_rows(const RowsArgs& ra, hipStream_t st) {
 
 // Combine the n_lists sorted lists (k entries each, zero-padded) of one (query, group).
 //   1. A lower bound theta on the k-th best score: the first j+1 entries of every list, with
-//      n_lists*(j+1) >= k, are that many distinct candidates; kth_best_bound of their scores.
-//   2. Survivors (score >= theta) are compacted into LDS and ranked by counting.
-//   3. If more than kMaxSurv survive (adversarial order), fall back to k rounds of block-wide argmax.
+//      n_lists*(j+1) >= k, are that many distinct candidates; kth_best_bound of their scores.  Where several of them tie with
+//      it, or differ in the bits only that it leaves out, or more than kFewSurv entries reach it, their k-th best key instead.
+//   2. Survivors (key >= theta) are compacted into LDS and ranked by counting.
+//   3. If more than kMaxSurv survive (k > 32: the best of every list in a few lists), fall back to k rounds of block-wide argmax.
 constexpr int kMaxSub = 1152;
 constexpr int kMaxSurv = 2048;
+constexpr int kFewSurv = 256;  // one entry per thread to rank
+constexpr int kFewTies = 8;
 
 // out_key != null: the winners are written as 64-bit keys instead (input of pool_tokens_kernel).
 // out_parts > 1: first level of a two-level merge for very many lists.  Block (g, qg, part), part < parts, combines
@@ -1208,9 +1211,10 @@ __global__ __launch_bounds__(256) void score_merge_kernel(const unsigned long lo
                                                           int lpp, int parts, int part0, int out_parts,
                                                           const int* __restrict__ gate, int gate_tokens,
                                                           int gate_blocks, int nan_docs) {
-  __shared__ unsigned long long sub[kMaxSub];
+  __shared__ unsigned long long sub[kMaxSub + 8];
   __shared__ unsigned long long surv[kMaxSurv];
   __shared__ unsigned long long red[4];
+  __shared__ unsigned long long theta_s;
   __shared__ uint32_t theta_w[2][4];
   __shared__ int n_surv;
   const int tid = threadIdx.x;
@@ -1230,57 +1234,92 @@ __global__ __launch_bounds__(256) void score_merge_kernel(const unsigned long lo
   // k <= P < k + n_lists; any kMaxSub >= k heads of lists bound the k-th best key just as well
   const int P = (n_lists * depth <= kMaxSub) ? n_lists * depth : kMaxSub;
   for (int i = tid; i < P; i += 256) sub[i] = src[(i / depth) * k + (i % depth)];
+  if (tid < 8) sub[P + tid] = 0ull;  // read eight at a time below (zero: greater than no key)
   if (tid == 0) n_surv = 0;
   __syncthreads();
-  // (Ranking the heads one against the other for their exact k-th took 2 us of this kernel's 7.5 with 256 lists: 8 queries,
-  // 97656 documents, k = 32, whole call 264.8 -> 262.0; 2 of 60000 195.4 -> 192.7.)
+  // (Ranking the heads one against the other for their exact k-th took 2 us of this kernel's 7.5 with 256 lists.)
   uint32_t ob = 0u;
   for (int i = tid; i < P; i += 256) {
     const uint32_t o = (uint32_t)(sub[i] >> 32);
     ob = o > ob ? o : ob;
   }
-  const unsigned long long theta = (unsigned long long)kth_best_bound<4>(ob, k, theta_w) << 32;
-  if (n_lists * depth <= kMaxSub) {
-    // The heads of all lists are in LDS already, and the lists are sorted: a list holds further survivors only if
-    // the last entry seen of it is still >= theta, and then only as far as its entries stay >= theta.  After the
-    // streams' thresholds have converged that is a handful of entries per (query, head) instead of n_lists * k.
-    for (int l = tid; l < n_lists; l += 256) {
-      bool more = true;
-      for (int j = 0; j < depth; ++j) {
-        const unsigned long long x = sub[l * depth + j];
-        more = x != 0ull && x >= theta;
-        if (!more) break;
-        const int slot = atomicAdd(&n_surv, 1);
-        if (slot < kMaxSurv) surv[slot] = x;
+  const uint32_t bound = kth_best_bound<4>(ob, k, theta_w);
+  unsigned long long theta = (unsigned long long)bound << 32;
+  // A query of zeros (an empty slot of a batch) ties with every document, copies of the best documents with each other: all
+  // entries of all lists may reach a bound of score bits, and every list would be walked to its end (8 queries, 2 of them zeros,
+  // 97656 documents, k = 32, whole call 428 us, with their exact k-th key 291; 3000 copies of the best document 405, 270).
+  int ties = 0;  // heads in the interval of scores that starts with the bound (the same in every wave)
+  for (int i0 = 0; i0 < P; i0 += 64) {
+    const uint32_t o = i0 + (tid & 63) < P ? (uint32_t)(sub[i0 + (tid & 63)] >> 32) : 0u;
+    ties += __popcll(__ballot(o != 0u && (o & ~0xfffu) == bound));
+  }
+  bool exact = ties > kFewTies;
+  int S;
+  for (;;) {  // once or twice
+    if (exact) {
+      if (tid == 0) theta_s = 0ull;
+      __syncthreads();
+      for (int i = tid; i < P; i += 256) {
+        const unsigned long long x = sub[i];
+        int rank = 0;
+        for (int j = 0; j < P; j += 8) {
+          unsigned long long y[8];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) y[u] = sub[j + u];
+#pragma unroll
+          for (int u = 0; u < 8; ++u) rank += (y[u] > x) ? 1 : 0;
+        }
+        if (rank == k - 1 && x != 0ull) theta_s = x;  // keys are distinct, zeros are padding
       }
-      for (int j = depth; more && j < k; ++j) {
-        const unsigned long long x = src[l * k + j];
-        more = x != 0ull && x >= theta;
-        if (more) {
+      __syncthreads();
+      theta = theta_s;
+    }
+    if (n_lists * depth <= kMaxSub) {
+      // The heads of all lists are in LDS already, and the lists are sorted: a list holds further survivors only if
+      // the last entry seen of it is still >= theta, and then only as far as its entries stay >= theta.  After the
+      // streams' thresholds have converged that is a handful of entries per (query, head) instead of n_lists * k.
+      for (int l = tid; l < n_lists; l += 256) {
+        bool more = true;
+        for (int j = 0; j < depth; ++j) {
+          const unsigned long long x = sub[l * depth + j];
+          more = x != 0ull && x >= theta;
+          if (!more) break;
           const int slot = atomicAdd(&n_surv, 1);
           if (slot < kMaxSurv) surv[slot] = x;
         }
+        for (int j = depth; more && j < k; ++j) {
+          const unsigned long long x = src[l * k + j];
+          more = x != 0ull && x >= theta;
+          if (more) {
+            const int slot = atomicAdd(&n_surv, 1);
+            if (slot < kMaxSurv) surv[slot] = x;
+          }
+        }
       }
-    }
-  } else {
-    for (int i0 = 0; i0 < T; i0 += 256 * 8) {  // eight independent loads per thread in flight
-      unsigned long long x[8];
+    } else {
+      for (int i0 = 0; i0 < T; i0 += 256 * 8) {  // eight independent loads per thread in flight
+        unsigned long long x[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int i = i0 + u * 256 + tid;
-        x[u] = (i < T) ? src[i] : 0ull;
-      }
+        for (int u = 0; u < 8; ++u) {
+          const int i = i0 + u * 256 + tid;
+          x[u] = (i < T) ? src[i] : 0ull;
+        }
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        if (x[u] != 0ull && x[u] >= theta) {
-          const int slot = atomicAdd(&n_surv, 1);
-          if (slot < kMaxSurv) surv[slot] = x[u];
+        for (int u = 0; u < 8; ++u) {
+          if (x[u] != 0ull && x[u] >= theta) {
+            const int slot = atomicAdd(&n_surv, 1);
+            if (slot < kMaxSurv) surv[slot] = x[u];
+          }
         }
       }
     }
+    __syncthreads();
+    S = n_surv;
+    if (exact || S <= kFewSurv) break;  // block-uniform
+    exact = true;
+    __syncthreads();
+    if (tid == 0) n_surv = 0;
   }
-  __syncthreads();
-  const int S = n_surv;
   if (S <= kMaxSurv) {
     for (int i = tid; i < S; i += 256) {
       const unsigned long long x = surv[i];
