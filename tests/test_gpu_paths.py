@@ -25,6 +25,21 @@ def device_index(seed, Hkv, NC, d):
     return keys[:, :NC], keys.reshape(Hkv, tiles, 16, d // 8, 8).transpose(2, 3).contiguous()
 
 
+def call_us(cfg, q, KR, inv, k):
+    """Outputs of msa_score_topk and the shortest of its calls."""
+    ws = torch.empty(msa.score_topk_workspace_bytes(cfg, q.shape[0], q.shape[1], k), dtype=torch.uint8, device="cuda")
+    idx, val = msa.msa_score_topk(cfg, q, KR, inv, k, workspace=ws)
+    best = 1e9
+    for _ in range(15):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        msa.msa_score_topk(cfg, q, KR, inv, k, idx, val, ws)
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3)
+    return idx, val, best
+
+
 # (N, Hkv, r, C, d, B, M, k, sim): the all-heads scan writes a score matrix
 ALL_SCAN = [
     (5, 8, 1, 8, 128, 1, 1, 5, "cos"),            # fewer tiles than one workgroup has waves
@@ -284,6 +299,24 @@ def test_token_pooling_of_copies_and_zeros(N, copies, k, zeros):
         assert np.array_equal(gi, np.arange(k)) and np.all(gv == 0)
 
 
+def test_token_pooling_of_nothing_but_zeros():
+    """A question of zeros takes no longer than another one: of the documents that tie the first k go on, not k of every
+    workgroup (which took 1.7 times as long).  A question that is not a number selects nothing."""
+    N, Hkv, C, d, M, k = 8192, 8, 8, 128, 150, 32
+    say("token pooling of a question of zeros")
+    cfg = msa.MsaConfig(N, 8 * C, 8, Hkv, Hkv, d, 1e6, select_scope=msa.MSA_SCOPE_ALL, token_pool=1)
+    keys, KR = device_index(61001, Hkv, N * C, d)
+    inv = 1.0 / keys.float().norm(dim=-1)
+    q = torch.randn((1, M, Hkv, d), generator=torch.Generator("cuda").manual_seed(1), device="cuda").to(torch.bfloat16)
+    _, _, plain = call_us(cfg, q, KR, inv, k)
+    idx, val, zeros = call_us(cfg, torch.zeros_like(q), KR, inv, k)
+    assert torch.equal(idx.view(-1), torch.arange(k, dtype=torch.int32, device="cuda")) and bool((val == 0).all())
+    say(f"  {plain:.0f} us, zeros {zeros:.0f}")
+    assert zeros <= 1.3 * plain
+    idx, val, _ = call_us(cfg, torch.full_like(q, float("nan")), KR, inv, k)
+    assert bool((idx == -1).all()) and bool((val == float("-inf")).all())
+
+
 # (N, Hkv, C, d, B, M, k, scope, pool): a row's k best where every document ties
 ALL_TIED = [
     (97656, 8, 8, 128, 8, 1, 32, "group", 0),     # candidate lists of long streams and their merge
@@ -346,20 +379,7 @@ def test_merge_of_tied_lists(what, k):
     q = torch.randn((B, 1, Hkv, d), generator=torch.Generator("cuda").manual_seed(k), device="cuda").to(torch.bfloat16)
     inv = torch.zeros((Hkv, cfg.n_tiles * 16), device="cuda")
     inv[:, :N * C] = 1.0 / keys.float().norm(dim=-1)
-
-    def call_us(q, KR, inv):
-        ws = torch.empty(msa.score_topk_workspace_bytes(cfg, B, 1, k), dtype=torch.uint8, device="cuda")
-        idx, val = msa.msa_score_topk(cfg, q, KR, inv, k, workspace=ws)
-        best = 1e9
-        for _ in range(15):
-            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            a.record()
-            msa.msa_score_topk(cfg, q, KR, inv, k, idx, val, ws)
-            b.record()
-            torch.cuda.synchronize()
-            best = min(best, a.elapsed_time(b) * 1e3)
-        return idx[:, 0], val[:, 0], best
-    _, _, plain = call_us(q, KR, inv)
+    _, _, plain = call_us(cfg, q, KR, inv, k)
     at = torch.arange(k, device="cuda")
     if what == "zeros":
         q[-2:] = 0
@@ -369,7 +389,8 @@ def test_merge_of_tied_lists(what, k):
         keys[:, at] = q[0, 0][:, None, None, :]
         KR = keys.reshape(Hkv, -1, 16, d // 8, 8).transpose(2, 3).contiguous()
         inv[:, :N * C] = 1.0 / keys.float().norm(dim=-1).reshape(Hkv, -1)
-    idx, val, tied = call_us(q, KR, inv)
+    idx, val, tied = call_us(cfg, q, KR, inv, k)
+    idx, val = idx[:, 0], val[:, 0]
     rows = idx[-2:] if what == "zeros" else idx[:1]
     assert torch.equal(rows, at[:k].int().expand_as(rows))
     assert bool((val[-2:] == 0).all()) if what == "zeros" else (val[0] - 1).abs().max() <= 2e-5
