@@ -1235,30 +1235,37 @@ __global__ __launch_bounds__(256) void score_merge_kernel(const unsigned long lo
   const int P = (n_lists * depth <= kMaxSub) ? n_lists * depth : kMaxSub;
   for (int i = tid; i < P; i += 256) sub[i] = src[(i / depth) * k + (i % depth)];
   if (tid < 8) sub[P + tid] = 0ull;  // read eight at a time below (zero: greater than no key)
-  if (tid == 0) n_surv = 0;
+  if (tid == 0) {
+    n_surv = 0;
+    theta_s = 0ull;
+  }
   __syncthreads();
-  // (Ranking the heads one against the other for their exact k-th took 2 us of this kernel's 7.5 with 256 lists.)
-  uint32_t ob = 0u;
-  for (int i = tid; i < P; i += 256) {
-    const uint32_t o = (uint32_t)(sub[i] >> 32);
-    ob = o > ob ? o : ob;
+  // (Ranking the heads one against the other for their exact k-th took 2 us of this kernel's 7.5 with 256 lists.  Up to 64 are
+  // ranked sooner than bounded: 16384 merges of the GEMM's few lists, k = 16, whole call 352 -> 343 us, 6464 of 65 documents
+  // 108 -> 103.)
+  bool exact = P <= 64;
+  unsigned long long theta = 0ull;
+  if (!exact) {  // block-uniform
+    uint32_t ob = 0u;
+    for (int i = tid; i < P; i += 256) {
+      const uint32_t o = (uint32_t)(sub[i] >> 32);
+      ob = o > ob ? o : ob;
+    }
+    const uint32_t bound = kth_best_bound<4>(ob, k, theta_w);
+    theta = (unsigned long long)bound << 32;
+    // A query of zeros (an empty slot of a batch) ties with every document, copies of the best documents with each other: all
+    // entries of all lists may reach a bound of score bits, and every list would be walked to its end (8 queries, 2 of them zeros,
+    // 97656 documents, k = 32, whole call 428 us, with their exact k-th key 291; 3000 copies of the best document 405, 270).
+    int ties = 0;  // heads in the interval of scores that starts with the bound (the same in every wave)
+    for (int i0 = 0; i0 < P; i0 += 64) {
+      const uint32_t o = i0 + (tid & 63) < P ? (uint32_t)(sub[i0 + (tid & 63)] >> 32) : 0u;
+      ties += __popcll(__ballot(o != 0u && (o & ~0xfffu) == bound));
+    }
+    exact = ties > kFewTies;
   }
-  const uint32_t bound = kth_best_bound<4>(ob, k, theta_w);
-  unsigned long long theta = (unsigned long long)bound << 32;
-  // A query of zeros (an empty slot of a batch) ties with every document, copies of the best documents with each other: all
-  // entries of all lists may reach a bound of score bits, and every list would be walked to its end (8 queries, 2 of them zeros,
-  // 97656 documents, k = 32, whole call 428 us, with their exact k-th key 291; 3000 copies of the best document 405, 270).
-  int ties = 0;  // heads in the interval of scores that starts with the bound (the same in every wave)
-  for (int i0 = 0; i0 < P; i0 += 64) {
-    const uint32_t o = i0 + (tid & 63) < P ? (uint32_t)(sub[i0 + (tid & 63)] >> 32) : 0u;
-    ties += __popcll(__ballot(o != 0u && (o & ~0xfffu) == bound));
-  }
-  bool exact = ties > kFewTies;
   int S;
   for (;;) {  // once or twice
     if (exact) {
-      if (tid == 0) theta_s = 0ull;
-      __syncthreads();
       for (int i = tid; i < P; i += 256) {
         const unsigned long long x = sub[i];
         int rank = 0;
