@@ -217,7 +217,8 @@ __device__ __forceinline__ void fold_query_tile(const FoldRegs<D>& fr, long long
 //       are made of.  Scans with the threshold exchange keep the prepared operands: that launch also resets the
 //       exchange buffer, and their waves never synchronise.
 // STREAM: streaming loads of the index (load_stream16; see stream_index_of).
-template <int D, int NQT, bool COS, int MODE, bool FOLD, bool STREAM>
+// LATE: with FOLD, one tile is requested ahead of the folding and the others behind it, else all ahead (see late_requests).
+template <int D, int NQT, bool COS, int MODE, bool FOLD, bool STREAM, bool LATE>
 __global__ __launch_bounds__(64 * kScanWaves) __attribute__((amdgpu_waves_per_eu(2)))
 void score_scan_kernel(ScoreArgs a) {
   constexpr bool DENSE = MODE != 0;
@@ -297,7 +298,9 @@ void score_scan_kernel(ScoreArgs a) {
     for (int s = 0; s < NS; ++s) buf[u][s] = load_tile16(KRg + t * TILE_ELEMS + s * 512);
     binv[u] = COS ? ing[t * 16] : 1.0f;
   };
-  first_tile(0);
+  constexpr int kAheadOfFold = LATE ? 1 : kPrefetch;
+#pragma unroll
+  for (int u = 0; u < kAheadOfFold; ++u) first_tile(u);
   // Wave t folds tile t.  It asks for one tile ahead of that and for the others behind it: with all of them ahead, the
   // wave is held up until the memory system has taken the first requests of every wave (3 to 6 us where the grid fills the
   // chip), and the operands are ready after the first tiles have come and the memory has had nothing to do in between (one
@@ -311,7 +314,7 @@ void score_scan_kernel(ScoreArgs a) {
                          reinterpret_cast<aop_tile_t*>(smem[wave] + kListBytes / 2), lane);
   }
 #pragma unroll
-  for (int u = 1; u < kPrefetch; ++u) first_tile(u);
+  for (int u = kAheadOfFold; u < kPrefetch; ++u) first_tile(u);
 
   // ---- A operands: row n of query tile t is query 8t + n/2, hi (even n) or lo (odd n) half of the folded fp32
   // routing query ------------------------------------------------------------------------------------------
@@ -1168,6 +1171,15 @@ bool stream_index_of(const Dims& dm, int n_pass) {
   return bytes > ((size_t)256 << 20) || (n_pass == 1 && bytes >= 128000000);
 }
 
+// Scans of four query tiles fold in every wave, so nobody requests tiles meanwhile; a stream of more than a few tiles per wave then
+// loses more than the operands that are ready earlier give (index again and again, all ahead -> one: 32 queries over 2048
+// documents, 4 tiles per wave, 18.4 -> 17.4 us, 3500, 7 tiles, 25.6 -> 26.2, 9000, 18 tiles, 44.3 -> 45.8, 13000 53.8 -> 56.4; 24
+// queries, whose last tile is empty, 4000, 8 tiles, 24.8 -> 24.3, 6000 30.6 -> 30.7, 13000 53.0 -> 54.1; index cold about half of
+// each).
+static bool late_requests(const ScorePlan& pl, int BM) {
+  return pl.q_per_pass < 32 || pl.tiles_per_wave <= (BM <= 24 ? 8 : 6);
+}
+
 // Waves per workgroup: sixteen where the rows leave the chip idle anyway (one round of 256 workgroups or fewer) and a row
 // is longer than four waves hold in registers: 32768 scores at once.  One workgroup then takes a row that went in parts
 // with a merge launch behind: 30000 documents of 64 dims, 2 queries, whole call 27.4 -> 24.6 us; 20000 of 128, one query,
@@ -1784,13 +1796,19 @@ do { \
   for (int pass = 0; pass < pl.n_pass; ++pass) {
     a.q0 = pass * pl.q_per_pass;
     const int nqt = pl.q_per_pass / 8;  // 1, 2 or 4
+    const bool late = late_requests(pl, BM);
+#define MSA_SCAN_2(DD, QQ, CC, SS) \
+  do { \
+    if (late) hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 2, true, SS, true>), grid, block, 0, st, a); \
+    else hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 2, true, SS, QQ != 4>), grid, block, 0, st, a); \
+  } while (0)
 #define MSA_SCAN(DD, QQ, CC) \
   do { \
-    if (pl.mode == 2 && stream_index) hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 2, true, true>), grid, block, 0, st, a); \
-    else if (pl.mode == 2) hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 2, true, false>), grid, block, 0, st, a); \
-    else if (pl.mode == 1) hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 1, true, false>), grid, block, 0, st, a); \
-    else if (fold_in_scan) hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 0, true, true>), grid, block, 0, st, a); \
-    else hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 0, false, true>), grid, block, 0, st, a); \
+    if (pl.mode == 2 && stream_index) MSA_SCAN_2(DD, QQ, CC, true); \
+    else if (pl.mode == 2) MSA_SCAN_2(DD, QQ, CC, false); \
+    else if (pl.mode == 1) hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 1, true, false, true>), grid, block, 0, st, a); \
+    else if (fold_in_scan) hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 0, true, true, true>), grid, block, 0, st, a); \
+    else hipLaunchKernelGGL((score_scan_kernel<DD, QQ, CC, 0, false, true, true>), grid, block, 0, st, a); \
   } while (0)
     if (dm.d == 128) {
       if (dm.cos) {
@@ -1806,6 +1824,7 @@ do { \
       }
     }
 #undef MSA_SCAN
+#undef MSA_SCAN_2
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
   }
   profile_mark(dm, true, st);

@@ -74,6 +74,16 @@ def test_row_selection(N, Hkv, B, k):
     check_topk_generic(q, KRb, C, N, idx, val, k, "cos", "group", False)
 
 
+# a scan of four query tiles at the edges between one tile requested ahead of the folding and all (6 or 8 tiles per wave)
+FOUR_TILES = [(3072, 8, 2, 8, 64, 32, 1, 16, "cos"), (3073, 8, 1, 8, 64, 32, 1, 16, "dot"), (4096, 8, 1, 8, 128, 24, 1, 9, "cos"),
+              (4097, 8, 1, 8, 128, 23, 1, 9, "cos"), (4099, 8, 1, 8, 64, 25, 1, 9, "dot")]
+
+
+@pytest.mark.parametrize("N,Hkv,r,C,d,B,M,k,sim", FOUR_TILES)
+def test_scan_of_four_tiles(N, Hkv, r, C, d, B, M, k, sim):
+    test_prefill_scoring_k_above_16(N, Hkv, r, C, d, B, M, k, sim)
+
+
 @pytest.mark.parametrize("N,Hkv,r,C,d,B,M,k,sim", ALL_SCAN)
 def test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim):
     say(f"all-heads scan N={N} Hkv={Hkv} C={C} d={d} B={B} M={M} k={k} {sim}")
