@@ -679,7 +679,17 @@ constexpr int kAllGroups = 256;  // workgroups: one per CU
 // (head, 8 queries) tiles that a workgroup of the all-heads scan folds itself: one for each of its waves, which takes less than
 // the launch that would prepare them (4 queries over 13401 documents 18.1 -> 16.4 us, one over 2048 14.5 -> 12.7, 8 over 8192
 // 30.3 -> 28.8); with two for each it takes longer (14 queries over 2048, 8 heads: 16.1 -> 18.2).
+// Every workgroup reads all queries, so not more than kAllFoldElems of them (88 KiB) over a short index, which the launch takes less
+// time than (index again and again, prepared -> folded: 16 queries of 4 groups of 8 heads, 128 KiB, 2048 documents 13.8 -> 14.9, 5500
+// the same, 9000 1 us less; 32 of 2 groups of 8 heads 3500 14.8 -> 16.2; 10 of 4 groups, 80 KiB, the same at 2048, 18 of 2 groups,
+// 72 KiB, 0.3 less at 300 and 4500): the line at kAllFoldTilesIdx tiles of all heads, 49 MB.
 constexpr int kAllFoldTiles = 8;
+constexpr long long kAllFoldElems = 45056, kAllFoldTilesIdx = 12000;
+
+static bool all_heads_folds(const Dims& dm, const ScorePlan& pl, int BM) {
+  return pl.q_per_pass / 8 * dm.Hkv <= kAllFoldTiles &&
+         ((long long)BM * dm.Hq * dm.d <= kAllFoldElems || (long long)dm.Hkv * dm.tiles >= kAllFoldTilesIdx);
+}
 
 // log2(tiles per unit): the unit that keeps the longest stream shortest (whole units per wave), of equals the largest
 static int scan_all_ushift(long long seg_tiles, int C) {
@@ -1697,7 +1707,7 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
   a.tiles_per_wave = pl.tiles_per_wave;
   a.n_qtiles = pl.n_qtiles;
   a.q_route = (const uint16_t*)q_route;
-  const bool fold_in_scan = pl.all_heads ? pl.q_per_pass / 8 * dm.Hkv <= kAllFoldTiles : !pl.exchange;
+  const bool fold_in_scan = pl.all_heads ? all_heads_folds(dm, pl, BM) : !pl.exchange;
   if (!fold_in_scan) {
     const long long n_gmax = pl.exchange ? (long long)dm.Hkv * BM * pl.n_splits : 0;
     const unsigned blocks = (unsigned)(pl.n_qtiles * dm.Hkv);
@@ -1754,8 +1764,9 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
       dim3 grid((unsigned)(wgs < kAllGroups ? wgs : kAllGroups)), block(64 * kAllWaves);
 #define MSA_SCAN_ALL(DD, HH, QQ) \
 do { \
-  constexpr bool FF = HH * QQ <= kAllFoldTiles; /* fold_in_scan */ \
-  if (stream_index) hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, QQ, true, FF>), grid, block, 0, st, sa); \
+  constexpr bool FF = HH * QQ <= kAllFoldTiles; /* can fold */ \
+  if (FF && !fold_in_scan) hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, QQ, false, false>), grid, block, 0, st, sa); \
+  else if (stream_index) hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, QQ, true, FF>), grid, block, 0, st, sa); \
   else hipLaunchKernelGGL((score_scan_all_kernel<DD, HH, QQ, false, FF>), grid, block, 0, st, sa); \
 } while (0)
 #define MSA_SCAN_ALL_Q(DD, HH) \

@@ -110,6 +110,10 @@ ALL_FOLDED = [
     (33, 4, 3, 16, 64, 17, 1, 5, "dot"),
     (2100, 2, 1, 1, 128, 6, 5, 9, "dot"),     # four tiles of two heads, the last of 6 queries
     (70, 2, 2, 4, 64, 1, 1, 12, "cos"),       # waves without a tile
+    (97, 4, 8, 8, 128, 11, 1, 16, "cos"),     # as many queries as are folded over any index
+    (97, 4, 8, 8, 128, 12, 1, 16, "cos"),     # prepared: more of them ...
+    (3000, 4, 8, 16, 128, 16, 1, 16, "cos"),  # ... but over an index of 12000 tiles
+    (2999, 4, 8, 16, 128, 16, 1, 16, "cos"),
     (70000, 2, 2, 2, 64, 2, 4, 20, "cos"),    # parts of rows
 ]
 
