@@ -710,7 +710,7 @@ static int scan_all_ushift(long long seg_tiles, int C) {
 struct ScanAllArgs {
   const uint4* qop;       // [HKV][n_qtiles][NS][64] prepared A operands (prep_scan_operands_kernel)
   const uint16_t* q_route;  // FOLD: the queries themselves
-  int q0, BM, Hq, r;        // FOLD: first query of the pass, queries of the call
+  int BM, Hq, r;            // FOLD: queries of the call (one pass)
   const uint16_t* KR;     // tiled
   const float* inv_norm;  // null: dot product
   float* mat;             // [queries][mat_stride]
@@ -749,7 +749,7 @@ __global__ __launch_bounds__(64 * kAllWaves) void score_scan_all_kernel(ScanAllA
   // ---- operands: global -> LDS, requested first; the tiles requested next stay in flight across their wait -------
   FoldRegs<D> fr;
   if constexpr (FOLD) {
-    if (wave < HKV * NQT) fold_query_load<D>(a.q_route, a.q0 / 8 + wave / HKV, wave % HKV, a.BM, a.Hq, a.r, fr, lane);
+    if (wave < HKV * NQT) fold_query_load<D>(a.q_route, wave / HKV, wave % HKV, a.BM, a.Hq, a.r, fr, lane);
   } else {
     const uint32_t op_lds = lds_addr_of(&Aop[0][0][0][0]);
 #pragma unroll
@@ -796,11 +796,11 @@ __global__ __launch_bounds__(64 * kAllWaves) void score_scan_all_kernel(ScanAllA
   if constexpr (FOLD) {
     // (the folding behind one request, not behind all of them: see score_scan_kernel)
     first_entry(0);
-    for (int e = wave; e < HKV * NQT; e += kAllWaves) {
-      const int h = e % HKV, t = e / HKV;
-      if (e != wave) fold_query_load<D>(a.q_route, a.q0 / 8 + t, h, a.BM, a.Hq, a.r, fr, lane);
-      static_assert(8 * D * 4 == NS * 64 * 16, "the folded queries take the place of their operands");
-      fold_query_tile<D>(fr, a.q0 / 8 + t, a.BM, a.r, cos ? 1 : 0, reinterpret_cast<float*>(&Aop[h][t][0][0]), Aop[h][t], lane);
+    static_assert(HKV * NQT <= kAllWaves, "a tile per wave");
+    static_assert(8 * D * 4 == NS * 64 * 16, "the folded queries take the place of their operands");
+    if (wave < HKV * NQT) {
+      const int h = wave % HKV, t = wave / HKV;
+      fold_query_tile<D>(fr, t, a.BM, a.r, cos ? 1 : 0, reinterpret_cast<float*>(&Aop[h][t][0][0]), Aop[h][t], lane);
     }
 #pragma unroll
     for (int u = 1; u < kPrefetch; ++u) first_entry(u);
@@ -1734,7 +1734,6 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
     ScanAllArgs sa;
     sa.qop = (const uint4*)((char*)ws + pl.off_qop);
     sa.q_route = (const uint16_t*)q_route;
-    sa.q0 = 0;
     sa.BM = BM;
     sa.Hq = dm.Hq;
     sa.r = dm.r;
