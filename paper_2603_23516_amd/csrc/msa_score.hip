@@ -679,10 +679,10 @@ constexpr int kAllGroups = 256;  // workgroups: one per CU
 // (head, 8 queries) tiles that a workgroup of the all-heads scan folds itself: one for each of its waves, which takes less than
 // the launch that would prepare them (4 queries over 13401 documents 18.1 -> 16.4 us, one over 2048 14.5 -> 12.7, 8 over 8192
 // 30.3 -> 28.8); with two for each it takes longer (14 queries over 2048, 8 heads: 16.1 -> 18.2).
-// Every workgroup reads all queries, so not more than kAllFoldElems of them (88 KiB) over a short index, which the launch takes less
-// time than (index again and again, prepared -> folded: 16 queries of 4 groups of 8 heads, 128 KiB, 2048 documents 13.8 -> 14.9, 5500
-// the same, 9000 1 us less; 32 of 2 groups of 8 heads 3500 14.8 -> 16.2; 10 of 4 groups, 80 KiB, the same at 2048, 18 of 2 groups,
-// 72 KiB, 0.3 less at 300 and 4500): the line at kAllFoldTilesIdx tiles of all heads, 49 MB.
+// Every workgroup reads all queries, so not more than kAllFoldElems of them (88 KiB) over a short index (again and again, prepared ->
+// folded: 32 queries of 2 groups of 8 heads, 128 KiB, 1000 documents 13.9 -> 14.3 us, 3000 14.5 -> 15.4, 5500 15.8 -> 16.4, 7000 the
+// same; 16 of 4 groups 3000 14.0 -> 14.3, 7000 19.6 -> 18.6; 10 of 4 groups, 80 KiB, 2048 13.7 -> 12.5, 4500 16.4 -> 15.9); from
+// kAllFoldTilesIdx tiles of all heads on, 49 MB, they fold more too.
 constexpr int kAllFoldTiles = 8;
 constexpr long long kAllFoldElems = 45056, kAllFoldTilesIdx = 12000;
 

@@ -294,10 +294,11 @@ __device__ __forceinline__ void wide_store_pooled(const WideArgs& a, const float
   if (rr == 0 && (n & 7) < KT && doc < a.seg_docs) a.mat[tb * a.mat_stride + doc] = fmaxf(mine * inv_heads, -INFINITY);  // (not a number: last)
 }
 
-// POOL: token pooling, the matrix holds the best score of a block's tokens.  STREAM: streaming loads of the keys, where the scans
-// have them too (stream_index_of; index cold, whole call: 150 tokens, pooled, 97656 documents 330 -> 317 us, 120 over 20000 94.7
-// -> 90.8, 400, three blocks, over 30000 266 -> 260; 160 not pooled over 97656 422 -> 415, 90 over 16000 80.7 -> 78.2; the same
-// calls again and again up to 3 % slower up to 256 MB, not beyond).
+// POOL: token pooling, the matrix holds the best score of a block's tokens.  STREAM: streaming loads of the keys, with pooling where
+// the scans have them too (stream_index_of; index cold / again and again, whole call, 150 tokens: 9000 documents 73.8 / 67.7 -> 71.9 /
+// 71.7 us, 15600 76.6 / 69.7 -> 74.6 / 73.7, 20000 97.0 / 95.3 -> 93.0 / 91.0), without beyond 256 MB only: below, nothing is gained
+// (9000 documents 82.2 / 75.4 -> 82.0 / 79.8, 13000 86.0 / 79.9 -> 85.5 / 83.9; 20000 113.5 / 109.8 -> 112.1 / 110.2, 70 tokens 99.1 /
+// 97.4 -> 96.3 / 93.6).
 template <int NT, bool POOL, bool STREAM>
 __global__ __launch_bounds__(64 * kRowsWaves) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void score_wide_rows_kernel(WideArgs a) {
@@ -1026,7 +1027,7 @@ __global__ __launch_bounds__(512) void pool_best_kernel(WidePoolArgs a) {
 
 #define MSA_WIDE_ROWS(NN, PP) \
   do { \
-    if (stream_index_of(dm, 1)) hipLaunchKernelGGL((score_wide_rows_kernel<NN, PP, true>), grid, block, 0, st, a); \
+    if (stream_index_of(dm, PP ? 1 : 2)) hipLaunchKernelGGL((score_wide_rows_kernel<NN, PP, true>), grid, block, 0, st, a); \
     else hipLaunchKernelGGL((score_wide_rows_kernel<NN, PP, false>), grid, block, 0, st, a); \
   } while (0)
 
@@ -1165,6 +1166,29 @@ int launch_score_wide_pool(const Dims& dm, const WidePoolPlan& pp, const void* q
   return hipGetLastError() == hipSuccess ? MSA_OK : MSA_ERR_HIP;
 }
 
+// More rows per key for 65 to 160 tokens of eight groups, whose blocks of 64 rows are two or three times the reads of a key, the
+// third half empty (150 tokens, 97656 documents 496 -> 430 us; 80 401 -> 354; 70 over 300 41 -> 38).  Up to 192 three blocks are full
+// (190 over 20000 124 -> 124, on another card 127 -> 136).  More tokens are bound by the products, and these by the operand reads
+// (600 tokens, 30000 documents 483 -> 494, 2048 over 32768 1477 -> 1714); with four groups the resident operands leave room for
+// two workgroups per CU (100 tokens, 60000 documents 157 -> 160).
+// A wave's unit here is half as many keys with all rows, so the line follows the rounds of units that both take over a segment
+// (index cold / again and again, blocks of 64 rows -> here):
+//   six tiles of rows: as fast in a round at any size (8300 documents 76 / 64 -> 71 / 63, 10500 79 / 69 -> 74 / 69, 21500 111 / 106 -> 101);
+//   eight: faster in one round (2000 50 / 42 -> 46 / 42, 8100 56 / 50 -> 55 / 51), then slower (8300 77 / 65 -> 78 / 69, 13000 82 / 73
+//   -> 82 / 76) until the index is too large for the cache (19000 107 / 101 -> 105 / 103, 21500 111 / 107 -> 107 / 105);
+//   ten: faster with a round less (5600 68 / 58 -> 53 / 49, 11300 95 / 78 -> 82 / 77, 16800 115 / 105 -> 110 / 108), else not (300
+//   documents 42 -> 45, 5300 52 / 47 -> 52 / 48, 8300 75 / 66 -> 83 / 75).
+static bool rows_kernel_pays(int nq, int seg_tiles) {
+  if (nq <= kWideRows || nq > 16 * kRowsMost) return false;
+  const int blocks = (nq + kWideRows - 1) / kWideRows, waves = kWideGroups / blocks * kWideWaves;
+  const int rounds = ((seg_tiles + kWideTiles - 1) / kWideTiles + waves - 1) / waves;
+  const int rows_waves = kWideGroups * kRowsWaves;
+  const int rows_rounds = ((seg_tiles + kRowsTiles - 1) / kRowsTiles + rows_waves - 1) / rows_waves;
+  if (nq <= 96) return true;
+  if (nq <= 128) return rows_rounds == 1 || seg_tiles >= 10000;
+  return rows_rounds < rounds;
+}
+
 int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, int BM, const void* KR,
                       const float* inv_norm, int k, void* ws, hipStream_t st, int32_t* out_idx, float* out_score,
                       unsigned long long* out_key) {
@@ -1209,13 +1233,7 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
       a.tile0 = (long long)doc0 * dm.C / 16;  // doc0 is a multiple of 64 (or 0)
       a.seg_docs = n_docs;
       a.seg_tiles = (int)(((long long)n_docs * dm.C + 15) / 16);
-      // More rows per key for 65 to 160 tokens of eight groups, whose blocks of 64 rows are two or three times the reads of a
-      // key, the third half empty (150 tokens, 97656 documents 496 -> 430 us; 80 401 -> 354; 70 over 300 41 -> 38; 120 over
-      // 1000 the same).  Up to 192 three blocks are full (190 over 20000 124 -> 124, on another card 127 -> 136).  More tokens
-      // are bound by the products, and these by the operand reads (600 tokens, 30000 documents 483 -> 494, 2048 over 32768
-      // 1477 -> 1714); with four groups the resident operands leave room for two workgroups per CU (100 tokens, 60000
-      // documents 157 -> 160).
-      const bool rows = !pl.pair && dm.Hkv == 8 && nq > kWideRows && nq <= 16 * kRowsMost;
+      const bool rows = !pl.pair && dm.Hkv == 8 && rows_kernel_pays(nq, a.seg_tiles);
       const int units = (a.seg_tiles + (rows ? kRowsTiles : kWideTiles) - 1) / (rows ? kRowsTiles : kWideTiles);
       const int waves = rows ? kRowsWaves : kWideWaves;
       int nt = kWideRows / 16;

@@ -257,7 +257,11 @@ def test_all_heads_wide(N, Hkv, r, C, d, B, M, k, sim):
 # wave's keys, fewer documents than a workgroup has waves
 ALL_ROWS = [(37, 8, 1, 8, 128, 1, 64, 9, "cos"), (37, 8, 1, 8, 128, 1, 65, 9, "cos"), (1003, 8, 2, 8, 128, 1, 96, 16, "cos"),
             (2051, 8, 4, 8, 128, 1, 97, 32, "cos"), (5, 8, 1, 8, 128, 2, 64, 5, "cos"), (520, 8, 4, 8, 128, 3, 53, 12, "cos"),
-            (999, 8, 1, 8, 128, 1, 129, 16, "cos"), (4100, 8, 2, 8, 128, 1, 160, 8, "cos"), (300, 8, 1, 8, 128, 1, 161, 8, "cos")]
+            (999, 8, 1, 8, 128, 1, 129, 16, "cos"), (4100, 8, 2, 8, 128, 1, 160, 8, "cos"), (300, 8, 1, 8, 128, 1, 161, 8, "cos"),
+            # ten tiles of rows with a round of units less than blocks of 64 rows take, eight in one round, and just not
+            (5440, 8, 1, 8, 128, 1, 130, 8, "cos"), (5441, 8, 1, 8, 128, 1, 129, 16, "cos"), (8192, 8, 1, 8, 128, 1, 160, 8, "cos"),
+            (8193, 8, 1, 8, 128, 1, 145, 8, "cos"), (8192, 8, 1, 8, 128, 1, 128, 8, "cos"), (8193, 8, 1, 8, 128, 1, 97, 8, "cos"),
+            (10881, 8, 1, 8, 128, 1, 131, 8, "cos"), (20001, 8, 1, 8, 128, 1, 100, 8, "cos")]
 
 
 @pytest.mark.parametrize("N,Hkv,r,C,d,B,M,k,sim", ALL_ROWS)
