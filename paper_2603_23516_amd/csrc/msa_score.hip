@@ -1167,18 +1167,21 @@ __global__ __launch_bounds__(64 * WAVES) void topk_rows_kernel(RowsArgs a) {
   }
 }
 
-// Streaming loads of the index in the score-matrix scans: in one pass from 128 MB on, always beyond the 256 MB of cache behind
-// the L2s.  A program reads more than that cache holds between two scans of an index (the selected documents of eight streams,
-// the indexes of its other layers, its weights), so the scan finds it cold, and plain loads spend their time on caching what
-// nobody reads again (index cold, whole call, 8 queries: 8192 documents, 134 MB, 33.5 -> 31.2 us, 13000 51.0 -> 47.3, 18000
-// 67.1 -> 60.5, 32768 110 -> 99; 24 queries over all heads 37.7 -> 34.1, 30000 documents 107 -> 97; 5000, 82 MB, 24.6 -> 23.8 in
-// one kernel, 24.6 in the other).  Routing over one index again and again with nothing read in between is what the plain loads
-// are better at while it fits that cache: 8192 documents 28.6 -> 29.3, 13000 43.8 -> 46.0, 5000 21.2 -> 22.5, and a second pass
-// (13000 documents, 48 queries, keeps them); from 16384 documents on it gains too (53.6 -> 53.5, 20000 68.1 -> 64.9, 32768 106 ->
-// 95.5).
-bool stream_index_of(const Dims& dm, int n_pass) {
+// Streaming loads of the index: always beyond the 256 MB of cache behind the L2s (index cold / again and again, whole call, 8
+// queries: 20000 documents, 328 MB, 72.9 / 69.1 -> 65.7 / 64.5 us, 32768 110 / 106 -> 99 / 95.5), and from 128 MB on where a scan finds
+// its index cold: plain loads then spend their time on caching what nobody reads again.
+//   The score-matrix scan gains 5 to 9 % on a cold index and loses 2 to 10 % on one that is read again and again (8 queries, 7400
+//   documents, 121 MB, 31.8 / 27.1 -> 30.0 / 28.7, 9000 39.7 / 33.9 -> 36.8 / 35.4, 13000 51.2 / 43.6 -> 47.0 / 45.6, 15600, 256 MB, 58.4
+//   / 51.0 -> 53.3 / 51.7; 32 queries over 13000 64.9 / 53.8 -> 59.6 / 59.3), so it has them in a step of layers whose indexes
+//   together outgrow the cache (four of 134 MB, 8 queries: 214 -> 194 us with the other changes of the scan; the first step after
+//   the indexes were written 692 -> 675, in its spread) and plain loads in a call of its own.
+//   The all-heads scan loses next to nothing (24 queries, 7900 documents 36.1 / 31.8 -> 33.8 / 31.6, 11000 49.1 / 42.6 -> 44.9 / 42.6,
+//   13000 55.2 / 47.0 -> 50.3 / 48.5, 15600 62.6 / 54.0 -> 56.1 / 54.2; 22000 of 64 dims 51.1 / 42.4 -> 45.8 / 44.4).
+// Below 128 MB an index may well be in the cache still when it is read again (5000 documents, 82 MB, 8 queries 24.6 / 21.5 -> 23.7 /
+// 22.6, 6800, 111 MB, 29.9 / 25.8 -> 28.3 / 27.4); so it may for the second pass of a call.
+bool stream_index_of(const Dims& dm, bool cold) {
   const size_t bytes = (size_t)dm.Hkv * dm.tiles * 16 * dm.d * 2;
-  return bytes > ((size_t)256 << 20) || (n_pass == 1 && bytes >= 128000000);
+  return bytes > kCacheBytes || (cold && bytes >= 128000000);
 }
 
 // Scans of four query tiles fold in every wave, so nobody requests tiles meanwhile; a stream of more than a few tiles per wave then
@@ -1721,7 +1724,7 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
                          dm.r, dm.cos, pl.n_qtiles, a.gmax, n_gmax);
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
   }
-  const bool stream_index = stream_index_of(dm, pl.n_pass);
+  const bool stream_index = stream_index_of(dm, pl.n_pass == 1 && (pl.all_heads || dm.cold_index));
   RowsArgs ra;
   ra.mat = (const float*)((char*)ws + pl.off_mat);
   ra.BM = BM;

@@ -1027,7 +1027,7 @@ __global__ __launch_bounds__(512) void pool_best_kernel(WidePoolArgs a) {
 
 #define MSA_WIDE_ROWS(NN, PP) \
   do { \
-    if (stream_index_of(dm, PP ? 1 : 2)) hipLaunchKernelGGL((score_wide_rows_kernel<NN, PP, true>), grid, block, 0, st, a); \
+    if (stream_index_of(dm, PP)) hipLaunchKernelGGL((score_wide_rows_kernel<NN, PP, true>), grid, block, 0, st, a); \
     else hipLaunchKernelGGL((score_wide_rows_kernel<NN, PP, false>), grid, block, 0, st, a); \
   } while (0)
 
@@ -1248,7 +1248,7 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
       // Streaming loads where one token block reads the keys and the cache behind the L2s cannot hold them: 40 tokens, 97656
       // documents 357 -> 321 us, 64 over 20000 106 -> 101 (102.4 -> 98.1 again and again).  A smaller index gains nothing when it
       // is cold and loses when it is not (50 over 8000 56.8, 57.9; again and again 49.6, 56.2).
-      const bool stream = a.n_tb == 1 && stream_index_of(dm, 2);
+      const bool stream = a.n_tb == 1 && stream_index_of(dm, false);
       dim3 grid((unsigned)((a.n_tb * streams + 7) / 8 * 8)), block(64 * waves);
       if (tok0 == 0 && doc0 == 0) profile_mark(dm, false, st);
 #define MSA_WIDE(DD, HH) \

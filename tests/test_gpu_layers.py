@@ -75,6 +75,32 @@ def test_three_routed_layers_against_the_oracle(tier):
     assert bank_bytes == L * 2 * N * Hkv * C * d * 2
 
 
+@pytest.mark.parametrize("L,N,B", [(2, 8192, 3), (2, 8193, 3), (3, 7813, 9), (3, 7811, 1), (2, 8195, 17)])
+def test_layers_whose_indexes_outgrow_the_cache(L, N, B):
+    """Layers of 128 MB each, together just under and just over 256 MB, below and above 128 MB: selections and scores are bit for
+    bit those of a call of its own, whatever loads the scans of a step use."""
+    G, P, Hkv, d, k, Lloc = 64, 8, 8, 128, 9, 16
+    print(f"{L} routed layers of {N} documents, {B} queries", flush=True)
+    cfg = msa.MsaConfig(N, G, P, Hkv, Hkv, d, 1e4)
+    stack = LayerStack(cfg, L, B, 1, k, Lloc)
+    gen = torch.Generator("cuda").manual_seed(97000 + N)
+    for l in range(L):
+        bank = torch.randn((N, Hkv, G, d), generator=gen, device="cuda", dtype=torch.bfloat16)
+        stack.set_layer_keys(l, bank)
+        stack.set_layer_values(l, bank)
+    del bank
+    qs = [torch.randn((B, 1, Hkv, d), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(L)]
+    loc = [torch.randn((B, Hkv, Lloc, d), generator=gen, device="cuda", dtype=torch.bfloat16) for _ in range(L)]
+    dpos = torch.full((B, 1), k + Lloc - 1, dtype=torch.int32, device="cuda")
+    for overlap in (False, True):
+        stack.step(qs, loc, loc, k, dpos, [None] * L, [None] * L, overlap=overlap)
+        torch.cuda.synchronize()
+        for l in range(L):
+            idx, val = msa.msa_score_topk(cfg, qs[l], stack.KR[l], stack.inv[l], k)
+            torch.cuda.synchronize()
+            assert torch.equal(idx, stack.idx[l]) and torch.equal(val.view(torch.int32), stack.val[l].view(torch.int32))
+
+
 def test_refused_layer_leaves_nothing_behind():
     """A step with one layer that attention refuses raises before anything runs; the next step is whole, on one stream, on
     two, and without outputs that are not wanted."""
