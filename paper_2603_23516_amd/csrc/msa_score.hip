@@ -1167,9 +1167,11 @@ __global__ __launch_bounds__(64 * WAVES) void topk_rows_kernel(RowsArgs a) {
   }
 }
 
-// Streaming loads of the index: always beyond the 256 MB of cache behind the L2s (index cold / again and again, whole call, 8
-// queries: 20000 documents, 328 MB, 72.9 / 69.1 -> 65.7 / 64.5 us, 32768 110 / 106 -> 99 / 95.5), and from 128 MB on where a scan finds
-// its index cold: plain loads then spend their time on caching what nobody reads again.
+// Streaming loads of the index: always from 300 MB on, of which the 256 MB of cache behind the L2s keep nothing until it is read again
+// (index cold / again and again, whole call, 8 queries: 20000 documents, 328 MB, 73.3 / 69.0 -> 66.0 / 64.8 us, 32768 110 / 106 -> 99 /
+// 95.5; 16600, 272 MB, 63.3 / 54.5 -> 57.6 / 56.6, 18000, 295 MB, 67 / 57.3 -> 60.5 / 59.4; 50 tokens over all heads 16600 98.6 / 85 ->
+// 93.7 / 89.7, 20000 104.8 / 101.5 -> 99.2 / 96.5), and from 128 MB on where a scan finds its index cold: plain loads then spend their
+// time on caching what nobody reads again.
 //   The score-matrix scan gains 5 to 9 % on a cold index and loses 2 to 10 % on one that is read again and again (8 queries, 7400
 //   documents, 121 MB, 31.8 / 27.1 -> 30.0 / 28.7, 9000 39.7 / 33.9 -> 36.8 / 35.4, 13000 51.2 / 43.6 -> 47.0 / 45.6, 15600, 256 MB, 58.4
 //   / 51.0 -> 53.3 / 51.7; 32 queries over 13000 64.9 / 53.8 -> 59.6 / 59.3), so it has them in a step of layers whose indexes
@@ -1181,7 +1183,7 @@ __global__ __launch_bounds__(64 * WAVES) void topk_rows_kernel(RowsArgs a) {
 // 22.6, 6800, 111 MB, 29.9 / 25.8 -> 28.3 / 27.4); so it may for the second pass of a call.
 bool stream_index_of(const Dims& dm, bool cold) {
   const size_t bytes = (size_t)dm.Hkv * dm.tiles * 16 * dm.d * 2;
-  return bytes > kCacheBytes || (cold && bytes >= 128000000);
+  return bytes >= 300000000 || (cold && bytes >= 128000000);
 }
 
 // Scans of four query tiles fold in every wave, so nobody requests tiles meanwhile; a stream of more than a few tiles per wave then

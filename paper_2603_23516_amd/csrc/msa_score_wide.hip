@@ -296,7 +296,7 @@ __device__ __forceinline__ void wide_store_pooled(const WideArgs& a, const float
 
 // POOL: token pooling, the matrix holds the best score of a block's tokens.  STREAM: streaming loads of the keys, with pooling where
 // the scans have them too (stream_index_of; index cold / again and again, whole call, 150 tokens: 9000 documents 73.8 / 67.7 -> 71.9 /
-// 71.7 us, 15600 76.6 / 69.7 -> 74.6 / 73.7, 20000 97.0 / 95.3 -> 93.0 / 91.0), without beyond 256 MB only: below, nothing is gained
+// 71.7 us, 15600 76.6 / 69.7 -> 74.6 / 73.7, 20000 97.0 / 95.3 -> 93.0 / 91.0), without from 300 MB on only: below, little is gained
 // (9000 documents 82.2 / 75.4 -> 82.0 / 79.8, 13000 86.0 / 79.9 -> 85.5 / 83.9; 20000 113.5 / 109.8 -> 112.1 / 110.2, 70 tokens 99.1 /
 // 97.4 -> 96.3 / 93.6).
 template <int NT, bool POOL, bool STREAM>
@@ -1245,7 +1245,7 @@ int launch_score_wide(const Dims& dm, const WidePlan& pl, const void* q_route, i
       if (streams > most) streams = most;
       a.n_streams = streams;
       a.m_blocks = a.n_tb;
-      // Streaming loads where one token block reads the keys and the cache behind the L2s cannot hold them: 40 tokens, 97656
+      // Streaming loads where one token block reads the keys and the cache behind the L2s keeps none of them: 40 tokens, 97656
       // documents 357 -> 321 us, 64 over 20000 106 -> 101 (102.4 -> 98.1 again and again).  A smaller index gains nothing when it
       // is cold and loses when it is not (50 over 8000 56.8, 57.9; again and again 49.6, 56.2).
       const bool stream = a.n_tb == 1 && stream_index_of(dm, false);

@@ -197,10 +197,10 @@ def test_scoring_gemm_of_two_passes(N, Hkv, r, C, d, B, M, k, sim):
 
 
 # score-matrix scans at the edge between plain and streaming loads of the index (all heads: 128 MB; a scan per group, in one pass and
-# in two: 256 MB), tails of half a tile
+# in two: 300 MB), tails of half a tile
 STREAMED = [(7812, 8, 1, 8, 128, 1, 1, 9, "cos"), (7813, 8, 1, 8, 128, 9, 1, 9, "cos"), (7815, 8, 1, 8, 128, 2, 1, 16, "dot"),
-            (7813, 8, 2, 8, 128, 20, 1, 16, "cos"), (31253, 4, 1, 8, 64, 3, 1, 8, "cos"), (16387, 8, 1, 8, 128, 2, 1, 9, "cos"),
-            (16384, 8, 1, 8, 128, 33, 1, 9, "dot"), (16387, 8, 1, 8, 128, 33, 1, 9, "dot")]
+            (7813, 8, 2, 8, 128, 20, 1, 16, "cos"), (31253, 4, 1, 8, 64, 3, 1, 8, "cos"), (18311, 8, 1, 8, 128, 2, 1, 9, "cos"),
+            (18310, 8, 1, 8, 128, 33, 1, 9, "dot"), (18311, 8, 1, 8, 128, 33, 1, 9, "dot")]
 
 
 @pytest.mark.parametrize("scope", ["group", "all"])
@@ -271,8 +271,9 @@ def test_all_heads_wide_rows(N, Hkv, r, C, d, B, M, k, sim):
     test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim)
 
 
-# the same with streaming loads of the index, from 128 MB on; up to 64 tokens beyond 256 MB
-@pytest.mark.parametrize("N,M", [(7813, 40), (7813, 70), (7815, 100), (7814, 131), (7812, 150), (16384, 33), (16387, 64)])
+# the same with streaming loads of the index: pooled from 128 MB on, else from 300 MB on with one block of tokens
+@pytest.mark.parametrize("N,M", [(7813, 40), (7813, 70), (7815, 100), (7814, 131), (7812, 150), (16384, 33), (16387, 64), (18311, 33),
+                                 (18313, 64), (18312, 90)])
 def test_all_heads_wide_rows_with_streaming_loads(N, M):
     test_all_heads_scan(N, 8, 1, 8, 128, 1, M, 9, "cos")
 
