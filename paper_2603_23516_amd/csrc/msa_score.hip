@@ -1290,24 +1290,25 @@ __global__ __launch_bounds__(256) void score_merge_kernel(const unsigned long lo
     }
     exact = ties > kFewTies;
   }
+  auto kth_head = [&]() -> unsigned long long {  // the k-th best of the heads (0: fewer); a barrier inside
+    for (int i = tid; i < P; i += 256) {
+      const unsigned long long x = sub[i];
+      int rank = 0;
+      for (int j = 0; j < P; j += 8) {
+        unsigned long long y[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) y[u] = sub[j + u];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) rank += (y[u] > x) ? 1 : 0;
+      }
+      if (rank == k - 1 && x != 0ull) theta_s = x;  // keys are distinct, zeros are padding
+    }
+    __syncthreads();
+    return theta_s;
+  };
   int S;
   for (;;) {  // once or twice
-    if (exact) {
-      for (int i = tid; i < P; i += 256) {
-        const unsigned long long x = sub[i];
-        int rank = 0;
-        for (int j = 0; j < P; j += 8) {
-          unsigned long long y[8];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) y[u] = sub[j + u];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) rank += (y[u] > x) ? 1 : 0;
-        }
-        if (rank == k - 1 && x != 0ull) theta_s = x;  // keys are distinct, zeros are padding
-      }
-      __syncthreads();
-      theta = theta_s;
-    }
+    if (exact) theta = kth_head();
     if (n_lists * depth <= kMaxSub) {
       // The heads of all lists are in LDS already, and the lists are sorted: a list holds further survivors only if
       // the last entry seen of it is still >= theta, and then only as far as its entries stay >= theta.  After the
@@ -1351,6 +1352,20 @@ __global__ __launch_bounds__(256) void score_merge_kernel(const unsigned long lo
     S = n_surv;
     if (exact || S <= kFewSurv) break;  // block-uniform
     exact = true;
+    if (S <= kMaxSurv) {  // what survived is in LDS: no second walk
+      unsigned long long x[kMaxSurv / 256];
+#pragma unroll
+      for (int u = 0; u < kMaxSurv / 256; ++u) x[u] = u * 256 + tid < S ? surv[u * 256 + tid] : 0ull;
+      theta = kth_head();  // (a barrier inside)
+      if (tid == 0) n_surv = 0;
+      __syncthreads();
+#pragma unroll
+      for (int u = 0; u < kMaxSurv / 256; ++u)
+        if (x[u] != 0ull && x[u] >= theta) surv[atomicAdd(&n_surv, 1)] = x[u];
+      __syncthreads();
+      S = n_surv;
+      break;
+    }
     __syncthreads();
     if (tid == 0) n_surv = 0;
   }
