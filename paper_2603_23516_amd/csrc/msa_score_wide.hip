@@ -1075,6 +1075,10 @@ WidePoolPlan plan_score_wide_pool(const Dims& dm, const WidePlan& pl, int B, int
   // 40 tokens over 60000 documents 277 -> 348 us).
   if (B * p.m_blocks > (B * M + kWideRows - 1) / kWideRows) return p;
   p.nt = ((M + p.m_blocks - 1) / p.m_blocks + 31) / 32 * 2;
+  // Next to no documents: the launches are what counts, and the most rows in a workgroup the longest (k = 9, selection per token ->
+  // here: 5 documents, 60 tokens 31.1 -> 32.8 us, 10 36.8 -> 34.0; 148 tokens, one block of ten tiles, 26 38.1 -> 43.4, 64 42.8 -> 43.0;
+  // 300, two blocks, 10 44.9 -> 44.0).
+  if (dm.tiles < (p.m_blocks == 1 && p.nt > 6 ? 32 : 5)) return p;
   p.m_tiles = (M + 15) / 16;
   p.part_docs = (dm.N + kPoolParts - 1) / kPoolParts;
   p.n_parts = (dm.N + p.part_docs - 1) / p.part_docs;
@@ -1176,10 +1180,11 @@ int launch_score_wide_pool(const Dims& dm, const WidePoolPlan& pp, const void* q
 //   six tiles of rows: as fast in a round at any size (8300 documents 76 / 64 -> 71 / 63, 10500 79 / 69 -> 74 / 69, 21500 111 / 106 -> 101);
 //   eight: faster in one round (2000 50 / 42 -> 46 / 42, 8100 56 / 50 -> 55 / 51), then slower (8300 77 / 65 -> 78 / 69, 13000 82 / 73
 //   -> 82 / 76) until the index is too large for the cache (19000 107 / 101 -> 105 / 103, 21500 111 / 107 -> 107 / 105);
+//   next to no documents: slower (96 tokens, 26 documents 31.6 -> 33.1, 64 36.1 -> 33.2; 128 31.8 -> 36.3, 36.2 -> 36.5);
 //   ten: faster with a round less (5600 68 / 58 -> 53 / 49, 11300 95 / 78 -> 82 / 77, 16800 115 / 105 -> 110 / 108), else not (300
 //   documents 42 -> 45, 5300 52 / 47 -> 52 / 48, 8300 75 / 66 -> 83 / 75).
 static bool rows_kernel_pays(int nq, int seg_tiles) {
-  if (nq <= kWideRows || nq > 16 * kRowsMost) return false;
+  if (nq <= kWideRows || nq > 16 * kRowsMost || seg_tiles < 32) return false;
   const int blocks = (nq + kWideRows - 1) / kWideRows, waves = kWideGroups / blocks * kWideWaves;
   const int rounds = ((seg_tiles + kWideTiles - 1) / kWideTiles + waves - 1) / waves;
   const int rows_waves = kWideGroups * kRowsWaves;

@@ -256,7 +256,7 @@ def test_all_heads_wide(N, Hkv, r, C, d, B, M, k, sim):
 
 
 # the same at the edges of the kernel that reads a key once for 65 to 160 rows: numbers of row tiles, units that end inside a
-# wave's keys, fewer documents than a workgroup has waves
+# wave's keys, from 64 documents on
 ALL_ROWS = [(37, 8, 1, 8, 128, 1, 64, 9, "cos"), (37, 8, 1, 8, 128, 1, 65, 9, "cos"), (1003, 8, 2, 8, 128, 1, 96, 16, "cos"),
             (2051, 8, 4, 8, 128, 1, 97, 32, "cos"), (5, 8, 1, 8, 128, 2, 64, 5, "cos"), (520, 8, 4, 8, 128, 3, 53, 12, "cos"),
             (999, 8, 1, 8, 128, 1, 129, 16, "cos"), (4100, 8, 2, 8, 128, 1, 160, 8, "cos"), (300, 8, 1, 8, 128, 1, 161, 8, "cos"),
@@ -281,11 +281,34 @@ def test_all_heads_wide_rows_with_streaming_loads(N, M):
 # tokens pooled by document: one token more than the scan takes, several blocks of tokens, batch rows, parts of one document
 POOL_DOCS = [(700, 2, 2, 8, 128, 1, 33, 20, "cos"), (1030, 4, 1, 8, 128, 2, 100, 9, "cos"), (64, 4, 2, 8, 128, 1, 330, 64, "cos"),
              (515, 2, 1, 8, 128, 1, 1000, 5, "cos"), (2600, 8, 1, 8, 128, 4, 66, 33, "cos"), (40, 8, 1, 8, 128, 1, 40, 40, "cos"),
-             (5, 2, 1, 8, 128, 1, 49, 1, "cos")]
+             (9, 8, 1, 8, 128, 1, 64, 9, "cos"), (64, 8, 1, 8, 128, 1, 150, 3, "cos")]
+# ... and just not: too few documents, more blocks than those of 64 tokens, a token too many
+POOL_TOKENS = [(5, 2, 1, 8, 128, 1, 49, 1, "cos"), (8, 8, 1, 8, 128, 1, 64, 8, "cos"), (62, 8, 1, 8, 128, 1, 150, 3, "cos"),
+               (300, 4, 1, 8, 128, 3, 40, 5, "cos"), (300, 2, 1, 8, 128, 1, 1025, 4, "cos")]
 
 
-@pytest.mark.parametrize("N,Hkv,r,C,d,B,M,k,sim", POOL_DOCS)
+def pooled_by_document(N, Hkv, B, M, k):
+    """Whether the tokens of an all-heads call (cosine, d = 128, C = 8) are pooled by document: few enough blocks of tokens, enough
+    documents, and buffers that fit where those of a selection per token lie."""
+    d, up = 128, lambda b: (b + 255) // 256 * 256
+    blocks, tiles = (M + 159) // 160, (N + 1) // 2
+    if M <= 32 or B * M > 1024 or B * blocks > (B * M + 63) // 64:
+        return False
+    if tiles < (32 if blocks == 1 and M > 96 else 5):
+        return False
+    seg = -(-N // -(-N // max(64, 5 * 2**20 // (B * M))))
+    common = up(B * M * Hkv * d * 4) + up(B * M * Hkv * 4)
+    per_token = up(Hkv * -(-B * M // 64) * 4 * d * 32) + up(B * M * k * 8) + up(B * M * min(N, (seg + 63) // 64 * 64) * 4)
+    by_doc = (up(Hkv * B * -(-M // 16) * d * 32) + up(B * blocks * N * 4) + up(B * 512 * 4) + 2 * up(B * 4) + up(B * N * 4) +
+              up(B * N * 8))
+    assert msa.score_topk_workspace_bytes(msa.MsaConfig(N, 64, 8, Hkv, Hkv, d, 1e6, select_scope=msa.MSA_SCOPE_ALL, token_pool=1),
+                                          B, M, k) >= common + per_token
+    return by_doc <= per_token
+
+
+@pytest.mark.parametrize("N,Hkv,r,C,d,B,M,k,sim", POOL_DOCS + POOL_TOKENS)
 def test_token_pooling_by_document(N, Hkv, r, C, d, B, M, k, sim):
+    assert pooled_by_document(N, Hkv, B, M, k) == ((N, Hkv, r, C, d, B, M, k, sim) in POOL_DOCS)
     test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim)
 
 
@@ -347,7 +370,9 @@ ALL_TIED = [
     (40007, 2, 1, 64, 2, 1, 33, "all", 0),        # rows in parts, the last of 7239 documents
     (70001, 2, 1, 64, 1, 40, 33, "all", 0),       # wide kernel, scores of hi and lo parts
     (9001, 8, 8, 128, 1, 50, 20, "all", 0),       # ... and behind the one-pass filter
-    (30011, 2, 8, 128, 1, 400, 9, "all", 1),      # three segments, pooled
+    (30011, 2, 8, 128, 1, 400, 9, "all", 1),      # pooled by document
+    (30011, 2, 8, 128, 1, 1100, 9, "all", 1),     # two passes of tokens, a selection per token in segments, pooled from those
+    (30011, 4, 8, 128, 3, 40, 9, "all", 1),       # blocks of tokens more than the rows: the same in one pass
 ]
 
 
