@@ -1079,6 +1079,10 @@ WidePoolPlan plan_score_wide_pool(const Dims& dm, const WidePlan& pl, int B, int
   // here: 5 documents, 60 tokens 31.1 -> 32.8 us, 10 36.8 -> 34.0; 148 tokens, one block of ten tiles, 26 38.1 -> 43.4, 64 42.8 -> 43.0;
   // 300, two blocks, 10 44.9 -> 44.0).
   if (dm.tiles < (p.m_blocks == 1 && p.nt > 6 ? 32 : 5)) return p;
+  // ... and for few winners, whose selection per token is short, that longest workgroup counts up to 2000 documents (148 tokens, index
+  // again and again: k = 2, 500 documents 38.8 -> 41.4 us, 2000 39.6 -> 42.8, cold the same; k = 9 44.2 -> 45.2, 45.4 -> 44.8; k = 32
+  // over 300 60 -> 50).
+  if (p.m_blocks == 1 && p.nt > 8 && k < 16 && dm.tiles < 1000) return p;
   p.m_tiles = (M + 15) / 16;
   p.part_docs = (dm.N + kPoolParts - 1) / kPoolParts;
   p.n_parts = (dm.N + p.part_docs - 1) / p.part_docs;

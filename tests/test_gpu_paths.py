@@ -281,9 +281,11 @@ def test_all_heads_wide_rows_with_streaming_loads(N, M):
 # tokens pooled by document: one token more than the scan takes, several blocks of tokens, batch rows, parts of one document
 POOL_DOCS = [(700, 2, 2, 8, 128, 1, 33, 20, "cos"), (1030, 4, 1, 8, 128, 2, 100, 9, "cos"), (64, 4, 2, 8, 128, 1, 330, 64, "cos"),
              (515, 2, 1, 8, 128, 1, 1000, 5, "cos"), (2600, 8, 1, 8, 128, 4, 66, 33, "cos"), (40, 8, 1, 8, 128, 1, 40, 40, "cos"),
-             (9, 8, 1, 8, 128, 1, 64, 9, "cos"), (64, 8, 1, 8, 128, 1, 150, 3, "cos")]
+             (9, 8, 1, 8, 128, 1, 64, 9, "cos"), (64, 8, 1, 8, 128, 1, 150, 16, "cos"),
+             (1999, 8, 1, 8, 128, 1, 130, 3, "cos")]
 # ... and just not: too few documents, more blocks than those of 64 tokens, a token too many
-POOL_TOKENS = [(5, 2, 1, 8, 128, 1, 49, 1, "cos"), (8, 8, 1, 8, 128, 1, 64, 8, "cos"), (62, 8, 1, 8, 128, 1, 150, 3, "cos"),
+POOL_TOKENS = [(5, 2, 1, 8, 128, 1, 49, 1, "cos"), (8, 8, 1, 8, 128, 1, 64, 8, "cos"), (62, 8, 1, 8, 128, 1, 150, 16, "cos"),
+               (1998, 8, 1, 8, 128, 1, 130, 3, "cos"),
                (300, 4, 1, 8, 128, 3, 40, 5, "cos"), (300, 2, 1, 8, 128, 1, 1025, 4, "cos")]
 
 
@@ -294,7 +296,7 @@ def pooled_by_document(N, Hkv, B, M, k):
     blocks, tiles = (M + 159) // 160, (N + 1) // 2
     if M <= 32 or B * M > 1024 or B * blocks > (B * M + 63) // 64:
         return False
-    if tiles < (32 if blocks == 1 and M > 96 else 5):
+    if tiles < (32 if blocks == 1 and M > 96 else 5) or (128 < M <= 160 and k < 16 and tiles < 1000):
         return False
     seg = -(-N // -(-N // max(64, 5 * 2**20 // (B * M))))
     common = up(B * M * Hkv * d * 4) + up(B * M * Hkv * 4)
