@@ -42,6 +42,44 @@ MEASURED_TRAFFIC = {     # measured at commit f514938
 }
 
 
+def mfma_scoring(wl, all_heads, pool, B, M, k):
+    """The matrix-core scoring path that msa_score_topk takes for these sizes (cosine), as (what runs, hi parts only); None:
+    a scan.  The lines are the library's."""
+    nq, cdiv = B * M, lambda a, b: -(-a // b)
+    one_pass = wl.d == 128 and wl.C == 8
+    tiles = cdiv(wl.N * wl.C, 16)
+    if all_heads:
+        if nq <= 32:
+            return None
+        hi = " on the hi parts of the queries" if one_pass else ""
+        blocks = cdiv(M, 160)
+        if (pool and one_pass and 32 < M <= 1024 >= nq and B * blocks <= cdiv(nq, 64) and
+                tiles >= (32 if blocks == 1 and M > 96 else 5) and not (128 < M <= 160 and k < 16 and tiles < 1000)):
+            return "score_wide_rows_kernel" + hi + " (inside msa_score_topk = fold + it + pooled selection by document)", True
+        seg = cdiv(cdiv(wl.N, cdiv(wl.N, max(64, 5 * 2**20 // min(nq, 1024)))), 64) * 64
+        seg_tiles = cdiv(min(seg, wl.N) * wl.C, 16)
+        rows_rounds = cdiv(cdiv(seg_tiles, 2), 2048)
+        rows = one_pass and wl.Hkv == 8 and 64 < nq <= 160 and seg_tiles >= 32 and (
+            nq <= 96 or (rows_rounds == 1 or seg_tiles >= 10000 if nq <= 128 else
+                         rows_rounds < cdiv(cdiv(seg_tiles, 4), 256 // cdiv(nq, 64) * 8)))
+        return (("score_wide_rows_kernel" if rows else "score_wide_kernel") + hi +
+                " (inside msa_score_topk = fold + it and the selection per segment of the bank)", one_pass)
+    two_passes = one_pass and 32 < nq < 64 and k <= 32 and (
+        wl.Hkv == 8 and wl.N * wl.C >= (64000 if k <= 16 else 320000) or
+        wl.Hkv == 4 and k <= 16 and wl.N * wl.C >= 320000)
+    gemm = wl.C in (4, 8, 16) and nq >= 64 and (k <= 16 or k <= 32 and cdiv(nq, 32 if k <= 24 else 16) - (2 if one_pass else 4) >=
+                                                cdiv(500000 if one_pass else 1250000, 100000 + wl.N * wl.C * wl.Hkv * wl.d // 128))
+    if not (two_passes or gemm):
+        return None
+    tb = 2 if nq > 128 and k <= 8 else 1
+    splits = max(512 // (wl.Hkv * cdiv(nq, 128 * tb)), 4 if k > 16 else 1)
+    splits = max(1, min(splits, cdiv(cdiv(tiles, 4), 8), 32 if k > 16 else 64))
+    hi_only = gemm and one_pass and 2 * splits * (8 if k <= 8 else 16) <= 1024 and (k <= 16 or 8 * splits >= k)
+    return ("score_gemm_kernel" + (" on the hi parts of the queries (inside msa_score_topk = fold + one-pass GEMM + candidates and "
+                                   "exact scores + gated two-pass GEMM and merge)" if hi_only else
+                                   " (inside msa_score_topk = fold + GEMM + merge)"), hi_only)
+
+
 def parse():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -471,27 +509,16 @@ def main():
     attend_gbs = ab["attend"] / (attend_ms * 1e-3) / 1e9
     build_gbs = ab["build"] / (build_ms * 1e-3) / 1e9
 
-    # the MFMA paths (many query tokens): the wide kernel from 33 tokens on with one selection for all heads, else the
-    # scoring GEMM from 64 tokens on (k = 17..32: from 544 on at the latest).  Algorithmic flops: the folded form of Eq. 2,
-    # one routing query per (token, KV group): 2 * tokens * Hkv * keys * d.  Issued: twice that where the query travels as a
-    # bf16 (hi, lo) pair, once where the product runs on the hi parts alone and the few candidates inside the error band are
-    # scored again exactly (cosine, d = 128, eight chunks per document)
+    # the MFMA paths (many query tokens).  Algorithmic flops: the folded form of Eq. 2, one routing query per (token, KV group):
+    # 2 * tokens * Hkv * keys * d.  Issued: twice that where the query travels as a bf16 (hi, lo) pair, once where the product
+    # runs on the hi parts alone and the few candidates inside the error band are scored again exactly
     flops = flops_issued = None
-    one_pass = wl.d == 128 and wl.C == 8
-    wide = args.scope == "all" and wl.Hkv > 1 and nq > 32
-    gemm = not (args.scope == "all" and wl.Hkv > 1) and wl.C in (4, 8, 16) and (
-        (nq >= 64 and k <= 16) or (nq >= 544 and k <= 32))
-    if wide or gemm:
+    path = mfma_scoring(wl, args.scope == "all" and wl.Hkv > 1, args.token_pool, B, M, k)
+    if path is not None:
+        mfma_kernel, hi_only = path
         tiles = (wl.N * wl.C + 15) // 16
         flops = 2.0 * nq * wl.Hkv * wl.N * wl.C * wl.d
-        flops_issued = 2.0 * nq * wl.Hkv * tiles * 16 * (1 if one_pass else 2) * wl.d
-    if wide:
-        mfma_kernel = ("score_wide_kernel" + (" on the hi parts of the queries" if one_pass else "") +
-                       " (inside msa_score_topk = fold + wide kernel and selection per segment of the bank)")
-    else:
-        mfma_kernel = ("score_gemm_kernel" +
-                       (" on the hi parts of the queries (inside msa_score_topk = fold + one-pass GEMM + candidates and exact "
-                        "scores + gated two-pass GEMM and merge)" if one_pass else " (inside msa_score_topk = fold + GEMM + merge)"))
+        flops_issued = 2.0 * nq * wl.Hkv * tiles * 16 * (1 if hi_only else 2) * wl.d
     # shared selection and many tokens: attention is a dense contraction on the matrix cores.  Algorithmic flops: two
     # products (QK, PV) of 2 flops per multiply-add over the keys each token sees; issued: twice that (bf16 (hi, lo) pairs
     # of Q and P)
