@@ -868,8 +868,8 @@ __global__ __launch_bounds__(256) void pool_cand_kernel(WidePoolArgs a) {
 // A workgroup takes kPoolTok tokens and four candidates, one per wave: the folded queries of the tokens lie in LDS, the keys of a
 // candidate, already fp32, in registers (lane: 16 dims of a chunk's key of every group).  A candidate passes over the blocks of
 // tokens whose best matrix score is too far below its best to hold its exact best.  Bound by latency and the reads of the
-// queries: with eight tokens of one candidate per wave and the queries from memory it took 37 us of the call below and 82 of
-// 1000 tokens over 2000 documents, now 18 and 30.
+// queries: with eight tokens of one candidate per wave and the queries from memory it took 37 us of the call of 150 tokens above
+// and 82 of 1000 tokens over 2000 documents, now 18 and 30.
 template <int HKV>
 __global__ __launch_bounds__(256) void pool_score_kernel(WidePoolArgs a) {
   constexpr int D = 128, C = 8;
@@ -1166,7 +1166,7 @@ int launch_score_wide_pool(const Dims& dm, const WidePoolPlan& pp, const void* q
   const unsigned quads = (unsigned)((pp.n_parts + 3) / 4);
   hipLaunchKernelGGL(pool_parts_kernel, dim3(quads + 1, (unsigned)B), dim3(256), 0, st, p);
   hipLaunchKernelGGL(pool_cand_kernel, dim3(quads, (unsigned)B), dim3(256), 0, st, p);
-  const dim3 sgrid(512, (unsigned)B);  // (about 100 candidates and 20 chunks of tokens)
+  const dim3 sgrid(512, (unsigned)B);  // (150 tokens, about 100 candidates: 25 quads and 38 chunks of tokens, two items each)
   if (dm.Hkv == 2) hipLaunchKernelGGL(pool_score_kernel<2>, sgrid, dim3(256), 0, st, p);
   else if (dm.Hkv == 4) hipLaunchKernelGGL(pool_score_kernel<4>, sgrid, dim3(256), 0, st, p);
   else hipLaunchKernelGGL(pool_score_kernel<8>, sgrid, dim3(256), 0, st, p);
