@@ -1,4 +1,4 @@
-// msa_score_topk for MANY query tokens (prefill routing, B*M >= 64): the relevance scores of Eq. 2
+// msa_score_topk for MANY query tokens (prefill routing, B*M >= 64; 33 to 63 over a large bank): the relevance scores of Eq. 2
 // (paper, Section 3.2.1) as a real GEMM on the matrix cores, with the document max and a per-query
 // top-k fused into the epilogue so that scores never reach memory.  This is the one place on the
 // path that is MFMA-bound: 2 * (B*M) * Hkv * (N*C) * 2d flops (the factor 2d: the folded fp32 query is
