@@ -282,11 +282,18 @@ def test_all_heads_wide_rows_with_streaming_loads(N, M):
 # tokens pooled by document: one token more than the scan takes, several blocks of tokens, batch rows, parts of one document
 POOL_DOCS = [(700, 2, 2, 8, 128, 1, 33, 20, "cos"), (1030, 4, 1, 8, 128, 2, 100, 9, "cos"), (64, 4, 2, 8, 128, 1, 330, 64, "cos"),
              (515, 2, 1, 8, 128, 1, 1000, 5, "cos"), (2600, 8, 1, 8, 128, 4, 66, 33, "cos"), (40, 8, 1, 8, 128, 1, 40, 40, "cos"),
-             (9, 8, 1, 8, 128, 1, 64, 9, "cos"), (64, 8, 1, 8, 128, 1, 150, 16, "cos"),
-             (1999, 8, 1, 8, 128, 1, 130, 3, "cos")]
+             (5, 2, 1, 8, 128, 1, 49, 1, "cos")]
+
+
+@pytest.mark.parametrize("N,Hkv,r,C,d,B,M,k,sim", POOL_DOCS)
+def test_token_pooling_by_document(N, Hkv, r, C, d, B, M, k, sim):
+    test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim)
+
+
+# the edges of the rule: the fewest documents that are pooled by document
+POOL_DOCS_LEAST = [(9, 8, 1, 8, 128, 1, 64, 9, "cos"), (64, 8, 1, 8, 128, 1, 150, 16, "cos"), (1999, 8, 1, 8, 128, 1, 130, 3, "cos")]
 # ... and just not: too few documents, more blocks than those of 64 tokens, a token too many
-POOL_TOKENS = [(5, 2, 1, 8, 128, 1, 49, 1, "cos"), (8, 8, 1, 8, 128, 1, 64, 8, "cos"), (62, 8, 1, 8, 128, 1, 150, 16, "cos"),
-               (1998, 8, 1, 8, 128, 1, 130, 3, "cos"),
+POOL_TOKENS = [(8, 8, 1, 8, 128, 1, 64, 8, "cos"), (62, 8, 1, 8, 128, 1, 150, 16, "cos"), (1998, 8, 1, 8, 128, 1, 130, 3, "cos"),
                (300, 4, 1, 8, 128, 3, 40, 5, "cos"), (300, 2, 1, 8, 128, 1, 1025, 4, "cos")]
 
 
@@ -309,9 +316,10 @@ def pooled_by_document(N, Hkv, B, M, k):
     return by_doc <= per_token
 
 
-@pytest.mark.parametrize("N,Hkv,r,C,d,B,M,k,sim", POOL_DOCS + POOL_TOKENS)
-def test_token_pooling_by_document(N, Hkv, r, C, d, B, M, k, sim):
-    assert pooled_by_document(N, Hkv, B, M, k) == ((N, Hkv, r, C, d, B, M, k, sim) in POOL_DOCS)
+@pytest.mark.parametrize("N,Hkv,r,C,d,B,M,k,sim", POOL_DOCS_LEAST + POOL_TOKENS)
+def test_token_pooling_at_the_edges_of_its_rule(N, Hkv, r, C, d, B, M, k, sim):
+    assert all(pooled_by_document(n, h, b, m, kk) == (n > 5) for n, h, _, _, _, b, m, kk, _ in POOL_DOCS)
+    assert pooled_by_document(N, Hkv, B, M, k) == ((N, Hkv, r, C, d, B, M, k, sim) in POOL_DOCS_LEAST)
     test_all_heads_scan(N, Hkv, r, C, d, B, M, k, sim)
 
 
