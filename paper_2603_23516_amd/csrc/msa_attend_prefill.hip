@@ -536,9 +536,13 @@ int launch_attend_prefill_partial(const Dims& dm, const AttendPlan& pl, const At
                                   const RopeTheta& th, int B, hipStream_t st, bool dominant) {
   if (a.Krot == nullptr) return MSA_ERR_INVALID_ARG;  // the plan always reserves the rotated keys
   {
-    // heads per workgroup: as many as leave two workgroups per CU
+    // heads per workgroup: as many as leave two workgroups per CU.  With 64 dims the angles are half the work, and fewer than eight
+    // heads lose to one each, as do steps that lie past the end of their documents (per head -> several, again and again / cold:
+    // whole calls of two heads 1.6 / 4.2 % slower, of four with 8 KV heads 0.2 to 1.4 / 3 to 4.5 %, of eight 4 / 1.7 % faster,
+    // with documents of different lengths 0.5 % faster / 2 to 4 % slower).
     int heads = 1;
     while (heads < dm.Hkv && (long long)a.steps_total * B * dm.Hkv >= 512ll * 2 * heads) heads *= 2;
+    if (dm.d == 64 && (heads < 8 || a.lens != nullptr)) heads = 1;
     dim3 rgrid(a.steps_total, (dm.Hkv + heads - 1) / heads, B);
 #define MSA_ROTATE(DD, MM) \
   hipLaunchKernelGGL((rotate_steps_kernel<DD, MM>), rgrid, dim3(256), 0, st, a, th, const_cast<uint16_t*>(a.Krot), heads)

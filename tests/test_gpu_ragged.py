@@ -269,6 +269,25 @@ def test_ragged_full_lengths_are_the_uniform_bank():
         assert torch.equal(a, b)
 
 
+# steps of a shared selection whose rotation takes eight heads at a time, four, two and one (512 steps of 8 heads: eight)
+@pytest.mark.parametrize("d,Hkv,k,ragged", [(64, 8, 32, False), (64, 8, 32, True), (64, 8, 31, False), (64, 4, 33, False), (64, 4, 64, False),
+                                            (128, 8, 32, True), (128, 4, 33, True), (128, 2, 33, False)])
+def test_shared_selection_rotated_for_several_heads(d, Hkv, k, ragged):
+    N, r, G, M, Lloc, base, pos0 = 65, 1, 512, 9, 17, 1e4, 512
+    say(f"shared selection d={d} Hkv={Hkv} k={k} ragged={ragged}")
+    case = Case(88000 + k, N, Hkv, r, G, d, 64, 1, M, Lloc, base).to_device()
+    lens = make_lens(88001, N, G, 64) if ragged else None
+    cfg = case.cfg(token_pool=1, doc_lens=torch.from_numpy(lens.astype(np.int32)).cuda() if ragged else None)
+    rng = np.random.default_rng(88002)
+    sel = np.stack([rng.permutation(N)[:k] for _ in range(Hkv)]).reshape(1, 1, Hkv, k)
+    sel[0, 0, 0, 1] = -1
+    q_pos = pos0 + np.arange(M)[None]
+    out, lse = msa.msa_sparse_attend(cfg, case.dq, case.dK, case.dV, torch.from_numpy(sel.astype(np.int32)).cuda(), case.dKl, case.dVl,
+                                     pos0, torch.from_numpy(q_pos.astype(np.int32)).cuda())
+    torch.cuda.synchronize()
+    attend_err(out, lse, *O.sparse_attend(case.q, case.K, case.V, sel, case.Kl, case.Vl, pos0, q_pos, base, lens=lens))
+
+
 def test_ragged_fetch_from_host_bank():
     """Tiered bank with lengths: only the rows a document holds travel, the staging bank carries the
     lengths, and attention over it equals attention over the device bank bit for bit."""
