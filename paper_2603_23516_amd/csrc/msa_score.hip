@@ -1179,6 +1179,9 @@ __global__ __launch_bounds__(64 * WAVES) void topk_rows_kernel(RowsArgs a) {
 //   the indexes were written 692 -> 675, in its spread) and plain loads in a call of its own.
 //   The all-heads scan loses next to nothing (24 queries, 7900 documents 36.1 / 31.8 -> 33.8 / 31.6, 11000 49.1 / 42.6 -> 44.9 / 42.6,
 //   13000 55.2 / 47.0 -> 50.3 / 48.5, 15600 62.6 / 54.0 -> 56.1 / 54.2; 22000 of 64 dims 51.1 / 42.4 -> 45.8 / 44.4).
+//   It has them there but for more than eight queries of one or two chunks per document, which gained 2 to 7 % cold and lost 4 to 12 %
+//   warm (13 queries over 79101 documents of one chunk, 8 heads of 128 dims, 50.1 / 42.8 -> 47.9 / 44.8; 26 over 52734 of two 67.6 /
+//   56.1 -> 63.1 / 59.6; 957 drawn calls 0.97 / 1.08 times).
 // Below 128 MB an index may well be in the cache still when it is read again (5000 documents, 82 MB, 8 queries 24.6 / 21.5 -> 23.7 /
 // 22.6, 6800, 111 MB, 29.9 / 25.8 -> 28.3 / 27.4); so it may for the second pass of a call.
 bool stream_index_of(const Dims& dm, bool cold) {
@@ -1741,7 +1744,8 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
                          dm.r, dm.cos, pl.n_qtiles, a.gmax, n_gmax);
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
   }
-  const bool stream_index = stream_index_of(dm, pl.n_pass == 1 && (pl.all_heads || dm.cold_index));
+  const bool cold = dm.cold_index || (pl.all_heads && (dm.C >= 4 || BM <= 8));
+  const bool stream_index = stream_index_of(dm, pl.n_pass == 1 && cold);
   RowsArgs ra;
   ra.mat = (const float*)((char*)ws + pl.off_mat);
   ra.BM = BM;

@@ -210,6 +210,12 @@ def test_scans_with_streaming_loads(N, Hkv, r, C, d, B, M, k, sim, scope):
     (test_all_heads_scan if scope == "all" else test_prefill_scoring_k_above_16)(N, Hkv, r, C, d, B, M, k, sim)
 
 
+# all heads over 128 MB of documents of one and two chunks: streaming loads up to eight queries, plain ones for more; four chunks
+@pytest.mark.parametrize("N,C,B", [(62501, 1, 8), (62501, 1, 9), (31253, 2, 17), (15627, 4, 9)])
+def test_all_heads_scan_loads_of_short_documents(N, C, B):
+    test_all_heads_scan(N, 8, 1, C, 128, B, 1, 9, "cos")
+
+
 @pytest.mark.parametrize("M", [250, 700, 2000])
 def test_token_pooling_of_many_documents(M):
     """One query head: the tokens' scores are alike and most of their listed documents reach the floor: 1300 and about
