@@ -684,11 +684,12 @@ constexpr int kAllGroups = 256;  // workgroups: one per CU
 // same; 16 of 4 groups 3000 14.0 -> 14.3, 7000 19.6 -> 18.6; 10 of 4 groups, 80 KiB, 2048 13.7 -> 12.5, 4500 16.4 -> 15.9); from
 // kAllFoldTilesIdx tiles of all heads on, 49 MB, they fold more too.
 constexpr int kAllFoldTiles = 8;
-constexpr long long kAllFoldElems = 45056, kAllFoldTilesIdx = 12000;
+// (Eight groups, where every wave folds: less than 80 KiB; five queries of 64 heads 13.4 -> 14.2 us, four 13.2 -> 12.3.)
+constexpr long long kAllFoldElems = 45056, kAllFoldElems8 = 40959, kAllFoldTilesIdx = 12000;
 
 static bool all_heads_folds(const Dims& dm, const ScorePlan& pl, int BM) {
   return pl.q_per_pass / 8 * dm.Hkv <= kAllFoldTiles &&
-         ((long long)BM * dm.Hq * dm.d <= kAllFoldElems || (long long)dm.Hkv * dm.tiles >= kAllFoldTilesIdx);
+         ((long long)BM * dm.Hq * dm.d <= (dm.Hkv == 8 ? kAllFoldElems8 : kAllFoldElems) || (long long)dm.Hkv * dm.tiles >= kAllFoldTilesIdx);
 }
 
 // log2(tiles per unit): the unit that keeps the longest stream shortest (whole units per wave), of equals the largest

@@ -113,6 +113,8 @@ ALL_FOLDED = [
     (97, 4, 8, 8, 128, 11, 1, 16, "cos"),     # as many queries as are folded over any index
     (97, 4, 8, 8, 128, 12, 1, 16, "cos"),     # prepared: more of them ...
     (97, 8, 8, 8, 128, 8, 1, 16, "dot"),
+    (97, 8, 8, 8, 128, 5, 1, 16, "dot"),      # prepared with eight groups, where four queries are folded
+    (97, 8, 8, 8, 128, 4, 1, 16, "dot"),
     (3000, 4, 8, 16, 128, 16, 1, 16, "cos"),  # ... but over an index of 12000 tiles
     (2999, 4, 8, 16, 128, 16, 1, 16, "cos"),
     (70000, 2, 2, 2, 64, 2, 4, 20, "cos"),    # parts of rows
