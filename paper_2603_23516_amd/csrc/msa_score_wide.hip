@@ -773,6 +773,9 @@ struct WidePoolArgs {
   long long tiles;
 };
 
+// ranks below every number
+__device__ __forceinline__ float not_a_number() { return __uint_as_float(0xffc00000u); }
+
 __device__ __forceinline__ float pooled_of(const WidePoolArgs& a, int b, int doc) {
   const float* p = a.mat + (long long)b * a.m_blocks * a.N + doc;
   float x = p[0];
@@ -786,12 +789,14 @@ __global__ __launch_bounds__(256) void pool_parts_kernel(WidePoolArgs a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int b = blockIdx.y;
   float best = -INFINITY;
+  bool listed = false;  // a token that is not a number and lists documents all the same, as a selection per token has it
   if (blockIdx.x == gridDim.x - 1) {  // block-uniform
     best = 0.f;
     for (int m = tid; m < a.M; m += 256) {
       float e = 0.f;
       for (int g = 0; g < a.Hkv; ++g) e += a.eps[((long long)b * a.M + m) * a.Hkv + g];
       best = fmaxf(best, e / (float)a.Hkv);
+      listed = listed || (e != e && __float_as_int(e) < 0);
     }
   } else {
     const int part = blockIdx.x * 4 + wave;
@@ -802,9 +807,10 @@ __global__ __launch_bounds__(256) void pool_parts_kernel(WidePoolArgs a) {
   for (int off = 32; off > 0; off >>= 1) best = fmaxf(best, __shfl_xor(best, off, 64));
   if (blockIdx.x == gridDim.x - 1) {
     if (lane == 0) red[wave] = best;
-    __syncthreads();
+    const bool any = __syncthreads_or(listed);
     if (tid == 0) {
-      a.band[b] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+      best = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+      a.band[b] = best == 0.f && any ? -0.f : best;
       a.cnt[b] = 0;
     }
   } else if (lane == 0 && blockIdx.x * 4 + wave < a.n_parts) {
@@ -828,8 +834,11 @@ __global__ __launch_bounds__(256) void pool_cand_kernel(WidePoolArgs a) {
   const uint32_t theta = kth_best_bound<4>(ob, a.k, theta_w);
   const uint32_t lim = theta ? orderable(unorderable(theta) - 2.f * band) : 0u;
   const int d0 = blockIdx.x * 4 * a.part_docs, d1 = d0 + 4 * a.part_docs < a.N ? d0 + 4 * a.part_docs : a.N;
+  // A question without a score that is a number selects the first k documents if one of its tokens does, else nothing.
+  const bool nothing = theta <= orderable(-INFINITY) && !__syncthreads_or(ob > orderable(-INFINITY));  // (theta: block-uniform)
+  const bool first_docs = band > 0.f || __float_as_int(band) < 0;  // -0
   int ties = 0;  // documents so far that tie with the limit or are above it, at least
-  if (band == 0.f) {  // block-uniform: one in every earlier part that reaches the limit
+  if (band == 0.f && !nothing) {  // block-uniform: one in every earlier part that reaches the limit
     int n = 0;
 #pragma unroll
     for (int i = 0; i < kPoolParts / 256; ++i)
@@ -842,8 +851,8 @@ __global__ __launch_bounds__(256) void pool_cand_kernel(WidePoolArgs a) {
     const int d = i0 + tid;
     const float x = d < d1 ? pooled_of(a, b, d) : -INFINITY;
     const uint32_t o = orderable(x);
-    bool take = x > -INFINITY && o >= lim;  // (a score that is not a number selects nothing)
-    if (band == 0.f) {  // block-uniform: the scores are exact; documents that tie with the limit in their order
+    bool take = d < d1 && (nothing ? first_docs && d < a.k : o >= lim);
+    if (band == 0.f && !nothing) {  // block-uniform: the scores are exact; documents that tie with the limit in their order
       const bool tie = d < d1 && o == lim;
       const unsigned long long m = __ballot(tie);
       __syncthreads();
@@ -860,7 +869,7 @@ __global__ __launch_bounds__(256) void pool_cand_kernel(WidePoolArgs a) {
     if (take) {
       const int slot = atomicAdd(&a.cnt[b], 1);
       a.cand[(long long)b * a.N + slot] = d;
-      a.keys[(long long)b * a.N + slot] = band == 0.f ? make_key(x, (uint32_t)d) : 0ull;
+      a.keys[(long long)b * a.N + slot] = band == 0.f ? make_key(nothing ? not_a_number() : x, (uint32_t)d) : 0ull;
     }
   }
 }
@@ -926,7 +935,7 @@ __global__ __launch_bounds__(256) void pool_score_kernel(WidePoolArgs a) {
     }
     __syncthreads();
     if (((need >> wave) & 1u) == 0u) continue;  // wave-uniform; the next item's barriers come for every wave
-    float best = -INFINITY;
+    float best = not_a_number();  // (dropped by the first score that is one)
     for (int t = 0; t < nt; ++t) {  // block-uniform
       float tot = 0.f;
 #pragma unroll
@@ -949,6 +958,7 @@ __global__ __launch_bounds__(256) void pool_score_kernel(WidePoolArgs a) {
     }
 #pragma unroll
     for (int off = 8; off < 8 * C; off <<= 1) best = fmaxf(best, __shfl_xor(best, off, 64));  // document max over its chunks
+    if (best != best) best = not_a_number();
     if (lane == 0) atomicMax(&a.keys[(long long)b * a.N + 4 * quad + wave], make_key(best, (uint32_t)doc));
   }
 }

@@ -380,6 +380,40 @@ def test_token_pooling_of_nothing_but_zeros():
     assert bool((idx == -1).all()) and bool((val == float("-inf")).all())
 
 
+@pytest.mark.parametrize("N,k,M", [(40, 40, 64), (9001, 20, 40), (600, 64, 330)])
+def test_token_pooling_of_what_is_not_a_number(N, k, M):
+    """Pooled by document as from a selection per token: a question that holds an infinity in every token lists the first k
+    documents without a score, such tokens beside others change nothing, and neither does a document without a score, which
+    goes on the list only where there are no others."""
+    Hkv, C, d = 8, 8, 128
+    say(f"token pooling of what is not a number N={N} k={k} M={M}")
+    assert pooled_by_document(N, Hkv, 1, M, k)
+    cfg = msa.MsaConfig(N, 8 * C, 8, Hkv, Hkv, d, 1e6, select_scope=msa.MSA_SCOPE_ALL, token_pool=1)
+    keys, KR = device_index(62001, Hkv, N * C, d)
+    inv = torch.ones((Hkv, KR.shape[1] * 16), device="cuda")
+    inv[:, :N * C] = 1.0 / keys.float().norm(dim=-1)
+    q = torch.randn((1, M, Hkv, d), generator=torch.Generator("cuda").manual_seed(2), device="cuda").to(torch.bfloat16)
+    bad = q.clone()
+    bad[:, :, 3, 5] = float("inf")
+    idx, val = msa.msa_score_topk(cfg, bad, KR, inv, k)
+    assert torch.equal(idx.view(-1), torch.arange(k, dtype=torch.int32, device="cuda")) and bool(val.isnan().all())
+    idx, val = msa.msa_score_topk(cfg, q, KR, inv, k)
+    for what in (float("inf"), float("nan")):
+        one = q.clone()
+        one[0, 1:, 3, 5] = what
+        first = msa.msa_score_topk(cfg, one, KR, inv, k)
+        alone = q.clone()
+        alone[0, 1:] = q[0, :1]
+        second = msa.msa_score_topk(cfg, alone, KR, inv, k)
+        assert torch.equal(first[0], second[0]) and torch.equal(first[1], second[1])
+    doc = int(idx[0, 0, 0, 0])                        # the best document
+    inv[:, doc * C:doc * C + C] = float("nan")
+    idx2, val2 = msa.msa_score_topk(cfg, q, KR, inv, k)
+    scored = ~val2.isnan()
+    assert int(scored.sum()) == (k - 1 if k == N else k) and (k < N or int(idx2[~scored]) == doc)
+    assert torch.equal(idx2[scored][:k - 1], idx.view(-1)[1:]) and torch.equal(val2[scored][:k - 1], val.view(-1)[1:])
+
+
 # (N, Hkv, C, d, B, M, k, scope, pool): a row's k best where every document ties
 ALL_TIED = [
     (97656, 8, 8, 128, 8, 1, 32, "group", 0),     # candidate lists of long streams and their merge
