@@ -62,7 +62,6 @@ static int make_dims(const msa_config_t* cfg, Dims* dm, DimsFor use = kForRoutin
   dm->prof_stop = (hipEvent_t)cfg->profile_stop_event;
   dm->NC = (int64_t)dm->N * C;
   dm->tiles = (dm->NC + 15) / 16;
-  dm->cold_index = 0;
   return MSA_OK;
 }
 
@@ -340,7 +339,6 @@ int msa_layers_step(const msa_config_t* cfg, const msa_config_t* attend_cfg, con
   const bool two = route != attend;
   for (int32_t l = 0; two && l < n_layers; ++l)
     if (layers[l].scored_event == nullptr) return MSA_ERR_INVALID_ARG;
-  size_t index_bytes = 0;  // of all layers, an index that several of them share once
   for (int32_t l = 0; l < n_layers; ++l) {  // nothing is enqueued unless every layer is accepted
     const msa_layer_t& y = layers[l];
     Dims dm;
@@ -348,13 +346,9 @@ int msa_layers_step(const msa_config_t* cfg, const msa_config_t* attend_cfg, con
     AttendPlan pa;
     int rc = check_score(cfg, y.q, y.B, y.M, y.KR, y.inv_norm, k, y.idx, y.score, score_workspace, score_workspace_bytes,
                          &dm, &ps);
-    if (rc == MSA_OK) {
-      bool first = true;
-      for (int32_t j = 0; j < l; ++j) first = first && layers[j].KR != y.KR;
-      if (first) index_bytes += (size_t)dm.Hkv * dm.tiles * 16 * dm.d * 2;
+    if (rc == MSA_OK)
       rc = check_attend(attend_cfg, y.q, y.B, y.M, y.K, y.V, y.idx, k, y.Kloc, y.Vloc, y.Lloc, local_pos0, q_pos, y.out,
                         y.lse, attend_workspace, attend_workspace_bytes, &dm, &pa);
-    }
     if (rc != MSA_OK) return rc;
   }
   const hipStream_t sc = (hipStream_t)caller, sr = (hipStream_t)route, sa = (hipStream_t)attend;
@@ -366,13 +360,8 @@ int msa_layers_step(const msa_config_t* cfg, const msa_config_t* attend_cfg, con
   int rc = MSA_OK;
   for (int32_t l = 0; l < n_layers && rc == MSA_OK; ++l) {
     const msa_layer_t& y = layers[l];
-    Dims dm;
-    ScorePlan ps;
-    rc = check_score(cfg, y.q, y.B, y.M, y.KR, y.inv_norm, k, y.idx, y.score, score_workspace, score_workspace_bytes, &dm, &ps);
-    if (rc == MSA_OK) {
-      dm.cold_index = index_bytes > kCacheBytes ? 1 : 0;
-      rc = launch_score(dm, ps, y.q, y.B, y.M, y.KR, y.inv_norm, k, y.idx, y.score, score_workspace, sr);
-    }
+    rc = msa_score_topk(cfg, y.q, y.B, y.M, y.KR, y.inv_norm, k, y.idx, y.score, score_workspace, score_workspace_bytes,
+                        route);
     if (rc == MSA_OK && two && !after((hipEvent_t)y.scored_event, sr, sa)) rc = MSA_ERR_HIP;
     if (rc == MSA_OK)
       rc = msa_sparse_attend(attend_cfg, y.q, y.B, y.M, y.K, y.V, y.idx, k, y.Kloc, y.Vloc, y.Lloc, local_pos0, q_pos,

@@ -19,7 +19,6 @@ struct Dims {
   hipEvent_t prof_start, prof_stop;  // the caller's events around the dominant kernel of this call, or null
   int64_t NC;     // N * C routing keys per KV head
   int64_t tiles;  // ceil(NC / 16) tiles of 16 keys per KV head
-  int cold_index; // 1: a step of several layers reads more index than the caches hold from one scan of an index to its next
 };
 
 // Work split of the MFMA-bound scoring path for many query tokens (msa_score_gemm.hip).
@@ -82,9 +81,8 @@ WidePoolPlan plan_score_wide_pool(const Dims& dm, const WidePlan& pl, int B, int
 int launch_score_wide_pool(const Dims& dm, const WidePoolPlan& pp, const void* q_route, int B, int M, const void* KR,
                            const float* inv_norm, int k, void* ws, hipStream_t st, int32_t* out_idx, float* out_score);
 
-// Streaming loads of the routing index; cold: no call finds it in the caches, or the kernel loses nothing where it is there.
+// Streaming loads of the routing index; cold: of one that the caches do not hold, or do and the kernel loses little.
 bool stream_index_of(const Dims& dm, bool cold);
-constexpr size_t kCacheBytes = (size_t)256 << 20;  // behind the L2s
 
 bool wide_path_applies(const Dims& dm, int BM);
 WidePlan plan_score_wide(const Dims& dm, int BM, int k);

@@ -1170,19 +1170,22 @@ __global__ __launch_bounds__(64 * WAVES) void topk_rows_kernel(RowsArgs a) {
 
 // Streaming loads of the index: always from 300 MB on, of which the 256 MB of cache behind the L2s keep nothing until it is read again
 // (index cold / again and again, whole call, 8 queries: 20000 documents, 328 MB, 73.3 / 69.0 -> 66.0 / 64.8 us, 32768 110 / 106 -> 99 /
-// 95.5; 16600, 272 MB, 63.3 / 54.5 -> 57.6 / 56.6, 18000, 295 MB, 67 / 57.3 -> 60.5 / 59.4; 50 tokens over all heads 16600 98.6 / 85 ->
-// 93.7 / 89.7, 20000 104.8 / 101.5 -> 99.2 / 96.5), and from 128 MB on where a scan finds its index cold: plain loads then spend their
-// time on caching what nobody reads again.
-//   The score-matrix scan gains 5 to 9 % on a cold index and loses 2 to 10 % on one that is read again and again (8 queries, 7400
-//   documents, 121 MB, 31.8 / 27.1 -> 30.0 / 28.7, 9000 39.7 / 33.9 -> 36.8 / 35.4, 13000 51.2 / 43.6 -> 47.0 / 45.6, 15600, 256 MB, 58.4
-//   / 51.0 -> 53.3 / 51.7; 32 queries over 13000 64.9 / 53.8 -> 59.6 / 59.3), so it has them in a step of layers whose indexes
-//   together outgrow the cache (four of 134 MB, 8 queries: 214 -> 194 us with the other changes of the scan; the first step after
-//   the indexes were written 692 -> 675, in its spread) and plain loads in a call of its own.
-//   The all-heads scan loses next to nothing (24 queries, 7900 documents 36.1 / 31.8 -> 33.8 / 31.6, 11000 49.1 / 42.6 -> 44.9 / 42.6,
-//   13000 55.2 / 47.0 -> 50.3 / 48.5, 15600 62.6 / 54.0 -> 56.1 / 54.2; 22000 of 64 dims 51.1 / 42.4 -> 45.8 / 44.4).
-//   It has them there but for more than eight queries of one or two chunks per document, which gained 2 to 7 % cold and lost 4 to 12 %
-//   warm (13 queries over 79101 documents of one chunk, 8 heads of 128 dims, 50.1 / 42.8 -> 47.9 / 44.8; 26 over 52734 of two 67.6 /
-//   56.1 -> 63.1 / 59.6; 957 drawn calls 0.97 / 1.08 times).
+// 95.5; 50 tokens over all heads 16600, 272 MB, 98.6 / 85 -> 93.7 / 89.7, 20000 104.8 / 101.5 -> 99.2 / 96.5), and from 128 MB on in one
+// pass of a scan.  A program reads more than that cache holds between two scans of an index (the selected documents of its
+// streams, the indexes of its other layers, its weights), so the scan finds it cold, and plain loads spend their time on caching
+// what nobody reads again; where the cache holds what was written just before, they wait for that to go to memory.  An index of
+// 128 to 300 MB that is routed over again and again with nothing read in between is what they are better at (cold / behind 640 MB
+// that were written / again and again):
+//   8 queries: 7900 documents, 129 MB, 34.6 / 54.7 / 29.5 -> 32.8 / 36.4 / 29.6 us, 9000 41.8 / 65.3 / 35.6 -> 38.9 / 43.8 / 36.5, 13000
+//   52.5 / 80.8 / 45.0 -> 49.0 / 55.6 / 46.6, 15600, 256 MB, 60.0 / 87.8 / 52.0 -> 55.8 / 62.4 / 53.9; one query the same;
+//   32 queries: 9000 53.6 / 76.4 / 47.3 -> 52.3 / 54.8 / 49.6, 13000 66.6 / 93.4 / 57.3 -> 62.8 / 68.1 / 60.9; from 290 MB on faster in all
+//   three (18000 80.2 / 121.6 / 75.8 -> 73.9 / 83.2 / 72.2);
+//   all heads, 24 queries, cold / again and again: 7900 36.1 / 31.8 -> 33.8 / 31.6, 11000 49.1 / 42.6 -> 44.9 / 42.6, 13000 55.2 / 47.0 ->
+//   50.3 / 48.5, 15600 62.6 / 54.0 -> 56.1 / 54.2; 22000 of 64 dims 51.1 / 42.4 -> 45.8 / 44.4; but more than eight queries of one or two
+//   chunks per document gained 2 to 7 % and lost 4 to 12 % (13 over 79101 documents of one chunk, 8 heads of 128 dims, 50.1 / 42.8 ->
+//   47.9 / 44.8; 26 over 52734 of two 67.6 / 56.1 -> 63.1 / 59.6; 957 drawn calls 0.97 / 1.08 times) and keep plain loads.
+// Four layers of 134 MB in turn, 8 queries: 214 -> 194 us with the other changes of the scan; the first step after the indexes
+// were written 692 -> 675, in its spread.
 // Below 128 MB an index may well be in the cache still when it is read again (5000 documents, 82 MB, 8 queries 24.6 / 21.5 -> 23.7 /
 // 22.6, 6800, 111 MB, 29.9 / 25.8 -> 28.3 / 27.4); so it may for the second pass of a call.
 bool stream_index_of(const Dims& dm, bool cold) {
@@ -1745,8 +1748,8 @@ int launch_score(const Dims& dm, const ScorePlan& pl, const void* q_route, int B
                          dm.r, dm.cos, pl.n_qtiles, a.gmax, n_gmax);
     if (hipGetLastError() != hipSuccess) return MSA_ERR_HIP;
   }
-  const bool cold = dm.cold_index || (pl.all_heads && (dm.C >= 4 || BM <= 8));
-  const bool stream_index = stream_index_of(dm, pl.n_pass == 1 && cold);
+  const bool cold = pl.n_pass == 1 && !(pl.all_heads && dm.C <= 2 && BM > 8);
+  const bool stream_index = stream_index_of(dm, cold);
   RowsArgs ra;
   ra.mat = (const float*)((char*)ws + pl.off_mat);
   ra.BM = BM;

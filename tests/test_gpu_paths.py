@@ -199,8 +199,8 @@ def test_scoring_gemm_of_two_passes(N, Hkv, r, C, d, B, M, k, sim):
     test_prefill_scoring_k_above_16(N, Hkv, r, C, d, B, M, k, sim)
 
 
-# score-matrix scans at the edge between plain and streaming loads of the index (all heads: 128 MB; a scan per group, in one pass and
-# in two: 300 MB), tails of half a tile
+# score-matrix scans at the edge between plain and streaming loads of the index (128 MB; a scan per group in two passes: 300 MB),
+# tails of half a tile
 STREAMED = [(7812, 8, 1, 8, 128, 1, 1, 9, "cos"), (7813, 8, 1, 8, 128, 9, 1, 9, "cos"), (7815, 8, 1, 8, 128, 2, 1, 16, "dot"),
             (7813, 8, 2, 8, 128, 20, 1, 16, "cos"), (31253, 4, 1, 8, 64, 3, 1, 8, "cos"), (18311, 8, 1, 8, 128, 2, 1, 9, "cos"),
             (18310, 8, 1, 8, 128, 33, 1, 9, "dot"), (18311, 8, 1, 8, 128, 33, 1, 9, "dot")]
