@@ -78,7 +78,7 @@ def test_three_routed_layers_against_the_oracle(tier):
 @pytest.mark.parametrize("L,N,B", [(2, 8192, 3), (2, 8193, 3), (3, 7813, 9), (3, 7811, 1), (2, 8195, 17)])
 def test_layers_whose_indexes_outgrow_the_cache(L, N, B):
     """Layers of 128 MB each, together just under and just over 256 MB, below and above 128 MB: selections and scores are bit for
-    bit those of a call of its own, whatever loads the scans of a step use."""
+    bit those of a call of its own, streaming loads or plain."""
     G, P, Hkv, d, k, Lloc = 64, 8, 8, 128, 9, 16
     print(f"{L} routed layers of {N} documents, {B} queries", flush=True)
     cfg = msa.MsaConfig(N, G, P, Hkv, Hkv, d, 1e4)
